@@ -29,6 +29,27 @@ EXPORTED_SYMBOLS = (
 )
 
 
+# Argument types of the entry points a decode round calls (p pointer, i int32, l int64, z size_t, f float): with them
+# ctypes converts plain Python ints, which costs a fraction of building a ctypes object for every argument of every call.
+_KIND = {"p": C.c_void_p, "i": C.c_int32, "l": C.c_int64, "z": C.c_size_t, "f": C.c_float}
+_ARGUMENTS = {
+    "dream_tree_verify_attn": "ppppp" "i" "pp" "l" "ppp" "z" "p",
+    "dream_draft_xattn": "ppppp" "i" "p" "i" "p" "l" "pp" "z" "p",
+    "dream_visual_compress": "ppp" "i" "p" "iiiii" "ppppp" "p" "l" "p" "l" "p" "z" "p",
+    "dream_accept_path": "p" "iiii" "pp" "i" "ppppp" "z" "p",
+    "dream_accept_path_static": "p" "iiii" "pp" "i" "pppp" "p",
+    "dream_kv_commit": "pp" "i" "p" "i" "p" "i" "ppp",
+    "dream_project_rows": "pp" "ii" "p" "i" "pppp",
+    "dream_project_rows_multi": "pp" "iii" "p",
+    "dream_spec_accept": "pp" "iiii" "pppp" "i" "f" "pppp" "z" "p",
+    "dream_attention_entropy": "ppp" "i" "p" "i" "ppp" "z" "p",
+    "dream_tree_expand_level": "p" "iiii" "p" "i" "pppp" "z" "p",
+    "dream_tree_finalize": "ppp" "iii" "ppppp",
+}
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch.cuda.current_device
+
+
 class DreamError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"libdream status {status}: {message}")
@@ -70,6 +91,8 @@ def load() -> C.CDLL:
         lib.dream_set_kv_splits.restype = None
         lib.dream_set_q_tiles.restype = None
         lib.dream_set_tile_waves.restype = None
+        for name, kinds in _ARGUMENTS.items():
+            getattr(lib, name).argtypes = [_KIND[c] for c in kinds]
         _lib = lib
     return _lib
 
@@ -81,12 +104,12 @@ def _dev(t: Optional[torch.Tensor]):
         raise ValueError("device tensor expected")
     if not t.is_contiguous():
         raise ValueError("contiguous tensor expected")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    # torch.cuda.current_stream() would build a Stream object: the raw handle of the same stream costs a tenth of it
+    return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def _check(status: int) -> None:
@@ -113,7 +136,7 @@ def dream_set_tile_waves(waves: int) -> None:
 def dream_stream_read(src: torch.Tensor, nbytes: int, sink: torch.Tensor, offset_bytes: int = 0, stream=None) -> None:
     if offset_bytes < 0 or offset_bytes + nbytes > src.numel() * src.element_size():
         raise ValueError("range outside the source tensor")
-    _check(load().dream_stream_read(C.c_void_p(src.data_ptr() + offset_bytes), C.c_size_t(nbytes), _dev(sink), _stream(stream)))
+    _check(load().dream_stream_read(C.c_void_p(src.data_ptr() + offset_bytes), C.c_size_t(nbytes), C.c_void_p(_dev(sink)), C.c_void_p(_stream(stream))))
 
 
 def dream_attn_variants() -> list:
@@ -153,9 +176,9 @@ def dream_tree_verify_attn_workspace(desc: AttnDesc, n_tree: int, max_kv_len: in
 def dream_tree_verify_attn(desc: AttnDesc, q, k_cache, v_cache, prefix_len, n_tree: int, parent, tree_mask,
                            max_kv_len: int, out, lse, workspace, stream=None) -> None:
     _check(load().dream_tree_verify_attn(C.byref(desc), _dev(q), _dev(k_cache), _dev(v_cache), _dev(prefix_len),
-                                         C.c_int32(n_tree), _dev(parent), _dev(tree_mask), C.c_int64(max_kv_len),
+                                         n_tree, _dev(parent), _dev(tree_mask), max_kv_len,
                                          _dev(out), _dev(lse), _dev(workspace),
-                                         C.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream)))
+                                         workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def dream_draft_xattn_workspace(desc: AttnDesc, n_q: int, max_kv_len: int) -> int:
@@ -165,9 +188,9 @@ def dream_draft_xattn_workspace(desc: AttnDesc, n_q: int, max_kv_len: int) -> in
 def dream_draft_xattn(desc: AttnDesc, q, kx_cache, vx_cache, prefix_len, n_tree: int, parent, n_q: int, q_node,
                       max_kv_len: int, out, workspace, stream=None) -> None:
     _check(load().dream_draft_xattn(C.byref(desc), _dev(q), _dev(kx_cache), _dev(vx_cache), _dev(prefix_len),
-                                    C.c_int32(n_tree), _dev(parent), C.c_int32(n_q), _dev(q_node),
-                                    C.c_int64(max_kv_len), _dev(out), _dev(workspace),
-                                    C.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream)))
+                                    n_tree, _dev(parent), n_q, _dev(q_node),
+                                    max_kv_len, _dev(out), _dev(workspace),
+                                    workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def dream_visual_compress_workspace(desc: AttnDesc, n_q: int, vis_len: int) -> int:
@@ -179,12 +202,12 @@ def dream_visual_compress(desc: AttnDesc, q, q_pos, n_q: int, k_cache, n_keys: i
                           gather_dst, row_elems: int, workspace, stream=None, row_lse_in=None) -> int:
     """Returns k, the kept count the library reports through its host out-parameter."""
     n_kept = C.c_int32(-1)
-    _check(load().dream_visual_compress(C.byref(desc), _dev(q), _dev(q_pos), C.c_int32(n_q), _dev(k_cache),
-                                        C.c_int32(n_keys), C.c_int32(vis_start), C.c_int32(vis_len),
-                                        C.c_int32(keep_num), C.c_int32(keep_den), _dev(scores_in), _dev(row_lse_in), _dev(scores_out),
-                                        _dev(kept_idx), C.byref(n_kept), _dev(gather_src), C.c_int64(n_rows_src),
-                                        _dev(gather_dst), C.c_int64(row_elems), _dev(workspace),
-                                        C.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream)))
+    _check(load().dream_visual_compress(C.byref(desc), _dev(q), _dev(q_pos), n_q, _dev(k_cache),
+                                        n_keys, vis_start, vis_len,
+                                        keep_num, keep_den, _dev(scores_in), _dev(row_lse_in), _dev(scores_out),
+                                        _dev(kept_idx), C.byref(n_kept), _dev(gather_src), n_rows_src,
+                                        _dev(gather_dst), row_elems, _dev(workspace),
+                                        workspace.numel() * workspace.element_size(), _stream(stream)))
     return int(n_kept.value)
 
 
@@ -194,10 +217,10 @@ def dream_accept_path_workspace(batch: int, n_tree: int, vocab: int) -> int:
 
 def dream_accept_path(logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent, max_depth: int,
                       node_argmax, accept_len, accept_path, bonus_token, workspace, stream=None) -> None:
-    _check(load().dream_accept_path(_dev(logits), C.c_int32(logits_dtype), C.c_int32(batch), C.c_int32(n_tree),
-                                    C.c_int32(vocab), _dev(token), _dev(parent), C.c_int32(max_depth),
+    _check(load().dream_accept_path(_dev(logits), logits_dtype, batch, n_tree,
+                                    vocab, _dev(token), _dev(parent), max_depth,
                                     _dev(node_argmax), _dev(accept_len), _dev(accept_path), _dev(bonus_token),
-                                    _dev(workspace), C.c_size_t(workspace.numel() * workspace.element_size()),
+                                    _dev(workspace), workspace.numel() * workspace.element_size(),
                                     _stream(stream)))
 
 
@@ -207,8 +230,8 @@ def dream_accept_static_init() -> None:
 
 def dream_accept_path_static(logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent, max_depth: int,
                              node_argmax, accept_len, accept_path, bonus_token, stream=None) -> None:
-    _check(load().dream_accept_path_static(_dev(logits), C.c_int32(logits_dtype), C.c_int32(batch), C.c_int32(n_tree),
-                                           C.c_int32(vocab), _dev(token), _dev(parent), C.c_int32(max_depth),
+    _check(load().dream_accept_path_static(_dev(logits), logits_dtype, batch, n_tree,
+                                           vocab, _dev(token), _dev(parent), max_depth,
                                            _dev(node_argmax), _dev(accept_len), _dev(accept_path), _dev(bonus_token),
                                            _stream(stream)))
 
@@ -216,14 +239,14 @@ def dream_accept_path_static(logits, logits_dtype: int, batch: int, n_tree: int,
 def dream_kv_commit(desc: AttnDesc, caches: Sequence[torch.Tensor], prefix_len: torch.Tensor, n_tree: int,
                     accept_path: torch.Tensor, accept_len: torch.Tensor, prefix_len_out: Optional[torch.Tensor] = None,
                     stream=None) -> None:
-    ptrs = (C.c_void_p * len(caches))(*[_dev(c).value for c in caches])
-    _check(load().dream_kv_commit(C.byref(desc), ptrs, C.c_int32(len(caches)), _dev(prefix_len), C.c_int32(n_tree),
-                                  _dev(accept_path), C.c_int32(accept_path.shape[-1]), _dev(accept_len),
+    ptrs = (C.c_void_p * len(caches))(*[_dev(c) for c in caches])
+    _check(load().dream_kv_commit(C.byref(desc), ptrs, len(caches), _dev(prefix_len), n_tree,
+                                  _dev(accept_path), accept_path.shape[-1], _dev(accept_len),
                                   _dev(prefix_len_out), _stream(stream)))
 
 
 def dream_project_rows(desc: AttnDesc, x, n_rows: int, hidden: int, w, n_heads: int, row_base, row_index, out, stream=None) -> None:
-    _check(load().dream_project_rows(C.byref(desc), _dev(x), C.c_int32(n_rows), C.c_int32(hidden), _dev(w), C.c_int32(n_heads),
+    _check(load().dream_project_rows(C.byref(desc), _dev(x), n_rows, hidden, _dev(w), n_heads,
                                      _dev(row_base), _dev(row_index), _dev(out), _stream(stream)))
 
 
@@ -236,7 +259,7 @@ def dream_project_rows_multi(desc: AttnDesc, jobs, n_rows: int, hidden: int, str
     """jobs: sequence of (x, w, n_heads, row_base, row_index, out)."""
     arr = (ProjJob * len(jobs))(*[ProjJob(_dev(x), _dev(w), n_heads, _dev(rb), _dev(ri), _dev(out))
                                   for x, w, n_heads, rb, ri, out in jobs])
-    _check(load().dream_project_rows_multi(C.byref(desc), arr, C.c_int32(len(jobs)), C.c_int32(n_rows), C.c_int32(hidden),
+    _check(load().dream_project_rows_multi(C.byref(desc), arr, len(jobs), n_rows, hidden,
                                            _stream(stream)))
 
 
@@ -247,10 +270,10 @@ def dream_spec_accept_workspace(batch: int, n_tree: int, vocab: int) -> int:
 def dream_spec_accept(target_logits, draft_logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent,
                       u_accept, u_bonus, max_depth: int, temperature: float, accept_len, accept_path, bonus_token, workspace,
                       stream=None) -> None:
-    _check(load().dream_spec_accept(_dev(target_logits), _dev(draft_logits), C.c_int32(logits_dtype), C.c_int32(batch),
-                                    C.c_int32(n_tree), C.c_int32(vocab), _dev(token), _dev(parent), _dev(u_accept), _dev(u_bonus),
-                                    C.c_int32(max_depth), C.c_float(temperature), _dev(accept_len), _dev(accept_path),
-                                    _dev(bonus_token), _dev(workspace), C.c_size_t(workspace.numel() * workspace.element_size()),
+    _check(load().dream_spec_accept(_dev(target_logits), _dev(draft_logits), logits_dtype, batch,
+                                    n_tree, vocab, _dev(token), _dev(parent), _dev(u_accept), _dev(u_bonus),
+                                    max_depth, temperature, _dev(accept_len), _dev(accept_path),
+                                    _dev(bonus_token), _dev(workspace), workspace.numel() * workspace.element_size(),
                                     _stream(stream)))
 
 
@@ -259,9 +282,9 @@ def dream_attention_entropy_workspace(desc: AttnDesc, n_q: int) -> int:
 
 
 def dream_attention_entropy(desc: AttnDesc, q, q_pos, n_q: int, k_cache, n_keys: int, row_entropy, ae, workspace, stream=None) -> None:
-    _check(load().dream_attention_entropy(C.byref(desc), _dev(q), _dev(q_pos), C.c_int32(n_q), _dev(k_cache), C.c_int32(n_keys),
+    _check(load().dream_attention_entropy(C.byref(desc), _dev(q), _dev(q_pos), n_q, _dev(k_cache), n_keys,
                                           _dev(row_entropy), _dev(ae), _dev(workspace),
-                                          C.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream)))
+                                          workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def dream_tree_expand_workspace(batch: int, n_frontier: int, vocab: int, k: int) -> int:
@@ -271,18 +294,18 @@ def dream_tree_expand_workspace(batch: int, n_frontier: int, vocab: int, k: int)
 def dream_tree_expand_level(logits: torch.Tensor, logits_dtype: int, batch: int, n_frontier: int, vocab: int,
                             cum_in: torch.Tensor, k: int, cand_token: torch.Tensor, cand_score: torch.Tensor,
                             next_frontier: torch.Tensor, workspace: torch.Tensor, stream=None) -> None:
-    _check(load().dream_tree_expand_level(_dev(logits), C.c_int32(logits_dtype), C.c_int32(batch), C.c_int32(n_frontier),
-                                          C.c_int32(vocab), _dev(cum_in), C.c_int32(k), _dev(cand_token), _dev(cand_score),
+    _check(load().dream_tree_expand_level(_dev(logits), logits_dtype, batch, n_frontier,
+                                          vocab, _dev(cum_in), k, _dev(cand_token), _dev(cand_score),
                                           _dev(next_frontier), _dev(workspace),
-                                          C.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream)))
+                                          workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def dream_tree_finalize(pool_score: torch.Tensor, pool_parent: torch.Tensor, pool_token: torch.Tensor, batch: int, n_pool: int,
                         budget: int, tree_parent: torch.Tensor, tree_token: torch.Tensor, tree_pool_index: torch.Tensor,
                         stream=None) -> int:
     n_tree = C.c_int32(0)
-    _check(load().dream_tree_finalize(_dev(pool_score), _dev(pool_parent), _dev(pool_token), C.c_int32(batch), C.c_int32(n_pool),
-                                      C.c_int32(budget), _dev(tree_parent), _dev(tree_token), _dev(tree_pool_index),
+    _check(load().dream_tree_finalize(_dev(pool_score), _dev(pool_parent), _dev(pool_token), batch, n_pool,
+                                      budget, _dev(tree_parent), _dev(tree_token), _dev(tree_pool_index),
                                       C.byref(n_tree), _stream(stream)))
     return int(n_tree.value)
 
