@@ -25,6 +25,10 @@ void dream_set_q_tiles(int32_t q_tiles);
  * (bf16, head_dim >= 128, unsplit key range), 0 = automatic. */
 void dream_set_tile_waves(int32_t waves);
 
+/* Polls after which a workgroup of dream_spec_accept stops waiting for the others of its sequence (workgroup 0 then
+ * does their share itself, with the same result): 0 = the default, negative = never wait. */
+void dream_set_accept_spin(int32_t polls);
+
 /* Host-only: the names of all bf16 attention kernel variants the launch plan can choose, separated by ';', in the
  * spelling dream_attn_plan_describe uses ("attn_wave_kernel<128,8,2,1>": head_dim, waves, column slices, query tiles
  * per workgroup; "attn_bf16_kernel<128,1,1,2>": head_dim, query tiles per wave, key tiles per step, steps in flight;

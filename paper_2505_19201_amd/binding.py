@@ -21,7 +21,7 @@ EXPORTED_SYMBOLS = (
     "dream_init", "dream_tree_verify_attn_workspace", "dream_tree_verify_attn",
     "dream_draft_xattn_workspace", "dream_draft_xattn", "dream_visual_compress_workspace",
     "dream_visual_compress", "dream_accept_path_workspace", "dream_accept_path",
-    "dream_tree_validate_host", "dream_last_error", "dream_set_kv_splits", "dream_set_q_tiles", "dream_set_tile_waves", "dream_attn_variants",
+    "dream_tree_validate_host", "dream_last_error", "dream_set_kv_splits", "dream_set_q_tiles", "dream_set_tile_waves", "dream_set_accept_spin", "dream_attn_variants",
     "dream_attn_plan_describe", "dream_stream_read", "dream_kv_commit",
     "dream_tree_expand_workspace", "dream_tree_expand_level", "dream_tree_finalize",
     "dream_attention_entropy_workspace", "dream_attention_entropy", "dream_spec_accept_workspace", "dream_spec_accept",
@@ -91,6 +91,7 @@ def load() -> C.CDLL:
         lib.dream_set_kv_splits.restype = None
         lib.dream_set_q_tiles.restype = None
         lib.dream_set_tile_waves.restype = None
+        lib.dream_set_accept_spin.restype = None
         for name, kinds in _ARGUMENTS.items():
             getattr(lib, name).argtypes = [_KIND[c] for c in kinds]
         _lib = lib
@@ -131,6 +132,10 @@ def dream_set_q_tiles(q_tiles: int) -> None:
 
 def dream_set_tile_waves(waves: int) -> None:
     load().dream_set_tile_waves(C.c_int32(waves))
+
+
+def dream_set_accept_spin(polls: int) -> None:
+    load().dream_set_accept_spin(C.c_int32(polls))
 
 
 def dream_stream_read(src: torch.Tensor, nbytes: int, sink: torch.Tensor, offset_bytes: int = 0, stream=None) -> None:

@@ -10,6 +10,7 @@ static thread_local char g_error[512] = "";
 static std::atomic<int> g_kv_splits{0};
 static std::atomic<int> g_q_tiles{0};
 static std::atomic<int> g_tile_waves{0};
+static std::atomic<int> g_accept_spin{0};
 
 char *error_buffer() { return g_error; }
 
@@ -32,6 +33,12 @@ int check_launch(const char *what)
 
 int kv_splits_override() { return g_kv_splits.load(std::memory_order_relaxed); }
 int q_tiles_override() { return g_q_tiles.load(std::memory_order_relaxed); }
+// polls of a wait of dream_spec_accept's workgroups for each other: about a millisecond, where one round takes microseconds
+int accept_spin_limit()
+{
+    const int s = g_accept_spin.load(std::memory_order_relaxed);
+    return s < 0 ? 0 : s == 0 ? 1000 : s;
+}
 int tile_waves_override() { return g_tile_waves.load(std::memory_order_relaxed); }
 
 // Reads n16 16-byte words once, grid-stride, and folds them into one word per thread; the fold is stored only
@@ -60,6 +67,8 @@ void dream_set_kv_splits(int32_t n_splits) { dream::g_kv_splits.store(n_splits <
 void dream_set_q_tiles(int32_t q_tiles) { dream::g_q_tiles.store(q_tiles < 0 ? 0 : q_tiles, std::memory_order_relaxed); }
 
 void dream_set_tile_waves(int32_t waves) { dream::g_tile_waves.store(waves == 4 || waves == 8 ? waves : 0, std::memory_order_relaxed); }
+
+void dream_set_accept_spin(int32_t polls) { dream::g_accept_spin.store(polls, std::memory_order_relaxed); }
 
 int dream_init(void)
 {

@@ -7,30 +7,31 @@
 // token is drawn from the current target distribution by inverting its cumulative sum in token order.  The
 // uniform random numbers are inputs.
 //
-// Three launches.  softmax_stats_kernel (parallel over rows and 8192-logit chunks) leaves (max, sum of
-// exponentials) per chunk for the target row of every node and the draft row of every node with children.
-// residual_stats_kernel (same grid) merges them per node and, for nodes with children, leaves the sum of the
-// first residual max(p - q, 0) per chunk.  spec_walk_kernel, one workgroup of 1024 threads per sequence, then
-// evaluates the test of every node against its parent's untouched distributions in parallel: that is exactly
-// the test the walk performs whenever a node is the first child tried, so the walk descends through first
-// children by table lookup.  After a first rejection the residual is known through its chunk sums: the second
-// child's test is two logit lookups, and a draw needs only the one chunk that holds the drawn point.  Only a
-// second rejection at the same node turns the distributions into arrays (one pass over the two logit rows
-// writes the second residual and the reduced draft: unnormalised floats in the workspace, L2-resident); later
-// siblings are tested against those, one pass per further rejection, and an accepted sibling returns to the
-// table walk.  A draw is per-thread contiguous partial sums, a block scan and one thread's rescan.  Every
-// reduction has a fixed order, so the result is reproducible.  With at most 12 chunks per row (98304 tokens)
-// the second kernel is skipped: the walk merges the statistics itself and sums the first residual of a node only
-// when a first child is rejected there, which is cheaper than a launch for short rows.  Roofline: HBM, one read
-// of the logit rows (a second read of the rows of nodes with children).
+// Two launches.  softmax_stats_kernel (parallel over rows and 8192-logit chunks) leaves (max, sum of exponentials)
+// per chunk for the target and the draft row of every node with children: the only rows a test can need.
+// spec_walk_kernel then evaluates the test of every node against its parent's untouched distributions in parallel:
+// that is exactly the test the walk performs whenever a node is the first child tried, so the walk descends through
+// first children by table lookup.  A rejection needs one number that no table holds, the mass of the new residual
+// over the whole vocabulary.  Every residual is a pointwise function of the two logits of a token and of a few
+// scalars (the masses of the residuals before it), so it is recomputed from the logit rows and never stored; several
+// workgroups share a sequence, each sums its chunks and all exchange one float per chunk.  The masses also give the
+// draw, which then reads one chunk.  Every reduction has a fixed order, so the result is reproducible.
+// Roofline: HBM, one read of the logit rows of nodes with children.
+//
+// Why several workgroups: one CU pulls about 50 GB/s, 20 us and more for one pass over two float32 rows of 131072
+// tokens, and the walk made one or more such passes for every second rejection at a node (three float arrays per sequence in the
+// workspace), after a launch that summed the first residual of every node of the tree, visited or not.  Measured, 4
+// sequences x 60 nodes x 131072 float32 logits: 200-245 us per call with one workgroup per sequence, 67-75 us here (22 us the statistics; a rejection about 4 us).
 #include "common.h"
+#include <algorithm>
 #include <type_traits>
 
 using namespace dream;
 
 namespace {
 
-constexpr int NT = 1024;
+constexpr int NT = 512;           // threads of the walk
+constexpr int NW = NT / 64;
 
 template <bool BF16>
 __device__ __forceinline__ float load_logit(const void *p, int64_t i)
@@ -38,7 +39,7 @@ __device__ __forceinline__ float load_logit(const void *p, int64_t i)
     return BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[i]) : reinterpret_cast<const float *>(p)[i];
 }
 
-// block-wide reductions over 1024 threads (16 waves) in a fixed order; `red` holds 16 floats
+// block-wide reductions over the walk's threads in a fixed order; `red` holds one value per wave
 __device__ __forceinline__ float block_sum(float v, float *red, int tid)
 {
     for (int off = 32; off > 0; off >>= 1)
@@ -49,7 +50,7 @@ __device__ __forceinline__ float block_sum(float v, float *red, int tid)
     __syncthreads();
     float t = 0.0f;
 #pragma unroll
-    for (int w = 0; w < 16; w++)
+    for (int w = 0; w < NW; w++)
         t += red[w];
     return t;
 }
@@ -63,7 +64,7 @@ __device__ __forceinline__ float block_max(float v, float *red, int tid)
     __syncthreads();
     float t = red[0];
 #pragma unroll
-    for (int w = 1; w < 16; w++)
+    for (int w = 1; w < NW; w++)
         t = fmaxf(t, red[w]);
     return t;
 }
@@ -77,7 +78,7 @@ __device__ __forceinline__ int block_min_int(int v, int *red, int tid)
     __syncthreads();
     int t = red[0];
 #pragma unroll
-    for (int w = 1; w < 16; w++)
+    for (int w = 1; w < NW; w++)
         t = min(t, red[w]);
     return t;
 }
@@ -110,31 +111,32 @@ __device__ __forceinline__ void load8(const void *base, int64_t row, int t, int 
     }
 }
 
-// (max, sum of exp(x/temp - max)) of one 8192-logit chunk of one row.  z = 0: target rows; z = 1: draft rows,
-// skipped (max = -inf, sum = 0) for nodes without children.
+// Exchange of the walk's partial sums: slots [B][2][2][MAX_SEG] of (round << 32 | float bits), cleared by
+// softmax_stats_kernel, which the stream orders before the walk.
+constexpr int MAX_SEG = 64;
+constexpr int SLOTS = 2 * 2 * MAX_SEG;
+
+// (max, sum of exp(x/temp - max)) of one 8192-logit chunk of one row.  z = 0: target rows; z = 1: draft rows; nothing
+// for nodes without children (a leaf's target row is summed by the walk if the walk ends there).
 template <bool BF16>
 __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits, const void *dlogits, int n_tree, int vocab,
                                                             int n_chunks, bool vec, const int32_t *parent, float inv_temp,
-                                                            float *stat_m, float *stat_s)
+                                                            float *stat_m, float *stat_s, uint64_t *slots)
 {
     const int chunk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t node_row = blockIdx.y;                      // b * n_tree + node
     const int which = blockIdx.z;
     const int64_t slot = ((int64_t)which * gridDim.y + node_row) * n_chunks + chunk;
     __shared__ float red[4];
-    if (which == 1) {
-        const int b = (int)(node_row / n_tree), node = (int)(node_row - (int64_t)b * n_tree);
-        int kids = 0;
-        for (int i = tid; i < n_tree; i += 256)
-            kids |= parent[(int64_t)b * n_tree + i] == node;
-        if (!__syncthreads_or(kids)) {
-            if (tid == 0) {
-                stat_m[slot] = -INFINITY;
-                stat_s[slot] = 0.0f;
-            }
-            return;
-        }
-    }
+    const int b = (int)(node_row / n_tree), node = (int)(node_row - (int64_t)b * n_tree);
+    if (slots && chunk == 0 && node == 0 && which == 0)
+        for (int i = tid; i < SLOTS; i += 256)
+            slots[(int64_t)b * SLOTS + i] = 0;
+    int kids = 0;
+    for (int i = tid; i < n_tree; i += 256)
+        kids |= parent[(int64_t)b * n_tree + i] == node;
+    if (!__syncthreads_or(kids))
+        return;
     const void *base = which ? dlogits : tlogits;
     const int64_t row = node_row * vocab;
     const int begin = chunk * STAT_CHUNK;
@@ -173,208 +175,339 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
     }
 }
 
-// (max, sum of exponentials relative to it) of the target row and, if asked, the draft row of a node from their
-// chunk statistics.  Every wave does the same: lane c takes chunk c (and c + 64, ... beyond 64 chunks), the
-// maximum and then the rescaled sum are reduced with xor shuffles, which is a fixed order.
-__device__ __forceinline__ void merge_node_stats(const float *stat_m, const float *stat_s, int64_t node_row, int64_t rows_all,
-                                                 int n_chunks, bool with_draft, int lane, float &mt, float &zt, float &md, float &zd)
+// (max, sum of exponentials relative to it) of a row from its chunk statistics.  Every lane of a wave calls this: lane
+// c takes chunk c (and c + 64, ...), the maximum and then the rescaled sum are reduced with xor shuffles, a fixed order.
+__device__ __forceinline__ void merge_row_stats(const float *cm, const float *cs, int n_chunks, int lane, float &m, float &z)
 {
-    const float *tm = stat_m + node_row * n_chunks, *ts = stat_s + node_row * n_chunks;
-    const float *dm = stat_m + (rows_all + node_row) * n_chunks, *dsum = stat_s + (rows_all + node_row) * n_chunks;
-    float m0 = -INFINITY, m1 = -INFINITY;
+    m = -INFINITY;
+    for (int c = lane; c < n_chunks; c += 64)
+        m = fmaxf(m, cm[c]);
+    for (int off = 32; off > 0; off >>= 1)
+        m = fmaxf(m, __shfl_xor(m, off));
+    z = 0.0f;
     for (int c = lane; c < n_chunks; c += 64) {
-        m0 = fmaxf(m0, tm[c]);
-        if (with_draft)
-            m1 = fmaxf(m1, dm[c]);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        m0 = fmaxf(m0, __shfl_xor(m0, off));
-        m1 = fmaxf(m1, __shfl_xor(m1, off));
-    }
-    float z0 = 0.0f, z1 = 0.0f;
-    for (int c = lane; c < n_chunks; c += 64) {
-        const float a = ts[c];
-        if (a > 0.0f)
-            z0 += a * __expf(tm[c] - m0);
-        if (with_draft) {
-            const float d = dsum[c];
-            if (d > 0.0f)
-                z1 += d * __expf(dm[c] - m1);
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        z0 += __shfl_xor(z0, off);
-        z1 += __shfl_xor(z1, off);
-    }
-    mt = m0; zt = z0; md = m1; zd = z1;
-}
-
-// The residual max(p - q, 0) of a node after its first rejected child (p, q: the normalised target and draft
-// distributions; p itself where the caller says the residual is empty).
-__device__ __forceinline__ float residual1(float lt, float ld, float inv_temp, float mt, float md, float ip, float iq)
-{
-    return fmaxf(__expf(lt * inv_temp - mt) * ip - __expf(ld * inv_temp - md) * iq, 0.0f);
-}
-
-// Per node: the merged statistics of its rows (written by the workgroup of chunk 0: the walk reads four
-// numbers per node instead of merging again) and, for a node with children, the sum of the first residual over
-// each 8192-logit chunk: what the walk needs to test a second child, or to draw after a single rejection,
-// without a pass of its own over the vocabulary.
-template <bool BF16>
-__global__ __launch_bounds__(256) void residual_stats_kernel(const void *tlogits, const void *dlogits, int n_tree, int vocab,
-                                                             int n_chunks, bool vec, const int32_t *parent, float inv_temp,
-                                                             const float *stat_m, const float *stat_s, float *res_sum,
-                                                             float4 *node_stats)
-{
-    const int chunk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t node_row = blockIdx.y, rows_all = gridDim.y;
-    const int b = (int)(node_row / n_tree), node = (int)(node_row - (int64_t)b * n_tree);
-    __shared__ float red[4];
-    int kids = 0;
-    for (int i = tid; i < n_tree; i += 256)
-        kids |= parent[(int64_t)b * n_tree + i] == node;
-    const bool has_kids = __syncthreads_or(kids);
-    if (!has_kids && chunk > 0) {
-        if (tid == 0)
-            res_sum[node_row * n_chunks + chunk] = 0.0f;
-        return;
-    }
-    // the logits of this chunk are requested before the statistics they will be scaled with
-    const int64_t row = node_row * vocab;
-    const int begin = chunk * STAT_CHUNK;
-    float tv[STAT_CHUNK / 256], dv[STAT_CHUNK / 256];
-    if (has_kids) {
-#pragma unroll
-        for (int r = 0; r < STAT_CHUNK / 2048; r++) {
-            const int t = begin + (r * 256 + tid) * 8;
-            load8<BF16>(tlogits, row, t, vocab, vec, tv + 8 * r);
-            load8<BF16>(dlogits, row, t, vocab, vec, dv + 8 * r);
-        }
-    }
-    float mt, zt, md, zd;
-    merge_node_stats(stat_m, stat_s, node_row, rows_all, n_chunks, has_kids, lane, mt, zt, md, zd);
-    if (chunk == 0 && tid == 0)
-        node_stats[node_row] = float4{mt, zt, md, zd};
-    if (!has_kids) {
-        if (tid == 0)
-            res_sum[node_row * n_chunks] = 0.0f;
-        return;
-    }
-    const float ip = 1.0f / zt, iq = zd > 0.0f ? 1.0f / zd : 0.0f;
-    float sum = 0.0f;
-#pragma unroll
-    for (int r = 0; r < STAT_CHUNK / 2048; r++) {
-        const int t = begin + (r * 256 + tid) * 8;
-#pragma unroll
-        for (int j = 0; j < 8; j++)
-            if (t + j < vocab)
-                sum += residual1(tv[8 * r + j], dv[8 * r + j], inv_temp, mt, md, ip, iq);
+        const float s = cs[c];
+        if (s > 0.0f)
+            z += s * __expf(cm[c] - m);
     }
     for (int off = 32; off > 0; off >>= 1)
-        sum += __shfl_xor(sum, off);
-    if (lane == 0)
-        red[wave] = sum;
-    __syncthreads();
-    if (tid == 0)
-        res_sum[node_row * n_chunks + chunk] = (red[0] + red[1]) + (red[2] + red[3]);
+        z += __shfl_xor(z, off);
 }
 
-// LAZY (at most LAZY_CHUNKS chunks per row): residual_stats_kernel has not run; the walk merges the chunk
-// statistics of every node itself and sums the first residual over the chunks of a node only when a first child
-// is rejected there: one pass of the workgroup over two short rows is cheaper than a launch.
-constexpr int LAZY_CHUNKS = 12;
+struct WalkArgs {
+    const void *tlogits, *dlogits;
+    int n_tree, vocab, n_chunks;
+    int seg_chunks, n_seg;         // a row is n_seg <= MAX_SEG segments of seg_chunks chunks (one chunk up to 524288 tokens)
+    bool vec;
+    const int32_t *token, *parent;
+    const float *u_accept, *u_bonus;
+    int max_depth;
+    float inv_temp;
+    int spin_limit;
+    const float *stat_m, *stat_s;  // [2][B * n_tree][n_chunks], written for nodes with children
+    uint64_t *slots;
+    int32_t *accept_len, *accept_path, *bonus_token;
+};
 
-template <bool BF16, bool LAZY>
-__global__ __launch_bounds__(NT) void spec_walk_kernel(const void *tlogits, const void *dlogits, int n_tree, int vocab, int n_chunks,
-                                                       bool vec, const int32_t *token, const int32_t *parent, const float *u_accept,
-                                                       const float *u_bonus, int max_depth, float inv_temp, const float *stat_m,
-                                                       const float *stat_s, const float *res_sum, const float4 *node_stats, float *work,
-                                                       int32_t *accept_len, int32_t *accept_path, int32_t *bonus_token)
+// gridDim.x workgroups walk one sequence together.  All of them take every decision (from the same numbers in the same
+// order), so they need no commands from each other: in a round each sums its segments (segment s belongs to workgroup
+// s % gridDim.x), publishes one word (round, sum) per segment and reads the others'.  The number travels in the word
+// itself, so the exchange is relaxed agent-scope loads and stores without fences.  Words of round r + 2 overwrite those
+// of round r: nobody publishes round r + 2 before having seen everybody's round r + 1, which everybody publishes after reading round r.
+// Nothing depends on the workgroups running at the same time: a wait is bounded, workgroup 0 sums missing segments itself
+// (the same arithmetic, so the same bits) and waits for nobody again, any other workgroup that waited in vain ends.
+// Only workgroup 0 writes results.
+template <bool BF16>
+__global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 {
     __shared__ int32_t s_par[DREAM_MAX_TREE_ACCEPT];
     __shared__ int32_t s_tok[DREAM_MAX_TREE_ACCEPT];
-    __shared__ int32_t s_first[DREAM_MAX_TREE_ACCEPT];     // first child of a node, or INT_MAX
-    __shared__ float s_mt[DREAM_MAX_TREE_ACCEPT], s_zt[DREAM_MAX_TREE_ACCEPT];   // target row: max, sum
+    __shared__ int32_t s_first[DREAM_MAX_TREE_ACCEPT];     // first child of a node, or NONE
+    __shared__ float s_mt[DREAM_MAX_TREE_ACCEPT], s_zt[DREAM_MAX_TREE_ACCEPT];   // target row: max, sum (nodes with children)
     __shared__ float s_md[DREAM_MAX_TREE_ACCEPT], s_zd[DREAM_MAX_TREE_ACCEPT];   // draft row
-    __shared__ float s_qx[DREAM_MAX_TREE_ACCEPT];          // unnormalised draft mass of a node's token at its parent
+    __shared__ float s_px[DREAM_MAX_TREE_ACCEPT], s_qx[DREAM_MAX_TREE_ACCEPT];   // a node's token at its parent: target and draft exponential
+    __shared__ float s_u[DREAM_MAX_TREE_ACCEPT];
     __shared__ uint8_t s_ok[DREAM_MAX_TREE_ACCEPT];        // the node passes its test when it is the first child tried
-    __shared__ float s_redf[16];
-    __shared__ int s_redi[16];
-    __shared__ float s_scan[16];
+    // rejections at the current node: P <- max(P * ip - Q * iq, 0) if `take`, then Q[x] <- 0
+    __shared__ float s_ip[DREAM_MAX_TREE_ACCEPT], s_iq[DREAM_MAX_TREE_ACCEPT];
+    __shared__ int32_t s_x[DREAM_MAX_TREE_ACCEPT];
+    __shared__ uint8_t s_take[DREAM_MAX_TREE_ACCEPT];
+    __shared__ float s_part[2][MAX_SEG], s_mass[MAX_SEG];
+    __shared__ float s_redf[NW], s_scan[NW];
+    __shared__ int s_redi[NW];
     constexpr int NONE = 0x7fffffff;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t bt = (int64_t)b * n_tree;
+    const int b = blockIdx.y, wg = blockIdx.x, n_wg = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_tree = a.n_tree, vocab = a.vocab, n_chunks = a.n_chunks, n_seg = a.n_seg;
+    const bool vec = a.vec;
+    const float inv_temp = a.inv_temp;
+    const int64_t bt = (int64_t)b * n_tree, rows_all = (int64_t)gridDim.y * n_tree;
+    const int max_depth = a.max_depth;
+    // Everything a test needs is brought into LDS up front, with as few dependent trips to memory as there are: (parent,
+    // token, random number), then (the two logits of every node's token at its parent; the chunk statistics).
     for (int i = tid; i < n_tree; i += NT) {
-        const int par = parent[bt + i];
-        s_par[i] = par < i ? par : -1;
-        s_tok[i] = min(max(token[bt + i], 0), vocab - 1);   // device metadata is trusted but kept inside the row
+        int par = a.parent[bt + i];
+        const int x = min(max(a.token[bt + i], 0), vocab - 1);   // device metadata is trusted but kept inside the row
+        par = par < i ? par : -1;
+        s_u[i] = a.u_accept[bt + i];
+        s_par[i] = par;
+        s_tok[i] = x;
         s_first[i] = NONE;
-        if (LAZY) {
-            const int64_t rows_all = (int64_t)gridDim.x * n_tree;
-            const float *tm = stat_m + (bt + i) * n_chunks, *ts = stat_s + (bt + i) * n_chunks;
-            const float *dm = stat_m + (rows_all + bt + i) * n_chunks, *dsum = stat_s + (rows_all + bt + i) * n_chunks;
-            // one row at a time: a workgroup of 1024 threads has 128 registers per thread
-            float mt = -INFINITY, md = -INFINITY, zt = 0.0f, zd = 0.0f;
-            {
-                float am[LAZY_CHUNKS], as[LAZY_CHUNKS];
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++) {
-                    am[u] = u < n_chunks ? tm[u] : -INFINITY;
-                    as[u] = u < n_chunks ? ts[u] : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++)
-                    mt = fmaxf(mt, am[u]);
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++)
-                    if (u < n_chunks && as[u] > 0.0f)
-                        zt += as[u] * __expf(am[u] - mt);
-            }
-            {
-                float bm[LAZY_CHUNKS], bs[LAZY_CHUNKS];
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++) {
-                    bm[u] = u < n_chunks ? dm[u] : -INFINITY;
-                    bs[u] = u < n_chunks ? dsum[u] : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++)
-                    md = fmaxf(md, bm[u]);
-#pragma unroll
-                for (int u = 0; u < LAZY_CHUNKS; u++)
-                    if (u < n_chunks && bs[u] > 0.0f)
-                        zd += bs[u] * __expf(bm[u] - md);
-            }
-            s_mt[i] = mt; s_zt[i] = zt; s_md[i] = md; s_zd[i] = zd;
-        } else {
-            const float4 ns = node_stats[bt + i];
-            s_mt[i] = ns.x; s_zt[i] = ns.y; s_md[i] = ns.z; s_zd[i] = ns.w;
+        if (i > 0 && par >= 0) {
+            s_px[i] = load_logit<BF16>(a.tlogits, (bt + par) * vocab + x) * inv_temp;
+            s_qx[i] = load_logit<BF16>(a.dlogits, (bt + par) * vocab + x) * inv_temp;
         }
     }
-    float *P = work + (int64_t)b * 3 * vocab, *Q = P + vocab, *R = Q + vocab;
-    int32_t *path = accept_path + (int64_t)b * (max_depth + 1);
-    if (tid <= max_depth)
-        path[tid] = tid == 0 ? 0 : -1;
+    int32_t *path = a.accept_path + (int64_t)b * (max_depth + 1);
+    if (wg == 0)
+        for (int i = tid; i <= max_depth; i += NT)
+            path[i] = i == 0 ? 0 : -1;
+    __syncthreads();
+    for (int i = tid; i < n_tree; i += NT)
+        if (i > 0 && s_par[i] >= 0)
+            atomicMin(&s_first[s_par[i]], i);
+    __syncthreads();
+    if (n_chunks <= 32) {
+        // a node per pass of a wave: its target row's chunks on lanes 0..31, its draft row's on 32..63; four nodes' loads in flight
+        const int c = lane & 31;
+        for (int i0 = wave * 4; i0 < n_tree; i0 += NW * 4) {
+            float m[4], z[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const bool live = i0 + u < n_tree && c < n_chunks && s_first[min(i0 + u, n_tree - 1)] != NONE;
+                const int64_t at = live ? ((lane < 32 ? 0 : rows_all) + bt + i0 + u) * n_chunks + c : 0;
+                m[u] = live ? a.stat_m[at] : -INFINITY;
+                z[u] = live ? a.stat_s[at] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                float mx = m[u];
+                for (int off = 16; off > 0; off >>= 1)
+                    mx = fmaxf(mx, __shfl_xor(mx, off));
+                float sum = z[u] > 0.0f ? z[u] * __expf(m[u] - mx) : 0.0f;
+                for (int off = 16; off > 0; off >>= 1)
+                    sum += __shfl_xor(sum, off);
+                if (c == 0 && i0 + u < n_tree && s_first[i0 + u] != NONE) {
+                    (lane < 32 ? s_mt : s_md)[i0 + u] = mx;
+                    (lane < 32 ? s_zt : s_zd)[i0 + u] = sum;
+                }
+            }
+        }
+    } else {
+        for (int i = wave; i < n_tree; i += NW) {
+            if (s_first[i] == NONE)
+                continue;
+            float mt, zt, md, zd;
+            merge_row_stats(a.stat_m + (bt + i) * n_chunks, a.stat_s + (bt + i) * n_chunks, n_chunks, lane, mt, zt);
+            merge_row_stats(a.stat_m + (rows_all + bt + i) * n_chunks, a.stat_s + (rows_all + bt + i) * n_chunks, n_chunks, lane, md, zd);
+            if (lane == 0) {
+                s_mt[i] = mt; s_zt[i] = zt; s_md[i] = md; s_zd[i] = zd;
+            }
+        }
+    }
     __syncthreads();
     for (int i = tid; i < n_tree; i += NT) {
         const int p = s_par[i];
         if (i > 0 && p >= 0) {
-            atomicMin(&s_first[p], i);
-            const int x = s_tok[i];
-            const float px = __expf(load_logit<BF16>(tlogits, (bt + p) * vocab + x) * inv_temp - s_mt[p]);
-            const float qx = __expf(load_logit<BF16>(dlogits, (bt + p) * vocab + x) * inv_temp - s_md[p]);
+            const float px = s_px[i] = __expf(s_px[i] - s_mt[p]);
+            const float qx = s_qx[i] = __expf(s_qx[i] - s_md[p]);
             const float ratio = qx > 0.0f ? (px / s_zt[p]) / (qx / s_zd[p]) : (px > 0.0f ? INFINITY : 0.0f);
-            s_qx[i] = qx;
-            s_ok[i] = u_accept[bt + i] < fminf(1.0f, ratio);
+            s_ok[i] = s_u[i] < fminf(1.0f, ratio);
         }
     }
     __syncthreads();
 
-    // Inverse-CDF draw over the values val(t) of tokens [r0, r1) (r0 a multiple of 8), read through
-    // `fetch8(t, v)` (8 tokens from t, zeros past r1): `before` is the mass below r0 and `target` the point to
-    // invert.  Contiguous tokens per thread, block scan, the owning thread rescans.  Without an owner (rounding
-    // left the target at or above the sum) the last token with mass in the range is taken.
-    auto draw = [&](int r0, int r1, float mass_before, float total, auto fetch8) {   // total < 0: the sum of the range itself
+    auto next_sibling = [&](int node) {      // every wave finds it for itself: no barrier
+        for (int i0 = node & ~63; i0 < n_tree; i0 += 64) {
+            const int i = i0 + lane;
+            const uint64_t hit = __ballot(i > node && i < n_tree && s_par[min(i, n_tree - 1)] == s_par[node]);
+            if (hit)
+                return i0 + __builtin_ctzll(hit);
+        }
+        return NONE;
+    };
+
+    int cur = 0, depth = 0, n_rej = 0;
+    int64_t row = 0;                                        // of the current node
+    float mt = 0.0f, md = 0.0f, ip = 0.0f, iq = 0.0f;       // its rows' normalisers: p = exp(t - mt) * ip, q = exp(d - md) * iq
+    // residual target and reduced draft of token t after the first n rejections at the current node
+    auto chain = [&](int n, int t, float &P, float &Q) {
+        for (int j = 0; j < n; j++) {
+            const float r = fmaxf(P * s_ip[j] - Q * s_iq[j], 0.0f);
+            P = s_take[j] ? r : P;
+            Q = t == s_x[j] ? 0.0f : Q;
+        }
+    };
+    auto fetch_residual = [&](int n, int t, float v[8]) {
+        float dv[8];
+        load8<BF16>(a.tlogits, row, t, vocab, vec, v);
+        load8<BF16>(a.dlogits, row, t, vocab, vec, dv);
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            v[j] = __expf(v[j] * inv_temp - mt) * ip;       // (0 past the end: the logits read as -inf there)
+            dv[j] = __expf(dv[j] * inv_temp - md) * iq;
+        }
+        for (int i = 0; i < n; i++) {
+            const float jp = s_ip[i], jq = s_iq[i];
+            const bool take = s_take[i];
+            const int x = s_x[i] - t;
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const float r = fmaxf(v[j] * jp - dv[j] * jq, 0.0f);
+                v[j] = take ? r : v[j];
+                dv[j] = x == j ? 0.0f : dv[j];
+            }
+        }
+    };
+    // A workgroup with one chunk keeps its residual target and reduced draft in registers from round to round: rp, rq hold
+    // them after the first reg_n rejections at the current node (-1: the chunk has not been read yet).
+    constexpr int PER = STAT_CHUNK / NT / 8;     // groups of 8 tokens a thread owns of a chunk
+    float rp[PER][8], rq[PER][8];
+    int reg_n = -1;
+    const bool keeps = n_seg <= n_wg && a.seg_chunks == 1;
+    // A segment's share of a round: the mass of the residual after n rejections (n > 0), or (max, sum of exponentials)
+    // of the target row (n == 0).
+    auto segment = [&](int seg, int n, float &v0, float &v1) {
+        v0 = n ? 0.0f : -INFINITY;
+        v1 = 0.0f;
+        if (n && keeps && seg == wg) {
+            if (reg_n < 0) {
+#pragma unroll
+                for (int h = 0; h < PER; h++) {
+                    load8<BF16>(a.tlogits, row, seg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rp[h]);
+                    load8<BF16>(a.dlogits, row, seg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rq[h]);
+                }
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+#pragma unroll
+                    for (int j = 0; j < 8; j++) {
+                        rp[h][j] = __expf(rp[h][j] * inv_temp - mt) * ip;
+                        rq[h][j] = __expf(rq[h][j] * inv_temp - md) * iq;
+                    }
+                reg_n = 0;
+            }
+            for (; reg_n < n - 1; reg_n++) {     // steps whose outcome is known
+                const float jp = s_ip[reg_n], jq = s_iq[reg_n];
+                const bool take = s_take[reg_n];
+                const int x = s_x[reg_n] - seg * STAT_CHUNK - tid * 8;
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+#pragma unroll
+                    for (int j = 0; j < 8; j++) {
+                        const float r = fmaxf(rp[h][j] * jp - rq[h][j] * jq, 0.0f);
+                        rp[h][j] = take ? r : rp[h][j];
+                        rq[h][j] = x == h * NT * 8 + j ? 0.0f : rq[h][j];
+                    }
+            }
+            const float jp = s_ip[n - 1], jq = s_iq[n - 1];   // the last one is only summed: whether it is taken depends on the sum
+            float s = 0.0f;
+#pragma unroll
+            for (int h = 0; h < PER; h++)
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    s += fmaxf(rp[h][j] * jp - rq[h][j] * jq, 0.0f);
+            v0 = block_sum(s, s_redf, tid);
+            return;
+        }
+        for (int c = seg * a.seg_chunks; c < min((seg + 1) * a.seg_chunks, n_chunks); c++) {
+            float v[PER][8];
+            const int t = c * STAT_CHUNK + tid * 8;
+            float m = -INFINITY, s = 0.0f;
+            if (n) {
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+                    fetch_residual(n, t + h * NT * 8, v[h]);
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        s += v[h][j];
+                v0 += block_sum(s, s_redf, tid);
+            } else {
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+                    load8<BF16>(a.tlogits, row, t + h * NT * 8, vocab, vec, v[h]);
+#pragma unroll
+                for (int h = 0; h < PER; h++)
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        m = fmaxf(m, v[h][j] *= inv_temp);
+                m = fmaxf(block_max(m, s_redf, tid), v0);
+                if (m > -INFINITY) {
+#pragma unroll
+                    for (int h = 0; h < PER; h++)
+#pragma unroll
+                        for (int j = 0; j < 8; j++)
+                            s += __expf(v[h][j] - m);
+                    s = block_sum(s, s_redf, tid);
+                    v1 = v1 * __expf(v0 - m) + s;
+                    v0 = m;
+                }
+            }
+        }
+    };
+    auto sum_segments = [&](const float *v) {     // every lane of every wave: the same tree over the segments
+        float t = lane < n_seg ? v[lane] : 0.0f;
+        for (int off = 32; off > 0; off >>= 1)
+            t += __shfl_xor(t, off);
+        return t;
+    };
+    int round = 0;
+    bool alone = n_wg == 1;
+    // One round: fills s_part for all segments.  False: this workgroup waited in vain and ends.
+    auto exchange = [&](int n) {
+        round++;
+        uint64_t *slot = a.slots + (int64_t)b * SLOTS + (round & 1) * 2 * MAX_SEG;
+        for (int seg = alone ? 0 : wg; seg < n_seg; seg += alone ? 1 : n_wg) {
+            float v0, v1;
+            segment(seg, n, v0, v1);
+            if (tid < (n ? 1 : 2)) {
+                const float v = tid ? v1 : v0;
+                s_part[tid][seg] = v;
+                if (!alone)
+                    __hip_atomic_store(slot + tid * MAX_SEG + seg, ((uint64_t)(uint32_t)round << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (!alone) {
+            bool missing = false;
+            const int val = tid / MAX_SEG, seg = tid % MAX_SEG;
+            if (val < (n ? 1 : 2) && seg < n_seg && seg % n_wg != wg) {
+                uint64_t w = 0;
+                missing = true;
+                for (int spin = 0; spin < a.spin_limit && missing; spin++) {
+                    w = __hip_atomic_load(slot + val * MAX_SEG + seg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    missing = (uint32_t)(w >> 32) != (uint32_t)round;
+                    if (missing)
+                        __builtin_amdgcn_s_sleep(2);
+                }
+                if (!missing)
+                    s_part[val][seg] = __uint_as_float((uint32_t)w);
+            }
+            if (__syncthreads_or(missing)) {
+                if (wg != 0)
+                    return false;
+                alone = true;
+                for (int sg = 0; sg < n_seg; sg++) {
+                    if (sg % n_wg == wg)
+                        continue;
+                    float v0, v1;
+                    segment(sg, n, v0, v1);
+                    if (tid == 0) {
+                        s_part[0][sg] = v0;
+                        s_part[1][sg] = v1;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        return true;
+    };
+
+    // Inverse-CDF draw over the values of tokens [r0, r1) (r0 a multiple of 8), read through `fetch8(t, v)` (8 tokens
+    // from t, zeros past the vocabulary): `mass_before` is the mass below r0, `target` the point to invert.  Contiguous
+    // tokens per thread, block scan, the owning thread rescans.  Without an owner (rounding left the target at or above
+    // the sum) the last token with mass in the range is taken.
+    auto draw = [&](int r0, int r1, float mass_before, float target, auto fetch8) {
         const int cpt = (((r1 - r0) + NT - 1) / NT + 7) & ~7;
         const int t0 = min(r0 + tid * cpt, r1), t1 = min(t0 + cpt, r1);
         float local = 0.0f;
@@ -395,14 +528,11 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(const void *tlogits, cons
         if (lane == 63)
             s_scan[wave] = inc;
         __syncthreads();
-        float base = mass_before, scanned = 0.0f;
+        float base = mass_before;
 #pragma unroll
-        for (int w = 0; w < 16; w++) {
+        for (int w = 0; w < NW; w++)
             if (w < wave)
                 base += s_scan[w];
-            scanned += s_scan[w];
-        }
-        const float target = u_bonus[b] * (total < 0.0f ? scanned : total);
         const float before = base + inc - local;        // mass of all tokens below t0
         int owner = (before + local > target && t1 > t0) ? tid : NONE;
         owner = block_min_int(owner, s_redi, tid);
@@ -418,7 +548,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(const void *tlogits, cons
             }
             last = -block_min_int(-last, s_redi, tid);
             if (tid == 0)
-                bonus_token[b] = last >= 0 ? last : min(r0, vocab - 1);
+                a.bonus_token[b] = last >= 0 ? last : min(r0, vocab - 1);
         } else if (tid == owner) {
             float run = before;
             int pick = t1 - 1;
@@ -435,34 +565,20 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(const void *tlogits, cons
                     }
                 }
             }
-            bonus_token[b] = pick;
+            a.bonus_token[b] = pick;
         }
     };
-    // The same draw when the mass of every 8192-token chunk is known (`chunk_mass(c)`): the chunk that holds the
-    // target is found from those sums, in chunk order, and only that chunk is read.  The sums are staged in LDS
-    // (one thread per chunk); beyond MAX_CHUNKS chunks the whole range is scanned instead.
-    constexpr int MAX_CHUNKS = 64;
-    __shared__ float s_cm[MAX_CHUNKS];
-    auto draw_by_chunks = [&](auto chunk_mass, auto fetch8) {
-        __syncthreads();
-        if (tid < min(n_chunks, MAX_CHUNKS))
-            s_cm[tid] = chunk_mass(tid);
-        __syncthreads();
-        if (n_chunks > MAX_CHUNKS) {
-            float total = 0.0f;
-            for (int c = 0; c < n_chunks; c++)
-                total += chunk_mass(c);
-            draw(0, vocab, 0.0f, total, fetch8);
-            return;
-        }
+    // The draw when s_mass holds the mass of every segment: the segment with the drawn point is found from those sums,
+    // in order, and only that one is read.
+    auto draw_by_segments = [&](auto fetch8) {
         float total = 0.0f;
-        for (int c = 0; c < n_chunks; c++)
-            total += s_cm[c];
-        const float target = u_bonus[b] * total;
+        for (int c = 0; c < n_seg; c++)
+            total += s_mass[c];
+        const float target = a.u_bonus[b] * total;
         int pick = -1, last_mass = 0;
         float before = 0.0f, before_last = 0.0f, run = 0.0f;
-        for (int c = 0; c < n_chunks; c++) {
-            const float mc = s_cm[c];
+        for (int c = 0; c < n_seg; c++) {
+            const float mc = s_mass[c];
             if (mc > 0.0f) {
                 last_mass = c;
                 before_last = run;
@@ -473,248 +589,117 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(const void *tlogits, cons
             }
             run += mc;
         }
-        if (pick < 0) {           // rounding left the target at or above the total: the last chunk with mass
+        if (pick < 0) {           // rounding left the target at or above the total: the last segment with mass
             pick = last_mass;
             before = before_last;
         }
-        draw(pick * STAT_CHUNK, min((pick + 1) * STAT_CHUNK, vocab), before, total, fetch8);
+        const int64_t seg_tokens = (int64_t)a.seg_chunks * STAT_CHUNK;
+        draw((int)(pick * seg_tokens), (int)min((pick + 1) * seg_tokens, (int64_t)vocab), before, target, fetch8);
     };
 
-    int cur = 0, depth = 0;
     for (;;) {
         // ---- descend through first children whose (precomputed) test passes
         int first = depth < max_depth ? s_first[cur] : NONE;
         while (first != NONE && s_ok[first]) {
             cur = first;
             depth++;
-            if (tid == 0)
+            if (wg == 0 && tid == 0)
                 path[depth] = cur;
             first = depth < max_depth ? s_first[cur] : NONE;
         }
-        const int64_t row = (bt + cur) * vocab;
-        const float mt = s_mt[cur], md = s_md[cur];
-        if (first == NONE) {
-            // ---- no child to try: draw from the node's own target distribution, straight from the logits
-            const float *cm = stat_m + (bt + cur) * n_chunks, *cs = stat_s + (bt + cur) * n_chunks;
-            draw_by_chunks([&](int c) { const float sc = cs[c]; return sc > 0.0f ? sc * __expf(cm[c] - mt) : 0.0f; },
-                           [&](int t, float v[8]) {
-                               load8<BF16>(tlogits, row, t, vocab, vec, v);
-#pragma unroll
-                               for (int j = 0; j < 8; j++)
-                                   v[j] = t + j < vocab ? __expf(v[j] * inv_temp - mt) : 0.0f;
-                           });
-            break;
+        row = (bt + cur) * vocab;
+        n_rej = 0;
+        reg_n = -1;
+        const bool inner = s_first[cur] != NONE;            // (a node at the depth limit may have children)
+        if (inner) {
+            mt = s_mt[cur];
+            md = s_md[cur];
+            ip = 1.0f / s_zt[cur];
+            iq = s_zd[cur] > 0.0f ? 1.0f / s_zd[cur] : 0.0f;
+        } else {
+            if (!exchange(0))
+                return;
+            mt = -INFINITY;
+            for (int s = 0; s < n_seg; s++)
+                mt = fmaxf(mt, s_part[0][s]);
+            ip = 1.0f;
+            if (tid < n_seg)
+                s_mass[tid] = s_part[1][tid] > 0.0f ? s_part[1][tid] * __expf(s_part[0][tid] - mt) : 0.0f;
         }
-        // ---- the first child was rejected.  The residual target max(p - q, 0) is known through its chunk sums;
-        // the draft loses the rejected token.
-        const float ip = 1.0f / s_zt[cur], iq = s_zd[cur] > 0.0f ? 1.0f / s_zd[cur] : 0.0f;
-        __shared__ float s_res[LAZY_CHUNKS];
-        __shared__ float s_wres[NT / 64][LAZY_CHUNKS];
-        if (LAZY) {
-            // chunk sums of the first residual of this node: iteration k of the workgroup covers chunk k exactly
-            for (int k = 0; k < n_chunks; k++) {
-                float tv[8], dv[8], part = 0.0f;
-                const int t = k * STAT_CHUNK + tid * 8;
-                load8<BF16>(tlogits, row, t, vocab, vec, tv);
-                load8<BF16>(dlogits, row, t, vocab, vec, dv);
-#pragma unroll
-                for (int j = 0; j < 8; j++)
-                    if (t + j < vocab)
-                        part += residual1(tv[j], dv[j], inv_temp, mt, md, ip, iq);
-                for (int off = 32; off > 0; off >>= 1)
-                    part += __shfl_xor(part, off);
-                if (lane == 0)
-                    s_wres[wave][k] = part;
+        bool have_mass = !inner;
+        int child = first, accepted = -1;
+        float Zp = 1.0f, Zq = 1.0f;                          // masses of the current P and Q
+        while (child != NONE) {
+            // ---- `child` was rejected: the target becomes the positive part of (target - draft), its token leaves the draft
+            const int x = s_tok[child];
+            if (tid == 0) {
+                s_ip[n_rej] = 1.0f / Zp;
+                s_iq[n_rej] = Zq > 0.0f ? 1.0f / Zq : 0.0f;
+                s_x[n_rej] = x;
+                s_take[n_rej] = 1;
             }
             __syncthreads();
-            if (tid < n_chunks) {
-                float t = 0.0f;
-#pragma unroll
-                for (int w = 0; w < NT / 64; w++)
-                    t += s_wres[w][tid];
-                s_res[tid] = t;
+            float qx = s_qx[child] * iq;
+            for (int j = 0; j < n_rej; j++)
+                qx = s_x[j] == x ? 0.0f : qx;
+            if (!exchange(n_rej + 1))
+                return;
+            const float Z = sum_segments(s_part[0]);
+            if (Z > 0.0f) {
+                Zp = Z;
+                have_mass = true;
+                if (tid < n_seg)
+                    s_mass[tid] = s_part[0][tid];
+            } else if (tid == 0) {
+                s_take[n_rej] = 0;                           // target == draft: the residual is empty and the target stays as it is
             }
+            Zq = fmaxf(Zq - qx, 0.0f);
+            n_rej++;
             __syncthreads();
-        }
-        const float *rs = LAZY ? s_res : res_sum + (bt + cur) * n_chunks;
-        float Z1 = 0.0f;
-        for (int c0 = 0; c0 < n_chunks; c0 += 16) {   // chunk order, 16 loads in flight
-            float a[16];
-#pragma unroll
-            for (int u = 0; u < 16; u++)
-                a[u] = rs[min(c0 + u, n_chunks - 1)];
-#pragma unroll
-            for (int u = 0; u < 16; u++)
-                if (c0 + u < n_chunks)
-                    Z1 += a[u];
-        }
-        const bool empty1 = !(Z1 > 0.0f);   // target == draft: the residual is empty and the target stays as it is
-        const int x1 = s_tok[first];
-        const float W1 = fmaxf(1.0f - s_qx[first] * iq, 0.0f);
-        // first residual of token t, and the draft after the first rejection (both normalised by Z1 resp. W1 later)
-        auto r1_of = [&](float lt, float ld) { return empty1 ? __expf(lt * inv_temp - mt) * ip : residual1(lt, ld, inv_temp, mt, md, ip, iq); };
-        const float Zr1 = empty1 ? 1.0f : Z1;
-
-        int child = NONE;
-        for (int i = tid; i < n_tree; i += NT)
-            if (i > first && s_par[i] == cur)
-                child = min(child, i);
-        child = block_min_int(child, s_redi, tid);
-        if (child == NONE) {
-            // ---- the only child was rejected: draw from the first residual, one chunk read
-            if (empty1) {
-                const float *cm = stat_m + (bt + cur) * n_chunks, *cs = stat_s + (bt + cur) * n_chunks;
-                draw_by_chunks([&](int c) { const float sc = cs[c]; return sc > 0.0f ? sc * __expf(cm[c] - mt) : 0.0f; },
-                               [&](int t, float v[8]) {
-                                   load8<BF16>(tlogits, row, t, vocab, vec, v);
-#pragma unroll
-                                   for (int j = 0; j < 8; j++)
-                                       v[j] = t + j < vocab ? __expf(v[j] * inv_temp - mt) : 0.0f;
-                               });
-            } else {
-                draw_by_chunks([&](int c) { return rs[c]; },
-                               [&](int t, float v[8]) {
-                                   float dv[8];
-                                   load8<BF16>(tlogits, row, t, vocab, vec, v);
-                                   load8<BF16>(dlogits, row, t, vocab, vec, dv);
-#pragma unroll
-                                   for (int j = 0; j < 8; j++)
-                                       v[j] = t + j < vocab ? residual1(v[j], dv[j], inv_temp, mt, md, ip, iq) : 0.0f;
-                               });
-            }
-            break;
-        }
-        // ---- second child: tested against the first residual and the reduced draft, two logit lookups
-        int accepted = -1;
-        {
+            child = next_sibling(child);
+            if (child == NONE)
+                break;
             const int x2 = s_tok[child];
-            const float lt = load_logit<BF16>(tlogits, row + x2), ld = load_logit<BF16>(dlogits, row + x2);
-            const float px = r1_of(lt, ld);
-            const float qx = x2 == x1 ? 0.0f : __expf(ld * inv_temp - md) * iq;
-            const float ratio = qx > 0.0f ? (px / Zr1) / (qx / W1) : (px > 0.0f ? INFINITY : 0.0f);
-            if (u_accept[bt + child] < fminf(1.0f, ratio))
+            float P = s_px[child] * ip, Q = s_qx[child] * iq;
+            chain(n_rej, x2, P, Q);
+            const float ratio = Q > 0.0f ? (P / Zp) / (Q / Zq) : (P > 0.0f ? INFINITY : 0.0f);
+            if (s_u[child] < fminf(1.0f, ratio)) {
                 accepted = child;
-        }
-        if (accepted < 0) {
-            // ---- second rejection: from here the distributions live as arrays.  One pass writes the second
-            // residual R2 = max(r1/Z1 - q1/W1, 0) and the reduced draft q1 (normalised probabilities).
-            const float iz1 = 1.0f / Zr1, iw1 = W1 > 0.0f ? 1.0f / W1 : 0.0f;
-            float s = 0.0f;
-            for (int t = tid * 8; t < vocab; t += NT * 8) {
-                float tv[8], dv[8], r[8];
-                load8<BF16>(tlogits, row, t, vocab, vec, tv);
-                load8<BF16>(dlogits, row, t, vocab, vec, dv);
-#pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    const float r1 = r1_of(tv[j], dv[j]);
-                    dv[j] = t + j == x1 ? 0.0f : __expf(dv[j] * inv_temp - md) * iq;
-                    tv[j] = r1;
-                    r[j] = t + j < vocab ? fmaxf(r1 * iz1 - dv[j] * iw1, 0.0f) : 0.0f;
-                    s += r[j];
-                }
-                if (vec) {
-                    *reinterpret_cast<float4 *>(R + t) = float4{r[0], r[1], r[2], r[3]};
-                    *reinterpret_cast<float4 *>(R + t + 4) = float4{r[4], r[5], r[6], r[7]};
-                    *reinterpret_cast<float4 *>(Q + t) = float4{dv[0], dv[1], dv[2], dv[3]};
-                    *reinterpret_cast<float4 *>(Q + t + 4) = float4{dv[4], dv[5], dv[6], dv[7]};
-                    *reinterpret_cast<float4 *>(P + t) = float4{tv[0], tv[1], tv[2], tv[3]};
-                    *reinterpret_cast<float4 *>(P + t + 4) = float4{tv[4], tv[5], tv[6], tv[7]};
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; j++)
-                        if (t + j < vocab) {
-                            R[t + j] = r[j];
-                            Q[t + j] = dv[j];
-                            P[t + j] = tv[j];
-                        }
-                }
-            }
-            s = block_sum(s, s_redf, tid);
-            float Zp = Zr1, Zq = W1;       // P holds r1 (sum Z1), Q the reduced draft (sum W1)
-            if (s > 0.0f) {                // otherwise the second residual is empty and the target stays r1
-                float *tmp = P;
-                P = R;
-                R = tmp;
-                Zp = s;
-            }
-            __syncthreads();               // the arrays are complete before anybody reads or clears an entry
-            {
-                const int x2 = s_tok[child];
-                const float q2 = Q[x2];
-                __syncthreads();
-                if (tid == 0)
-                    Q[x2] = 0.0f;
-                Zq = fmaxf(Zq - q2, 0.0f);
-            }
-            // ---- later siblings, one pass per further rejection
-            for (;;) {
-                int next = NONE;
-                for (int i = tid; i < n_tree; i += NT)
-                    if (i > child && s_par[i] == cur)
-                        next = min(next, i);
-                child = block_min_int(next, s_redi, tid);   // (its barriers also publish the cleared entry and the new P)
-                if (child == NONE)
-                    break;
-                const int x = s_tok[child];
-                const float px = P[x], qx = Q[x];
-                const float ratio = qx > 0.0f ? (px / Zp) / (qx / Zq) : (px > 0.0f ? INFINITY : 0.0f);
-                if (u_accept[bt + child] < fminf(1.0f, ratio)) {
-                    accepted = child;
-                    break;
-                }
-                const float ip2 = 1.0f / Zp, iq2 = Zq > 0.0f ? 1.0f / Zq : 0.0f;
-                float s2 = 0.0f;
-                if (vec) {
-                    for (int t = tid * 4; t < vocab; t += NT * 4) {
-                        const float4 pv = *reinterpret_cast<const float4 *>(P + t), qv = *reinterpret_cast<const float4 *>(Q + t);
-                        const float4 r = {fmaxf(pv.x * ip2 - qv.x * iq2, 0.0f), fmaxf(pv.y * ip2 - qv.y * iq2, 0.0f),
-                                          fmaxf(pv.z * ip2 - qv.z * iq2, 0.0f), fmaxf(pv.w * ip2 - qv.w * iq2, 0.0f)};
-                        *reinterpret_cast<float4 *>(R + t) = r;
-                        s2 += (r.x + r.y) + (r.z + r.w);
-                    }
-                } else {
-                    for (int t = tid; t < vocab; t += NT) {
-                        const float r = fmaxf(P[t] * ip2 - Q[t] * iq2, 0.0f);
-                        R[t] = r;
-                        s2 += r;
-                    }
-                }
-                s2 = block_sum(s2, s_redf, tid);
-                if (s2 > 0.0f) {
-                    float *tmp = P;
-                    P = R;
-                    R = tmp;
-                    Zp = s2;
-                }
-                __syncthreads();   // everybody has read Q[x] before it is cleared
-                if (tid == 0)
-                    Q[x] = 0.0f;
-                Zq = fmaxf(Zq - qx, 0.0f);
-            }
-            if (accepted < 0) {
-                // ---- every child rejected: draw from the residual array
-                const float *Pc = P;
-                draw(0, vocab, 0.0f, -1.0f, [&](int t, float v[8]) {
-                    if (vec && t + 8 <= vocab) {
-                        const float4 a = *reinterpret_cast<const float4 *>(Pc + t), c4 = *reinterpret_cast<const float4 *>(Pc + t + 4);
-                        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c4.x; v[5] = c4.y; v[6] = c4.z; v[7] = c4.w;
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 8; j++)
-                            v[j] = t + j < vocab ? Pc[t + j] : 0.0f;
-                    }
-                });
                 break;
             }
         }
+        if (accepted < 0) {
+            // ---- no child, or every child rejected: draw from the current target
+            if (wg != 0)
+                return;
+            if (!have_mass && tid < n_seg) {                 // the untouched target
+                float s = 0.0f;
+                for (int c = tid * a.seg_chunks; c < min((tid + 1) * a.seg_chunks, n_chunks); c++) {
+                    const float sc = a.stat_s[(bt + cur) * n_chunks + c];
+                    s += sc > 0.0f ? sc * __expf(a.stat_m[(bt + cur) * n_chunks + c] - mt) : 0.0f;
+                }
+                s_mass[tid] = s * ip;
+            }
+            __syncthreads();
+            if (n_rej)
+                draw_by_segments([&](int t, float v[8]) { fetch_residual(n_rej, t, v); });
+            else
+                draw_by_segments([&](int t, float v[8]) {
+                    load8<BF16>(a.tlogits, row, t, vocab, vec, v);
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        v[j] = __expf(v[j] * inv_temp - mt) * ip;
+                });
+            break;
+        }
         cur = accepted;
         depth++;
-        if (tid == 0)
+        if (wg == 0 && tid == 0)
             path[depth] = cur;
-        __syncthreads();   // the arrays may be rewritten at a deeper node: finish reading them first
+        __syncthreads();   // the lists of this node are rewritten at a deeper one: finish reading them first
     }
-    if (tid == 0)
-        accept_len[b] = depth;
+    if (wg == 0 && tid == 0)
+        a.accept_len[b] = depth;
 }
 
 }  // namespace
@@ -739,8 +724,8 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
         return fail(DREAM_ERR_INVALID_ARG, "%s: NULL argument", who);
     if (logits_dtype != DREAM_F32 && logits_dtype != DREAM_BF16)
         return fail(DREAM_ERR_INVALID_ARG, "%s: unknown logits dtype %d", who, logits_dtype);
-    if (batch < 1 || batch > 65535 || vocab < 1 || max_depth < 0 || max_depth >= NT)
-        return fail(DREAM_ERR_INVALID_ARG, "%s: batch in [1, 65535], vocab positive and 0 <= max_depth < %d required", who, NT);
+    if (batch < 1 || batch > 65535 || vocab < 1 || max_depth < 0 || max_depth >= DREAM_MAX_TREE_ACCEPT)
+        return fail(DREAM_ERR_INVALID_ARG, "%s: batch in [1, 65535], vocab positive and 0 <= max_depth < %d required", who, DREAM_MAX_TREE_ACCEPT);
     if (n_tree < 1 || n_tree > DREAM_MAX_TREE_ACCEPT)
         return fail(DREAM_ERR_UNSUPPORTED, "%s: n_tree %d outside [1, %d]", who, n_tree, DREAM_MAX_TREE_ACCEPT);
     if ((int64_t)batch * n_tree > 65535)
@@ -752,12 +737,15 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
         return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
     const int n_chunks = ceil_div(vocab, STAT_CHUNK);
     const size_t stats = align_up((size_t)2 * batch * n_tree * n_chunks * sizeof(float), 256);
+    // Workgroups per sequence: one per segment while all of them together stay within one per CU.
+    const int seg_chunks = ceil_div(n_chunks, MAX_SEG), n_seg = ceil_div(n_chunks, seg_chunks);
+    const int n_wg = std::max(1, std::min(n_seg, 256 / batch));
+    // the slots exist with more than one segment only, so they fit where a row of floats per sequence does
     char *wsb = static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES;
-    float *work = reinterpret_cast<float *>(wsb);
+    uint64_t *slots = n_wg > 1 ? reinterpret_cast<uint64_t *>(wsb) : nullptr;
+    static_assert(SLOTS * sizeof(uint64_t) <= 3 * sizeof(float) * STAT_CHUNK, "the slots of a sequence fit its part of the workspace");
     float *stat_m = reinterpret_cast<float *>(wsb + align_up((size_t)batch * 3 * vocab * sizeof(float), 256));
     float *stat_s = reinterpret_cast<float *>(reinterpret_cast<char *>(stat_m) + stats);
-    float *res_sum = reinterpret_cast<float *>(reinterpret_cast<char *>(stat_s) + stats);   // [B * n_tree, n_chunks]
-    float4 *node_stats = reinterpret_cast<float4 *>(reinterpret_cast<char *>(res_sum) + stats);   // [B * n_tree]
     const int esz = logits_dtype == DREAM_BF16 ? 2 : 4;
     const bool vec = vocab % 8 == 0 &&
                      ((reinterpret_cast<uintptr_t>(target_logits) | reinterpret_cast<uintptr_t>(draft_logits) |
@@ -765,22 +753,13 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
     const float inv_temp = 1.0f / temperature;
     hipStream_t st = as_stream(stream);
     const dim3 sgrid(n_chunks, batch * n_tree, 2);
-    const bool lazy = n_chunks <= LAZY_CHUNKS;
+    const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, token, parent, u_accept, u_bonus, max_depth,
+                         inv_temp, accept_spin_limit(), stat_m, stat_s, slots, accept_len, accept_path, bonus_token};
     auto launch_all = [&](auto bf16) {
         constexpr bool BF = decltype(bf16)::value;
         hipLaunchKernelGGL(softmax_stats_kernel<BF>, sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, vocab, n_chunks, vec,
-                           parent, inv_temp, stat_m, stat_s);
-        if (lazy) {
-            hipLaunchKernelGGL((spec_walk_kernel<BF, true>), dim3(batch), dim3(NT), 0, st, target_logits, draft_logits, n_tree, vocab, n_chunks,
-                               vec, token, parent, u_accept, u_bonus, max_depth, inv_temp, stat_m, stat_s, nullptr, nullptr, work, accept_len,
-                               accept_path, bonus_token);
-        } else {
-            hipLaunchKernelGGL(residual_stats_kernel<BF>, dim3(n_chunks, batch * n_tree), dim3(256), 0, st, target_logits, draft_logits, n_tree,
-                               vocab, n_chunks, vec, parent, inv_temp, stat_m, stat_s, res_sum, node_stats);
-            hipLaunchKernelGGL((spec_walk_kernel<BF, false>), dim3(batch), dim3(NT), 0, st, target_logits, draft_logits, n_tree, vocab, n_chunks,
-                               vec, token, parent, u_accept, u_bonus, max_depth, inv_temp, stat_m, stat_s, res_sum, node_stats, work,
-                               accept_len, accept_path, bonus_token);
-        }
+                           parent, inv_temp, stat_m, stat_s, slots);
+        hipLaunchKernelGGL(spec_walk_kernel<BF>, dim3(n_wg, batch), dim3(NT), 0, st, wa);
     };
     if (logits_dtype == DREAM_BF16)
         launch_all(std::true_type{});

@@ -179,3 +179,16 @@ def test_every_branch_of_the_walk_is_exercised(gu):
             ("all rejected, children", 1), ("all rejected, children", 2), ("all rejected, children", 3),
             ("draw at a node without children",)}
     assert want <= seen, want - seen
+
+
+@pytest.mark.parametrize("V", [8192, 8193, 24577, 65536, 540001])
+@pytest.mark.parametrize("polls", [0, -1])
+def test_workgroups_of_a_sequence(gu, V, polls):
+    """Rows of one, two, several and more than 64 chunks of 8192 tokens, summed by several workgroups that exchange their
+    sums, and (polls < 0: nobody waits) by workgroup 0 in the others' place."""
+    import paper_2505_19201_amd as dream
+    dream.dream_set_accept_spin(polls)
+    try:
+        _case(gu, 3 if V > 100000 else 8, 21, 5, V, "f32", 970 + V, noise=1.0, min_clear=0.0)
+    finally:
+        dream.dream_set_accept_spin(0)
