@@ -9,17 +9,17 @@
 // v_mfma_f32_16x16x32_bf16 (A = weight rows, B = feature rows).  With at most 16 feature rows (the paper's
 // shapes) a wave fetches 256 contiguous bytes of each row at a time and passes them through a private LDS area
 // to reach the operand layout: nobody else reads those bytes, but an operand-layout load touches 16 rows x 64
-// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows (up to 4 tiles of 16 at
-// a time) the operands are loaded directly.  The 4 partial tiles are summed through LDS in wave order and the
-// rows are rounded to bf16 and scattered.  Roofline: HBM, N*hidden*2 weight bytes per call.
+// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows project_rows_kernel (below)
+// is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
+// Roofline: HBM, N*hidden*2 weight bytes per call.
 #include "common.h"
+#include <atomic>
 
 using namespace dream;
 
 namespace {
 
 constexpr int NWAVE = 4;   // (8 waves measured 5-8 % slower on the narrower maps, 2 no faster)
-static_assert(NWAVE >= 4, "the final reduction gives each of up to 4 feature-row tiles to one wave");
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -45,22 +45,22 @@ struct ProjArgs {
     int64_t s_max;       // cache mode only
 };
 
-// MT: tiles of 16 feature rows handled per pass (1, 2 or 4)
-template <int MT>
-__global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
+// The job a workgroup belongs to (uniform: scalar selects) and the first workgroup of that job.
+struct ProjView {
+    const uint16_t *x, *w;
+    uint16_t *out;
+    const int32_t *row_base, *row_index;
+    int32_t n_heads, n_rows, m_total, hidden, head_dim;
+    int64_t s_max;
+    int first;
+};
+__device__ __forceinline__ ProjView select_job(const ProjArgs &args, int wg)
 {
-    // the job this workgroup belongs to (uniform: scalar selects)
     int ji = 0;
     for (int j = 0; j + 1 < args.n_jobs; j++)
-        ji += (int)blockIdx.x >= args.job[j].tile_end;
-    struct {
-        const uint16_t *x, *w;
-        uint16_t *out;
-        const int32_t *row_base, *row_index;
-        int32_t n_heads, n_rows, m_total, hidden, head_dim;
-        int64_t s_max;
-    } a;
-    int tile0 = 0;
+        ji += wg >= args.job[j].tile_end;
+    ProjView a;
+    a.first = 0;
     a.x = args.job[0].x; a.w = args.job[0].w; a.out = args.job[0].out; a.row_base = args.job[0].row_base;
     a.row_index = args.job[0].row_index; a.n_heads = args.job[0].n_heads;
 #pragma unroll
@@ -68,133 +68,259 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
         if (ji == j) {
             a.x = args.job[j].x; a.w = args.job[j].w; a.out = args.job[j].out; a.row_base = args.job[j].row_base;
             a.row_index = args.job[j].row_index; a.n_heads = args.job[j].n_heads;
-            tile0 = args.job[j - 1].tile_end;
+            a.first = args.job[j - 1].tile_end;
         }
     a.n_rows = args.n_rows; a.m_total = args.m_total; a.hidden = args.hidden; a.head_dim = args.head_dim; a.s_max = args.s_max;
+    return a;
+}
 
-    __shared__ __attribute__((aligned(16))) float s_part[NWAVE][MT][64][4];
+// The lane's four results, outputs n0 + g*4 .. +3 of feature row m, to where they belong.
+__device__ __forceinline__ void store_row_piece(const ProjView &a, int m, int n0, int g, f32x4 sum)
+{
+    if (m >= a.m_total)
+        return;
+    const int h = n0 / a.head_dim, d0 = n0 % a.head_dim;
+    const int b = m / a.n_rows, r = m - b * a.n_rows;
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        o[i] = (__bf16)sum[i];
+    int64_t dst;
+    if (a.row_base) {
+        const int row = a.row_base[b] + (a.row_index ? a.row_index[(int64_t)b * a.n_rows + r] : r);
+        dst = row >= 0 && row < a.s_max ? (((int64_t)b * a.n_heads + h) * a.s_max + row) * a.head_dim + d0 + g * 4 : -1;
+    } else {
+        dst = (((int64_t)b * a.n_rows + r) * a.n_heads + h) * a.head_dim + d0 + g * 4;
+    }
+    if (dst >= 0)                                        // a row outside the cache is dropped, never written
+        *reinterpret_cast<bf16x4 *>(a.out + dst) = o;
+}
+
+// At most 16 feature rows.
+__global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
+{
+    const ProjView a = select_job(args, blockIdx.x);
+    __shared__ __attribute__((aligned(16))) float s_part[NWAVE][64][4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int n0 = ((int)blockIdx.x - tile0) * 16;
+    const int n0 = ((int)blockIdx.x - a.first) * 16;
     const int K = a.hidden, kw = K / NWAVE;          // this wave's slice of the hidden dimension
-    const uint16_t *wrow = a.w + (int64_t)(n0 + c) * K + wave * kw + g * 8;
-    const int h = n0 / a.head_dim, d0 = n0 % a.head_dim;
-
-    for (int m0 = 0; m0 < a.m_total; m0 += 16 * MT) {
-        f32x4 acc[MT];
-        const uint16_t *xrow[MT];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    // Rows are fetched 256 contiguous bytes at a time (4 rows per load instruction: full cache lines) into
+    // a wave-private LDS area and read back in operand layout; loading the operands directly would make
+    // every instruction touch 16 rows x 64 bytes.
+    constexpr int SS = 128, RSTR = SS + 8;             // elements of a row per super-step; padded LDS row stride
+    constexpr int LPR = SS / 8, RPI = 64 / LPR, NI = 16 / RPI;   // lanes per row, rows per instruction, instructions per 16 rows
+    __shared__ __attribute__((aligned(16))) uint16_t s_stage[NWAVE][2][16 * RSTR];
+    uint16_t *lw = s_stage[wave][0], *lx = s_stage[wave][1];
+    const int lrow = lane / LPR, lcol = (lane % LPR) * 8;
+    const int n_ss = (kw + SS - 1) / SS;
+    const uint16_t *wsrc = a.w + (int64_t)n0 * K + wave * kw;
+    const uint16_t *xsrc = a.x + wave * kw;
+    const int xj = min((a.m_total + RPI - 1) / RPI, NI);
+    auto issue = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
+        s = min(s, n_ss - 1);                              // the prefetch past the end re-reads and is dropped
+        const int nvalid = min(SS, kw - s * SS);
+        const int col = s * SS + (lcol < nvalid ? lcol : 0);
 #pragma unroll
-        for (int mt = 0; mt < MT; mt++) {
-            acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int m = min(m0 + mt * 16 + c, a.m_total - 1);   // padding rows repeat the last row; never stored
-            xrow[mt] = a.x + (int64_t)m * K + wave * kw + g * 8;
-        }
-        if (MT == 1) {
-            // Rows are fetched 256 contiguous bytes at a time (4 rows per load instruction: full cache lines) into
-            // a wave-private LDS area and read back in operand layout; loading the operands directly would make
-            // every instruction touch 16 rows x 64 bytes.
-            constexpr int SS = 128, RSTR = SS + 8;             // elements of a row per super-step; padded LDS row stride
-            constexpr int LPR = SS / 8, RPI = 64 / LPR, NI = 16 / RPI;   // lanes per row, rows per instruction, instructions per 16 rows
-            __shared__ __attribute__((aligned(16))) uint16_t s_stage[NWAVE][2][16 * RSTR];
-            uint16_t *lw = s_stage[wave][0], *lx = s_stage[wave][1];
-            const int lrow = lane / LPR, lcol = (lane % LPR) * 8;
-            const int n_ss = (kw + SS - 1) / SS;
-            const uint16_t *wsrc = a.w + (int64_t)n0 * K + wave * kw;
-            const uint16_t *xsrc = a.x + wave * kw;
-            const int xj = min((a.m_total - m0 + RPI - 1) / RPI, NI);
-            auto issue = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
-                s = min(s, n_ss - 1);                              // the prefetch past the end re-reads and is dropped
-                const int nvalid = min(SS, kw - s * SS);
-                const int col = s * SS + (lcol < nvalid ? lcol : 0);
-#pragma unroll
-                for (int j = 0; j < NI; j++) {
-                    wr[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wsrc + (int64_t)(j * RPI + lrow) * K + col));   // weights: read once
-                    if (j < xj) {   // feature rows are fetched RPI at a time, only as many as exist
-                        const int m = min(m0 + j * RPI + lrow, a.m_total - 1);
-                        xr[j] = *reinterpret_cast<const u32x4 *>(xsrc + (int64_t)m * K + col);
-                    }
-                }
-            };
-            // one super-step: registers -> LDS, request the super-step that reuses these registers, multiply
-            auto step = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
-#pragma unroll
-                for (int j = 0; j < NI; j++) {
-                    *reinterpret_cast<u32x4 *>(lw + (j * RPI + lrow) * RSTR + lcol) = wr[j];
-                    if (j < xj)     // (the other LDS rows feed output columns that are never stored)
-                        *reinterpret_cast<u32x4 *>(lx + (j * RPI + lrow) * RSTR + lcol) = xr[j];
-                }
-                issue(s + 1, wr, xr);
-                wave_lds_fence();
-                const int nvalid = min(SS, kw - s * SS);
-#pragma unroll
-                for (int ks = 0; ks < SS / 32; ks++) {
-                    if (ks * 32 < nvalid) {
-                        const bf16x8 af = *reinterpret_cast<const bf16x8 *>(lw + c * RSTR + ks * 32 + g * 8);
-                        const bf16x8 bfr = *reinterpret_cast<const bf16x8 *>(lx + c * RSTR + ks * 32 + g * 8);
-                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc[0], 0, 0, 0);
-                    }
-                }
-                wave_lds_fence();
-            };
-            u32x4 wr[NI], xr[NI];
-            issue(0, wr, xr);
-            for (int s = 0; s < n_ss; s++)
-                step(s, wr, xr);
-        } else
-        {
-        constexpr int U = 8 / MT;        // k-steps whose loads are in flight together
-            for (int k = 0; k < kw; k += 32 * U) {
-                bf16x8 wf[U], xf[U][MT];
-#pragma unroll
-                for (int u = 0; u < U; u++) {
-                    const int kk = min(k + 32 * u, kw - 32);            // (kw is a multiple of 32; a short tail re-reads and is skipped below)
-                    wf[u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(wrow + kk));   // weights: read once
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++)
-                        xf[u][mt] = *reinterpret_cast<const bf16x8 *>(xrow[mt] + kk);
-                }
-#pragma unroll
-                for (int u = 0; u < U; u++) {
-                    if (k + 32 * u < kw) {
-#pragma unroll
-                        for (int mt = 0; mt < MT; mt++)
-                            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u], xf[u][mt], acc[mt], 0, 0, 0);
-                    }
-                }
+        for (int j = 0; j < NI; j++) {
+            wr[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wsrc + (int64_t)(j * RPI + lrow) * K + col));   // weights: read once
+            if (j < xj) {   // feature rows are fetched RPI at a time, only as many as exist
+                const int m = min(j * RPI + lrow, a.m_total - 1);
+                xr[j] = *reinterpret_cast<const u32x4 *>(xsrc + (int64_t)m * K + col);
             }
         }
-        // sum the waves' partial tiles in wave order; thread (wave, lane) finishes tile mt = wave % MT ... spread evenly
-        __syncthreads();
+    };
+    // one super-step: registers -> LDS, request the super-step that reuses these registers, multiply
+    auto step = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
 #pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-            *reinterpret_cast<f32x4 *>(s_part[wave][mt][lane]) = acc[mt];
-        __syncthreads();
-        if (wave < MT) {
-            const int mt = wave;
-            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NI; j++) {
+            *reinterpret_cast<u32x4 *>(lw + (j * RPI + lrow) * RSTR + lcol) = wr[j];
+            if (j < xj)     // (the other LDS rows feed output columns that are never stored)
+                *reinterpret_cast<u32x4 *>(lx + (j * RPI + lrow) * RSTR + lcol) = xr[j];
+        }
+        issue(s + 1, wr, xr);
+        wave_lds_fence();
+        const int nvalid = min(SS, kw - s * SS);
 #pragma unroll
-            for (int w = 0; w < NWAVE; w++)
-                sum += *reinterpret_cast<const f32x4 *>(s_part[w][mt][lane]);
-            const int m = m0 + mt * 16 + c;                          // lane holds outputs n0 + g*4 .. +3 of feature row m
-            if (m < a.m_total) {
-                const int b = m / a.n_rows, r = m - b * a.n_rows;
-                bf16x4 o;
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    o[i] = (__bf16)sum[i];
-                int64_t dst;
-                if (a.row_base) {
-                    const int row = a.row_base[b] + (a.row_index ? a.row_index[(int64_t)b * a.n_rows + r] : r);
-                    dst = row >= 0 && row < a.s_max ? (((int64_t)b * a.n_heads + h) * a.s_max + row) * a.head_dim + d0 + g * 4 : -1;
-                } else {
-                    dst = (((int64_t)b * a.n_rows + r) * a.n_heads + h) * a.head_dim + d0 + g * 4;
-                }
-                if (dst >= 0)                                        // a row outside the cache is dropped, never written
-                    *reinterpret_cast<bf16x4 *>(a.out + dst) = o;
+        for (int ks = 0; ks < SS / 32; ks++) {
+            if (ks * 32 < nvalid) {
+                const bf16x8 af = *reinterpret_cast<const bf16x8 *>(lw + c * RSTR + ks * 32 + g * 8);
+                const bf16x8 bfr = *reinterpret_cast<const bf16x8 *>(lx + c * RSTR + ks * 32 + g * 8);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc, 0, 0, 0);
             }
         }
+        wave_lds_fence();
+    };
+    u32x4 wr[NI], xr[NI];
+    issue(0, wr, xr);
+    for (int s = 0; s < n_ss; s++)
+        step(s, wr, xr);
+    // sum the waves' partial tiles in wave order
+    *reinterpret_cast<f32x4 *>(s_part[wave][lane]) = acc;
+    __syncthreads();
+    if (wave == 0) {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NWAVE; w++)
+            sum += *reinterpret_cast<const f32x4 *>(s_part[w][lane]);
+        store_row_piece(a, c, n0, g, sum);
     }
+}
+
+// 16 bytes per lane from `src` straight to LDS: lane i's land at lds + 16 * i.  Inline assembly, because the compiler
+// makes every LDS read wait for all such loads in flight, also for those of later steps.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved; naming it as clobbered is right all the same
+template <bool ONCE>
+__device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds)
+{
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(src) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// More than 16 feature rows.  Every workgroup reads all of them (from L2) beside its own weight rows, so what bounds the
+// call is feature rows + weight rows per workgroup times workgroups per CU: a workgroup owns NT tiles of 16 output
+// features and MT tiles of 16 rows (up to 128 rows per pass), and the launch picks NT for the fewest bytes through the
+// busiest CU.  The hidden dimension is walked in steps of 128 elements: 256-byte pieces of the rows go from memory
+// straight to LDS, NS - 1 steps in flight, one barrier per step; wave w multiplies row tile w % MP with all NT weight
+// tiles over its share of the step's 128 elements.  (The same kernel with the operands loaded from memory in MFMA layout,
+// 16 rows x 64 bytes per instruction, pulled 17 bytes per nanosecond and CU whatever was in flight: 71 us at LLaVA, 80 rows.)
+// Measured per call of three maps (Q, K, V), before (16 features and up to 64 rows per workgroup) and here: 80 rows LLaVA 116 -> 40 us,
+// Pixtral 110 -> 27, Gemma3 83 -> 23, SmolVLM 42 -> 13.5; 20 rows LLaVA 36 -> 25, Pixtral 34 -> 17.  At 10 rows project_kernel is 0.5-2 us faster.
+constexpr int RW = 8;                                // waves per workgroup
+constexpr int STEP = 128, STEP_BYTES = STEP * 2;     // elements, bytes of a row per step
+
+template <int MT, int NT>
+struct RowsGeom {
+    static constexpr int MP = MT <= 1 ? 1 : MT <= 2 ? 2 : MT <= 4 ? 4 : 8;        // row-tile slots
+    static constexpr int KS = RW / MP > 4 ? 4 : RW / MP;                          // waves that share a row tile's elements
+    static constexpr int LOADS = 4 * (MT + NT);                                   // load instructions per step (1024 bytes: 4 row pieces)
+    static constexpr int NLD = (LOADS + RW - 1) / RW;
+    static constexpr int STAGE = LOADS * 1024;
+    static constexpr int FIT = 156 * 1024 / STAGE;
+    static constexpr int NS = FIT > 6 ? 6 : FIT;
+    static constexpr size_t LDS_BYTES = (size_t)NS * STAGE;
+    static_assert(NS >= 3 && (NS - 2) * NLD < 64, "stages");
+    static_assert((size_t)RW * NT * 1024 <= LDS_BYTES, "the partial tiles reuse the stages");
+};
+
+template <int MT, int NT>
+__global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
+{
+    using G = RowsGeom<MT, NT>;
+    const ProjView a = select_job(args, blockIdx.x);
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int n_tiles = a.n_heads * a.head_dim / 16, nt0 = ((int)blockIdx.x - a.first) * NT;
+    const int K = a.hidden, steps = K / STEP;
+    const int mt = wave % G::MP, kg = wave / G::MP;
+    // The workgroups of an XCD start at different steps: the rows are a power of two or nearly so apart, so one step's pieces
+    // of all rows sit in few L2 channels, and everybody would ask the same ones at the same time (LLaVA, 20 rows: 32 us without).
+    const int first = ((int)blockIdx.x >> 3) % steps;
+    for (int m0 = 0; m0 < a.m_total; m0 += 16 * MT) {
+        // load instruction `at`: weight rows first, then feature rows, 4 rows each; 16-byte chunk p of LDS row r holds
+        // chunk p ^ (r & 15) of the row, so that the 16 rows of a fragment read sit in different banks.  Rows past the last
+        // one repeat it (never stored); the instructions past the last repeat an earlier one of the same wave.
+        const unsigned char *src[G::NLD];
+        uint32_t dst[G::NLD];
+#pragma unroll
+        for (int j = 0; j < G::NLD; j++) {
+            const int at = wave + j * RW < G::LOADS ? wave + j * RW : wave + (j - 1) * RW;
+            const int row = at * 4 + lane / 16, chunk = (lane & 15) ^ (row & 15);
+            const uint16_t *base = row < NT * 16 ? a.w + (int64_t)min(nt0 * 16 + row, n_tiles * 16 - 1) * K
+                                                 : a.x + (int64_t)min(m0 + row - NT * 16, a.m_total - 1) * K;
+            src[j] = reinterpret_cast<const unsigned char *>(base) + chunk * 16;
+            dst[j] = lds0 + at * 1024;
+        }
+        auto issue = [&](int s) {
+            const int at = min(s, steps - 1) + first;             // past the end: a load nobody reads keeps the count constant
+            const int off = (at < steps ? at : at - steps) * STEP_BYTES;
+            const uint32_t stage = s % G::NS * G::STAGE;
+#pragma unroll
+            for (int j = 0; j < G::NLD; j++) {
+                if (j * RW + RW <= NT * 4)
+                    load_to_lds<true>(src[j] + off, dst[j] + stage);     // weights: read once
+                else
+                    load_to_lds<false>(src[j] + off, dst[j] + stage);
+            }
+        };
+        f32x4 acc[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+            acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();                                          // (an earlier pass has read its partial tiles)
+#pragma unroll
+        for (int s = 0; s < G::NS - 1; s++)
+            issue(s);
+        for (int s = 0; s < steps; s++) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step s has landed
+            __syncthreads();                                      // everybody's has, and step s - 1 is no longer read
+            issue(s + G::NS - 1);
+            if (mt < MT && kg < G::KS) {
+                const unsigned char *stage = smem + s % G::NS * G::STAGE;
+#pragma unroll
+                for (int i = 0; i < 4 / G::KS; i++) {
+                    const int pos = (((kg * (4 / G::KS) + i) * 4 + g) ^ c) * 16;
+                    const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(stage + ((NT + mt) * 16 + c) * STEP_BYTES + pos);
+#pragma unroll
+                    for (int nt = 0; nt < NT; nt++) {
+                        const bf16x8 wf = *reinterpret_cast<const bf16x8 *>(stage + (nt * 16 + c) * STEP_BYTES + pos);
+                        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, acc[nt], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // nothing lands in the stages any more
+        __syncthreads();
+        if (G::KS > 1) {                                          // sum the partial tiles of a row tile in wave order
+            f32x4 *part = reinterpret_cast<f32x4 *>(smem);
+            if (mt < MT && kg > 0 && kg < G::KS)
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++)
+                    part[(wave * NT + nt) * 64 + lane] = acc[nt];
+            __syncthreads();
+            if (mt < MT && kg == 0)
+#pragma unroll
+                for (int k = 1; k < G::KS; k++)
+#pragma unroll
+                    for (int nt = 0; nt < NT; nt++)
+                        acc[nt] += part[((k * G::MP + mt) * NT + nt) * 64 + lane];
+        }
+        if (mt < MT && kg == 0)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++)
+                if (nt0 + nt < n_tiles)
+                    store_row_piece(a, m0 + mt * 16 + c, (nt0 + nt) * 16, g, acc[nt]);
+    }
+}
+
+template <int MT, int NT>
+int launch_rows(unsigned wgs, hipStream_t st, const ProjArgs &a)
+{
+    static std::atomic<bool> attr_set{false};
+    constexpr size_t bytes = RowsGeom<MT, NT>::LDS_BYTES;
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&project_rows_kernel<MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
+            hipSuccess)
+            return fail(DREAM_ERR_HIP, "dream_project_rows: cannot reserve %zu bytes of LDS", bytes);
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), dim3(wgs), dim3(64 * RW), bytes, st, a);
+    return check_launch("project_rows_kernel");
+}
+
+template <int MT>
+int launch_rows(int nt, unsigned wgs, hipStream_t st, const ProjArgs &a)
+{
+    return nt == 1 ? launch_rows<MT, 1>(wgs, st, a) : nt == 2 ? launch_rows<MT, 2>(wgs, st, a) : launch_rows<MT, 3>(wgs, st, a);
 }
 
 }  // namespace
@@ -240,15 +366,41 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     }
     a.n_jobs = n_jobs; a.n_rows = n_rows; a.m_total = desc->batch * n_rows; a.hidden = hidden; a.head_dim = desc->head_dim;
     a.s_max = desc->s_max;
-    const dim3 grid((unsigned)tiles);
     hipStream_t st = as_stream(stream);
-    if (a.m_total <= 16)
-        hipLaunchKernelGGL(project_kernel<1>, grid, dim3(64 * NWAVE), 0, st, a);
-    else if (a.m_total <= 32)
-        hipLaunchKernelGGL(project_kernel<2>, grid, dim3(64 * NWAVE), 0, st, a);
-    else
-        hipLaunchKernelGGL(project_kernel<4>, grid, dim3(64 * NWAVE), 0, st, a);
-    return check_launch("project_kernel");
+    if (a.m_total <= 16) {
+        hipLaunchKernelGGL(project_kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, a);
+        return check_launch("project_kernel");
+    }
+    // feature tiles per workgroup: the fewest bytes through the busiest CU
+    int nt = 1;
+    int64_t best = 0;
+    for (int t = 1; t <= 3; t++) {
+        int64_t wgs = 0;
+        for (int j = 0; j < n_jobs; j++)
+            wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, t);
+        const int64_t cost = ceil_div(wgs, 256) * (int64_t)(a.m_total + 16 * t);
+        if (t == 1 || cost < best) {
+            best = cost;
+            nt = t;
+        }
+    }
+    int wgs = 0;
+    for (int j = 0; j < n_jobs; j++) {
+        wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
+        a.job[j].tile_end = wgs;
+    }
+    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size
+    const int m_tiles = ceil_div(a.m_total, 16);
+    switch (ceil_div(m_tiles, ceil_div(m_tiles, 8))) {
+    case 1: return launch_rows<1>(nt, wgs, st, a);
+    case 2: return launch_rows<2>(nt, wgs, st, a);
+    case 3: return launch_rows<3>(nt, wgs, st, a);
+    case 4: return launch_rows<4>(nt, wgs, st, a);
+    case 5: return launch_rows<5>(nt, wgs, st, a);
+    case 6: return launch_rows<6>(nt, wgs, st, a);
+    case 7: return launch_rows<7>(nt, wgs, st, a);
+    default: return launch_rows<8>(nt, wgs, st, a);
+    }
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,

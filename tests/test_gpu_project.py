@@ -103,3 +103,11 @@ def test_rows_outside_the_cache_are_dropped(gu):
     assert np.array_equal(got[0][:, :16], cache[0][:, :16].view(np.int16))
     for r in range(4):
         _close(di.bf16_bits_to_f32(got[0][:, 16 + r].view(np.uint16)).astype(np.float64), want[0, r])
+
+
+@pytest.mark.parametrize("B,R,hidden,H,D", [(1, 17, 512, 5, 16), (1, 32, 256, 5, 16), (3, 11, 768, 1, 48), (1, 65, 256, 3, 32), (7, 14, 512, 3, 16),
+                                            (1, 113, 256, 4, 16), (1, 128, 256, 4, 16), (1, 129, 256, 4, 16), (1, 20, 256, 770, 16)])
+def test_row_and_feature_tile_edges(gu, B, R, hidden, H, D):
+    """One row past a tile, whole tiles, every tile count, a second pass (129 rows), a last workgroup with fewer feature tiles (770)."""
+    x, w = _inputs(B, R, hidden, H, D, 140 + R)
+    _close(gu.run_project(x, w, H, D), oracle.project(x, w, "bf16", H, D))
