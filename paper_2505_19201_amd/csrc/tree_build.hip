@@ -12,7 +12,7 @@
 //       (log-sum-exp; k rounds of a wave arg-max over the chunk candidates), writes tokens and scores, then
 //       ranks the F*k candidates by counting (score descending, index ascending) for the next frontier.
 // dream_tree_finalize  the root and the `budget` best candidates of all levels, in creation order, parents
-//   re-indexed: rank by counting in LDS, block scan for the new indices.
+//   re-indexed: one wave finds the last kept score bit by bit and numbers the kept entries with ballots.
 // Roofline: the expansion is an HBM scan of B*F*V logits (launch-latency bound at one sequence); the rest is
 // latency bound by construction (a few hundred candidates).
 #include "common.h"
@@ -74,6 +74,32 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t k)
     return ab > cd ? ab : cd;
 }
 
+// Sum and maximum over the wave in every lane: rotations inside the rows of 16 lanes, then the four row values as scalars.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v += row_rotate_f<8>(v);
+    v += row_rotate_f<4>(v);
+    v += row_rotate_f<2>(v);
+    v += row_rotate_f<1>(v);
+    auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, row_rotate_f<8>(v));
+    v = fmaxf(v, row_rotate_f<4>(v));
+    v = fmaxf(v, row_rotate_f<2>(v));
+    return fmaxf(v, row_rotate_f<1>(v));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = row_max(v);
+    auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
+    return fmaxf(fmaxf(row(0), row(16)), fmaxf(row(32), row(48)));
+}
+
+// What bounds it is latency, not bytes (one LLaVA level is 0.6 MB): the chunk is read once, and between the loads and the
+// stores there are two barriers and no cross-lane exchange through LDS.
 template <bool BF16>
 __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits, int vocab, int n_chunks, int k, float *part_m,
                                                              float *part_s, uint64_t *part_key)
@@ -126,65 +152,45 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
         }
     }
 
-    // chunk maximum and sum of exponentials relative to it
+    // ---- the 256 thread maxima fall into 16 rows of 16 lanes.  Their maximum is the chunk's, and the k-th largest of the 16 row
+    // maxima is a lower bound of the chunk's k-th largest logit (at least k elements are at or above it).  Every wave ranks
+    // the 16 for itself.
+    __shared__ __attribute__((aligned(16))) float s_row[16];
+    __shared__ int s_count;
+    __shared__ uint64_t s_cand[256];
     float m = -INFINITY;
 #pragma unroll
     for (int e = 0; e < PER_THREAD; e++)
-        m = fmaxf(m, x[e]);
-    const float tmax = m;   // this thread's maximum (padding is -inf)
-    for (int off = 32; off > 0; off >>= 1)
-        m = fmaxf(m, __shfl_xor(m, off));
-    if (lane == 0)
-        s_f[wave] = m;
+        m = fmaxf(m, x[e]);                              // (padding is -inf)
+    m = row_max(m);
+    if ((lane & 15) == 0)
+        s_row[tid >> 4] = m;
+    if (tid == 0)
+        s_count = 0;
     __syncthreads();
-    m = fmaxf(fmaxf(s_f[0], s_f[1]), fmaxf(s_f[2], s_f[3]));
-    __syncthreads();
+    float rows[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++)
+        rows[j] = s_row[j];
+    const float mine = s_row[lane & 15];
+    int row_rank = 0;
+    m = rows[0];
+#pragma unroll
+    for (int j = 0; j < 16; j++) {
+        row_rank += (rows[j] > mine || (rows[j] == mine && j < (lane & 15))) ? 1 : 0;
+        m = fmaxf(m, rows[j]);
+    }
+    const float tau = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_ctzll(__ballot(row_rank == min(k, 16) - 1))));
+    // sum of exponentials relative to the maximum
     float s = 0.0f;
 #pragma unroll
     for (int e = 0; e < PER_THREAD; e++)
         s += x[e] == -INFINITY ? 0.0f : __expf(x[e] - m);
-    for (int off = 32; off > 0; off >>= 1)
-        s += __shfl_xor(s, off);
+    s = wave_sum(s);
     if (lane == 0)
         s_f[wave] = s;
-    __syncthreads();
-    if (tid == 0) {
-        part_m[row * n_chunks + chunk] = m;
-        part_s[row * n_chunks + chunk] = (s_f[0] + s_f[1]) + (s_f[2] + s_f[3]);
-    }
-
-    // ---- the chunk's k largest.  A lower bound of the k-th largest value first: the 256 thread maxima fall into
-    // 16 rows of 16 lanes, and the k-th largest of the 16 row maxima has at least k elements at or above it.
-    // Elements at or above that bound (a few dozen for ordinary logits) are collected in LDS and ranked by
-    // counting; more than 256 of them (heavy ties) fall back to k rounds of a block-wide arg-max.
-    __shared__ float s_row[16];
-    __shared__ float s_tau;
-    __shared__ int s_count;
-    __shared__ uint64_t s_cand[256];
-    float rm = tmax;
-    rm = fmaxf(rm, row_rotate_f<8>(rm));
-    rm = fmaxf(rm, row_rotate_f<4>(rm));
-    rm = fmaxf(rm, row_rotate_f<2>(rm));
-    rm = fmaxf(rm, row_rotate_f<1>(rm));
-    if ((lane & 15) == 0)
-        s_row[tid >> 4] = rm;
-    if (tid == 0)
-        s_count = 0;
-    __syncthreads();
-    if (tid < 16) {
-        const float mine = s_row[tid];
-        int rank = 0;
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-            const float o = s_row[j];
-            rank += (o > mine || (o == mine && j < tid)) ? 1 : 0;
-        }
-        if (rank == min(k, 16) - 1)
-            s_tau = mine;
-    }
-    __syncthreads();
-    const float tau = s_tau;
-    int overflow = 0;
+    // ---- the chunk's k largest: the elements at or above the bound (a few dozen for ordinary logits) are collected in LDS and
+    // ranked by counting; more than 256 of them (heavy ties) fall back to k rounds of a block-wide arg-max.
 #pragma unroll
     for (int e = 0; e < PER_THREAD; e++) {
         const int t = begin + (e >> 3) * 2048 + tid * 8 + (e & 7);
@@ -192,11 +198,13 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
             const int slot = atomicAdd(&s_count, 1);
             if (slot < 256)
                 s_cand[slot] = make_key(x[e], t);
-            else
-                overflow = 1;
         }
     }
     __syncthreads();
+    if (tid == 0) {
+        part_m[row * n_chunks + chunk] = m;
+        part_s[row * n_chunks + chunk] = (s_f[0] + s_f[1]) + (s_f[2] + s_f[3]);
+    }
     const int n_cand = s_count;
     uint64_t *out_key = part_key + (row * n_chunks + chunk) * k;
     if (n_cand <= 256) {
@@ -213,7 +221,6 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
             out_key[tid] = 0ull;   // fewer than k tokens in the chunk
         return;
     }
-    (void)overflow;
     // keys of this thread's elements (0 for tokens past the vocabulary: below every real key)
     uint64_t key[PER_THREAD];
 #pragma unroll
@@ -245,43 +252,48 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
     }
 }
 
-// One workgroup of 16 waves per sequence; wave f merges the chunk partials of frontier row f.
+// One workgroup of 16 waves per sequence; wave f merges the chunk partials of frontier row f.  PART: chunk candidates a lane
+// holds (1, 2, 4 or 8).  Latency bound: every load of a row is issued before the first result is needed.
+template <int PART>
 __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *part_m, const float *part_s, const uint64_t *part_key,
                                                                   int n_frontier, int n_chunks, int k, const float *cum_in,
                                                                   int32_t *cand_token, float *cand_score, int32_t *next_frontier)
 {
     __shared__ uint64_t s_key[MAX_F * MAX_K];   // (score, flat index) keys of the level's candidates
-    constexpr int MAX_PART = 8;                 // chunk candidates per lane: 64 * 8 = 32 chunks * 16
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int f = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_cand = n_frontier * k;
     if (f < n_frontier) {
         const int64_t row = (int64_t)b * n_frontier + f;
         const int n_part = n_chunks * k;
-        uint64_t pk[MAX_PART];
+        uint64_t pk[PART];
 #pragma unroll
-        for (int j = 0; j < MAX_PART; j++)
+        for (int j = 0; j < PART; j++)
             pk[j] = lane + j * 64 < n_part ? part_key[row * n_part + lane + j * 64] : 0ull;
-        // log-sum-exp of the row from the chunk partials
-        float M = -INFINITY;
-        for (int ch = lane; ch < n_chunks; ch += 64)
-            M = fmaxf(M, part_m[row * n_chunks + ch]);
-        for (int off = 32; off > 0; off >>= 1)
-            M = fmaxf(M, __shfl_xor(M, off));
-        float S = 0.0f;
-        for (int ch = lane; ch < n_chunks; ch += 64) {
-            const float mc = part_m[row * n_chunks + ch];
-            S += mc == -INFINITY ? 0.0f : part_s[row * n_chunks + ch] * __expf(mc - M);
+        // log-sum-exp of the row from the chunk partials (8 per lane: with k = 1 there may be 512 chunks)
+        float M = -INFINITY, cm[8], cs[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const int ch = lane + j * 64;
+            cm[j] = ch < n_chunks ? part_m[row * n_chunks + ch] : -INFINITY;
+            cs[j] = ch < n_chunks ? part_s[row * n_chunks + ch] : 0.0f;
         }
-        for (int off = 32; off > 0; off >>= 1)
-            S += __shfl_xor(S, off);
-        const float lse = M + __logf(S);
         const float cum = cum_in[row];
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            M = fmaxf(M, cm[j]);
+        M = wave_max(M);
+        float S = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            S += cm[j] == -INFINITY ? 0.0f : cs[j] * __expf(cm[j] - M);
+        S = wave_sum(S);
+        const float lse = M + __logf(S);
         uint64_t prev = ~0ull;
         for (int r = 0; r < k; r++) {
             uint64_t best = 0ull;
 #pragma unroll
-            for (int j = 0; j < MAX_PART; j++) {
+            for (int j = 0; j < PART; j++) {
                 const uint64_t c = pk[j] < prev ? pk[j] : 0ull;
                 best = c > best ? c : best;
             }
@@ -312,59 +324,82 @@ __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *p
         next_frontier[(int64_t)b * kf + rank] = cand;
 }
 
-// One workgroup of 1024 threads per sequence.  `share` threads (a power of two, adjacent lanes) count the
-// rank of one pool entry together.
-__global__ __launch_bounds__(1024) void tree_finalize_kernel(const float *pool_score, const int32_t *pool_parent, const int32_t *pool_token,
-                                                             int n_pool, int keep_n, int share_log2, int32_t *tree_parent,
-                                                             int32_t *tree_token, int32_t *tree_pool_index)
+// One wave per sequence, the whole pool in its registers (entry r * 64 + lane in register r), so nothing has to be
+// synchronised: the score of the last kept entry is found bit by bit, counting entries at or above a trial value with a compare
+// and a population count per register, and stops as soon as a trial value keeps exactly the asked number.  (Ranking
+// every entry by counting larger ones took 10.7 us for a pool of 511: a quarter of a million compares fed from LDS.)
+template <int NR>
+__global__ __launch_bounds__(64) void tree_finalize_kernel(const float *pool_score, const int32_t *pool_parent, const int32_t *pool_token,
+                                                           int n_pool, int keep_n, int32_t *tree_parent, int32_t *tree_token,
+                                                           int32_t *tree_pool_index)
 {
-    __shared__ uint64_t s_key[DREAM_MAX_POOL];
-    __shared__ int32_t s_new[DREAM_MAX_POOL];   // new index of a kept entry, -2 for a dropped one
-    __shared__ uint8_t s_keep[DREAM_MAX_POOL];
-    __shared__ int s_wave[16];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *sc = pool_score + (int64_t)b * n_pool;
-    if (tid < n_pool)
-        s_key[tid] = tid == 0 ? ~0ull : make_key(sc[tid], tid);   // the root outranks everything
-    __syncthreads();
-    {
-        const int share = 1 << share_log2;
-        const int e = tid >> share_log2, part = tid & (share - 1);
-        int rank = 0;
-        if (e < n_pool) {
-            const uint64_t mine = s_key[e];
-#pragma unroll 8
-            for (int j = part; j < n_pool; j += share)
-                rank += s_key[j] > mine ? 1 : 0;
+    __shared__ int32_t s_new[NR * 64];          // new index of a kept entry, -2 for a dropped one
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int64_t at = (int64_t)b * n_pool;
+    float sc[NR];
+    uint32_t key[NR];
+    int32_t par[NR], tok[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        const int64_t i = at + min(r * 64 + lane, n_pool - 1);   // (unconditional loads: all in flight together)
+        sc[r] = pool_score[i];
+        par[r] = pool_parent[i];
+        tok[r] = pool_token[i];
+    }
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        const int i = r * 64 + lane;
+        key[r] = i > 0 && i < n_pool ? order_bits(sc[r]) : 0u;    // (0 is below every score's key)
+    }
+    // the largest value with at least keep_n entries at or above it
+    uint32_t cut = 0u;
+    int at_cut = -1;                              // entries at or above `cut`
+#pragma unroll 1
+    for (int bit = 31; bit >= 0 && keep_n > 0; bit--) {
+        const uint32_t trial = cut | (1u << bit);
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            n += __popcll(__ballot(key[r] >= trial));
+        if (n >= keep_n) {
+            cut = trial;
+            at_cut = n;
+            if (n == keep_n)
+                break;
         }
-        for (int off = 1; off < share; off <<= 1)
-            rank += __shfl_xor(rank, off);
-        if (e < n_pool && part == 0)
-            s_keep[e] = rank <= keep_n ? 1 : 0;   // rank counts the root too: root has rank 0
     }
-    __syncthreads();
-    const bool keep = tid < n_pool && s_keep[tid];
-    // exclusive scan of the keep flags: ballot inside a wave, wave totals through LDS
-    const uint64_t bal = __ballot(keep);
-    const int within = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0)
-        s_wave[wave] = __popcll(bal);
-    __syncthreads();
+    // with more entries than asked for, those at the cut itself are kept in index order
+    int spare = 0x7fffffff;
+    if (at_cut > keep_n) {
+        int above = 0;
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            above += __popcll(__ballot(key[r] > cut));
+        spare = keep_n - above;
+    }
+    const uint64_t below = (1ull << lane) - 1ull;
     int base = 0;
-    for (int w = 0; w < wave; w++)
-        base += s_wave[w];
-    const int my_new = base + within;
-    if (tid < n_pool)
-        s_new[tid] = keep ? my_new : -2;
-    __syncthreads();
-    if (keep) {
-        const int T = 1 + keep_n;
-        const int64_t o = (int64_t)b * T + my_new;
-        const int pp = pool_parent[(int64_t)b * n_pool + tid];
-        tree_parent[o] = tid == 0 ? -1 : ((pp >= 0 && pp < n_pool) ? s_new[pp] : -2);
-        tree_token[o] = pool_token[(int64_t)b * n_pool + tid];
-        tree_pool_index[o] = tid;
+    bool keep[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        const bool tie = keep_n > 0 && key[r] == cut && key[r] != 0u;
+        const uint64_t ties = __ballot(tie);
+        const bool take_tie = tie && (int)__popcll(ties & below) < spare;
+        keep[r] = (r == 0 && lane == 0) || (keep_n > 0 && key[r] > cut) || take_tie;
+        spare -= (int)__popcll(ties);
+        const uint64_t kept = __ballot(keep[r]);
+        s_new[r * 64 + lane] = keep[r] ? base + __popcll(kept & below) : -2;
+        base += __popcll(kept);
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+        if (keep[r]) {
+            const int64_t o = (int64_t)b * (1 + keep_n) + s_new[r * 64 + lane];
+            tree_parent[o] = r == 0 && lane == 0 ? -1 : ((par[r] >= 0 && par[r] < n_pool) ? s_new[par[r]] : -2);
+            tree_token[o] = tok[r];
+            tree_pool_index[o] = r * 64 + lane;
+        }
 }
 
 struct ExpandPlan {
@@ -429,8 +464,9 @@ int dream_tree_expand_level(const void *logits, int32_t logits_dtype, int32_t ba
     int rc = check_launch("expand_partial_kernel");
     if (rc)
         return rc;
-    hipLaunchKernelGGL(expand_merge_kernel, dim3(batch), dim3(64 * MAX_F), 0, st, pm, ps, pkey, n_frontier, p.n_chunks, k, cum_in,
-                       cand_token, cand_score, next_frontier);
+    const int n_part = p.n_chunks * k;
+    auto merge = n_part <= 64 ? expand_merge_kernel<1> : n_part <= 128 ? expand_merge_kernel<2> : n_part <= 256 ? expand_merge_kernel<4> : expand_merge_kernel<8>;
+    hipLaunchKernelGGL(merge, dim3(batch), dim3(64 * MAX_F), 0, st, pm, ps, pkey, n_frontier, p.n_chunks, k, cum_in, cand_token, cand_score, next_frontier);
     return check_launch("expand_merge_kernel");
 }
 
@@ -450,11 +486,9 @@ int dream_tree_finalize(const float *pool_score, const int32_t *pool_parent, con
     const int keep_n = budget < n_pool - 1 ? budget : n_pool - 1;
     if (n_tree_host)
         *n_tree_host = 1 + keep_n;
-    int share_log2 = 0;   // threads that count one entry's rank together: 1024 / next power of two >= n_pool
-    while ((n_pool << (share_log2 + 1)) <= 1024 && share_log2 < 6)
-        share_log2++;
-    hipLaunchKernelGGL(tree_finalize_kernel, dim3(batch), dim3(1024), 0, as_stream(stream), pool_score, pool_parent, pool_token, n_pool,
-                       keep_n, share_log2, tree_parent, tree_token, tree_pool_index);
+    auto kernel = n_pool <= 128 ? tree_finalize_kernel<2> : n_pool <= 256 ? tree_finalize_kernel<4> : n_pool <= 512 ? tree_finalize_kernel<8> : tree_finalize_kernel<16>;
+    hipLaunchKernelGGL(kernel, dim3(batch), dim3(64), 0, as_stream(stream), pool_score, pool_parent, pool_token, n_pool, keep_n, tree_parent,
+                       tree_token, tree_pool_index);
     return check_launch("tree_finalize_kernel");
 }
 
