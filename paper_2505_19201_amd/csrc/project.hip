@@ -11,7 +11,10 @@
 // to reach the operand layout: nobody else reads those bytes, but an operand-layout load touches 16 rows x 64
 // bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows project_rows_kernel (below)
 // is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
-// Roofline: HBM, N*hidden*2 weight bytes per call.
+// Roofline: HBM, N*hidden*2 weight bytes per call.  The weights are loaded without the nontemporal hint: the next level
+// reads them again, and what the memory-side cache has kept of them by then is worth more than the hint (drafting 6 levels:
+// LLaVA 243 -> 237 us, 8 SmolVLM sequences 285 -> 279; a single call on cold weights is 0-3 us faster but for LLaVA at 10
+// rows, 19.2 -> 20.6).
 #include "common.h"
 #include <atomic>
 
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
         const int col = s * SS + (lcol < nvalid ? lcol : 0);
 #pragma unroll
         for (int j = 0; j < NI; j++) {
-            wr[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wsrc + (int64_t)(j * RPI + lrow) * K + col));   // weights: read once
+            wr[j] = *reinterpret_cast<const u32x4 *>(wsrc + (int64_t)(j * RPI + lrow) * K + col);
             if (j < xj) {   // feature rows are fetched RPI at a time, only as many as exist
                 const int m = min(j * RPI + lrow, a.m_total - 1);
                 xr[j] = *reinterpret_cast<const u32x4 *>(xsrc + (int64_t)m * K + col);
@@ -173,13 +176,9 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
 // makes every LDS read wait for all such loads in flight, also for those of later steps.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved; naming it as clobbered is right all the same
-template <bool ONCE>
 __device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds)
 {
-    if constexpr (ONCE)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(src) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
@@ -191,7 +190,7 @@ __device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds)
 // tiles over its share of the step's 128 elements.  (The same kernel with the operands loaded from memory in MFMA layout,
 // 16 rows x 64 bytes per instruction, pulled 17 bytes per nanosecond and CU whatever was in flight: 71 us at LLaVA, 80 rows.)
 // Measured per call of three maps (Q, K, V), before (16 features and up to 64 rows per workgroup) and here: 80 rows LLaVA 116 -> 40 us,
-// Pixtral 110 -> 27, Gemma3 83 -> 23, SmolVLM 42 -> 13.5; 20 rows LLaVA 36 -> 25, Pixtral 34 -> 17.  At 10 rows project_kernel is 0.5-2 us faster.
+// Pixtral 110 -> 23, Gemma3 83 -> 20, SmolVLM 42 -> 11.6; 20 rows LLaVA 36 -> 27, Pixtral 34 -> 14.  At 10 rows project_kernel is 0.5-2 us faster.
 constexpr int RW = 8;                                // waves per workgroup
 constexpr int STEP = 128, STEP_BYTES = STEP * 2;     // elements, bytes of a row per step
 
@@ -245,12 +244,8 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
             const int off = (at < steps ? at : at - steps) * STEP_BYTES;
             const uint32_t stage = s % G::NS * G::STAGE;
 #pragma unroll
-            for (int j = 0; j < G::NLD; j++) {
-                if (j * RW + RW <= NT * 4)
-                    load_to_lds<true>(src[j] + off, dst[j] + stage);     // weights: read once
-                else
-                    load_to_lds<false>(src[j] + off, dst[j] + stage);
-            }
+            for (int j = 0; j < G::NLD; j++)
+                load_to_lds(src[j] + off, dst[j] + stage);
         };
         f32x4 acc[NT];
 #pragma unroll
