@@ -27,8 +27,8 @@
 // coherent with each other.)  Workgroups that read the same K/V stream get ids congruent mod 8 so that they run on one
 // XCD and share its L2.
 //
-// fp32 path (attn_f32_kernel): plain vector-ALU kernel, one workgroup per (query row, head,
-// sequence), used for float32 tensors (the small correctness configuration).
+// fp32 path (attn_f32_kernel): vector-ALU kernel, one workgroup per (query row, head, sequence), used for float32
+// tensors (the small configuration).
 #include "common.h"
 #include "dream_tuning.h"
 #include <atomic>
@@ -896,94 +896,127 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// float32 path: one workgroup per (query row, head, sequence); 256 keys per pass.
+// float32 path: one workgroup of 4 waves per (query row, head, sequence).  D / 4 adjacent lanes share a key, each with four
+// dimensions of its K row and of its V row; a wave serves 256 / D keys at a time and each lane U of them per pass, so the score of a
+// key is reduced inside its lanes and multiplied with the V row there.  Every wave keeps its own online-softmax state;
+// the four meet in LDS at the end.  Latency bound (the tiny configuration reads 0.2 MB): the first pass's K and V rows, the
+// query, the parents and the prefix length are all requested before any of them is needed.
+// Measured, 4 heads x 8 rows x 104 keys: 19.2 us before (a dependent chain of parent loads, then one V row after the other), 5.8 us here, which is what the host takes.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int D)
+template <int LANES>
+__device__ __forceinline__ float sum_lanes(float v)   // over aligned groups of LANES lanes, in every lane of the group
 {
-    __shared__ float sq[256];
-    __shared__ float sp[256];
-    __shared__ float red[8];
-    __shared__ uint64_t smask[4];
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));   // row_ror:8 of 16 lanes, and so on
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));
+    if (LANES >= 32)
+        v += __shfl_xor(v, 16);
+    if (LANES >= 64)
+        v += __shfl_xor(v, 32);
+    return v;
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a)
+{
+    constexpr int LPK = D / 4, KPW = 64 / LPK, U = 8, PASS = 4 * KPW * U;   // lanes per key; keys per wave at a time; keys per pass
+    __shared__ int32_t s_par[DREAM_MAX_TREE];
+    __shared__ float s_o[4][D];
+    __shared__ float s_m[4], s_l[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
     const int kvh = hq / a.group;
-    const int P = (int)min((int64_t)max(a.prefix_len[b], 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
-    const int kv_len = P + a.n_tree;
-    const float *q = reinterpret_cast<const float *>(a.q) + (((int64_t)b * a.n_q + row) * a.n_q_heads + hq) * D;
-    const float *kb = reinterpret_cast<const float *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
-    const float *vb = reinterpret_cast<const float *>(a.v) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
-    if (tid < D)
-        sq[tid] = q[tid];
-    if (tid == 0) {
-        const int node = a.q_node ? min(max(a.q_node[(int64_t)b * a.n_q + row], 0), a.n_tree - 1) : row;
-        NodeMask<4> m = empty_mask<4>();
-        if (a.tree_mask) {
+    const int slot = wave * KPW + lane / LPK, col = lane % LPK;              // this lane's keys: slot + 4 * KPW * u of a pass
+    const f32x4 *kb = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D) + col;
+    const f32x4 *vb = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.v) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D) + col;
+    f32x4 kr[U], vr[U];
+    auto issue = [&](int k0, int64_t rows) {     // keys past `rows` read the last of them; they are masked
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                if (i < a.mask_words)
-                    m.w[i] = a.tree_mask[((int64_t)b * a.n_tree + node) * a.mask_words + i];
-        } else {
-            const int32_t *par = a.parent + (int64_t)b * a.n_tree;
-            if (a.include_self)
-                mask_set(m, node);
-            for (int prev = node, p = par[node]; p >= 0 && p < prev; prev = p, p = par[p])   // parents decrease: the walk ends
-                mask_set(m, p);
+        for (int u = 0; u < U; u++) {
+            const int64_t key = min((int64_t)(k0 + slot + u * 4 * KPW), rows - 1);
+            kr[u] = kb[key * LPK];
+            vr[u] = vb[key * LPK];
         }
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            smask[i] = m.w[i];
+    };
+    issue(0, a.s_max);                           // before the prefix length is known: any row of the cache may be read
+    const int P0 = a.prefix_len[b];
+    const f32x4 q = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(a.q) + (((int64_t)b * a.n_q + row) * a.n_q_heads + hq) * D)[col];
+    int node = row;
+    if (a.q_node)
+        node = min(max(a.q_node[(int64_t)b * a.n_q + row], 0), a.n_tree - 1);
+    if (!a.tree_mask && tid < a.n_tree) {
+        const int p = a.parent[(int64_t)b * a.n_tree + tid];
+        s_par[tid] = p < tid ? p : -1;           // a walk up the tree always ends
     }
     __syncthreads();
-    float m_run = -INFINITY, l_run = 0.0f, o = 0.0f;
-    for (int k0 = 0; k0 < kv_len; k0 += 256) {
-        int key = k0 + tid;
-        float s = -INFINITY;
-        bool vis = key < P || (key < kv_len && ((smask[((key - P) >> 6) & 3] >> ((key - P) & 63)) & 1ull));
-        if (vis) {
-            const float4 *kr = reinterpret_cast<const float4 *>(kb + (int64_t)key * D);
-            float dot = 0.0f;
-            for (int d = 0; d < D / 4; d++) {
-                float4 kk = kr[d];
-                dot += sq[4 * d] * kk.x + sq[4 * d + 1] * kk.y + sq[4 * d + 2] * kk.z + sq[4 * d + 3] * kk.w;
-            }
-            s = dot * a.scale;
+    const NodeMask<4> mask = visible_nodes<4>(a, b, node, s_par);
+    const int P = (int)min((int64_t)max(P0, 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
+    const int kv_len = P + a.n_tree;
+    float m_run = -INFINITY, l_run = 0.0f;       // of this wave; l_run of this lane's keys only until the end
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < kv_len; k0 += PASS) {
+        if (k0 > 0)
+            issue(k0, kv_len);
+        float sc[U], mx = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int key = k0 + slot + u * 4 * KPW, rel = key - P;
+            const bool vis = rel < 0 || (rel < a.n_tree && mask_bit(mask, rel));
+            const float dot = sum_lanes<LPK>((q[0] * kr[u][0] + q[1] * kr[u][1]) + (q[2] * kr[u][2] + q[3] * kr[u][3]));
+            sc[u] = vis ? dot * a.scale : -INFINITY;
+            mx = fmaxf(mx, sc[u]);
         }
-        float mx = s;
-        for (int off = 32; off > 0; off >>= 1)
-            mx = fmaxf(mx, __shfl_xor(mx, off));
-        if (lane == 0)
-            red[wave] = mx;
-        __syncthreads();
-        mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        float m_new = fmaxf(m_run, mx);
-        float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
-        float alpha = expf(m_run - m_safe);
-        float p = vis ? expf(s - m_safe) : 0.0f;
-        sp[tid] = p;
-        float ps = p;
-        for (int off = 32; off > 0; off >>= 1)
-            ps += __shfl_xor(ps, off);
-        if (lane == 0)
-            red[4 + wave] = ps;
-        __syncthreads();
-        l_run = l_run * alpha + ((red[4] + red[5]) + (red[6] + red[7]));
+        if (KPW >= 4)
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+        if (KPW >= 2)
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run, mx), m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
+        const float alpha = expf(m_run - m_safe);
+        l_run *= alpha;
+        o *= alpha;
         m_run = m_new;
-        if (tid < D) {
-            float acc = 0.0f;
-            int n = min(256, kv_len - k0);
-            for (int j = 0; j < n; j++) {
-                float pj = sp[j];
-                if (pj != 0.0f)
-                    acc += pj * vb[(int64_t)(k0 + j) * D + tid];
-            }
-            o = o * alpha + acc;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const float p = expf(sc[u] - m_safe);
+            l_run += p;
+            if (p != 0.0f)                        // (an invisible key's V row is never used)
+                o += vr[u] * p;
         }
-        __syncthreads();
     }
-    if (tid < D)
-        reinterpret_cast<float *>(a.out)[(((int64_t)b * a.n_q + row) * a.n_q_heads + hq) * D + tid] = l_run > 0.0f ? o / l_run : 0.0f;
-    if (a.lse && tid == 0)
-        a.lse[((int64_t)b * a.n_q_heads + hq) * a.n_q + row] = l_run > 0.0f ? m_run + logf(l_run) : -INFINITY;
+    // the lanes that hold other keys of the same dimensions, then the four waves
+    if (KPW >= 4) {
+        l_run += __shfl_xor(l_run, 16);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            o[i] += __shfl_xor(o[i], 16);
+    }
+    if (KPW >= 2) {
+        l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            o[i] += __shfl_xor(o[i], 32);
+    }
+    if (lane < LPK)
+        reinterpret_cast<f32x4 *>(s_o[wave])[col] = o;
+    if (lane == 0) {
+        s_m[wave] = m_run;
+        s_l[wave] = l_run;
+    }
+    __syncthreads();
+    if (tid < D) {
+        const float m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3])), ms = (m == -INFINITY) ? 0.0f : m;
+        float l = 0.0f, r = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; w++) {
+            const float f = expf(s_m[w] - ms);
+            l += s_l[w] * f;
+            r += s_o[w][tid] * f;
+        }
+        reinterpret_cast<float *>(a.out)[(((int64_t)b * a.n_q + row) * a.n_q_heads + hq) * D + tid] = l > 0.0f ? r / l : 0.0f;
+        if (a.lse && tid == 0)
+            a.lse[((int64_t)b * a.n_q_heads + hq) * a.n_q + row] = l > 0.0f ? m + logf(l) : -INFINITY;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1371,7 +1404,8 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
 
     if (d->dtype == DREAM_F32) {
         dim3 grid(n_q, d->n_q_heads, d->batch);
-        hipLaunchKernelGGL(attn_f32_kernel, grid, dim3(256), 0, st, a, d->head_dim);
+        hipLaunchKernelGGL(d->head_dim == 64 ? attn_f32_kernel<64> : d->head_dim == 128 ? attn_f32_kernel<128> : attn_f32_kernel<256>, grid, dim3(256),
+                           0, st, a);
         return check_launch("attn_f32_kernel");
     }
 

@@ -325,3 +325,15 @@ def test_malformed_device_metadata_stays_in_bounds(gu, dtype):
 def dream_to_device(a):
     import paper_2505_19201_amd as dream
     return dream.to_device(a)
+
+
+@pytest.mark.parametrize("D,kv", [(D, kv) for D in (64, 128, 256) for kv in (9, 31, 32, 33, 64, 65, 127, 128, 129, 300)])
+def test_f32_pass_edges(gu, D, kv):
+    """Key counts around the float32 kernel's passes (128, 64 and 32 keys at head_dim 64, 128 and 256), grouped queries, one
+    sequence shorter than the other."""
+    T = 9
+    cfg = _cfg("f32edge", "f32", 2, 4, 2, D, kv - T, 0, T, 4, 46)
+    x = di.verify_inputs(cfg, prefix_len=[kv - T, (kv - T) // 2])
+    got, lse = gu.run_verify(x)
+    want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "f32", x.prefix_len, x.parent, True)
+    assert np.abs(got - want).max() <= TOL["f32"] and np.abs(lse - want_lse).max() <= 1e-5
