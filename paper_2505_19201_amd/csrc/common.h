@@ -35,4 +35,15 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
+// 16 bytes per lane from base + offset straight to LDS: lane i's land at lds + 16 * i.  Inline assembly, because the compiler
+// makes every LDS read wait for all such loads in flight; the caller waits with s_waitcnt vmcnt.  (Loads that the compiler
+// counts itself are only waited for longer than needed beside these.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved; naming it as clobbered is right all the same
+__device__ __forceinline__ void lds_load16(const void *base, uint32_t offset, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 }  // namespace dream

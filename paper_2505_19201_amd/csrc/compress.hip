@@ -13,11 +13,40 @@
 // plus the first ties in position order, and compacts the survivors in position order; the optional
 // gather copies the surviving rows of a [rows, row_elems] matrix.
 #include "common.h"
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 using namespace dream;
 
 namespace {
+
+constexpr int CT = 2;              // MFMA column tiles per wave of both passes (4 halves the loads per score and measured 5-20 % slower: fewer workgroups)
+constexpr int MAX_SPLITS = 8;
+
+// Which blocks are split how often.  The causal triangle gives the blocks of a pass different numbers of steps; a block with
+// more than `S` of them is divided evenly over several workgroups, so that no workgroup of the launch walks more than S.
+// rank: position of a block when they are sorted by falling length; the first count[j] of them have a split j.
+struct SplitMap {
+    int32_t count[MAX_SPLITS];
+};
+struct SplitUnit {
+    int rank, split, n;     // block (by rank), its split, and how many splits it has
+};
+__device__ __forceinline__ SplitUnit split_unit(const SplitMap &map, int u)
+{
+    SplitUnit r = {u, 0, 0};
+#pragma unroll
+    for (int j = 0; j < MAX_SPLITS - 1; j++)
+        if (r.split == j && r.rank >= map.count[j]) {
+            r.rank -= map.count[j];
+            r.split = j + 1;
+        }
+#pragma unroll
+    for (int j = 0; j < MAX_SPLITS; j++)
+        r.n += r.rank < map.count[j];
+    return r;
+}
 
 struct ScoreArgs {
     const void *q, *k;
@@ -27,166 +56,277 @@ struct ScoreArgs {
     float *part;   // [B, Hq, ns2, vis_len]  column sums per head and row split
     int32_t n_q, n_q_pad, n_keys, n_q_heads, n_kv_heads, vis_start, vis_len;
     float *ent_part;    // [ns1, B, Hq, n_q_pad]  expected score of the row under its attention weights, per split (entropy only)
-    int32_t ns1, ns2;   // splits of the streamed axis: keys in pass 1, query rows in pass 2
+    int32_t ns1, ns2;   // most splits of the streamed axis a block has: keys in pass 1, query rows in pass 2
+    SplitMap map1, map2;
     int64_t lse_split_stride;   // B * Hq * n_q_pad
     int64_t s_max;
     float scale, scale_log2;
 };
 
-// Pass 1: log-sum-exp of every causal row.  One workgroup per (64 query rows, head, sequence, key split); wave w
-// owns rows w*16..w*16+15; with ns1 > 1 the block's key tiles are divided evenly over ns1 workgroups, each of
-// which writes a partial log-sum-exp that pass 2 combines.  All 256 threads stream K in 32-key tiles (two tiles ahead in registers, two LDS stages,
-// one barrier per tile); scores are formed transposed (lane = query column), so a lane keeps a private running
-// (max, sum) over its own key rows and the four row groups are combined once at the end.
+// ---- what the two passes share: a stream of 64-row steps from memory straight into LDS ------------------------------------
+// Both passes hold one operand of q k^T in registers and stream the other.  Ablations of the first versions (rows through
+// registers into padded LDS, 4 waves that each read every row) showed no single bound: at 16 SmolVLM sequences the column-sum
+// pass lost 9-25 % when any one of loads, LDS reads, MFMA, exponentials or additions was left out, so the waves wait on each
+// other's latencies.  Hence: loads that need no registers, no LDS write instructions and next to no address arithmetic, which also
+// leaves room for one more workgroup per CU; no bank conflicts; fragments that serve two MFMA tiles per LDS read.
+constexpr int STEP = 64;           // rows per step
+
+template <int D>
+struct StreamGeom {
+    static constexpr int ROW = D * 2, CPR = D / 8, RPI = 64 / CPR;         // bytes and 16-byte chunks of a row; rows per load instruction
+    static constexpr int STAGE = STEP * ROW, NLD = STEP / RPI / 4;         // bytes of a step; load instructions of a wave per step
+    static constexpr int NS = 2;                                           // stages (a third costs resident workgroups: 154 -> 162 us at 16 SmolVLM sequences)
+};
+
+// Position of 16-byte chunk i of row r within the row: i ^ swizzle(r).  A load instruction writes 1024 contiguous bytes, so rows
+// cannot be padded; permuted like this, the 16 rows of a fragment read sit in 16 different bank groups.
+template <int D>
+__device__ __forceinline__ int swizzle(int r)
+{
+    return D == 64 ? (r >> 1) & 7 : r & 15;
+}
+
+template <int D>
+struct RowStream {
+    using G = StreamGeom<D>;
+    const unsigned char *base;     // row 0
+    int64_t row_bytes;             // between rows
+    int n_rows, next;              // rows there are; the next step to load
+    uint32_t lds0;
+    int wave;
+    uint32_t at[G::NLD];           // this lane's byte offsets from the step's first row
+
+    __device__ __forceinline__ void init(const void *rows, int64_t bytes_between, int n, int first_step, const void *lds, int wave_, int lane)
+    {
+        base = reinterpret_cast<const unsigned char *>(rows);
+        row_bytes = bytes_between;
+        n_rows = n;
+        next = first_step;
+        lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)lds;
+        wave = wave_;
+#pragma unroll
+        for (int j = 0; j < G::NLD; j++) {
+            const int row = (wave * G::NLD + j) * G::RPI + lane / G::CPR;
+            at[j] = (uint32_t)(row * (int)row_bytes + ((lane % G::CPR) ^ swizzle<D>(row)) * 16);
+        }
+    }
+    // rows past the last one re-read it (nobody uses their scores)
+    __device__ __forceinline__ void issue(int stage)
+    {
+        const int row0 = min(next * STEP, n_rows - 1), left = n_rows - 1 - row0;
+        next++;
+        const unsigned char *from = base + row0 * row_bytes;
+        const uint32_t to = lds0 + stage * G::STAGE + wave * G::NLD * 1024;
+        if (left >= STEP - 1) {
+#pragma unroll
+            for (int j = 0; j < G::NLD; j++)
+                lds_load16(from, at[j], to + j * 1024);
+        } else {
+#pragma unroll
+            for (int j = 0; j < G::NLD; j++)
+                lds_load16(from, min(at[j], (uint32_t)(left * (int)row_bytes) + (at[j] & (G::ROW - 1))), to + j * 1024);
+        }
+    }
+};
+
+// Pass 1: log-sum-exp of every causal row.  One workgroup per (32 CT query rows, head, sequence, key split).  K is streamed (RowStream, one
+// barrier per step of 64 keys); the four waves are two row slots x two key halves of a step, each with CT MFMA column tiles of
+// 16 rows, so that a K fragment read once serves both.  Scores are formed transposed (lane = query column), so a lane keeps a
+// private running (max, sum) per column; the row groups of the wave and the two halves are combined once at the end.  With
+// several splits each workgroup writes a partial log-sum-exp that pass 2 combines.
 // With ENT the kernel also keeps t = sum_j 2^(x_j - m) x_j, so that the expected score sum_j A_j x_j = t / l of
 // the row is known and the row's entropy -sum A log A = LSE - sum A_j s_j (Eq. 2, Section 3.2) needs no
 // second pass.
+// Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 23 us, 16 SmolVLM sequences 251 -> 200 us.
 template <int D, bool ENT>
-__global__ __launch_bounds__(256) void scores_lse_bf16_kernel(ScoreArgs a)
+__global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
-    constexpr int NKS = D / 32, STR = D + 8, CH = 32 * D / 8 / 256;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2][32 * STR];
+    using G = StreamGeom<D>;
+    constexpr int NKS = D / 32;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
+    __shared__ float s_half[2][CT][ENT ? 3 : 2][16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slot = wave & 1, half = wave >> 1;
     const int c = lane & 15, g = lane >> 4;
     // x walks the heads with the KV head fastest: workgroup ids that share a KV head are congruent mod 8
     // (when there are 8 or more KV heads), so its K is fetched into one XCD's L2 only
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
-    // later row blocks see more keys: they are dispatched first so that the launch does not end on the longest workgroups
-    const int blk = gridDim.y - 1 - blockIdx.y, b = blockIdx.z / a.ns1, split = blockIdx.z % a.ns1;
-    const int row = blk * 64 + wave * 16 + c;
-    const bool valid = row < a.n_q;
-    const int pos = valid ? (a.q_pos ? a.q_pos[(int64_t)b * a.n_q + row] : row) : -1;
+    // later row blocks see more keys: they come first
+    const SplitUnit unit = split_unit(a.map1, blockIdx.y);
+    const int blk = a.map1.count[0] - 1 - unit.rank, b = blockIdx.z, split = unit.split;
+    int row[CT], pos[CT];
+    bool valid[CT];
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        row[q] = (blk * 2 + slot) * 16 * CT + q * 16 + c;
+        valid[q] = row[q] < a.n_q;
+        pos[q] = valid[q] ? (a.q_pos ? a.q_pos[(int64_t)b * a.n_q + row[q]] : row[q]) : -1;
+    }
     // keys this workgroup has to see: without explicit positions, up to its last row
-    const int key_lim = a.q_pos ? a.n_keys : min(min(blk * 64 + 64, a.n_q), a.n_keys);
-    const int n_tiles_all = (key_lim + 31) / 32;
-    const int tps = (n_tiles_all + a.ns1 - 1) / a.ns1;
-    const int t0 = split * tps, n_tiles = max(min(tps, n_tiles_all - t0), 0);   // tiles t0 .. t0 + n_tiles - 1
-    int wave_max_pos = pos;
-    for (int off = 32; off > 0; off >>= 1)
-        wave_max_pos = max(wave_max_pos, __shfl_xor(wave_max_pos, off));
-    wave_max_pos = __builtin_amdgcn_readfirstlane(wave_max_pos);
-    int wave_min_pos = valid ? pos : 0x7fffffff;   // rows that do not exist keep nothing, so they do not count
-    for (int off = 32; off > 0; off >>= 1)
-        wave_min_pos = min(wave_min_pos, __shfl_xor(wave_min_pos, off));
-    wave_min_pos = __builtin_amdgcn_readfirstlane(wave_min_pos);
+    const int key_lim = a.q_pos ? a.n_keys : min(min((blk + 1) * 32 * CT, a.n_q), a.n_keys);
+    const int n_steps_all = (key_lim + STEP - 1) / STEP;
+    const int sps = (n_steps_all + unit.n - 1) / unit.n;
+    const int s0 = split * sps, n_steps = max(min(sps, n_steps_all - s0), 0);   // steps s0 .. s0 + n_steps - 1
+    // the wave's first and last position (rows that do not exist keep nothing, so they do not count)
+    int wave_min_pos = (blk * 2 + slot) * 16 * CT, wave_max_pos = min(wave_min_pos + 16 * CT, a.n_q) - 1;
+    if (a.q_pos) {
+        wave_max_pos = -1;
+        wave_min_pos = 0x7fffffff;
+#pragma unroll
+        for (int q = 0; q < CT; q++) {
+            wave_max_pos = max(wave_max_pos, pos[q]);
+            wave_min_pos = min(wave_min_pos, valid[q] ? pos[q] : 0x7fffffff);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            wave_max_pos = max(wave_max_pos, __shfl_xor(wave_max_pos, off));
+            wave_min_pos = min(wave_min_pos, __shfl_xor(wave_min_pos, off));
+        }
+        wave_max_pos = __builtin_amdgcn_readfirstlane(wave_max_pos);
+        wave_min_pos = __builtin_amdgcn_readfirstlane(wave_min_pos);
+    }
 
     const uint16_t *kb = reinterpret_cast<const uint16_t *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
-    u32x4 kreg[2][CH];
-    const int ld_row = tid / (D / 8), ld_col = tid % (D / 8);
-    auto load_tile = [&](int i, u32x4(&kr)[CH]) {
-        const int t = t0 + max(min(i, n_tiles - 1), 0);
+    RowStream<D> keys;
+    keys.init(kb, D * 2, a.n_keys, s0, lds, wave, lane);
+    if (n_steps > 0) {
 #pragma unroll
-        for (int j = 0; j < CH; j++) {
-            const int key = min(t * 32 + ld_row + j * (2048 / D), a.n_keys - 1);
-            kr[j] = *reinterpret_cast<const u32x4 *>(kb + (int64_t)key * D + ld_col * 8);
-        }
-    };
-    load_tile(0, kreg[0]);
-    load_tile(1, kreg[1]);
-    bf16x8 qf[NKS];
-    {
-        const uint16_t *qp = reinterpret_cast<const uint16_t *>(a.q) + (((int64_t)b * a.n_q + (valid ? row : 0)) * a.n_q_heads + h) * D + g * 8;
+        for (int i = 0; i < G::NS - 1; i++)
+            keys.issue(i);
+    }
+    bf16x8 qf[CT][NKS];
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        const uint16_t *qp = reinterpret_cast<const uint16_t *>(a.q) + (((int64_t)b * a.n_q + (valid[q] ? row[q] : 0)) * a.n_q_heads + h) * D + g * 8;
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 32);
+            qf[q][ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 32);
     }
-    float m = -INFINITY, l = 0.0f, tx = 0.0f;
-    auto step = [&](int i, u32x4(&kr)[CH]) {
-        uint16_t *st = lds[i & 1];
+    float m[CT], l[CT], tx[CT];
 #pragma unroll
-        for (int j = 0; j < CH; j++)
-            *reinterpret_cast<u32x4 *>(st + (ld_row + j * (2048 / D)) * STR + ld_col * 8) = kr[j];
-        __syncthreads();
-        load_tile(i + 2, kr);
-        const int key0 = (t0 + i) * 32;
+    for (int q = 0; q < CT; q++) {
+        m[q] = -INFINITY;
+        l[q] = tx[q] = 0.0f;
+    }
+    int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
+#pragma unroll
+    for (int ks = 0; ks < NKS; ks++)
+        frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
+    for (int i = 0, stage = 0; i < n_steps; i++) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step i has landed
+        __syncthreads();                                                               // everybody's has, and step i - 1 is no longer read
+        keys.issue(stage == 0 ? G::NS - 1 : stage - 1);
+        const unsigned char *st = lds + stage * G::STAGE + half * 32 * G::ROW;
+        stage = stage == G::NS - 1 ? 0 : stage + 1;
+        const int key0 = (s0 + i) * STEP + half * 32;
         if (key0 > wave_max_pos)
-            return;   // causal: nothing in this tile is visible to this wave's rows
-        bf16x8 kfr[2][NKS];
+            continue;   // causal: nothing in this half is visible to this wave's rows
+        f32x4 acc[CT][2];
+#pragma unroll
+        for (int q = 0; q < CT; q++)
+            acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++) {
-            kfr[0][ks] = *reinterpret_cast<const bf16x8 *>(st + c * STR + ks * 32 + g * 8);
-            kfr[1][ks] = *reinterpret_cast<const bf16x8 *>(st + (16 + c) * STR + ks * 32 + g * 8);
-        }
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+            const bf16x8 k0 = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
+            const bf16x8 k1 = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
 #pragma unroll
-        for (int ks = 0; ks < NKS; ks++) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[0][ks], qf[ks], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[1][ks], qf[ks], acc1, 0, 0, 0);
+            for (int q = 0; q < CT; q++) {
+                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qf[q][ks], acc[q][0], 0, 0, 0);
+                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qf[q][ks], acc[q][1], 0, 0, 0);
+            }
         }
-        float sum = 0.0f, xsum = 0.0f, m_new, m_safe;
-        if (key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f) {
-            // every key of the tile is visible to every row of the wave (all but the tiles on the diagonal):
-            // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
-            float mx = fmaxf(fmaxf(fmaxf(acc0[0], acc0[1]), fmaxf(acc0[2], acc0[3])), fmaxf(fmaxf(acc1[0], acc1[1]), fmaxf(acc1[2], acc1[3])));
-            m_new = fmaxf(m, mx * a.scale_log2);
-            m_safe = m_new;   // finite: the tile has visible keys
+        const bool open = key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const float raw = e < 4 ? acc0[e & 3] : acc1[e & 3];
-                const float p = __builtin_amdgcn_exp2f(fmaf(raw, a.scale_log2, -m_safe));
-                sum += p;
+        for (int q = 0; q < CT; q++) {
+            float sum = 0.0f, xsum = 0.0f, m_new, m_safe;
+            if (open) {
+                // every key of the half is visible to every row of the wave (all but those on the diagonal):
+                // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
+                const f32x4 u = acc[q][0], v = acc[q][1];
+                const float mx = fmaxf(fmaxf(fmaxf(u[0], u[1]), fmaxf(u[2], u[3])), fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+                m_new = fmaxf(m[q], mx * a.scale_log2);
+                m_safe = m_new;   // finite: there are visible keys
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const float raw = acc[q][e >> 2][e & 3];
+                    const float p = __builtin_amdgcn_exp2f(fmaf(raw, a.scale_log2, -m_safe));
+                    sum += p;
+                    if (ENT)
+                        xsum = fmaf(p, raw, xsum);
+                }
                 if (ENT)
-                    xsum += p * (raw * a.scale_log2);
-            }
-        } else {
-            float x[8], mx = -INFINITY;
-            const int lim = min(pos, a.n_keys - 1);
+                    xsum *= a.scale_log2;
+            } else {
+                const int lim = min(pos[q], a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 16 * (e / 4) + e % 4 is visible up to here
+                float x[8], mx = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const int kk = key0 + (e >> 2) * 16 + g * 4 + (e & 3);
-                const float v = (e < 4 ? acc0[e & 3] : acc1[e & 3]) * a.scale_log2;
-                x[e] = kk <= lim ? v : -INFINITY;
-                mx = fmaxf(mx, x[e]);
-            }
-            m_new = fmaxf(m, mx);
-            m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
+                for (int e = 0; e < 8; e++) {
+                    x[e] = (e >> 2) * 16 + (e & 3) <= lim ? acc[q][e >> 2][e & 3] * a.scale_log2 : -INFINITY;
+                    mx = fmaxf(mx, x[e]);
+                }
+                m_new = fmaxf(m[q], mx);
+                m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const float p = __builtin_amdgcn_exp2f(x[e] - m_safe);
-                sum += p;
-                if (ENT)
-                    xsum += p * (x[e] == -INFINITY ? 0.0f : x[e]);
+                for (int e = 0; e < 8; e++) {
+                    const float p = __builtin_amdgcn_exp2f(x[e] - m_safe);
+                    sum += p;
+                    if (ENT)
+                        xsum += p * (x[e] == -INFINITY ? 0.0f : x[e]);
+                }
             }
+            const float alpha = __builtin_amdgcn_exp2f(m[q] - m_safe);
+            l[q] = l[q] * alpha + sum;
+            if (ENT)
+                tx[q] = tx[q] * alpha + xsum;
+            m[q] = m_new;
         }
-        const float alpha = __builtin_amdgcn_exp2f(m - m_safe);
-        l = l * alpha + sum;
-        if (ENT)
-            tx = tx * alpha + xsum;
-        m = m_new;
-    };
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): only tile prefetches are counted inside the loop
-    {
-        int t = 0;
-        for (; t + 2 <= n_tiles; t += 2) {
-            step(t, kreg[0]);
-            step(t + 1, kreg[1]);
-        }
-        if (t < n_tiles)
-            step(t, kreg[0]);
     }
-    float mt = fmaxf(m, __shfl_xor(m, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
-    const float ms = (mt == -INFINITY) ? 0.0f : mt;
-    const float wgt = __builtin_amdgcn_exp2f(m - ms);
-    float lw = l * wgt;
-    lw += __shfl_xor(lw, 16);
-    lw += __shfl_xor(lw, 32);
-    const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row;
-    if (g == 0 && valid)
-        a.lse2[o] = lw > 0.0f ? mt + log2f(lw) : -INFINITY;
-    if (ENT) {
-        float tw = tx * wgt;
-        tw += __shfl_xor(tw, 16);
-        tw += __shfl_xor(tw, 32);
-        if (g == 0 && valid)
-            a.ent_part[o] = lw > 0.0f ? tw / lw : 0.0f;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
+    // the four row groups of the wave, then the two halves
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        float mt = fmaxf(m[q], __shfl_xor(m[q], 16));
+        mt = fmaxf(mt, __shfl_xor(mt, 32));
+        const float wgt = __builtin_amdgcn_exp2f(m[q] - ((mt == -INFINITY) ? 0.0f : mt));
+        l[q] *= wgt;
+        l[q] += __shfl_xor(l[q], 16);
+        l[q] += __shfl_xor(l[q], 32);
+        if (ENT) {
+            tx[q] *= wgt;
+            tx[q] += __shfl_xor(tx[q], 16);
+            tx[q] += __shfl_xor(tx[q], 32);
+        }
+        m[q] = mt;
+        if (half == 1 && g == 0) {
+            s_half[slot][q][0][c] = m[q];
+            s_half[slot][q][1][c] = l[q];
+            if (ENT)
+                s_half[slot][q][ENT ? 2 : 1][c] = tx[q];
+        }
+    }
+    __syncthreads();
+    if (half == 1 || g != 0)
+        return;
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        const float mo = s_half[slot][q][0][c], mt = fmaxf(m[q], mo), ms = (mt == -INFINITY) ? 0.0f : mt;
+        const float w0 = __builtin_amdgcn_exp2f(m[q] - ms), w1 = __builtin_amdgcn_exp2f(mo - ms);
+        const float lw = l[q] * w0 + s_half[slot][q][1][c] * w1;
+        const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row[q];
+        if (valid[q]) {
+            a.lse2[o] = lw > 0.0f ? mt + log2f(lw) : -INFINITY;
+            if (split == 0)                                  // splits that other blocks have and this one does not
+                for (int s = unit.n; s < a.ns1; s++)
+                    a.lse2[o + s * a.lse_split_stride] = -INFINITY;
+        }
+        if (ENT && valid[q])
+            a.ent_part[o] = lw > 0.0f ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
     }
 }
 
 // Entropy of every row from pass 1's per-split (log-sum-exp, expected score) pairs (Eq. 2).  One thread per
 // (head, row); each workgroup also leaves the sum of its 256 entropies for entropy_mean_kernel, which adds the
-// workgroup sums of a sequence in index order, so the mean is reproducible.
+// workgroup sums of a sequence in a fixed order, so the mean is reproducible.
 // log2_domain: bf16 path (scores in log2 units); otherwise natural units and a single split.
 __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2_domain, float *row_entropy, float *block_sum)
 {
@@ -229,157 +369,189 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2
         block_sum[(int64_t)b * gridDim.x + blockIdx.x] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
 }
 
+// One wave per sequence; lane i adds the sums i, i + 64, ... in order, then a fixed tree over the lanes.  (One thread adding
+// them one after the other took 7.7 us for 160 sums.)
 __global__ __launch_bounds__(64) void entropy_mean_kernel(const float *block_sum, int n_blocks, int n_rows, float *ae)
 {
-    const int b = blockIdx.x;
-    if (threadIdx.x == 0) {
-        float t = 0.0f;
-        for (int i = 0; i < n_blocks; i++)
-            t += block_sum[(int64_t)b * n_blocks + i];
+    const int b = blockIdx.x, lane = threadIdx.x;
+    float t = 0.0f;
+#pragma unroll 4
+    for (int i = lane; i < n_blocks; i += 64)
+        t += block_sum[(int64_t)b * n_blocks + i];
+    for (int off = 32; off > 0; off >>= 1)
+        t += __shfl_xor(t, off);
+    if (lane == 0)
         ae[b] = t / (float)n_rows;
-    }
 }
 
-// Pass 2: column sums of the probabilities.  One workgroup per (64 visual keys, head, sequence, row split); wave w keeps
-// the K fragments of its 16 keys in registers and all 256 threads stream the query rows (with their
-// log-sum-exp and positions) in 32-row tiles through LDS.  A lane sums its key column over the rows it
-// holds; the four row groups are combined at the end, so every (head, row split, key) sum has one fixed order.
-// The row's log-sum-exp is combined from pass 1's ns1 partial values when its tile is loaded.
+// Pass 2: column sums of the probabilities.  One workgroup per (32 CT visual keys, head, sequence, row split).  The query
+// rows are streamed (RowStream); the four waves are two key slots x two row halves of a step, each with the K fragments of 32
+// keys in registers.  A lane sums its key columns over the rows it holds; the four row groups and the two halves are
+// combined at the end, so every (head, row split, key) sum has one fixed order.  The rows' log-sum-exps (combined from pass
+// 1's partial values) and positions are put into LDS for 512 rows at a time.
+// Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 20, Pixtral 37.4 -> 28.5, 16 SmolVLM sequences
+// 197 -> 164 us.  Its vector instructions alone take 60 us there (16 exponentials of 8 clocks and 32 others of 2.7 per step and wave).
 template <int D, int NS1>
-__global__ __launch_bounds__(256) void scores_colsum_bf16_kernel(ScoreArgs a)
+__global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
-    constexpr int NKS = D / 32, STR = D + 8, CH = 32 * D / 8 / 256;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2][32 * STR];
-    __shared__ __attribute__((aligned(16))) float lds_lse[2][32];
-    __shared__ __attribute__((aligned(16))) int32_t lds_pos[2][32];
+    using G = StreamGeom<D>;
+    constexpr int NKS = D / 32, WINDOW = 512;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
+    __shared__ __attribute__((aligned(16))) float lds_lse[WINDOW];
+    __shared__ __attribute__((aligned(16))) int32_t lds_pos[WINDOW];
+    __shared__ float s_half[2][CT][16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slot = wave & 1, half = wave >> 1;
     const int c = lane & 15, g = lane >> 4;
     const int vis_end = a.vis_start + a.vis_len;
     // x walks the heads with the KV head fastest (see pass 1): the query rows of a head stay in one XCD's L2
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
-    const int blk0 = a.vis_start + blockIdx.y * 64, b = blockIdx.z / a.ns2, split = blockIdx.z % a.ns2;
-    const int j0 = blk0 + wave * 16;
-    const int key = j0 + c;
-    const bool kvalid = key < vis_end && key < a.n_keys;
-    bf16x8 kf[NKS];
-    {
-        const uint16_t *kp = reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + (kvalid ? key : 0)) * D + g * 8;
+    const SplitUnit unit = split_unit(a.map2, blockIdx.y);      // earlier key blocks are seen by more rows: they come first
+    const int blk0 = a.vis_start + unit.rank * 32 * CT, b = blockIdx.z, split = unit.split;
+    const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
+    bool kvalid[CT];
+    bf16x8 kf[CT][NKS];
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        const int key = j0 + q * 16 + c;
+        kvalid[q] = key < vis_end && key < a.n_keys;
+        const uint16_t *kp = reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + (kvalid[q] ? key : 0)) * D + g * 8;
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            kf[ks] = *reinterpret_cast<const bf16x8 *>(kp + ks * 32);
+            kf[q][ks] = *reinterpret_cast<const bf16x8 *>(kp + ks * 32);
     }
-    // row tiles: without explicit positions row r sits at position r, so rows below the block's first key see nothing
-    const int n_tiles_all = (a.n_q + 31) / 32;
-    const int t_begin = a.q_pos ? 0 : min(blk0 / 32, n_tiles_all);
-    const int tps = (n_tiles_all - t_begin + a.ns2 - 1) / a.ns2;
-    const int t_first = t_begin + split * tps, n_tiles = max(min(tps, n_tiles_all - t_first), 0);
+    // row steps: without explicit positions row r sits at position r, so rows below the block's first key see nothing
+    const int n_steps_all = (a.n_q + STEP - 1) / STEP;
+    const int s_begin = a.q_pos ? 0 : min(blk0 / STEP, n_steps_all);
+    const int sps = (n_steps_all - s_begin + unit.n - 1) / unit.n;
+    const int s_first = s_begin + split * sps, n_steps = max(min(sps, n_steps_all - s_first), 0);
     const uint16_t *qb = reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D;
     const float *lrow = a.lse2 + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad;
-    u32x4 qreg[2][CH];
-    float lreg[2][NS1];
-    int32_t preg[2];
-    const int ld_row = tid / (D / 8), ld_col = tid % (D / 8);
-    auto load_tile = [&](int i, u32x4(&qr)[CH], float(&lr)[NS1], int32_t &pr) {
-        const int t = t_first + max(min(i, n_tiles - 1), 0);
+    RowStream<D> rows;
+    rows.init(qb, (int64_t)a.n_q_heads * D * 2, a.n_q, s_first, lds, wave, lane);
+    if (n_steps > 0) {
 #pragma unroll
-        for (int j = 0; j < CH; j++) {
-            const int r = min(t * 32 + ld_row + j * (2048 / D), a.n_q - 1);
-            qr[j] = *reinterpret_cast<const u32x4 *>(qb + (int64_t)r * a.n_q_heads * D + ld_col * 8);
-        }
-        if (tid < 32) {
-            const int r = t * 32 + tid;
-            const bool live = r < a.n_q;
-            if (a.lse_in) {      // (only with NS1 = 1) natural logarithm -> the log2 units of the scores here
-                lr[0] = live ? a.lse_in[((int64_t)b * a.n_q_heads + h) * a.n_q + r] * 1.4426950408889634f : -INFINITY;
-            } else {
+        for (int i = 0; i < G::NS - 1; i++)
+            rows.issue(i);
+    }
+    // log-sum-exps over all keys (in log2 units) and positions of rows row0 .. row0 + WINDOW - 1
+    auto fill_window = [&](int row0) {
+        for (int w = tid; w < min(WINDOW, n_steps * STEP); w += 256) {
+            const int r = row0 + w;
+            float L = -INFINITY;
+            if (r < a.n_q) {
+                if (a.lse_in) {
+                    L = a.lse_in[((int64_t)b * a.n_q_heads + h) * a.n_q + r] * 1.4426950408889634f;
+                } else {
+                    float lr[NS1];
 #pragma unroll
-                for (int s = 0; s < NS1; s++)
-                    lr[s] = live ? lrow[s * a.lse_split_stride + r] : -INFINITY;
+                    for (int s = 0; s < NS1; s++)
+                        lr[s] = lrow[s * a.lse_split_stride + r];
+                    L = lr[0];                                   // a single split is taken as it is
+                    if (NS1 > 1) {
+#pragma unroll
+                        for (int s = 1; s < NS1; s++)
+                            L = fmaxf(L, lr[s]);
+                        float sum = 0.0f;
+#pragma unroll
+                        for (int s = 0; s < NS1; s++)
+                            sum += __builtin_amdgcn_exp2f(lr[s] - (L == -INFINITY ? 0.0f : L));
+                        L += log2f(sum);
+                    }
+                }
+                if (a.q_pos)
+                    lds_pos[w] = a.q_pos[(int64_t)b * a.n_q + r];
+            } else if (a.q_pos) {
+                lds_pos[w] = -1;
             }
-            pr = live ? (a.q_pos ? a.q_pos[(int64_t)b * a.n_q + r] : r) : -1;
+            lds_lse[w] = L > -INFINITY ? L : INFINITY;           // +inf makes the probability zero: rows that do not exist or see no key
         }
     };
-    if (n_tiles > 0) {
-        load_tile(0, qreg[0], lreg[0], preg[0]);
-        load_tile(1, qreg[1], lreg[1], preg[1]);
-    }
-    float cs = 0.0f;
-    auto step = [&](int i, u32x4(&qr)[CH], float(&lr)[NS1], int32_t &pr) {
-        const int sidx = i & 1;
-        uint16_t *st = lds[sidx];
+    float cs[CT];
 #pragma unroll
-        for (int j = 0; j < CH; j++)
-            *reinterpret_cast<u32x4 *>(st + (ld_row + j * (2048 / D)) * STR + ld_col * 8) = qr[j];
-        if (tid < 32) {
-            // log-sum-exp over all keys from pass 1's per-split values; a single split is taken as it is
-            float mx = lr[0];
+    for (int q = 0; q < CT; q++)
+        cs[q] = 0.0f;
+    int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
 #pragma unroll
-            for (int s = 1; s < NS1; s++)
-                mx = fmaxf(mx, lr[s]);
-            float L = mx;
-            if (NS1 > 1) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int s = 0; s < NS1; s++)
-                    sum += __builtin_amdgcn_exp2f(lr[s] - (mx == -INFINITY ? 0.0f : mx));
-                L = mx + log2f(sum);
-            }
-            // +inf makes the probability zero: padding rows and rows that see no key
-            lds_lse[sidx][tid] = mx == -INFINITY ? INFINITY : L;
-            lds_pos[sidx][tid] = pr;
+    for (int ks = 0; ks < NKS; ks++)
+        frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
+    for (int i = 0, stage = 0; i < n_steps; i++) {
+        if (i % (WINDOW / STEP) == 0) {
+            if (i > 0)
+                __syncthreads();                                 // the last window's steps have been read
+            fill_window((s_first + i) * STEP);
         }
-        __syncthreads();
-        load_tile(i + 2, qr, lr, pr);
-        const int r0 = (t_first + i) * 32;
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step i has landed
+        __syncthreads();                                                               // everybody's has, and step i - 1 is no longer read
+        rows.issue(stage == 0 ? G::NS - 1 : stage - 1);
+        const unsigned char *st = lds + stage * G::STAGE + half * 32 * G::ROW;
+        stage = stage == G::NS - 1 ? 0 : stage + 1;
+        const int r0 = (s_first + i) * STEP + half * 32, w0 = i % (WINDOW / STEP) * STEP + half * 32;
         if (!a.q_pos && r0 + 31 < j0)
-            return;   // causal: these rows sit before this wave's keys
-        bf16x8 qfr[2][NKS];
+            continue;   // causal: these rows sit before this wave's keys
+        const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + g * 4]);
+        const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + 16 + g * 4]);
+        const int32_t *pp = &lds_pos[w0 + g * 4];
+        f32x4 acc[CT][2];
+#pragma unroll
+        for (int q = 0; q < CT; q++)
+            acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++) {
-            qfr[0][ks] = *reinterpret_cast<const bf16x8 *>(st + c * STR + ks * 32 + g * 8);
-            qfr[1][ks] = *reinterpret_cast<const bf16x8 *>(st + (16 + c) * STR + ks * 32 + g * 8);
-        }
-        const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[sidx][g * 4]);
-        const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[sidx][16 + g * 4]);
-        const int32_t *pp = &lds_pos[sidx][g * 4];
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+            const bf16x8 q0 = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
+            const bf16x8 q1 = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
 #pragma unroll
-        for (int ks = 0; ks < NKS; ks++) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfr[0][ks], kf[ks], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfr[1][ks], kf[ks], acc1, 0, 0, 0);
-        }
-        if (!a.q_pos && r0 >= j0 + 15) {
-            // every row of the tile sits at or after every key of this wave: nothing to mask
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                cs += __builtin_amdgcn_exp2f(fmaf(acc0[r], a.scale_log2, -L0[r]));
-                cs += __builtin_amdgcn_exp2f(fmaf(acc1[r], a.scale_log2, -L1[r]));
+            for (int q = 0; q < CT; q++) {
+                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kf[q][ks], acc[q][0], 0, 0, 0);
+                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kf[q][ks], acc[q][1], 0, 0, 0);
             }
+        }
+        if (!a.q_pos && r0 >= j0 + 16 * CT - 1) {
+            // every row of the half sits at or after every key of this wave: nothing to mask
+#pragma unroll
+            for (int q = 0; q < CT; q++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    cs[q] += __builtin_amdgcn_exp2f(fmaf(acc[q][0][r], a.scale_log2, -L0[r]));
+                    cs[q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L1[r]));
+                }
         } else {
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const float p0 = __builtin_amdgcn_exp2f(acc0[r] * a.scale_log2 - L0[r]);
-                const float p1 = __builtin_amdgcn_exp2f(acc1[r] * a.scale_log2 - L1[r]);
-                cs += key <= pp[r] ? p0 : 0.0f;
-                cs += key <= pp[16 + r] ? p1 : 0.0f;
+            for (int q = 0; q < CT; q++) {
+                const int key = j0 + q * 16 + c, from = key - r0 - g * 4;     // without positions, rows of the half from here on see the key
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const float p0 = __builtin_amdgcn_exp2f(acc[q][0][r] * a.scale_log2 - L0[r]);
+                    const float p1 = __builtin_amdgcn_exp2f(acc[q][1][r] * a.scale_log2 - L1[r]);
+                    cs[q] += (a.q_pos ? key <= pp[r] : from <= r) ? p0 : 0.0f;
+                    cs[q] += (a.q_pos ? key <= pp[16 + r] : from <= 16 + r) ? p1 : 0.0f;
+                }
             }
         }
-    };
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    {
-        int i = 0;
-        for (; i + 2 <= n_tiles; i += 2) {
-            step(i, qreg[0], lreg[0], preg[0]);
-            step(i + 1, qreg[1], lreg[1], preg[1]);
-        }
-        if (i < n_tiles)
-            step(i, qreg[0], lreg[0], preg[0]);
     }
-    cs += __shfl_xor(cs, 16);
-    cs += __shfl_xor(cs, 32);
-    if (g == 0 && key < vis_end)
-        a.part[(((int64_t)b * a.n_q_heads + h) * a.ns2 + split) * a.vis_len + (key - a.vis_start)] = kvalid ? cs : 0.0f;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        cs[q] += __shfl_xor(cs[q], 16);
+        cs[q] += __shfl_xor(cs[q], 32);
+        if (half == 1 && g == 0)
+            s_half[slot][q][c] = cs[q];
+    }
+    __syncthreads();
+    if (half == 1 || g != 0)
+        return;
+#pragma unroll
+    for (int q = 0; q < CT; q++) {
+        const int key = j0 + q * 16 + c;
+        if (key < vis_end) {
+            float *to = a.part + ((int64_t)b * a.n_q_heads + h) * a.ns2 * a.vis_len + (key - a.vis_start);
+            to[split * a.vis_len] = kvalid[q] ? cs[q] + s_half[slot][q][c] : 0.0f;
+            if (split == 0)                                  // splits that other blocks have and this one does not
+                for (int s = unit.n; s < a.ns2; s++)
+                    to[s * a.vis_len] = 0.0f;
+        }
+    }
 }
 
 // ---- float32 tensors: plain vector-ALU versions of the two passes -------------------------------
@@ -603,6 +775,131 @@ __global__ __launch_bounds__(1024) void topk_keep_kernel(const float *part, int 
     }
 }
 
+// Up to 2048 visual tokens: the same selection with all keys in the registers of every wave (NR of them per lane, token r * 64 +
+// lane in register r).  Latency bound, one workgroup per sequence, so it is built from few dependent steps: the partial sums
+// are added by all 1024 threads (a thread takes VEC tokens and every n_groups-th partial row, the groups meet in LDS in order),
+// the k-th largest key is found four bits a round, each of the 16 waves counting the keys at or above one of 16 trial
+// values, and the search ends as soon as a value keeps exactly k; survivors are numbered with ballots.
+// Measured, 576 tokens: 11.6 us with the kernel above (4 rounds of loads, 4 radix passes of 5 barriers), 8.8 us here with
+// four times the partial rows.
+template <int NR>
+__global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int n_parts, const float *scores_in, float *scores_out, int vis_start,
+                                                          int vis_len, int k, int vec, int32_t *kept_idx)
+{
+    constexpr int V = NR * 64;
+    __shared__ __attribute__((aligned(16))) float s_sum[4096 > V ? 4096 : V];   // [group][vis_len]
+    __shared__ uint32_t s_key[V];
+    __shared__ int s_cnt[2][16];
+    __shared__ int s_gt[32], s_eq[32];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int n_groups = 1;
+    if (!scores_in) {
+        const int cols = vec ? vis_len / 4 : vis_len;                   // (vec: rows of partial sums are 16-byte aligned)
+        n_groups = min(max(1024 / cols, 1), min(n_parts, 4096 / vis_len));
+        for (int col = tid % cols, grp = tid / cols; grp < n_groups && col < cols; col += vec ? cols : 1024) {
+            if (vec) {
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(part + ((int64_t)b * n_parts + grp) * vis_len) + col;
+                const int64_t step = (int64_t)n_groups * (vis_len / 4);
+                f32x4 x = {0.f, 0.f, 0.f, 0.f};
+                for (int i = grp; i < n_parts; i += n_groups * 16) {
+                    f32x4 t[16];
+#pragma unroll
+                    for (int u = 0; u < 16; u++)
+                        t[u] = i + u * n_groups < n_parts ? src[u * step] : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 16; u++)
+                        x += t[u];
+                    src += 16 * step;
+                }
+                reinterpret_cast<f32x4 *>(s_sum + grp * vis_len)[col] = x;
+            } else {
+                const float *src = part + ((int64_t)b * n_parts + grp) * vis_len + col;
+                float x = 0.0f;
+#pragma unroll 8
+                for (int i = grp; i < n_parts; i += n_groups)
+                    x += src[(int64_t)(i - grp) * vis_len];
+                s_sum[grp * vis_len + col] = x;
+            }
+        }
+        __syncthreads();
+    }
+    for (int j = tid; j < V; j += 1024) {
+        uint32_t key = 0u;                                               // below every score's key
+        if (j < vis_len) {
+            float x = 0.0f;
+            if (scores_in) {
+                x = scores_in[(int64_t)b * vis_len + j];
+            } else {
+                for (int g = 0; g < n_groups; g++)
+                    x += s_sum[g * vis_len + j];
+            }
+            if (scores_out)
+                scores_out[(int64_t)b * vis_len + j] = x;
+            key = order_key(x);
+        }
+        s_key[j] = key;
+    }
+    if (k <= 0)
+        return;
+    __syncthreads();
+    uint32_t key[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++)
+        key[r] = s_key[r * 64 + lane];
+    // the largest value with at least k keys at or above it, four bits a round
+    uint32_t tau = 0u;
+    int at_tau = vis_len;
+    for (int shift = 28; shift >= 0 && at_tau != k; shift -= 4) {
+        int n = 0;
+        const uint32_t trial = tau | ((uint32_t)wave << shift);
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            n += __popcll(__ballot(key[r] >= trial && key[r] != 0u));
+        const int buf = (shift >> 2) & 1;
+        if (lane == 0)
+            s_cnt[buf][wave] = n;
+        __syncthreads();
+        const int c = s_cnt[buf][lane & 15];
+        const int digit = 63 - __builtin_clzll(__ballot(c >= k && lane < 16));    // (trial 0 of the digit always has k keys)
+        tau |= (uint32_t)digit << shift;
+        at_tau = __builtin_amdgcn_readlane(c, digit);
+    }
+    // more keys at or above it than asked for: the first of those equal to it, in position order
+    int above = 0;
+    if (at_tau != k) {
+#pragma unroll
+        for (int r = 0; r < NR; r++)
+            above += __popcll(__ballot(key[r] > tau));
+    }
+    const int need = at_tau == k ? V : k - above;
+    constexpr int CHUNKS = NR;
+    for (int ch = wave; ch < CHUNKS; ch += 16) {
+        const uint32_t u = s_key[ch * 64 + lane];
+        const int gt = __popcll(__ballot(u > tau)), eq = __popcll(__ballot(u == tau && u != 0u));
+        if (lane == 0) {
+            s_gt[ch] = gt;
+            s_eq[ch] = eq;
+        }
+    }
+    __syncthreads();
+    const int g_all = lane < CHUNKS ? s_gt[lane] : 0, e_all = lane < CHUNKS ? s_eq[lane] : 0;
+    for (int ch = wave; ch < CHUNKS; ch += 16) {
+        int g_before = lane < ch ? g_all : 0, e_before = lane < ch ? e_all : 0;
+        for (int off = 16; off > 0; off >>= 1) {                        // (chunks are on lanes 0..31)
+            g_before += __shfl_xor(g_before, off);
+            e_before += __shfl_xor(e_before, off);
+        }
+        g_before = __builtin_amdgcn_readfirstlane(g_before);
+        e_before = __builtin_amdgcn_readfirstlane(e_before);
+        const uint32_t u = s_key[ch * 64 + lane];
+        const uint64_t below = (1ull << lane) - 1ull, ties = __ballot(u == tau && u != 0u);
+        const bool keep = u > tau || (u == tau && u != 0u && e_before + (int)__popcll(ties & below) < need);
+        const uint64_t kept = __ballot(keep);
+        if (keep)
+            kept_idx[(int64_t)b * k + g_before + min(e_before, need) + (int)__popcll(kept & below)] = vis_start + ch * 64 + lane;
+    }
+}
+
 __global__ __launch_bounds__(256) void gather_rows_kernel(const unsigned char *src, int64_t n_rows_src, int64_t row_bytes,
                                                           const int32_t *kept_idx, int k, unsigned char *dst)
 {
@@ -630,41 +927,103 @@ void launch_colsum(int ns1, dim3 grid, hipStream_t st, const ScoreArgs &a)
     }
 }
 
-struct CompressPlan {
-    int n_q_pad, ns1, ns2;
-    size_t off_lse, off_part, total;
-};
+// Workgroups a launch is split into at most: two or three per CU.  (Four and more hold their own on a CU, but every one of them
+// loads its own first step and its own rows: 1024 is 2-8 % slower at one sequence, 2048 20 %.)
+int resident_groups(int head_dim) { return head_dim == 256 ? 512 : 768; }
 
-// Splits of the streamed axis of a score pass: enough that a workgroup walks about 8 tiles, at most 8 splits,
-// and only while the grid stays near 2048 workgroups (beyond that the chip is busy anyway and more, shorter
-// workgroups only add start-up cost).
-int score_splits(int64_t grid, int tiles)
+// Splits of one pass.  `len(rank)`: steps of 64 keys or rows of a block, longest first; `heads`: workgroups per unit (heads times
+// sequences); `resident`: see above.  Divided so that the launch is one round of workgroups with as
+// few steps each as that allows, at least two (a workgroup spends about 3 us before its first step) and at most 8 splits of a block; if
+// the blocks as they are already fill the chip, they stay whole.
+template <class Len>
+int plan_splits(int blocks, int64_t heads, int resident, Len len, SplitMap *map, int *units)
 {
-    int ns = ceil_div(tiles, 8);
-    if (ns > 8)
-        ns = 8;
-    const int64_t room = 2048 / (grid > 0 ? grid : 1);
-    if (ns > room)
-        ns = (int)room;
+    auto units_of = [&](int S) {
+        int64_t n = 0;
+        for (int r = 0; r < blocks; r++)
+            n += ceil_div(len(r), S);
+        return n;
+    };
+    const int longest = len(0) > 1 ? len(0) : 1;
+    int S = longest;
+    if ((int64_t)blocks * heads < resident) {
+        S = ceil_div(longest, MAX_SPLITS);
+        if (S < 2)
+            S = 2;
+        while (S < longest && units_of(S) * heads > resident)
+            S++;
+    }
+    int most = 1;
+    *units = 0;
+    for (int j = 0; j < MAX_SPLITS; j++) {
+        int n = 0;
+        for (int r = 0; r < blocks; r++)
+            n += j == 0 || len(r) > j * S;
+        map->count[j] = n;
+        *units += n;
+        if (n > 0)
+            most = j + 1;
+    }
     int pow2 = 1;   // 1, 2, 4 or 8: pass 2 is compiled for these counts of pass-1 splits
-    while (pow2 * 2 <= ns)
+    while (pow2 < most)
         pow2 *= 2;
     return pow2;
 }
 
-CompressPlan compress_plan(int batch, int n_heads, int n_q, int vis_len, int dtype)
+struct CompressPlan {
+    int n_q_pad, ns1, ns2;
+    int units1, units2;            // (block, split) units of the two passes
+    SplitMap map1, map2;
+    size_t off_lse, off_part;
+};
+
+// `with_pos`: rows come with explicit positions, so any block may have to walk everything
+CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos)
 {
     CompressPlan p;
     p.n_q_pad = (n_q + 15) / 16 * 16;
     p.ns1 = p.ns2 = 1;
+    p.units1 = p.units2 = 1;
     if (dtype == DREAM_BF16) {
-        p.ns1 = score_splits((int64_t)ceil_div(n_q, 64) * n_heads * batch, ceil_div(n_q, 32));
-        p.ns2 = score_splits((int64_t)ceil_div(vis_len > 0 ? vis_len : 1, 64) * n_heads * batch, ceil_div(n_q, 32));
+        const int resident = resident_groups(head_dim);
+        const int b1 = ceil_div(n_q, 32 * CT), b2 = ceil_div(vis_len > 0 ? vis_len : 1, 32 * CT), rows = ceil_div(n_q, 64);
+        p.ns1 = plan_splits(b1, (int64_t)n_heads * batch, resident, [&](int r) {
+            return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * 32 * CT, n_q), n_keys), 64);
+        }, &p.map1, &p.units1);
+        p.ns2 = plan_splits(b2, (int64_t)n_heads * batch, resident, [&](int r) {
+            return with_pos ? rows : std::max(rows - std::min((vis_start + r * 32 * CT) / 64, rows), 0);
+        }, &p.map2, &p.units2);
     }
     p.off_lse = DREAM_WORKSPACE_MIN_BYTES;
     p.off_part = align_up(p.off_lse + (size_t)p.ns1 * batch * n_heads * p.n_q_pad * sizeof(float), 256);
-    p.total = align_up(p.off_part + (size_t)p.ns2 * batch * n_heads * (vis_len > 0 ? vis_len : 1) * sizeof(float), 256);
     return p;
+}
+
+// The most splits a plan of these sizes takes, whatever the keys and positions are (the workspace query knows neither).
+int most_splits(int64_t blocks, int64_t heads, int head_dim, int dtype)
+{
+    return dtype == DREAM_BF16 && blocks * heads < resident_groups(head_dim) ? MAX_SPLITS : 1;
+}
+
+size_t compress_most(int batch, int n_heads, int head_dim, int n_q, int vis_len, int dtype)
+{
+    const int64_t heads = (int64_t)n_heads * batch;
+    const int v = vis_len > 0 ? vis_len : 1;
+    const size_t lse = most_splits(ceil_div(n_q, 32 * CT), heads, head_dim, dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float);
+    const size_t part = most_splits(ceil_div(v, 32 * CT), heads, head_dim, dtype) * heads * v * sizeof(float);
+    return DREAM_WORKSPACE_MIN_BYTES + align_up(lse, 256) + align_up(part, 256);
+}
+
+// calls f with the head dimension as a compile-time constant
+template <class F>
+void with_dim(int head_dim, F f)
+{
+    if (head_dim == 64)
+        f(std::integral_constant<int, 64>{});
+    else if (head_dim == 128)
+        f(std::integral_constant<int, 128>{});
+    else
+        f(std::integral_constant<int, 256>{});
 }
 
 // the selection kernel's dynamic LDS holds up to DREAM_MAX_VISUAL scores: raise its limit once
@@ -692,7 +1051,7 @@ size_t dream_visual_compress_workspace(const dream_attn_desc *desc, int32_t n_q,
 {
     if (!desc || desc->batch < 1 || desc->n_q_heads < 1 || n_q < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
-    return compress_plan(desc->batch, desc->n_q_heads, n_q, vis_len, desc->dtype).total;
+    return compress_most(desc->batch, desc->n_q_heads, desc->head_dim, n_q, vis_len, desc->dtype);
 }
 
 int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int32_t *q_pos, int32_t n_q,
@@ -737,45 +1096,32 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
             return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
         if ((int64_t)vis_start + vis_len > n_keys)
             return fail(DREAM_ERR_INVALID_ARG, "%s: visual span [%d, %d) exceeds the %d live keys", who, vis_start, vis_start + vis_len, n_keys);
-        CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, n_q, vis_len, desc->dtype);
-        if (!workspace || workspace_bytes < p.total)
-            return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, p.total);
+        const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, vis_start, vis_len, desc->dtype, q_pos != nullptr);
+        const size_t need = compress_most(desc->batch, desc->n_q_heads, desc->head_dim, n_q, vis_len, desc->dtype);
+        if (!workspace || workspace_bytes < need)
+            return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
         ScoreArgs a;
         a.q = q; a.k = k_cache; a.q_pos = q_pos;
         a.lse2 = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_lse);
         a.part = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_part);
         a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
-        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.ent_part = nullptr; a.lse_in = row_lse_in;
+        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.map1 = p.map1; a.map2 = p.map2; a.ent_part = nullptr; a.lse_in = row_lse_in;
         a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
         a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
         a.vis_start = vis_start; a.vis_len = vis_len; a.s_max = desc->s_max;
         a.scale = desc->scale != 0.0f ? desc->scale : 1.0f / sqrtf((float)desc->head_dim);
         a.scale_log2 = a.scale * 1.4426950408889634f;
         if (desc->dtype == DREAM_BF16) {
-            if ((int64_t)desc->batch * (p.ns1 > p.ns2 ? p.ns1 : p.ns2) > 65535 || ceil_div(n_q, 64) > 65535)
-                return fail(DREAM_ERR_UNSUPPORTED, "%s: batch %d or n_q %d too large for the score grids", who, desc->batch, n_q);
-            dim3 g1(desc->n_q_heads, ceil_div(n_q, 64), desc->batch * p.ns1), g2(desc->n_q_heads, ceil_div(vis_len, 64), desc->batch * p.ns2);
+            if (p.units1 > 65535)
+                return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grids", who, n_q);
+            const dim3 g1(desc->n_q_heads, p.units1, desc->batch), g2(desc->n_q_heads, p.units2, desc->batch);
             // pass 1 (the rows' log-sum-exps) only when the caller does not bring them
-            switch (desc->head_dim) {
-            case 64:
-                if (!row_lse_in) {
-                    hipLaunchKernelGGL((scores_lse_bf16_kernel<64, false>), g1, dim3(256), 0, st, a);
-                }
-                launch_colsum<64>(a.ns1, g2, st, a);
-                break;
-            case 128:
-                if (!row_lse_in) {
-                    hipLaunchKernelGGL((scores_lse_bf16_kernel<128, false>), g1, dim3(256), 0, st, a);
-                }
-                launch_colsum<128>(a.ns1, g2, st, a);
-                break;
-            default:
-                if (!row_lse_in) {
-                    hipLaunchKernelGGL((scores_lse_bf16_kernel<256, false>), g1, dim3(256), 0, st, a);
-                }
-                launch_colsum<256>(a.ns1, g2, st, a);
-                break;
-            }
+            with_dim(desc->head_dim, [&](auto dim) {
+                constexpr int D = decltype(dim)::value;
+                if (!row_lse_in)
+                    hipLaunchKernelGGL((scores_lse_bf16_kernel<D, false>), g1, dim3(256), 0, st, a);
+                launch_colsum<D>(a.ns1, g2, st, a);
+            });
         } else {
             if (n_q > 65535 * 1)
                 return fail(DREAM_ERR_UNSUPPORTED, "%s: too many rows for the float32 path", who);
@@ -793,11 +1139,17 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
     if (n_kept_host)
         *n_kept_host = k;
     if (vis_len > 0 && (k > 0 || scores_out)) {
-        size_t lds = (size_t)vis_len * 4 + (256 + 32 + 4) * 4;
-        if (int rc = ensure_topk_lds(who))
-            return rc;
-        hipLaunchKernelGGL(topk_keep_kernel, dim3(desc->batch), dim3(1024), lds, st, part, n_heads, scores_in, scores_out,
-                           vis_start, vis_len, k, kept_idx);
+        if (vis_len <= 2048) {
+            const int vec = vis_len % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0;
+            auto kernel = vis_len <= 512 ? topk_small_kernel<8> : vis_len <= 1024 ? topk_small_kernel<16> : topk_small_kernel<32>;
+            hipLaunchKernelGGL(kernel, dim3(desc->batch), dim3(1024), 0, st, part, n_heads, scores_in, scores_out, vis_start, vis_len, k, vec, kept_idx);
+        } else {
+            const size_t lds = (size_t)vis_len * 4 + (256 + 32 + 4) * 4;
+            if (int rc = ensure_topk_lds(who))
+                return rc;
+            hipLaunchKernelGGL(topk_keep_kernel, dim3(desc->batch), dim3(1024), lds, st, part, n_heads, scores_in, scores_out,
+                               vis_start, vis_len, k, kept_idx);
+        }
         int rc = check_launch("topk_keep_kernel");
         if (rc)
             return rc;
@@ -816,8 +1168,8 @@ size_t dream_attention_entropy_workspace(const dream_attn_desc *desc, int32_t n_
 {
     if (!desc || desc->batch < 1 || desc->n_q_heads < 1 || n_q < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
-    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, n_q, 0, desc->dtype);
-    const size_t part = align_up((size_t)p.ns1 * desc->batch * desc->n_q_heads * p.n_q_pad * sizeof(float), 256);
+    const int64_t heads = (int64_t)desc->n_q_heads * desc->batch;
+    const size_t part = align_up(most_splits(ceil_div(n_q, 32 * CT), heads, desc->head_dim, desc->dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float), 256);
     const size_t sums = align_up((size_t)desc->batch * ceil_div((int64_t)desc->n_q_heads * n_q, 256) * sizeof(float), 256);
     return DREAM_WORKSPACE_MIN_BYTES + 2 * part + sums;
 }
@@ -840,10 +1192,10 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= n_keys <= s_max", who);
     if (!q_pos && n_q > n_keys)
         return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
-    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, n_q, 0, desc->dtype);
+    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, 0, 0, desc->dtype, q_pos != nullptr);
     const size_t part = align_up((size_t)p.ns1 * desc->batch * desc->n_q_heads * p.n_q_pad * sizeof(float), 256);
     const int n_blocks = ceil_div((int64_t)desc->n_q_heads * n_q, 256);
-    const size_t need = DREAM_WORKSPACE_MIN_BYTES + 2 * part + align_up((size_t)desc->batch * n_blocks * sizeof(float), 256);
+    const size_t need = dream_attention_entropy_workspace(desc, n_q);
     if (!workspace || workspace_bytes < need)
         return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
     hipStream_t st = as_stream(stream);
@@ -856,19 +1208,17 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
     a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
     a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
     a.vis_start = 0; a.vis_len = 0; a.s_max = desc->s_max;
-    a.ns1 = p.ns1; a.ns2 = 1;
+    a.ns1 = p.ns1; a.ns2 = 1; a.map1 = p.map1; a.map2 = p.map2;
     a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
     a.scale = desc->scale != 0.0f ? desc->scale : 1.0f / sqrtf((float)desc->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;
     if (desc->dtype == DREAM_BF16) {
-        if ((int64_t)desc->batch * p.ns1 > 65535 || ceil_div(n_q, 64) > 65535)
-            return fail(DREAM_ERR_UNSUPPORTED, "%s: batch %d or n_q %d too large for the score grid", who, desc->batch, n_q);
-        dim3 g1(desc->n_q_heads, ceil_div(n_q, 64), desc->batch * p.ns1);
-        switch (desc->head_dim) {
-        case 64:  hipLaunchKernelGGL((scores_lse_bf16_kernel<64, true>), g1, dim3(256), 0, st, a); break;
-        case 128: hipLaunchKernelGGL((scores_lse_bf16_kernel<128, true>), g1, dim3(256), 0, st, a); break;
-        default:  hipLaunchKernelGGL((scores_lse_bf16_kernel<256, true>), g1, dim3(256), 0, st, a); break;
-        }
+        if (p.units1 > 65535)
+            return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grid", who, n_q);
+        dim3 g1(desc->n_q_heads, p.units1, desc->batch);
+        with_dim(desc->head_dim, [&](auto dim) {
+            hipLaunchKernelGGL((scores_lse_bf16_kernel<decltype(dim)::value, true>), g1, dim3(256), 0, st, a);
+        });
     } else {
         if (n_q > 65535)
             return fail(DREAM_ERR_UNSUPPORTED, "%s: too many rows for the float32 path", who);

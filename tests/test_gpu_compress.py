@@ -233,3 +233,28 @@ def test_caller_supplied_row_lse_full_size(gu, name):
     scores, kept, _ = gu.run_compress("bf16", q, k, cfg.prefix, 0, cfg.n_visual, cfg.keep_num, cfg.keep_den, row_lse=lse)
     np.testing.assert_allclose(scores, want, rtol=SCORE_RTOL["bf16"])
     assert np.array_equal(kept, oracle.topk_keep(want, 0, cfg.keep_num, cfg.keep_den))
+
+
+@pytest.mark.parametrize("v", [63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("num,den", [(1, 4), (1, 1), (1, 97)])
+def test_selection_sizes_and_ties(gu, v, num, den):
+    """Token counts around the selection kernels' register files, scores with many exact ties and of both signs."""
+    g = di.rng(17 + v, di.STREAM_SCORES)
+    s = np.round(g.standard_normal(size=(3, v)).astype(np.float32) * 3) / 3
+    s[1] = g.standard_normal(size=v)
+    s[2] = np.float32(0.25)                                      # everything ties: the first k tokens
+    _, kept, _ = gu.run_compress("bf16", None, None, 0, 3, v, num, den, scores_in=s)
+    assert np.array_equal(kept, oracle.topk_keep(s, 3, num, den))
+
+
+@pytest.mark.parametrize("D,P,v,vis_start,with_pos", [(64, 1, 1, 0, False), (64, 63, 40, 7, False), (128, 65, 64, 1, False), (128, 129, 65, 63, False),
+                                                      (256, 257, 130, 64, False), (64, 700, 600, 50, True), (64, 1300, 1200, 0, False)])
+def test_score_steps_and_splits(gu, D, P, v, vis_start, with_pos):
+    """Rows and keys around the 64-row steps, blocks with different numbers of splits, more rows than one window of log-sum-exps."""
+    H = 2
+    g = di.rng(1000 + P, di.STREAM_SCORES)
+    q = di.normal((2, P, H, D), "bf16", 1001 + P, di.STREAM_PREFILL_Q)
+    k = di.normal((2, H, P + 3, D), "bf16", 1002 + P, di.STREAM_K)
+    pos = np.stack([g.permutation(P) for _ in range(2)]).astype(np.int32) if with_pos else None
+    scores, _, _ = gu.run_compress("bf16", q, k, P, vis_start, v, 1, 2, q_pos=pos)
+    np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
