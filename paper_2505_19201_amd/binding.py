@@ -1,8 +1,9 @@
-"""ctypes binding of libdream.so: same names and argument order as include/dream.h.
+"""Binding of libdream.so: same names and argument order as include/dream.h.
 
 Device buffers are torch tensors (only their data_ptr() crosses the boundary); sizes are Python
 ints; `stream` is a torch.cuda.Stream or None (= torch's current stream).  Every wrapper raises
-DreamError on a non-zero status.  Nothing is computed here.
+DreamError on a non-zero status.  Nothing is computed here.  The calls that work on tensors go through the
+extension built from csrc/call.cpp, the host-only ones through ctypes.
 """
 from __future__ import annotations
 
@@ -29,23 +30,6 @@ EXPORTED_SYMBOLS = (
 )
 
 
-# Argument types of the entry points a decode round calls (p pointer, i int32, l int64, z size_t, f float): with them
-# ctypes converts plain Python ints, which costs a fraction of building a ctypes object for every argument of every call.
-_KIND = {"p": C.c_void_p, "i": C.c_int32, "l": C.c_int64, "z": C.c_size_t, "f": C.c_float}
-_ARGUMENTS = {
-    "dream_tree_verify_attn": "ppppp" "i" "pp" "l" "ppp" "z" "p",
-    "dream_draft_xattn": "ppppp" "i" "p" "i" "p" "l" "pp" "z" "p",
-    "dream_visual_compress": "ppp" "i" "p" "iiiii" "ppppp" "p" "l" "p" "l" "p" "z" "p",
-    "dream_accept_path": "p" "iiii" "pp" "i" "ppppp" "z" "p",
-    "dream_accept_path_static": "p" "iiii" "pp" "i" "pppp" "p",
-    "dream_kv_commit": "pp" "i" "p" "i" "p" "i" "ppp",
-    "dream_project_rows": "pp" "ii" "p" "i" "pppp",
-    "dream_project_rows_multi": "pp" "iii" "p",
-    "dream_spec_accept": "pp" "iiii" "pppp" "i" "f" "pppp" "z" "p",
-    "dream_attention_entropy": "ppp" "i" "p" "i" "ppp" "z" "p",
-    "dream_tree_expand_level": "p" "iiii" "p" "i" "pppp" "z" "p",
-    "dream_tree_finalize": "ppp" "iii" "ppppp",
-}
 _raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch.cuda.current_device
 
@@ -92,10 +76,21 @@ def load() -> C.CDLL:
         lib.dream_set_q_tiles.restype = None
         lib.dream_set_tile_waves.restype = None
         lib.dream_set_accept_spin.restype = None
-        for name, kinds in _ARGUMENTS.items():
-            getattr(lib, name).argtypes = [_KIND[c] for c in kinds]
         _lib = lib
     return _lib
+
+
+_call = None
+
+
+def _native():
+    """The extension that converts arguments and calls the library (built with it)."""
+    global _call
+    if _call is None:
+        load()
+        from . import _call as module
+        _call = module
+    return _call
 
 
 def _dev(t: Optional[torch.Tensor]):
@@ -180,10 +175,8 @@ def dream_tree_verify_attn_workspace(desc: AttnDesc, n_tree: int, max_kv_len: in
 
 def dream_tree_verify_attn(desc: AttnDesc, q, k_cache, v_cache, prefix_len, n_tree: int, parent, tree_mask,
                            max_kv_len: int, out, lse, workspace, stream=None) -> None:
-    _check(load().dream_tree_verify_attn(C.byref(desc), _dev(q), _dev(k_cache), _dev(v_cache), _dev(prefix_len),
-                                         n_tree, _dev(parent), _dev(tree_mask), max_kv_len,
-                                         _dev(out), _dev(lse), _dev(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native().dream_tree_verify_attn(desc, q, k_cache, v_cache, prefix_len, n_tree, parent, tree_mask, max_kv_len, out, lse,
+                                            workspace, workspace, _stream(stream)))
 
 
 def dream_draft_xattn_workspace(desc: AttnDesc, n_q: int, max_kv_len: int) -> int:
@@ -192,10 +185,8 @@ def dream_draft_xattn_workspace(desc: AttnDesc, n_q: int, max_kv_len: int) -> in
 
 def dream_draft_xattn(desc: AttnDesc, q, kx_cache, vx_cache, prefix_len, n_tree: int, parent, n_q: int, q_node,
                       max_kv_len: int, out, workspace, stream=None) -> None:
-    _check(load().dream_draft_xattn(C.byref(desc), _dev(q), _dev(kx_cache), _dev(vx_cache), _dev(prefix_len),
-                                    n_tree, _dev(parent), n_q, _dev(q_node),
-                                    max_kv_len, _dev(out), _dev(workspace),
-                                    workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native().dream_draft_xattn(desc, q, kx_cache, vx_cache, prefix_len, n_tree, parent, n_q, q_node, max_kv_len, out, workspace,
+                                       workspace, _stream(stream)))
 
 
 def dream_visual_compress_workspace(desc: AttnDesc, n_q: int, vis_len: int) -> int:
@@ -207,12 +198,9 @@ def dream_visual_compress(desc: AttnDesc, q, q_pos, n_q: int, k_cache, n_keys: i
                           gather_dst, row_elems: int, workspace, stream=None, row_lse_in=None) -> int:
     """Returns k, the kept count the library reports through its host out-parameter."""
     n_kept = C.c_int32(-1)
-    _check(load().dream_visual_compress(C.byref(desc), _dev(q), _dev(q_pos), n_q, _dev(k_cache),
-                                        n_keys, vis_start, vis_len,
-                                        keep_num, keep_den, _dev(scores_in), _dev(row_lse_in), _dev(scores_out),
-                                        _dev(kept_idx), C.byref(n_kept), _dev(gather_src), n_rows_src,
-                                        _dev(gather_dst), row_elems, _dev(workspace),
-                                        workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native().dream_visual_compress(desc, q, q_pos, n_q, k_cache, n_keys, vis_start, vis_len, keep_num, keep_den, scores_in,
+                                           row_lse_in, scores_out, kept_idx, n_kept, gather_src, n_rows_src, gather_dst, row_elems,
+                                           workspace, workspace, _stream(stream)))
     return int(n_kept.value)
 
 
@@ -222,11 +210,8 @@ def dream_accept_path_workspace(batch: int, n_tree: int, vocab: int) -> int:
 
 def dream_accept_path(logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent, max_depth: int,
                       node_argmax, accept_len, accept_path, bonus_token, workspace, stream=None) -> None:
-    _check(load().dream_accept_path(_dev(logits), logits_dtype, batch, n_tree,
-                                    vocab, _dev(token), _dev(parent), max_depth,
-                                    _dev(node_argmax), _dev(accept_len), _dev(accept_path), _dev(bonus_token),
-                                    _dev(workspace), workspace.numel() * workspace.element_size(),
-                                    _stream(stream)))
+    _check(_native().dream_accept_path(logits, logits_dtype, batch, n_tree, vocab, token, parent, max_depth, node_argmax, accept_len,
+                                       accept_path, bonus_token, workspace, workspace, _stream(stream)))
 
 
 def dream_accept_static_init() -> None:
@@ -235,37 +220,30 @@ def dream_accept_static_init() -> None:
 
 def dream_accept_path_static(logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent, max_depth: int,
                              node_argmax, accept_len, accept_path, bonus_token, stream=None) -> None:
-    _check(load().dream_accept_path_static(_dev(logits), logits_dtype, batch, n_tree,
-                                           vocab, _dev(token), _dev(parent), max_depth,
-                                           _dev(node_argmax), _dev(accept_len), _dev(accept_path), _dev(bonus_token),
-                                           _stream(stream)))
+    _check(_native().dream_accept_path_static(logits, logits_dtype, batch, n_tree, vocab, token, parent, max_depth, node_argmax,
+                                              accept_len, accept_path, bonus_token, _stream(stream)))
 
 
 def dream_kv_commit(desc: AttnDesc, caches: Sequence[torch.Tensor], prefix_len: torch.Tensor, n_tree: int,
                     accept_path: torch.Tensor, accept_len: torch.Tensor, prefix_len_out: Optional[torch.Tensor] = None,
                     stream=None) -> None:
-    ptrs = (C.c_void_p * len(caches))(*[_dev(c) for c in caches])
-    _check(load().dream_kv_commit(C.byref(desc), ptrs, len(caches), _dev(prefix_len), n_tree,
-                                  _dev(accept_path), accept_path.shape[-1], _dev(accept_len),
-                                  _dev(prefix_len_out), _stream(stream)))
+    _check(_native().dream_kv_commit(desc, caches, len(caches), prefix_len, n_tree, accept_path, accept_path.shape[-1], accept_len,
+                                     prefix_len_out, _stream(stream)))
 
 
 def dream_project_rows(desc: AttnDesc, x, n_rows: int, hidden: int, w, n_heads: int, row_base, row_index, out, stream=None) -> None:
-    _check(load().dream_project_rows(C.byref(desc), _dev(x), n_rows, hidden, _dev(w), n_heads,
-                                     _dev(row_base), _dev(row_index), _dev(out), _stream(stream)))
+    _check(_native().dream_project_rows(desc, x, n_rows, hidden, w, n_heads, row_base, row_index, out, _stream(stream)))
 
 
 class ProjJob(C.Structure):
+    """The C layout of a job (dream_proj_job), for callers of the library itself."""
     _fields_ = [("x", C.c_void_p), ("w", C.c_void_p), ("n_heads", C.c_int32), ("row_base", C.c_void_p),
                 ("row_index", C.c_void_p), ("out", C.c_void_p)]
 
 
 def dream_project_rows_multi(desc: AttnDesc, jobs, n_rows: int, hidden: int, stream=None) -> None:
     """jobs: sequence of (x, w, n_heads, row_base, row_index, out)."""
-    arr = (ProjJob * len(jobs))(*[ProjJob(_dev(x), _dev(w), n_heads, _dev(rb), _dev(ri), _dev(out))
-                                  for x, w, n_heads, rb, ri, out in jobs])
-    _check(load().dream_project_rows_multi(C.byref(desc), arr, len(jobs), n_rows, hidden,
-                                           _stream(stream)))
+    _check(_native().dream_project_rows_multi(desc, jobs, len(jobs), n_rows, hidden, _stream(stream)))
 
 
 def dream_spec_accept_workspace(batch: int, n_tree: int, vocab: int) -> int:
@@ -275,11 +253,9 @@ def dream_spec_accept_workspace(batch: int, n_tree: int, vocab: int) -> int:
 def dream_spec_accept(target_logits, draft_logits, logits_dtype: int, batch: int, n_tree: int, vocab: int, token, parent,
                       u_accept, u_bonus, max_depth: int, temperature: float, accept_len, accept_path, bonus_token, workspace,
                       stream=None) -> None:
-    _check(load().dream_spec_accept(_dev(target_logits), _dev(draft_logits), logits_dtype, batch,
-                                    n_tree, vocab, _dev(token), _dev(parent), _dev(u_accept), _dev(u_bonus),
-                                    max_depth, temperature, _dev(accept_len), _dev(accept_path),
-                                    _dev(bonus_token), _dev(workspace), workspace.numel() * workspace.element_size(),
-                                    _stream(stream)))
+    _check(_native().dream_spec_accept(target_logits, draft_logits, logits_dtype, batch, n_tree, vocab, token, parent, u_accept,
+                                       u_bonus, max_depth, temperature, accept_len, accept_path, bonus_token, workspace, workspace,
+                                       _stream(stream)))
 
 
 def dream_attention_entropy_workspace(desc: AttnDesc, n_q: int) -> int:
@@ -287,9 +263,8 @@ def dream_attention_entropy_workspace(desc: AttnDesc, n_q: int) -> int:
 
 
 def dream_attention_entropy(desc: AttnDesc, q, q_pos, n_q: int, k_cache, n_keys: int, row_entropy, ae, workspace, stream=None) -> None:
-    _check(load().dream_attention_entropy(C.byref(desc), _dev(q), _dev(q_pos), n_q, _dev(k_cache), n_keys,
-                                          _dev(row_entropy), _dev(ae), _dev(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native().dream_attention_entropy(desc, q, q_pos, n_q, k_cache, n_keys, row_entropy, ae, workspace, workspace,
+                                             _stream(stream)))
 
 
 def dream_tree_expand_workspace(batch: int, n_frontier: int, vocab: int, k: int) -> int:
@@ -299,19 +274,16 @@ def dream_tree_expand_workspace(batch: int, n_frontier: int, vocab: int, k: int)
 def dream_tree_expand_level(logits: torch.Tensor, logits_dtype: int, batch: int, n_frontier: int, vocab: int,
                             cum_in: torch.Tensor, k: int, cand_token: torch.Tensor, cand_score: torch.Tensor,
                             next_frontier: torch.Tensor, workspace: torch.Tensor, stream=None) -> None:
-    _check(load().dream_tree_expand_level(_dev(logits), logits_dtype, batch, n_frontier,
-                                          vocab, _dev(cum_in), k, _dev(cand_token), _dev(cand_score),
-                                          _dev(next_frontier), _dev(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native().dream_tree_expand_level(logits, logits_dtype, batch, n_frontier, vocab, cum_in, k, cand_token, cand_score,
+                                             next_frontier, workspace, workspace, _stream(stream)))
 
 
 def dream_tree_finalize(pool_score: torch.Tensor, pool_parent: torch.Tensor, pool_token: torch.Tensor, batch: int, n_pool: int,
                         budget: int, tree_parent: torch.Tensor, tree_token: torch.Tensor, tree_pool_index: torch.Tensor,
                         stream=None) -> int:
     n_tree = C.c_int32(0)
-    _check(load().dream_tree_finalize(_dev(pool_score), _dev(pool_parent), _dev(pool_token), batch, n_pool,
-                                      budget, _dev(tree_parent), _dev(tree_token), _dev(tree_pool_index),
-                                      C.byref(n_tree), _stream(stream)))
+    _check(_native().dream_tree_finalize(pool_score, pool_parent, pool_token, batch, n_pool, budget, tree_parent, tree_token,
+                                         tree_pool_index, n_tree, _stream(stream)))
     return int(n_tree.value)
 
 

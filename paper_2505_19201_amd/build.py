@@ -1,7 +1,8 @@
 """Builds libdream.so (the C-ABI HIP library) for gfx950 with hipcc.
 
 `python -m paper_2505_19201_amd.build` compiles every csrc/*.hip to an object in csrc/_build/
-(in parallel) and links them into paper_2505_19201_amd/libdream.so.
+(in parallel) and links them into paper_2505_19201_amd/libdream.so; csrc/call.cpp becomes the extension
+paper_2505_19201_amd/_call.so through which the binding calls it.
 """
 from __future__ import annotations
 
@@ -9,12 +10,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdream.so")
+CALL = os.path.join(HERE, "_call.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -44,11 +47,21 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def _call_command(out: str):
+    """Host compiler only: the extension holds no GPU code and finds libdream.so beside itself."""
+    from torch.utils import cpp_extension
+    import torch
+    inc = ["-I" + d for d in (sysconfig.get_paths()["include"], INCLUDE, *cpp_extension.include_paths())]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+            os.path.join(CSRC, "call.cpp"), "-o", out, "-L" + HERE, "-l:libdream.so", "-Wl,-rpath,$ORIGIN", "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(CALL)):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
+    t = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
+    deps = sources() + [os.path.join(CSRC, "call.cpp")] + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -72,6 +85,9 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     if verbose and out.strip():
         print(out)
     os.replace(tmp, LIB)
+    tmp = CALL + ".tmp.%d" % os.getpid()
+    _run(_call_command(tmp))
+    os.replace(tmp, CALL)
     return LIB
 
 
