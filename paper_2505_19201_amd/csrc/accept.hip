@@ -31,9 +31,16 @@ __device__ __forceinline__ void better(float &v, int &i, float ov, int oi)
     }
 }
 
+// (value, index) as one integer whose order is "larger value, then lower index"
+__device__ __forceinline__ uint64_t make_key(float v, int i)
+{
+    v += 0.0f;   // -0 and +0 are equal values
+    const uint32_t u = __float_as_uint(v);
+    return ((uint64_t)((u & 0x80000000u) ? ~u : (u | 0x80000000u)) << 32) | (0xffffffffu - (uint32_t)i);
+}
+
 template <bool BF16>
-__global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits, int vocab, int n_chunks,
-                                                             float *part_val, int32_t *part_idx)
+__global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits, int vocab, int n_chunks, uint64_t *part)
 {
     const int chunk = blockIdx.x;
     const int64_t row = blockIdx.y;
@@ -92,36 +99,60 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits,
     if (tid == 0) {
         for (int w = 1; w < 4; w++)
             better(best, best_i, sv[w], si[w]);
-        part_val[row * n_chunks + chunk] = best;
-        part_idx[row * n_chunks + chunk] = best_i;
+        part[row * n_chunks + chunk] = make_key(best, best_i);
     }
 }
 
-// One wave per sequence.  Every node checks its own root path in parallel (a node is accepted iff every
-// edge above it matches the target's arg-max and it is not deeper than max_depth); the deepest accepted
-// node, lowest index among equals, wins a wave reduction; lane 0 writes its path.
-__global__ __launch_bounds__(64) void accept_walk_kernel(const float *part_val, const int32_t *part_idx, int n_chunks,
-                                                         int n_tree, const int32_t *token, const int32_t *parent,
-                                                         int max_depth, int32_t *node_argmax, int32_t *accept_len,
-                                                         int32_t *accept_path, int32_t *bonus_token)
+// One workgroup per sequence.  `lanes` adjacent lanes (a power of two) merge the chunk results of a node; then one wave lets every
+// node check its own root path (a node is accepted iff every edge above it matches the target's arg-max and it is not deeper
+// than max_depth); the deepest accepted node, lowest index among equals, wins a wave reduction; lane 0 writes its path.
+// Latency bound.  Measured, 60 nodes of 32 chunks: 7.8 us with one wave that read a node's chunks one lane each, 5.6 us here.
+constexpr int WALK = 512;
+
+__global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part, int n_chunks, int lanes, int n_tree, const int32_t *token,
+                                                           const int32_t *parent, int max_depth, int32_t *node_argmax, int32_t *accept_len,
+                                                           int32_t *accept_path, int32_t *bonus_token)
 {
     __shared__ int32_t s_am[DREAM_MAX_TREE_ACCEPT];
     __shared__ int32_t s_par[DREAM_MAX_TREE_ACCEPT];
     __shared__ int32_t s_tok[DREAM_MAX_TREE_ACCEPT];
-    const int b = blockIdx.x, lane = threadIdx.x;
-    for (int i = lane; i < n_tree; i += 64) {
-        int64_t row = (int64_t)b * n_tree + i;
-        float v = part_val[row * n_chunks];
-        int idx = part_idx[row * n_chunks];
-        for (int ch = 1; ch < n_chunks; ch++)
-            better(v, idx, part_val[row * n_chunks + ch], part_idx[row * n_chunks + ch]);
-        s_am[i] = idx;
-        const int par = parent[row];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int64_t bt = (int64_t)b * n_tree;
+    for (int i = tid; i < n_tree; i += WALK) {
+        const int par = parent[bt + i];
         s_par[i] = par < i ? par : -1;   // a walk up the tree always ends
-        s_tok[i] = token[row];
-        node_argmax[row] = idx;
+        s_tok[i] = token[bt + i];
+    }
+    const int sub = tid & (lanes - 1), per_pass = WALK / lanes;
+    constexpr int U = 4;                 // passes whose loads are in flight together
+    for (int i0 = tid / lanes; i0 < n_tree; i0 += U * per_pass) {
+        uint64_t best[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int i = i0 + u * per_pass;
+            best[u] = i < n_tree && sub < n_chunks ? part[(bt + i) * n_chunks + sub] : 0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int i = i0 + u * per_pass;
+            for (int ch = sub + lanes; i < n_tree && ch < n_chunks; ch += lanes) {
+                const uint64_t o = part[(bt + i) * n_chunks + ch];
+                best[u] = o > best[u] ? o : best[u];
+            }
+            for (int off = 1; off < lanes; off <<= 1) {
+                const uint64_t o = __shfl_xor((unsigned long long)best[u], off);
+                best[u] = o > best[u] ? o : best[u];
+            }
+            if (i < n_tree && sub == 0) {
+                const int idx = (int)(0xffffffffu - (uint32_t)best[u]);
+                s_am[i] = idx;
+                node_argmax[bt + i] = idx;
+            }
+        }
     }
     __syncthreads();
+    if (tid >= 64)
+        return;
     int best_d = -1, best_i = 0x7fffffff;
     for (int i = lane; i < n_tree; i += 64) {
         int d = 0;
@@ -184,20 +215,21 @@ int launch_accept(const void *logits, int logits_dtype, int batch, int n_tree, i
                   void *stream)
 {
     const int n_chunks = ceil_div(vocab, CHUNK_ELEMS);
-    const size_t n = (size_t)batch * n_tree * n_chunks;
-    float *part_val = reinterpret_cast<float *>(partials);
-    int32_t *part_idx = reinterpret_cast<int32_t *>(static_cast<char *>(partials) + align_up(n * 4, 256));
+    uint64_t *part = static_cast<uint64_t *>(partials);
+    int lanes = 1;
+    while (lanes < n_chunks && lanes < 64)
+        lanes *= 2;
     hipStream_t st = as_stream(stream);
     dim3 grid(n_chunks, batch * n_tree);
     if (logits_dtype == DREAM_BF16)
-        hipLaunchKernelGGL(argmax_partial_kernel<true>, grid, dim3(256), 0, st, logits, vocab, n_chunks, part_val, part_idx);
+        hipLaunchKernelGGL(argmax_partial_kernel<true>, grid, dim3(256), 0, st, logits, vocab, n_chunks, part);
     else
-        hipLaunchKernelGGL(argmax_partial_kernel<false>, grid, dim3(256), 0, st, logits, vocab, n_chunks, part_val, part_idx);
+        hipLaunchKernelGGL(argmax_partial_kernel<false>, grid, dim3(256), 0, st, logits, vocab, n_chunks, part);
     int rc = check_launch("argmax_partial_kernel");
     if (rc)
         return rc;
-    hipLaunchKernelGGL(accept_walk_kernel, dim3(batch), dim3(64), 0, st, part_val, part_idx, n_chunks, n_tree, token, parent,
-                       max_depth, node_argmax, accept_len, accept_path, bonus_token);
+    hipLaunchKernelGGL(accept_walk_kernel, dim3(batch), dim3(WALK), 0, st, part, n_chunks, lanes, n_tree, token, parent, max_depth, node_argmax,
+                       accept_len, accept_path, bonus_token);
     return check_launch("accept_walk_kernel");
 }
 
