@@ -1077,7 +1077,9 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
     p->wave_mode = q_tiles_override() == 0 && kv_splits_override() == 0 && tile_waves_override() == 0 &&
                    d->dtype == DREAM_BF16 && n_qtiles <= 16 && G <= 4 && base * n_qtiles <= 512 && base * n_qtiles >= 32 &&
                    (base * n_qtiles <= 256 || d->head_dim <= 128) && (int64_t)tiles * d->head_dim <= (G > 1 ? 12288 : 8192) &&
-                   d->s_max * d->head_dim < (1ll << 31);
+                   // (four full tiles of one head: above one tile per CU the two key groups below are as fast at 24 key tiles of
+                   // head_dim 128, 17.2 against 16.5 us, and ahead at 49, 29.8 against 26.6 us; at head_dim 64 they are not)
+                   !(base * n_qtiles > 256 && n_qtiles == 4 && G == 1 && d->head_dim == 128) && d->s_max * d->head_dim < (1ll << 31);
     if (p->wave_mode) {
         p->qg = 1;
         p->n_qg = n_qtiles;
@@ -1101,16 +1103,24 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
         p->total = DREAM_WORKSPACE_MIN_BYTES;
         return 0;
     }
-    // grouped-query shapes with enough streams to give every CU a workgroup without splitting keys: 8 waves share
-    // one LDS tile, so the 8-16 query tiles of a KV head are served by ONE workgroup (K/V leave L2 once per head
-    // instead of once per 4 query tiles) while the CU still holds 8 waves.  head_dim 64 tiles are too small to
-    // spread over 512 threads; with more than 16 (8 at head_dim 256) query tiles a KV head takes several workgroups.
+    // grouped-query shapes with more 4-wave workgroups than the chip runs well: 8 waves share one LDS tile, so the 8-16
+    // query tiles of a KV head are served by ONE workgroup (K/V leave L2 once per head instead of once per 4 query tiles)
+    // while the CU still holds 8 waves.  head_dim 64 tiles are too small to spread over 512 threads; with more than 16
+    // (8 at head_dim 256) query tiles a KV head takes several workgroups.  The lines, from 42 key tiles at 4-32 sequences:
+    // head_dim 128, 16 query tiles: 47-52 us whatever the number of workgroups up to one per CU, against 38-42 us of two 4-wave
+    // workgroups per CU and 62-76 us of more; up to 8 query tiles: 33-36 us against 37-40 us of two per CU; head_dim 256: 58-70 us
+    // against 52 us of one per CU and 102 us of two, and with up to 4 query tiles (where it replaces a second
+    // key split as well, unless the range is long) 41-50 us against 50 us of one per CU and 37-43 us of two splits (14 key
+    // tiles: 19 us against 23-27 us of two splits).
     {
         const int tw = tile_waves_override();
         const int qg8_max = d->head_dim == 256 ? 1 : 2;
         int qg8 = q_tiles_override() > 0 ? (q_tiles_override() > qg8_max ? qg8_max : q_tiles_override()) : (n_qtiles > 8 ? qg8_max : 1);
         const bool can8 = d->dtype == DREAM_BF16 && d->head_dim >= 128 && kv_splits_override() <= 1 && tw != 4;
-        const bool want8 = n_qtiles > 4 && (tw == 8 || (q_tiles_override() == 0 && base >= 256));   // (up to 4 tiles: see the two key groups below)
+        const int64_t wg4 = base * ceil_div(n_qtiles, 4);
+        const bool few = n_qtiles <= 4;        // (at head_dim 128: see the two key groups below)
+        const bool full = few ? d->head_dim == 256 && (wg4 > 128 || (wg4 > 64 && tiles <= 32)) : wg4 > (qg8 == 2 ? 512 : 256);
+        const bool want8 = (tw == 8 && !few) || (tw == 0 && q_tiles_override() == 0 && full);
         // (the 8-wave variants read K/V with the nontemporal hint, so a KV head must not need two of them)
         if (can8 && want8 && ceil_div(n_qtiles, 8 * qg8) == 1) {
             p->nw = 8;
@@ -1123,9 +1133,15 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
     if (p->nw == 8)
         s = 1;
     if (s <= 0) {
-        s = ceil_div(256, base * p->n_qg);   // one workgroup per CU before anything is split further
+        // at most one workgroup per CU: a few more leave most of the chip waiting for the last ones (96 groups of head_dim 256,
+        // 42 key tiles: 49.8 us in 3 splits, 37.4 us in 2; 160 groups: 65.7 us in 2, 52.1 us in 1)
+        s = (int)(256 / (base * p->n_qg));
         if (s > 8)
             s = 8;                           // more splits cost more in the merge than they save
+        // ... as do two or three of a short range whose workgroups can have two key groups instead (96 and 128 groups, 24 key
+        // tiles: 19.4 and 20.7 us in 2 splits, 16.3 and 16.5 us unsplit)
+        if (s <= 3 && d->head_dim <= 128 && tiles <= 64)
+            s = 1;
     }
     if (s > tiles)
         s = tiles;
@@ -1155,11 +1171,12 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
     if (p->nw == 8) {
         p->kt = 1;
         p->pfd = DREAM_W8_PFD;
-    } else if (qg == 1 && p->pfd == 2 && p->n_qg == 1) {
-        p->once = 1;
-        // multi-head shapes that leave a CU with at most DREAM_KG2_MAX_WG 4-wave workgroups: 8 waves as two key groups
+    } else if (qg == 1 && p->pfd == 2) {
+        p->once = p->n_qg == 1;
+        // shapes that leave a CU with at most DREAM_KG2_MAX_WG 4-wave workgroups: 8 waves as two key groups (several query
+        // groups per KV head, 42 key tiles, 256 workgroups: 29.8 us with 4 waves, 23.8 us)
         const int tw = tile_waves_override();
-        if (s == 1 && d->head_dim <= 128 && tw != 4 && (tw == 8 || groups <= 256 * DREAM_KG2_MAX_WG)) {
+        if (s == 1 && d->head_dim <= 128 && tw != 4 && (tw == 8 || (groups <= 256 * DREAM_KG2_MAX_WG && (p->n_qg == 1 || q_tiles_override() == 0)))) {
             p->nw = 8;
             p->kg = 2;
         }
@@ -1297,6 +1314,7 @@ struct Variant {
 #define TILE_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 4, 1, 0, 1, &launch_bf16<D, QG, KT, PFD>, &ensure_bf16_lds<D, QG, KT, PFD>}
 #define ONCE_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 4, 1, 1, 1, &launch_bf16<D, QG, KT, PFD, 4, 1, true>, &ensure_bf16_lds<D, QG, KT, PFD, 4, 1, true>}
 #define KG2_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 8, 1, 1, 2, &launch_bf16<D, QG, KT, PFD, 8, 1, true, 2>, &ensure_bf16_lds<D, QG, KT, PFD, 8, 1, true, 2>}
+#define KG2S_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 8, 1, 0, 2, &launch_bf16<D, QG, KT, PFD, 8, 1, false, 2>, &ensure_bf16_lds<D, QG, KT, PFD, 8, 1, false, 2>}
 #define WIDE_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 4, 4, 0, 1, &launch_bf16<D, QG, KT, PFD, 4, 4>, &ensure_bf16_lds<D, QG, KT, PFD, 4, 4>}
 #define TILE8_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 8, 1, 1, 1, &launch_bf16<D, QG, KT, PFD, 8, 1, true>, &ensure_bf16_lds<D, QG, KT, PFD, 8, 1, true>}
 #define WAVE_VARIANT(D, NW, DS, QT) {FAMILY_WAVE, D, NW, DS, QT, 0, 1, 0, 1, &launch_wave<D, NW, DS, QT>, &ensure_wave_lds<D, NW, DS, QT>}
@@ -1311,6 +1329,8 @@ const Variant VARIANTS[] = {
     ONCE_VARIANT(64, 1, 2, 2), ONCE_VARIANT(128, 1, 1, 2), ONCE_VARIANT(256, 1, 1, 2),
     // the same with 8 waves as two key groups (few streams per CU): name arguments ...,8,1,1,2
     KG2_VARIANT(64, 1, 2, 2), KG2_VARIANT(128, 1, 1, 2),
+    // ... and with several query groups per KV head: name arguments ...,8,1,0,2
+    KG2S_VARIANT(64, 1, 2, 2), KG2S_VARIANT(128, 1, 1, 2),
     // 8 waves per workgroup (unsplit key range, grouped queries, always the only reader): a fifth name argument 8
     TILE8_VARIANT(128, 1, 1, DREAM_W8_PFD), TILE8_VARIANT(128, 2, 1, DREAM_W8_PFD), TILE8_VARIANT(256, 1, 1, DREAM_W8_PFD),
     // trees of 65-256 nodes (four mask words): a sixth name argument 4
@@ -1327,6 +1347,7 @@ const Variant VARIANTS[] = {
 #undef TILE8_VARIANT
 #undef ONCE_VARIANT
 #undef KG2_VARIANT
+#undef KG2S_VARIANT
 #undef WIDE_VARIANT
 #undef WAVE_VARIANT
 constexpr int N_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);

@@ -32,6 +32,9 @@ VARIANT_CASES = [
     # 8 waves as two key groups (multi-head shapes with few streams per CU)
     VariantCase("attn_bf16_kernel<64,1,2,2,8,1,1,2>", 2, 4, 4, 64, 60, 6, 333, 1, 0, 8),
     VariantCase("attn_bf16_kernel<128,1,1,2,8,1,1,2>", 2, 4, 4, 128, 60, 6, 333, 1, 0, 8),
+    # the same with several query groups per KV head
+    VariantCase("attn_bf16_kernel<64,1,2,2,8,1,0,2>", 2, 4, 2, 64, 60, 6, 333, 1, 0),
+    VariantCase("attn_bf16_kernel<128,1,1,2,8,1,0,2>", 2, 4, 2, 128, 60, 6, 333, 1, 0),
     # 8 waves per workgroup: 8 query tiles of a KV head (one per wave), 16 (two per wave), head_dim 256
     VariantCase("attn_bf16_kernel<128,1,1,2,8>", 2, 4, 2, 128, 60, 6, 150, 0, 0, 8),
     VariantCase("attn_bf16_kernel<128,2,1,2,8>", 2, 8, 2, 128, 60, 6, 150, 0, 0, 8),
@@ -72,6 +75,9 @@ EXTRA_W8_CASES = [
     # two key groups: idle query-tile waves, sequences whose key range is shorter than one step, an odd number of tiles
     VariantCase("attn_bf16_kernel<64,1,2,2,8,1,1,2>", 3, 2, 2, 64, 17, 4, 170, 1, 0, 8),
     VariantCase("attn_bf16_kernel<128,1,1,2,8,1,1,2>", 2, 2, 2, 128, 33, 5, 225, 1, 0, 8),
+    # ... with an idle query-tile slot in the last of three query groups
+    VariantCase("attn_bf16_kernel<64,1,2,2,8,1,0,2>", 3, 6, 2, 64, 50, 6, 170, 1, 0),
+    VariantCase("attn_bf16_kernel<128,1,1,2,8,1,0,2>", 2, 6, 2, 128, 49, 6, 225, 1, 0),
     VariantCase("attn_bf16_kernel<128,1,1,2,8>", 2, 6, 2, 128, 17, 4, 700, 0, 0, 8),
     VariantCase("attn_bf16_kernel<128,2,1,2,8>", 1, 6, 2, 128, 60, 6, 333, 0, 0, 8),
     VariantCase("attn_bf16_kernel<256,1,1,2,8>", 3, 4, 2, 256, 33, 5, 410, 0, 0, 8),
