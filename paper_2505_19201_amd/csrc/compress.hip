@@ -137,7 +137,8 @@ struct RowStream {
 // With ENT the kernel also keeps t = sum_j 2^(x_j - m) x_j, so that the expected score sum_j A_j x_j = t / l of
 // the row is known and the row's entropy -sum A log A = LSE - sum A_j s_j (Eq. 2, Section 3.2) needs no
 // second pass.
-// Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 23 us, 16 SmolVLM sequences 251 -> 200 us.
+// Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 22.2 us, 16 SmolVLM sequences 251 -> 200 us.
+// The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
 template <int D, bool ENT>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
@@ -194,24 +195,28 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         for (int i = 0; i < G::NS - 1; i++)
             keys.issue(i);
     }
-    bf16x8 qf[CT][NKS];
+    // the rows come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
+    RowStream<D> rows;
+    rows.init(reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D, (int64_t)a.n_q_heads * D * 2, a.n_q, blk, lds, wave, lane);
+    rows.issue(1);
+    int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
 #pragma unroll
-    for (int q = 0; q < CT; q++) {
-        const uint16_t *qp = reinterpret_cast<const uint16_t *>(a.q) + (((int64_t)b * a.n_q + (valid[q] ? row[q] : 0)) * a.n_q_heads + h) * D + g * 8;
+    for (int ks = 0; ks < NKS; ks++)
+        frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
+    bf16x8 qf[CT][NKS];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < CT; q++)
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            qf[q][ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 32);
-    }
+            qf[q][ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + (slot * CT + q) * 16 * G::ROW + frag[ks]);
     float m[CT], l[CT], tx[CT];
 #pragma unroll
     for (int q = 0; q < CT; q++) {
         m[q] = -INFINITY;
         l[q] = tx[q] = 0.0f;
     }
-    int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
-#pragma unroll
-    for (int ks = 0; ks < NKS; ks++)
-        frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
     for (int i = 0, stage = 0; i < n_steps; i++) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step i has landed
         __syncthreads();                                                               // everybody's has, and step i - 1 is no longer read
@@ -389,8 +394,8 @@ __global__ __launch_bounds__(64) void entropy_mean_kernel(const float *block_sum
 // keys in registers.  A lane sums its key columns over the rows it holds; the four row groups and the two halves are
 // combined at the end, so every (head, row split, key) sum has one fixed order.  The rows' log-sum-exps (combined from pass
 // 1's partial values) and positions are put into LDS for 512 rows at a time.
-// Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 20, Pixtral 37.4 -> 28.5, 16 SmolVLM sequences
-// 197 -> 164 us.  Its vector instructions alone take 60 us there (16 exponentials of 8 clocks and 32 others of 2.7 per step and wave).
+// Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 19, Pixtral 37.4 -> 27.1, 16 SmolVLM sequences
+// 197 -> 151 us.  Its vector instructions alone take 60 us there (16 exponentials of 8 clocks and 32 others of 2.7 per step and wave).
 template <int D, int NS1>
 __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
@@ -411,15 +416,10 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     const int blk0 = a.vis_start + unit.rank * 32 * CT, b = blockIdx.z, split = unit.split;
     const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
     bool kvalid[CT];
-    bf16x8 kf[CT][NKS];
 #pragma unroll
     for (int q = 0; q < CT; q++) {
         const int key = j0 + q * 16 + c;
         kvalid[q] = key < vis_end && key < a.n_keys;
-        const uint16_t *kp = reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + (kvalid[q] ? key : 0)) * D + g * 8;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ks++)
-            kf[q][ks] = *reinterpret_cast<const bf16x8 *>(kp + ks * 32);
     }
     // row steps: without explicit positions row r sits at position r, so rows below the block's first key see nothing
     const int n_steps_all = (a.n_q + STEP - 1) / STEP;
@@ -435,6 +435,10 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
         for (int i = 0; i < G::NS - 1; i++)
             rows.issue(i);
     }
+    // the keys come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
+    RowStream<D> keys;
+    keys.init(reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + blk0) * D, D * 2, a.n_keys - blk0, 0, lds, wave, lane);
+    keys.issue(1);
     // log-sum-exps over all keys (in log2 units) and positions of rows row0 .. row0 + WINDOW - 1
     auto fill_window = [&](int row0) {
         for (int w = tid; w < min(WINDOW, n_steps * STEP); w += 256) {
@@ -476,6 +480,14 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 #pragma unroll
     for (int ks = 0; ks < NKS; ks++)
         frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
+    bf16x8 kf[CT][NKS];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < CT; q++)
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++)
+            kf[q][ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + (slot * CT + q) * 16 * G::ROW + frag[ks]);
     for (int i = 0, stage = 0; i < n_steps; i++) {
         if (i % (WINDOW / STEP) == 0) {
             if (i > 0)
