@@ -320,12 +320,15 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row[q];
         if (valid[q]) {
             a.lse2[o] = lw > 0.0f ? mt + log2f(lw) : -INFINITY;
-            if (split == 0)                                  // splits that other blocks have and this one does not
-                for (int s = unit.n; s < a.ns1; s++)
+            if (ENT)
+                a.ent_part[o] = lw > 0.0f ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
+            if (split == 0)                                  // splits that other blocks have and this one does not: both values, since
+                for (int s = unit.n; s < a.ns1; s++) {       // a weight of 0 does not make a NaN left in the workspace harmless
                     a.lse2[o + s * a.lse_split_stride] = -INFINITY;
+                    if (ENT)
+                        a.ent_part[o + s * a.lse_split_stride] = 0.0f;
+                }
         }
-        if (ENT && valid[q])
-            a.ent_part[o] = lw > 0.0f ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
     }
 }
 

@@ -13,6 +13,11 @@ DT = {"f32": dream.F32, "bf16": dream.BF16}
 TORCH_DT = {"f32": torch.float32, "bf16": torch.bfloat16}
 
 
+def workspace(nbytes: int) -> torch.Tensor:
+    """Scratch full of 0xFF bytes (NaN as floats): the library promises to read no part of it that the call has not written."""
+    return dream.alloc_workspace(nbytes).fill_(0xFF)
+
+
 def out_to_f64(t: torch.Tensor) -> np.ndarray:
     return t.float().cpu().numpy().astype(np.float64)
 
@@ -52,7 +57,7 @@ def run_verify(x: di.AttnInputs, tree_mask=None, scale: float = 0.0, want_lse: b
     B, T, Hq, D = x.q.shape
     out = torch.full((B, T, Hq, D), float("nan"), dtype=TORCH_DT[x.dtype], device="cuda")
     lse = torch.full((B, Hq, T), float("nan"), dtype=torch.float32, device="cuda") if want_lse else None
-    ws = dream.alloc_workspace(dream.dream_tree_verify_attn_workspace(desc, T, dev.max_kv))
+    ws = workspace(dream.dream_tree_verify_attn_workspace(desc, T, dev.max_kv))
     tm = None if tree_mask is None else dream.to_device(tree_mask)
     dream.dream_tree_verify_attn(desc, dev.q, dev.k, dev.v, dev.prefix_len, T, dev.parent, tm, dev.max_kv, out, lse, ws)
     torch.cuda.synchronize()
@@ -68,7 +73,7 @@ def run_xattn(x: di.AttnInputs, rows: np.ndarray, q_node, scale: float = 0.0, de
     qsel = np.stack([x.q[b, rows[b]] for b in range(B)])
     q = dream.to_device(qsel, x.dtype)
     out = torch.full((B, n_q, Hq, D), float("nan"), dtype=TORCH_DT[x.dtype], device="cuda")
-    ws = dream.alloc_workspace(dream.dream_draft_xattn_workspace(desc, n_q, dev.max_kv))
+    ws = workspace(dream.dream_draft_xattn_workspace(desc, n_q, dev.max_kv))
     qn = None if q_node is None else dream.to_device(np.ascontiguousarray(q_node, dtype=np.int32))
     dream.dream_draft_xattn(desc, q, dev.k, dev.v, dev.prefix_len, dev.n_tree, dev.parent, n_q, qn, dev.max_kv, out, ws)
     torch.cuda.synchronize()
@@ -83,7 +88,7 @@ def run_accept(logits: np.ndarray, dtype: str, token: np.ndarray, parent: np.nda
     alen = torch.full((B,), -7, dtype=torch.int32, device="cuda")
     path = torch.full((B, max_depth + 1), -7, dtype=torch.int32, device="cuda")
     bonus = torch.full((B,), -7, dtype=torch.int32, device="cuda")
-    ws = dream.alloc_workspace(dream.dream_accept_path_workspace(B, T, V))
+    ws = workspace(dream.dream_accept_path_workspace(B, T, V))
     dream.dream_accept_path(lg, DT[dtype], B, T, V, tok, par, max_depth, am, alen, path, bonus, ws)
     torch.cuda.synchronize()
     return am.cpu().numpy(), alen.cpu().numpy(), path.cpu().numpy(), bonus.cpu().numpy()
@@ -113,7 +118,7 @@ def run_compress(dtype: str, q, k, n_keys, vis_start, vis_len, keep_num, keep_de
         gsrc = dream.to_device(gather_src, dtype)
         n_rows_src, row_elems = gather_src.shape[1], gather_src.shape[2]
         gdst = torch.zeros((B, max(k_keep, 1), row_elems), dtype=TORCH_DT[dtype], device="cuda")
-    ws = dream.alloc_workspace(dream.dream_visual_compress_workspace(desc, n_q, vis_len))
+    ws = workspace(dream.dream_visual_compress_workspace(desc, n_q, vis_len))
     dlse = None if row_lse is None else dream.to_device(np.ascontiguousarray(row_lse, dtype=np.float32))
     k_rep = dream.dream_visual_compress(desc, dq, dpos, n_q, dk, n_keys, vis_start, vis_len, keep_num, keep_den, dsi,
                                         sc_out, kept, gsrc, n_rows_src, gdst, row_elems, ws, row_lse_in=dlse)
@@ -151,7 +156,7 @@ def run_expand(logits: np.ndarray, dtype: str, cum: np.ndarray, k: int):
     tok = torch.full((B, F, k), -7, dtype=torch.int32, device="cuda")
     sc = torch.full((B, F, k), float("nan"), dtype=torch.float32, device="cuda")
     nxt = torch.full((B, kf), -7, dtype=torch.int32, device="cuda")
-    ws = dream.alloc_workspace(dream.dream_tree_expand_workspace(B, F, V, k))
+    ws = workspace(dream.dream_tree_expand_workspace(B, F, V, k))
     dream.dream_tree_expand_level(lg, DT[dtype], B, F, V, cm, k, tok, sc, nxt, ws)
     torch.cuda.synchronize()
     return tok.cpu().numpy(), sc.cpu().numpy(), nxt.cpu().numpy()
@@ -179,7 +184,7 @@ def run_entropy(dtype: str, q: np.ndarray, k: np.ndarray, n_keys: int, q_pos=Non
     qp = None if q_pos is None else dream.to_device(np.ascontiguousarray(q_pos, dtype=np.int32))
     row = torch.full((B, Hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
     ae = torch.full((B,), float("nan"), dtype=torch.float32, device="cuda")
-    ws = dream.alloc_workspace(dream.dream_attention_entropy_workspace(desc, n_q))
+    ws = workspace(dream.dream_attention_entropy_workspace(desc, n_q))
     dream.dream_attention_entropy(desc, dq, qp, n_q, dk, n_keys, row, ae, ws)
     torch.cuda.synchronize()
     return row.cpu().numpy(), ae.cpu().numpy()
@@ -196,7 +201,7 @@ def run_spec_accept(tlogits: np.ndarray, dlogits: np.ndarray, dtype: str, token,
     alen = torch.full((B,), -7, dtype=torch.int32, device="cuda")
     path = torch.full((B, max_depth + 1), -7, dtype=torch.int32, device="cuda")
     bonus = torch.full((B,), -7, dtype=torch.int32, device="cuda")
-    ws = dream.alloc_workspace(dream.dream_spec_accept_workspace(B, T, V))
+    ws = workspace(dream.dream_spec_accept_workspace(B, T, V))
     dream.dream_spec_accept(tl, dl, DT[dtype], B, T, V, tok, par, ua, ub, max_depth, temperature, alen, path, bonus, ws)
     torch.cuda.synchronize()
     return alen.cpu().numpy(), path.cpu().numpy(), bonus.cpu().numpy()

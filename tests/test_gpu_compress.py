@@ -258,3 +258,12 @@ def test_score_steps_and_splits(gu, D, P, v, vis_start, with_pos):
     pos = np.stack([g.permutation(P) for _ in range(2)]).astype(np.int32) if with_pos else None
     scores, _, _ = gu.run_compress("bf16", q, k, P, vis_start, v, 1, 2, q_pos=pos)
     np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
+
+
+@pytest.mark.parametrize("D,P,v", [(128, 1279, 1023), (64, 333, 300), (256, 449, 200)])
+def test_stale_workspace_is_never_read(gu, D, P, v):
+    """Blocks with fewer splits than others, in both score passes, over a workspace of NaN patterns (the harness fills it)."""
+    q = di.normal((1, P, 4, D), "bf16", 1101 + P, di.STREAM_PREFILL_Q)
+    k = di.normal((1, 2, P, D), "bf16", 1102 + P, di.STREAM_K)
+    scores, _, _ = gu.run_compress("bf16", q, k, P, 0, v, 1, 2)
+    np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", 0, v), rtol=SCORE_RTOL["bf16"])
