@@ -2,9 +2,11 @@
 // status out.  A decode round makes dozens of calls of up to 20 arguments, and the commit takes the caches of every layer: the
 // three attribute lookups per tensor from Python took 22 us for 96 caches, more than the kernels of the call.
 //
-// Every wrapper follows from the entry point's own signature (one template): a pointer takes None, a tensor on the GPU
-// (contiguous; its data pointer), an integer, or an object with a buffer (ctypes structures, arrays and out-parameters); an array
-// of pointers takes a sequence of tensors, the projection jobs a sequence of tuples; size_t takes an integer or a tensor (its bytes); the rest are numbers.
+// Every wrapper follows from the entry point's own signature (one template).  A pointer is a device pointer: it takes a contiguous
+// tensor on the GPU or None, and nothing else, so that host memory never reaches a kernel as one.  The exceptions have types of
+// their own: the descriptor (a ctypes structure), host out-parameters (ENTRY_HOST names their position) and the stream (always the
+// last argument, a raw handle).  An array of pointers takes a sequence of tensors, the projection jobs a sequence of tuples; size_t
+// takes an integer or a tensor (its bytes); the rest are numbers.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -61,30 +63,59 @@ struct Arg<float> {
 template <class T>
 struct Arg<T *> {
     T *value = nullptr;
-    Py_buffer view = {};
     explicit Arg(PyObject *o)
     {
         if (o == Py_None)
             return;
-        if (THPVariable_Check(o)) {
-            value = static_cast<T *>(device_pointer(o));
-        } else if (PyLong_Check(o)) {
-            value = static_cast<T *>(PyLong_AsVoidPtr(o));
-            if (PyErr_Occurred())
-                throw Failed();
-        } else {
-            if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE))
-                throw Failed();
-            value = static_cast<T *>(view.buf);
+        if (!THPVariable_Check(o)) {
+            PyErr_Format(PyExc_TypeError, "device tensor or None expected, not %.100s", Py_TYPE(o)->tp_name);
+            throw Failed();
         }
+        value = static_cast<T *>(device_pointer(o));
     }
-    ~Arg()
+};
+
+// Host memory of exactly one T, through the buffer interface (ctypes structures and numbers are writable buffers).
+template <class T>
+struct HostObject {
+    T *value = nullptr;
+    Py_buffer view = {};
+    explicit HostObject(PyObject *o, bool nullable)
+    {
+        if (nullable && o == Py_None)
+            return;
+        if (PyObject_GetBuffer(o, &view, PyBUF_WRITABLE))
+            throw Failed();
+        if (view.len != (Py_ssize_t)sizeof(T)) {
+            PyBuffer_Release(&view);
+            PyErr_Format(PyExc_TypeError, "an object of %d bytes is expected", (int)sizeof(T));
+            throw Failed();
+        }
+        value = static_cast<T *>(view.buf);
+    }
+    ~HostObject()
     {
         if (view.obj)
             PyBuffer_Release(&view);
     }
-    Arg(const Arg &) = delete;
+    HostObject(const HostObject &) = delete;
 };
+template <>
+struct Arg<const dream_attn_desc *> : HostObject<dream_attn_desc> {
+    explicit Arg(PyObject *o) : HostObject(o, false) {}
+};
+struct HostInt : HostObject<int32_t> {
+    explicit HostInt(PyObject *o) : HostObject(o, true) {}
+};
+struct Stream {
+    void *value;
+    explicit Stream(PyObject *o) : value(PyLong_AsVoidPtr(o))
+    {
+        if (PyErr_Occurred())
+            throw Failed();
+    }
+};
+
 template <>
 struct Arg<void *const *> {
     std::vector<void *> pointers;
@@ -145,14 +176,17 @@ struct Arg<const dream_proj_job *> {
     }
 };
 
-template <auto F>
+// HOST: position of the host out-parameter, or -1
+template <auto F, int HOST>
 struct Entry;
-template <class... A, int (*F)(A...)>
-struct Entry<F> {
+template <class... A, int (*F)(A...), int HOST>
+struct Entry<F, HOST> {
+    template <class T, int I>
+    using ArgAt = std::conditional_t<I == (int)sizeof...(A) - 1, Stream, std::conditional_t<I == HOST, HostInt, Arg<T>>>;
     template <size_t... I>
     static int run(PyObject *const *args, std::index_sequence<I...>)
     {
-        const std::tuple<Arg<A>...> a(args[I]...);     // (converted in place: some are neither copied nor moved)
+        const std::tuple<ArgAt<A, I>...> a(args[I]...);     // (converted in place: some are neither copied nor moved)
         int status;
         Py_BEGIN_ALLOW_THREADS
         status = F(std::get<I>(a).value...);
@@ -171,12 +205,14 @@ struct Entry<F> {
     }
 };
 
-#define ENTRY(name) {#name, (PyCFunction)(void (*)(void))&Entry<&name>::call, METH_FASTCALL, nullptr}
+#define ENTRY_HOST(name, host) {#name, (PyCFunction)(void (*)(void))&Entry<&name, host>::call, METH_FASTCALL, nullptr}
+#define ENTRY(name) ENTRY_HOST(name, -1)
 PyMethodDef methods[] = {
-    ENTRY(dream_tree_verify_attn), ENTRY(dream_draft_xattn), ENTRY(dream_visual_compress), ENTRY(dream_accept_path), ENTRY(dream_accept_path_static),
+    ENTRY(dream_tree_verify_attn), ENTRY(dream_draft_xattn), ENTRY_HOST(dream_visual_compress, 14), ENTRY(dream_accept_path), ENTRY(dream_accept_path_static),
     ENTRY(dream_kv_commit), ENTRY(dream_project_rows), ENTRY(dream_project_rows_multi), ENTRY(dream_spec_accept), ENTRY(dream_attention_entropy),
-    ENTRY(dream_tree_expand_level), ENTRY(dream_tree_finalize), {nullptr, nullptr, 0, nullptr}};
+    ENTRY(dream_tree_expand_level), ENTRY_HOST(dream_tree_finalize, 9), {nullptr, nullptr, 0, nullptr}};
 #undef ENTRY
+#undef ENTRY_HOST
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

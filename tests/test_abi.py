@@ -309,3 +309,75 @@ def test_every_plan_names_a_built_variant(lib):
                         assert dream.dream_tree_verify_attn_workspace(desc, n_q, kv) >= 256
                         seen.add(name)
     assert len(seen) >= 25, sorted(built - seen)   # the sweep reaches most of the table without any override
+
+
+def _signature(name):
+    """Parameters of an entry point as include/dream.h declares them: [(type, name)]."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    text = re.sub(r"/\*.*?\*/", "", open(os.path.join(root, "include", "dream.h")).read(), flags=re.S)
+    params = re.search(r"\bint %s\((.*?)\);" % name, text, flags=re.S).group(1)
+    return [tuple(re.match(r"(.*?)(\w+)$", " ".join(p.split())).groups()) for p in params.split(",")]
+
+
+ENTRY_POINTS = ("dream_tree_verify_attn", "dream_draft_xattn", "dream_visual_compress", "dream_accept_path", "dream_accept_path_static",
+                "dream_kv_commit", "dream_project_rows", "dream_project_rows_multi", "dream_spec_accept", "dream_attention_entropy",
+                "dream_tree_expand_level", "dream_tree_finalize")
+
+
+def _plain_arguments(name):
+    """One argument per parameter that converts, every device pointer NULL: the library refuses the call without a launch."""
+    args = []
+    for kind, param in _signature(name):
+        if "dream_attn_desc" in kind:
+            args.append(dream.attn_desc(1, 4, 4, 64, dream.BF16, 128))
+        elif "*const *" in kind or "dream_proj_job" in kind:
+            args.append([])
+        elif param == "stream":
+            args.append(0)
+        else:
+            args.append(None if "*" in kind else 1)
+    return args
+
+
+@pytest.mark.parametrize("name", ENTRY_POINTS)
+def test_device_pointers_take_device_tensors_only(lib, name):
+    """Host memory in any form, and plain addresses, are refused in every device slot; a tensor on the host as before."""
+    import torch
+    from paper_2505_19201_amd.binding import _native
+    call = getattr(_native(), name)
+    assert call(*_plain_arguments(name)) < 0
+    device = [i for i, (kind, param) in enumerate(_signature(name))
+              if "*" in kind and not param.endswith("_host") and param not in ("desc", "jobs", "stream")]
+    assert device or name == "dream_project_rows_multi"
+    for i in device:
+        for bad, error in ((np.zeros(64), TypeError), (b"0" * 64, TypeError), (bytearray(64), TypeError), (0x1000, TypeError),
+                           (C.c_int32(0), TypeError), (torch.zeros(64), ValueError)):
+            args = _plain_arguments(name)
+            args[i] = bad
+            with pytest.raises(error):
+                call(*args)
+    for i, (kind, param) in enumerate(_signature(name)):
+        args = _plain_arguments(name)
+        if param == "desc":
+            for bad in (None, b"0" * C.sizeof(dream.AttnDesc), bytearray(8), C.c_int32(0), 0x1000):
+                args[i] = bad
+                with pytest.raises((TypeError, BufferError)):
+                    call(*args)
+        elif kind.strip() == "int32_t *" and param.endswith("_host"):
+            for bad in (b"0000", bytearray(8), 0x1000):
+                args[i] = bad
+                with pytest.raises((TypeError, BufferError)):
+                    call(*args)
+            args[i] = C.c_int32(7)
+            assert call(*args) < 0
+        elif param == "jobs":
+            for field in (0, 1, 3, 4, 5):
+                job = [None, None, 1, None, None, None]
+                job[field] = np.zeros(64)
+                args[i] = [tuple(job)]
+                with pytest.raises(TypeError):
+                    call(*args)
+        elif param == "caches_host":
+            args[i] = [np.zeros(64)]
+            with pytest.raises(TypeError):
+                call(*args)
