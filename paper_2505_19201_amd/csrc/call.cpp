@@ -9,8 +9,10 @@
 // takes an integer or a tensor (its bytes); the rest are numbers.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <cstdint>
+#include <exception>
 #include <tuple>
 #include <utility>
 #include <vector>
@@ -176,6 +178,11 @@ struct Arg<const dream_proj_job *> {
     }
 };
 
+struct WithoutGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 // HOST: position of the host out-parameter, or -1
 template <auto F, int HOST>
 struct Entry;
@@ -187,11 +194,8 @@ struct Entry<F, HOST> {
     static int run(PyObject *const *args, std::index_sequence<I...>)
     {
         const std::tuple<ArgAt<A, I>...> a(args[I]...);     // (converted in place: some are neither copied nor moved)
-        int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = F(std::get<I>(a).value...);
-        Py_END_ALLOW_THREADS
-        return status;
+        const WithoutGil unlocked;
+        return F(std::get<I>(a).value...);
     }
     static PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n)
     {
@@ -200,8 +204,10 @@ struct Entry<F, HOST> {
         try {
             return PyLong_FromLong(run(args, std::index_sequence_for<A...>{}));
         } catch (const Failed &) {
-            return nullptr;
+        } catch (...) {     // torch's own errors (a sparse tensor has no bytes) and the allocator's: nothing may leave a C function
+            torch::translate_exception_to_python(std::current_exception());
         }
+        return nullptr;
     }
 };
 

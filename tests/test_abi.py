@@ -381,3 +381,29 @@ def test_device_pointers_take_device_tensors_only(lib, name):
             args[i] = [np.zeros(64)]
             with pytest.raises(TypeError):
                 call(*args)
+
+
+def test_torch_errors_become_python_errors(lib):
+    """A tensor that cannot name its bytes (a sparse one) raises; in a process of its own, since an exception that leaves the
+    extension's C functions would end Python."""
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = ("import torch\n"
+            "from tests.test_abi import ENTRY_POINTS, _plain_arguments, _signature\n"
+            "from paper_2505_19201_amd.binding import _native\n"
+            "sparse = torch.zeros(4, 4).to_sparse()\n"
+            "tried = 0\n"
+            "for name in ENTRY_POINTS:\n"
+            "    for i, (kind, param) in enumerate(_signature(name)):\n"
+            "        if kind.strip() == 'size_t':\n"
+            "            args = _plain_arguments(name)\n"
+            "            args[i] = sparse\n"
+            "            try:\n"
+            "                getattr(_native(), name)(*args)\n"
+            "            except RuntimeError:\n"
+            "                tried += 1\n"
+            "print('refused', tried)\n")
+    p = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr[-2000:]
+    assert p.stdout.strip() == "refused 7"
