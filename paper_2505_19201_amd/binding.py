@@ -227,6 +227,7 @@ def dream_accept_path_static(logits, logits_dtype: int, batch: int, n_tree: int,
 def dream_kv_commit(desc: AttnDesc, caches: Sequence[torch.Tensor], prefix_len: torch.Tensor, n_tree: int,
                     accept_path: torch.Tensor, accept_len: torch.Tensor, prefix_len_out: Optional[torch.Tensor] = None,
                     stream=None) -> None:
+    caches = tuple(caches)     # the count handed over is that of the pointers, whatever kind of sequence this is
     _check(_native().dream_kv_commit(desc, caches, len(caches), prefix_len, n_tree, accept_path, accept_path.shape[-1], accept_len,
                                      prefix_len_out, _stream(stream)))
 
@@ -243,6 +244,7 @@ class ProjJob(C.Structure):
 
 def dream_project_rows_multi(desc: AttnDesc, jobs, n_rows: int, hidden: int, stream=None) -> None:
     """jobs: sequence of (x, w, n_heads, row_base, row_index, out)."""
+    jobs = tuple(jobs)         # (see dream_kv_commit)
     _check(_native().dream_project_rows_multi(desc, jobs, len(jobs), n_rows, hidden, _stream(stream)))
 
 

@@ -5,7 +5,7 @@
 // Every wrapper follows from the entry point's own signature (one template).  A pointer is a device pointer: it takes a contiguous
 // tensor on the GPU or None, and nothing else, so that host memory never reaches a kernel as one.  The exceptions have types of
 // their own: the descriptor (a ctypes structure), host out-parameters (ENTRY_HOST names their position) and the stream (always the
-// last argument, a raw handle).  An array of pointers takes a sequence of tensors, the projection jobs a sequence of tuples; size_t
+// last argument, a raw handle).  An array of pointers takes a sequence of tensors, the projection jobs a sequence of sequences; size_t
 // takes an integer or a tensor (its bytes); the rest are numbers.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -160,13 +160,19 @@ struct Arg<const dream_proj_job *> {
         try {
             const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
             for (Py_ssize_t i = 0; i < n; i++) {
-                PyObject *job = PySequence_Fast_GET_ITEM(seq, i);
-                if (!PyTuple_Check(job) || PyTuple_GET_SIZE(job) != 6) {
-                    PyErr_SetString(PyExc_ValueError, "a job is a tuple (x, w, n_heads, row_base, row_index, out)");
+                // (a tuple of its own: converting a field may run Python code, which must not take the others away)
+                struct Owned {
+                    PyObject *o;
+                    ~Owned() { Py_XDECREF(o); }
+                } job = {PySequence_Tuple(PySequence_Fast_GET_ITEM(seq, i))};
+                if (!job.o)
+                    throw Failed();
+                if (PyTuple_GET_SIZE(job.o) != 6) {
+                    PyErr_SetString(PyExc_ValueError, "a job is (x, w, n_heads, row_base, row_index, out)");
                     throw Failed();
                 }
-                auto pointer = [&](int k) { return Arg<void *>(PyTuple_GET_ITEM(job, k)).value; };
-                jobs.push_back({pointer(0), pointer(1), Arg<int32_t>(PyTuple_GET_ITEM(job, 2)).value, static_cast<int32_t *>(pointer(3)),
+                auto pointer = [&](int k) { return Arg<void *>(PyTuple_GET_ITEM(job.o, k)).value; };
+                jobs.push_back({pointer(0), pointer(1), Arg<int32_t>(PyTuple_GET_ITEM(job.o, 2)).value, static_cast<int32_t *>(pointer(3)),
                                 static_cast<int32_t *>(pointer(4)), pointer(5)});
             }
         } catch (...) {

@@ -407,3 +407,18 @@ def test_torch_errors_become_python_errors(lib):
     p = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
     assert p.returncode == 0, p.stderr[-2000:]
     assert p.stdout.strip() == "refused 7"
+
+
+def test_a_projection_job_is_any_sequence_of_six(lib):
+    """Jobs given as lists, tuples or iterators reach the library (which refuses the NULL tensors in them); five fields do not."""
+    desc = dream.attn_desc(1, 4, 4, 64, dream.BF16, 128)
+    job = (None, None, 4, None, None, None)
+    for form in (tuple, list, iter):
+        with pytest.raises(dream.DreamError, match="NULL tensor in job 0"):
+            dream.dream_project_rows_multi(desc, [form(job)], 1, 256, stream=_NoStream())
+    with pytest.raises(ValueError):
+        dream.dream_project_rows_multi(desc, [job[:5]], 1, 256, stream=_NoStream())
+
+
+class _NoStream:
+    cuda_stream = 0
