@@ -662,7 +662,7 @@ __device__ __forceinline__ uint32_t order_key(float x)
 {
     x += 0.0f;   // -0 and +0 are equal scores: give them one key
     const uint32_t u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return (u & 0x80000000u) ? max(~u, 1u) : (u | 0x80000000u);   // (never 0, the key of no token: the NaN of all ones would have it)
 }
 
 __global__ __launch_bounds__(1024) void topk_keep_kernel(const float *part, int n_heads, const float *scores_in,

@@ -267,3 +267,22 @@ def test_stale_workspace_is_never_read(gu, D, P, v):
     k = di.normal((1, 2, P, D), "bf16", 1102 + P, di.STREAM_K)
     scores, _, _ = gu.run_compress("bf16", q, k, P, 0, v, 1, 2)
     np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", 0, v), rtol=SCORE_RTOL["bf16"])
+
+
+@pytest.mark.parametrize("v", [40, 576, 1500, 2500])
+@pytest.mark.parametrize("num,den", [(1, 2), (3, 4), (1, 1)])
+def test_every_score_is_a_token_even_the_lowest_key(gu, v, num, den):
+    """Scores that are NaN patterns of all ones, the lowest of all keys: exactly k distinct tokens are kept, lower ones first among
+    equals, and the gather follows them.  (Host scores in sort order: larger key first, the key being the float's bits made monotone.)"""
+    g = di.rng(19 + v, di.STREAM_SCORES)
+    s = g.standard_normal(size=(2, v)).astype(np.float32)
+    s.view(np.uint32)[0, g.permutation(v)[: (v * 3) // 5]] = 0xFFFFFFFF
+    s.view(np.uint32)[1] = 0xFFFFFFFF
+    rows = di.normal((2, v + 3, 8), "bf16", 1200 + v, di.STREAM_ROWS)
+    _, kept, gathered = gu.run_compress("bf16", None, None, 0, 3, v, num, den, scores_in=s, gather_src=rows)
+    u = s.view(np.uint32).astype(np.int64)
+    key = np.where(u & 0x80000000, 0xFFFFFFFF - u, u | 0x80000000)
+    k = oracle.keep_count(v, num, den)
+    want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1) + 3
+    assert np.array_equal(kept, want)
+    assert np.array_equal(gathered, oracle.gather_rows(rows, "bf16", want.astype(np.int32)))
