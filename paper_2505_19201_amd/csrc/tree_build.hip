@@ -349,7 +349,7 @@ __global__ __launch_bounds__(64) void tree_finalize_kernel(const float *pool_sco
 #pragma unroll
     for (int r = 0; r < NR; r++) {
         const int i = r * 64 + lane;
-        key[r] = i > 0 && i < n_pool ? order_bits(sc[r]) : 0u;    // (0 is below every score's key)
+        key[r] = i > 0 && i < n_pool ? max(order_bits(sc[r]), 1u) : 0u;    // (0 is no entry: the NaN of all ones would have it too)
     }
     // the largest value with at least keep_n entries at or above it
     uint32_t cut = 0u;

@@ -167,3 +167,24 @@ def test_whole_tree_level_by_level_matches_the_oracle(gu, V, dtype, k, depth, bu
         assert got_paths == want_paths
         np.testing.assert_allclose(np.sort(ps[0, pidx[0, 1:]])[::-1], np.sort(want["pool_score"][want["pool_index"][1:]])[::-1],
                                    atol=10 * SCORE_TOL)
+
+
+@pytest.mark.parametrize("n_pool,budget", [(2, 1), (60, 32), (130, 129), (511, 400), (1024, 1000)])
+def test_finalize_keeps_as_many_whatever_the_scores_are(gu, n_pool, budget):
+    """Scores that are NaN patterns of all ones, the lowest of all keys, still fill the budget, lower entries first."""
+    g = di.rng(77 + n_pool, di.STREAM_SCORES)
+    score = (-g.random(size=(2, n_pool))).astype(np.float32)
+    score.view(np.uint32)[0, g.permutation(n_pool)[: (n_pool * 3) // 5]] = 0xFFFFFFFF
+    score.view(np.uint32)[1] = 0xFFFFFFFF
+    parent = np.zeros((2, n_pool), dtype=np.int32)
+    parent[:, 0] = -1
+    token = g.integers(0, 1000, size=(2, n_pool)).astype(np.int32)
+    n_tree, par, tok, pidx = gu.run_finalize(score, parent, token, budget)
+    keep = min(budget, n_pool - 1)
+    assert n_tree == 1 + keep
+    u = score.view(np.uint32).astype(np.int64)
+    key = np.where(u & 0x80000000, 0xFFFFFFFF - u, u | 0x80000000)
+    for b in range(2):
+        want = np.concatenate([[0], np.sort(1 + np.argsort(-key[b, 1:], kind="stable")[:keep])])
+        assert np.array_equal(pidx[b], want)
+        assert np.array_equal(tok[b], token[b, want]) and par[b, 0] == -1 and (par[b, 1:] == 0).all()
