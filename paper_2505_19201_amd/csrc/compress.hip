@@ -86,24 +86,29 @@ __device__ __forceinline__ int swizzle(int r)
     return D == 64 ? (r >> 1) & 7 : r & 15;
 }
 
-template <int D>
+// DIRECT: the loads go straight to LDS, which needs 16-byte aligned rows.  Tensors that start anywhere else (a slice of a larger buffer) take
+// the same way through registers, with the alignment of their elements and the same results.
+template <int D, bool DIRECT>
 struct RowStream {
     using G = StreamGeom<D>;
     const unsigned char *base;     // row 0
     int64_t row_bytes;             // between rows
     int n_rows, next;              // rows there are; the next step to load
     uint32_t lds0;
-    int wave;
+    unsigned char *stage0;
+    int wave, lane;
     uint32_t at[G::NLD];           // this lane's byte offsets from the step's first row
 
-    __device__ __forceinline__ void init(const void *rows, int64_t bytes_between, int n, int first_step, const void *lds, int wave_, int lane)
+    __device__ __forceinline__ void init(const void *rows, int64_t bytes_between, int n, int first_step, unsigned char *lds, int wave_, int lane_)
     {
         base = reinterpret_cast<const unsigned char *>(rows);
         row_bytes = bytes_between;
         n_rows = n;
         next = first_step;
         lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)lds;
+        stage0 = lds;
         wave = wave_;
+        lane = lane_;
 #pragma unroll
         for (int j = 0; j < G::NLD; j++) {
             const int row = (wave * G::NLD + j) * G::RPI + lane / G::CPR;
@@ -116,15 +121,28 @@ struct RowStream {
         const int row0 = min(next * STEP, n_rows - 1), left = n_rows - 1 - row0;
         next++;
         const unsigned char *from = base + row0 * row_bytes;
-        const uint32_t to = lds0 + stage * G::STAGE + wave * G::NLD * 1024;
+        const uint32_t to = stage * G::STAGE + wave * G::NLD * 1024;
         if (left >= STEP - 1) {
 #pragma unroll
             for (int j = 0; j < G::NLD; j++)
-                lds_load16(from, at[j], to + j * 1024);
+                load(from, at[j], to + j * 1024);
         } else {
 #pragma unroll
             for (int j = 0; j < G::NLD; j++)
-                lds_load16(from, min(at[j], (uint32_t)(left * (int)row_bytes) + (at[j] & (G::ROW - 1))), to + j * 1024);
+                load(from, min(at[j], (uint32_t)(left * (int)row_bytes) + (at[j] & (G::ROW - 1))), to + j * 1024);
+        }
+    }
+    __device__ __forceinline__ void load(const unsigned char *from, uint32_t offset, uint32_t to)
+    {
+        if (DIRECT) {
+            lds_load16(from, offset, lds0 + to);
+        } else {
+            const uint16_t *e = reinterpret_cast<const uint16_t *>(from + offset);
+            s16x8 v;
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                v[i] = (short)e[i];
+            *reinterpret_cast<s16x8 *>(stage0 + to + lane * 16) = v;
         }
     }
 };
@@ -139,7 +157,7 @@ struct RowStream {
 // second pass.
 // Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 22.2 us, 16 SmolVLM sequences 251 -> 200 us.
 // The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
-template <int D, bool ENT>
+template <int D, bool ENT, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
@@ -188,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     }
 
     const uint16_t *kb = reinterpret_cast<const uint16_t *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
-    RowStream<D> keys;
+    RowStream<D, DIRECT> keys;
     keys.init(kb, D * 2, a.n_keys, s0, lds, wave, lane);
     if (n_steps > 0) {
 #pragma unroll
@@ -196,7 +214,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
             keys.issue(i);
     }
     // the rows come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
-    RowStream<D> rows;
+    RowStream<D, DIRECT> rows;
     rows.init(reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D, (int64_t)a.n_q_heads * D * 2, a.n_q, blk, lds, wave, lane);
     rows.issue(1);
     int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
@@ -399,7 +417,7 @@ __global__ __launch_bounds__(64) void entropy_mean_kernel(const float *block_sum
 // 1's partial values) and positions are put into LDS for 512 rows at a time.
 // Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 19, Pixtral 37.4 -> 27.1, 16 SmolVLM sequences
 // 197 -> 151 us.  Its vector instructions alone take 60 us there (16 exponentials of 8 clocks and 32 others of 2.7 per step and wave).
-template <int D, int NS1>
+template <int D, int NS1, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
@@ -431,7 +449,7 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     const int s_first = s_begin + split * sps, n_steps = max(min(sps, n_steps_all - s_first), 0);
     const uint16_t *qb = reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D;
     const float *lrow = a.lse2 + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad;
-    RowStream<D> rows;
+    RowStream<D, DIRECT> rows;
     rows.init(qb, (int64_t)a.n_q_heads * D * 2, a.n_q, s_first, lds, wave, lane);
     if (n_steps > 0) {
 #pragma unroll
@@ -439,7 +457,7 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
             rows.issue(i);
     }
     // the keys come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
-    RowStream<D> keys;
+    RowStream<D, DIRECT> keys;
     keys.init(reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + blk0) * D, D * 2, a.n_keys - blk0, 0, lds, wave, lane);
     keys.issue(1);
     // log-sum-exps over all keys (in log2 units) and positions of rows row0 .. row0 + WINDOW - 1
@@ -931,14 +949,14 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const unsigned char *s
     }
 }
 
-template <int D>
+template <int D, bool DIRECT>
 void launch_colsum(int ns1, dim3 grid, hipStream_t st, const ScoreArgs &a)
 {
     switch (ns1) {
-    case 1:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 1>), grid, dim3(256), 0, st, a); break;
-    case 2:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 2>), grid, dim3(256), 0, st, a); break;
-    case 4:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 4>), grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 8>), grid, dim3(256), 0, st, a); break;
+    case 1:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 1, DIRECT>), grid, dim3(256), 0, st, a); break;
+    case 2:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 2, DIRECT>), grid, dim3(256), 0, st, a); break;
+    case 4:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 4, DIRECT>), grid, dim3(256), 0, st, a); break;
+    default: hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 8, DIRECT>), grid, dim3(256), 0, st, a); break;
     }
 }
 
@@ -1029,16 +1047,22 @@ size_t compress_most(int batch, int n_heads, int head_dim, int n_q, int vis_len,
     return DREAM_WORKSPACE_MIN_BYTES + align_up(lse, 256) + align_up(part, 256);
 }
 
-// calls f with the head dimension as a compile-time constant
+// calls f with the head dimension, and whether the rows of q and k are 16-byte aligned (see RowStream), as compile-time constants
 template <class F>
-void with_dim(int head_dim, F f)
+void with_rows(int head_dim, const void *q, const void *k, F f)
 {
-    if (head_dim == 64)
-        f(std::integral_constant<int, 64>{});
-    else if (head_dim == 128)
-        f(std::integral_constant<int, 128>{});
+    auto with_dim = [&](auto direct) {
+        if (head_dim == 64)
+            f(std::integral_constant<int, 64>{}, direct);
+        else if (head_dim == 128)
+            f(std::integral_constant<int, 128>{}, direct);
+        else
+            f(std::integral_constant<int, 256>{}, direct);
+    };
+    if (((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k)) & 15) == 0)   // (a row is D * 2 bytes, a multiple of 128)
+        with_dim(std::true_type{});
     else
-        f(std::integral_constant<int, 256>{});
+        with_dim(std::false_type{});
 }
 
 // the selection kernel's dynamic LDS holds up to DREAM_MAX_VISUAL scores: raise its limit once
@@ -1131,11 +1155,12 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
                 return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grids", who, n_q);
             const dim3 g1(desc->n_q_heads, p.units1, desc->batch), g2(desc->n_q_heads, p.units2, desc->batch);
             // pass 1 (the rows' log-sum-exps) only when the caller does not bring them
-            with_dim(desc->head_dim, [&](auto dim) {
+            with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
                 constexpr int D = decltype(dim)::value;
+                constexpr bool DIRECT = decltype(direct)::value;
                 if (!row_lse_in)
-                    hipLaunchKernelGGL((scores_lse_bf16_kernel<D, false>), g1, dim3(256), 0, st, a);
-                launch_colsum<D>(a.ns1, g2, st, a);
+                    hipLaunchKernelGGL((scores_lse_bf16_kernel<D, false, DIRECT>), g1, dim3(256), 0, st, a);
+                launch_colsum<D, DIRECT>(a.ns1, g2, st, a);
             });
         } else {
             if (n_q > 65535 * 1)
@@ -1231,8 +1256,8 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
         if (p.units1 > 65535)
             return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grid", who, n_q);
         dim3 g1(desc->n_q_heads, p.units1, desc->batch);
-        with_dim(desc->head_dim, [&](auto dim) {
-            hipLaunchKernelGGL((scores_lse_bf16_kernel<decltype(dim)::value, true>), g1, dim3(256), 0, st, a);
+        with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
+            hipLaunchKernelGGL((scores_lse_bf16_kernel<decltype(dim)::value, true, decltype(direct)::value>), g1, dim3(256), 0, st, a);
         });
     } else {
         if (n_q > 65535)

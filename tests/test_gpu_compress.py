@@ -286,3 +286,40 @@ def test_every_score_is_a_token_even_the_lowest_key(gu, v, num, den):
     want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1) + 3
     assert np.array_equal(kept, want)
     assert np.array_equal(gathered, oracle.gather_rows(rows, "bf16", want.astype(np.int32)))
+
+
+@pytest.mark.parametrize("D,P,v", [(64, 333, 300), (128, 200, 129), (256, 97, 64)])
+@pytest.mark.parametrize("shift_q,shift_k", [(1, 0), (0, 3), (4, 4)])
+def test_rows_that_are_not_16_byte_aligned(gu, D, P, v, shift_q, shift_k):
+    """q and the cache as slices that start a few elements into a larger buffer: the loads straight to LDS need 16-byte alignment, so these
+    calls take another way, with the same bits in every result (both score passes, positions, the entropy)."""
+    import torch
+    import paper_2505_19201_amd as dream
+    q = di.normal((2, P, 4, D), "bf16", 1301 + P, di.STREAM_PREFILL_Q)
+    k = di.normal((2, 2, P + 1, D), "bf16", 1302 + P, di.STREAM_K)
+    pos = dream.to_device(np.stack([di.rng(1303 + P, di.STREAM_SCORES).permutation(P) for _ in range(2)]).astype(np.int32))
+    desc = dream.attn_desc(2, 4, 2, D, dream.BF16, P + 1)
+
+    def placed(a, shift):
+        flat = torch.zeros(a.size + 16, dtype=torch.bfloat16, device="cuda")
+        t = flat[shift:shift + a.size].view(a.shape)
+        assert t.data_ptr() % 16 == shift * 2 and t.is_contiguous()
+        return t.copy_(dream.to_device(a, "bf16"))
+
+    def results(sq, sk):
+        dq, dk = placed(q, sq), placed(k, sk)
+        out = []
+        for p in (None, pos):
+            scores = torch.full((2, v), float("nan"), device="cuda")
+            kept = torch.full((2, oracle.keep_count(v, 1, 2)), -7, dtype=torch.int32, device="cuda")
+            dream.dream_visual_compress(desc, dq, p, P, dk, P, 0, v, 1, 2, None, scores, kept, None, 0, None, 0,
+                                        gu.workspace(dream.dream_visual_compress_workspace(desc, P, v)))
+            row = torch.full((2, 4, P), float("nan"), device="cuda")
+            ae = torch.full((2,), float("nan"), device="cuda")
+            dream.dream_attention_entropy(desc, dq, p, P, dk, P, row, ae, gu.workspace(dream.dream_attention_entropy_workspace(desc, P)))
+            out += [scores, kept, row, ae]
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in out]
+
+    for got, want in zip(results(shift_q, shift_k), results(0, 0)):
+        assert np.isfinite(got).all() and np.array_equal(got, want)
