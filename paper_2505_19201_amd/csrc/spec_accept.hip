@@ -741,15 +741,16 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
     const int seg_chunks = ceil_div(n_chunks, MAX_SEG), n_seg = ceil_div(n_chunks, seg_chunks);
     const int n_wg = std::max(1, std::min(n_seg, 256 / batch));
     // the slots exist with more than one segment only, so they fit where a row of floats per sequence does
-    char *wsb = static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES;
+    // (aligned here, in the room the first DREAM_WORKSPACE_MIN_BYTES leave: a slot is one 64-bit word to readers and writers only where it is aligned)
+    char *wsb = reinterpret_cast<char *>(align_up(reinterpret_cast<uintptr_t>(workspace), DREAM_WORKSPACE_MIN_BYTES));
     uint64_t *slots = n_wg > 1 ? reinterpret_cast<uint64_t *>(wsb) : nullptr;
     static_assert(SLOTS * sizeof(uint64_t) <= 3 * sizeof(float) * STAT_CHUNK, "the slots of a sequence fit its part of the workspace");
     float *stat_m = reinterpret_cast<float *>(wsb + align_up((size_t)batch * 3 * vocab * sizeof(float), 256));
     float *stat_s = reinterpret_cast<float *>(reinterpret_cast<char *>(stat_m) + stats);
     const int esz = logits_dtype == DREAM_BF16 ? 2 : 4;
     const bool vec = vocab % 8 == 0 &&
-                     ((reinterpret_cast<uintptr_t>(target_logits) | reinterpret_cast<uintptr_t>(draft_logits) |
-                       reinterpret_cast<uintptr_t>(workspace)) & 15) == 0 && ((size_t)vocab * esz) % 16 == 0;
+                     ((reinterpret_cast<uintptr_t>(target_logits) | reinterpret_cast<uintptr_t>(draft_logits)) & 15) == 0 &&
+                     ((size_t)vocab * esz) % 16 == 0;
     const float inv_temp = 1.0f / temperature;
     hipStream_t st = as_stream(stream);
     const dim3 sgrid(n_chunks, batch * n_tree, 2);

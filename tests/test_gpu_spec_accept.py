@@ -192,3 +192,30 @@ def test_workgroups_of_a_sequence(gu, V, polls):
         _case(gu, 3 if V > 100000 else 8, 21, 5, V, "f32", 970 + V, noise=1.0, min_clear=0.0)
     finally:
         dream.dream_set_accept_spin(0)
+
+
+@pytest.mark.parametrize("V", [1000, 24577, 65536])
+@pytest.mark.parametrize("offset", [1, 4, 72, 255])
+def test_workspace_at_any_address(gu, V, offset):
+    """The workgroups of a sequence exchange 64-bit words in the workspace, which may start at any byte: same results as with an aligned
+    one, and nothing written outside the bytes handed over."""
+    import torch
+    import paper_2505_19201_amd as dream
+    B, T, depth = 4, 21, 5
+    g = di.rng(980 + V, 700)
+    parent = np.stack([di.random_tree(T, depth, 981, b) for b in range(B)])
+    t32 = di.normal((B, T, V), "f32", 982, di.STREAM_LOGITS) * np.float32(2.0)
+    d32 = t32 + di.normal((B, T, V), "f32", 983, di.STREAM_DRAFT_LOGITS)
+    token = _draft_children(parent, d32.astype(np.float64), g)
+    ua, ub = g.uniform(size=(B, T)).astype(np.float32), g.uniform(size=B).astype(np.float32)
+    want = gu.run_spec_accept(t32, d32, "f32", token, parent, ua, ub, depth)
+    need = dream.dream_spec_accept_workspace(B, T, V)
+    buf = torch.full((offset + need + 300,), 0xFF, dtype=torch.uint8, device="cuda")
+    dev = [dream.to_device(np.ascontiguousarray(a)) for a in (t32, d32, token.astype(np.int32), parent.astype(np.int32), ua, ub)]
+    out = [torch.full(s, -7, dtype=torch.int32, device="cuda") for s in ((B,), (B, depth + 1), (B,))]
+    dream.dream_spec_accept(dev[0], dev[1], dream.F32, B, T, V, dev[2], dev[3], dev[4], dev[5], depth, 1.0, *out, buf[offset:offset + need])
+    torch.cuda.synchronize()
+    for got, w in zip(out, want):
+        assert np.array_equal(got.cpu().numpy(), w)
+    outside = torch.cat([buf[:offset], buf[offset + need:]])
+    assert (outside == 0xFF).all()
