@@ -111,6 +111,11 @@ __device__ __forceinline__ void load8(const void *base, int64_t row, int t, int 
     }
 }
 
+// A token's exponential times its row's normaliser, and one step of the residual chain.  Written with explicit fused operations, so that
+// every loop that evaluates a token (in registers, from memory, at one token) gives it the same bits.
+__device__ __forceinline__ float token_mass(float logit, float inv_temp, float m, float inv_z) { return __expf(fmaf(logit, inv_temp, -m)) * inv_z; }
+__device__ __forceinline__ float residual(float P, float jp, float Q, float jq) { return fmaxf(fmaf(P, jp, -(Q * jq)), 0.0f); }
+
 // Exchange of the walk's partial sums: slots [B][2][2][MAX_SEG] of (round << 32 | float bits), cleared by
 // softmax_stats_kernel, which the stream orders before the walk.
 constexpr int MAX_SEG = 64;
@@ -215,7 +220,7 @@ struct WalkArgs {
 // itself, so the exchange is relaxed agent-scope loads and stores without fences.  Words of round r + 2 overwrite those
 // of round r: nobody publishes round r + 2 before having seen everybody's round r + 1, which everybody publishes after reading round r.
 // Nothing depends on the workgroups running at the same time: a wait is bounded, workgroup 0 sums missing segments itself
-// (the same arithmetic, so the same bits) and waits for nobody again, any other workgroup that waited in vain ends.
+// (token_mass and residual, added in the same order, so the same bits) and waits for nobody again, any other workgroup that waited in vain ends.
 // Only workgroup 0 writes results.
 template <bool BF16>
 __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
     // residual target and reduced draft of token t after the first n rejections at the current node
     auto chain = [&](int n, int t, float &P, float &Q) {
         for (int j = 0; j < n; j++) {
-            const float r = fmaxf(P * s_ip[j] - Q * s_iq[j], 0.0f);
+            const float r = residual(P, s_ip[j], Q, s_iq[j]);
             P = s_take[j] ? r : P;
             Q = t == s_x[j] ? 0.0f : Q;
         }
@@ -343,8 +348,8 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         load8<BF16>(a.dlogits, row, t, vocab, vec, dv);
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            v[j] = __expf(v[j] * inv_temp - mt) * ip;       // (0 past the end: the logits read as -inf there)
-            dv[j] = __expf(dv[j] * inv_temp - md) * iq;
+            v[j] = token_mass(v[j], inv_temp, mt, ip);      // (0 past the end: the logits read as -inf there)
+            dv[j] = token_mass(dv[j], inv_temp, md, iq);
         }
         for (int i = 0; i < n; i++) {
             const float jp = s_ip[i], jq = s_iq[i];
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
             const int x = s_x[i] - t;
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                const float r = fmaxf(v[j] * jp - dv[j] * jq, 0.0f);
+                const float r = residual(v[j], jp, dv[j], jq);
                 v[j] = take ? r : v[j];
                 dv[j] = x == j ? 0.0f : dv[j];
             }
@@ -380,8 +385,8 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
                 for (int h = 0; h < PER; h++)
 #pragma unroll
                     for (int j = 0; j < 8; j++) {
-                        rp[h][j] = __expf(rp[h][j] * inv_temp - mt) * ip;
-                        rq[h][j] = __expf(rq[h][j] * inv_temp - md) * iq;
+                        rp[h][j] = token_mass(rp[h][j], inv_temp, mt, ip);
+                        rq[h][j] = token_mass(rq[h][j], inv_temp, md, iq);
                     }
                 reg_n = 0;
             }
@@ -393,7 +398,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
                 for (int h = 0; h < PER; h++)
 #pragma unroll
                     for (int j = 0; j < 8; j++) {
-                        const float r = fmaxf(rp[h][j] * jp - rq[h][j] * jq, 0.0f);
+                        const float r = residual(rp[h][j], jp, rq[h][j], jq);
                         rp[h][j] = take ? r : rp[h][j];
                         rq[h][j] = x == h * NT * 8 + j ? 0.0f : rq[h][j];
                     }
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
             for (int h = 0; h < PER; h++)
 #pragma unroll
                 for (int j = 0; j < 8; j++)
-                    s += fmaxf(rp[h][j] * jp - rq[h][j] * jq, 0.0f);
+                    s += residual(rp[h][j], jp, rq[h][j], jq);
             v0 = block_sum(s, s_redf, tid);
             return;
         }
@@ -688,7 +693,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
                     load8<BF16>(a.tlogits, row, t, vocab, vec, v);
 #pragma unroll
                     for (int j = 0; j < 8; j++)
-                        v[j] = __expf(v[j] * inv_temp - mt) * ip;
+                        v[j] = token_mass(v[j], inv_temp, mt, ip);
                 });
             break;
         }
