@@ -196,8 +196,8 @@ constexpr int STEP = 128, STEP_BYTES = STEP * 2;     // elements, bytes of a row
 
 template <int MT, int NT>
 struct RowsGeom {
-    static constexpr int MP = MT <= 1 ? 1 : MT <= 2 ? 2 : MT <= 4 ? 4 : 8;        // row-tile slots
-    static constexpr int KS = RW / MP > 4 ? 4 : RW / MP;                          // waves that share a row tile's elements
+    static constexpr int MP = MT <= 2 ? 2 : MT <= 4 ? 4 : 8;                      // row-tile slots (at least 17 rows, so at least 2 tiles)
+    static constexpr int KS = RW / MP;                                            // waves that share a row tile's elements
     static constexpr int LOADS = 4 * (MT + NT);                                   // load instructions per step (1024 bytes: 4 row pieces)
     static constexpr int NLD = (LOADS + RW - 1) / RW;
     static constexpr int STAGE = LOADS * 1024;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step s has landed
             __syncthreads();                                      // everybody's has, and step s - 1 is no longer read
             issue(s + G::NS - 1);
-            if (mt < MT && kg < G::KS) {
+            if (mt < MT) {
                 const unsigned char *stage = smem + s % G::NS * G::STAGE;
 #pragma unroll
                 for (int i = 0; i < 4 / G::KS; i++) {
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
         __syncthreads();
         if (G::KS > 1) {                                          // sum the partial tiles of a row tile in wave order
             f32x4 *part = reinterpret_cast<f32x4 *>(smem);
-            if (mt < MT && kg > 0 && kg < G::KS)
+            if (mt < MT && kg > 0)
 #pragma unroll
                 for (int nt = 0; nt < NT; nt++)
                     part[(wave * NT + nt) * 64 + lane] = acc[nt];
@@ -384,10 +384,9 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
         a.job[j].tile_end = wgs;
     }
-    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size
+    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size (2 to 8 tiles: there are at least 17 rows)
     const int m_tiles = ceil_div(a.m_total, 16);
     switch (ceil_div(m_tiles, ceil_div(m_tiles, 8))) {
-    case 1: return launch_rows<1>(nt, wgs, st, a);
     case 2: return launch_rows<2>(nt, wgs, st, a);
     case 3: return launch_rows<3>(nt, wgs, st, a);
     case 4: return launch_rows<4>(nt, wgs, st, a);
