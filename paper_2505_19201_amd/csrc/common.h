@@ -25,6 +25,7 @@ int accept_spin_limit();
 // per-file parts of dream_init()
 int attn_init();
 int compress_init();
+int project_init();
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));

@@ -79,6 +79,8 @@ int dream_init(void)
     if (!rc)
         rc = compress_init();
     if (!rc)
+        rc = project_init();
+    if (!rc)
         rc = dream_accept_static_init();
     return rc;
 }

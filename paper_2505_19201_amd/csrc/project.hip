@@ -297,28 +297,55 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
     }
 }
 
+constexpr int MAX_MT = 8, MAX_NT = 3;
+
+// The dynamic-LDS limit of a variant is raised once (dream_init does it for all of them; a call that is first to a variant otherwise).
+// Two threads may both set it: harmless.
 template <int MT, int NT>
-int launch_rows(unsigned wgs, hipStream_t st, const ProjArgs &a)
+int ensure_rows_lds(const char *who)
 {
     static std::atomic<bool> attr_set{false};
     constexpr size_t bytes = RowsGeom<MT, NT>::LDS_BYTES;
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(&project_rows_kernel<MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
             hipSuccess)
-            return fail(DREAM_ERR_HIP, "dream_project_rows: cannot reserve %zu bytes of LDS", bytes);
+            return fail(DREAM_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", who, bytes);
         attr_set = true;
     }
-    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), dim3(wgs), dim3(64 * RW), bytes, st, a);
+    return DREAM_OK;
+}
+
+template <int MT, int NT>
+int launch_rows(unsigned wgs, hipStream_t st, const ProjArgs &a)
+{
+    if (int rc = ensure_rows_lds<MT, NT>("dream_project_rows"))
+        return rc;
+    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), dim3(wgs), dim3(64 * RW), (RowsGeom<MT, NT>::LDS_BYTES), st, a);
     return check_launch("project_rows_kernel");
 }
 
-template <int MT>
-int launch_rows(int nt, unsigned wgs, hipStream_t st, const ProjArgs &a)
-{
-    return nt == 1 ? launch_rows<MT, 1>(wgs, st, a) : nt == 2 ? launch_rows<MT, 2>(wgs, st, a) : launch_rows<MT, 3>(wgs, st, a);
-}
+// The variants, by row tiles per pass and feature tiles per workgroup: project_init walks the table, a call picks from it.
+struct RowsVariant {
+    int (*launch)(unsigned, hipStream_t, const ProjArgs &);
+    int (*ensure)(const char *);
+};
+#define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, 3>, &ensure_rows_lds<MT, 3>}}
+const RowsVariant ROWS[MAX_MT - 1][MAX_NT] = {ROWS_VARIANTS(2), ROWS_VARIANTS(3), ROWS_VARIANTS(4), ROWS_VARIANTS(5),
+                                              ROWS_VARIANTS(6), ROWS_VARIANTS(7), ROWS_VARIANTS(8)};
+#undef ROWS_VARIANTS
 
 }  // namespace
+
+namespace dream {
+int project_init()
+{
+    for (const auto &row : ROWS)
+        for (const RowsVariant &v : row)
+            if (int rc = v.ensure("dream_init"))
+                return rc;
+    return DREAM_OK;
+}
+}  // namespace dream
 
 extern "C" {
 
@@ -369,7 +396,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     // feature tiles per workgroup: the fewest bytes through the busiest CU
     int nt = 1;
     int64_t best = 0;
-    for (int t = 1; t <= 3; t++) {
+    for (int t = 1; t <= MAX_NT; t++) {
         int64_t wgs = 0;
         for (int j = 0; j < n_jobs; j++)
             wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, t);
@@ -386,15 +413,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     }
     // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size (2 to 8 tiles: there are at least 17 rows)
     const int m_tiles = ceil_div(a.m_total, 16);
-    switch (ceil_div(m_tiles, ceil_div(m_tiles, 8))) {
-    case 2: return launch_rows<2>(nt, wgs, st, a);
-    case 3: return launch_rows<3>(nt, wgs, st, a);
-    case 4: return launch_rows<4>(nt, wgs, st, a);
-    case 5: return launch_rows<5>(nt, wgs, st, a);
-    case 6: return launch_rows<6>(nt, wgs, st, a);
-    case 7: return launch_rows<7>(nt, wgs, st, a);
-    default: return launch_rows<8>(nt, wgs, st, a);
-    }
+    return ROWS[ceil_div(m_tiles, ceil_div(m_tiles, MAX_MT)) - 2][nt - 1].launch(wgs, st, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,

@@ -422,3 +422,21 @@ def test_a_projection_job_is_any_sequence_of_six(lib):
 
 class _NoStream:
     cuda_stream = 0
+
+
+def test_dream_init_raises_every_limit_and_launches_stay_within_it(lib, tmp_path):
+    """tests/c/launch_check.c stands in for HIP's launch functions: after dream_init no entry point sets a kernel attribute, and every
+    launch of a sweep over all entry points fits its kernel's LDS limit and the grid limits."""
+    import shutil
+    import subprocess
+    gcc = shutil.which("gcc")
+    if gcc is None:
+        pytest.skip("no gcc")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    libdir = os.path.dirname(dream.library_path())
+    exe = str(tmp_path / "launch_check")
+    subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-Werror", "-rdynamic", "-I", os.path.join(root, "include"),
+                    os.path.join(root, "tests", "c", "launch_check.c"), "-o", exe, "-L", libdir, "-ldream", "-Wl,-rpath," + libdir],
+                   check=True, capture_output=True, text=True)
+    p = subprocess.run([exe], capture_output=True, text=True)
+    assert p.returncode == 0, p.stdout[-3000:] + p.stderr[-1000:]
