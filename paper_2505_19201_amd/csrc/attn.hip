@@ -31,7 +31,6 @@
 // tensors (the small configuration).
 #include "common.h"
 #include "dream_tuning.h"
-#include <atomic>
 #include <math.h>
 
 using namespace dream;
@@ -1232,20 +1231,11 @@ int validate_desc(const dream_attn_desc *d, const char *who)
     return DREAM_OK;
 }
 
-// The dynamic-LDS limit of a kernel is raised once (dream_init does it for every variant up front; a variant
-// that is reached first by a call does it then).  Two threads may both set it once: harmless.
 template <int D, int QG, int KT, int PFD, int NW = 4, int MW = 1, bool ONCE = false, int KG = 1>
 int ensure_bf16_lds()
 {
-    using G = Geom<D, QG, KT * KG>;
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<D, QG, KT, PFD, NW, MW, ONCE, KG>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES) != hipSuccess)
-            return fail(DREAM_ERR_HIP, "attention: cannot reserve %zu bytes of LDS", G::LDS_BYTES);
-        attr_set = true;
-    }
-    return DREAM_OK;
+    static std::atomic<uint64_t> done{0};
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_bf16_kernel<D, QG, KT, PFD, NW, MW, ONCE, KG>), Geom<D, QG, KT * KG>::LDS_BYTES, "attention");
 }
 
 template <int D, int QG, int KT, int PFD, int NW = 4, int MW = 1, bool ONCE = false, int KG = 1>
@@ -1279,14 +1269,8 @@ struct WaveLds {
 template <int D, int NW, int DS, int QT = 1>
 int ensure_wave_lds()
 {
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)WaveLds<D, NW, DS, QT>::bytes) != hipSuccess)
-            return fail(DREAM_ERR_HIP, "attention: cannot reserve %zu bytes of LDS", WaveLds<D, NW, DS, QT>::bytes);
-        attr_set = true;
-    }
-    return DREAM_OK;
+    static std::atomic<uint64_t> done{0};
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT>), WaveLds<D, NW, DS, QT>::bytes, "attention");
 }
 
 template <int D, int NW, int DS, int QT = 1>

@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdarg.h>
+#include <atomic>
 #include "dream.h"
 
 namespace dream {
@@ -16,6 +17,10 @@ int check_launch(const char *what);
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// Raises the dynamic-LDS limit of `kernel` on the current device, once per device; `done` is the kernel's own mask of devices.  (dream_init does it
+// for every kernel, a call that is first to one otherwise.  Two threads may both do it: harmless.)
+int raise_lds_limit(std::atomic<uint64_t> &done, const void *kernel, size_t bytes, const char *who);
 
 int kv_splits_override();
 int q_tiles_override();

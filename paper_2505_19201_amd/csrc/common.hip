@@ -1,7 +1,6 @@
 // Error reporting, launch-shape overrides, the read-only measurement kernel and tree validation shared by all entry points.
 #include "common.h"
 #include "dream_tuning.h"
-#include <atomic>
 #include <string.h>
 
 namespace dream {
@@ -28,6 +27,20 @@ int check_launch(const char *what)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail(DREAM_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+    return DREAM_OK;
+}
+
+int raise_lds_limit(std::atomic<uint64_t> &done, const void *kernel, size_t bytes, const char *who)
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0)
+        return fail(DREAM_ERR_HIP, "%s: no current HIP device", who);
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;   // (devices past 64 have it raised every time)
+    if (done.load(std::memory_order_relaxed) & bit)
+        return DREAM_OK;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        return fail(DREAM_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", who, bytes);
+    done.fetch_or(bit, std::memory_order_relaxed);
     return DREAM_OK;
 }
 

@@ -14,7 +14,6 @@
 // gather copies the surviving rows of a [rows, row_elems] matrix.
 #include "common.h"
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 using namespace dream;
@@ -1065,17 +1064,11 @@ void with_rows(int head_dim, const void *q, const void *k, F f)
         with_dim(std::false_type{});
 }
 
-// the selection kernel's dynamic LDS holds up to DREAM_MAX_VISUAL scores: raise its limit once
+// the selection kernel's dynamic LDS holds up to DREAM_MAX_VISUAL scores
 int ensure_topk_lds(const char *who)
 {
-    static std::atomic<bool> attr_set{false};   // (two threads may both set the attribute once: harmless)
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_keep_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                DREAM_MAX_VISUAL * 4 + (256 + 32 + 4) * 4) != hipSuccess)
-            return fail(DREAM_ERR_HIP, "%s: cannot reserve LDS for the selection kernel", who);
-        attr_set = true;
-    }
-    return DREAM_OK;
+    static std::atomic<uint64_t> done{0};
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&topk_keep_kernel), DREAM_MAX_VISUAL * 4 + (256 + 32 + 4) * 4, who);
 }
 
 }  // namespace

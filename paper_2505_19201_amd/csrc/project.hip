@@ -16,7 +16,6 @@
 // LLaVA 243 -> 237 us, 8 SmolVLM sequences 285 -> 279; a single call on cold weights is 0-3 us faster but for LLaVA at 10
 // rows, 19.2 -> 20.6).
 #include "common.h"
-#include <atomic>
 
 using namespace dream;
 
@@ -299,20 +298,11 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
 
 constexpr int MAX_MT = 8, MAX_NT = 3;
 
-// The dynamic-LDS limit of a variant is raised once (dream_init does it for all of them; a call that is first to a variant otherwise).
-// Two threads may both set it: harmless.
 template <int MT, int NT>
 int ensure_rows_lds(const char *who)
 {
-    static std::atomic<bool> attr_set{false};
-    constexpr size_t bytes = RowsGeom<MT, NT>::LDS_BYTES;
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&project_rows_kernel<MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
-            hipSuccess)
-            return fail(DREAM_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", who, bytes);
-        attr_set = true;
-    }
-    return DREAM_OK;
+    static std::atomic<uint64_t> done{0};
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&project_rows_kernel<MT, NT>), RowsGeom<MT, NT>::LDS_BYTES, who);
 }
 
 template <int MT, int NT>

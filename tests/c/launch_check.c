@@ -1,7 +1,8 @@
 /* Host-only check of what the entry points ask HIP for.  This program defines the few HIP functions through which libdream sets
  * kernel attributes and launches, so its definitions are used instead of the runtime's and nothing reaches a device.
  *
- *   - dream_init() raises the dynamic-LDS limit of every kernel that needs it: no later call raises one (it might be under capture);
+ *   - dream_init() raises, for the current device, the dynamic-LDS limit of every kernel that needs it: no later call raises one (it
+ *     might be under capture);
  *   - no launch asks for more LDS than its kernel's limit (64 KB where none was raised), nor for an empty or oversized grid.
  */
 #include <stdio.h>
@@ -12,7 +13,7 @@ typedef struct { unsigned x, y, z; } grid3;
 
 enum { MAX_FUNCS = 256 };
 static const void *func[MAX_FUNCS];
-static int limit[MAX_FUNCS], launched[MAX_FUNCS], n_funcs, initialised, late, bad;
+static int limits[2][MAX_FUNCS], launched[MAX_FUNCS], n_funcs, initialised, late, bad, device;   /* two devices, each with limits of its own */
 static long launches;
 
 static int index_of(const void *f)
@@ -24,18 +25,19 @@ static int index_of(const void *f)
         exit(3);
     if (i == n_funcs) {
         func[n_funcs] = f;
-        limit[n_funcs++] = 65536;
+        limits[0][n_funcs] = limits[1][n_funcs] = 65536;
+        n_funcs++;
     }
     return i;
 }
-int hipGetDevice(int *device) { *device = 0; return 0; }
+int hipGetDevice(int *current) { *current = device; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetSymbolAddress(void **p, const void *symbol) { (void)symbol; *p = (void *)0x10000; return 0; }
 int hipFuncSetAttribute(const void *f, int attribute, int value)
 {
     (void)attribute;
     late += initialised;
-    limit[index_of(f)] = value > 65536 ? value : 65536;
+    limits[device][index_of(f)] = value > 65536 ? value : 65536;
     return 0;
 }
 /* (a launch is these two around the kernel's host stub, which calls hipLaunchKernel) */
@@ -58,12 +60,12 @@ int __hipPopCallConfiguration(grid3 *grid, grid3 *block, size_t *lds, void **str
 }
 int hipLaunchKernel(const void *f, grid3 grid, grid3 block, void **args, size_t lds, void *stream)
 {
-    const int i = index_of(f);
+    const int i = index_of(f), limit = limits[device][i];
     (void)args; (void)stream;
     launches++;
     launched[i]++;
-    if (lds > (size_t)limit[i] || lds > 163840 || !grid.x || !grid.y || !grid.z || grid.y > 65535 || grid.z > 65535 || block.x * block.y * block.z > 1024) {
-        printf("launch %ld: %zu bytes of LDS with a limit of %d, grid %u x %u x %u\n", launches, lds, limit[i], grid.x, grid.y, grid.z);
+    if (lds > (size_t)limit || lds > 163840 || !grid.x || !grid.y || !grid.z || grid.y > 65535 || grid.z > 65535 || block.x * block.y * block.z > 1024) {
+        printf("launch %ld: %zu bytes of LDS with a limit of %d, grid %u x %u x %u\n", launches, lds, limit, grid.x, grid.y, grid.z);
         bad++;
     }
     return 0;
@@ -78,16 +80,12 @@ static void expect(int status, int line)
 }
 #define OK(call) expect(call, __LINE__)
 
-int main(void)
+static void sweep(void)
 {
     static const int dims[3] = {64, 128, 256};
     void *const p = (void *)0x10000;         /* never dereferenced: nothing runs */
     const size_t all = (size_t)1 << 40;
-    int i, j, b, raised = 0;
-    OK(dream_init());
-    initialised = 1;
-    for (i = 0; i < n_funcs; i++)
-        raised += limit[i] > 65536;
+    int i, j, b;
     for (i = 0; i < 3; i++) {
         static const int rows[] = {1, 16, 17, 32, 33, 48, 64, 65, 80, 96, 97, 112, 113, 128, 129, 300};
         static const int heads[] = {1, 8, 32, 64, 200};
@@ -130,9 +128,27 @@ int main(void)
         }
     for (i = 1; i <= DREAM_MAX_POOL; i *= 2)
         OK(dream_tree_finalize(p, p, p, 4, i, 59, p, p, p, NULL, NULL));
-    for (i = j = 0; i < n_funcs; i++)
-        j += launched[i] > 0 && limit[i] > 65536;
-    printf("%d kernels with a raised limit, %d of them launched; raised after dream_init: %d; bad: %d; kernels seen: %d; launches: %ld\n", raised, j, late,
-           bad, n_funcs, launches);
-    return late || bad || !launches || !j;
+}
+
+int main(void)
+{
+    int i, used, raised;
+    for (device = 0; device < 2; device++) {
+        launches = 0;
+        initialised = raised = used = 0;
+        OK(dream_init());
+        initialised = 1;
+        for (i = 0; i < n_funcs; i++) {
+            raised += limits[device][i] > 65536;
+            launched[i] = 0;
+        }
+        sweep();
+        for (i = 0; i < n_funcs; i++)
+            used += launched[i] > 0 && limits[device][i] > 65536;
+        printf("device %d: %d kernels with a raised limit, %d of them launched; raised after dream_init: %d; bad: %d; kernels seen: %d; launches: %ld\n",
+               device, raised, used, late, bad, n_funcs, launches);
+        if (late || bad || !launches || !used)
+            return 1;
+    }
+    return 0;
 }
