@@ -1109,8 +1109,12 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
     // head_dim 128, 16 query tiles: 47-52 us whatever the number of workgroups up to one per CU, against 38-42 us of two 4-wave
     // workgroups per CU and 62-76 us of more; up to 8 query tiles: 33-36 us against 37-40 us of two per CU; head_dim 256: 58-70 us
     // against 52 us of one per CU and 102 us of two, and with up to 4 query tiles (where it replaces a second
-    // key split as well, unless the range is long) 41-50 us against 50 us of one per CU and 37-43 us of two splits (14 key
-    // tiles: 19 us against 23-27 us of two splits).
+    // key split as well, unless the range is long) 41-50 us against 50 us of one per CU and 37-43 us of two splits (32 key
+    // tiles: 34 us against 35-38; three splits win earlier, 72 workgroups: 27.1 against 27.8 us at 24 tiles, 33.6 against 30.7 at 32).
+    // The other lines hold at every length from 8 to 130 tiles: 17 sequences, head_dim 128, 16 query tiles 16.6 against 20.2 and 125
+    // against 174 us, 8 query tiles 12.1 against 13.3 and 94 against 105 us, head_dim 256 18.3 against 31.2 and 162 against 283 us,
+    // its 4 query tiles 14.4 against 16.6 and 117 against 142 us; 16 sequences are still faster with 4 waves (114.6 against 130.2,
+    // 62.9 against 98.6, 147 against 164 us at 130 tiles).
     {
         const int tw = tile_waves_override();
         const int qg8_max = d->head_dim == 256 ? 1 : 2;
@@ -1118,7 +1122,7 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
         const bool can8 = d->dtype == DREAM_BF16 && d->head_dim >= 128 && kv_splits_override() <= 1 && tw != 4;
         const int64_t wg4 = base * ceil_div(n_qtiles, 4);
         const bool few = n_qtiles <= 4;        // (at head_dim 128: see the two key groups below)
-        const bool full = few ? d->head_dim == 256 && (wg4 > 128 || (wg4 > 64 && tiles <= 32)) : wg4 > (qg8 == 2 ? 512 : 256);
+        const bool full = few ? d->head_dim == 256 && (wg4 > 128 || (wg4 > 64 && tiles <= (wg4 <= 85 ? 24 : 32))) : wg4 > (qg8 == 2 ? 512 : 256);
         const bool want8 = (tw == 8 && !few) || (tw == 0 && q_tiles_override() == 0 && full);
         // (the 8-wave variants read K/V with the nontemporal hint, so a KV head must not need two of them)
         if (can8 && want8 && ceil_div(n_qtiles, 8 * qg8) == 1) {
@@ -1137,9 +1141,12 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
         s = (int)(256 / (base * p->n_qg));
         if (s > 8)
             s = 8;                           // more splits cost more in the merge than they save
-        // ... as do two or three of a short range whose workgroups can have two key groups instead (96 and 128 groups, 24 key
-        // tiles: 19.4 and 20.7 us in 2 splits, 16.3 and 16.5 us unsplit)
-        if (s <= 3 && d->head_dim <= 128 && tiles <= 64)
+        // ... as do two or three of a short range whose workgroups can have two key groups instead.  Unsplit against split, us at
+        // head_dim 128 (64 crosses at the same lengths): three splits, 72 groups: 15.9 / 17.2 at 24 key tiles, 18.9 / 18.4 at 32,
+        // 30.9 / 24.8 at 64, 84 groups: 18.9 / 20.5 at 32, 26.5 / 25.4 at 52; two splits, 88 groups: 22.6 / 23.3 at 42, 26.4 / 26.3
+        // at 52, 31.1 / 29.6 at 64, 128 groups: 16.4 / 20.7 at 24, 31.3 / 32.3 at 64, 37.8 / 36.5 at 80
+        const int64_t groups = base * p->n_qg;
+        if (d->head_dim <= 128 && s <= 3 && tiles <= (s == 3 ? 32 : groups <= 96 ? 52 : 64))
             s = 1;
     }
     if (s > tiles)

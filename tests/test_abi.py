@@ -440,3 +440,21 @@ def test_dream_init_raises_every_limit_and_launches_stay_within_it(lib, tmp_path
                    check=True, capture_output=True, text=True)
     p = subprocess.run([exe], capture_output=True, text=True)
     assert p.returncode == 0, p.stdout[-3000:] + p.stderr[-1000:]
+
+
+@pytest.mark.parametrize("B,hq,hkv,D,n_tree,line,short,long", [
+    # three splits or two against one workgroup with two key groups, at the key tile where the measurements cross
+    (9, 8, 1, 128, 60, 32, "attn_bf16_kernel<128,1,1,2,8,1,0,2> workgroups=72 splits=1", "attn_bf16_kernel<128,1,1,2> workgroups=216 splits=3"),
+    (3, 28, 4, 64, 60, 32, "attn_bf16_kernel<64,1,2,2,8,1,0,2> workgroups=84 splits=1", "attn_bf16_kernel<64,1,2,2> workgroups=252 splits=3"),
+    (11, 16, 2, 128, 30, 52, "attn_bf16_kernel<128,1,1,2,8,1,0,2> workgroups=88 splits=1", "attn_bf16_kernel<128,1,1,2> workgroups=176 splits=2"),
+    (3, 32, 32, 128, 60, 52, "attn_bf16_kernel<128,1,1,2,8,1,1,2> workgroups=96 splits=1", "attn_bf16_kernel<128,1,1,2,4,1,1> workgroups=192 splits=2"),
+    (2, 64, 8, 128, 60, 64, "attn_bf16_kernel<128,1,1,2,8,1,0,2> workgroups=128 splits=1", "attn_bf16_kernel<128,1,1,2> workgroups=256 splits=2"),
+    # head_dim 256, up to 4 query tiles: the 8-wave form against three splits and two
+    (9, 8, 8, 256, 60, 24, "attn_bf16_kernel<256,1,1,2,8> workgroups=72 splits=1", "attn_bf16_kernel<256,1,1,2,4,1,1> workgroups=216 splits=3"),
+    (12, 8, 8, 256, 60, 32, "attn_bf16_kernel<256,1,1,2,8> workgroups=96 splits=1", "attn_bf16_kernel<256,1,1,2,4,1,1> workgroups=192 splits=2"),
+])
+def test_launch_plans_on_both_sides_of_a_length_line(lib, B, hq, hkv, D, n_tree, line, short, long):
+    """The lengths at which a plan changes (attn.hip names the times on both sides), one key tile of 32 before and after."""
+    desc = dream.attn_desc(B, hq, hkv, D, dream.BF16, 4200)
+    assert dream.dream_attn_plan_describe(desc, n_tree, line * 32).startswith(short)
+    assert dream.dream_attn_plan_describe(desc, n_tree, line * 32 + 1).startswith(long)
