@@ -177,8 +177,8 @@ int dream_accept_path(const void *logits, int32_t logits_dtype, int32_t batch, i
  * dream_accept_path without the workspace: the per-chunk partial results live in a scratch array inside the
  * library (DREAM_ACCEPT_STATIC_SCRATCH_BYTES of device memory per GPU, held until the process ends).  The
  * call allocates nothing and frees nothing.
- *   Limit: batch * n_tree * ceil(vocab / 8192) partial results of 8 bytes (two arrays, each rounded up to
- *   256 bytes) must fit the scratch: up to 131040 of them, e.g. 32 sequences x 60 nodes at a vocabulary
+ *   Limit: batch * n_tree * ceil(vocab / 8192) partial results of 8 bytes (counted as two parts of 4
+ *   bytes, each rounded up to 256 bytes) must fit the scratch: up to 131040 of them, e.g. 32 sequences x 60 nodes at a vocabulary
  *   of 524288; larger problems return DREAM_ERR_UNSUPPORTED (use dream_accept_path).
  *   Every call on a GPU shares that GPU's scratch: calls that overlap on one GPU (two streams, two host
  *   threads) race; calls ordered on one stream do not.  Nothing in the scratch has to start at zero.
@@ -299,6 +299,10 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
  *              of the cache keeps its content).  Uses desc->batch, head_dim (D), dtype (bf16 only),
  *              s_max.  hidden must be a multiple of 256, D of 16; x, w, out 16-byte aligned.
  *              A destination row outside [0, s_max) is dropped (nothing is written for it).
+ * A call repeated with the same arguments gives the same bits.  The order in which an output's products are added
+ * depends on B * n_rows, and above 16 rows also on the call's jobs and the output's place among them: the same row and
+ * weights may round to neighbouring bf16 values in calls of different shape, or in dream_project_rows and
+ * dream_project_rows_multi.
  * dream_project_rows_multi runs up to DREAM_MAX_PROJ_JOBS such maps over the same B, n_rows and
  * hidden in ONE launch (a draft level's W_Q, W_K and W_V: together they fill the chip where the
  * narrow K/V maps of a grouped-query model alone would not).  `jobs` is a host array read during

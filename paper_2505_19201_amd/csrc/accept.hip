@@ -5,15 +5,15 @@
 // the target's own choice at the last accepted node is emitted as the bonus token (Section 4).
 //
 // argmax_partial_kernel streams the logits once (16-byte loads, one workgroup per row chunk) and
-// reduces (value, index) pairs with wavefront shuffles; ties always keep the lower index, so the
-// result does not depend on how rows are chunked.  accept_walk_kernel merges the chunk results and
-// walks the tree in node order in a single wavefront per sequence.
+// reduces (value, index) pairs with wavefront shuffles to one 64-bit key per chunk; ties always keep the lower
+// index, so the result does not depend on how rows are chunked.  accept_walk_kernel, one workgroup per sequence, merges
+// the chunk keys of a node with adjacent lanes; then one wave lets every node check its own path to the root.
 #include "common.h"
 #include <mutex>
 
 using namespace dream;
 
-// Scratch of dream_accept_path_static: the per-chunk (value, index) partial results live here instead of in a
+// Scratch of dream_accept_path_static: the per-chunk keys live here instead of in a
 // caller's workspace.  One copy per GPU, held until the process ends; host code only ever uses the address
 // hipGetSymbolAddress reports for the current device, never the symbol itself.
 static __device__ __align__(256) unsigned char scratch[DREAM_ACCEPT_STATIC_SCRATCH_BYTES];

@@ -21,7 +21,8 @@
 // Why several workgroups: one CU pulls about 50 GB/s, 20 us and more for one pass over two float32 rows of 131072
 // tokens, and the walk made one or more such passes for every second rejection at a node (three float arrays per sequence in the
 // workspace), after a launch that summed the first residual of every node of the tree, visited or not.  Measured, 4
-// sequences x 60 nodes x 131072 float32 logits: 200-245 us per call with one workgroup per sequence, 67-75 us here (22 us the statistics; a rejection about 4 us).
+// sequences x 60 nodes x 131072 float32 logits: 200-262 us per call with one workgroup per sequence, 61-81 us here, depending on how many
+// children the inputs make the walk reject (20 us the statistics; a rejection about 4 us).
 #include "common.h"
 #include <algorithm>
 #include <type_traits>
@@ -715,6 +716,8 @@ size_t dream_spec_accept_workspace(int32_t batch, int32_t n_tree, int32_t vocab)
 {
     if (batch < 1 || n_tree < 1 || vocab < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
+    // The size is part of the boundary: programs hold it as a number.  Of it the calls use the statistics' two arrays and SLOTS words per
+    // sequence, which sit where an earlier form of the walk kept three vocabulary rows; the rest is not touched.
     const size_t stats = align_up((size_t)2 * batch * n_tree * ceil_div(vocab, STAT_CHUNK) * sizeof(float), 256);
     return DREAM_WORKSPACE_MIN_BYTES + align_up((size_t)batch * 3 * vocab * sizeof(float), 256) + 3 * stats + align_up((size_t)batch * n_tree * 4 * sizeof(float), 256);
 }

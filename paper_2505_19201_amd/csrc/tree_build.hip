@@ -5,8 +5,9 @@
 //   logits, its k most probable tokens as candidate children with score = score(node) + log p(token | node),
 //   and the k best candidates of the level as the next frontier.
 //     expand_partial_kernel  one workgroup per 8192-logit chunk of a row: the chunk is read once (16-byte
-//       loads) into registers; block reductions give the chunk's maximum and sum of exponentials, then k rounds
-//       of a block-wide arg-max pick the chunk's k largest logits.  The order is (logit descending, token
+//       loads) into registers; it leaves the chunk's maximum and sum of exponentials and its k largest logits: the
+//       elements at or above a lower bound of the k-th are collected in LDS and ranked by counting (k rounds of a
+//       block-wide arg-max where ties make them too many).  The order is (logit descending, token
 //       ascending) and compares the logits themselves, so the chosen tokens are exact whatever the chunking.
 //     expand_merge_kernel    one workgroup per sequence, one wave per frontier row: merges the chunk partials
 //       (log-sum-exp; k rounds of a wave arg-max over the chunk candidates), writes tokens and scores, then
