@@ -922,7 +922,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a)
 {
     constexpr int LPK = D / 4, KPW = 64 / LPK, U = 8, PASS = 4 * KPW * U;   // lanes per key; keys per wave at a time; keys per pass
     __shared__ int32_t s_par[DREAM_MAX_TREE];
-    __shared__ float s_o[4][D];
+    __shared__ __attribute__((aligned(16))) float s_o[4][D];   // (written 16 bytes at a time)
     __shared__ float s_m[4], s_l[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
