@@ -458,3 +458,14 @@ def test_launch_plans_on_both_sides_of_a_length_line(lib, B, hq, hkv, D, n_tree,
     desc = dream.attn_desc(B, hq, hkv, D, dream.BF16, 4200)
     assert dream.dream_attn_plan_describe(desc, n_tree, line * 32).startswith(short)
     assert dream.dream_attn_plan_describe(desc, n_tree, line * 32 + 1).startswith(long)
+
+
+def test_a_workspace_for_the_longest_range_fits_every_shorter_call(lib):
+    """Programs query once, for the longest key range; the plans of shorter ranges (other splits, other kernels) never need more."""
+    for D in (64, 128, 256):
+        for hq, hkv in ((8, 8), (32, 8), (28, 4), (16, 8), (8, 1), (16, 2)):
+            for B in (1, 2, 3, 4, 6, 9, 11, 12, 16, 24):
+                desc = dream.attn_desc(B, hq, hkv, D, dream.BF16, 4200)
+                for n_q in (1, 10, 33, 60):
+                    need = [dream.dream_tree_verify_attn_workspace(desc, n_q, tiles * 32) for tiles in range(2, 131, 3)]
+                    assert need == sorted(need), (D, hq, hkv, B, n_q)

@@ -219,3 +219,27 @@ def test_workspace_at_any_address(gu, V, offset):
         assert np.array_equal(got.cpu().numpy(), w)
     outside = torch.cat([buf[:offset], buf[offset + need:]])
     assert (outside == 0xFF).all()
+
+
+@pytest.mark.parametrize("V,dtype", [(24577, "f32"), (65536, "bf16"), (131072, "f32")])
+def test_whoever_sums_a_segment_the_result_is_the_same(gu, V, dtype):
+    """Every result, close calls included, is the same whether the workgroups exchange their sums or workgroup 0 forms them all
+    (polls < 0): one sum kept in registers from rejection to rejection, the other recomputed from the logits.  Identical draft and
+    target rows but for a few tokens make the masses small and the comparisons close."""
+    import paper_2505_19201_amd as dream
+    B, T, depth = 16, 33, 6
+    g = di.rng(990 + V, 700)
+    parent = np.stack([di.random_tree(T, depth, 991, b) for b in range(B)])
+    t32 = di.normal((B, T, V), "f32", 992, di.STREAM_LOGITS) * np.float32(2.0)
+    d32 = t32 + di.normal((B, T, V), "f32", 993, di.STREAM_DRAFT_LOGITS) * (g.random((B, T, 1)) < 0.7).astype(np.float32)
+    tl, dl = (t32, d32) if dtype == "f32" else (di.f32_to_bf16_bits(t32), di.f32_to_bf16_bits(d32))
+    token = np.argsort(-t32[:, 0], axis=1)[:, :T].astype(np.int32)            # likely tokens, so that siblings are rejected one after the other
+    ua, ub = g.uniform(0.5, 1.0, size=(B, T)).astype(np.float32), g.uniform(size=B).astype(np.float32)
+    want = gu.run_spec_accept(tl, dl, dtype, token, parent, ua, ub, depth)
+    dream.dream_set_accept_spin(-1)
+    try:
+        got = gu.run_spec_accept(tl, dl, dtype, token, parent, ua, ub, depth)
+    finally:
+        dream.dream_set_accept_spin(0)
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
