@@ -21,8 +21,9 @@ extern "C" {
  * it again after changing either, and change neither while another thread is inside an attention call. */
 void dream_set_kv_splits(int32_t n_splits);
 void dream_set_q_tiles(int32_t q_tiles);
-/* Waves per workgroup of the shared-tile kernel: 4 = never the 8-wave form, 8 = the 8-wave form wherever it exists
- * (bf16, head_dim >= 128, unsplit key range), 0 = automatic. */
+/* Waves per workgroup of the shared-tile kernel: 4 = never one of the 8-wave forms, 8 = one wherever it exists (bf16, unsplit
+ * key range: one workgroup per KV head at head_dim >= 128 with 5 query tiles or more, two key groups at head_dim <= 128),
+ * 0 = automatic. */
 void dream_set_tile_waves(int32_t waves);
 
 /* Polls after which a workgroup of dream_spec_accept stops waiting for the others of its sequence (workgroup 0 then
@@ -32,7 +33,7 @@ void dream_set_accept_spin(int32_t polls);
 /* Host-only: the names of all bf16 attention kernel variants the launch plan can choose, separated by ';', in the
  * spelling dream_attn_plan_describe uses ("attn_wave_kernel<128,8,2,1>": head_dim, waves, column slices, query tiles
  * per workgroup; "attn_bf16_kernel<128,1,1,2>": head_dim, query tiles per wave, key tiles per step, steps in flight;
- * a fifth argument 8 marks the form with 8 waves per workgroup).
+ * a fifth argument 8 marks the forms with 8 waves per workgroup, an eighth the number of key groups).
  * The tests use it to make sure every variant has a parity case.  0, or -1 if buf is too small. */
 int dream_attn_variants(char *buf, size_t buf_bytes);
 

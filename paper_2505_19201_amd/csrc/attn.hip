@@ -7,7 +7,7 @@
 // bf16, shared tiles (attn_bf16_kernel).  A workgroup serves one (sequence, KV head, key-range split, query
 // group).  The query rows that share a KV head - every tree row of every query head of the GQA
 // group - are cut into 16-row tiles; each wave owns QG of them (4 waves, or 8 waves for grouped-query shapes, or
-// 8 waves as two key groups for multi-head shapes with one workgroup per CU).  All threads stream the key range in
+// 8 waves as two key groups where a CU gets one workgroup).  All threads stream the key range in
 // 32-key K/V tiles with 16-byte coalesced loads kept one or two steps ahead in registers, park each tile in one of
 // two LDS stages (one barrier per step), and every wave reads the tile's MFMA fragments from LDS: a K/V byte leaves
 // HBM once and serves all tree rows and all heads of the group.  Scores are formed transposed, S^T = K Q^T, with
@@ -392,7 +392,7 @@ __device__ __forceinline__ void state_merge(WaveState<QG, NDT> &s, const float *
 
 // KG: key groups (1 or 2).  With 2, the 8 waves are two groups of 4: both serve the same (up to 4·QG) query tiles, a step
 // stages 2·KT tiles and each group computes its KT of them; the two partial states of a query tile meet in LDS at the
-// end.  For multi-head shapes with few streams per CU: twice the waves and twice the bytes in flight per workgroup.
+// end.  Where a CU gets at most one workgroup: twice the waves and twice the bytes in flight.
 template <int D, int QG, int KT, int PFD, int NW = 4, int MW = 1, bool ONCE = false, int KG = 1>
 __global__ __launch_bounds__(64 * NW, (QG == 1 && D <= 128) ? (NW == 4 ? DREAM_Q1_WAVES : DREAM_W8Q1_WAVES) : 1) void attn_bf16_kernel(AttnArgs a)
 {
