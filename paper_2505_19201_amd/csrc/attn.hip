@@ -18,20 +18,21 @@
 // score exceeds it by 8 octaves, so accumulators are rescaled a handful of times per call.  Where a workgroup is the
 // only reader of its K/V rows the loads carry the nontemporal hint; output rows leave as whole lines with it.
 //
-// One CU can keep only a few tens of KB of loads in flight, so a short stream is bandwidth-starved
-// unless all 256 CUs pull a share of it: when B * Hkv * query groups is small either attn_wave_kernel serves a
-// query tile per workgroup in one launch (waves stream disjoint key tiles and merge in LDS), or the key range is
-// split over several workgroups, each writes its (reference, sum, O) state to the workspace, and
-// attn_merge_kernel merges the states of a group in split order (deterministic) and writes the
-// rows.  (A merge across workgroups inside one launch costs more than the second launch: the L2s of the XCDs are not
-// coherent with each other.)  Workgroups that read the same K/V stream get ids congruent mod 8 so that they run on one
-// XCD and share its L2.
+// bf16, few streams (attn_wave_kernel, attn_pair_kernel).  A CU pulls at most about 65 GB/s through its L1, so a short stream is
+// bandwidth-starved unless all 256 CUs pull a share of it.  While at most one workgroup per CU comes of it, the work of a KV head is cut into
+// query tiles and column slices only: a workgroup's waves stream disjoint key tiles, straight to LDS, and their states meet in LDS at
+// the end, in one launch.  Beyond the lengths where that pays, the key range is split over several workgroups of attn_bf16_kernel, each
+// writes its (reference, sum, O) state to the workspace, and attn_merge_kernel merges the states of a group in split order
+// (deterministic) and writes the rows.  (A merge across workgroups inside one launch costs more than the second launch: the L2s of
+// the XCDs are not coherent with each other.)  Workgroups that read the same K/V stream get ids congruent mod 8 so that they run on
+// one XCD and share its L2.
 //
 // fp32 path (attn_f32_kernel): vector-ALU kernel, one workgroup per (query row, head, sequence), used for float32
 // tensors (the small configuration).
 #include "common.h"
 #include "dream_tuning.h"
 #include <math.h>
+#include <type_traits>
 
 using namespace dream;
 
@@ -53,6 +54,7 @@ struct AttnArgs {
     int32_t n_streams;       // B * Hkv * n_splits
     int64_t s_max;
     float scale, scale_log2;
+    uint32_t nq_magic;       // for quick_div by n_q
 };
 
 // Visibility of the tree nodes to one query: bit (a % 64) of word a / 64 is set iff node a is visible.  MW = 1 serves
@@ -119,14 +121,13 @@ __device__ __forceinline__ NodeMask<MW> empty_mask()
     return m;
 }
 
-// D: head dimension (K rows, Q); DV: V columns handled (D, or a slice of it when the output columns are split)
-template <int D, int QG, int KT, int DV = D>
+template <int D, int QG, int KT>
 struct Geom {
     static constexpr int KSTR = D + 8;    // K row stride in LDS (elements): 16-byte pad, b128 reads spread over all banks
-    static constexpr int VSTR = DV + 16;  // V row stride in LDS (elements): 4 consecutive rows land 8 banks apart
+    static constexpr int VSTR = D + 16;  // V row stride in LDS (elements): 4 consecutive rows land 8 banks apart
     static constexpr int TILE_ELEMS = 32 * (KSTR + VSTR);   // one 32-key K tile followed by its V tile
     static constexpr int STAGE_ELEMS = KT * TILE_ELEMS;     // a step handles KT tiles
-    static constexpr int NDT = DV / 16;
+    static constexpr int NDT = D / 16;
     static constexpr int NKS = D / 32;
     static constexpr int CH = 32 * D / 8 / 256;             // 16-byte chunks per thread per tensor per tile
     static constexpr size_t LDS_BYTES = (size_t)2 * STAGE_ELEMS * 2 + DREAM_MAX_TREE * sizeof(int32_t);
@@ -189,6 +190,7 @@ __device__ __forceinline__ RowOwner row_owner(const AttnArgs &a, int kvh, int qg
 #ifndef DREAM_W8_PFD
 #define DREAM_W8_PFD 2   // steps in flight of the 8-wave shared-tile form
 #endif
+
 
 // Online softmax of KT 32-key tiles for the QG query tiles of a wave.  sacc holds the raw scores S^T (lane owns
 // query column c and key rows g*4+r of every 16-key block); on return pf holds the probabilities as the bf16 B
@@ -282,10 +284,10 @@ __device__ __forceinline__ void softmax_exponentials(const f32x4 (&sacc)[KT][2][
 
 // S^T = K Q^T for the KT 32-key tiles held in LDS at `stage` (K tile, then V tile, per 32 keys) x the (16 * QG) query
 // columns of this wave; independent accumulators keep the MFMA pipe full.
-template <int D, int QG, int KT, int DV = D>
+template <int D, int QG, int KT>
 __device__ __forceinline__ void tiles_scores(const uint16_t *stage, const bf16x8 (&qf)[QG][D / 32], f32x4 (&sacc)[KT][2][QG], int c, int g)
 {
-    using G = Geom<D, QG, KT, DV>;
+    using G = Geom<D, QG, KT>;
     constexpr int KSTR = G::KSTR, NKS = G::NKS;
 #pragma unroll
     for (int kt = 0; kt < KT; kt++) {
@@ -313,17 +315,17 @@ __device__ __forceinline__ void tiles_scores(const uint16_t *stage, const bf16x8
 }
 
 // Online softmax of the raw scores `sacc` of the KT tiles at `stage` (first key key0) and O^T += V^T P^T.
-template <int D, int QG, int KT, int DV = D, int MW>
+template <int D, int QG, int KT, int MW>
 __device__ __forceinline__ void tiles_softmax_pv(const uint16_t *stage, int key0, int P, int key_end, int n_tree, float scale_log2,
-                                                 f32x4 (&sacc)[KT][2][QG], const NodeMask<MW> (&qmask)[QG], WaveState<QG, DV / 16> &st, int c, int g)
+                                                 f32x4 (&sacc)[KT][2][QG], const NodeMask<MW> (&qmask)[QG], WaveState<QG, D / 16> &st, int c, int g)
 {
-    using G = Geom<D, QG, KT, DV>;
+    using G = Geom<D, QG, KT>;
     constexpr int KSTR = G::KSTR, VSTR = G::VSTR, NDT = G::NDT;
     // step touches tree rows, the ragged end or the next split (a negative scale also goes the general way)
     const bool needs_mask = key0 + KT * 32 > min(P, key_end) || scale_log2 < 0.0f;
     // ---- V^T fragments of the first tile (first half of the head dimension for D = 256) are requested
     // now, so their LDS latency hides behind the softmax arithmetic
-    constexpr int VH = DV == 256 ? 2 : 1, NDH = NDT / VH;
+    constexpr int VH = D == 256 ? 2 : 1, NDH = NDT / VH;
     s16x4 vfr[NDH][2];
     const int v_off = 32 * KSTR + (g * 4 + (c >> 2)) * VSTR + (c & 3) * 4;
     auto read_v = [&](int kt, int h) {
@@ -360,15 +362,15 @@ __device__ __forceinline__ void tiles_softmax_pv(const uint16_t *stage, int key0
 
 // QK^T, online softmax and PV for KT consecutive 32-key tiles held in LDS at `stage`, for the QG query tiles of this
 // wave.  key0 is the global key index of the first row.
-template <int D, int QG, int KT, int DV = D, int MW>
+template <int D, int QG, int KT, int MW>
 __device__ __forceinline__ void tiles_compute(const uint16_t *stage, int key0, int P, int key_end, int n_tree, float scale_log2,
                                               const bf16x8 (&qf)[QG][D / 32], const NodeMask<MW> (&qmask)[QG],
-                                              WaveState<QG, DV / 16> &st, int c, int g)
+                                              WaveState<QG, D / 16> &st, int c, int g)
 {
     f32x4 sacc[KT][2][QG];
-    tiles_scores<D, QG, KT, DV>(stage, qf, sacc, c, g);
+    tiles_scores<D, QG, KT>(stage, qf, sacc, c, g);
     __builtin_amdgcn_sched_barrier(0);
-    tiles_softmax_pv<D, QG, KT, DV, MW>(stage, key0, P, key_end, n_tree, scale_log2, sacc, qmask, st, c, g);
+    tiles_softmax_pv<D, QG, KT, MW>(stage, key0, P, key_end, n_tree, scale_log2, sacc, qmask, st, c, g);
 }
 
 // LDS traffic inside one wave needs no barrier, only program order.
@@ -541,7 +543,7 @@ __global__ __launch_bounds__(64 * NW, (QG == 1 && D <= 128) ? (NW == 4 ? DREAM_Q
         load_step(i + PFD, kr, vr);
         if (!wave_active)
             return;
-        tiles_compute<D, QG, KT, D, MW>(stage + kgrp * KT * G::TILE_ELEMS, (t_begin + (i * KG + kgrp) * KT) * 32, P, key_end, a.n_tree, a.scale_log2, qf,
+        tiles_compute<D, QG, KT, MW>(stage + kgrp * KT * G::TILE_ELEMS, (t_begin + (i * KG + kgrp) * KT) * 32, P, key_end, a.n_tree, a.scale_log2, qf,
                                         qmask, st, c, g);
     };
 
@@ -649,175 +651,6 @@ __device__ __forceinline__ void state_merge(WaveState<QG, NDT> &s, const float *
     }
 }
 
-// Short streams with few query tiles (one sequence; up to 4 query heads per KV head): a workgroup serves ONE 16-row query tile of one
-// head over the whole key range, its NW waves stream disjoint 32-key tiles (each through a private LDS
-// area, no workgroup barrier in the loop) and merge their states through LDS at the end, in a fixed
-// order.  No key split, so no second launch; the workgroups of a head re-read its K/V through the L2 of
-// one XCD.  With DS > 1 the output columns are split over DS workgroups: each computes all the scores
-// (reads all of K) but only its slice of V and of the output, which multiplies the CUs that pull data when
-// there are few query tiles and needs no merge across workgroups.
-// Grid: x = (query tile * DS + column slice) * 8 + XCD slot, y = KV head / 8, z = sequence, so that the
-// workgroups of one K/V stream share an XCD and the index arithmetic needs no division.  a.n_qg holds
-// the number of query tiles per KV head.
-//
-// Each wave keeps one tile in flight in registers: a CU holds about 64 KB of outstanding loads whatever is
-// asked of it, so a second tile in flight per wave only queues behind the first.
-// QT: query tiles a workgroup serves (1, or 2 when there are more (KV head, query tile) pairs than CUs: the
-// same K/V stream then feeds two tiles and half as many workgroups pull it).
-template <int D, int NW, int DS, int QT = 1>
-__global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a)
-{
-    constexpr int DV = D / DS;
-    using G = Geom<D, 1, 1, DV>;
-    constexpr int KSTR = G::KSTR, VSTR = G::VSTR, NDT = G::NDT, NKS = G::NKS;
-    constexpr int CHK = 32 * D / 8 / 64, CHV = 32 * DV / 8 / 64;   // 16-byte chunks per lane per tile of K, V
-    constexpr int STATE = StateGeom<DV, QT>::STATE_FLOATS;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    uint16_t *lds = reinterpret_cast<uint16_t *>(smem_raw);
-    int32_t *lds_parent = reinterpret_cast<int32_t *>(smem_raw + (size_t)NW * G::TILE_ELEMS * 2);
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, g = lane >> 4;
-    const int unit = blockIdx.x >> 3;
-    const int kvh = blockIdx.y * 8 + (blockIdx.x & 7), tq0 = (unit / DS) * QT, ds = unit % DS, b = blockIdx.z;
-    if (kvh >= a.n_kv_heads)
-        return;
-    const uint16_t *kbase = reinterpret_cast<const uint16_t *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
-    const uint16_t *vbase = reinterpret_cast<const uint16_t *>(a.v) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D + ds * DV;
-
-    int32_t my_parent = -1;
-    if (!a.tree_mask && tid < a.n_tree)
-        my_parent = a.parent[(int64_t)b * a.n_tree + tid];
-    const int P = (int)min((int64_t)max(a.prefix_len[b], 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
-    const int kv_len = P + a.n_tree;
-    const int t_end = (kv_len + 31) / 32;
-    const int n = t_end > wave ? (t_end - wave + NW - 1) / NW : 0;   // tiles of this wave: wave, wave + NW, ...
-
-    u32x4 kr[CHK], vr[CHV];
-    const int k_row = lane / (D / 8), k_col = lane % (D / 8), v_row = lane / (DV / 8), v_col = lane % (DV / 8);
-    // Unconditional (the tile index is clamped), so the number of loads in flight does not depend on
-    // control flow; the prefetch past the last tile re-reads it and is dropped.
-    auto issue = [&](int t) {
-        t = min(t, t_end - 1);
-#pragma unroll
-        for (int j = 0; j < CHK; j++) {
-            const int key = min(t * 32 + k_row + j * (512 / D), kv_len - 1);
-            kr[j] = *reinterpret_cast<const u32x4 *>(kbase + key * D + k_col * 8);
-        }
-#pragma unroll
-        for (int j = 0; j < CHV; j++) {
-            const int key = min(t * 32 + v_row + j * (512 / DV), kv_len - 1);
-            vr[j] = *reinterpret_cast<const u32x4 *>(vbase + key * D + v_col * 8);
-        }
-    };
-    issue(wave);
-
-    // the query tiles: head hh of the group, rows nt*16 .. nt*16+15 (at most 4 heads per group, so three compares instead of a division)
-    const int tph = a.tiles_per_head;
-    int row[QT], head[QT], node[QT];
-    bool valid[QT];
-    bf16x8 qf[QT][NKS];
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        const int tq = tq0 + qt;
-        const int hh = (tq >= tph) + (tq >= 2 * tph) + (tq >= 3 * tph), nt = tq - hh * tph;
-        row[qt] = nt * 16 + c;
-        valid[qt] = hh < a.group && row[qt] < a.n_q;     // (the second tile of the last pair may not exist)
-        head[qt] = kvh * a.group + (hh < a.group ? hh : 0);
-        const int rr = valid[qt] ? row[qt] : 0;
-        node[qt] = a.q_node ? min(max(a.q_node[(int64_t)b * a.n_q + rr], 0), a.n_tree - 1) : rr;
-        const uint16_t *qp = reinterpret_cast<const uint16_t *>(a.q) + (((int64_t)b * a.n_q + rr) * a.n_q_heads + head[qt]) * D + g * 8;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ks++)
-            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 32);
-    }
-    if (!a.tree_mask && tid < a.n_tree)
-        lds_parent[tid] = my_parent < tid ? my_parent : -1;   // a walk up the tree always ends
-    __syncthreads();
-    NodeMask<1> qmask[QT];
-    WaveState<QT, NDT> st;
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        qmask[qt] = valid[qt] ? visible_nodes<1>(a, b, node[qt], lds_parent) : empty_mask<1>();
-        if (!valid[qt]) {
-#pragma unroll
-            for (int ks = 0; ks < NKS; ks++)
-#pragma unroll
-                for (int i = 0; i < 8; i++)
-                    qf[qt][ks][i] = (__bf16)0.0f;
-        }
-        st.m[qt] = -INFINITY;
-        st.l[qt] = 0.0f;
-#pragma unroll
-        for (int dt = 0; dt < NDT; dt++)
-            st.o[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): from here on only tile prefetches are in flight
-
-    uint16_t *wt = lds + wave * G::TILE_ELEMS;
-    for (int i = 0; i < n; i++) {
-        const int t = wave + i * NW;
-        uint16_t *dk = wt + k_row * KSTR + k_col * 8, *dv = wt + 32 * KSTR + v_row * VSTR + v_col * 8;
-#pragma unroll
-        for (int j = 0; j < CHK; j++)
-            *reinterpret_cast<u32x4 *>(dk + j * (512 / D) * KSTR) = kr[j];
-#pragma unroll
-        for (int j = 0; j < CHV; j++)
-            *reinterpret_cast<u32x4 *>(dv + j * (512 / DV) * VSTR) = vr[j];
-        wave_lds_fence();
-        issue(t + NW);
-        tiles_compute<D, QT, 1, DV, 1>(wt, t * 32, P, kv_len, a.n_tree, a.scale_log2, qf, qmask, st, c, g);
-        wave_lds_fence();
-    }
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        float l = st.l[qt];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        st.l[qt] = l;
-    }
-    // merge the waves through LDS (the tile areas are free by then) in one round: every wave parks its
-    // state, then wave w sums the 16-wide output column tiles w, w+NW, ... over the states in wave order
-    float *mbuf = reinterpret_cast<float *>(smem_raw);
-    __syncthreads();
-    state_store<QT, NDT>(st, mbuf + wave * STATE, lane);
-    __syncthreads();
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        if (!valid[qt])
-            continue;
-        float mj[NW], m = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < NW; j++) {
-            mj[j] = mbuf[j * STATE + QT * NDT * 256 + (qt * 2) * 64 + lane];
-            m = fmaxf(m, mj[j]);
-        }
-        const float ms = (m == -INFINITY) ? 0.0f : m;
-        float l = 0.0f;
-#pragma unroll
-        for (int j = 0; j < NW; j++) {
-            mj[j] = __builtin_amdgcn_exp2f(mj[j] - ms);
-            l += mj[j] * mbuf[j * STATE + QT * NDT * 256 + (qt * 2 + 1) * 64 + lane];
-        }
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        uint16_t *op = reinterpret_cast<uint16_t *>(a.out) + (((int64_t)b * a.n_q + row[qt]) * a.n_q_heads + head[qt]) * D + ds * DV + g * 4;
-        for (int dt = wave; dt < NDT; dt += NW) {
-            f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int j = 0; j < NW; j++)
-                o += reinterpret_cast<const f32x4 *>(mbuf + j * STATE)[(qt * NDT + dt) * 64 + lane] * mj[j];
-            bf16x4 ob;
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                ob[r] = (__bf16)(o[r] * inv);
-            *reinterpret_cast<bf16x4 *>(op + dt * 16) = ob;
-        }
-        if (wave == 0 && ds == 0 && a.lse && g == 0)
-            a.lse[((int64_t)b * a.n_q_heads + head[qt]) * a.n_q + row[qt]] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
-    }
-}
-
 // Merge the split states of one (group, wave, query tile) in split order and write the rows.  One
 // workgroup of 4 waves per state; wave w owns the 16-wide output column tiles w, w+4, ...; loads of
 // up to 8 splits are in flight at once.
@@ -892,6 +725,483 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     }
     if (a.lse && g == 0 && w == 0)
         a.lse[((int64_t)b * a.n_q_heads + ro.head) * a.n_q + ro.row] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
+}
+
+// A few query tiles for one key stream (attn_wave_kernel, attn_pair_kernel).  A workgroup serves QS * QT query tiles of one KV head and one
+// slice of DV = D / DS output columns; its QS * KG waves are KG key groups, which take the KEYS-key tiles of the range in turn, times QS
+// query slots of QT tiles.  The key groups' states meet in LDS once, at the end.  The rows that share a KV head are numbered through
+// all heads of the group (row f is row f % n_q of head f / n_q), so only a KV head's last tile can be partly empty: 33 rows of 2 heads
+// are 5 tiles, not 6.
+//
+// What bounds such a launch is what a CU can pull: 60 to 75 GB/s whatever is in flight and however it is loaded (nothing but loads: 256
+// workgroups of 672 KB, four to a stream, 14.1 us; 8 to a stream of 1344 KB, 21.7 us), then the chain ahead of the first tile and
+// behind the last one.  So the work that goes with the bytes stays out of their way:
+// - Tiles go from memory straight to LDS, with no staging registers, no LDS write instructions and no barrier in the loop: with one slot
+//   a wave has its own tiles (K of the tile after next is requested when this tile's scores are formed, V of the next one when this
+//   tile's product is), with two the slots of a group share them, one loading K and one V into the stage that is free, and meet once a
+//   step.  The groups drift apart, so that some waves are in their exponentials while others are in their MFMAs (a barrier per step
+//   instead of the meeting: 14.6 us for the loop below instead of 11.2).
+// - A fragment read from LDS serves QT MFMAs; with one query tile per wave the LDS reads alone took half the time of such a kernel.  Four
+//   tiles in every wave need no slots, but twice the states to merge: 3.6 us of 20 at head_dim 128, against 2.2 with two slots.
+// - With DS slices the scores are formed DS times, but K and 1 / DS of V is all a workgroup pulls, and the states are small.
+// Measured per launch, the kernels these replaced / here: 32 heads x 764 keys x 60 rows 10.0 / 8.9 us; 4 sequences x 8 KV heads x up to 1316
+// keys x 33 rows of 2 heads, head_dim 256, 27.3 / 20.6 us; 8 sequences x 8 KV heads x up to 1340 keys x 60 rows of 4 heads 23.2 / 20.8 us
+// (start to scores 3 us, loop 11, states and rows 2.3).
+//
+// 16-byte chunk i of row r of a K tile sits at i ^ (r mod 16) (at head_dim 64, two rows to a bank line: i ^ (r/2 mod 8)), and pair i of the
+// chunks of a V row at i ^ (r mod 8) (slices of 64 columns: r/2 mod 4, of 32: r/4 mod 2), so that neither the 16-byte reads of K nor the
+// transposing reads of V meet in a bank.  The loads need 16-byte aligned tensors: others take attn_bf16_kernel.
+template <int D, int DS, int QT, int QS, int KG, int KEYS>
+struct RowsGeom {
+    static constexpr int DV = D / DS, KROW = D * 2, VROW = DV * 2, NW = QS * KG;   // bytes of a K row, of a V slice's row; waves
+    static constexpr int KTILE = KEYS * KROW, VTILE = KEYS * VROW, NK = KTILE / 1024, NV = VTILE / 1024;   // bytes and 16-byte loads per lane of a tile
+    static constexpr int NDT = DV / 16, NKS = D / 32, NH = KEYS / 16;              // column tiles, key steps, 16-key halves
+    static constexpr int UNIT = QT * NDT * 1024, QTILE = 16 * KROW;                // bytes of a wave's outputs, of a query tile
+    // LDS: the tiles of the key groups (K, V and a second K stage, with two query slots a second V stage as well), whose place the waves'
+    // outputs take at the end; references and sums; every wave's masks; parents; the pairs' step counts.  The queries lie where they fit:
+    // with one slot tile i where group i's second K stage will be, else behind the stages of the groups or of all
+    static constexpr int GROUP = KTILE + VTILE, STAGES = QS == 2 ? 2 * GROUP : GROUP + KTILE, STRIDE = STAGES > QS * UNIT ? STAGES : QS * UNIT, TILES = KG * STRIDE;
+    static constexpr bool Q_APART = QS == 2 && STRIDE - STAGES < QTILE;
+    static constexpr int Q_OFF = Q_APART ? TILES : QS == 2 ? STAGES : GROUP, Q_STRIDE = Q_APART ? QTILE : STRIDE;
+    static constexpr int ML_OFF = TILES + (Q_APART ? QS * QT * QTILE : 0), MASK_OFF = ML_OFF + NW * QT * 32 * 4, PAR_OFF = MASK_OFF + NW * QT * 16 * 8, MEET_OFF = PAR_OFF + 64 * 4;
+    static constexpr size_t BYTES = MEET_OFF + NW * 4;
+    static_assert(BYTES <= 160 * 1024 && (Q_APART || QS * QT <= KG) && (QS == 2 || QTILE <= KTILE), "a workgroup's LDS");
+};
+
+template <int N>
+__device__ __forceinline__ void wait_loads()   // until at most N of this wave's loads are in flight
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// x / d for x * d below 2^32: magic = ceil(2^32 / d), or 0 for d = 1
+__device__ __forceinline__ int quick_div(int x, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)x, magic) : x; }
+
+// what the rows of load instruction j of a tile add to a lane's 16-byte chunk (in bytes), and the pair number that row r of V is swizzled by
+template <int ROW>
+__device__ __forceinline__ constexpr int swizzle_k(int j) { return ROW == 128 ? ((j * 4) & 7) * 16 : ((j * (1024 / ROW)) & 15) * 16; }
+template <int ROW>
+__device__ __forceinline__ constexpr int swizzle_v(int j) { return ROW <= 128 ? 0 : ((j * (1024 / ROW)) & 7) * 32; }
+template <int ROW>
+__device__ __forceinline__ constexpr int pair_of_v(int r) { return ROW == 64 ? (r >> 2) & 1 : ROW == 128 ? (r >> 1) & 3 : r & 7; }
+
+// Waves 2j and 2j + 1 of a workgroup wait for each other: each writes how often it has been here and reads the other's count until it has
+// come as far.  The LDS operations of a wave take effect in order, so what a wave wrote or read before, the other finds done.
+__device__ __forceinline__ void pair_meet(uint32_t meet, int wave, int count)
+{
+    typedef __attribute__((address_space(3))) volatile int lds_int;
+    asm volatile("" ::: "memory");
+    *(lds_int *)(uintptr_t)(meet + 4 * wave) = count;
+    while (__builtin_amdgcn_readfirstlane(*(lds_int *)(uintptr_t)(meet + 4 * (wave ^ 1))) < count)
+        ;
+    asm volatile("" ::: "memory");
+}
+
+template <int D, int DS, int QT, int QS, int KG, int KEYS>
+__device__ __forceinline__ void attend_rows(const AttnArgs &a)
+{
+    using G = RowsGeom<D, DS, QT, QS, KG, KEYS>;
+    constexpr int KROW = G::KROW, VROW = G::VROW, NW = G::NW, NDT = G::NDT, NKS = G::NKS, NH = G::NH, NK = G::NK, NV = G::NV, TILES_Q = QS * QT;
+    constexpr int LPK = KROW / 16, LPV = VROW / 16;                // lanes per row of a load
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qs = wave % QS, kg = wave / QS;
+    const int c = lane & 15, g = lane >> 4;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
+
+    // workgroups of a KV head have ids congruent mod 8 (same XCD)
+    const int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z, unit = blockIdx.x >> 3, ds = unit % DS;
+    const int n_rows = a.group * a.n_q, row0 = unit / DS * (TILES_Q * 16);
+    if (kvh >= a.n_kv_heads || row0 >= n_rows)
+        return;
+    const int prefix = a.prefix_len[b];   // (ahead of the first asm statement, so that it stays a scalar load)
+
+    // ---- the queries and the parents, straight to LDS (rows past the last one: the last one again; they are never stored)
+    {
+        const uint16_t *qb = reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + (int64_t)kvh * a.group) * D;
+        for (int i = wave; i < TILES_Q * 16 * KROW / 1024; i += NW) {
+            const int r = i * (64 / LPK) + lane / LPK;             // row of the workgroup
+            const int f = min(row0 + r, n_rows - 1), hh = quick_div(f, a.nq_magic), row = f - hh * a.n_q;
+            lds_load16(qb, (uint32_t)((row * a.n_q_heads + hh) * KROW + (((lane % LPK) ^ (D == 64 ? (r >> 1) & 7 : r & 15)) * 16)), lds0 + G::Q_OFF + i / (G::QTILE / 1024) * G::Q_STRIDE + i % (G::QTILE / 1024) * 1024);
+        }
+        if (wave == NW - 1 && !a.tree_mask)
+            lds_load4(a.parent + (int64_t)b * a.n_tree, (uint32_t)min(lane, a.n_tree - 1) * 4, lds0 + G::PAR_OFF);
+    }
+
+    const int P = (int)min((int64_t)max(prefix, 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
+    const int kv_len = P + a.n_tree;
+    const int t_end = (kv_len + KEYS - 1) / KEYS;
+
+    // ---- tile loads: a lane's 16 bytes of instruction j go to 1024 * j + 16 * lane of the tile's area
+    const unsigned char *kbase = reinterpret_cast<const unsigned char *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * KROW;
+    const unsigned char *vbase = reinterpret_cast<const unsigned char *>(a.v) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * KROW + ds * VROW;
+    const int krow = lane / LPK, vrow = lane / LPV;
+    const int kl = ((lane % LPK) ^ (D == 64 ? krow >> 1 : krow)) * 16, vl = ((lane % LPV) ^ (2 * pair_of_v<VROW>(vrow))) * 16;
+    auto issue_k = [&](int t, int at) {
+        if ((t + 1) * KEYS <= kv_len) {
+            const unsigned char *p = kbase + (int64_t)t * (KEYS * KROW);
+#pragma unroll
+            for (int j = 0; j < NK; j++)
+                lds_load16(p + j * 1024, (uint32_t)(krow * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
+        } else {
+            // the ragged end: rows past the last live one are that one again (their scores are masked)
+#pragma unroll
+            for (int j = 0; j < NK; j++)
+                lds_load16(kbase, (uint32_t)(min(t * KEYS + j * (64 / LPK) + krow, kv_len - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
+        }
+    };
+    auto issue_v = [&](int t, int at) {
+        if ((t + 1) * KEYS <= kv_len) {
+            const unsigned char *p = vbase + (int64_t)t * (KEYS * KROW);
+#pragma unroll
+            for (int j = 0; j < NV; j++)
+                lds_load16(p + j * (64 / LPV) * KROW, (uint32_t)(vrow * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NV; j++)
+                lds_load16(vbase, (uint32_t)(min(t * KEYS + j * (64 / LPV) + vrow, kv_len - 1) * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
+        }
+    };
+    // one query slot: a wave's own K, V and second K areas.  Two: the key group's, stage by stage; slot 0 loads its K tiles, slot 1 its V tiles
+    int ktile = kg * G::STRIDE, ktile2 = ktile + G::GROUP;
+    const int vtile = ktile + G::KTILE;
+    int t = kg;
+    auto wait_slot = [&](auto n) {      // until the loads of at most n steps are in flight
+        if (qs == 0)
+            wait_loads<n * NK>();
+        else
+            wait_loads<n * NV>();
+    };
+    auto issue_slot = [&](int t, int at) {
+        if (qs == 0)
+            issue_k(t, at);
+        else
+            issue_v(t, at + G::KTILE);
+    };
+    const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
+    const uint32_t meet = lds0 + G::MEET_OFF;
+    if (QS == 2)
+        *reinterpret_cast<int *>(smem_raw + G::MEET_OFF + 4 * wave) = 0;
+    if (t < t_end) {
+        if constexpr (QS == 2) {
+            issue_slot(t, ktile);
+            if (t + KG < t_end) {
+                issue_slot(t + KG, ktile2);
+                wait_slot(std::integral_constant<int, 2>());   // the queries and parents are there; the first tiles stay in flight
+            } else {
+                wait_slot(std::integral_constant<int, 1>());
+            }
+        } else {
+            issue_k(t, ktile);
+            issue_v(t, vtile);
+            if (early && t + KG < t_end) {
+                issue_k(t + KG, ktile2);
+                wait_loads<2 * NK + NV>();
+            } else {
+                wait_loads<NK + NV>();
+            }
+        }
+    } else {
+        wait_loads<0>();
+    }
+    __syncthreads();
+    // ---- query fragments
+    bf16x8 qf[QT][NKS];
+    const int foff = c * KROW + ((g ^ (D == 64 ? c >> 1 : c)) * 16);
+#pragma unroll
+    for (int qt = 0; qt < QT; qt++)
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++)
+            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(smem_raw + G::Q_OFF + (qs * QT + qt) * G::Q_STRIDE + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
+    if constexpr (!G::Q_APART)
+        __syncthreads();                // every wave has its queries
+    if constexpr (QS == 1) {
+        if (!early && t + KG < t_end)
+            issue_k(t + KG, ktile2);
+    }
+    // ---- what the wave's rows see of the tree: lanes 16 * qt .. work out query tile qt's
+    uint64_t *masks = reinterpret_cast<uint64_t *>(smem_raw + G::MASK_OFF) + wave * QT * 16;
+    if (g < QT) {
+        const int f = row0 + (qs * QT + g) * 16 + c;
+        uint64_t mk = 0ull;
+        if (f < n_rows) {
+            const int row = f - quick_div(f, a.nq_magic) * a.n_q;
+            const int node = a.q_node ? min(max(a.q_node[(int64_t)b * a.n_q + row], 0), a.n_tree - 1) : row;
+            if (a.tree_mask) {
+                mk = a.tree_mask[(int64_t)b * a.n_tree + node] & (~0ull >> (64 - a.n_tree));
+            } else {
+                const int32_t *par = reinterpret_cast<const int32_t *>(smem_raw + G::PAR_OFF);
+                if (a.include_self)
+                    mk = 1ull << node;
+                for (int p = node, q = par[p]; q >= 0 && q < p; p = q, q = par[p])   // (a parent that does not precede its node is none)
+                    mk |= 1ull << q;
+            }
+        }
+        masks[lane] = mk;
+    }
+    wave_lds_fence();
+
+    f32x4 o[QT][NDT];
+    float m[QT], l[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; qt++) {
+        m[qt] = -INFINITY;
+        l[qt] = 0.0f;
+#pragma unroll
+        for (int dt = 0; dt < NDT; dt++)
+            o[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int trow = g * 4 + (c >> 2), voff = trow * VROW + pair_of_v<VROW>(trow) * 32 + (c & 3) * 8;
+    const float scale_log2 = a.scale_log2;
+
+    // S^T = K Q^T of the tile at `at`: its fragments are all requested first
+    auto scores = [&](int at, f32x4(&s)[NH][QT]) {
+        bf16x8 kf[NKS][NH];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++)
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+                kf[ks][h] = *reinterpret_cast<const bf16x8 *>(smem_raw + at + h * 16 * KROW + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < NH; h++)
+#pragma unroll
+            for (int qt = 0; qt < QT; qt++)
+                s[h][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++)
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+#pragma unroll
+                for (int qt = 0; qt < QT; qt++)
+                    s[h][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][h], qf[qt][ks], s[h][qt], 0, 0, 0);
+    };
+    // V^T fragments of column tiles dt0 .. dt0 + N - 1 of the tile at `at`
+    auto read_v = [&](int at, int dt0, auto &vf) {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof vf / sizeof vf[0]); i++) {
+            const unsigned char *vp = smem_raw + at + (voff ^ (((dt0 + i) & 7) * 32)) + ((dt0 + i) >> 3) * 256;
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+                vf[i][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vp + h * 16 * VROW));
+        }
+    };
+    // online softmax of tile t; a column's reference is raised only when a score exceeds it by DREAM_SOFTMAX_SLACK octaves
+    auto softmax = [&](int t, f32x4(&s)[NH][QT], __bf16(&p)[QT][NH * 4]) {
+        const int r0 = t * KEYS - P;   // tree node of the tile's first key
+        float mult = scale_log2, mx[QT];
+        if (r0 + KEYS > 0 || scale_log2 < 0.0f) {
+            mult = 1.0f;
+#pragma unroll
+            for (int qt = 0; qt < QT; qt++) {
+                const uint64_t mk = masks[qt * 16 + c];
+                // bit i: key i of the tile is visible (all of the prefix, what the mask says of the tree, nothing behind it)
+                const uint32_t vis = (r0 <= -32 ? ~0u : r0 >= 64 ? 0u : r0 >= 0 ? (uint32_t)(mk >> r0) : (uint32_t)((mk << -r0) | ((1ull << -r0) - 1))) >> (g * 4);
+                mx[qt] = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < NH * 4; e++) {
+                    const float x = (vis >> ((e >> 2) * 16 + (e & 3))) & 1u ? s[e >> 2][qt][e & 3] * scale_log2 : -INFINITY;
+                    s[e >> 2][qt][e & 3] = x;
+                    mx[qt] = fmaxf(mx[qt], x);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int qt = 0; qt < QT; qt++) {
+                float x = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < NH * 4; e++)
+                    x = fmaxf(x, s[e >> 2][qt][e & 3]);
+                mx[qt] = x * scale_log2;
+            }
+        }
+        bool raise = false;
+#pragma unroll
+        for (int qt = 0; qt < QT; qt++)
+            raise = raise || mx[qt] > m[qt] + DREAM_SOFTMAX_SLACK;
+        if (__any(raise)) {
+#pragma unroll
+            for (int qt = 0; qt < QT; qt++) {
+                float x = fmaxf(mx[qt], __shfl_xor(mx[qt], 16));
+                x = fmaxf(x, __shfl_xor(x, 32));
+                if (x > m[qt] + DREAM_SOFTMAX_SLACK) {
+                    const float alpha = __builtin_amdgcn_exp2f(m[qt] - x);   // 0 when the old reference was -inf
+                    m[qt] = x;
+                    l[qt] *= alpha;
+#pragma unroll
+                    for (int dt = 0; dt < NDT; dt++)
+                        o[qt][dt] *= alpha;
+                }
+            }
+        }
+#pragma unroll
+        for (int qt = 0; qt < QT; qt++) {
+            const float neg_m = m[qt] == -INFINITY ? 0.0f : -m[qt];
+            float sum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < NH * 4; e++) {
+                const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e >> 2][qt][e & 3], mult, neg_m));
+                sum += x;
+                p[qt][e] = (__bf16)x;
+            }
+            l[qt] += sum;
+        }
+    };
+    // O^T += V^T P^T for column tiles dt0 ..
+    auto product = [&](int dt0, const auto &vf, const __bf16(&p)[QT][NH * 4]) {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof vf / sizeof vf[0]); i++)
+#pragma unroll
+            for (int qt = 0; qt < QT; qt++) {
+                if constexpr (NH == 2) {
+                    const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vf[i][0], vf[i][NH - 1], 0, 1, 2, 3, 4, 5, 6, 7));
+                    const bf16x8 pf = {p[qt][0], p[qt][1], p[qt][2], p[qt][3], p[qt][NH * 4 - 4], p[qt][NH * 4 - 3], p[qt][NH * 4 - 2], p[qt][NH * 4 - 1]};
+                    o[qt][dt0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pf, o[qt][dt0 + i], 0, 0, 0);
+                } else {
+                    const bf16x4 pf = {p[qt][0], p[qt][1], p[qt][2], p[qt][3]};
+                    o[qt][dt0 + i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[i][0], __builtin_bit_cast(s16x4, pf), o[qt][dt0 + i], 0, 0, 0);
+                }
+            }
+    };
+    constexpr int VB = NDT / 2;         // column tiles whose V fragments are requested together
+    s16x4 va[VB][NH], vb[VB][NH];
+    f32x4 s[NH][QT];
+    __bf16 p[QT][NH * 4];
+    if constexpr (QS == 2) {
+        // The two waves of a key group meet at every step: each says that its half of the step's tiles is there, which also says that it is
+        // done with the stage before.  (Both always come: a key group's waves take the same number of steps.)
+        const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
+        for (int i = 1; i <= n_steps; i++, t += KG) {
+            if (i == 1 && t + KG < t_end)
+                wait_slot(std::integral_constant<int, 1>());
+            else
+                wait_loads<0>();
+            pair_meet(meet, wave, i);
+            if (i > 1 && t + KG < t_end)
+                issue_slot(t + KG, ktile2);
+            scores(ktile, s);
+            read_v(ktile + G::KTILE, 0, va);
+            softmax(t, s, p);
+            read_v(ktile + G::KTILE, VB, vb);
+            __builtin_amdgcn_sched_barrier(0);
+            product(0, va, p);
+            product(VB, vb, p);
+            const int x = ktile;
+            ktile = ktile2;
+            ktile2 = x;
+        }
+        wait_lds();
+        pair_meet(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
+    } else {
+        for (; t < t_end; t += KG) {
+            const bool more = t + KG < t_end, more2 = t + 2 * KG < t_end;
+            if (more)
+                wait_loads<NK + NV>();  // this tile's K (behind it: this tile's V and the next one's K)
+            else
+                wait_loads<NV>();
+            scores(ktile, s);
+            wait_lds();
+            if (more2)
+                issue_k(t + 2 * KG, ktile);
+            softmax(t, s, p);
+            if (more2)
+                wait_loads<NK>();       // this tile's V
+            else
+                wait_loads<0>();
+            read_v(vtile, 0, va);
+            read_v(vtile, VB, vb);
+            __builtin_amdgcn_sched_barrier(0);
+            product(0, va, p);
+            wait_lds();
+            if (more)
+                issue_v(t + KG, vtile);
+            product(VB, vb, p);
+            const int x = ktile;
+            ktile = ktile2;
+            ktile2 = x;
+        }
+    }
+
+    // ---- the key groups' states meet: every wave leaves its outputs, references and sums where its own tiles were, and takes its share of
+    // the column tiles, adding them in the order of the groups
+    float *ml = reinterpret_cast<float *>(smem_raw + G::ML_OFF);      // [query tile][key group][16 references, 16 sums]
+    f32x4 *xch = reinterpret_cast<f32x4 *>(smem_raw + kg * G::STRIDE + qs * G::UNIT);
+#pragma unroll
+    for (int qt = 0; qt < QT; qt++) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; dt++)
+            xch[(qt * NDT + dt) * 64 + lane] = o[qt][dt];
+        float x = l[qt];
+        x += __shfl_xor(x, 16);
+        x += __shfl_xor(x, 32);
+        if (g == 0) {
+            ml[((qs * QT + qt) * KG + kg) * 32 + c] = m[qt];
+            ml[((qs * QT + qt) * KG + kg) * 32 + 16 + c] = x;
+        }
+    }
+    constexpr int UNITS = TILES_Q * NDT, UPW = (UNITS + NW - 1) / NW;
+    static_assert(NDT % UPW == 0, "a wave's column tiles belong to one query tile");
+    const int qt = wave * UPW / NDT, dt0 = wave * UPW % NDT;
+    const int f = row0 + qt * 16 + c, hh = quick_div(min(f, n_rows - 1), a.nq_magic), row = f - hh * a.n_q, head = kvh * a.group + hh;
+    uint16_t *op = reinterpret_cast<uint16_t *>(a.out) + (((int64_t)b * a.n_q + row) * a.n_q_heads + head) * D + ds * G::DV + dt0 * 16 + g * 4;
+    __syncthreads();
+    if (wave * UPW >= UNITS)
+        return;
+    float wgt[KG], mt = -INFINITY, lt = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KG; k++) {
+        wgt[k] = ml[(qt * KG + k) * 32 + c];
+        mt = fmaxf(mt, wgt[k]);
+    }
+    f32x4 sum[UPW];
+#pragma unroll
+    for (int u = 0; u < UPW; u++)
+        sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KG; k++) {
+        wgt[k] = __builtin_amdgcn_exp2f(wgt[k] - (mt == -INFINITY ? 0.0f : mt));
+        lt += ml[(qt * KG + k) * 32 + 16 + c] * wgt[k];
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(smem_raw + k * G::STRIDE + qt / QT * G::UNIT) + ((qt % QT) * NDT + dt0) * 64 + lane;
+#pragma unroll
+        for (int u = 0; u < UPW; u++)
+            sum[u] += src[u * 64] * wgt[k];
+    }
+    if (f >= n_rows)
+        return;
+    const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
+#pragma unroll
+    for (int u = 0; u < UPW; u++) {
+        bf16x4 ob;
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+            ob[r] = (__bf16)(sum[u][r] * inv);
+        *reinterpret_cast<bf16x4 *>(op + u * 16) = ob;
+    }
+    if (ds == 0 && dt0 == 0 && g == 0 && a.lse)
+        a.lse[((int64_t)b * a.n_q_heads + head) * a.n_q + row] = lt > 0.0f ? (mt + log2f(lt)) * 0.6931471805599453f : -INFINITY;
+}
+
+// keys per tile: 32 where the key groups' tiles fit a workgroup's LDS
+template <int D, int NW, int DS>
+constexpr int wave_keys() { return D == 64 || (D == 128 && (DS == 4 || NW == 4)) || (D == 256 && DS == 4 && NW == 4) ? 32 : 16; }
+template <int D, int NW, int DS, int QT>
+using WaveGeom = RowsGeom<D, DS, QT, 1, NW, wave_keys<D, NW, DS>()>;
+template <int D, int DS, int QT>
+using PairGeom = RowsGeom<D, DS, QT, 2, 4, D == 256 ? 16 : 32>;
+
+// one query slot: NW key groups of one wave, QT query tiles and one of DS column slices a workgroup
+template <int D, int NW, int DS, int QT>
+__global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a)
+{
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>()>(a);
+}
+
+// two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
+template <int D, int DS, int QT>
+__global__ __launch_bounds__(512) void attn_pair_kernel(AttnArgs a)
+{
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1028,16 +1338,107 @@ struct Plan {
     int mw;           // 64-bit words of a node's visibility mask (1, or 4 for trees above 64 nodes)
     int once;         // 1: the variant whose K/V loads carry the nontemporal hint (one query group per KV head)
     int kg;           // key groups per workgroup of the shared-tile kernel (1; 2 = 8 waves as two groups of 4)
-    bool wave_mode;   // one query tile per workgroup, waves split the keys, no key split (attn_wave_kernel)
+    bool wave_mode;   // attn_wave_kernel or attn_pair_kernel: waves split the keys of a workgroup, workgroups do not
     int wave_nw;      // waves per workgroup in that mode
     int wave_ds;      // workgroups that share the output columns of a query tile in that mode (1, 2 or 4)
-    int wave_qt;      // query tiles per workgroup in that mode (1 or 2)
+    int wave_qt;      // query tiles per wave in that mode
+    bool pair;        // ... two slots of as many (attn_pair_kernel)
     size_t state_floats, off_part, total;
 };
 
-int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
+// The kernels that cut the work into query tiles and column slices only (attn_wave_kernel, attn_pair_kernel): one launch, no key split.
+// What such a launch costs is what its busiest CU pulls, K and 1 / DS of V per workgroup, as long as all workgroups run at once; so
+// the decompositions below are tried from the one that spreads the bytes thinnest, and the first with at most one workgroup per CU is
+// taken, up to the number of 32-key tiles at which key splits with their merge launch (or the shared-tile kernel) catch up.  Measured
+// in us, this kernel / the plan without it, caches larger than any cache level:
+//   head_dim 128, 32 KV heads: DS 4, 10 rows, 1 sequence: 41 tiles 12.3 / 12.5, 55 tiles 15.1 / 13.5; DS 2, 60 rows: 24 tiles 8.9 / 16, 67 tiles
+//   17.5 / 17.8, 80 tiles 20.1 / 19.1; two tiles in 2 slices, 2 sequences: 24 tiles 10.9 / 17, 80 tiles 23.6 / 24.7, 102 tiles 29.2 / 28.0; two
+//   tiles unsliced, 4 sequences: 24 tiles 15.2 / 16.1, 102 tiles 42.2 / 43.5, 127 tiles 51.2 / 51.0
+//   8 KV heads, groups of 4: DS 4: 42 tiles 9.2 / 12.2, 55 tiles 13.4 / 12.6; DS 2: 80 tiles 18.2 / 18.6, 102 tiles 21.7 / 20.1; two tiles in 2 slices:
+//   102 tiles 23.8 / 26.3, 127 tiles 29.0 / 29.2; three tiles in 2 slices, 8 sequences of 24 rows, 41 tiles: 17.0 / 23; two tiles
+//   unsliced, 4 sequences: 127 tiles 38.1 / 47.3; pairs of two tiles, 8 sequences: 13 tiles 12.2 / 13.1, 42 tiles 21.6 / 24.6, 127 tiles 50.1 / 59.3
+//   (not with 4 query tiles or fewer, where the shared-tile kernel is the only reader of its rows: 6 sequences, 24 tiles: 20.0 / 17.7)
+//   head_dim 64, 32 KV heads: DS 2, 60 rows: 67 tiles 11.9 / 13.4, 80 tiles 13.5 / 13.4; unsliced, 2 sequences: 80 tiles 15.2 / 16.3, 102 tiles 18.4 /
+//   17.9; 8 sequences of 10 rows: 67 tiles 25.2 / 25.7, 80 tiles 29.5 / 29.2; two tiles, 4 sequences: 127 tiles 27.9 / 30.2
+//   head_dim 256, 8 KV heads, groups of 2: DS 4: 55 tiles 20.4 / 21.7, 67 tiles 23.5 / 23.2 (24 rows: 42 tiles 16.5 / 18.3, 55 tiles 20.5 / 19.3); two
+//   tiles: 55 tiles 22.8 / 23.2, 67 tiles 26.5 / 25.3; three: 55 tiles 25.3 / 25.8, 67 tiles 29.1 / 28.8; pairs of one: 55 tiles 30.3 / 30.5, 67 tiles
+//   36.1 / 33.8; pairs of two, 8 sequences: 13 tiles 14.4 / 23.8, 42 tiles 32.2 / 39.4, 127 tiles 80.8 / 82.7
+struct Decomposition {
+    int d;
+    bool pair;
+    int ds, qt;
+    int tiles_1, tiles_n;    // longest range in 32-key tiles with one query head per KV head, with several (0: not used)
+};
+const Decomposition DECOMPOSITIONS[] = {
+    {128, false, 4, 1, 40, 48}, {128, false, 2, 1, 72, 88}, {128, false, 2, 2, 92, 128}, {128, false, 2, 3, 92, 128}, {128, false, 1, 2, 120, 160},
+    {128, true, 1, 2, 0, 1 << 30},
+    {64, false, 2, 1, 72, 88}, {64, false, 1, 1, 80, 96}, {64, false, 1, 2, 128, 160},
+    {256, false, 4, 1, 0, 52}, {256, false, 4, 2, 0, 56}, {256, false, 4, 3, 0, 60}, {256, true, 2, 1, 0, 56}, {256, true, 2, 2, 0, 128},
+};
+
+bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
+    const int64_t base = (int64_t)d->batch * d->n_kv_heads;
+    const int tiles = ceil_div(max_kv_len, 32), rows = ceil_div((int64_t)G * n_q, 16);
+    const int n_qtiles = G * ceil_div(n_q, 16);      // as many as the heads' rows would need one head after the other
+    p->wave_mode = p->pair = false;
+    if (d->dtype != DREAM_BF16 || q_tiles_override() != 0 || kv_splits_override() != 0 || tile_waves_override() != 0 || n_qtiles > 16 || G > 4 ||
+        base * n_qtiles < 32 || d->s_max * d->head_dim >= (1ll << 30))
+        return false;
+    if (G == 3 || (G == 1 && d->head_dim == 256)) {
+        // not measured with the decompositions above: one query tile a workgroup in as many column slices as leave one workgroup per CU, or
+        // two tiles, up to the lengths at which key splits won against a slower kernel of this kind
+        if (base * n_qtiles > (d->head_dim <= 128 ? 512 : 256) || (int64_t)tiles * d->head_dim > (G > 1 ? 12288 : 8192))
+            return false;
+        p->wave_ds = 1;
+        while (p->wave_ds < 4 && base * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
+            p->wave_ds *= 2;
+        p->wave_qt = base * n_qtiles > 256 ? 2 : 1;
+    } else {
+        const Decomposition *use = nullptr;
+        for (const Decomposition &c : DECOMPOSITIONS)
+            if (!use && c.d == d->head_dim && base * ceil_div(rows, (c.pair ? 2 : 1) * c.qt) * c.ds <= 256)
+                use = &c;
+        if (!use || tiles > (G == 1 ? use->tiles_1 : use->tiles_n))
+            return false;
+        // (up to 96 KV heads with 4 tiles each change to key groups and splits where they always have: measured here at 24 key tiles only)
+        if (use->d == 128 && use->ds == 1 && !use->pair && G == 1 && base <= 96 && tiles > 48)
+            return false;
+        p->pair = use->pair;
+        p->wave_ds = use->ds;
+        p->wave_qt = use->qt;
+    }
+    p->wave_mode = true;
+    // 4 waves while each has about one tile (5 tiles: 6.8 us with 4, 6.9 with 8), and at head_dim 256 with one query tile, where a wave's 32
+    // keys of 4 waves and 16 keys of 8 take the same LDS (42 tiles: 16.4 us with 4, 15.9 with 8)
+    p->wave_nw = 8;
+    if (!p->pair && (d->head_dim == 256 ? p->wave_qt == 1 : p->wave_ds == 1 && tiles <= 5))
+        p->wave_nw = 4;
+    p->qg = 1;
+    p->n_qg = p->wave_qt == 1 && !p->pair ? n_qtiles : rows;    // (a tile that the rows do not need ends at once)
+    p->n_splits = 1;
+    p->n_groups = p->n_streams = (int)base;
+    p->grid = 0;
+    p->kt = p->pfd = 1;
+    p->state_floats = 0;
+    p->off_part = DREAM_WORKSPACE_MIN_BYTES;
+    p->total = DREAM_WORKSPACE_MIN_BYTES;
+    return true;
+}
+
+// direct: q and the caches are 16-byte aligned, as loads straight to LDS need them
+int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool direct, Plan *p)
+{
+    const int G = d->n_q_heads / d->n_kv_heads;
+    if (make_wave_plan(d, n_q, max_kv_len, p)) {
+        if (direct)
+            return 0;
+        p->wave_mode = p->pair = false;
+    } else {
+        direct = true;
+    }
+    p->wave_nw = p->wave_ds = 0;
     p->wave_qt = 1;
     p->tiles_per_head = ceil_div(n_q, 16);
     const int n_qtiles = G * p->tiles_per_head;
@@ -1070,39 +1471,6 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
     p->once = 0;
     p->kg = 1;
     p->n_qg = ceil_div(n_qtiles, 4 * qg);
-    // few, short streams with at most 16 query tiles each: a workgroup per query tile fills at least half the chip
-    // without splitting keys, which saves the merge launch (short: up to 64 key tiles at head_dim 128, twice that
-    // at 64: the measured crossover against the key-split path, which comes a little later for grouped-query
-    // shapes because their split states are larger)
-    p->wave_mode = q_tiles_override() == 0 && kv_splits_override() == 0 && tile_waves_override() == 0 &&
-                   d->dtype == DREAM_BF16 && n_qtiles <= 16 && G <= 4 && base * n_qtiles <= 512 && base * n_qtiles >= 32 &&
-                   (base * n_qtiles <= 256 || d->head_dim <= 128) && (int64_t)tiles * d->head_dim <= (G > 1 ? 12288 : 8192) &&
-                   // (four full tiles of one head: above one tile per CU the two key groups below are as fast at 24 key tiles of
-                   // head_dim 128, 17.2 against 16.5 us, and ahead at 49, 29.8 against 26.6 us; at head_dim 64 they are not)
-                   !(base * n_qtiles > 256 && n_qtiles == 4 && G == 1 && d->head_dim == 128) && d->s_max * d->head_dim < (1ll << 31);
-    if (p->wave_mode) {
-        p->qg = 1;
-        p->n_qg = n_qtiles;
-        // output columns split over 2 or 4 workgroups while that still leaves at most one workgroup per CU
-        p->wave_ds = 1;
-        while (p->wave_ds < 4 && base * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
-            p->wave_ds *= 2;
-        // more pairs than CUs (up to twice as many; beyond that the shared-tile kernel measures faster): a
-        // workgroup serves two query tiles from the one K/V stream
-        p->wave_qt = base * n_qtiles > 256 ? 2 : 1;
-        // 8 waves (two per SIMD) where the registers allow it and each wave still gets a few tiles
-        p->wave_nw = (d->head_dim <= 128 && (tiles > 32 || p->wave_ds > 1)) ? 8 : 4;
-        p->n_splits = 1;
-        p->n_groups = (int)base;
-        p->n_streams = (int)base;
-        p->grid = ceil_div(p->n_streams, 8) * 8 * n_qtiles;
-        p->kt = 1;
-        p->pfd = 1;
-        p->state_floats = 0;
-        p->off_part = DREAM_WORKSPACE_MIN_BYTES;
-        p->total = DREAM_WORKSPACE_MIN_BYTES;
-        return 0;
-    }
     // grouped-query shapes with more 4-wave workgroups than the chip runs well: 8 waves share one LDS tile, so the 8-16
     // query tiles of a KV head are served by ONE workgroup (K/V leave L2 once per head instead of once per 4 query tiles)
     // while the CU still holds 8 waves.  head_dim 64 tiles are too small to spread over 512 threads; with more than 16
@@ -1134,7 +1502,7 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
         }
     }
     int s = kv_splits_override();
-    if (p->nw == 8)
+    if (p->nw == 8 || !direct)     // (a call in place of one without splits has a workspace for none)
         s = 1;
     if (s <= 0) {
         // at most one workgroup per CU: a few more leave most of the chip waiting for the last ones (96 groups of head_dim 256,
@@ -1205,6 +1573,7 @@ void make_wide_plan(const dream_attn_desc *d, int n_q, Plan *p)
     p->tiles_per_head = ceil_div(n_q, 16);
     p->wave_mode = false;
     p->wave_nw = p->wave_ds = p->wave_qt = 0;
+    p->pair = false;
     p->qg = 1;
     p->nw = 4;
     p->mw = 4;
@@ -1267,37 +1636,43 @@ int launch_bf16(const AttnArgs &a, const Plan &p, hipStream_t st)
 }
 
 template <int D, int NW, int DS, int QT>
-struct WaveLds {
-    using G = Geom<D, 1, 1, D / DS>;
-    static constexpr size_t tile_bytes = (size_t)NW * G::TILE_ELEMS * 2, merge_bytes = (size_t)NW * StateGeom<D / DS, QT>::STATE_FLOATS * 4;
-    static constexpr size_t bytes = (tile_bytes > merge_bytes ? tile_bytes : merge_bytes) + DREAM_MAX_TREE * sizeof(int32_t);
-    static_assert(merge_bytes <= tile_bytes, "the wave merge buffers reuse the tile area");
-};
-
-template <int D, int NW, int DS, int QT = 1>
 int ensure_wave_lds()
 {
     static std::atomic<uint64_t> done{0};
-    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT>), WaveLds<D, NW, DS, QT>::bytes, "attention");
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT>), WaveGeom<D, NW, DS, QT>::BYTES, "attention");
 }
 
-template <int D, int NW, int DS, int QT = 1>
+template <int D, int NW, int DS, int QT>
 int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
-    constexpr size_t lds_bytes = WaveLds<D, NW, DS, QT>::bytes;
     if (int rc = ensure_wave_lds<D, NW, DS, QT>())
         return rc;
-    if (a.n_qg > 16 || a.group > 4)
-        return fail(DREAM_ERR_INVALID_ARG, "attention: the wave kernel serves at most 16 query tiles and 4 query heads per KV head");
-    const dim3 grid(8 * ceil_div(a.n_qg, QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_streams / a.n_kv_heads);
-    hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT>), grid, dim3(64 * NW), lds_bytes, st, a);
+    const dim3 grid(8 * ceil_div(a.n_qg, QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
     return check_launch("attn_wave_kernel");
+}
+
+template <int D, int DS, int QT>
+int ensure_pair_lds()
+{
+    static std::atomic<uint64_t> done{0};
+    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT>), PairGeom<D, DS, QT>::BYTES, "attention");
+}
+
+template <int D, int DS, int QT>
+int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
+{
+    if (int rc = ensure_pair_lds<D, DS, QT>())
+        return rc;
+    const dim3 grid(8 * ceil_div(a.n_qg, 2 * QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
+    return check_launch("attn_pair_kernel");
 }
 
 // Every bf16 kernel variant the launch plan can choose, in one table: the plan names a variant by
 // (kernel family, head_dim, three template arguments); the table gives its launcher and the routine that raises
 // its dynamic-LDS limit.  The launch, dream_init, dream_attn_plan_describe and dream_attn_variants all read it.
-enum { FAMILY_TILE = 0, FAMILY_WAVE = 1 };
+enum { FAMILY_TILE = 0, FAMILY_WAVE = 1, FAMILY_PAIR = 2 };
 struct Variant {
     int family, d, p1, p2, p3, p4, p5, p6, p7;   // tile: (QG, KT, PFD, waves, mask words, read-once, key groups); wave: (NW, DS, QT, 0, 1, 0, 1)
     int (*launch)(const AttnArgs &, const Plan &, hipStream_t);
@@ -1310,6 +1685,7 @@ struct Variant {
 #define WIDE_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 4, 4, 0, 1, &launch_bf16<D, QG, KT, PFD, 4, 4>, &ensure_bf16_lds<D, QG, KT, PFD, 4, 4>}
 #define TILE8_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 8, 1, 1, 1, &launch_bf16<D, QG, KT, PFD, 8, 1, true>, &ensure_bf16_lds<D, QG, KT, PFD, 8, 1, true>}
 #define WAVE_VARIANT(D, NW, DS, QT) {FAMILY_WAVE, D, NW, DS, QT, 0, 1, 0, 1, &launch_wave<D, NW, DS, QT>, &ensure_wave_lds<D, NW, DS, QT>}
+#define PAIR_VARIANT(D, DS, QT) {FAMILY_PAIR, D, 8, DS, QT, 0, 1, 0, 1, &launch_pair<D, DS, QT>, &ensure_pair_lds<D, DS, QT>}
 const Variant VARIANTS[] = {
     // shared-tile kernel, one query tile per wave: a short key range in one step (2-4 tiles), or streamed
     TILE_VARIANT(64, 1, 2, 1), TILE_VARIANT(64, 1, 3, 1), TILE_VARIANT(64, 1, 4, 1), TILE_VARIANT(64, 1, 2, 2),
@@ -1327,13 +1703,15 @@ const Variant VARIANTS[] = {
     TILE8_VARIANT(128, 1, 1, DREAM_W8_PFD), TILE8_VARIANT(128, 2, 1, DREAM_W8_PFD), TILE8_VARIANT(256, 1, 1, DREAM_W8_PFD),
     // trees of 65-256 nodes (four mask words): a sixth name argument 4
     WIDE_VARIANT(64, 1, 2, 2), WIDE_VARIANT(128, 1, 1, 2), WIDE_VARIANT(256, 1, 1, 2),
-    // single-launch wave kernel: (waves, column slices, query tiles per workgroup); split output columns always come
-    // with 8 waves at head_dim <= 128
+    // one query slot: (waves, column slices, query tiles per workgroup)
     WAVE_VARIANT(64, 8, 1, 1), WAVE_VARIANT(64, 8, 2, 1), WAVE_VARIANT(64, 4, 1, 1),
     WAVE_VARIANT(64, 8, 1, 2), WAVE_VARIANT(64, 4, 1, 2),
     WAVE_VARIANT(128, 8, 1, 1), WAVE_VARIANT(128, 8, 2, 1), WAVE_VARIANT(128, 8, 4, 1), WAVE_VARIANT(128, 4, 1, 1),
     WAVE_VARIANT(128, 8, 1, 2), WAVE_VARIANT(128, 4, 1, 2),
     WAVE_VARIANT(256, 4, 1, 1), WAVE_VARIANT(256, 4, 2, 1), WAVE_VARIANT(256, 4, 4, 1),
+    WAVE_VARIANT(128, 8, 2, 2), WAVE_VARIANT(128, 8, 2, 3), WAVE_VARIANT(256, 8, 4, 2), WAVE_VARIANT(256, 8, 4, 3),
+    // two query slots: (column slices, query tiles per slot)
+    PAIR_VARIANT(128, 1, 2), PAIR_VARIANT(256, 2, 1), PAIR_VARIANT(256, 2, 2),
 };
 #undef TILE_VARIANT
 #undef TILE8_VARIANT
@@ -1342,12 +1720,13 @@ const Variant VARIANTS[] = {
 #undef KG2S_VARIANT
 #undef WIDE_VARIANT
 #undef WAVE_VARIANT
+#undef PAIR_VARIANT
 constexpr int N_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
 
 // the variant a plan asks for, or nullptr
 const Variant *find_variant(const dream_attn_desc *d, const Plan &p)
 {
-    const int family = p.wave_mode ? FAMILY_WAVE : FAMILY_TILE;
+    const int family = p.pair ? FAMILY_PAIR : p.wave_mode ? FAMILY_WAVE : FAMILY_TILE;
     const int p1 = p.wave_mode ? p.wave_nw : p.qg, p2 = p.wave_mode ? p.wave_ds : p.kt, p3 = p.wave_mode ? p.wave_qt : p.pfd;
     const int p4 = p.wave_mode ? 0 : p.nw, p5 = p.wave_mode ? 1 : p.mw, p6 = p.wave_mode ? 0 : p.once, p7 = p.wave_mode ? 1 : p.kg;
     for (int i = 0; i < N_VARIANTS; i++) {
@@ -1360,7 +1739,9 @@ const Variant *find_variant(const dream_attn_desc *d, const Plan &p)
 
 void variant_name(const Variant &v, char *buf, size_t n)
 {
-    if (v.family == FAMILY_WAVE)
+    if (v.family == FAMILY_PAIR)
+        snprintf(buf, n, "attn_pair_kernel<%d,%d,%d>", v.d, v.p2, v.p3);
+    else if (v.family == FAMILY_WAVE)
         snprintf(buf, n, "attn_wave_kernel<%d,%d,%d,%d>", v.d, v.p1, v.p2, v.p3);
     else if (v.p7 != 1)
         snprintf(buf, n, "attn_bf16_kernel<%d,%d,%d,%d,%d,%d,%d,%d>", v.d, v.p1, v.p2, v.p3, v.p4, v.p5, v.p6, v.p7);
@@ -1395,7 +1776,7 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     if (max_kv_len < n_tree || max_kv_len > d->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: max_kv_len %lld outside [n_tree, s_max]", who, (long long)max_kv_len);
     Plan p;
-    make_plan(d, n_q, max_kv_len, &p);
+    make_plan(d, n_q, max_kv_len, !((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15), &p);
     if (n_tree > 64 && d->dtype == DREAM_BF16)
         make_wide_plan(d, n_q, &p);
     if (!ws || ws_bytes < p.total)
@@ -1410,6 +1791,8 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     a.n_q = n_q; a.n_tree = n_tree; a.include_self = include_self;
     a.mask_words = ceil_div(n_tree, 64);
     a.tiles_per_head = p.tiles_per_head; a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
+    auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
+    a.nq_magic = magic(n_q);
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;
@@ -1435,7 +1818,7 @@ size_t workspace_for(const dream_attn_desc *d, int n_q, int64_t max_kv_len)
         d->batch < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
     Plan p;
-    make_plan(d, n_q, max_kv_len, &p);
+    make_plan(d, n_q, max_kv_len, true, &p);
     return p.total;
 }
 
@@ -1465,7 +1848,7 @@ int dream_attn_plan_describe(const dream_attn_desc *desc, int32_t n_q, int64_t m
     if (n_q < 1 || max_kv_len < 1 || max_kv_len > desc->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= max_kv_len <= s_max", who);
     Plan p;
-    make_plan(desc, n_q, max_kv_len, &p);
+    make_plan(desc, n_q, max_kv_len, true, &p);
     if (n_q > 64 && desc->dtype == DREAM_BF16)   // more than 64 query rows: taken as a verification call over a tree of n_q nodes
         make_wide_plan(desc, n_q, &p);
     if (desc->dtype == DREAM_F32) {
@@ -1479,7 +1862,7 @@ int dream_attn_plan_describe(const dream_attn_desc *desc, int32_t n_q, int64_t m
     variant_name(*v, name, sizeof name);
     if (p.wave_mode)
         snprintf(buf, buf_bytes, "%s workgroups=%d splits=1 merge_launch=0", name,
-                 ceil_div(p.n_qg, p.wave_qt) * p.wave_ds * desc->n_kv_heads * desc->batch);
+                 ceil_div(p.n_qg, p.pair ? 2 * p.wave_qt : p.wave_qt) * p.wave_ds * desc->n_kv_heads * desc->batch);
     else
         snprintf(buf, buf_bytes, "%s workgroups=%d splits=%d merge_launch=%d", name, p.n_groups * p.n_splits, p.n_splits,
                  p.n_splits > 1 ? 1 : 0);

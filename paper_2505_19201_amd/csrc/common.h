@@ -50,6 +50,11 @@ __device__ __forceinline__ void lds_load16(const void *base, uint32_t offset, ui
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
 }
+// the same with 4 bytes per lane
+__device__ __forceinline__ void lds_load4(const void *base, uint32_t offset, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 }  // namespace dream

@@ -57,6 +57,15 @@ VARIANT_CASES = [
     VariantCase("attn_wave_kernel<256,4,1,1>", 3, 24, 8, 256, 17, 4, 150, 0, 0),
     VariantCase("attn_wave_kernel<256,4,2,1>", 3, 12, 4, 256, 17, 4, 150, 0, 0),
     VariantCase("attn_wave_kernel<256,4,4,1>", 8, 2, 2, 256, 17, 4, 150, 0, 0),
+    # several query tiles of one or more heads a workgroup, a last tile that is partly empty
+    VariantCase("attn_wave_kernel<128,8,2,2>", 4, 32, 16, 128, 17, 4, 333, 0, 0),
+    VariantCase("attn_wave_kernel<128,8,2,3>", 4, 32, 16, 128, 40, 5, 301, 0, 0),
+    VariantCase("attn_wave_kernel<256,8,4,2>", 3, 16, 8, 256, 17, 4, 333, 0, 0),
+    VariantCase("attn_wave_kernel<256,8,4,3>", 4, 16, 8, 256, 33, 5, 410, 0, 0),
+    # two query slots
+    VariantCase("attn_pair_kernel<128,1,2>", 8, 32, 8, 128, 33, 5, 410, 0, 0),
+    VariantCase("attn_pair_kernel<256,2,1>", 4, 16, 8, 256, 60, 6, 333, 0, 0),
+    VariantCase("attn_pair_kernel<256,2,2>", 6, 16, 8, 256, 60, 6, 301, 0, 0),
 ]
 
 # The launch the benchmark times: dream_tree_verify_attn at each full-size configuration.

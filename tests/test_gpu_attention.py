@@ -201,6 +201,59 @@ def test_every_kernel_variant_all_elements(gu, case):
     assert np.abs(lse - want_lse).max() <= 2e-3
 
 
+# shapes whose plans are the kernels that cut the work into query tiles and column slices, one per way of cutting: batch, heads, KV heads, head_dim, rows
+SLICED = [(1, 32, 32, 128, 9), (2, 32, 32, 128, 60), (4, 32, 16, 128, 40), (4, 32, 32, 128, 60), (8, 32, 8, 128, 33), (2, 32, 32, 64, 17),
+          (4, 32, 32, 64, 60), (1, 16, 8, 256, 60), (4, 16, 8, 256, 33), (4, 16, 8, 256, 60), (6, 16, 8, 256, 49)]
+
+
+@pytest.mark.parametrize("shape", SLICED, ids=["x".join(map(str, x)) for x in SLICED])
+def test_sliced_kernels_at_tile_edges(gu, shape):
+    """Ranges around the 16- and 32-key tiles and around the number of key groups, sequences without a prefix beside full ones, a last query
+    tile that is partly empty; and the same rows as a cross-attention call that names its nodes, under an explicit mask."""
+    B, Hq, Hkv, D, T = shape
+    plans = set()
+    for prefix in (0, 15, 32 - T % 32, 128 - T, 129 - T, 256 - T, 257 - T):
+        prefix = max(prefix, 0)
+        cfg = _cfg("edge", "bf16", B, Hq, Hkv, D, prefix, 0, T, min(5, T - 1), 48)
+        x = di.verify_inputs(cfg, prefix_len=[prefix if b % 3 != 1 else prefix // 2 for b in range(B)])
+        plans.add(gu.verify_plan(x).split("<")[0])
+        got, lse = gu.run_verify(x)
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+        assert np.isfinite(got).all(), prefix
+        assert np.abs(got - want).max() <= TOL["bf16"], (prefix, np.abs(got - want).max())
+        assert np.abs(lse - want_lse).max() <= 2e-3, prefix
+    assert plans <= {"attn_wave_kernel", "attn_pair_kernel"}, plans
+    star = np.stack([di.ancestor_mask_bits(di.star_tree(T), True)[:, 0]] * B)
+    got, _ = gu.run_verify(x, tree_mask=star)
+    want, _ = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, np.stack([di.star_tree(T)] * B), True)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+    rows = np.stack([np.roll(np.arange(T, dtype=np.int32), 3)] * B)
+    got, qsel = gu.run_xattn(x, rows, rows)
+    want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+
+
+def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
+    """Loads straight to LDS need 16-byte aligned tensors: queries or caches that start elsewhere give the same rows within rounding, in
+    the workspace the query returned."""
+    import torch
+    import paper_2505_19201_amd as dream
+    cfg = _cfg("shifted", "bf16", 1, 32, 32, 128, 150, 43, 60, 6, 49)
+    x = di.verify_inputs(cfg)
+    assert gu.verify_plan(x).startswith("attn_wave_kernel")
+    base, _ = gu.run_verify(x)
+    for name in ("q", "k", "v"):
+        dev = gu.DeviceAttn(x)
+        t = getattr(dev, name)
+        flat = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+        shifted = flat[2:2 + t.numel()].view(t.shape)
+        shifted.copy_(t)
+        assert shifted.data_ptr() % 16 == 4
+        setattr(dev, name, shifted)
+        got, _ = gu.run_verify(x, dev=dev)
+        assert np.abs(got - base).max() <= TOL["bf16"], name
+
+
 FULL = ["llava", "pixtral", "gemma3", "smolvlm_b1", "smolvlm_b8", "smolvlm_b32"]
 
 

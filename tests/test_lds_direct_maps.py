@@ -1,0 +1,77 @@
+"""Host model of the LDS layout of the attention kernels whose tiles go from memory straight to LDS (attend_rows in csrc/attn.hip; the
+areas in test_lds_index_maps.py are those of tiles staged in registers).  Restated from the source: where every lane of a load
+instruction puts its 16 bytes, where the fragment reads look for them, and which banks the lanes of a read touch together."""
+import pytest
+
+
+def swizzle_k(row_bytes, j):
+    return ((j * 4) & 7) * 16 if row_bytes == 128 else ((j * (1024 // row_bytes)) & 15) * 16
+
+
+def swizzle_v(row_bytes, j):
+    return 0 if row_bytes <= 128 else ((j * (1024 // row_bytes)) & 7) * 32
+
+
+def pair_of_v(row_bytes, r):
+    return (r >> 2) & 1 if row_bytes == 64 else (r >> 1) & 3 if row_bytes == 128 else r & 7
+
+
+def loaded(row_bytes, keys, kind):
+    """LDS byte -> (row, byte of the row) after the loads of one tile."""
+    lanes = row_bytes // 16
+    at = {}
+    for j in range(keys * row_bytes // 1024):
+        for lane in range(64):
+            row, ch = lane // lanes, lane % lanes
+            if kind == "k":
+                chunk = ((ch ^ (row >> 1 if row_bytes == 128 else row)) * 16) ^ swizzle_k(row_bytes, j)
+            else:
+                chunk = ((ch ^ (2 * pair_of_v(row_bytes, row))) * 16) ^ swizzle_v(row_bytes, j)
+            assert 0 <= chunk < row_bytes
+            for i in range(0, 16, 2):
+                at[j * 1024 + lane * 16 + i] = (j * (64 // lanes) + row, chunk + i)
+    assert sorted(at) == list(range(0, keys * row_bytes, 2))
+    assert len(set(at.values())) == len(at)          # every element of the tile once
+    return at
+
+
+def bank_groups(addresses, width):
+    """Lanes served together: 256 bytes of the 64 banks at a time."""
+    per = 256 // width
+    for first in range(0, 64, per):
+        yield [(a // 4 + w) % 64 for a in addresses[first:first + per] for w in range(width // 4)]
+
+
+@pytest.mark.parametrize("D,keys", [(64, 32), (128, 16), (128, 32), (256, 16), (256, 32)])
+def test_key_fragments(D, keys):
+    row_bytes = 2 * D
+    at = loaded(row_bytes, keys, "k")
+    for h in range(keys // 16):
+        for ks in range(D // 32):
+            addresses = []
+            for lane in range(64):
+                c, g = lane & 15, lane >> 4
+                a = h * 16 * row_bytes + ((c * row_bytes + (g ^ (c >> 1 if D == 64 else c)) * 16) ^ ((ks & 3) * 64)) + (ks >> 2) * 256
+                addresses.append(a)
+                for e in range(8):               # lane (c, g): key c of the half, dimensions 32 ks + 8 g ..
+                    assert at[a + 2 * e] == (h * 16 + c, (ks * 32 + g * 8 + e) * 2)
+            for banks in bank_groups(addresses, 16):
+                assert len(set(banks)) == len(banks)
+
+
+@pytest.mark.parametrize("DV,keys", [(32, 16), (32, 32), (64, 16), (64, 32), (128, 16), (128, 32), (256, 16)])
+def test_value_fragments(DV, keys):
+    row_bytes = 2 * DV
+    at = loaded(row_bytes, keys, "v")
+    for h in range(keys // 16):
+        for dt in range(DV // 16):
+            addresses = []
+            for lane in range(64):
+                c, g = lane & 15, lane >> 4
+                row = g * 4 + (c >> 2)
+                a = h * 16 * row_bytes + ((row * row_bytes + pair_of_v(row_bytes, row) * 32 + (c & 3) * 8) ^ ((dt & 7) * 32)) + (dt >> 3) * 256
+                addresses.append(a)
+                for e in range(4):               # the transposing read takes 4 columns of row g*4 + c/4 from lane (c, g)
+                    assert at[a + 2 * e] == (h * 16 + row, (dt * 16 + (c & 3) * 4 + e) * 2)
+            for banks in bank_groups(addresses, 8):
+                assert len(set(banks)) == len(banks)
