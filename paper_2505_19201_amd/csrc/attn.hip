@@ -55,6 +55,7 @@ struct AttnArgs {
     int64_t s_max;
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
+    int32_t once;            // the caches will not be read again before others have displaced them (the ONCE forms of attend_rows)
 };
 
 // Visibility of the tree nodes to one query: bit (a % 64) of word a / 64 is set iff node a is visible.  MW = 1 serves
@@ -798,7 +799,7 @@ __device__ __forceinline__ void pair_meet(uint32_t meet, int wave, int count)
     asm volatile("" ::: "memory");
 }
 
-template <int D, int DS, int QT, int QS, int KG, int KEYS>
+template <int D, int DS, int QT, int QS, int KG, int KEYS, bool ONCE>
 __device__ __forceinline__ void attend_rows(const AttnArgs &a)
 {
     using G = RowsGeom<D, DS, QT, QS, KG, KEYS>;
@@ -843,7 +844,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             const unsigned char *p = kbase + (int64_t)t * (KEYS * KROW);
 #pragma unroll
             for (int j = 0; j < NK; j++)
-                lds_load16(p + j * 1024, (uint32_t)(krow * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
+                lds_load16<ONCE>(p + j * 1024, (uint32_t)(krow * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
         } else {
             // the ragged end: rows past the last live one are that one again (their scores are masked)
 #pragma unroll
@@ -856,7 +857,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             const unsigned char *p = vbase + (int64_t)t * (KEYS * KROW);
 #pragma unroll
             for (int j = 0; j < NV; j++)
-                lds_load16(p + j * (64 / LPV) * KROW, (uint32_t)(vrow * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
+                lds_load16<ONCE>(p + j * (64 / LPV) * KROW, (uint32_t)(vrow * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
         } else {
 #pragma unroll
             for (int j = 0; j < NV; j++)
@@ -1190,18 +1191,19 @@ using WaveGeom = RowsGeom<D, DS, QT, 1, NW, wave_keys<D, NW, DS>()>;
 template <int D, int DS, int QT>
 using PairGeom = RowsGeom<D, DS, QT, 2, 4, D == 256 ? 16 : 32>;
 
+// ONCE: the loads of whole tiles carry the nontemporal hint (see AttnArgs::once)
 // one query slot: NW key groups of one wave, QT query tiles and one of DS column slices a workgroup
-template <int D, int NW, int DS, int QT>
+template <int D, int NW, int DS, int QT, bool ONCE>
 __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a)
 {
-    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>()>(a);
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), ONCE>(a);
 }
 
 // two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
-template <int D, int DS, int QT>
+template <int D, int DS, int QT, bool ONCE>
 __global__ __launch_bounds__(512) void attn_pair_kernel(AttnArgs a)
 {
-    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32>(a);
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, ONCE>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1638,8 +1640,10 @@ int launch_bf16(const AttnArgs &a, const Plan &p, hipStream_t st)
 template <int D, int NW, int DS, int QT>
 int ensure_wave_lds()
 {
-    static std::atomic<uint64_t> done{0};
-    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT>), WaveGeom<D, NW, DS, QT>::BYTES, "attention");
+    static std::atomic<uint64_t> done[2];
+    constexpr size_t bytes = WaveGeom<D, NW, DS, QT>::BYTES;
+    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, false>), bytes, "attention");
+    return rc || DS == 4 ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, DS != 4>), bytes, "attention");
 }
 
 template <int D, int NW, int DS, int QT>
@@ -1648,15 +1652,20 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
     if (int rc = ensure_wave_lds<D, NW, DS, QT>())
         return rc;
     const dim3 grid(8 * ceil_div(a.n_qg, QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
-    hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
+    if (DS != 4 && a.once)
+        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, DS != 4>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
+    else
+        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, false>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
     return check_launch("attn_wave_kernel");
 }
 
 template <int D, int DS, int QT>
 int ensure_pair_lds()
 {
-    static std::atomic<uint64_t> done{0};
-    return raise_lds_limit(done, reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT>), PairGeom<D, DS, QT>::BYTES, "attention");
+    static std::atomic<uint64_t> done[2];
+    constexpr size_t bytes = PairGeom<D, DS, QT>::BYTES;
+    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, false>), bytes, "attention");
+    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, true>), bytes, "attention");
 }
 
 template <int D, int DS, int QT>
@@ -1665,7 +1674,10 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
     if (int rc = ensure_pair_lds<D, DS, QT>())
         return rc;
     const dim3 grid(8 * ceil_div(a.n_qg, 2 * QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
-    hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
+    if (a.once)
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, true>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
+    else
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, false>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
     return check_launch("attn_pair_kernel");
 }
 
@@ -1793,6 +1805,12 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     a.tiles_per_head = p.tiles_per_head; a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
     auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
     a.nq_magic = magic(n_q);
+    // Verification reads every layer's caches once a round; from 8 MB a layer on the 24 to 48 layers of a model displace each other in the 256 MB
+    // memory-side cache anyway, and the hint keeps them from displacing the rows other workgroups still read (us with plain loads / with the hint: 32 heads
+    // of head_dim 128 and 764 keys 8.97 / 8.73, 4 sequences of them 15.2 / 13.2; 8 sequences of 10 rows, head_dim 64, 20.1 / 17.8; but 5.5
+    // MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2:
+    // never).  A draft's one cache is read again at the next level.
+    a.once = include_self && (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 >= (8 << 20);
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;

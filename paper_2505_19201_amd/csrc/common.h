@@ -43,14 +43,18 @@ __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_
 
 // 16 bytes per lane from base + offset straight to LDS: lane i's land at lds + 16 * i.  Inline assembly, because the compiler
 // makes every LDS read wait for all such loads in flight; the caller waits with s_waitcnt vmcnt.  (Loads that the compiler
-// counts itself are only waited for longer than needed beside these.)
+// counts itself are only waited for longer than needed beside these.)  ONCE: with the nontemporal hint.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved; naming it as clobbered is right all the same
+template <bool ONCE = false>
 __device__ __forceinline__ void lds_load16(const void *base, uint32_t offset, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+    if (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
 }
-// the same with 4 bytes per lane
+// 4 bytes per lane
 __device__ __forceinline__ void lds_load4(const void *base, uint32_t offset, uint32_t lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
