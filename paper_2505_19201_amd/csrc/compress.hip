@@ -8,8 +8,8 @@
 //   scores_colsum_*  one workgroup per 64 visual keys, query rows streamed through LDS: sum over rows of
 //                    exp(score - lse), per head.
 // Every (sequence, head, row split, key) partial sum has one fixed order of additions, and the selection kernel adds
-// heads and splits in a fixed order, so scores are reproducible bit for bit.  Stage B finds the k-th largest score
-// (up to 2048 tokens four bits a round with all keys in registers, more of them with a radix select in LDS), keeps
+// heads and splits in a fixed order (in a launch of its own where they are many), so scores are reproducible bit for bit.  Stage B finds the
+// k-th largest score (up to 2048 tokens four bits a round with all keys in registers, more of them with a radix select in LDS), keeps
 // everything above it plus the first ties in position order, and numbers the survivors in position order; the optional
 // gather copies the surviving rows of a [rows, row_elems] matrix.
 #include "common.h"
@@ -808,30 +808,70 @@ __global__ __launch_bounds__(1024) void topk_keep_kernel(const float *part, int 
     }
 }
 
-// Up to 2048 visual tokens: the same selection with all keys in the registers of every wave (NR of them per lane, token r * 64 +
-// lane in register r).  Latency bound, one workgroup per sequence, so it is built from few dependent steps: the partial sums
-// are added by all 1024 threads (a thread takes VEC tokens and every n_groups-th partial row, the groups meet in LDS in order),
-// the k-th largest key is found four bits a round, each of the 16 waves counting the keys at or above one of 16 trial
-// values, and the search ends as soon as a value keeps exactly k; survivors are numbered with ballots.
-// Measured, 576 tokens: 11.6 us with the kernel above (4 rounds of loads, 4 radix passes of 5 barriers), 8.8 us here with
-// four times the partial rows.
+// Adds the partial column sums of 64 tokens of one sequence, all heads and row splits, into row 0: one workgroup of 16 waves, wave w the
+// rows w, w + 16, ... in order, then the waves in order.  (The sums are a few hundred KB: one CU pulls them in about 5 us, the
+// many of this launch at once.)
+__global__ __launch_bounds__(1024) void sum_parts_kernel(float *part, int n_parts, int vis_len)
+{
+    __shared__ float s_sum[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
+    float *at = part + (int64_t)blockIdx.y * n_parts * vis_len + min(j, vis_len - 1);
+    float x = 0.0f;
+    for (int i0 = wave; i0 < n_parts; i0 += 16 * 8) {
+        float t[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            t[u] = i0 + 16 * u < n_parts ? at[(int64_t)(i0 + 16 * u) * vis_len] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            x += t[u];
+    }
+    s_sum[wave][lane] = x;
+    __syncthreads();
+    if (wave == 0 && j < vis_len) {
+        x = s_sum[0][lane];
+#pragma unroll
+        for (int w = 1; w < 16; w++)
+            x += s_sum[w][lane];
+        *at = x;
+    }
+}
+
+// Up to 2048 visual tokens: the same selection, and the copy of the kept rows where it is asked for.  NR: tokens per lane if one wave held
+// them all.  Latency bound, so it is built from few dependent steps.  The k-th largest key is found four bits a round: lane
+// (trial, group) of wave w counts the keys at or above one of 16 trial values in a quarter of the wave's sixteenth of the tokens
+// (16 lanes read the same four keys at once), and the search ends as soon as a value keeps exactly k; survivors are numbered
+// with ballots.  Several workgroups per sequence all find the same selection and copy some of the kept rows each, which is faster than a
+// launch for the copy.
+// n_parts partial sums a token are added here (a thread takes VEC tokens and every n_groups-th partial row, the groups meet in LDS in
+// order) where they are few; of a sum formed by sum_parts_kernel n_parts is 1 and the rows of a sequence are `stride` apart.
+// Measured, LLaVA prompt (576 tokens, 128 partial rows) / 16 SmolVLM prompts (1088 tokens, 32), us: one kernel for sums and selection and a gather
+// 9.8 + 3.3 / 18.5 + 7.7; here sums 3.0, selection with gather 6.2 / sums 4.8, selection 9.8, gather 7.5.
+struct GatherArgs {
+    const unsigned char *src;      // NULL: no gather
+    unsigned char *dst;
+    int64_t n_rows_src, row_bytes;
+    int32_t lanes;                 // threads per row (a power of two)
+};
 template <int NR>
-__global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int n_parts, const float *scores_in, float *scores_out, int vis_start,
-                                                          int vis_len, int k, int vec, int32_t *kept_idx)
+__global__ __launch_bounds__(1024) void select_kernel(const float *part, int64_t stride, int n_parts, const float *scores_in, float *scores_out, int vis_start,
+                                                      int vis_len, int k, int vec, int32_t *kept_idx, GatherArgs ga)
 {
     constexpr int V = NR * 64;
-    __shared__ __attribute__((aligned(16))) float s_sum[4096 > V ? 4096 : V];   // [group][vis_len]
-    __shared__ uint32_t s_key[V];
-    __shared__ int s_cnt[2][16];
+    __shared__ __attribute__((aligned(16))) float s_sum[4096 > V ? 4096 : V];   // [group][vis_len]; then the kept tokens
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[V];
+    __shared__ int s_cnt[2][16][16];
     __shared__ int s_gt[32], s_eq[32];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float *mine = scores_in ? scores_in + (int64_t)b * vis_len : part + b * stride;
+    const bool many = !scores_in && n_parts > 1;
     int n_groups = 1;
-    if (!scores_in) {
+    if (many) {
         const int cols = vec ? vis_len / 4 : vis_len;                   // (vec: rows of partial sums are 16-byte aligned)
         n_groups = min(max(1024 / cols, 1), min(n_parts, 4096 / vis_len));
         for (int col = tid % cols, grp = tid / cols; grp < n_groups && col < cols; col += vec ? cols : 1024) {
             if (vec) {
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(part + ((int64_t)b * n_parts + grp) * vis_len) + col;
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(mine + (int64_t)grp * vis_len) + col;
                 const int64_t step = (int64_t)n_groups * (vis_len / 4);
                 f32x4 x = {0.f, 0.f, 0.f, 0.f};
                 for (int i = grp; i < n_parts; i += n_groups * 16) {
@@ -846,7 +886,7 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int
                 }
                 reinterpret_cast<f32x4 *>(s_sum + grp * vis_len)[col] = x;
             } else {
-                const float *src = part + ((int64_t)b * n_parts + grp) * vis_len + col;
+                const float *src = mine + (int64_t)grp * vis_len + col;
                 float x = 0.0f;
 #pragma unroll 8
                 for (int i = grp; i < n_parts; i += n_groups)
@@ -860,13 +900,13 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int
         uint32_t key = 0u;                                               // below every score's key
         if (j < vis_len) {
             float x = 0.0f;
-            if (scores_in) {
-                x = scores_in[(int64_t)b * vis_len + j];
+            if (!many) {
+                x = mine[j];
             } else {
                 for (int g = 0; g < n_groups; g++)
                     x += s_sum[g * vis_len + j];
             }
-            if (scores_out)
+            if (scores_out && blockIdx.x == 0)
                 scores_out[(int64_t)b * vis_len + j] = x;
             key = order_key(x);
         }
@@ -875,36 +915,37 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int
     if (k <= 0)
         return;
     __syncthreads();
-    uint32_t key[NR];
+    u32x4 key[NR / 4];
+    const int group = lane >> 4;
 #pragma unroll
-    for (int r = 0; r < NR; r++)
-        key[r] = s_key[r * 64 + lane];
+    for (int r = 0; r < NR / 4; r++)
+        key[r] = reinterpret_cast<const u32x4 *>(s_key)[(wave * 4 + group) * (NR / 4) + r];
     // the largest value with at least k keys at or above it, four bits a round
     uint32_t tau = 0u;
     int at_tau = vis_len;
     for (int shift = 28; shift >= 0 && at_tau != k; shift -= 4) {
+        const uint32_t trial = max(tau | ((uint32_t)(lane & 15) << shift), 1u);    // (key 0 is no token)
         int n = 0;
-        const uint32_t trial = tau | ((uint32_t)wave << shift);
 #pragma unroll
-        for (int r = 0; r < NR; r++)
-            n += __popcll(__ballot(key[r] >= trial && key[r] != 0u));
-        const int buf = (shift >> 2) & 1;
-        if (lane == 0)
-            s_cnt[buf][wave] = n;
+        for (int r = 0; r < NR / 4; r++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                n += key[r][e] >= trial ? 1 : 0;
+        n += __shfl_xor(n, 16);
+        n += __shfl_xor(n, 32);
+        auto cnt = s_cnt[(shift >> 2) & 1];
+        if (group == 0)
+            cnt[wave][lane] = n;
         __syncthreads();
-        const int c = s_cnt[buf][lane & 15];
+        int c = (cnt[group * 4][lane & 15] + cnt[group * 4 + 1][lane & 15]) + (cnt[group * 4 + 2][lane & 15] + cnt[group * 4 + 3][lane & 15]);
+        c += __shfl_xor(c, 16);
+        c += __shfl_xor(c, 32);
         const int digit = 63 - __builtin_clzll(__ballot(c >= k && lane < 16));    // (trial 0 of the digit always has k keys)
         tau |= (uint32_t)digit << shift;
         at_tau = __builtin_amdgcn_readlane(c, digit);
     }
-    // more keys at or above it than asked for: the first of those equal to it, in position order
-    int above = 0;
-    if (at_tau != k) {
-#pragma unroll
-        for (int r = 0; r < NR; r++)
-            above += __popcll(__ballot(key[r] > tau));
-    }
-    const int need = at_tau == k ? V : k - above;
+    // how many keys are above it and equal to it before every chunk of 64; with more keys than asked for the first of those equal to it
+    // are kept, in position order
     constexpr int CHUNKS = NR;
     for (int ch = wave; ch < CHUNKS; ch += 16) {
         const uint32_t u = s_key[ch * 64 + lane];
@@ -916,9 +957,14 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int
     }
     __syncthreads();
     const int g_all = lane < CHUNKS ? s_gt[lane] : 0, e_all = lane < CHUNKS ? s_eq[lane] : 0;
+    int above = g_all;
+    for (int off = 16; off > 0; off >>= 1)                               // (chunks are on lanes 0..31)
+        above += __shfl_xor(above, off);
+    const int need = k - __builtin_amdgcn_readfirstlane(above);
+    int32_t *s_kept = reinterpret_cast<int32_t *>(s_sum);
     for (int ch = wave; ch < CHUNKS; ch += 16) {
         int g_before = lane < ch ? g_all : 0, e_before = lane < ch ? e_all : 0;
-        for (int off = 16; off > 0; off >>= 1) {                        // (chunks are on lanes 0..31)
+        for (int off = 16; off > 0; off >>= 1) {
             g_before += __shfl_xor(g_before, off);
             e_before += __shfl_xor(e_before, off);
         }
@@ -928,8 +974,30 @@ __global__ __launch_bounds__(1024) void topk_small_kernel(const float *part, int
         const uint64_t below = (1ull << lane) - 1ull, ties = __ballot(u == tau && u != 0u);
         const bool keep = u > tau || (u == tau && u != 0u && e_before + (int)__popcll(ties & below) < need);
         const uint64_t kept = __ballot(keep);
-        if (keep)
-            kept_idx[(int64_t)b * k + g_before + min(e_before, need) + (int)__popcll(kept & below)] = vis_start + ch * 64 + lane;
+        if (keep) {
+            const int at = g_before + min(e_before, need) + (int)__popcll(kept & below), token = vis_start + ch * 64 + lane;
+            if (blockIdx.x == 0)
+                kept_idx[(int64_t)b * k + at] = token;
+            s_kept[at] = token;
+        }
+    }
+    if (!ga.src)
+        return;
+    __syncthreads();
+    const int lanes = ga.lanes, per = 1024 / lanes, col = tid & (lanes - 1);
+    const unsigned char *src = ga.src + (int64_t)b * ga.n_rows_src * ga.row_bytes;
+    unsigned char *dst = ga.dst + (int64_t)b * k * ga.row_bytes;
+    const bool wide = ((ga.row_bytes | (uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+    for (int t = blockIdx.x * per + tid / lanes; t < k; t += gridDim.x * per) {
+        const unsigned char *s = src + (int64_t)s_kept[t] * ga.row_bytes;
+        unsigned char *d = dst + (int64_t)t * ga.row_bytes;
+        if (wide) {
+            for (int64_t i = col; i < ga.row_bytes / 16; i += lanes)
+                reinterpret_cast<uint4 *>(d)[i] = reinterpret_cast<const uint4 *>(s)[i];
+        } else {
+            for (int64_t i = col; i < ga.row_bytes; i += lanes)
+                d[i] = s[i];
+        }
     }
 }
 
@@ -1172,11 +1240,38 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
     }
     if (n_kept_host)
         *n_kept_host = k;
+    const int64_t row_bytes = gather_src ? row_elems * (desc->dtype == DREAM_F32 ? 4 : 2) : 0;
     if (vis_len > 0 && (k > 0 || scores_out)) {
         if (vis_len <= 2048) {
+            // From 64 KB of partial sums a sequence on a launch of its own adds them; see sum_parts_kernel.
+            int64_t stride = (int64_t)n_heads * vis_len;
+            if (part && stride >= 16384) {
+                hipLaunchKernelGGL(sum_parts_kernel, dim3(ceil_div(vis_len, 64), desc->batch), dim3(1024), 0, st, const_cast<float *>(part), n_heads, vis_len);
+                if (int rc = check_launch("sum_parts_kernel"))
+                    return rc;
+                n_heads = 1;
+            }
+            // The selection's own workgroups copy the rows while one round of them does it: each finds the selection for itself, 4.6 us of the
+            // 6.2 with 72 workgroups for one LLaVA prompt (4.6 and a gather of 2.7 us apart), but 22 us with 32 workgroups for each of 16 SmolVLM
+            // prompts (9.8 and 7.5 us apart).
+            GatherArgs ga = {nullptr, static_cast<unsigned char *>(gather_dst), n_rows_src, row_bytes, 1024};
+            int wgs = 1;
+            if (gather_src && k > 0) {
+                while (ga.lanes > 64 && ga.lanes / 2 >= row_bytes / 16)
+                    ga.lanes /= 2;
+                wgs = ceil_div(k, 1024 / ga.lanes);
+                if ((int64_t)wgs * desc->batch <= 256)
+                    ga.src = static_cast<const unsigned char *>(gather_src);
+                else
+                    wgs = 1;
+            }
             const int vec = vis_len % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0;
-            auto kernel = vis_len <= 512 ? topk_small_kernel<8> : vis_len <= 1024 ? topk_small_kernel<16> : topk_small_kernel<32>;
-            hipLaunchKernelGGL(kernel, dim3(desc->batch), dim3(1024), 0, st, part, n_heads, scores_in, scores_out, vis_start, vis_len, k, vec, kept_idx);
+            static constexpr decltype(&select_kernel<4>) SELECT[] = {select_kernel<4>,  select_kernel<8>,  select_kernel<12>, select_kernel<16>,
+                                                                     select_kernel<20>, select_kernel<24>, select_kernel<28>, select_kernel<32>};
+            hipLaunchKernelGGL(SELECT[(vis_len - 1) / 256], dim3(wgs, desc->batch), dim3(1024), 0, st, part, stride, n_heads, scores_in, scores_out, vis_start,
+                               vis_len, k, vec, kept_idx, ga);
+            if (ga.src)
+                return check_launch("select_kernel");
         } else {
             const size_t lds = (size_t)vis_len * 4 + (256 + 32 + 4) * 4;
             if (int rc = ensure_topk_lds(who))
@@ -1184,12 +1279,11 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
             hipLaunchKernelGGL(topk_keep_kernel, dim3(desc->batch), dim3(1024), lds, st, part, n_heads, scores_in, scores_out,
                                vis_start, vis_len, k, kept_idx);
         }
-        int rc = check_launch("topk_keep_kernel");
+        int rc = check_launch("selection kernel");
         if (rc)
             return rc;
     }
     if (gather_src && k > 0) {
-        const int64_t row_bytes = row_elems * (desc->dtype == DREAM_F32 ? 4 : 2);
         hipLaunchKernelGGL(gather_rows_kernel, dim3(k, desc->batch), dim3(256), 0, st,
                            static_cast<const unsigned char *>(gather_src), n_rows_src, row_bytes, kept_idx, k,
                            static_cast<unsigned char *>(gather_dst));

@@ -323,3 +323,18 @@ def test_rows_that_are_not_16_byte_aligned(gu, D, P, v, shift_q, shift_k):
 
     for got, want in zip(results(shift_q, shift_k), results(0, 0)):
         assert np.isfinite(got).all() and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("v", [1, 255, 256, 257, 768, 769, 1281, 1793])
+@pytest.mark.parametrize("B,row_elems", [(1, 8), (2, 1000), (1, 8200), (40, 64), (3, 7)])
+def test_selection_with_its_rows(gu, v, B, row_elems):
+    """Registers filled to the last token and one over; rows copied by the selection's own workgroups (few sequences) and by a launch of
+    their own (40 sequences), rows of fewer chunks than lanes, of more, and of bytes that are no multiple of 16.  Scores with ties: bit for bit."""
+    rng = np.random.default_rng(v * 31 + B)
+    scores = rng.integers(0, max(v // 3, 2), size=(B, v)).astype(np.float32) / 7.0
+    src = rng.integers(0, 1 << 16, size=(B, v + 5, row_elems)).astype(np.uint16)
+    _, kept, rows = gu.run_compress("bf16", None, None, v + 5, 3, v, 1, 2, scores_in=scores, gather_src=src)
+    want = oracle.topk_keep(scores, 3, 1, 2)
+    assert np.array_equal(kept, want)
+    for b in range(B):
+        assert np.array_equal(rows[b], src[b][want[b]])
