@@ -156,6 +156,7 @@ struct RowStream {
 // second pass.
 // Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 22.2 us, 16 SmolVLM sequences 251 -> 200 us.
 // The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
+// The reference raised by octaves and a step's fragments requested together: 22.7 -> 21.7 us and 188 -> 185 us for larger prompts, all launches.
 template <int D, bool ENT, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
@@ -247,60 +248,80 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 #pragma unroll
         for (int q = 0; q < CT; q++)
             acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bf16x8 kf[NKS][2];                                       // requested together: the waits then fall behind the first products
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++) {
-            const bf16x8 k0 = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
-            const bf16x8 k1 = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
+            kf[ks][0] = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
+            kf[ks][1] = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++)
 #pragma unroll
             for (int q = 0; q < CT; q++) {
-                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qf[q][ks], acc[q][0], 0, 0, 0);
-                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qf[q][ks], acc[q][1], 0, 0, 0);
+                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][0], qf[q][ks], acc[q][0], 0, 0, 0);
+                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][1], qf[q][ks], acc[q][1], 0, 0, 0);
             }
-        }
         const bool open = key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f;
+        // A column's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
+        // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores
+        auto add_scores = [&](const float(&mx)[CT], float mult) {
+            bool raise = false;
 #pragma unroll
-        for (int q = 0; q < CT; q++) {
-            float sum = 0.0f, xsum = 0.0f, m_new, m_safe;
-            if (open) {
-                // every key of the half is visible to every row of the wave (all but those on the diagonal):
-                // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
-                const f32x4 u = acc[q][0], v = acc[q][1];
-                const float mx = fmaxf(fmaxf(fmaxf(u[0], u[1]), fmaxf(u[2], u[3])), fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
-                m_new = fmaxf(m[q], mx * a.scale_log2);
-                m_safe = m_new;   // finite: there are visible keys
+            for (int q = 0; q < CT; q++)
+                raise = raise || mx[q] > m[q] + 8.0f;
+            if (__any(raise)) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float raw = acc[q][e >> 2][e & 3];
-                    const float p = __builtin_amdgcn_exp2f(fmaf(raw, a.scale_log2, -m_safe));
-                    sum += p;
+                for (int q = 0; q < CT; q++) {
+                    const float m_new = mx[q] > m[q] + 8.0f ? mx[q] : m[q], alpha = m_new == m[q] ? 1.0f : __builtin_amdgcn_exp2f(m[q] - m_new);   // (0 when the old reference was -inf)
+                    m[q] = m_new;
+                    l[q] *= alpha;
                     if (ENT)
-                        xsum = fmaf(p, raw, xsum);
-                }
-                if (ENT)
-                    xsum *= a.scale_log2;
-            } else {
-                const int lim = min(pos[q], a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 16 * (e / 4) + e % 4 is visible up to here
-                float x[8], mx = -INFINITY;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    x[e] = (e >> 2) * 16 + (e & 3) <= lim ? acc[q][e >> 2][e & 3] * a.scale_log2 : -INFINITY;
-                    mx = fmaxf(mx, x[e]);
-                }
-                m_new = fmaxf(m[q], mx);
-                m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float p = __builtin_amdgcn_exp2f(x[e] - m_safe);
-                    sum += p;
-                    if (ENT)
-                        xsum += p * (x[e] == -INFINITY ? 0.0f : x[e]);
+                        tx[q] *= alpha;
                 }
             }
-            const float alpha = __builtin_amdgcn_exp2f(m[q] - m_safe);
-            l[q] = l[q] * alpha + sum;
-            if (ENT)
-                tx[q] = tx[q] * alpha + xsum;
-            m[q] = m_new;
+#pragma unroll
+            for (int q = 0; q < CT; q++) {
+                const float neg_m = m[q] == -INFINITY ? 0.0f : -m[q];
+                float sum = 0.0f, xsum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const float x = acc[q][e >> 2][e & 3], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
+                    sum += p;
+                    if (ENT)
+                        xsum = fmaf(p, x, xsum);
+                }
+                l[q] += sum;
+                if (ENT)
+                    tx[q] = fmaf(xsum, mult, tx[q]);
+            }
+        };
+        float mx[CT];
+        if (open) {
+            // every key of the half is visible to every row of the wave (all but those on the diagonal):
+            // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
+#pragma unroll
+            for (int q = 0; q < CT; q++) {
+                float x = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    x = fmaxf(x, acc[q][e >> 2][e & 3]);
+                mx[q] = x * a.scale_log2;
+            }
+            add_scores(mx, a.scale_log2);
+        } else {
+#pragma unroll
+            for (int q = 0; q < CT; q++) {
+                const int lim = min(pos[q], a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 16 * (e / 4) + e % 4 is visible up to here
+                mx[q] = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const float x = (e >> 2) * 16 + (e & 3) <= lim ? acc[q][e >> 2][e & 3] * a.scale_log2 : -INFINITY;
+                    acc[q][e >> 2][e & 3] = ENT ? fmaxf(x, -3.0e38f) : x;    // (finite, so that times a probability of 0 it is 0)
+                    mx[q] = fmaxf(mx[q], x);
+                }
+            }
+            add_scores(mx, 1.0f);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
