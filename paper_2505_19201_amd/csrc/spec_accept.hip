@@ -7,22 +7,23 @@
 // token is drawn from the current target distribution by inverting its cumulative sum in token order.  The
 // uniform random numbers are inputs.
 //
-// Two launches.  softmax_stats_kernel (parallel over rows and 8192-logit chunks) leaves (max, sum of exponentials)
+// Two launches.  softmax_stats_kernel (parallel over rows and chunks of them) leaves (max, sum of exponentials)
 // per chunk for the target and the draft row of every node with children: the only rows a test can need.
 // spec_walk_kernel then evaluates the test of every node against its parent's untouched distributions in parallel:
 // that is exactly the test the walk performs whenever a node is the first child tried, so the walk descends through
-// first children by table lookup.  A rejection needs one number that no table holds, the mass of the new residual
+// first children by table lookup.  Where the rows are many the first launch covers the roots only, and the walk works out the statistics of
+// a node's two rows when it comes to the node: a handful of nodes per sequence instead of all.
+// A rejection needs one number that no table holds, the mass of the new residual
 // over the whole vocabulary.  Every residual is a pointwise function of the two logits of a token and of a few
 // scalars (the masses of the residuals before it), so it is recomputed from the logit rows and never stored; several
 // workgroups share a sequence, each sums its chunks and all exchange one float per chunk.  The masses also give the
 // draw, which then reads one chunk.  Every reduction has a fixed order, so the result is reproducible.
-// Roofline: HBM, one read of the logit rows of nodes with children.
+// Bound by latency: the exchanges between the workgroups of a sequence follow each other, one per rejection and, with few statistics
+// beforehand, one per node.
 //
-// Why several workgroups: one CU pulls about 50 GB/s, 20 us and more for one pass over two float32 rows of 131072
-// tokens, and the walk made one or more such passes for every second rejection at a node (three float arrays per sequence in the
-// workspace), after a launch that summed the first residual of every node of the tree, visited or not.  Measured, 4
-// sequences x 60 nodes x 131072 float32 logits: 200-262 us per call with one workgroup per sequence, 61-81 us here, depending on how many
-// children the inputs make the walk reject (20 us the statistics; a rejection about 4 us).
+// Why several workgroups: one CU pulls 60 to 75 GB/s, 14 us and more for one pass over two float32 rows of 131072 tokens.
+// Measured, us per call (mean of 4 inputs), one read of all rows with children and a walk in chunks of 8192 tokens / now: 4 sequences x 60 nodes x
+// 131072 float32 logits 65.3 / 50.6, 8 x 60 x 262144 bf16 109.5 / 64.4, 32 x 60 x 32000 float32 91.0 / 53.9, 1 x 60 x 32000 bf16 27.1 / 24.2.
 #include "common.h"
 #include <algorithm>
 #include <type_traits>
@@ -40,34 +41,29 @@ __device__ __forceinline__ float load_logit(const void *p, int64_t i)
     return BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[i]) : reinterpret_cast<const float *>(p)[i];
 }
 
-// block-wide reductions over the walk's threads in a fixed order; `red` holds one value per wave
-__device__ __forceinline__ float block_sum(float v, float *red, int tid)
+// Wave-wide reductions in a fixed order, in every lane: rotations inside the rows of 16 lanes (register moves; a shuffle is a trip through
+// LDS), then the four rows' values as scalars.
+template <int ROT>
+__device__ __forceinline__ float rotate(float v)
 {
-    for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_xor(v, off);
-    __syncthreads();
-    if ((tid & 63) == 0)
-        red[tid >> 6] = v;
-    __syncthreads();
-    float t = 0.0f;
-#pragma unroll
-    for (int w = 0; w < NW; w++)
-        t += red[w];
-    return t;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));   // row_ror:ROT
 }
-__device__ __forceinline__ float block_max(float v, float *red, int tid)
+__device__ __forceinline__ float of_row(float v, int row) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16)); }
+__device__ __forceinline__ float wave_sum(float v)
 {
-    for (int off = 32; off > 0; off >>= 1)
-        v = fmaxf(v, __shfl_xor(v, off));
-    __syncthreads();
-    if ((tid & 63) == 0)
-        red[tid >> 6] = v;
-    __syncthreads();
-    float t = red[0];
-#pragma unroll
-    for (int w = 1; w < NW; w++)
-        t = fmaxf(t, red[w]);
-    return t;
+    v += rotate<8>(v);
+    v += rotate<4>(v);
+    v += rotate<2>(v);
+    v += rotate<1>(v);
+    return (of_row(v, 0) + of_row(v, 1)) + (of_row(v, 2) + of_row(v, 3));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, rotate<8>(v));
+    v = fmaxf(v, rotate<4>(v));
+    v = fmaxf(v, rotate<2>(v));
+    v = fmaxf(v, rotate<1>(v));
+    return fmaxf(fmaxf(of_row(v, 0), of_row(v, 1)), fmaxf(of_row(v, 2), of_row(v, 3)));
 }
 __device__ __forceinline__ int block_min_int(int v, int *red, int tid)
 {
@@ -84,7 +80,11 @@ __device__ __forceinline__ int block_min_int(int v, int *red, int tid)
     return t;
 }
 
-constexpr int STAT_CHUNK = 8192;    // logits per workgroup of the statistics pass
+// Logits of a chunk: a workgroup's share of the statistics pass, and what a workgroup of the walk keeps in its registers.  PER groups of 8 a
+// thread of the walk: 1, or 2 or 4 where the walk's workgroups would otherwise have several chunks each and read them again in
+// every round.
+template <int PER>
+constexpr int CHUNK = NT * 8 * PER;
 
 // tokens t .. t+7 of a row (t a multiple of 8); `vec`: the row is 16-byte aligned and holds a multiple of 8 tokens.
 // Tokens past the end come back as -inf.
@@ -117,24 +117,23 @@ __device__ __forceinline__ void load8(const void *base, int64_t row, int t, int 
 __device__ __forceinline__ float token_mass(float logit, float inv_temp, float m, float inv_z) { return __expf(fmaf(logit, inv_temp, -m)) * inv_z; }
 __device__ __forceinline__ float residual(float P, float jp, float Q, float jq) { return fmaxf(fmaf(P, jp, -(Q * jq)), 0.0f); }
 
-// Exchange of the walk's partial sums: slots [B][2][2][MAX_SEG] of (round << 32 | float bits), cleared by
+// Exchange of the walk's partial sums: slots [B][2][MAX_VAL][MAX_SEG] of (round << 32 | float bits), cleared by
 // softmax_stats_kernel, which the stream orders before the walk.
-constexpr int MAX_SEG = 64;
-constexpr int SLOTS = 2 * 2 * MAX_SEG;
+constexpr int MAX_SEG = 64, MAX_VAL = 4;
+constexpr int SLOTS = 2 * MAX_VAL * MAX_SEG;
 
-// (max, sum of exp(x/temp - max)) of one 8192-logit chunk of one row.  z = 0: target rows; z = 1: draft rows; nothing
-// for nodes without children (a leaf's target row is summed by the walk if the walk ends there).
-template <bool BF16>
-__global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits, const void *dlogits, int n_tree, int vocab,
+// (max, sum of exp(x/temp - max)) of one chunk of one row of the first n_nodes nodes of a sequence.  z = 0: target rows;
+// z = 1: draft rows; nothing for nodes without children (a leaf's target row is summed by the walk if the walk ends there).
+template <bool BF16, int PER>
+__global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits, const void *dlogits, int n_tree, int n_nodes, int vocab,
                                                             int n_chunks, bool vec, const int32_t *parent, float inv_temp,
                                                             float *stat_m, float *stat_s, uint64_t *slots)
 {
     const int chunk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t node_row = blockIdx.y;                      // b * n_tree + node
-    const int which = blockIdx.z;
-    const int64_t slot = ((int64_t)which * gridDim.y + node_row) * n_chunks + chunk;
+    const int b = blockIdx.y / n_nodes, node = blockIdx.y - b * n_nodes, which = blockIdx.z;
+    const int64_t node_row = (int64_t)b * n_tree + node, rows_all = (int64_t)(gridDim.y / n_nodes) * n_tree;
+    const int64_t slot = (which * rows_all + node_row) * n_chunks + chunk;
     __shared__ float red[4];
-    const int b = (int)(node_row / n_tree), node = (int)(node_row - (int64_t)b * n_tree);
     if (slots && chunk == 0 && node == 0 && which == 0)
         for (int i = tid; i < SLOTS; i += 256)
             slots[(int64_t)b * SLOTS + i] = 0;
@@ -145,6 +144,7 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
         return;
     const void *base = which ? dlogits : tlogits;
     const int64_t row = node_row * vocab;
+    constexpr int STAT_CHUNK = CHUNK<PER>;
     const int begin = chunk * STAT_CHUNK;
     float x[STAT_CHUNK / 256];
     float m = -INFINITY;
@@ -157,8 +157,7 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
             m = fmaxf(m, x[8 * r + j]);
         }
     }
-    for (int off = 32; off > 0; off >>= 1)
-        m = fmaxf(m, __shfl_xor(m, off));
+    m = wave_max(m);
     if (lane == 0)
         red[wave] = m;
     __syncthreads();
@@ -169,8 +168,7 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
         for (int j = 0; j < STAT_CHUNK / 256; j++)
             sum += __expf(x[j] - m);                          // exp(-inf) = 0 for the padding
     }
-    for (int off = 32; off > 0; off >>= 1)
-        sum += __shfl_xor(sum, off);
+    sum = wave_sum(sum);
     __syncthreads();
     if (lane == 0)
         red[wave] = sum;
@@ -205,6 +203,7 @@ struct WalkArgs {
     int n_tree, vocab, n_chunks;
     int seg_chunks, n_seg;         // a row is n_seg <= MAX_SEG segments of seg_chunks chunks (one chunk up to 524288 tokens)
     bool vec;
+    bool lazy;                     // statistics of the roots only; the walk works out those of the nodes it comes to
     const int32_t *token, *parent;
     const float *u_accept, *u_bonus;
     int max_depth;
@@ -223,7 +222,7 @@ struct WalkArgs {
 // Nothing depends on the workgroups running at the same time: a wait is bounded, workgroup 0 sums missing segments itself
 // (token_mass and residual, added in the same order, so the same bits) and waits for nobody again, any other workgroup that waited in vain ends.
 // Only workgroup 0 writes results.
-template <bool BF16>
+template <bool BF16, int PER>
 __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 {
     __shared__ int32_t s_par[DREAM_MAX_TREE_ACCEPT];
@@ -238,16 +237,17 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
     __shared__ float s_ip[DREAM_MAX_TREE_ACCEPT], s_iq[DREAM_MAX_TREE_ACCEPT];
     __shared__ int32_t s_x[DREAM_MAX_TREE_ACCEPT];
     __shared__ uint8_t s_take[DREAM_MAX_TREE_ACCEPT];
-    __shared__ float s_part[2][MAX_SEG], s_mass[MAX_SEG];
-    __shared__ float s_redf[NW], s_scan[NW];
+    __shared__ float s_part[MAX_VAL][MAX_SEG], s_mass[MAX_SEG];
+    __shared__ float s_red[2][4][NW], s_scan[NW];
     __shared__ int s_redi[NW];
-    constexpr int NONE = 0x7fffffff;
+    constexpr int NONE = 0x7fffffff, STAT_CHUNK = CHUNK<PER>;
     const int b = blockIdx.y, wg = blockIdx.x, n_wg = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_tree = a.n_tree, vocab = a.vocab, n_chunks = a.n_chunks, n_seg = a.n_seg;
     const bool vec = a.vec;
     const float inv_temp = a.inv_temp;
     const int64_t bt = (int64_t)b * n_tree, rows_all = (int64_t)gridDim.y * n_tree;
     const int max_depth = a.max_depth;
+    const int n_known = a.lazy ? 1 : n_tree;     // nodes whose statistics the launch before has left
     // Everything a test needs is brought into LDS up front, with as few dependent trips to memory as there are: (parent,
     // token, random number), then (the two logits of every node's token at its parent; the chunk statistics).
     for (int i = tid; i < n_tree; i += NT) {
@@ -272,34 +272,34 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         if (i > 0 && s_par[i] >= 0)
             atomicMin(&s_first[s_par[i]], i);
     __syncthreads();
-    if (n_chunks <= 32) {
-        // a node per pass of a wave: its target row's chunks on lanes 0..31, its draft row's on 32..63; four nodes' loads in flight
-        const int c = lane & 31;
-        for (int i0 = wave * 4; i0 < n_tree; i0 += NW * 4) {
-            float m[4], z[4];
+    if (n_chunks <= 64) {
+        // a node per pass of a wave, a chunk per lane; four nodes' loads in flight
+        for (int i0 = wave * 4; i0 < n_known; i0 += NW * 4) {
+            float m[4][2], z[4][2];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                const bool live = i0 + u < n_tree && c < n_chunks && s_first[min(i0 + u, n_tree - 1)] != NONE;
-                const int64_t at = live ? ((lane < 32 ? 0 : rows_all) + bt + i0 + u) * n_chunks + c : 0;
-                m[u] = live ? a.stat_m[at] : -INFINITY;
-                z[u] = live ? a.stat_s[at] : 0.0f;
-            }
+                const bool live = i0 + u < n_known && lane < n_chunks && s_first[min(i0 + u, n_tree - 1)] != NONE;
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                float mx = m[u];
-                for (int off = 16; off > 0; off >>= 1)
-                    mx = fmaxf(mx, __shfl_xor(mx, off));
-                float sum = z[u] > 0.0f ? z[u] * __expf(m[u] - mx) : 0.0f;
-                for (int off = 16; off > 0; off >>= 1)
-                    sum += __shfl_xor(sum, off);
-                if (c == 0 && i0 + u < n_tree && s_first[i0 + u] != NONE) {
-                    (lane < 32 ? s_mt : s_md)[i0 + u] = mx;
-                    (lane < 32 ? s_zt : s_zd)[i0 + u] = sum;
+                for (int w = 0; w < 2; w++) {
+                    const int64_t at = live ? (w * rows_all + bt + i0 + u) * n_chunks + lane : 0;
+                    m[u][w] = live ? a.stat_m[at] : -INFINITY;
+                    z[u][w] = live ? a.stat_s[at] : 0.0f;
                 }
             }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int w = 0; w < 2; w++) {
+                    const float mx = wave_max(m[u][w]);
+                    const float sum = wave_sum(z[u][w] > 0.0f ? z[u][w] * __expf(m[u][w] - mx) : 0.0f);
+                    if (lane == 0 && i0 + u < n_known && s_first[i0 + u] != NONE) {
+                        (w ? s_md : s_mt)[i0 + u] = mx;
+                        (w ? s_zd : s_zt)[i0 + u] = sum;
+                    }
+                }
         }
     } else {
-        for (int i = wave; i < n_tree; i += NW) {
+        for (int i = wave; i < n_known; i += NW) {
             if (s_first[i] == NONE)
                 continue;
             float mt, zt, md, zd;
@@ -311,15 +311,19 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         }
     }
     __syncthreads();
-    for (int i = tid; i < n_tree; i += NT) {
-        const int p = s_par[i];
-        if (i > 0 && p >= 0) {
-            const float px = s_px[i] = __expf(s_px[i] - s_mt[p]);
-            const float qx = s_qx[i] = __expf(s_qx[i] - s_md[p]);
-            const float ratio = qx > 0.0f ? (px / s_zt[p]) / (qx / s_zd[p]) : (px > 0.0f ? INFINITY : 0.0f);
-            s_ok[i] = s_u[i] < fminf(1.0f, ratio);
+    // the test every child of nodes first .. last faces when it is the first one tried
+    auto test_children = [&](int first, int last) {
+        for (int i = tid; i < n_tree; i += NT) {
+            const int p = s_par[i];
+            if (i > 0 && p >= first && p <= last) {
+                const float px = s_px[i] = __expf(s_px[i] - s_mt[p]);
+                const float qx = s_qx[i] = __expf(s_qx[i] - s_md[p]);
+                const float ratio = qx > 0.0f ? (px / s_zt[p]) / (qx / s_zd[p]) : (px > 0.0f ? INFINITY : 0.0f);
+                s_ok[i] = s_u[i] < fminf(1.0f, ratio);
+            }
         }
-    }
+    };
+    test_children(0, n_known - 1);
     __syncthreads();
 
     auto next_sibling = [&](int node) {      // every wave finds it for itself: no barrier
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
     };
 
     int cur = 0, depth = 0, n_rej = 0;
-    int64_t row = 0;                                        // of the current node
+    int64_t row = bt * vocab;                               // of the current node
     float mt = 0.0f, md = 0.0f, ip = 0.0f, iq = 0.0f;       // its rows' normalisers: p = exp(t - mt) * ip, q = exp(d - md) * iq
     // residual target and reduced draft of token t after the first n rejections at the current node
     auto chain = [&](int n, int t, float &P, float &Q) {
@@ -365,23 +369,94 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         }
     };
     // A workgroup with one chunk keeps its residual target and reduced draft in registers from round to round: rp, rq hold
-    // them after the first reg_n rejections at the current node (-1: the chunk has not been read yet).
-    constexpr int PER = STAT_CHUNK / NT / 8;     // groups of 8 tokens a thread owns of a chunk
+    // them after the first reg_n rejections at the current node (RAW: the logits; UNREAD: nothing yet).
+    constexpr int RAW = -1, UNREAD = -2;
     float rp[PER][8], rq[PER][8];
-    int reg_n = -1;
+    int reg_n = UNREAD;
     const bool keeps = n_seg <= n_wg && a.seg_chunks == 1;
-    // A segment's share of a round: the mass of the residual after n rejections (n > 0), or (max, sum of exponentials)
-    // of the target row (n == 0).
-    auto segment = [&](int seg, int n, float &v0, float &v1) {
-        v0 = n ? 0.0f : -INFINITY;
-        v1 = 0.0f;
-        if (n && keeps && seg == wg) {
-            if (reg_n < 0) {
+    auto read_own = [&]() {
 #pragma unroll
-                for (int h = 0; h < PER; h++) {
-                    load8<BF16>(a.tlogits, row, seg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rp[h]);
-                    load8<BF16>(a.dlogits, row, seg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rq[h]);
-                }
+        for (int h = 0; h < PER; h++) {
+            load8<BF16>(a.tlogits, row, wg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rp[h]);
+            load8<BF16>(a.dlogits, row, wg * STAT_CHUNK + (h * NT + tid) * 8, vocab, vec, rq[h]);
+        }
+        reg_n = RAW;
+    };
+    // The waves' values meet in one of two places in turn: whoever writes a place again has passed the barrier behind the reads of it.
+    int red_at = 0;
+    auto block_sum = [&](float v) {
+        float *red = s_red[red_at][0];
+        red_at ^= 1;
+        v = wave_sum(v);
+        if (lane == 0)
+            red[wave] = v;
+        __syncthreads();
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; w++)
+            t += red[w];
+        return t;
+    };
+    // (max, sum of exponentials) of a chunk of a target row, its logits in x, and with `two` of a draft row, joined to those of the chunks
+    // before it: every wave relative to its own maximum, then the waves in order
+    auto add_stats = [&](const float (&x)[PER][8], const float (&y)[PER][8], bool two, float (&val)[MAX_VAL]) {
+        float(&red)[4][NW] = s_red[red_at];
+        red_at ^= 1;
+        auto of_wave = [&](const float (&r)[PER][8], int at) {
+            float mx = -INFINITY, sum = 0.0f;
+#pragma unroll
+            for (int h = 0; h < PER; h++)
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    mx = fmaxf(mx, r[h][j] * inv_temp);
+            mx = wave_max(mx);
+            const float ms = mx == -INFINITY ? 0.0f : mx;
+#pragma unroll
+            for (int h = 0; h < PER; h++)
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    sum += __expf(r[h][j] * inv_temp - ms);       // (0 for the padding)
+            sum = wave_sum(sum);
+            if (lane == 0) {
+                red[at][wave] = mx;
+                red[at + 1][wave] = sum;
+            }
+        };
+        of_wave(x, 0);
+        if (two)
+            of_wave(y, 2);
+        __syncthreads();
+        auto join = [&](int at) {
+            float m = val[at], z;
+#pragma unroll
+            for (int w = 0; w < NW; w++)
+                m = fmaxf(m, red[at][w]);
+            z = val[at + 1] > 0.0f ? val[at + 1] * __expf(val[at] - m) : 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; w++)
+                z += red[at + 1][w] > 0.0f ? red[at + 1][w] * __expf(red[at][w] - m) : 0.0f;
+            val[at] = m;
+            val[at + 1] = z;
+        };
+        join(0);
+        if (two)
+            join(2);
+    };
+    // A segment's share of a round: the mass of the residual after n rejections (n > 0), (max, sum of exponentials) of the target row
+    // (TARGET), or those of the target row and of the draft row (BOTH).
+    constexpr int TARGET = 0, BOTH = -1;
+    auto values_of = [&](int n) { return n > 0 ? 1 : n == TARGET ? 2 : 4; };
+    auto segment = [&](int seg, int n, float (&val)[MAX_VAL]) {
+        val[0] = val[2] = n > 0 ? 0.0f : -INFINITY;
+        val[1] = val[3] = 0.0f;
+        if (n != TARGET && keeps && seg == wg) {
+            if (reg_n == UNREAD)
+                read_own();
+            if (n == BOTH) {
+                add_stats(rp, rq, true, val);
+                return;
+            }
+            if (reg_n == RAW) {
 #pragma unroll
                 for (int h = 0; h < PER; h++)
 #pragma unroll
@@ -411,14 +486,14 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 #pragma unroll
                 for (int j = 0; j < 8; j++)
                     s += residual(rp[h][j], jp, rq[h][j], jq);
-            v0 = block_sum(s, s_redf, tid);
+            val[0] = block_sum(s);
             return;
         }
         for (int c = seg * a.seg_chunks; c < min((seg + 1) * a.seg_chunks, n_chunks); c++) {
             float v[PER][8];
             const int t = c * STAT_CHUNK + tid * 8;
-            float m = -INFINITY, s = 0.0f;
-            if (n) {
+            if (n > 0) {
+                float s = 0.0f;
 #pragma unroll
                 for (int h = 0; h < PER; h++)
                     fetch_residual(n, t + h * NT * 8, v[h]);
@@ -427,83 +502,65 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 #pragma unroll
                     for (int j = 0; j < 8; j++)
                         s += v[h][j];
-                v0 += block_sum(s, s_redf, tid);
+                val[0] += block_sum(s);
             } else {
+                float d[PER][8];
 #pragma unroll
-                for (int h = 0; h < PER; h++)
+                for (int h = 0; h < PER; h++) {
                     load8<BF16>(a.tlogits, row, t + h * NT * 8, vocab, vec, v[h]);
-#pragma unroll
-                for (int h = 0; h < PER; h++)
-#pragma unroll
-                    for (int j = 0; j < 8; j++)
-                        m = fmaxf(m, v[h][j] *= inv_temp);
-                m = fmaxf(block_max(m, s_redf, tid), v0);
-                if (m > -INFINITY) {
-#pragma unroll
-                    for (int h = 0; h < PER; h++)
-#pragma unroll
-                        for (int j = 0; j < 8; j++)
-                            s += __expf(v[h][j] - m);
-                    s = block_sum(s, s_redf, tid);
-                    v1 = v1 * __expf(v0 - m) + s;
-                    v0 = m;
+                    if (n == BOTH)
+                        load8<BF16>(a.dlogits, row, t + h * NT * 8, vocab, vec, d[h]);
                 }
+                add_stats(v, d, n == BOTH, val);
             }
         }
     };
     auto sum_segments = [&](const float *v) {     // every lane of every wave: the same tree over the segments
-        float t = lane < n_seg ? v[lane] : 0.0f;
-        for (int off = 32; off > 0; off >>= 1)
-            t += __shfl_xor(t, off);
-        return t;
+        return wave_sum(lane < n_seg ? v[lane] : 0.0f);
     };
     int round = 0;
     bool alone = n_wg == 1;
     // One round: fills s_part for all segments.  False: this workgroup waited in vain and ends.
     auto exchange = [&](int n) {
         round++;
-        uint64_t *slot = a.slots + (int64_t)b * SLOTS + (round & 1) * 2 * MAX_SEG;
-        for (int seg = alone ? 0 : wg; seg < n_seg; seg += alone ? 1 : n_wg) {
-            float v0, v1;
-            segment(seg, n, v0, v1);
-            if (tid < (n ? 1 : 2)) {
-                const float v = tid ? v1 : v0;
-                s_part[tid][seg] = v;
-                if (!alone)
-                    __hip_atomic_store(slot + tid * MAX_SEG + seg, ((uint64_t)(uint32_t)round << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t *slot = a.slots + (int64_t)b * SLOTS + (round & 1) * MAX_VAL * MAX_SEG;
+        const int n_val = values_of(n);
+        for (bool again = false;; again = true) {           // (again: the segments that others did not sum)
+            for (int seg = alone || again ? 0 : wg; seg < n_seg; seg += alone || again ? 1 : n_wg) {
+                if (again && seg % n_wg == wg)
+                    continue;
+                float val[MAX_VAL];
+                segment(seg, n, val);
+                if (tid < n_val) {
+                    const float v = tid == 0 ? val[0] : tid == 1 ? val[1] : tid == 2 ? val[2] : val[3];
+                    s_part[tid][seg] = v;
+                    if (!alone && !again)
+                        __hip_atomic_store(slot + tid * MAX_SEG + seg, ((uint64_t)(uint32_t)round << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
-        }
-        if (!alone) {
+            if (again)
+                alone = true;
+            if (alone)
+                break;
             bool missing = false;
             const int val = tid / MAX_SEG, seg = tid % MAX_SEG;
-            if (val < (n ? 1 : 2) && seg < n_seg && seg % n_wg != wg) {
+            if (val < n_val && seg < n_seg && seg % n_wg != wg) {
                 uint64_t w = 0;
                 missing = true;
                 for (int spin = 0; spin < a.spin_limit && missing; spin++) {
                     w = __hip_atomic_load(slot + val * MAX_SEG + seg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     missing = (uint32_t)(w >> 32) != (uint32_t)round;
                     if (missing)
-                        __builtin_amdgcn_s_sleep(2);
+                        __builtin_amdgcn_s_sleep(1);
                 }
                 if (!missing)
                     s_part[val][seg] = __uint_as_float((uint32_t)w);
             }
-            if (__syncthreads_or(missing)) {
-                if (wg != 0)
-                    return false;
-                alone = true;
-                for (int sg = 0; sg < n_seg; sg++) {
-                    if (sg % n_wg == wg)
-                        continue;
-                    float v0, v1;
-                    segment(sg, n, v0, v1);
-                    if (tid == 0) {
-                        s_part[0][sg] = v0;
-                        s_part[1][sg] = v1;
-                    }
-                }
-            }
+            if (!__syncthreads_or(missing))
+                break;
+            if (wg != 0)
+                return false;
         }
         __syncthreads();
         return true;
@@ -577,134 +634,162 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
     // The draw when s_mass holds the mass of every segment: the segment with the drawn point is found from those sums,
     // in order, and only that one is read.
     auto draw_by_segments = [&](auto fetch8) {
-        float total = 0.0f;
-        for (int c = 0; c < n_seg; c++)
-            total += s_mass[c];
-        const float target = a.u_bonus[b] * total;
-        int pick = -1, last_mass = 0;
-        float before = 0.0f, before_last = 0.0f, run = 0.0f;
-        for (int c = 0; c < n_seg; c++) {
-            const float mc = s_mass[c];
-            if (mc > 0.0f) {
-                last_mass = c;
-                before_last = run;
-            }
-            if (pick < 0 && run + mc > target) {
-                pick = c;
-                before = run;
-            }
-            run += mc;
+        const float mine = lane < n_seg ? s_mass[lane] : 0.0f;
+        float upto = mine;                      // of the segments up to lane's
+        for (int off = 1; off < 64; off <<= 1) {
+            const float o = __shfl_up(upto, off);
+            if (lane >= off)
+                upto += o;
         }
-        if (pick < 0) {           // rounding left the target at or above the total: the last segment with mass
-            pick = last_mass;
-            before = before_last;
-        }
+        const float prev = __shfl_up(upto, 1), below = lane ? prev : 0.0f;
+        const float target = a.u_bonus[b] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(upto), 63));
+        const uint64_t past = __ballot(mine > 0.0f && upto > target), some = __ballot(mine > 0.0f);
+        // (rounding may leave the target at or above the total: the last segment with mass)
+        const int pick = past ? __builtin_ctzll(past) : some ? 63 - __builtin_clzll(some) : 0;
+        const float before = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(below), pick));
         const int64_t seg_tokens = (int64_t)a.seg_chunks * STAT_CHUNK;
         draw((int)(pick * seg_tokens), (int)min((pick + 1) * seg_tokens, (int64_t)vocab), before, target, fetch8);
     };
 
-    for (;;) {
-        // ---- descend through first children whose (precomputed) test passes
-        int first = depth < max_depth ? s_first[cur] : NONE;
-        while (first != NONE && s_ok[first]) {
-            cur = first;
-            depth++;
-            if (wg == 0 && tid == 0)
-                path[depth] = cur;
-            first = depth < max_depth ? s_first[cur] : NONE;
+    bool have_mass = false;                    // s_mass holds the masses of the segments of the current target
+    int first = NONE, child = NONE;
+    float Zp = 1.0f, Zq = 1.0f, qx = 0.0f;     // masses of the current P and Q; the rejected child's draft probability
+    // `child` is rejected: the target becomes the positive part of (target - draft), its token leaves the draft
+    auto reject = [&]() {
+        const int x = s_tok[child];
+        if (tid == 0) {
+            s_ip[n_rej] = 1.0f / Zp;
+            s_iq[n_rej] = Zq > 0.0f ? 1.0f / Zq : 0.0f;
+            s_x[n_rej] = x;
+            s_take[n_rej] = 1;
         }
-        row = (bt + cur) * vocab;
-        n_rej = 0;
-        reg_n = -1;
-        const bool inner = s_first[cur] != NONE;            // (a node at the depth limit may have children)
-        if (inner) {
-            mt = s_mt[cur];
-            md = s_md[cur];
-            ip = 1.0f / s_zt[cur];
-            iq = s_zd[cur] > 0.0f ? 1.0f / s_zd[cur] : 0.0f;
-        } else {
-            if (!exchange(0))
-                return;
-            mt = -INFINITY;
-            for (int s = 0; s < n_seg; s++)
-                mt = fmaxf(mt, s_part[0][s]);
-            ip = 1.0f;
-            if (tid < n_seg)
-                s_mass[tid] = s_part[1][tid] > 0.0f ? s_part[1][tid] * __expf(s_part[0][tid] - mt) : 0.0f;
-        }
-        bool have_mass = !inner;
-        int child = first, accepted = -1;
-        float Zp = 1.0f, Zq = 1.0f;                          // masses of the current P and Q
-        while (child != NONE) {
-            // ---- `child` was rejected: the target becomes the positive part of (target - draft), its token leaves the draft
-            const int x = s_tok[child];
-            if (tid == 0) {
-                s_ip[n_rej] = 1.0f / Zp;
-                s_iq[n_rej] = Zq > 0.0f ? 1.0f / Zq : 0.0f;
-                s_x[n_rej] = x;
-                s_take[n_rej] = 1;
-            }
-            __syncthreads();
-            float qx = s_qx[child] * iq;
-            for (int j = 0; j < n_rej; j++)
-                qx = s_x[j] == x ? 0.0f : qx;
-            if (!exchange(n_rej + 1))
-                return;
-            const float Z = sum_segments(s_part[0]);
-            if (Z > 0.0f) {
-                Zp = Z;
-                have_mass = true;
-                if (tid < n_seg)
-                    s_mass[tid] = s_part[0][tid];
-            } else if (tid == 0) {
-                s_take[n_rej] = 0;                           // target == draft: the residual is empty and the target stays as it is
-            }
-            Zq = fmaxf(Zq - qx, 0.0f);
-            n_rej++;
-            __syncthreads();
-            child = next_sibling(child);
-            if (child == NONE)
-                break;
-            const int x2 = s_tok[child];
-            float P = s_px[child] * ip, Q = s_qx[child] * iq;
-            chain(n_rej, x2, P, Q);
-            const float ratio = Q > 0.0f ? (P / Zp) / (Q / Zq) : (P > 0.0f ? INFINITY : 0.0f);
-            if (s_u[child] < fminf(1.0f, ratio)) {
-                accepted = child;
-                break;
-            }
-        }
-        if (accepted < 0) {
-            // ---- no child, or every child rejected: draw from the current target
-            if (wg != 0)
-                return;
-            if (!have_mass && tid < n_seg) {                 // the untouched target
-                float s = 0.0f;
-                for (int c = tid * a.seg_chunks; c < min((tid + 1) * a.seg_chunks, n_chunks); c++) {
-                    const float sc = a.stat_s[(bt + cur) * n_chunks + c];
-                    s += sc > 0.0f ? sc * __expf(a.stat_m[(bt + cur) * n_chunks + c] - mt) : 0.0f;
-                }
-                s_mass[tid] = s * ip;
-            }
-            __syncthreads();
-            if (n_rej)
-                draw_by_segments([&](int t, float v[8]) { fetch_residual(n_rej, t, v); });
-            else
-                draw_by_segments([&](int t, float v[8]) {
-                    load8<BF16>(a.tlogits, row, t, vocab, vec, v);
-#pragma unroll
-                    for (int j = 0; j < 8; j++)
-                        v[j] = token_mass(v[j], inv_temp, mt, ip);
-                });
-            break;
-        }
-        cur = accepted;
+        __syncthreads();
+        qx = s_qx[child] * iq;
+        for (int j = 0; j < n_rej; j++)
+            qx = s_x[j] == x ? 0.0f : qx;
+    };
+    auto visit = [&](int node) {
+        cur = node;
         depth++;
         if (wg == 0 && tid == 0)
             path[depth] = cur;
-        __syncthreads();   // the lists of this node are rewritten at a deeper one: finish reading them first
+        row = (bt + cur) * vocab;
+        have_mass = false;
+        reg_n = UNREAD;
+    };
+    // `ask` is what the next round is about: BOTH, TARGET, the number of rejections with the last one, or nothing before the walk has gone
+    // down from the current node (DESCEND).  (All workgroups of the sequence go the same way.)
+    constexpr int DESCEND = -2;
+    for (int ask = DESCEND;;) {
+        if (ask == DESCEND) {
+            // ---- through first children whose (precomputed) test passes
+            first = depth < max_depth ? s_first[cur] : NONE;
+            bool learn = false;
+            while (first != NONE && s_ok[first] && !learn) {
+                visit(first);
+                first = depth < max_depth ? s_first[cur] : NONE;
+                learn = a.lazy && s_first[cur] != NONE;
+            }
+            n_rej = 0;
+            if (learn) {
+                ask = BOTH;
+            } else if (s_first[cur] != NONE) {              // (a node at the depth limit may have children)
+                mt = s_mt[cur];
+                md = s_md[cur];
+                ip = 1.0f / s_zt[cur];
+                iq = s_zd[cur] > 0.0f ? 1.0f / s_zd[cur] : 0.0f;
+                Zp = Zq = 1.0f;
+                child = first;
+                if (child == NONE)
+                    break;
+                reject();
+                ask = 1;
+            } else {
+                ask = TARGET;
+            }
+        }
+        if (!exchange(ask))
+            return;
+        if (ask == BOTH) {
+            // ---- the statistics of the current node's rows, and with them the tests of its children; the masses of its target's segments
+            float m[2], z[2];
+#pragma unroll
+            for (int w = 0; w < 2; w++) {      // lane s: segment s; the same tree over the segments in every wave
+                const float ms = lane < n_seg ? s_part[2 * w][lane] : -INFINITY, zs = lane < n_seg ? s_part[2 * w + 1][lane] : 0.0f;
+                m[w] = wave_max(ms);
+                z[w] = wave_sum(zs > 0.0f ? zs * __expf(ms - m[w]) : 0.0f);
+            }
+            if (tid < n_seg)
+                s_mass[tid] = s_part[1][tid] > 0.0f ? s_part[1][tid] * __expf(s_part[0][tid] - m[0]) * (1.0f / z[0]) : 0.0f;
+            if (tid == 0) {
+                s_mt[cur] = m[0]; s_zt[cur] = z[0]; s_md[cur] = m[1]; s_zd[cur] = z[1];
+            }
+            have_mass = true;
+            __syncthreads();
+            test_children(cur, cur);
+            __syncthreads();
+            ask = DESCEND;
+            continue;
+        }
+        if (ask == TARGET) {
+            mt = wave_max(lane < n_seg ? s_part[0][lane] : -INFINITY);
+            ip = 1.0f;
+            if (tid < n_seg)
+                s_mass[tid] = s_part[1][tid] > 0.0f ? s_part[1][tid] * __expf(s_part[0][tid] - mt) : 0.0f;
+            have_mass = true;
+            break;
+        }
+        // ---- `child` is rejected: the mass of what is left of the target
+        const float Z = sum_segments(s_part[0]);
+        if (Z > 0.0f) {
+            Zp = Z;
+            have_mass = true;
+            if (tid < n_seg)
+                s_mass[tid] = s_part[0][tid];
+        } else if (tid == 0) {
+            s_take[n_rej] = 0;                               // target == draft: the residual is empty and the target stays as it is
+        }
+        Zq = fmaxf(Zq - qx, 0.0f);
+        n_rej++;
+        __syncthreads();
+        child = next_sibling(child);
+        if (child == NONE)
+            break;
+        float P = s_px[child] * ip, Q = s_qx[child] * iq;
+        chain(n_rej, s_tok[child], P, Q);
+        const float ratio = Q > 0.0f ? (P / Zp) / (Q / Zq) : (P > 0.0f ? INFINITY : 0.0f);
+        if (s_u[child] < fminf(1.0f, ratio)) {
+            visit(child);
+            __syncthreads();   // the lists of the node before are rewritten: finish reading them first
+            ask = a.lazy && s_first[cur] != NONE ? BOTH : DESCEND;
+            n_rej = 0;
+        } else {
+            reject();
+            ask = n_rej + 1;
+        }
     }
-    if (wg == 0 && tid == 0)
+    // ---- no child, or every child rejected: draw from the current target
+    if (wg != 0)
+        return;
+    if (!have_mass && tid < n_seg) {                         // the untouched target
+        float s = 0.0f;
+        for (int c = tid * a.seg_chunks; c < min((tid + 1) * a.seg_chunks, n_chunks); c++) {
+            const float sc = a.stat_s[(bt + cur) * n_chunks + c];
+            s += sc > 0.0f ? sc * __expf(a.stat_m[(bt + cur) * n_chunks + c] - mt) : 0.0f;
+        }
+        s_mass[tid] = s * ip;
+    }
+    __syncthreads();
+    if (n_rej)
+        draw_by_segments([&](int t, float v[8]) { fetch_residual(n_rej, t, v); });
+    else
+        draw_by_segments([&](int t, float v[8]) {
+            load8<BF16>(a.tlogits, row, t, vocab, vec, v);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                v[j] = token_mass(v[j], inv_temp, mt, ip);
+        });
+    if (tid == 0)
         a.accept_len[b] = depth;
 }
 
@@ -718,7 +803,7 @@ size_t dream_spec_accept_workspace(int32_t batch, int32_t n_tree, int32_t vocab)
         return DREAM_WORKSPACE_MIN_BYTES;
     // The size is part of the boundary: programs hold it as a number.  Of it the calls use the statistics' two arrays and SLOTS words per
     // sequence, which sit where an earlier form of the walk kept three vocabulary rows; the rest is not touched.
-    const size_t stats = align_up((size_t)2 * batch * n_tree * ceil_div(vocab, STAT_CHUNK) * sizeof(float), 256);
+    const size_t stats = align_up((size_t)2 * batch * n_tree * ceil_div(vocab, 8192) * sizeof(float), 256);
     return DREAM_WORKSPACE_MIN_BYTES + align_up((size_t)batch * 3 * vocab * sizeof(float), 256) + 3 * stats + align_up((size_t)batch * n_tree * 4 * sizeof(float), 256);
 }
 
@@ -743,37 +828,55 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
     const size_t need = dream_spec_accept_workspace(batch, n_tree, vocab);
     if (!workspace || workspace_bytes < need)
         return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
-    const int n_chunks = ceil_div(vocab, STAT_CHUNK);
+    int per = 1;
+    while (per < 4 && ceil_div(vocab, NT * 8 * per) > std::min(MAX_SEG, std::max(1, 256 / batch)))
+        per *= 2;
+    const int n_chunks = ceil_div(vocab, NT * 8 * per);
     const size_t stats = align_up((size_t)2 * batch * n_tree * n_chunks * sizeof(float), 256);
     // Workgroups per sequence: one per segment while all of them together stay within one per CU.
     const int seg_chunks = ceil_div(n_chunks, MAX_SEG), n_seg = ceil_div(n_chunks, seg_chunks);
     const int n_wg = std::max(1, std::min(n_seg, 256 / batch));
-    // the slots exist with more than one segment only, so they fit where a row of floats per sequence does
+    // the slots exist with more than one segment only, so they fit where a row of floats per sequence does, and the statistics in the other two
     // (aligned here, in the room the first DREAM_WORKSPACE_MIN_BYTES leave: a slot is one 64-bit word to readers and writers only where it is aligned)
     char *wsb = reinterpret_cast<char *>(align_up(reinterpret_cast<uintptr_t>(workspace), DREAM_WORKSPACE_MIN_BYTES));
     uint64_t *slots = n_wg > 1 ? reinterpret_cast<uint64_t *>(wsb) : nullptr;
-    static_assert(SLOTS * sizeof(uint64_t) <= 3 * sizeof(float) * STAT_CHUNK, "the slots of a sequence fit its part of the workspace");
-    float *stat_m = reinterpret_cast<float *>(wsb + align_up((size_t)batch * 3 * vocab * sizeof(float), 256));
-    float *stat_s = reinterpret_cast<float *>(reinterpret_cast<char *>(stat_m) + stats);
+    const size_t slot_bytes = n_wg > 1 ? (size_t)batch * SLOTS * sizeof(uint64_t) : 0;
+    float *stat_m = reinterpret_cast<float *>(wsb + slot_bytes);
+    float *stat_s = reinterpret_cast<float *>(wsb + slot_bytes + stats);
+    if (align_up(reinterpret_cast<uintptr_t>(workspace), DREAM_WORKSPACE_MIN_BYTES) - reinterpret_cast<uintptr_t>(workspace) + slot_bytes + 2 * stats > need)
+        return fail(DREAM_ERR_WORKSPACE, "%s: the statistics do not fit the workspace", who);
     const int esz = logits_dtype == DREAM_BF16 ? 2 : 4;
     const bool vec = vocab % 8 == 0 &&
                      ((reinterpret_cast<uintptr_t>(target_logits) | reinterpret_cast<uintptr_t>(draft_logits)) & 15) == 0 &&
                      ((size_t)vocab * esz) % 16 == 0;
     const float inv_temp = 1.0f / temperature;
     hipStream_t st = as_stream(stream);
-    const dim3 sgrid(n_chunks, batch * n_tree, 2);
-    const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, token, parent, u_accept, u_bonus, max_depth,
+    // The statistics of all nodes beforehand cost a read of about half of all rows, those of the visited ones an exchange each.  us, all / visited: 24 MB of
+    // logits 24.7 / 38.6, 31 MB 37.8 / 38.8, 63 MB equal within 1 % (37.5 and 34.3); beyond that the figures at the head of this file.
+    const bool lazy = (int64_t)2 * batch * n_tree * vocab * esz >= 60000000;
+    const int n_nodes = lazy ? 1 : n_tree;
+    const dim3 sgrid(n_chunks, batch * n_nodes, 2);
+    const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, lazy, token, parent, u_accept, u_bonus, max_depth,
                          inv_temp, accept_spin_limit(), stat_m, stat_s, slots, accept_len, accept_path, bonus_token};
-    auto launch_all = [&](auto bf16) {
+    auto launch_all = [&](auto bf16, auto groups) {
         constexpr bool BF = decltype(bf16)::value;
-        hipLaunchKernelGGL(softmax_stats_kernel<BF>, sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, vocab, n_chunks, vec,
+        constexpr int PER = decltype(groups)::value;
+        hipLaunchKernelGGL((softmax_stats_kernel<BF, PER>), sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, n_nodes, vocab, n_chunks, vec,
                            parent, inv_temp, stat_m, stat_s, slots);
-        hipLaunchKernelGGL(spec_walk_kernel<BF>, dim3(n_wg, batch), dim3(NT), 0, st, wa);
+        hipLaunchKernelGGL((spec_walk_kernel<BF, PER>), dim3(n_wg, batch), dim3(NT), 0, st, wa);
+    };
+    auto with_groups = [&](auto bf16) {
+        if (per == 1)
+            launch_all(bf16, std::integral_constant<int, 1>{});
+        else if (per == 2)
+            launch_all(bf16, std::integral_constant<int, 2>{});
+        else
+            launch_all(bf16, std::integral_constant<int, 4>{});
     };
     if (logits_dtype == DREAM_BF16)
-        launch_all(std::true_type{});
+        with_groups(std::true_type{});
     else
-        launch_all(std::false_type{});
+        with_groups(std::false_type{});
     return check_launch("spec_accept kernels");
 }
 

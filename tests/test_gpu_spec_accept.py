@@ -194,6 +194,19 @@ def test_workgroups_of_a_sequence(gu, V, polls):
         dream.dream_set_accept_spin(0)
 
 
+@pytest.mark.parametrize("B,T,V", [(40, 6, 40000), (64, 4, 60000), (100, 3, 20000), (20, 5, 262145), (300, 3, 9001)])
+@pytest.mark.parametrize("polls", [0, -1])
+def test_shares_of_a_workgroup(gu, B, T, V, polls):
+    """Two and four times as many logits in a workgroup's registers, more than they hold, one workgroup per sequence; with the statistics of all
+    nodes formed beforehand (below 60 MB of logits) and by the walk."""
+    import paper_2505_19201_amd as dream
+    dream.dream_set_accept_spin(polls)
+    try:
+        _case(gu, B, T, 3, V, "f32", 1970 + V, noise=1.0, min_clear=0.0)
+    finally:
+        dream.dream_set_accept_spin(0)
+
+
 @pytest.mark.parametrize("V", [1000, 24577, 65536])
 @pytest.mark.parametrize("offset", [1, 4, 72, 255])
 def test_workspace_at_any_address(gu, V, offset):
