@@ -89,6 +89,19 @@ def test_heavily_tied_logits(gu, levels):
     assert np.abs(sc - want_sc).max() <= SCORE_TOL
 
 
+@pytest.mark.parametrize("V,k", [(131072, 16), (131000, 10), (32000, 10), (32000, 3), (600000, 6), (524288, 1), (8200, 16)])
+@pytest.mark.parametrize("where", ["anywhere", "one chunk", "all but one chunk"])
+def test_best_tokens_of_a_row_wherever_they_lie(gu, V, k, where):
+    """Merging the chunks of a row: many chunks and few, more than a wave has lanes, and chunks whose candidates all stay (a low chunk lowers
+    the bound of the k-th) or all go.  Equal values across chunks resolve toward the lower token."""
+    g = di.rng(700 + V + k, 402)
+    logits = (np.round(g.standard_normal((2, 2, V)) * 64.0) / 64.0).astype(np.float32)
+    part = (np.arange(V) // 8192) == min(1, (V - 1) // 8192)
+    if where != "anywhere":
+        logits[..., part if where == "one chunk" else ~part] += 20.0
+    _check_level(gu, logits, "f32", np.array([[-1.0, -1.5], [0.0, -3.0]], dtype=np.float32), k)
+
+
 def test_finalize_bit_exact_including_ties(gu):
     g = di.rng(77, 400)
     for N, budget in [(85, 32), (85, 100), (2, 1), (1, 5), (1024, 59), (601, 600), (333, 0)]:
