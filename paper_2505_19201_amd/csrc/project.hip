@@ -171,40 +171,27 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
     }
 }
 
-// 16 bytes per lane from `src` straight to LDS: lane i's land at lds + 16 * i.  Inline assembly, because the compiler
-// makes every LDS read wait for all such loads in flight, also for those of later steps.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved; naming it as clobbered is right all the same
-__device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 // More than 16 feature rows.  Every workgroup reads all of them (from L2) beside its own weight rows, so what bounds the
-// call is feature rows + weight rows per workgroup times workgroups per CU: a workgroup owns NT tiles of 16 output
+// call is feature rows + weight rows per workgroup times workgroups per CU (a CU pulls 60 to 75 GB/s): a workgroup owns NT tiles of 16 output
 // features and MT tiles of 16 rows (up to 128 rows per pass), and the launch picks NT for the fewest bytes through the
-// busiest CU.  The hidden dimension is walked in steps of 128 elements: 256-byte pieces of the rows go from memory
-// straight to LDS, NS - 1 steps in flight, one barrier per step; wave w multiplies row tile w % MP with all NT weight
-// tiles over its share of the step's 128 elements.  (The same kernel with the operands loaded from memory in MFMA layout,
-// 16 rows x 64 bytes per instruction, pulled 17 bytes per nanosecond and CU whatever was in flight: 71 us at LLaVA, 80 rows.)
-// Measured per call of three maps (Q, K, V), before (16 features and up to 64 rows per workgroup) and here: 80 rows LLaVA 116 -> 40 us,
-// Pixtral 110 -> 23, Gemma3 83 -> 20, SmolVLM 42 -> 11.6; 20 rows LLaVA 36 -> 27, Pixtral 34 -> 14.  At 10 rows project_kernel is 0.5-2 us faster.
+// busiest CU.  The hidden dimension is dealt to the 8 waves in steps of 64 elements, 1024 contiguous bytes of every row for the eight;
+// each wave passes its 128-byte pieces through LDS that only it uses, the next step's loads in flight meanwhile, and keeps all MT x NT
+// tiles: no barrier before the partial tiles meet, and every byte is read from LDS once.  (One wave per row tile, stages shared by the
+// workgroup and a barrier per step read the weights once per row tile and left 5 of 8 waves multiplying at 80 rows.  Two steps ahead
+// were slower at short hidden dimensions and no faster at long ones.)
+// Measured per call of three maps (Q, K, V), shared stages / here: 80 rows SmolVLM 11.4 / 10.3 us, LLaVA 40.9 / 40.0, Pixtral 27.1 / 27.3, 40 rows
+// 9.1 / 7.2, 30.4 / 28.4, 21.0 / 20.3 with the weights in HBM; as much of them as the memory-side cache kept from the level before, 80 rows LLaVA
+// 34.7 / 28.1, Pixtral 21.9 / 19.1, 20 rows LLaVA 25.3 / 18.0.  Whole drafts of 6 levels are 8 to 19 % faster, the expansion's share included.
+// At 10 rows project_kernel and this one are equal within 5 % but for LLaVA (warm 16.5 against 18.0).
 constexpr int RW = 8;                                // waves per workgroup
-constexpr int STEP = 128, STEP_BYTES = STEP * 2;     // elements, bytes of a row per step
+constexpr int STEP = 64, STEP_BYTES = STEP * 2;      // elements, bytes of a row per step
+constexpr int TILE_BYTES = 16 * STEP_BYTES;
 
 template <int MT, int NT>
 struct RowsGeom {
-    static constexpr int MP = MT <= 2 ? 2 : MT <= 4 ? 4 : 8;                      // row-tile slots (at least 17 rows, so at least 2 tiles)
-    static constexpr int KS = RW / MP;                                            // waves that share a row tile's elements
-    static constexpr int LOADS = 4 * (MT + NT);                                   // load instructions per step (1024 bytes: 4 row pieces)
-    static constexpr int NLD = (LOADS + RW - 1) / RW;
-    static constexpr int STAGE = LOADS * 1024;
-    static constexpr int FIT = 156 * 1024 / STAGE;
-    static constexpr int NS = FIT > 6 ? 6 : FIT;
-    static constexpr size_t LDS_BYTES = (size_t)NS * STAGE;
-    static_assert(NS >= 3 && (NS - 2) * NLD < 64, "stages");
-    static_assert((size_t)RW * NT * 1024 <= LDS_BYTES, "the partial tiles reuse the stages");
+    static constexpr int STAGE = (MT + NT) * TILE_BYTES;                          // of a wave
+    static constexpr size_t LDS_BYTES = RW * (STAGE > MT * NT * 1024 ? STAGE : MT * NT * 1024);   // (the partial tiles reuse the stages)
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
 template <int MT, int NT>
@@ -213,90 +200,105 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
     using G = RowsGeom<MT, NT>;
     const ProjView a = select_job(args, blockIdx.x);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     const int n_tiles = a.n_heads * a.head_dim / 16, nt0 = ((int)blockIdx.x - a.first) * NT;
-    const int K = a.hidden, steps = K / STEP;
-    const int mt = wave % G::MP, kg = wave / G::MP;
+    const int K = a.hidden, n_steps = (K / STEP - wave + RW - 1) / RW;   // this wave's: steps wave, wave + RW, ...
+    unsigned char *stage = smem + wave * G::STAGE;
     // The workgroups of an XCD start at different steps: the rows are a power of two or nearly so apart, so one step's pieces
-    // of all rows sit in few L2 channels, and everybody would ask the same ones at the same time (LLaVA, 20 rows: 32 us without).
-    const int first = ((int)blockIdx.x >> 3) % steps;
+    // of all rows sit in few L2 channels, and everybody would ask the same ones at the same time (LLaVA, 20 rows: 29 us without, 18 with).
+    const int first = n_steps > 0 ? ((int)blockIdx.x >> 3) % n_steps : 0;
+    const int lrow = lane >> 3, lchunk = lane & 7;           // a load instruction: 8 rows x 128 bytes
     for (int m0 = 0; m0 < a.m_total; m0 += 16 * MT) {
-        // load instruction `at`: weight rows first, then feature rows, 4 rows each; 16-byte chunk p of LDS row r holds
-        // chunk p ^ (r & 15) of the row, so that the 16 rows of a fragment read sit in different banks.  Rows past the last
-        // one repeat it (never stored); the instructions past the last repeat an earlier one of the same wave.
-        const unsigned char *src[G::NLD];
-        uint32_t dst[G::NLD];
+        const uint16_t *wsrc[NT], *xsrc[MT * 2];
 #pragma unroll
-        for (int j = 0; j < G::NLD; j++) {
-            const int at = wave + j * RW < G::LOADS ? wave + j * RW : wave + (j - 1) * RW;
-            const int row = at * 4 + lane / 16, chunk = (lane & 15) ^ (row & 15);
-            const uint16_t *base = row < NT * 16 ? a.w + (int64_t)min(nt0 * 16 + row, n_tiles * 16 - 1) * K
-                                                 : a.x + (int64_t)min(m0 + row - NT * 16, a.m_total - 1) * K;
-            src[j] = reinterpret_cast<const unsigned char *>(base) + chunk * 16;
-            dst[j] = lds0 + at * 1024;
-        }
+        for (int nt = 0; nt < NT; nt++)                       // (tiles past the last repeat it, never stored)
+            wsrc[nt] = a.w + ((int64_t)min(nt0 + nt, n_tiles - 1) * 16 + lrow) * K + wave * STEP + lchunk * 8;
+#pragma unroll
+        for (int j = 0; j < MT * 2; j++)
+            xsrc[j] = a.x + (int64_t)min(m0 + j * 8 + lrow, a.m_total - 1) * K + wave * STEP + lchunk * 8;
+        const int xj = min((a.m_total - m0 + 7) / 8, MT * 2);
+        u32x4 wr[NT * 2], xr[MT * 2];
         auto issue = [&](int s) {
-            const int at = min(s, steps - 1) + first;             // past the end: a load nobody reads keeps the count constant
-            const int off = (at < steps ? at : at - steps) * STEP_BYTES;
-            const uint32_t stage = s % G::NS * G::STAGE;
+            const int at = s + first;
+            const int col = (at < n_steps ? at : at - n_steps) * (RW * STEP);
 #pragma unroll
-            for (int j = 0; j < G::NLD; j++)
-                load_to_lds(src[j] + off, dst[j] + stage);
-        };
-        f32x4 acc[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-            acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();                                          // (an earlier pass has read its partial tiles)
-#pragma unroll
-        for (int s = 0; s < G::NS - 1; s++)
-            issue(s);
-        for (int s = 0; s < steps; s++) {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step s has landed
-            __syncthreads();                                      // everybody's has, and step s - 1 is no longer read
-            issue(s + G::NS - 1);
-            if (mt < MT) {
-                const unsigned char *stage = smem + s % G::NS * G::STAGE;
-#pragma unroll
-                for (int i = 0; i < 4 / G::KS; i++) {
-                    const int pos = (((kg * (4 / G::KS) + i) * 4 + g) ^ c) * 16;
-                    const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(stage + ((NT + mt) * 16 + c) * STEP_BYTES + pos);
-#pragma unroll
-                    for (int nt = 0; nt < NT; nt++) {
-                        const bf16x8 wf = *reinterpret_cast<const bf16x8 *>(stage + (nt * 16 + c) * STEP_BYTES + pos);
-                        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, acc[nt], 0, 0, 0);
-                    }
-                }
+            for (int nt = 0; nt < NT; nt++) {
+                wr[nt * 2] = *reinterpret_cast<const u32x4 *>(wsrc[nt] + col);
+                wr[nt * 2 + 1] = *reinterpret_cast<const u32x4 *>(wsrc[nt] + (int64_t)8 * K + col);
             }
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // nothing lands in the stages any more
-        __syncthreads();
-        if (G::KS > 1) {                                          // sum the partial tiles of a row tile in wave order
-            f32x4 *part = reinterpret_cast<f32x4 *>(smem);
-            if (mt < MT && kg > 0)
 #pragma unroll
-                for (int nt = 0; nt < NT; nt++)
-                    part[(wave * NT + nt) * 64 + lane] = acc[nt];
-            __syncthreads();
-            if (mt < MT && kg == 0)
+            for (int j = 0; j < MT * 2; j++)
+                if (j < MT * 2 - 2 || j < xj)                 // all but the last tile are full
+                    xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
+        };
+        f32x4 acc[MT][NT];
 #pragma unroll
-                for (int k = 1; k < G::KS; k++)
-#pragma unroll
-                    for (int nt = 0; nt < NT; nt++)
-                        acc[nt] += part[((k * G::MP + mt) * NT + nt) * 64 + lane];
-        }
-        if (mt < MT && kg == 0)
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
             for (int nt = 0; nt < NT; nt++)
-                if (nt0 + nt < n_tiles)
-                    store_row_piece(a, m0 + mt * 16 + c, (nt0 + nt) * 16, g, acc[nt]);
+                acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // chunk p of row r of a tile lies at p ^ (r & 7): the 16 rows of a fragment read sit in different banks
+        const int put = lrow * STEP_BYTES + ((lchunk ^ lrow) * 16);
+        auto step = [&](int s, bool more) {
+#pragma unroll
+            for (int j = 0; j < NT * 2; j++)
+                *reinterpret_cast<u32x4 *>(stage + j * 1024 + put) = wr[j];
+#pragma unroll
+            for (int j = 0; j < MT * 2; j++)
+                if (j < MT * 2 - 2 || j < xj)
+                    *reinterpret_cast<u32x4 *>(stage + (NT * 2 + j) * 1024 + put) = xr[j];
+            if (more)
+                issue(s + 1);
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < STEP / 32; i++) {
+                const int pos = c * STEP_BYTES + (((i * 4 + g) ^ (c & 7)) * 16);
+                bf16x8 wf[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++)
+                    wf[nt] = *reinterpret_cast<const bf16x8 *>(stage + nt * TILE_BYTES + pos);
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) {
+                    const bf16x8 xf = *reinterpret_cast<const bf16x8 *>(stage + (NT + mt) * TILE_BYTES + pos);
+#pragma unroll
+                    for (int nt = 0; nt < NT; nt++)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nt], xf, acc[mt][nt], 0, 0, 0);
+                }
+            }
+            wave_lds_fence();
+        };
+        if (n_steps > 0) {                                    // (a wave of a narrow map may have none)
+            issue(0);
+            for (int s = 0; s + 1 < n_steps; s++)
+                step(s, true);
+            step(n_steps - 1, false);
+        }
+        // the waves' partial tiles, summed in wave order
+        __syncthreads();
+        f32x4 *part = reinterpret_cast<f32x4 *>(smem);
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++)
+                part[((mt * NT + nt) * RW + wave) * 64 + lane] = acc[mt][nt];
+        __syncthreads();
+        for (int t = wave; t < MT * NT; t += RW) {
+            f32x4 sum = part[t * RW * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < RW; w++)
+                sum += part[(t * RW + w) * 64 + lane];
+            const int mt = t / NT, nt = t - mt * NT;
+            if (nt0 + nt < n_tiles)
+                store_row_piece(a, m0 + mt * 16 + c, (nt0 + nt) * 16, g, sum);
+        }
+        __syncthreads();
     }
 }
 
 constexpr int MAX_MT = 8, MAX_NT = 3;
+constexpr int max_nt(int mt) { return mt < 7 ? 3 : 2; }   // (what LDS holds)
 
 template <int MT, int NT>
 int ensure_rows_lds(const char *who)
@@ -319,7 +321,7 @@ struct RowsVariant {
     int (*launch)(unsigned, hipStream_t, const ProjArgs &);
     int (*ensure)(const char *);
 };
-#define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, 3>, &ensure_rows_lds<MT, 3>}}
+#define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, max_nt(MT)>, &ensure_rows_lds<MT, max_nt(MT)>}}
 const RowsVariant ROWS[MAX_MT - 1][MAX_NT] = {ROWS_VARIANTS(2), ROWS_VARIANTS(3), ROWS_VARIANTS(4), ROWS_VARIANTS(5),
                                               ROWS_VARIANTS(6), ROWS_VARIANTS(7), ROWS_VARIANTS(8)};
 #undef ROWS_VARIANTS
@@ -383,10 +385,12 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         hipLaunchKernelGGL(project_kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, a);
         return check_launch("project_kernel");
     }
+    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size (2 to 8 tiles: there are at least 17 rows)
+    const int m_tiles = ceil_div(a.m_total, 16), mt = ceil_div(m_tiles, ceil_div(m_tiles, MAX_MT));
     // feature tiles per workgroup: the fewest bytes through the busiest CU
     int nt = 1;
     int64_t best = 0;
-    for (int t = 1; t <= MAX_NT; t++) {
+    for (int t = 1; t <= max_nt(mt); t++) {
         int64_t wgs = 0;
         for (int j = 0; j < n_jobs; j++)
             wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, t);
@@ -401,9 +405,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
         a.job[j].tile_end = wgs;
     }
-    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size (2 to 8 tiles: there are at least 17 rows)
-    const int m_tiles = ceil_div(a.m_total, 16);
-    return ROWS[ceil_div(m_tiles, ceil_div(m_tiles, MAX_MT)) - 2][nt - 1].launch(wgs, st, a);
+    return ROWS[mt - 2][nt - 1].launch(wgs, st, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,

@@ -105,6 +105,15 @@ def test_rows_outside_the_cache_are_dropped(gu):
         _close(di.bf16_bits_to_f32(got[0][:, 16 + r].view(np.uint16)).astype(np.float64), want[0, r])
 
 
+@pytest.mark.parametrize("R", [17, 40, 56, 65, 96, 97, 128, 129, 260])
+@pytest.mark.parametrize("hidden,tiles", [(256, 300), (768, 700), (1280, 64)])
+def test_tiles_of_a_workgroup(gu, R, hidden, tiles):
+    """Every number of row tiles with one, two and three feature tiles (two at most beside seven and eight row tiles), waves with no, one and
+    several steps of the hidden dimension, a last workgroup with fewer feature tiles and a last pass with fewer rows."""
+    x, w = _inputs(1, R, hidden, tiles, 16, 140 + R)
+    _close(gu.run_project(x, w, tiles, 16), oracle.project(x, w, "bf16", tiles, 16))
+
+
 @pytest.mark.parametrize("B,R,hidden,H,D", [(1, 17, 512, 5, 16), (1, 32, 256, 5, 16), (3, 11, 768, 1, 48), (1, 65, 256, 3, 32), (7, 14, 512, 3, 16),
                                             (1, 113, 256, 4, 16), (1, 128, 256, 4, 16), (1, 129, 256, 4, 16), (1, 20, 256, 770, 16)])
 def test_row_and_feature_tile_edges(gu, B, R, hidden, H, D):
