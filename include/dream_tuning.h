@@ -32,7 +32,8 @@ void dream_set_accept_spin(int32_t polls);
 
 /* Host-only: the names of all bf16 attention kernel variants the launch plan can choose, separated by ';', in the
  * spelling dream_attn_plan_describe uses ("attn_wave_kernel<128,8,2,1>": head_dim, waves, column slices, query tiles
- * per workgroup; "attn_pair_kernel<128,1,2>": head_dim, column slices, query tiles of each of two slots; "attn_bf16_kernel<128,1,1,2>": head_dim, query tiles per wave, key tiles per step, steps in flight;
+ * per workgroup; "attn_pair_kernel<128,1,2>", "attn_quad_kernel<128,1,2>": head_dim, column slices, query tiles of each of two, of
+ * four slots; "attn_bf16_kernel<128,1,1,2>": head_dim, query tiles per wave, key tiles per step, steps in flight;
  * a fifth argument 8 marks the forms with 8 waves per workgroup, an eighth the number of key groups).
  * The tests use it to make sure every variant has a parity case.  0, or -1 if buf is too small. */
 int dream_attn_variants(char *buf, size_t buf_bytes);

@@ -18,7 +18,7 @@
 // score exceeds it by 8 octaves, so accumulators are rescaled a handful of times per call.  Where a workgroup is the
 // only reader of its K/V rows the loads carry the nontemporal hint; output rows leave as whole lines with it.
 //
-// bf16, few streams (attn_wave_kernel, attn_pair_kernel).  A CU pulls at most about 65 GB/s through its L1, so a short stream is
+// bf16, few streams (attn_wave_kernel, attn_pair_kernel, attn_quad_kernel).  A CU pulls at most about 65 GB/s through its L1, so a short stream is
 // bandwidth-starved unless all 256 CUs pull a share of it.  While at most one workgroup per CU comes of it, the work of a KV head is cut into
 // query tiles and column slices only: a workgroup's waves stream disjoint key tiles, straight to LDS, and their states meet in LDS at
 // the end, in one launch.  Beyond the lengths where that pays, the key range is split over several workgroups of attn_bf16_kernel, each
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
         a.lse[((int64_t)b * a.n_q_heads + ro.head) * a.n_q + ro.row] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-// A few query tiles for one key stream (attn_wave_kernel, attn_pair_kernel).  A workgroup serves QS * QT query tiles of one KV head and one
+// A few query tiles for one key stream (attn_wave_kernel, attn_pair_kernel, attn_quad_kernel).  A workgroup serves QS * QT query tiles of one KV head and one
 // slice of DV = D / DS output columns; its QS * KG waves are KG key groups, which take the KEYS-key tiles of the range in turn, times QS
 // query slots of QT tiles.  The key groups' states meet in LDS once, at the end.  The rows that share a KV head are numbered through
 // all heads of the group (row f is row f % n_q of head f / n_q), so only a KV head's last tile can be partly empty: 33 rows of 2 heads
@@ -740,14 +740,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 // - Tiles go from memory straight to LDS, with no staging registers, no LDS write instructions and no barrier in the loop: with one slot
 //   a wave has its own tiles (K of the tile after next is requested when this tile's scores are formed, V of the next one when this
 //   tile's product is), with two the slots of a group share them, one loading K and one V into the stage that is free, and meet once a
-//   step.  The groups drift apart, so that some waves are in their exponentials while others are in their MFMAs (a barrier per step
+//   step; with four, two load K and two V, into a ring of four stages.  The groups drift apart, so that some waves are in their exponentials while others are in their MFMAs (a barrier per step
 //   instead of the meeting: 14.6 us for the loop below instead of 11.2).
 // - A fragment read from LDS serves QT MFMAs; with one query tile per wave the LDS reads alone took half the time of such a kernel.  Four
 //   tiles in every wave need no slots, but twice the states to merge: 3.6 us of 20 at head_dim 128, against 2.2 with two slots.
+// - 8 query tiles take four slots: as long as that leaves one workgroup per CU, two with 4 tiles each on a CU pull the keys twice, one
+//   after the other.  There the MFMAs and exponentials of a step (0.9 us of the 1.3 it takes) bound the launch, no longer the pull.
 // - With DS slices the scores are formed DS times, but K and 1 / DS of V is all a workgroup pulls, and the states are small.
 // Measured per launch, the kernels these replaced / here: 32 heads x 764 keys x 60 rows 10.0 / 8.9 us; 4 sequences x 8 KV heads x up to 1316
 // keys x 33 rows of 2 heads, head_dim 256, 27.3 / 20.6 us; 8 sequences x 8 KV heads x up to 1340 keys x 60 rows of 4 heads 23.2 / 20.8 us
-// (start to scores 3 us, loop 11, states and rows 2.3).
+// (start to scores 3 us, loop 11, states and rows 2.3); 16 sequences of that, in four slots, 40.6 / 33.5 us.
 //
 // 16-byte chunk i of row r of a K tile sits at i ^ (r mod 16) (at head_dim 64, two rows to a bank line: i ^ (r/2 mod 8)), and pair i of the
 // chunks of a V row at i ^ (r mod 8) (slices of 64 columns: r/2 mod 4, of 32: r/4 mod 2), so that neither the 16-byte reads of K nor the
@@ -759,14 +761,19 @@ struct RowsGeom {
     static constexpr int NDT = DV / 16, NKS = D / 32, NH = KEYS / 16;              // column tiles, key steps, 16-key halves
     static constexpr int UNIT = QT * NDT * 1024, QTILE = 16 * KROW;                // bytes of a wave's outputs, of a query tile
     // LDS: the tiles of the key groups (K, V and a second K stage, with two query slots a second V stage as well), whose place the waves'
-    // outputs take at the end; references and sums; every wave's masks; parents; the pairs' step counts.  The queries lie where they fit:
-    // with one slot tile i where group i's second K stage will be, else behind the stages of the groups or of all
-    static constexpr int GROUP = KTILE + VTILE, STAGES = QS == 2 ? 2 * GROUP : GROUP + KTILE, STRIDE = STAGES > QS * UNIT ? STAGES : QS * UNIT, TILES = KG * STRIDE;
+    // outputs take at the end; references and sums; every wave's masks; parents; the slots' step counts.  The queries lie where they fit:
+    // with one slot tile i where group i's second K stage will be, with two behind the stages of the groups or of all, with four where the last
+    // stages will be, filled when the queries are in registers
+    static constexpr int GROUP = KTILE + VTILE, NS = QS == 4 ? 4 : 2, STAGES = QS > 1 ? NS * GROUP : GROUP + KTILE, STRIDE = STAGES > QS * UNIT ? STAGES : QS * UNIT, TILES = KG * STRIDE;
     static constexpr bool Q_APART = QS == 2 && STRIDE - STAGES < QTILE;
-    static constexpr int Q_OFF = Q_APART ? TILES : QS == 2 ? STAGES : GROUP, Q_STRIDE = Q_APART ? QTILE : STRIDE;
+    static constexpr int Q_PER = QS == 4 ? QS * QT / KG : 1;                       // query tiles that lie together
+    static constexpr int EARLY = QS == 4 ? (STRIDE - Q_PER * QTILE) / GROUP : NS;  // stages that hold no queries
+    static constexpr int Q_OFF = Q_APART ? TILES : QS > 1 ? EARLY * GROUP : GROUP, Q_STRIDE = Q_APART ? QTILE : STRIDE;
+    static constexpr int q_at(int i) { return Q_OFF + i / Q_PER * Q_STRIDE + i % Q_PER * QTILE; }
+    static constexpr int LOADERS = QS == 4 ? 2 : 1;                                // waves that share the loads of a K tile, and of a V tile
     static constexpr int ML_OFF = TILES + (Q_APART ? QS * QT * QTILE : 0), MASK_OFF = ML_OFF + NW * QT * 32 * 4, PAR_OFF = MASK_OFF + NW * QT * 16 * 8, MEET_OFF = PAR_OFF + 64 * 4;
     static constexpr size_t BYTES = MEET_OFF + NW * 4;
-    static_assert(BYTES <= 160 * 1024 && (Q_APART || QS * QT <= KG) && (QS == 2 || QTILE <= KTILE), "a workgroup's LDS");
+    static_assert(BYTES <= 160 * 1024 && (Q_APART || QS * QT <= KG * Q_PER) && (QS > 1 || QTILE <= KTILE) && EARLY >= 1 && EARLY <= NS, "a workgroup's LDS");
 };
 
 template <int N>
@@ -787,15 +794,27 @@ __device__ __forceinline__ constexpr int swizzle_v(int j) { return ROW <= 128 ? 
 template <int ROW>
 __device__ __forceinline__ constexpr int pair_of_v(int r) { return ROW == 64 ? (r >> 2) & 1 : ROW == 128 ? (r >> 1) & 3 : r & 7; }
 
-// Waves 2j and 2j + 1 of a workgroup wait for each other: each writes how often it has been here and reads the other's count until it has
-// come as far.  The LDS operations of a wave take effect in order, so what a wave wrote or read before, the other finds done.
-__device__ __forceinline__ void pair_meet(uint32_t meet, int wave, int count)
+// The SLOTS adjacent waves of a key group wait for each other: each writes how often it has been here and reads the others' counts until they
+// have come as far.  The LDS operations of a wave take effect in order, so what a wave wrote or read before, the others find done.
+template <int SLOTS>
+__device__ __forceinline__ void slots_meet(uint32_t meet, int wave, int count)
 {
     typedef __attribute__((address_space(3))) volatile int lds_int;
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) volatile i32x4 lds_int4;
     asm volatile("" ::: "memory");
     *(lds_int *)(uintptr_t)(meet + 4 * wave) = count;
-    while (__builtin_amdgcn_readfirstlane(*(lds_int *)(uintptr_t)(meet + 4 * (wave ^ 1))) < count)
-        ;
+    if constexpr (SLOTS == 2) {
+        while (__builtin_amdgcn_readfirstlane(*(lds_int *)(uintptr_t)(meet + 4 * (wave ^ 1))) < count)
+            ;
+    } else {
+        static_assert(SLOTS == 4, "a key group's counts are read together");
+        for (;;) {
+            const i32x4 at = *(lds_int4 *)(uintptr_t)(meet + 4 * (wave & ~3));
+            if (__builtin_amdgcn_readfirstlane(min(min(at[0], at[1]), min(at[2], at[3]))) >= count)
+                break;
+        }
+    }
     asm volatile("" ::: "memory");
 }
 
@@ -824,7 +843,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         for (int i = wave; i < TILES_Q * 16 * KROW / 1024; i += NW) {
             const int r = i * (64 / LPK) + lane / LPK;             // row of the workgroup
             const int f = min(row0 + r, n_rows - 1), hh = quick_div(f, a.nq_magic), row = f - hh * a.n_q;
-            lds_load16(qb, (uint32_t)((row * a.n_q_heads + hh) * KROW + (((lane % LPK) ^ (D == 64 ? (r >> 1) & 7 : r & 15)) * 16)), lds0 + G::Q_OFF + i / (G::QTILE / 1024) * G::Q_STRIDE + i % (G::QTILE / 1024) * 1024);
+            lds_load16(qb, (uint32_t)((row * a.n_q_heads + hh) * KROW + (((lane % LPK) ^ (D == 64 ? (r >> 1) & 7 : r & 15)) * 16)), lds0 + G::q_at(i / (G::QTILE / 1024)) + i % (G::QTILE / 1024) * 1024);
         }
         if (wave == NW - 1 && !a.tree_mask)
             lds_load4(a.parent + (int64_t)b * a.n_tree, (uint32_t)min(lane, a.n_tree - 1) * 4, lds0 + G::PAR_OFF);
@@ -837,62 +856,81 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     // ---- tile loads: a lane's 16 bytes of instruction j go to 1024 * j + 16 * lane of the tile's area
     const unsigned char *kbase = reinterpret_cast<const unsigned char *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * KROW;
     const unsigned char *vbase = reinterpret_cast<const unsigned char *>(a.v) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * KROW + ds * VROW;
+    // (two loaders of a tile take a half of its instructions each: the second's rows lie k_half, v_half rows on, and the half's number is a bit of
+    // its own in the swizzle)
+    auto scalar = [](uint32_t x) { return G::LOADERS == 2 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)x) : x; };   // (the same in every lane; the compiler puts the half in a vector register)
+    constexpr int KJ = NK / G::LOADERS, VJ = NV / G::LOADERS;
+    static_assert(G::LOADERS == 1 || ((swizzle_k<KROW>(KJ) & swizzle_k<KROW>(KJ - 1)) == 0 && (swizzle_v<VROW>(VJ) & swizzle_v<VROW>(VJ - 1)) == 0), "loaders");
+    const int half = G::LOADERS == 2 ? qs & 1 : 0, k_half = half * (KJ * (64 / LPK)), v_half = half * (VJ * (64 / LPV));
     const int krow = lane / LPK, vrow = lane / LPV;
-    const int kl = ((lane % LPK) ^ (D == 64 ? krow >> 1 : krow)) * 16, vl = ((lane % LPV) ^ (2 * pair_of_v<VROW>(vrow))) * 16;
+    const int kl = (((lane % LPK) ^ (D == 64 ? krow >> 1 : krow)) * 16) ^ (half * swizzle_k<KROW>(KJ)), vl = (((lane % LPV) ^ (2 * pair_of_v<VROW>(vrow))) * 16) ^ (half * swizzle_v<VROW>(VJ));
     auto issue_k = [&](int t, int at) {
+        const uint32_t dst = scalar(lds0 + at + half * (KJ * 1024));
         if ((t + 1) * KEYS <= kv_len) {
-            const unsigned char *p = kbase + (int64_t)t * (KEYS * KROW);
+            const unsigned char *p = kbase + (int64_t)t * (KEYS * KROW) + k_half * KROW;
 #pragma unroll
-            for (int j = 0; j < NK; j++)
-                lds_load16<ONCE>(p + j * 1024, (uint32_t)(krow * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
+            for (int j = 0; j < KJ; j++)
+                lds_load16<ONCE>(p + j * 1024, (uint32_t)(krow * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
         } else {
             // the ragged end: rows past the last live one are that one again (their scores are masked)
 #pragma unroll
-            for (int j = 0; j < NK; j++)
-                lds_load16(kbase, (uint32_t)(min(t * KEYS + j * (64 / LPK) + krow, kv_len - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), lds0 + at + j * 1024);
+            for (int j = 0; j < KJ; j++)
+                lds_load16(kbase, (uint32_t)(min(t * KEYS + k_half + j * (64 / LPK) + krow, kv_len - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
         }
     };
     auto issue_v = [&](int t, int at) {
+        const uint32_t dst = scalar(lds0 + at + half * (VJ * 1024));
         if ((t + 1) * KEYS <= kv_len) {
-            const unsigned char *p = vbase + (int64_t)t * (KEYS * KROW);
+            const unsigned char *p = vbase + (int64_t)t * (KEYS * KROW) + v_half * KROW;
 #pragma unroll
-            for (int j = 0; j < NV; j++)
-                lds_load16<ONCE>(p + j * (64 / LPV) * KROW, (uint32_t)(vrow * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
+            for (int j = 0; j < VJ; j++)
+                lds_load16<ONCE>(p + j * (64 / LPV) * KROW, (uint32_t)(vrow * KROW + (vl ^ swizzle_v<VROW>(j))), dst + j * 1024);
         } else {
 #pragma unroll
-            for (int j = 0; j < NV; j++)
-                lds_load16(vbase, (uint32_t)(min(t * KEYS + j * (64 / LPV) + vrow, kv_len - 1) * KROW + (vl ^ swizzle_v<VROW>(j))), lds0 + at + j * 1024);
+            for (int j = 0; j < VJ; j++)
+                lds_load16(vbase, (uint32_t)(min(t * KEYS + v_half + j * (64 / LPV) + vrow, kv_len - 1) * KROW + (vl ^ swizzle_v<VROW>(j))), dst + j * 1024);
         }
     };
-    // one query slot: a wave's own K, V and second K areas.  Two: the key group's, stage by stage; slot 0 loads its K tiles, slot 1 its V tiles
-    int ktile = kg * G::STRIDE, ktile2 = ktile + G::GROUP;
+    // one query slot: a wave's own K, V and second K areas.  Two and four: the key group's, stage by stage; the lower half of the slots loads its K
+    // tiles, the upper half its V tiles
+    int ktile = kg * G::STRIDE;
+    [[maybe_unused]] int ktile2 = ktile + G::GROUP;
     const int vtile = ktile + G::KTILE;
     int t = kg;
     auto wait_slot = [&](auto n) {      // until the loads of at most n steps are in flight
-        if (qs == 0)
-            wait_loads<n * NK>();
+        if (qs < QS / 2)
+            wait_loads<n * KJ>();
         else
-            wait_loads<n * NV>();
+            wait_loads<n * VJ>();
+    };
+    auto wait_steps = [&](int n) {
+        if (n <= 0)
+            wait_loads<0>();
+        else if (n == 1)
+            wait_slot(std::integral_constant<int, 1>());
+        else if (n == 2 || G::NS == 2)
+            wait_slot(std::integral_constant<int, 2>());
+        else
+            wait_slot(std::integral_constant<int, G::NS == 2 ? 2 : 3>());
     };
     auto issue_slot = [&](int t, int at) {
-        if (qs == 0)
+        if (qs < QS / 2)
             issue_k(t, at);
         else
             issue_v(t, at + G::KTILE);
     };
+    const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
     const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
     const uint32_t meet = lds0 + G::MEET_OFF;
-    if (QS == 2)
+    if (QS > 1)
         *reinterpret_cast<int *>(smem_raw + G::MEET_OFF + 4 * wave) = 0;
     if (t < t_end) {
-        if constexpr (QS == 2) {
-            issue_slot(t, ktile);
-            if (t + KG < t_end) {
-                issue_slot(t + KG, ktile2);
-                wait_slot(std::integral_constant<int, 2>());   // the queries and parents are there; the first tiles stay in flight
-            } else {
-                wait_slot(std::integral_constant<int, 1>());
-            }
+        if constexpr (QS > 1) {
+#pragma unroll
+            for (int i = 0; i < G::EARLY; i++)
+                if (i < n_steps)
+                    issue_slot(t + i * KG, ktile + i * G::GROUP);
+            wait_steps(min(n_steps, G::EARLY));   // the queries and parents are there; the first tiles stay in flight
         } else {
             issue_k(t, ktile);
             issue_v(t, vtile);
@@ -914,12 +952,17 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     for (int qt = 0; qt < QT; qt++)
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(smem_raw + G::Q_OFF + (qs * QT + qt) * G::Q_STRIDE + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
+            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(smem_raw + G::q_at(qs * QT + qt) + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
     if constexpr (!G::Q_APART)
         __syncthreads();                // every wave has its queries
     if constexpr (QS == 1) {
         if (!early && t + KG < t_end)
             issue_k(t + KG, ktile2);
+    } else {
+#pragma unroll
+        for (int i = G::EARLY; i < G::NS; i++)
+            if (i < n_steps)
+                issue_slot(t + i * KG, ktile + i * G::GROUP);
     }
     // ---- what the wave's rows see of the tree: lanes 16 * qt .. work out query tile qt's
     uint64_t *masks = reinterpret_cast<uint64_t *>(smem_raw + G::MASK_OFF) + wave * QT * 16;
@@ -1069,18 +1112,22 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     s16x4 va[VB][NH], vb[VB][NH];
     f32x4 s[NH][QT];
     __bf16 p[QT][NH * 4];
-    if constexpr (QS == 2) {
-        // The two waves of a key group meet at every step: each says that its half of the step's tiles is there, which also says that it is
-        // done with the stage before.  (Both always come: a key group's waves take the same number of steps.)
-        const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
+    if constexpr (QS > 1) {
+        // The waves of a key group meet at every step: each says that its share of the step's tiles is there, which also says that it is
+        // done with the stage before.  (All always come: a key group's waves take the same number of steps.)
+        int before = ktile + (G::NS - 1) * G::GROUP;      // the stage of the step before
         for (int i = 1; i <= n_steps; i++, t += KG) {
-            if (i == 1 && t + KG < t_end)
-                wait_slot(std::integral_constant<int, 1>());
-            else
-                wait_loads<0>();
-            pair_meet(meet, wave, i);
-            if (i > 1 && t + KG < t_end)
-                issue_slot(t + KG, ktile2);
+            if constexpr (G::NS == 2) {
+                if (i == 1 && t + KG < t_end)
+                    wait_slot(std::integral_constant<int, 1>());
+                else
+                    wait_loads<0>();
+            } else {
+                wait_steps(min(n_steps - i, i == 1 ? G::NS - 1 : G::NS - 2));
+            }
+            slots_meet<QS>(meet, wave, i);
+            if (i > 1 && t + (G::NS - 1) * KG < t_end)
+                issue_slot(t + (G::NS - 1) * KG, before);
             scores(ktile, s);
             read_v(ktile + G::KTILE, 0, va);
             softmax(t, s, p);
@@ -1089,11 +1136,11 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             product(0, va, p);
             product(VB, vb, p);
             const int x = ktile;
-            ktile = ktile2;
-            ktile2 = x;
+            ktile = G::NS == 2 ? before : i % G::NS ? ktile + G::GROUP : kg * G::STRIDE;
+            before = x;
         }
         wait_lds();
-        pair_meet(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
+        slots_meet<QS>(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
     } else {
         for (; t < t_end; t += KG) {
             const bool more = t + KG < t_end, more2 = t + 2 * KG < t_end;
@@ -1190,6 +1237,8 @@ template <int D, int NW, int DS, int QT>
 using WaveGeom = RowsGeom<D, DS, QT, 1, NW, wave_keys<D, NW, DS>()>;
 template <int D, int DS, int QT>
 using PairGeom = RowsGeom<D, DS, QT, 2, 4, D == 256 ? 16 : 32>;
+template <int D, int DS, int QT>
+using QuadGeom = RowsGeom<D, DS, QT, 4, 2, D == 256 ? 16 : 32>;
 
 // ONCE: the loads of whole tiles carry the nontemporal hint (see AttnArgs::once)
 // one query slot: NW key groups of one wave, QT query tiles and one of DS column slices a workgroup
@@ -1204,6 +1253,13 @@ template <int D, int DS, int QT, bool ONCE>
 __global__ __launch_bounds__(512) void attn_pair_kernel(AttnArgs a)
 {
     attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, ONCE>(a);
+}
+
+// four query slots: 2 key groups of four waves, 4 * QT query tiles a workgroup
+template <int D, int DS, int QT, bool ONCE>
+__global__ __launch_bounds__(512) void attn_quad_kernel(AttnArgs a)
+{
+    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, ONCE>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1340,15 +1396,15 @@ struct Plan {
     int mw;           // 64-bit words of a node's visibility mask (1, or 4 for trees above 64 nodes)
     int once;         // 1: the variant whose K/V loads carry the nontemporal hint (one query group per KV head)
     int kg;           // key groups per workgroup of the shared-tile kernel (1; 2 = 8 waves as two groups of 4)
-    bool wave_mode;   // attn_wave_kernel or attn_pair_kernel: waves split the keys of a workgroup, workgroups do not
+    bool wave_mode;   // attn_wave_kernel, attn_pair_kernel or attn_quad_kernel: waves split the keys of a workgroup, workgroups do not
     int wave_nw;      // waves per workgroup in that mode
     int wave_ds;      // workgroups that share the output columns of a query tile in that mode (1, 2 or 4)
     int wave_qt;      // query tiles per wave in that mode
-    bool pair;        // ... two slots of as many (attn_pair_kernel)
+    int slots;        // query slots of a workgroup in that mode: 1, 2 (attn_pair_kernel) or 4 (attn_quad_kernel)
     size_t state_floats, off_part, total;
 };
 
-// The kernels that cut the work into query tiles and column slices only (attn_wave_kernel, attn_pair_kernel): one launch, no key split.
+// The kernels that cut the work into query tiles and column slices only (attn_wave_kernel, attn_pair_kernel, attn_quad_kernel): one launch, no key split.
 // What such a launch costs is what its busiest CU pulls, K and 1 / DS of V per workgroup, as long as all workgroups run at once; so
 // the decompositions below are tried from the one that spreads the bytes thinnest, and the first with at most one workgroup per CU is
 // taken, up to the number of 32-key tiles at which key splits with their merge launch (or the shared-tile kernel) catch up.  Measured
@@ -1365,17 +1421,17 @@ struct Plan {
 //   head_dim 256, 8 KV heads, groups of 2: DS 4: 55 tiles 20.4 / 21.7, 67 tiles 23.5 / 23.2 (24 rows: 42 tiles 16.5 / 18.3, 55 tiles 20.5 / 19.3); two
 //   tiles: 55 tiles 22.8 / 23.2, 67 tiles 26.5 / 25.3; three: 55 tiles 25.3 / 25.8, 67 tiles 29.1 / 28.8; pairs of one: 55 tiles 30.3 / 30.5, 67 tiles
 //   36.1 / 33.8; pairs of two, 8 sequences: 13 tiles 14.4 / 23.8, 42 tiles 32.2 / 39.4, 127 tiles 80.8 / 82.7
+//   four slots of two tiles, 16 sequences (9 to 12 within 3 us of that): head_dim 128, 8 tiles 14.5 / 14.2, 21 tiles 21.2 / 24.5, 42 tiles 33.5 / 40.6, 80 tiles
+//   54.9 / 70.9, 127 tiles 82.7 / 109.2; head_dim 256, 8 tiles 18.1 / 18.0, 42 tiles 51.7 / 54.5, 80 tiles 90.1 / 93.9, 127 tiles 138.1 / 145.9
 struct Decomposition {
-    int d;
-    bool pair;
-    int ds, qt;
+    int d, slots, ds, qt;
     int tiles_1, tiles_n;    // longest range in 32-key tiles with one query head per KV head, with several (0: not used)
 };
 const Decomposition DECOMPOSITIONS[] = {
-    {128, false, 4, 1, 40, 48}, {128, false, 2, 1, 72, 88}, {128, false, 2, 2, 92, 128}, {128, false, 2, 3, 92, 128}, {128, false, 1, 2, 120, 160},
-    {128, true, 1, 2, 0, 1 << 30},
-    {64, false, 2, 1, 72, 88}, {64, false, 1, 1, 80, 96}, {64, false, 1, 2, 128, 160},
-    {256, false, 4, 1, 0, 52}, {256, false, 4, 2, 0, 56}, {256, false, 4, 3, 0, 60}, {256, true, 2, 1, 0, 56}, {256, true, 2, 2, 0, 128},
+    {128, 1, 4, 1, 40, 48}, {128, 1, 2, 1, 72, 88}, {128, 1, 2, 2, 92, 128}, {128, 1, 2, 3, 92, 128}, {128, 1, 1, 2, 120, 160},
+    {128, 2, 1, 2, 0, 1 << 30}, {128, 4, 1, 2, 0, 1 << 30},
+    {64, 1, 2, 1, 72, 88}, {64, 1, 1, 1, 80, 96}, {64, 1, 1, 2, 128, 160},
+    {256, 1, 4, 1, 0, 52}, {256, 1, 4, 2, 0, 56}, {256, 1, 4, 3, 0, 60}, {256, 2, 2, 1, 0, 56}, {256, 2, 2, 2, 0, 128}, {256, 4, 2, 2, 0, 128},
 };
 
 bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
@@ -1384,7 +1440,8 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     const int64_t base = (int64_t)d->batch * d->n_kv_heads;
     const int tiles = ceil_div(max_kv_len, 32), rows = ceil_div((int64_t)G * n_q, 16);
     const int n_qtiles = G * ceil_div(n_q, 16);      // as many as the heads' rows would need one head after the other
-    p->wave_mode = p->pair = false;
+    p->wave_mode = false;
+    p->slots = 1;
     if (d->dtype != DREAM_BF16 || q_tiles_override() != 0 || kv_splits_override() != 0 || tile_waves_override() != 0 || n_qtiles > 16 || G > 4 ||
         base * n_qtiles < 32 || d->s_max * d->head_dim >= (1ll << 30))
         return false;
@@ -1400,14 +1457,14 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     } else {
         const Decomposition *use = nullptr;
         for (const Decomposition &c : DECOMPOSITIONS)
-            if (!use && c.d == d->head_dim && base * ceil_div(rows, (c.pair ? 2 : 1) * c.qt) * c.ds <= 256)
+            if (!use && c.d == d->head_dim && base * ceil_div(rows, c.slots * c.qt) * c.ds <= 256)
                 use = &c;
         if (!use || tiles > (G == 1 ? use->tiles_1 : use->tiles_n))
             return false;
         // (up to 96 KV heads with 4 tiles each change to key groups and splits where they always have: measured here at 24 key tiles only)
-        if (use->d == 128 && use->ds == 1 && !use->pair && G == 1 && base <= 96 && tiles > 48)
+        if (use->d == 128 && use->ds == 1 && use->slots == 1 && G == 1 && base <= 96 && tiles > 48)
             return false;
-        p->pair = use->pair;
+        p->slots = use->slots;
         p->wave_ds = use->ds;
         p->wave_qt = use->qt;
     }
@@ -1415,10 +1472,10 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     // 4 waves while each has about one tile (5 tiles: 6.8 us with 4, 6.9 with 8), and at head_dim 256 with one query tile, where a wave's 32
     // keys of 4 waves and 16 keys of 8 take the same LDS (42 tiles: 16.4 us with 4, 15.9 with 8)
     p->wave_nw = 8;
-    if (!p->pair && (d->head_dim == 256 ? p->wave_qt == 1 : p->wave_ds == 1 && tiles <= 5))
+    if (p->slots == 1 && (d->head_dim == 256 ? p->wave_qt == 1 : p->wave_ds == 1 && tiles <= 5))
         p->wave_nw = 4;
     p->qg = 1;
-    p->n_qg = p->wave_qt == 1 && !p->pair ? n_qtiles : rows;    // (a tile that the rows do not need ends at once)
+    p->n_qg = p->wave_qt == 1 && p->slots == 1 ? n_qtiles : rows;    // (a tile that the rows do not need ends at once)
     p->n_splits = 1;
     p->n_groups = p->n_streams = (int)base;
     p->grid = 0;
@@ -1436,7 +1493,8 @@ int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool direct
     if (make_wave_plan(d, n_q, max_kv_len, p)) {
         if (direct)
             return 0;
-        p->wave_mode = p->pair = false;
+        p->wave_mode = false;
+        p->slots = 1;
     } else {
         direct = true;
     }
@@ -1575,7 +1633,7 @@ void make_wide_plan(const dream_attn_desc *d, int n_q, Plan *p)
     p->tiles_per_head = ceil_div(n_q, 16);
     p->wave_mode = false;
     p->wave_nw = p->wave_ds = p->wave_qt = 0;
-    p->pair = false;
+    p->slots = 1;
     p->qg = 1;
     p->nw = 4;
     p->mw = 4;
@@ -1681,10 +1739,32 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
     return check_launch("attn_pair_kernel");
 }
 
+template <int D, int DS, int QT>
+int ensure_quad_lds()
+{
+    static std::atomic<uint64_t> done[2];
+    constexpr size_t bytes = QuadGeom<D, DS, QT>::BYTES;
+    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, false>), bytes, "attention");
+    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, true>), bytes, "attention");
+}
+
+template <int D, int DS, int QT>
+int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
+{
+    if (int rc = ensure_quad_lds<D, DS, QT>())
+        return rc;
+    const dim3 grid(8 * ceil_div(a.n_qg, 4 * QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    if (a.once)
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, true>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, a);
+    else
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, false>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, a);
+    return check_launch("attn_quad_kernel");
+}
+
 // Every bf16 kernel variant the launch plan can choose, in one table: the plan names a variant by
 // (kernel family, head_dim, three template arguments); the table gives its launcher and the routine that raises
 // its dynamic-LDS limit.  The launch, dream_init, dream_attn_plan_describe and dream_attn_variants all read it.
-enum { FAMILY_TILE = 0, FAMILY_WAVE = 1, FAMILY_PAIR = 2 };
+enum { FAMILY_TILE = 0, FAMILY_WAVE = 1, FAMILY_PAIR = 2, FAMILY_QUAD = 4 };
 struct Variant {
     int family, d, p1, p2, p3, p4, p5, p6, p7;   // tile: (QG, KT, PFD, waves, mask words, read-once, key groups); wave: (NW, DS, QT, 0, 1, 0, 1)
     int (*launch)(const AttnArgs &, const Plan &, hipStream_t);
@@ -1698,6 +1778,7 @@ struct Variant {
 #define TILE8_VARIANT(D, QG, KT, PFD) {FAMILY_TILE, D, QG, KT, PFD, 8, 1, 1, 1, &launch_bf16<D, QG, KT, PFD, 8, 1, true>, &ensure_bf16_lds<D, QG, KT, PFD, 8, 1, true>}
 #define WAVE_VARIANT(D, NW, DS, QT) {FAMILY_WAVE, D, NW, DS, QT, 0, 1, 0, 1, &launch_wave<D, NW, DS, QT>, &ensure_wave_lds<D, NW, DS, QT>}
 #define PAIR_VARIANT(D, DS, QT) {FAMILY_PAIR, D, 8, DS, QT, 0, 1, 0, 1, &launch_pair<D, DS, QT>, &ensure_pair_lds<D, DS, QT>}
+#define QUAD_VARIANT(D, DS, QT) {FAMILY_QUAD, D, 8, DS, QT, 0, 1, 0, 1, &launch_quad<D, DS, QT>, &ensure_quad_lds<D, DS, QT>}
 const Variant VARIANTS[] = {
     // shared-tile kernel, one query tile per wave: a short key range in one step (2-4 tiles), or streamed
     TILE_VARIANT(64, 1, 2, 1), TILE_VARIANT(64, 1, 3, 1), TILE_VARIANT(64, 1, 4, 1), TILE_VARIANT(64, 1, 2, 2),
@@ -1724,6 +1805,8 @@ const Variant VARIANTS[] = {
     WAVE_VARIANT(128, 8, 2, 2), WAVE_VARIANT(128, 8, 2, 3), WAVE_VARIANT(256, 8, 4, 2), WAVE_VARIANT(256, 8, 4, 3),
     // two query slots: (column slices, query tiles per slot)
     PAIR_VARIANT(128, 1, 2), PAIR_VARIANT(256, 2, 1), PAIR_VARIANT(256, 2, 2),
+    // four
+    QUAD_VARIANT(128, 1, 2), QUAD_VARIANT(256, 2, 2),
 };
 #undef TILE_VARIANT
 #undef TILE8_VARIANT
@@ -1733,12 +1816,13 @@ const Variant VARIANTS[] = {
 #undef WIDE_VARIANT
 #undef WAVE_VARIANT
 #undef PAIR_VARIANT
+#undef QUAD_VARIANT
 constexpr int N_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
 
 // the variant a plan asks for, or nullptr
 const Variant *find_variant(const dream_attn_desc *d, const Plan &p)
 {
-    const int family = p.pair ? FAMILY_PAIR : p.wave_mode ? FAMILY_WAVE : FAMILY_TILE;
+    const int family = !p.wave_mode ? FAMILY_TILE : p.slots == 1 ? FAMILY_WAVE : p.slots == 2 ? FAMILY_PAIR : FAMILY_QUAD;
     const int p1 = p.wave_mode ? p.wave_nw : p.qg, p2 = p.wave_mode ? p.wave_ds : p.kt, p3 = p.wave_mode ? p.wave_qt : p.pfd;
     const int p4 = p.wave_mode ? 0 : p.nw, p5 = p.wave_mode ? 1 : p.mw, p6 = p.wave_mode ? 0 : p.once, p7 = p.wave_mode ? 1 : p.kg;
     for (int i = 0; i < N_VARIANTS; i++) {
@@ -1751,8 +1835,8 @@ const Variant *find_variant(const dream_attn_desc *d, const Plan &p)
 
 void variant_name(const Variant &v, char *buf, size_t n)
 {
-    if (v.family == FAMILY_PAIR)
-        snprintf(buf, n, "attn_pair_kernel<%d,%d,%d>", v.d, v.p2, v.p3);
+    if (v.family == FAMILY_PAIR || v.family == FAMILY_QUAD)
+        snprintf(buf, n, "attn_%s_kernel<%d,%d,%d>", v.family == FAMILY_PAIR ? "pair" : "quad", v.d, v.p2, v.p3);
     else if (v.family == FAMILY_WAVE)
         snprintf(buf, n, "attn_wave_kernel<%d,%d,%d,%d>", v.d, v.p1, v.p2, v.p3);
     else if (v.p7 != 1)
@@ -1880,7 +1964,7 @@ int dream_attn_plan_describe(const dream_attn_desc *desc, int32_t n_q, int64_t m
     variant_name(*v, name, sizeof name);
     if (p.wave_mode)
         snprintf(buf, buf_bytes, "%s workgroups=%d splits=1 merge_launch=0", name,
-                 ceil_div(p.n_qg, p.pair ? 2 * p.wave_qt : p.wave_qt) * p.wave_ds * desc->n_kv_heads * desc->batch);
+                 ceil_div(p.n_qg, p.slots * p.wave_qt) * p.wave_ds * desc->n_kv_heads * desc->batch);
     else
         snprintf(buf, buf_bytes, "%s workgroups=%d splits=%d merge_launch=%d", name, p.n_groups * p.n_splits, p.n_splits,
                  p.n_splits > 1 ? 1 : 0);

@@ -66,6 +66,9 @@ VARIANT_CASES = [
     VariantCase("attn_pair_kernel<128,1,2>", 8, 32, 8, 128, 33, 5, 410, 0, 0),
     VariantCase("attn_pair_kernel<256,2,1>", 4, 16, 8, 256, 60, 6, 333, 0, 0),
     VariantCase("attn_pair_kernel<256,2,2>", 6, 16, 8, 256, 60, 6, 301, 0, 0),
+    # four
+    VariantCase("attn_quad_kernel<128,1,2>", 12, 32, 8, 128, 60, 6, 410, 0, 0),
+    VariantCase("attn_quad_kernel<256,2,2>", 12, 16, 8, 256, 60, 6, 333, 0, 0),
 ]
 
 # The launch the benchmark times: dream_tree_verify_attn at each full-size configuration.

@@ -233,6 +233,30 @@ def test_sliced_kernels_at_tile_edges(gu, shape):
     assert np.abs(got - want).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,T", [(16, 32, 8, 128, 33), (12, 32, 8, 128, 60), (12, 16, 8, 256, 60), (9, 16, 8, 256, 49)])
+def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
+    """The same for four query slots: no, one, fewer and more steps than a key group has stages, a last workgroup with few query tiles; under a
+    mask, and as a cross-attention call."""
+    for prefix in (0, 32 - T % 32, 64 - T % 64, 128 - T, 129 - T, 256 - T, 257 - T, 333, 400):
+        prefix = max(prefix, 0)
+        cfg = _cfg("edge", "bf16", B, Hq, Hkv, D, prefix, 0, T, min(5, T - 1), 48)
+        x = di.verify_inputs(cfg, prefix_len=[prefix if b % 3 != 1 else prefix // 2 for b in range(B)])
+        assert gu.verify_plan(x).startswith("attn_quad_kernel"), gu.verify_plan(x)
+        got, lse = gu.run_verify(x)
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+        assert np.isfinite(got).all(), prefix
+        assert np.abs(got - want).max() <= TOL["bf16"], (prefix, np.abs(got - want).max())
+        assert np.abs(lse - want_lse).max() <= 2e-3, prefix
+    star = np.stack([di.ancestor_mask_bits(di.star_tree(T), True)[:, 0]] * B)
+    got, _ = gu.run_verify(x, tree_mask=star)
+    want, _ = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, np.stack([di.star_tree(T)] * B), True)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+    rows = np.stack([np.roll(np.arange(T, dtype=np.int32), 3)] * B)
+    got, qsel = gu.run_xattn(x, rows, rows)
+    want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+
+
 def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
     """Loads straight to LDS need 16-byte aligned tensors: queries or caches that start elsewhere give the same rows within rounding, in
     the workspace the query returned."""

@@ -35,6 +35,22 @@ def loaded(row_bytes, keys, kind):
     return at
 
 
+@pytest.mark.parametrize("row_bytes,keys,kind", [(256, 32, "k"), (512, 16, "k"), (256, 32, "v"), (256, 16, "v")])
+def test_two_loaders_put_the_tile_where_one_does(row_bytes, keys, kind):
+    """The second loader's instructions, its half of the rows further, with the half's own bit of the swizzle in the lane's chunk."""
+    lanes, at = row_bytes // 16, {}
+    n = keys * row_bytes // 1024 // 2
+    swizzle = swizzle_k if kind == "k" else swizzle_v
+    for half in range(2):
+        for j in range(n):
+            for lane in range(64):
+                row, ch = lane // lanes, lane % lanes
+                own = (ch ^ (row if kind == "k" else 2 * pair_of_v(row_bytes, row))) * 16 ^ half * swizzle(row_bytes, n)
+                for i in range(0, 16, 2):
+                    at[half * n * 1024 + j * 1024 + lane * 16 + i] = (half * n * (64 // lanes) + j * (64 // lanes) + row, (own ^ swizzle(row_bytes, j)) + i)
+    assert at == loaded(row_bytes, keys, kind)
+
+
 def bank_groups(addresses, width):
     """Lanes served together: 256 bytes of the 64 banks at a time."""
     per = 256 // width
