@@ -1417,7 +1417,9 @@ struct Plan {
 //   unsliced, 4 sequences: 127 tiles 38.1 / 47.3; pairs of two tiles, 8 sequences: 13 tiles 12.2 / 13.1, 42 tiles 21.6 / 24.6, 127 tiles 50.1 / 59.3
 //   (not with 4 query tiles or fewer, where the shared-tile kernel is the only reader of its rows: 6 sequences, 24 tiles: 20.0 / 17.7)
 //   head_dim 64, 32 KV heads: DS 2, 60 rows: 67 tiles 11.9 / 13.4, 80 tiles 13.5 / 13.4; unsliced, 2 sequences: 80 tiles 15.2 / 16.3, 102 tiles 18.4 /
-//   17.9; 8 sequences of 10 rows: 67 tiles 25.2 / 25.7, 80 tiles 29.5 / 29.2; two tiles, 4 sequences: 127 tiles 27.9 / 30.2
+//   17.9; 8 sequences of 10 rows: 67 tiles 25.2 / 25.7, 80 tiles 29.5 / 29.2; two tiles, 4 sequences: 127 tiles 27.9 / 30.2; pairs of two, 8 sequences:
+//   10 tiles 8.2 / 10.1, 24 tiles 12.7 / 13.5, 52 tiles 20.8 / 21.6, 5 sequences: 10 tiles 7.5 / 9.2, 24 tiles 10.9 / 11.7, 52 tiles 17.6 / 18.0, 96 tiles
+//   28.3 / 27.8 (at head_dim 128 equal from 6 sequences on)
 //   head_dim 256, 8 KV heads, groups of 2: DS 4: 55 tiles 20.4 / 21.7, 67 tiles 23.5 / 23.2 (24 rows: 42 tiles 16.5 / 18.3, 55 tiles 20.5 / 19.3); two
 //   tiles: 55 tiles 22.8 / 23.2, 67 tiles 26.5 / 25.3; three: 55 tiles 25.3 / 25.8, 67 tiles 29.1 / 28.8; pairs of one: 55 tiles 30.3 / 30.5, 67 tiles
 //   36.1 / 33.8; pairs of two, 8 sequences: 13 tiles 14.4 / 23.8, 42 tiles 32.2 / 39.4, 127 tiles 80.8 / 82.7
@@ -1430,7 +1432,7 @@ struct Decomposition {
 const Decomposition DECOMPOSITIONS[] = {
     {128, 1, 4, 1, 40, 48}, {128, 1, 2, 1, 72, 88}, {128, 1, 2, 2, 92, 128}, {128, 1, 2, 3, 92, 128}, {128, 1, 1, 2, 120, 160},
     {128, 2, 1, 2, 0, 1 << 30}, {128, 4, 1, 2, 0, 1 << 30},
-    {64, 1, 2, 1, 72, 88}, {64, 1, 1, 1, 80, 96}, {64, 1, 1, 2, 128, 160},
+    {64, 1, 2, 1, 72, 88}, {64, 1, 1, 1, 80, 96}, {64, 1, 1, 2, 128, 160}, {64, 2, 1, 2, 40, 0},
     {256, 1, 4, 1, 0, 52}, {256, 1, 4, 2, 0, 56}, {256, 1, 4, 3, 0, 60}, {256, 2, 2, 1, 0, 56}, {256, 2, 2, 2, 0, 128}, {256, 4, 2, 2, 0, 128},
 };
 
@@ -1804,7 +1806,7 @@ const Variant VARIANTS[] = {
     WAVE_VARIANT(256, 4, 1, 1), WAVE_VARIANT(256, 4, 2, 1), WAVE_VARIANT(256, 4, 4, 1),
     WAVE_VARIANT(128, 8, 2, 2), WAVE_VARIANT(128, 8, 2, 3), WAVE_VARIANT(256, 8, 4, 2), WAVE_VARIANT(256, 8, 4, 3),
     // two query slots: (column slices, query tiles per slot)
-    PAIR_VARIANT(128, 1, 2), PAIR_VARIANT(256, 2, 1), PAIR_VARIANT(256, 2, 2),
+    PAIR_VARIANT(64, 1, 2), PAIR_VARIANT(128, 1, 2), PAIR_VARIANT(256, 2, 1), PAIR_VARIANT(256, 2, 2),
     // four
     QUAD_VARIANT(128, 1, 2), QUAD_VARIANT(256, 2, 2),
 };

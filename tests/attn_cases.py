@@ -63,6 +63,7 @@ VARIANT_CASES = [
     VariantCase("attn_wave_kernel<256,8,4,2>", 3, 16, 8, 256, 17, 4, 333, 0, 0),
     VariantCase("attn_wave_kernel<256,8,4,3>", 4, 16, 8, 256, 33, 5, 410, 0, 0),
     # two query slots
+    VariantCase("attn_pair_kernel<64,1,2>", 5, 32, 32, 64, 60, 6, 410, 0, 0),
     VariantCase("attn_pair_kernel<128,1,2>", 8, 32, 8, 128, 33, 5, 410, 0, 0),
     VariantCase("attn_pair_kernel<256,2,1>", 4, 16, 8, 256, 60, 6, 333, 0, 0),
     VariantCase("attn_pair_kernel<256,2,2>", 6, 16, 8, 256, 60, 6, 301, 0, 0),

@@ -233,6 +233,10 @@ def test_sliced_kernels_at_tile_edges(gu, shape):
     assert np.abs(got - want).max() <= TOL["bf16"]
 
 
+def test_two_slots_of_narrow_heads_at_tile_edges(gu):
+    test_sliced_kernels_at_tile_edges(gu, (6, 32, 32, 64, 49))
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,T", [(16, 32, 8, 128, 33), (12, 32, 8, 128, 60), (12, 16, 8, 256, 60), (9, 16, 8, 256, 49)])
 def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     """The same for four query slots: no, one, fewer and more steps than a key group has stages, a last workgroup with few query tiles; under a
