@@ -770,6 +770,12 @@ struct RowsGeom {
     static constexpr int EARLY = QS == 4 ? (STRIDE - Q_PER * QTILE) / GROUP : NS;  // stages that hold no queries
     static constexpr int Q_OFF = Q_APART ? TILES : QS > 1 ? EARLY * GROUP : GROUP, Q_STRIDE = Q_APART ? QTILE : STRIDE;
     static constexpr int q_at(int i) { return Q_OFF + i / Q_PER * Q_STRIDE + i % Q_PER * QTILE; }
+    // Odd workgroups of a KV head take the tiles of every two steps in the other order: half of what a workgroup reads it then finds in L2, where a CU
+    // pulls twice as fast (138 against 70 GB/s).  That pays while the keys and values which an XCD's heads have in flight stay in L2: 32 heads of 64 in two
+    // slices, 1660 keys 9.9 -> 9.3 us, 2260 keys 12.4 -> 11.5, up to 560 keys equal.  Elsewhere sharing a miss in lock step is better: two tiles unsliced
+    // at 4 sequences 13.3 -> 16.6, pairs at 8 sequences 20.3 -> 21.0; four slices 1 % either way.  The hint undoes it, so these kernels read without
+    // (10.0 with both).
+    static constexpr bool SWAPPED = QS == 1 && D == 64 && DS == 2;
     static constexpr int LOADERS = QS == 4 ? 2 : 1;                                // waves that share the loads of a K tile, and of a V tile
     static constexpr int ML_OFF = TILES + (Q_APART ? QS * QT * QTILE : 0), MASK_OFF = ML_OFF + NW * QT * 32 * 4, PAR_OFF = MASK_OFF + NW * QT * 16 * 8, MEET_OFF = PAR_OFF + 64 * 4;
     static constexpr size_t BYTES = MEET_OFF + NW * 4;
@@ -920,6 +926,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             issue_v(t, at + G::KTILE);
     };
     const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
+    const int odd = G::SWAPPED ? unit & 1 : 0;
+    auto tile = [&](int i) { return kg + KG * (G::SWAPPED && (i | 1) < n_steps ? i ^ odd : i); };   // the key tile of this wave's step i
     const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
     const uint32_t meet = lds0 + G::MEET_OFF;
     if (QS > 1)
@@ -932,10 +940,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
                     issue_slot(t + i * KG, ktile + i * G::GROUP);
             wait_steps(min(n_steps, G::EARLY));   // the queries and parents are there; the first tiles stay in flight
         } else {
-            issue_k(t, ktile);
-            issue_v(t, vtile);
-            if (early && t + KG < t_end) {
-                issue_k(t + KG, ktile2);
+            issue_k(tile(0), ktile);
+            issue_v(tile(0), vtile);
+            if (early && n_steps > 1) {
+                issue_k(tile(1), ktile2);
                 wait_loads<2 * NK + NV>();
             } else {
                 wait_loads<NK + NV>();
@@ -956,8 +964,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     if constexpr (!G::Q_APART)
         __syncthreads();                // every wave has its queries
     if constexpr (QS == 1) {
-        if (!early && t + KG < t_end)
-            issue_k(t + KG, ktile2);
+        if (!early && n_steps > 1)
+            issue_k(tile(1), ktile2);
     } else {
 #pragma unroll
         for (int i = G::EARLY; i < G::NS; i++)
@@ -1142,8 +1150,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         wait_lds();
         slots_meet<QS>(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
     } else {
-        for (; t < t_end; t += KG) {
-            const bool more = t + KG < t_end, more2 = t + 2 * KG < t_end;
+        for (int i = 0; i < n_steps; i++) {
+            const bool more = i + 1 < n_steps, more2 = i + 2 < n_steps;
             if (more)
                 wait_loads<NK + NV>();  // this tile's K (behind it: this tile's V and the next one's K)
             else
@@ -1151,8 +1159,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             scores(ktile, s);
             wait_lds();
             if (more2)
-                issue_k(t + 2 * KG, ktile);
-            softmax(t, s, p);
+                issue_k(tile(i + 2), ktile);
+            softmax(tile(i), s, p);
             if (more2)
                 wait_loads<NK>();       // this tile's V
             else
@@ -1163,7 +1171,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             product(0, va, p);
             wait_lds();
             if (more)
-                issue_v(t + KG, vtile);
+                issue_v(tile(i + 1), vtile);
             product(VB, vb, p);
             const int x = ktile;
             ktile = ktile2;
@@ -1702,8 +1710,9 @@ int ensure_wave_lds()
 {
     static std::atomic<uint64_t> done[2];
     constexpr size_t bytes = WaveGeom<D, NW, DS, QT>::BYTES;
+    constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
     const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, false>), bytes, "attention");
-    return rc || DS == 4 ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, DS != 4>), bytes, "attention");
+    return rc || !hinted ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), bytes, "attention");
 }
 
 template <int D, int NW, int DS, int QT>
@@ -1712,8 +1721,9 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
     if (int rc = ensure_wave_lds<D, NW, DS, QT>())
         return rc;
     const dim3 grid(8 * ceil_div(a.n_qg, QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
-    if (DS != 4 && a.once)
-        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, DS != 4>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
+    constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
+    if (hinted && a.once)
+        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, hinted>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
     else
         hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, false>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
     return check_launch("attn_wave_kernel");

@@ -237,6 +237,19 @@ def test_two_slots_of_narrow_heads_at_tile_edges(gu):
     test_sliced_kernels_at_tile_edges(gu, (6, 32, 32, 64, 49))
 
 
+@pytest.mark.parametrize("kv_len", [256, 257, 288, 511, 512, 513, 768, 1024, 1057])
+def test_swapped_steps(gu, kv_len):
+    """Two slices of heads of 64: odd workgroups swap the tiles of every two steps; one, two, three and four steps, a last step without a partner,
+    the tree and the ragged end in the first tile that a workgroup takes."""
+    cfg = _cfg("swap", "bf16", 1, 32, 32, 64, kv_len - 60, 0, 60, 6, 51)
+    x = di.verify_inputs(cfg)
+    assert gu.verify_plan(x).startswith("attn_wave_kernel<64,8,2,1>"), gu.verify_plan(x)
+    got, lse = gu.run_verify(x)
+    want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+    assert np.abs(lse - want_lse).max() <= 2e-3
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,T", [(16, 32, 8, 128, 33), (12, 32, 8, 128, 60), (12, 16, 8, 256, 60), (9, 16, 8, 256, 49)])
 def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     """The same for four query slots: no, one, fewer and more steps than a key group has stages, a last workgroup with few query tiles; under a
