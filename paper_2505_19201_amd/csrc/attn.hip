@@ -774,7 +774,8 @@ struct RowsGeom {
     // pulls twice as fast (138 against 70 GB/s).  That pays while the keys and values which an XCD's heads have in flight stay in L2: 32 heads of 64 in two
     // slices, 1660 keys 9.9 -> 9.3 us, 2260 keys 12.4 -> 11.5, up to 560 keys equal.  Elsewhere sharing a miss in lock step is better: two tiles unsliced
     // at 4 sequences 13.3 -> 16.6, pairs at 8 sequences 20.3 -> 21.0; four slices 1 % either way.  The hint undoes it, so these kernels read without
-    // (10.0 with both).
+    // (10.0 with both).  With the keys still in the memory-side cache, as between the levels of a draft, the same within 1 % (7.38 / 7.45), the first
+    // level 11.2 -> 10.2.
     static constexpr bool SWAPPED = QS == 1 && D == 64 && DS == 2;
     static constexpr int LOADERS = QS == 4 ? 2 : 1;                                // waves that share the loads of a K tile, and of a V tile
     static constexpr int ML_OFF = TILES + (Q_APART ? QS * QT * QTILE : 0), MASK_OFF = ML_OFF + NW * QT * 32 * 4, PAR_OFF = MASK_OFF + NW * QT * 16 * 8, MEET_OFF = PAR_OFF + 64 * 4;
@@ -1150,8 +1151,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         wait_lds();
         slots_meet<QS>(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
     } else {
+        int now = tile(0), next = tile(1);
         for (int i = 0; i < n_steps; i++) {
             const bool more = i + 1 < n_steps, more2 = i + 2 < n_steps;
+            const int after = tile(i + 2);
             if (more)
                 wait_loads<NK + NV>();  // this tile's K (behind it: this tile's V and the next one's K)
             else
@@ -1159,8 +1162,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             scores(ktile, s);
             wait_lds();
             if (more2)
-                issue_k(tile(i + 2), ktile);
-            softmax(tile(i), s, p);
+                issue_k(after, ktile);
+            softmax(now, s, p);
             if (more2)
                 wait_loads<NK>();       // this tile's V
             else
@@ -1171,8 +1174,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             product(0, va, p);
             wait_lds();
             if (more)
-                issue_v(tile(i + 1), vtile);
+                issue_v(next, vtile);
             product(VB, vb, p);
+            now = next;
+            next = after;
             const int x = ktile;
             ktile = ktile2;
             ktile2 = x;

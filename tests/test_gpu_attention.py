@@ -237,10 +237,10 @@ def test_two_slots_of_narrow_heads_at_tile_edges(gu):
     test_sliced_kernels_at_tile_edges(gu, (6, 32, 32, 64, 49))
 
 
-@pytest.mark.parametrize("kv_len", [256, 257, 288, 511, 512, 513, 768, 1024, 1057])
+@pytest.mark.parametrize("kv_len", [256, 257, 288, 511, 512, 513, 768, 1024, 1057, 1280, 1300, 2048])
 def test_swapped_steps(gu, kv_len):
-    """Two slices of heads of 64: odd workgroups swap the tiles of every two steps; one, two, three and four steps, a last step without a partner,
-    the tree and the ragged end in the first tile that a workgroup takes."""
+    """Two slices of heads of 64: odd workgroups swap the tiles of every two steps; one to eight steps, a last step without a partner, the tree and
+    the ragged end in a tile that is taken ahead of an earlier one."""
     cfg = _cfg("swap", "bf16", 1, 32, 32, 64, kv_len - 60, 0, 60, 6, 51)
     x = di.verify_inputs(cfg)
     assert gu.verify_plan(x).startswith("attn_wave_kernel<64,8,2,1>"), gu.verify_plan(x)
