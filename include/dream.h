@@ -199,7 +199,8 @@ int dream_accept_path_static(const void *logits, int32_t logits_dtype, int32_t b
  *   ae[b]                = mean of row_entropy over heads and rows   ([B] float32)
  * q [B, n_q, Hq, D] and k_cache [B, Hkv, s_max, D] of desc->dtype, n_keys live key rows.  The
  * attention matrix is never stored: one streaming pass keeps a running (max, sum, score-weighted sum)
- * per row, as the log-sum-exp pass of dream_visual_compress does.
+ * per row, as the log-sum-exp pass of dream_visual_compress does.  A row that sees a NaN score has entropy NaN,
+ * and so has the mean of its sequence.
  * ------------------------------------------------------------------------------------------- */
 size_t dream_attention_entropy_workspace(const dream_attn_desc *desc, int32_t n_q);
 int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const int32_t *q_pos, int32_t n_q,

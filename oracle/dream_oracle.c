@@ -424,7 +424,7 @@ int oracle_attention_entropy(const void *q, const int32_t *q_pos, int n_q, const
             double H = 0.0;
             for (int j = 0; j < n_keys; j++) {
                 double a = exp(s[j] - m) / denom;
-                if (a > 0.0)
+                if (a != 0.0) /* (a NaN score makes its row NaN) */
                     H -= a * log(a);
             }
             row_entropy[bh * n_q + r] = H;

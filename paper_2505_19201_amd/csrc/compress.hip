@@ -264,8 +264,9 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
             }
         const bool open = key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f;
         // A column's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
-        // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores
-        auto add_scores = [&](const float(&mx)[CT], float mult) {
+        // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores; masked: some are -inf, the mark of a
+        // key that the row does not see (a NaN is no mark: it makes the row's sums NaN)
+        auto add_scores = [&](const float(&mx)[CT], float mult, auto masked) {
             bool raise = false;
 #pragma unroll
             for (int q = 0; q < CT; q++)
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
                     const float x = acc[q][e >> 2][e & 3], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
                     sum += p;
                     if (ENT)
-                        xsum = fmaf(p, x, xsum);
+                        xsum = fmaf(p, decltype(masked)::value ? fmaxf(x, -3.0e38f) : x, xsum);   // (finite, so that times a probability of 0 it is 0)
                 }
                 l[q] += sum;
                 if (ENT)
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
                     x = fmaxf(x, acc[q][e >> 2][e & 3]);
                 mx[q] = x * a.scale_log2;
             }
-            add_scores(mx, a.scale_log2);
+            add_scores(mx, a.scale_log2, std::false_type{});
         } else {
 #pragma unroll
             for (int q = 0; q < CT; q++) {
@@ -317,11 +318,11 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
                     const float x = (e >> 2) * 16 + (e & 3) <= lim ? acc[q][e >> 2][e & 3] * a.scale_log2 : -INFINITY;
-                    acc[q][e >> 2][e & 3] = ENT ? fmaxf(x, -3.0e38f) : x;    // (finite, so that times a probability of 0 it is 0)
+                    acc[q][e >> 2][e & 3] = x;
                     mx[q] = fmaxf(mx[q], x);
                 }
             }
-            add_scores(mx, 1.0f);
+            add_scores(mx, 1.0f, std::true_type{});
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
@@ -357,9 +358,10 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         const float lw = l[q] * w0 + s_half[slot][q][1][c] * w1;
         const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row[q];
         if (valid[q]) {
-            a.lse2[o] = lw > 0.0f ? mt + log2f(lw) : -INFINITY;
+            const bool some = ENT ? lw != 0.0f : lw > 0.0f;   // (a row with a NaN score: its entropy is NaN, its column sums leave it out)
+            a.lse2[o] = some ? mt + log2f(lw) : -INFINITY;
             if (ENT)
-                a.ent_part[o] = lw > 0.0f ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
+                a.ent_part[o] = some ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
             if (split == 0)                                  // splits that other blocks have and this one does not: both values, since
                 for (int s = unit.n; s < a.ns1; s++) {       // a weight of 0 does not make a NaN left in the workspace harmless
                     a.lse2[o + s * a.lse_split_stride] = -INFINITY;
@@ -386,9 +388,13 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2
         const int64_t o = ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + r;
         if (log2_domain) {
             float M = -INFINITY;
-            for (int s = 0; s < a.ns1; s++)
-                M = fmaxf(M, a.lse2[s * a.lse_split_stride + o]);
-            if (M != -INFINITY) {
+            bool some = false;
+            for (int s = 0; s < a.ns1; s++) {
+                const float L = a.lse2[s * a.lse_split_stride + o];
+                M = fmaxf(M, L);
+                some |= L != -INFINITY;                       // (a NaN, which the maximum drops and the weights below keep)
+            }
+            if (some) {
                 float W = 0.0f, U = 0.0f;
                 for (int s = 0; s < a.ns1; s++) {
                     const float w = __builtin_amdgcn_exp2f(a.lse2[s * a.lse_split_stride + o] - M);
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2
             const float L = a.lse2[o];
             H = L == INFINITY ? 0.0f : L - a.ent_part[o];
         }
-        H = fmaxf(H, 0.0f);   // rounding can leave a tiny negative value for a one-hot row
+        H = H < 0.0f ? 0.0f : H;   // rounding can leave a tiny negative value for a one-hot row; NaN stays
         if (row_entropy)
             row_entropy[((int64_t)b * a.n_q_heads + h) * a.n_q + r] = H;
     }
@@ -659,9 +665,10 @@ __global__ __launch_bounds__(256) void scores_lse_f32_kernel(ScoreArgs a, int D)
             tt += red_t[w] * expf(red_m[w] - ms);
         }
         const int64_t o = ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row;
-        a.lse2[o] = ll > 0.0f ? mm + logf(ll) : INFINITY;   // natural log here
+        const bool some = a.ent_part ? ll != 0.0f : ll > 0.0f;   // (as in the bf16 kernel)
+        a.lse2[o] = some ? mm + logf(ll) : INFINITY;             // natural log here
         if (a.ent_part)
-            a.ent_part[o] = ll > 0.0f ? tt / ll : 0.0f;
+            a.ent_part[o] = some ? tt / ll : 0.0f;
     }
 }
 

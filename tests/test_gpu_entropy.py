@@ -71,3 +71,36 @@ def test_stale_workspace_is_never_read(gu, B, Hq, Hkv, D, n):
     cfg = di.Config("e", "bf16", B, Hq, Hkv, D, Hq * D, n, 0, 4, 2, 1, 2, 100, 1, 35)
     row, ae = _check(gu, cfg)
     assert (row[:, :, 1:] > 0).all() and (ae > 0).all()      # only the first row sees a single key
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,n", [("bf16", 4, 4, 64, 200), ("bf16", 8, 2, 128, 333), ("bf16", 2, 1, 256, 449), ("bf16", 2, 2, 128, 1279), ("f32", 4, 2, 64, 90)])
+def test_a_nan_score_reaches_the_rows_that_see_it(gu, dtype, Hq, Hkv, D, n):
+    """One key of NaN scores, at the edges of the steps and of the key splits: exactly the rows that see it become NaN, whether the key lies in
+    a step with masked keys (the rows' diagonal, the ragged end, explicit positions) or in one without; the others keep every bit.  A row of
+    NaN scores alone is NaN too."""
+    cfg = di.Config("e", dtype, 1, Hq, Hkv, D, Hq * D, n, 0, 4, 2, 1, 2, 100, 1, 36)
+    q, k = di.prefill_q(cfg), di.verify_inputs(cfg).k
+    nan = np.float32(np.nan) if dtype == "f32" else np.uint16(0x7FC0)
+    pos = np.stack([np.random.default_rng(37).permutation(n)]).astype(np.int32)
+    for q_pos in (None, pos):
+        at = np.arange(n) if q_pos is None else q_pos[0]
+        base, _ = gu.run_entropy(dtype, q, k, n, q_pos=q_pos)
+        assert np.isfinite(base).all()
+        for key in sorted({0, 1, 31, 63, 64, n // 2, n - 1}):
+            kn = k.copy()
+            kn[0, Hkv - 1, key, D // 2] = nan
+            row, ae = gu.run_entropy(dtype, q, kn, n, q_pos=q_pos)
+            want, _ = oracle.attention_entropy(q, kn, dtype, q_pos=q_pos) if n < 100 else (None, None)
+            hit = np.zeros(base.shape, dtype=bool)
+            hit[0, Hq - Hq // Hkv:] = at >= key
+            assert np.array_equal(np.isnan(row), hit), (key, np.isnan(row).sum(), hit.sum())
+            assert want is None or np.array_equal(np.isnan(want), hit)
+            assert np.array_equal(row[~hit], base[~hit])
+            assert np.isnan(ae).all() == hit.any()
+        qn = q.copy()
+        rows = sorted({0, 1, n // 3, n - 1})
+        qn[0, rows, 0, 0] = nan
+        row, ae = gu.run_entropy(dtype, qn, k, n, q_pos=q_pos)
+        hit = np.zeros(base.shape, dtype=bool)
+        hit[0, 0, rows] = True
+        assert np.array_equal(np.isnan(row), hit) and np.array_equal(row[~hit], base[~hit]) and np.isnan(ae).all()

@@ -66,3 +66,17 @@ def test_against_a_dense_torch_softmax():
     row, ae = oracle.attention_entropy(q, k, "f32")
     np.testing.assert_allclose(row[0], h.numpy(), atol=1e-12)
     np.testing.assert_allclose(ae[0], float(h.mean()), atol=1e-12)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_nan_score_makes_the_entropy_of_the_rows_that_see_it_nan(dtype):
+    cfg = _cfg(dtype, B=2, Hq=4, Hkv=2, D=64, n=21)
+    q, k = di.prefill_q(cfg), di.verify_inputs(cfg).k
+    row, _ = oracle.attention_entropy(q, k, dtype)
+    k = k.copy()
+    k[0, 1, 7, 5] = np.float32(np.nan) if dtype == "f32" else np.uint16(0x7FC0)
+    got, ae = oracle.attention_entropy(q, k, dtype)
+    hit = np.zeros(row.shape, dtype=bool)
+    hit[0, 2:, 7:] = True                                                # the two query heads of KV head 1, rows at or after the key
+    assert np.isnan(got[hit]).all() and np.array_equal(got[~hit], row[~hit])
+    assert np.isnan(ae[0]) and np.isfinite(ae[1])
