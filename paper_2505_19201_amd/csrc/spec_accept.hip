@@ -22,8 +22,10 @@
 // beforehand, one per node.
 //
 // Why several workgroups: one CU pulls 60 to 75 GB/s, 14 us and more for one pass over two float32 rows of 131072 tokens.
-// Measured, us per call (mean of 4 inputs), one read of all rows with children and a walk in chunks of 8192 tokens / now: 4 sequences x 60 nodes x
-// 131072 float32 logits 65.3 / 50.6, 8 x 60 x 262144 bf16 109.5 / 64.4, 32 x 60 x 32000 float32 91.0 / 53.9, 1 x 60 x 32000 bf16 27.1 / 24.2.
+// Measured, us per call, one read of all rows with children and a walk in chunks of 8192 tokens / now, the same tensors every call (mean of 4 inputs);
+// then 1.2 GB and more of tensors in turn, so that no row is left in a cache: 4 sequences x 60 nodes x 131072 float32 logits 57.7 / 45.9; 64.9 / 46.3,
+// 8 x 60 x 262144 bf16 103 / 67; 111 / 68, 32 x 60 x 32000 float32 93 / 51; 102 / 52, 1 x 60 x 32000 bf16 34.3 / 30.3; 32.7 / 28.4.  The very
+// first call on a new set of tensors, with its page translations to be fetched too: 71.6 / 63.5 at 4 x 60 x 131072.
 #include "common.h"
 #include <algorithm>
 #include <type_traits>
@@ -201,7 +203,7 @@ __device__ __forceinline__ void merge_row_stats(const float *cm, const float *cs
 struct WalkArgs {
     const void *tlogits, *dlogits;
     int n_tree, vocab, n_chunks;
-    int seg_chunks, n_seg;         // a row is n_seg <= MAX_SEG segments of seg_chunks chunks (one chunk up to 524288 tokens)
+    int seg_chunks, n_seg;         // a row is n_seg <= MAX_SEG segments of seg_chunks chunks (one chunk up to 1048576 tokens)
     bool vec;
     bool lazy;                     // statistics of the roots only; the walk works out those of the nodes it comes to
     const int32_t *token, *parent;
@@ -851,9 +853,15 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
                      ((size_t)vocab * esz) % 16 == 0;
     const float inv_temp = 1.0f / temperature;
     hipStream_t st = as_stream(stream);
-    // The statistics of all nodes beforehand cost a read of about half of all rows, those of the visited ones an exchange each.  us, all / visited: 24 MB of
-    // logits 24.7 / 38.6, 31 MB 37.8 / 38.8, 63 MB equal within 1 % (37.5 and 34.3); beyond that the figures at the head of this file.
-    const bool lazy = (int64_t)2 * batch * n_tree * vocab * esz >= 60000000;
+    // The statistics of all nodes beforehand cost a read of about half of all rows, those of the visited ones an exchange each, which also brings the rows
+    // that the rejections there need.  A small tree has as many levels to visit for its bytes as a large one and fewer rejections on the way, so
+    // the line is one of bytes times nodes, with a floor for large trees.  us, all / visited, the same tensors every call; then several sets in turn, 1 GB and
+    // more: 8 nodes, 134 MB of logits 37 / 50; 42 / 55, 268 MB 60 / 65; 67 / 70; 16 nodes, 134 MB 35 / 43; 38 / 44, 201 MB 48 / 48; 55 / 49, 268 MB
+    // 52 / 46; 59 / 50; 24 nodes, 101 MB 33 / 41; 37 / 43, 151 MB 39 / 39; 42 / 41, 201 MB 43 / 43; 47 / 46; 32 nodes, 67 MB 33 / 36; 35 / 37, 134 MB 43 / 42;
+    // 45 / 43; 48 nodes, 50 MB 27 / 37; 29 / 34, 75 MB 36 / 36; 39 / 39, 101 MB 38 / 38; 43 / 39; 64 nodes, 50 MB 42 / 44; 37 / 41, 67 MB 29 / 29; 31 / 31,
+    // 134 MB 48 / 44; 53 / 48.
+    const int64_t logit_bytes = (int64_t)2 * batch * n_tree * vocab * esz;
+    const bool lazy = logit_bytes >= 60000000 && logit_bytes * n_tree >= 3600000000ll;
     const int n_nodes = lazy ? 1 : n_tree;
     const dim3 sgrid(n_chunks, batch * n_nodes, 2);
     const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, lazy, token, parent, u_accept, u_bonus, max_depth,

@@ -71,7 +71,31 @@ def _draft_children(parent, dl_f64, g):
     return token
 
 
-def _case(gu, B, T, depth, V, dtype, seed, spread=2.0, noise=0.7, temperature=1.0, min_clear=0.5, min_compared=0):
+def _formed_by_the_walk(B, T, V, dtype):
+    """Whether the statistics of the nodes' rows are formed by the walk (the line of spec_accept.hip) and not beforehand."""
+    nbytes = 2 * B * T * V * (4 if dtype == "f32" else 2)
+    return nbytes >= 60000000 and nbytes * T >= 3600000000
+
+
+def _branches(parent, detail, clear):
+    """What happened at the nodes the compared sequences came to: accepted as which child, or all of how many rejected."""
+    seen = set()
+    for b in np.flatnonzero(clear):
+        by_node = {}
+        for node, ratio, u in detail[b]["tests"]:
+            by_node.setdefault(int(parent[b, node]), []).append(u < min(1.0, ratio))
+        for outcomes in by_node.values():
+            if outcomes[-1]:
+                seen.add(("accepted as child number", min(len(outcomes), 3)))
+            else:
+                seen.add(("all rejected, children", min(len(outcomes), 3)))
+        if not by_node or all(o[-1] for o in by_node.values()):
+            seen.add(("draw at a node without children",))
+    return seen
+
+
+def _case(gu, B, T, depth, V, dtype, seed, spread=2.0, noise=0.7, temperature=1.0, min_clear=0.5, min_compared=0, limit=None, never=0.0):
+    """limit: depth limit of the call, below the tree's depth.  never: share of the nodes whose random number lets no test pass."""
     g = di.rng(seed, 700)
     parent = np.stack([di.random_tree(T, depth, seed, b) for b in range(B)]) if T > 1 else np.full((B, 1), -1, dtype=np.int32)
     t32 = di.normal((B, T, V), "f32", seed, di.STREAM_LOGITS) * np.float32(spread)
@@ -82,6 +106,9 @@ def _case(gu, B, T, depth, V, dtype, seed, spread=2.0, noise=0.7, temperature=1.
     token = _draft_children(parent, dl64 / temperature, g)
     ua = g.uniform(size=(B, T)).astype(np.float32)
     ub = g.uniform(size=B).astype(np.float32)
+    if never:
+        ua[g.random(size=(B, T)) < never] = 2.0
+    depth = depth if limit is None else limit
     want_len, want_path, want_bonus, detail = oracle.spec_accept(tl64, dl64, token, parent, ua.astype(np.float64), ub.astype(np.float64),
                                                                 depth, inv_temperature=1.0 / temperature)
     clear = np.array([_clear(d) for d in detail])
@@ -163,18 +190,7 @@ def test_every_branch_of_the_walk_is_exercised(gu):
     three different ways; the oracle's record of the tests says which of these each compared sequence took."""
     _case(gu, 96, 33, 6, 4000, "bf16", 950, noise=1.0)
     parent, detail, clear = _case.last
-    seen = set()
-    for b in np.flatnonzero(clear):
-        by_node = {}
-        for node, ratio, u in detail[b]["tests"]:
-            by_node.setdefault(int(parent[b, node]), []).append(u < min(1.0, ratio))
-        for outcomes in by_node.values():
-            if outcomes[-1]:
-                seen.add(("accepted as child number", min(len(outcomes), 3)))
-            else:
-                seen.add(("all rejected, children", min(len(outcomes), 3)))
-        if not by_node or all(o[-1] for o in by_node.values()):
-            seen.add(("draw at a node without children",))
+    seen = _branches(parent, detail, clear)
     want = {("accepted as child number", 1), ("accepted as child number", 2), ("accepted as child number", 3),
             ("all rejected, children", 1), ("all rejected, children", 2), ("all rejected, children", 3),
             ("draw at a node without children",)}
@@ -184,7 +200,7 @@ def test_every_branch_of_the_walk_is_exercised(gu):
 @pytest.mark.parametrize("V", [8192, 8193, 24577, 65536, 540001])
 @pytest.mark.parametrize("polls", [0, -1])
 def test_workgroups_of_a_sequence(gu, V, polls):
-    """Rows of one, two, several and more than 64 chunks of 8192 tokens, summed by several workgroups that exchange their
+    """Rows of 2, 3, 7, 16 and (of 16384) 33 chunks of 4096 tokens, summed by several workgroups that exchange their
     sums, and (polls < 0: nobody waits) by workgroup 0 in the others' place."""
     import paper_2505_19201_amd as dream
     dream.dream_set_accept_spin(polls)
@@ -198,13 +214,67 @@ def test_workgroups_of_a_sequence(gu, V, polls):
 @pytest.mark.parametrize("polls", [0, -1])
 def test_shares_of_a_workgroup(gu, B, T, V, polls):
     """Two and four times as many logits in a workgroup's registers, more than they hold, one workgroup per sequence; with the statistics of all
-    nodes formed beforehand (below 60 MB of logits) and by the walk."""
+    nodes formed beforehand (test_statistics_formed_by_the_walk has them formed by the walk)."""
+    assert not _formed_by_the_walk(B, T, V, "f32")
     import paper_2505_19201_amd as dream
     dream.dream_set_accept_spin(polls)
     try:
         _case(gu, B, T, 3, V, "f32", 1970 + V, noise=1.0, min_clear=0.0)
     finally:
         dream.dream_set_accept_spin(0)
+
+
+@pytest.mark.parametrize("polls", [0, -1])
+@pytest.mark.parametrize("B,T,V,dtype,temperature", [
+    (4, 60, 40000, "f32", 1.0), (8, 60, 40003, "bf16", 0.7),                # a chunk of 4096 logits a workgroup
+    (16, 33, 70000, "f32", 0.7), (32, 24, 80000, "bf16", 1.0),              # of 8192, of 16384
+    (64, 16, 70000, "bf16", 1.0), (260, 16, 17001, "bf16", 1.0),             # more segments than workgroups; one workgroup, no exchange
+    (2, 21, 1060001, "f32", 1.0)])                                          # two chunks a segment
+def test_statistics_formed_by_the_walk(gu, B, T, V, dtype, temperature, polls):
+    """Many logits: the walk works out the statistics of a node's rows when it comes to the node.  Every share of a workgroup, both types, with the
+    exchange and without; then a depth limit inside the tree, so that walks end at nodes with children and draw from the masses of that
+    round."""
+    import paper_2505_19201_amd as dream
+    assert _formed_by_the_walk(B, T, V, dtype)
+    dream.dream_set_accept_spin(polls)
+    try:
+        if polls == 0:
+            _case(gu, B, T, 5, V, dtype, 2970 + V, noise=1.0, temperature=temperature, min_clear=0.0)
+        alen, clear = _case(gu, B, T, 5, V, dtype, 2971 + V, noise=0.5, temperature=temperature, min_clear=0.0, limit=2)
+        assert alen.max() == 2
+    finally:
+        dream.dream_set_accept_spin(0)
+
+
+@pytest.mark.parametrize("polls", [0, -1])
+def test_every_branch_with_statistics_formed_by_the_walk(gu, polls):
+    """Accepted as first, second and third child, all of one, two and three children rejected, a walk that ends at a leaf."""
+    import paper_2505_19201_amd as dream
+    B, T, V = 96, 33, 9000
+    assert _formed_by_the_walk(B, T, V, "f32")
+    dream.dream_set_accept_spin(polls)
+    try:
+        _case(gu, B, T, 6, V, "f32", 953, noise=1.0)
+    finally:
+        dream.dream_set_accept_spin(0)
+    assert _branches(*_case.last) >= {(what, n) for what in ("accepted as child number", "all rejected, children") for n in (1, 2, 3)} | \
+        {("draw at a node without children",)}
+
+
+@pytest.mark.parametrize("polls", [0, -1])
+@pytest.mark.parametrize("B,T,V,dtype", [(6, 33, 4000, "f32"), (8, 60, 20000, "f32"), (16, 33, 70000, "bf16")])
+def test_a_draft_equal_to_the_target(gu, B, T, V, dtype, polls):
+    """Equal rows leave no residual behind a rejection (which the random numbers force): the target stays as it is and the rejected token leaves the
+    draft.  The smallest with the statistics formed beforehand, the others with those of the walk."""
+    import paper_2505_19201_amd as dream
+    assert _formed_by_the_walk(B, T, V, dtype) == (V > 4000)
+    dream.dream_set_accept_spin(polls)
+    try:
+        _case(gu, B, T, 5, V, dtype, 3970 + V, noise=0.0, never=0.5, min_clear=0.25)
+    finally:
+        dream.dream_set_accept_spin(0)
+    parent, detail, clear = _case.last
+    assert any(u > 1.0 for b in np.flatnonzero(clear) for _, _, u in detail[b]["tests"])
 
 
 @pytest.mark.parametrize("V", [1000, 24577, 65536])
