@@ -1469,6 +1469,8 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
         while (p->wave_ds < 4 && base * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
             p->wave_ds *= 2;
         p->wave_qt = base * n_qtiles > 256 ? 2 : 1;
+        if (base * ceil_div(rows, p->wave_qt) * p->wave_ds > 256)
+            return false;       // (3 tiles a head are two workgroups: 20 sequences of 8 KV heads, head_dim 128: 320 workgroups 48 us, the 160 of the plan without 32, 64 key tiles)
     } else {
         const Decomposition *use = nullptr;
         for (const Decomposition &c : DECOMPOSITIONS)
@@ -1490,7 +1492,10 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     if (p->slots == 1 && (d->head_dim == 256 ? p->wave_qt == 1 : p->wave_ds == 1 && tiles <= 5))
         p->wave_nw = 4;
     p->qg = 1;
-    p->n_qg = p->wave_qt == 1 && p->slots == 1 ? n_qtiles : rows;    // (a tile that the rows do not need ends at once)
+    // The grid has a workgroup for every tile that the heads would need one after the other while each has a CU of its own: those beyond the rows
+    // end at once and cost nothing there (60 rows of 4 heads, 8 KV heads, 1340 keys: 256 workgroups 9.65 us, the 240 with rows 9.6).  With more of
+    // them than CUs, two that work would share one while others idle (3 sequences of 17 rows, 384 workgroups and 240: 23.7 / 12.6 us at 1417 keys, 35.5 / 18.5 at 2417).
+    p->n_qg = p->wave_qt == 1 && p->slots == 1 && base * n_qtiles * p->wave_ds <= 256 ? n_qtiles : rows;
     p->n_splits = 1;
     p->n_groups = p->n_streams = (int)base;
     p->grid = 0;

@@ -311,6 +311,20 @@ def test_every_plan_names_a_built_variant(lib):
     assert len(seen) >= 25, sorted(built - seen)   # the sweep reaches most of the table without any override
 
 
+def test_few_stream_kernels_launch_at_most_one_workgroup_per_cu(lib):
+    """The kernels without a key split are chosen for shapes whose workgroups all run at once; a second one on a CU would double the time."""
+    seen = set()
+    for D in (64, 128, 256):
+        for hkv, g in ((8, 1), (8, 2), (8, 3), (8, 4), (16, 2), (32, 1), (5, 4)):
+            for B in list(range(1, 25)) + [32, 40]:
+                for n_q in (1, 8, 10, 12, 16, 17, 24, 33, 48, 49, 64):
+                    plan = dream.dream_attn_plan_describe(dream.attn_desc(B, hkv * g, hkv, D, dream.BF16, 400), n_q, 400)
+                    if re.match("attn_(wave|pair|quad)_kernel", plan):
+                        assert int(re.search(r"workgroups=(\d+)", plan).group(1)) <= 256, (D, hkv, g, B, n_q, plan)
+                        seen.add(plan.split(" ")[0])
+    assert len(seen) >= 15
+
+
 def _signature(name):
     """Parameters of an entry point as include/dream.h declares them: [(type, name)]."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
