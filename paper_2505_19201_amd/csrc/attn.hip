@@ -1420,34 +1420,40 @@ struct Plan {
 // The kernels that cut the work into query tiles and column slices only (attn_wave_kernel, attn_pair_kernel, attn_quad_kernel): one launch, no key split.
 // What such a launch costs is what its busiest CU pulls, K and 1 / DS of V per workgroup, as long as all workgroups run at once; so
 // the decompositions below are tried from the one that spreads the bytes thinnest, and the first with at most one workgroup per CU is
-// taken, up to the number of 32-key tiles at which key splits with their merge launch (or the shared-tile kernel) catch up.  Measured
-// in us, this kernel / the plan without it, caches larger than any cache level:
-//   head_dim 128, 32 KV heads: DS 4, 10 rows, 1 sequence: 41 tiles 12.3 / 12.5, 55 tiles 15.1 / 13.5; DS 2, 60 rows: 24 tiles 8.9 / 16, 67 tiles
-//   17.5 / 17.8, 80 tiles 20.1 / 19.1; two tiles in 2 slices, 2 sequences: 24 tiles 10.9 / 17, 80 tiles 23.6 / 24.7, 102 tiles 29.2 / 28.0; two
-//   tiles unsliced, 4 sequences: 24 tiles 15.2 / 16.1, 102 tiles 42.2 / 43.5, 127 tiles 51.2 / 51.0
-//   8 KV heads, groups of 4: DS 4: 42 tiles 9.2 / 12.2, 55 tiles 13.4 / 12.6; DS 2: 80 tiles 18.2 / 18.6, 102 tiles 21.7 / 20.1; two tiles in 2 slices:
-//   102 tiles 23.8 / 26.3, 127 tiles 29.0 / 29.2; three tiles in 2 slices, 8 sequences of 24 rows, 41 tiles: 17.0 / 23; two tiles
-//   unsliced, 4 sequences: 127 tiles 38.1 / 47.3; pairs of two tiles, 8 sequences: 13 tiles 12.2 / 13.1, 42 tiles 21.6 / 24.6, 127 tiles 50.1 / 59.3
-//   (not with 4 query tiles or fewer, where the shared-tile kernel is the only reader of its rows: 6 sequences, 24 tiles: 20.0 / 17.7)
-//   head_dim 64, 32 KV heads: DS 2, 60 rows: 67 tiles 11.9 / 13.4, 80 tiles 13.5 / 13.4; unsliced, 2 sequences: 80 tiles 15.2 / 16.3, 102 tiles 18.4 /
-//   17.9; 8 sequences of 10 rows: 67 tiles 25.2 / 25.7, 80 tiles 29.5 / 29.2; two tiles, 4 sequences: 127 tiles 27.9 / 30.2; pairs of two, 8 sequences:
-//   10 tiles 8.2 / 10.1, 24 tiles 12.7 / 13.5, 52 tiles 20.8 / 21.6, 5 sequences: 10 tiles 7.5 / 9.2, 24 tiles 10.9 / 11.7, 52 tiles 17.6 / 18.0, 96 tiles
-//   28.3 / 27.8 (at head_dim 128 equal from 6 sequences on)
-//   head_dim 256, 8 KV heads, groups of 2: DS 4: 55 tiles 20.4 / 21.7, 67 tiles 23.5 / 23.2 (24 rows: 42 tiles 16.5 / 18.3, 55 tiles 20.5 / 19.3); two
-//   tiles: 55 tiles 22.8 / 23.2, 67 tiles 26.5 / 25.3; three: 55 tiles 25.3 / 25.8, 67 tiles 29.1 / 28.8; pairs of one: 55 tiles 30.3 / 30.5, 67 tiles
-//   36.1 / 33.8; pairs of two, 8 sequences: 13 tiles 14.4 / 23.8, 42 tiles 32.2 / 39.4, 127 tiles 80.8 / 82.7
-//   four slots of two tiles, 16 sequences (9 to 12 within 3 us of that): head_dim 128, 8 tiles 14.5 / 14.2, 21 tiles 21.2 / 24.5, 42 tiles 33.5 / 40.6, 80 tiles
-//   54.9 / 70.9, 127 tiles 82.7 / 109.2; head_dim 256, 8 tiles 18.1 / 18.0, 42 tiles 51.7 / 54.5, 80 tiles 90.1 / 93.9, 127 tiles 138.1 / 145.9
+// taken, while the range is no longer than longest_range() says.
 struct Decomposition {
     int d, slots, ds, qt;
-    int tiles_1, tiles_n;    // longest range in 32-key tiles with one query head per KV head, with several (0: not used)
+    int tiles_1, tiles_n;    // line against five splits or more with every CU at work, in 32-key tiles, with one query head per KV head and with several (0: not used)
 };
 const Decomposition DECOMPOSITIONS[] = {
-    {128, 1, 4, 1, 40, 48}, {128, 1, 2, 1, 72, 88}, {128, 1, 2, 2, 92, 128}, {128, 1, 2, 3, 92, 128}, {128, 1, 1, 2, 120, 160},
-    {128, 2, 1, 2, 0, 1 << 30}, {128, 4, 1, 2, 0, 1 << 30},
-    {64, 1, 2, 1, 72, 88}, {64, 1, 1, 1, 80, 96}, {64, 1, 1, 2, 128, 160}, {64, 2, 1, 2, 40, 0},
-    {256, 1, 4, 1, 0, 52}, {256, 1, 4, 2, 0, 56}, {256, 1, 4, 3, 0, 60}, {256, 2, 2, 1, 0, 56}, {256, 2, 2, 2, 0, 128}, {256, 4, 2, 2, 0, 128},
+    {128, 1, 4, 1, 52, 72}, {128, 1, 2, 1, 64, 84}, {128, 1, 2, 2, 72, 106}, {128, 1, 2, 3, 60, 76}, {128, 1, 1, 2, 48, 76}, {128, 2, 1, 2, 0, 76}, {128, 4, 1, 2, 0, 76},
+    {64, 1, 2, 1, 90, 108}, {64, 1, 1, 1, 84, 108}, {64, 1, 1, 2, 84, 108}, {64, 2, 1, 2, 84, 0},
+    {256, 1, 4, 1, 0, 58}, {256, 1, 4, 2, 0, 60}, {256, 1, 4, 3, 0, 70}, {256, 2, 2, 1, 0, 50}, {256, 2, 2, 2, 0, 52}, {256, 4, 2, 2, 0, 52},
 };
+
+// The number of 32-key tiles up to which one launch without key splits beats what the general plan makes of the shape: key splits with a merge launch,
+// which cost more to start and less per tile, while few sequences leave CUs idle, or one workgroup for all rows of a KV head.  `line`: where the two meet
+// against five splits or more with every CU at work; earlier when fewer CUs pull, later against fewer splits.  Against two or none the single
+// launch is ahead at every length measured, up to 128 tiles.
+// The lines are those of least regret over 16 groupings of heads, 1 to 32 sequences, 8 to 64 rows and 7 to 104 tiles, the caches of 24 to 48 layers in turn:
+// against three splits or more the rule takes 0.2 % more than the better of both on average (one line per decomposition, whatever it replaces: 0.7 %).  The worst
+// are single sequences whose caches of all layers fit the memory-side cache, where the single launch is ahead for longer (8 heads, 64 rows, 48 tiles 9.2 / 12.6).  us, single launch /
+// general plan, last length below the line and first above:
+//   head_dim 128: 32 heads, 1 sequence, 8 rows, 128 workgroups, 40 tiles 12.0 / 12.1, 44 tiles 12.6 / 12.5; 2 sequences, against four splits, 60 tiles
+//   17.4 / 18.0, 64 tiles 19.4 / 19.5; 33 rows in 2 slices, 56 tiles 15.2 / 15.6, 60 tiles 16.1 / 15.7; 64 rows 64 tiles 17.5 / 17.7, 70 tiles 17.8 / 17.9; 8 KV heads, groups
+//   of 4, 64 rows, 78 tiles 17.8 / 18.2, 90 tiles 19.9 / 19.3; against two splits, 4 sequences of 8 rows, 104 tiles 38.0 / 41.0
+//   head_dim 64: 32 heads, 1 sequence, 8 rows, 64 workgroups, 60 tiles 10.4 / 10.7, 64 tiles 11.4 / 10.7; 64 rows, 256 workgroups, 90 tiles 13.5 / 13.9, 104 tiles
+//   15.1 / 14.8; 3 sequences of 8 rows, against two splits, 104 tiles 19.8 / 22.6
+//   head_dim 256, 8 KV heads, groups of 2: 64 rows 56 tiles 20.2 / 21.7, 64 tiles 22.5 / 21.4; 2 sequences of 8 rows, 64 workgroups, 36 tiles 16.0 / 16.1, 44 tiles 18.5 / 17.1
+int64_t longest_range(const dream_attn_desc *d, int n_qtiles, int64_t workgroups, int slots, int line)
+{
+    const int G = d->n_q_heads / d->n_kv_heads;
+    const int64_t splits = 256 / ((int64_t)d->batch * d->n_kv_heads * ceil_div(n_qtiles, 4));
+    if (splits < 3)
+        return d->head_dim == 256 ? (G == 1 ? 96 : 128) : slots > 1 && G > 1 ? 1 << 30 : G == 1 ? 120 : 160;
+    const int64_t tiles = line * (384 + workgroups) / 640;
+    return splits == 4 ? tiles * 6 / 5 : splits == 3 ? tiles * 8 / 5 : tiles;
+}
 
 bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
 {
@@ -1461,25 +1467,41 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
         base * n_qtiles < 32 || d->s_max * d->head_dim >= (1ll << 30))
         return false;
     if (G == 3 || (G == 1 && d->head_dim == 256)) {
-        // not measured with the decompositions above: one query tile a workgroup in as many column slices as leave one workgroup per CU, or
-        // two tiles, up to the lengths at which key splits won against a slower kernel of this kind
-        if (base * n_qtiles > (d->head_dim <= 128 ? 512 : 256) || (int64_t)tiles * d->head_dim > (G > 1 ? 12288 : 8192))
+        // one query tile a workgroup in as many column slices as leave one workgroup per CU, or two tiles
+        if (base * n_qtiles > (d->head_dim <= 128 ? 512 : 256))
             return false;
         p->wave_ds = 1;
         while (p->wave_ds < 4 && base * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
             p->wave_ds *= 2;
         p->wave_qt = base * n_qtiles > 256 ? 2 : 1;
-        if (base * ceil_div(rows, p->wave_qt) * p->wave_ds > 256)
-            return false;       // (3 tiles a head are two workgroups: 20 sequences of 8 KV heads, head_dim 128: 320 workgroups 48 us, the 160 of the plan without 32, 64 key tiles)
+        // (3 tiles a head are two workgroups: 20 sequences of 8 KV heads, head_dim 128, 64 key tiles: 320 workgroups 48 us, the 160 of the plan without 32)
+        const int64_t workgroups = base * ceil_div(rows, p->wave_qt) * p->wave_ds;
+        if (workgroups > 256)
+            return false;
+        // us on both sides of a line, 8 KV heads in groups of 3: head_dim 64, 2 sequences, 96 tiles 14.9 / 15.6, 128 tiles 19.2 / 17.5; head_dim 128, unsliced, 48 tiles 15.6 / 17.1,
+        // 64 tiles 19.7 / 19.9; head_dim 256, 26 tiles 18.2 / 22.2, 40 tiles 26.8 / 25.5; one head of 256, 2 slices, 48 tiles 23.2 / 24.4, 56 tiles 26.3 / 25.2
+        static const int LINES[3][3] = {{108, 108, 108}, {64, 74, 76}, {36, 50, 54}};    // by head_dim; unsliced, 2 slices, 4
+        if (tiles > longest_range(d, n_qtiles, workgroups, 1, LINES[d->head_dim / 128][p->wave_ds / 2]))
+            return false;
     } else {
         const Decomposition *use = nullptr;
         for (const Decomposition &c : DECOMPOSITIONS)
             if (!use && c.d == d->head_dim && base * ceil_div(rows, c.slots * c.qt) * c.ds <= 256)
                 use = &c;
-        if (!use || tiles > (G == 1 ? use->tiles_1 : use->tiles_n))
+        const int line = !use ? 0 : G == 1 ? use->tiles_1 : use->tiles_n;
+        if (!line)
             return false;
-        // (up to 96 KV heads with 4 tiles each change to key groups and splits where they always have: measured here at 24 key tiles only)
-        if (use->d == 128 && use->ds == 1 && use->slots == 1 && G == 1 && base <= 96 && tiles > 48)
+        const int units = ceil_div(rows, use->slots * use->qt);
+        if (tiles > longest_range(d, n_qtiles, base * units * use->ds, use->slots, line))
+            return false;
+        // Three exceptions.  Four slots for all rows of a KV head start slower than the 8 waves of the shared-tile kernel, which do the same, the more so
+        // the more CUs are at work: 18 sequences of 17 rows 18 tiles 17.9 / 18.0, 24 sequences
+        // 8 tiles 13.2 / 11.5 us, 16 tiles 17.9 / 17.1, 24 tiles 22.2 / 22.2, 32 tiles 26.7 / 28.0, 32 sequences 30 tiles 28.4 / 28.5.  Up to 96 KV heads with 4 tiles each, and pairs of heads of 64,
+        // change earlier than they would have to (3 sequences, 64 rows, 52 tiles 22.3 / 26.4, 64 tiles 25.8 / 30.2; 5 sequences, 64 rows, 40 tiles 14.5 / 15.1, 52 tiles 17.4 / 17.6, 8
+        // sequences 52 tiles 20.7 / 23.5).
+        if (use->slots == 4 && use->d == 128 && units == 1 && tiles < 8 + base / 12)
+            return false;
+        if (G == 1 && use->ds == 1 && use->qt == 2 && (use->d == 128 ? base <= 96 && tiles > 48 : use->slots == 2 && tiles > 40))
             return false;
         p->slots = use->slots;
         p->wave_ds = use->ds;

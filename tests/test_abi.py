@@ -474,6 +474,28 @@ def test_launch_plans_on_both_sides_of_a_length_line(lib, B, hq, hkv, D, n_tree,
     assert dream.dream_attn_plan_describe(desc, n_tree, line * 32 + 1).startswith(long)
 
 
+@pytest.mark.parametrize("B,hq,hkv,D,n_q,line,upto,beyond", [
+    # one launch without key splits against eight splits: fewer workgroups, an earlier line
+    (1, 32, 32, 128, 8, 41, "attn_wave_kernel<128,8,4,1>", "attn_bf16_kernel<128,1,1,2,4,1,1> workgroups=256 splits=8"),
+    (1, 32, 32, 64, 8, 63, "attn_wave_kernel<64,8,2,1>", "attn_bf16_kernel<64,1,2,2,4,1,1> workgroups=256 splits=8"),
+    (1, 32, 32, 64, 64, 90, "attn_wave_kernel<64,8,2,1>", "attn_bf16_kernel<64,1,2,2,4,1,1> workgroups=256 splits=8"),
+    (1, 32, 8, 128, 64, 84, "attn_wave_kernel<128,8,2,1>", "attn_bf16_kernel<128,1,1,2> workgroups=256 splits=8"),
+    (2, 16, 8, 256, 8, 40, "attn_wave_kernel<256,4,4,1>", "attn_bf16_kernel<256,1,1,2,4,1,1> workgroups=128 splits=8"),
+    (2, 24, 8, 128, 33, 49, "attn_wave_kernel<128,8,1,1>", "attn_bf16_kernel<128,1,1,2> workgroups=240 splits=5"),
+    # against four, three and two
+    (2, 32, 32, 128, 8, 62, "attn_wave_kernel<128,8,4,1>", "attn_bf16_kernel<128,1,1,2,4,1,1> workgroups=256 splits=4"),
+    (3, 24, 8, 128, 33, 88, "attn_wave_kernel<128,8,1,1>", "attn_bf16_kernel<128,1,1,2> workgroups=216 splits=3"),
+    (3, 32, 32, 64, 8, 120, "attn_wave_kernel<64,8,2,1>", "attn_bf16_kernel<64,1,2,2,4,1,1> workgroups=192 splits=2"),
+    # four slots for all rows of a KV head, from a length on
+    (24, 32, 8, 128, 17, 23, "attn_bf16_kernel<128,1,1,2,8>", "attn_quad_kernel<128,1,2>"),
+])
+def test_single_launches_on_both_sides_of_their_line(lib, B, hq, hkv, D, n_q, line, upto, beyond):
+    """The lengths at which the kernels without key splits begin and end, in key tiles; each depends on the splits replaced and on the workgroups."""
+    desc = dream.attn_desc(B, hq, hkv, D, dream.BF16, 4200)
+    plans = [dream.dream_attn_plan_describe(desc, n_q, n) for n in (line * 32, line * 32 + 1)]
+    assert plans[0].startswith(upto) and plans[1].startswith(beyond), plans
+
+
 def test_a_workspace_for_the_longest_range_fits_every_shorter_call(lib):
     """Programs query once, for the longest key range; the plans of shorter ranges (other splits, other kernels) never need more."""
     for D in (64, 128, 256):

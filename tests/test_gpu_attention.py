@@ -250,6 +250,23 @@ def test_swapped_steps(gu, kv_len):
     assert np.abs(lse - want_lse).max() <= 2e-3
 
 
+@pytest.mark.parametrize("kv_len", [300, 513, 1024, 1300])
+@pytest.mark.parametrize("B,T", [(2, 17), (3, 9)])
+def test_swapped_steps_of_ragged_sequences_under_a_mask(gu, B, T, kv_len):
+    """The same for sequences of different lengths, one of them without a prefix, and under an explicit mask: several pairs of steps, with and without
+    a last one that has no partner."""
+    cfg = _cfg("swap", "bf16", B, 32, 32, 64, kv_len - T, 0, T, 4, 53)
+    x = di.verify_inputs(cfg, prefix_len=[kv_len - T, (kv_len - T) * 2 // 3, 0][:B])
+    assert gu.verify_plan(x).startswith("attn_wave_kernel<64,8,2,1>"), gu.verify_plan(x)
+    got, lse = gu.run_verify(x)
+    want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+    assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3
+    star = di.star_tree(T)
+    got, _ = gu.run_verify(x, tree_mask=np.stack([di.ancestor_mask_bits(star, True)[:, 0]] * B))
+    want, _ = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, np.stack([star] * B), True)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,T", [(16, 32, 8, 128, 33), (12, 32, 8, 128, 60), (12, 16, 8, 256, 60), (9, 16, 8, 256, 49)])
 def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     """The same for four query slots: no, one, fewer and more steps than a key group has stages, a last workgroup with few query tiles; under a
@@ -272,6 +289,24 @@ def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     got, qsel = gu.run_xattn(x, rows, rows)
     want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
     assert np.abs(got - want).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("shape,kv_len", [((2, 32, 32, 128, 9), 1984), ((1, 32, 32, 64, 9), 2016), ((1, 32, 8, 128, 64), 2688), ((2, 24, 8, 128, 33), 1568), ((8, 16, 8, 256, 9), 2304),
+                                          ((3, 32, 32, 64, 9), 3840), ((24, 32, 8, 128, 17), 736), ((24, 32, 8, 128, 17), 737)])
+def test_the_longest_ranges_of_single_launches(gu, shape, kv_len):
+    """Ragged sequences at the lengths up to which a shape takes one launch without key splits (and from which it takes four slots)."""
+    B, Hq, Hkv, D, T = shape
+    cfg = _cfg("long", "bf16", B, Hq, Hkv, D, kv_len - T, 0, T, min(5, T - 1), 52)
+    x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) // (1 + b % 3) for b in range(B)])
+    plan = gu.verify_plan(x)
+    assert "splits=1 " in plan and (kv_len == 736 or not plan.startswith("attn_bf16")), plan
+    got, lse = gu.run_verify(x)
+    oracle.set_threads(16)
+    try:
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+    finally:
+        oracle.set_threads(1)
+    assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3
 
 
 def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
