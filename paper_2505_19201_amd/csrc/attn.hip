@@ -1933,12 +1933,13 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     a.tiles_per_head = p.tiles_per_head; a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
     auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
     a.nq_magic = magic(n_q);
-    // Verification reads every layer's caches once a round; from 8 MB a layer on the 24 to 48 layers of a model displace each other in the 256 MB
-    // memory-side cache anyway, and the hint keeps them from displacing the rows other workgroups still read (us with plain loads / with the hint: 32 heads
-    // of head_dim 128 and 764 keys 8.97 / 8.73, 4 sequences of them 15.2 / 13.2; 8 sequences of 10 rows, head_dim 64, 20.1 / 17.8; but 5.5
-    // MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2:
-    // never).  A draft's one cache is read again at the next level.
-    a.once = include_self && (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 >= (8 << 20);
+    // The nontemporal hint, from 8 MB of keys and values on.  Verification reads every layer's caches once a round; from 8 MB a layer on the 24 to 48 layers of a
+    // model displace each other in the 256 MB memory-side cache anyway, and the hint keeps them from displacing the rows other workgroups still read (us with
+    // plain loads / with the hint: 32 heads of head_dim 128 and 764 keys 8.97 / 8.73, 4 sequences of them 15.2 / 13.2; 8 sequences of 10 rows, head_dim 64, 20.1 / 17.8;
+    // but 5.5 MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2: never).
+    // A draft's one cache is read again at the next level, and is still in that cache while it fits beside the level's projection weights: up to 152 MB (a whole
+    // LLaVA draft: 4 sequences, 110 MB 324 / 332, 147 MB 364 / 371; 8 sequences, 156 MB 441 / 424, 192 MB 482 / 422, 294 MB 633 / 544).
+    a.once = (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 >= (include_self ? 8 : 152) << 20;
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;

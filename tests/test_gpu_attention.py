@@ -466,3 +466,17 @@ def test_f32_pass_edges(gu, D, kv):
     got, lse = gu.run_verify(x)
     want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "f32", x.prefix_len, x.parent, True)
     assert np.abs(got - want).max() <= TOL["f32"] and np.abs(lse - want_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("shape", [(8, 32, 32, 128, 1300), (16, 32, 8, 128, 2500)])
+def test_levels_over_a_cache_beyond_the_memory_side_cache(gu, shape):
+    """Cross-attention reads caches of more than 152 MB with the nontemporal hint."""
+    B, Hq, Hkv, D, prefix = shape
+    assert B * Hkv * (prefix + 17) * D * 4 >= 152 << 20
+    cfg = _cfg("large", "bf16", B, Hq, Hkv, D, prefix, 0, 17, 4, 54)
+    x = di.verify_inputs(cfg, prefix_len=[prefix - 61 * b for b in range(B)], streams=(di.STREAM_XQ, di.STREAM_XK, di.STREAM_XV))
+    rows = np.stack([np.arange(5, 9, dtype=np.int32)] * B)
+    assert gu.xattn_plan(x, 4).startswith("attn_wave_kernel"), gu.xattn_plan(x, 4)
+    got, qsel = gu.run_xattn(x, rows, rows)
+    want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
+    assert np.abs(got - want).max() <= TOL["bf16"]
