@@ -150,14 +150,21 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
     const int begin = chunk * STAT_CHUNK;
     float x[STAT_CHUNK / 256];
     float m = -INFINITY;
+    // one question for the whole chunk: with one per group of 8 tokens its load was waited for before the next was asked for (a chunk of 16384 bfloat16 tokens, 32
+    // sequences x 8 nodes x 131072: 35.5 us instead of 26.0)
+    if (vec && begin + STAT_CHUNK <= vocab) {
 #pragma unroll
-    for (int r = 0; r < STAT_CHUNK / 2048; r++) {
-        load8<BF16>(base, row, begin + (r * 256 + tid) * 8, vocab, vec, x + 8 * r);
+        for (int r = 0; r < STAT_CHUNK / 2048; r++)
+            load8<BF16>(base, row, begin + (r * 256 + tid) * 8, 0x7fffffff, true, x + 8 * r);
+    } else {
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            x[8 * r + j] *= inv_temp;
-            m = fmaxf(m, x[8 * r + j]);
-        }
+        for (int r = 0; r < STAT_CHUNK / 2048; r++)
+            load8<BF16>(base, row, begin + (r * 256 + tid) * 8, vocab, vec, x + 8 * r);
+    }
+#pragma unroll
+    for (int j = 0; j < STAT_CHUNK / 256; j++) {
+        x[j] *= inv_temp;
+        m = fmaxf(m, x[j]);
     }
     m = wave_max(m);
     if (lane == 0)
