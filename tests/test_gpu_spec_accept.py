@@ -74,7 +74,7 @@ def _draft_children(parent, dl_f64, g):
 def _formed_by_the_walk(B, T, V, dtype):
     """Whether the statistics of the nodes' rows are formed by the walk (the line of spec_accept.hip) and not beforehand."""
     nbytes = 2 * B * T * V * (4 if dtype == "f32" else 2)
-    return nbytes >= 60000000 and nbytes * T >= 3600000000
+    return nbytes >= 60000000 and nbytes * T >= 3000000000
 
 
 def _branches(parent, detail, clear):
