@@ -52,6 +52,7 @@ struct AttnArgs {
     int32_t mask_words;      // 64-bit words of a node's visibility mask: ceil(n_tree / 64)
     int32_t n_splits;
     int32_t n_streams;       // B * Hkv * n_splits
+    uint32_t spread;         // attend_rows: ceil(2^16 / Hkv) where the KV heads of all sequences are numbered together, 0 where Hkv is a multiple of 8
     int64_t s_max;
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
@@ -837,8 +838,15 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     const int c = lane & 15, g = lane >> 4;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
 
-    // workgroups of a KV head have ids congruent mod 8 (same XCD)
-    const int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z, unit = blockIdx.x >> 3, ds = unit % DS;
+    // workgroups of a KV head have ids congruent mod 8 (same XCD).  The KV heads of all sequences take the XCDs in turn: 4 or 5 heads numbered
+    // per sequence left XCDs idle (24 sequences of 4 KV heads, 33 rows of 4 heads, 340 keys: 27.1 us, 15.0 in turn)
+    int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z;
+    const int unit = blockIdx.x >> 3, ds = unit % DS;
+    if (a.spread) {
+        const int stream = kvh;
+        b = (int)((stream * a.spread) >> 16);          // exact: fewer than 264 streams
+        kvh = stream < a.n_streams ? stream - b * a.n_kv_heads : a.n_kv_heads;
+    }
     const int n_rows = a.group * a.n_q, row0 = unit / DS * (TILES_Q * 16);
     if (kvh >= a.n_kv_heads || row0 >= n_rows)
         return;
@@ -1459,6 +1467,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
 {
     const int G = d->n_q_heads / d->n_kv_heads;
     const int64_t base = (int64_t)d->batch * d->n_kv_heads;
+    const int64_t places = (base + 7) / 8 * 8;       // 8 times the KV heads of the XCD that has most: one workgroup per CU counts these
     const int tiles = ceil_div(max_kv_len, 32), rows = ceil_div((int64_t)G * n_q, 16);
     const int n_qtiles = G * ceil_div(n_q, 16);      // as many as the heads' rows would need one head after the other
     p->wave_mode = false;
@@ -1468,15 +1477,15 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
         return false;
     if (G == 3 || (G == 1 && d->head_dim == 256)) {
         // one query tile a workgroup in as many column slices as leave one workgroup per CU, or two tiles
-        if (base * n_qtiles > (d->head_dim <= 128 ? 512 : 256))
+        if (places * n_qtiles > (d->head_dim <= 128 ? 512 : 256))
             return false;
         p->wave_ds = 1;
-        while (p->wave_ds < 4 && base * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
+        while (p->wave_ds < 4 && places * n_qtiles * p->wave_ds * 2 <= 256 && d->head_dim / (p->wave_ds * 2) >= 32)
             p->wave_ds *= 2;
-        p->wave_qt = base * n_qtiles > 256 ? 2 : 1;
+        p->wave_qt = places * n_qtiles > 256 ? 2 : 1;
         // (3 tiles a head are two workgroups: 20 sequences of 8 KV heads, head_dim 128, 64 key tiles: 320 workgroups 48 us, the 160 of the plan without 32)
         const int64_t workgroups = base * ceil_div(rows, p->wave_qt) * p->wave_ds;
-        if (workgroups > 256)
+        if (places * ceil_div(rows, p->wave_qt) * p->wave_ds > 256)
             return false;
         // us on both sides of a line, 8 KV heads in groups of 3: head_dim 64, 2 sequences, 96 tiles 14.9 / 15.6, 128 tiles 19.2 / 17.5; head_dim 128, unsliced, 48 tiles 15.6 / 17.1,
         // 64 tiles 19.7 / 19.9; head_dim 256, 26 tiles 18.2 / 22.2, 40 tiles 26.8 / 25.5; one head of 256, 2 slices, 48 tiles 23.2 / 24.4, 56 tiles 26.3 / 25.2
@@ -1486,7 +1495,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     } else {
         const Decomposition *use = nullptr;
         for (const Decomposition &c : DECOMPOSITIONS)
-            if (!use && c.d == d->head_dim && base * ceil_div(rows, c.slots * c.qt) * c.ds <= 256)
+            if (!use && c.d == d->head_dim && places * ceil_div(rows, c.slots * c.qt) * c.ds <= 256)
                 use = &c;
         const int line = !use ? 0 : G == 1 ? use->tiles_1 : use->tiles_n;
         if (!line)
@@ -1517,7 +1526,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     // The grid has a workgroup for every tile that the heads would need one after the other while each has a CU of its own: those beyond the rows
     // end at once and cost nothing there (60 rows of 4 heads, 8 KV heads, 1340 keys: 256 workgroups 9.65 us, the 240 with rows 9.6).  With more of
     // them than CUs, two that work would share one while others idle (3 sequences of 17 rows, 384 workgroups and 240: 23.7 / 12.6 us at 1417 keys, 35.5 / 18.5 at 2417).
-    p->n_qg = p->wave_qt == 1 && p->slots == 1 && base * n_qtiles * p->wave_ds <= 256 ? n_qtiles : rows;
+    p->n_qg = p->wave_qt == 1 && p->slots == 1 && places * n_qtiles * p->wave_ds <= 256 ? n_qtiles : rows;
     p->n_splits = 1;
     p->n_groups = p->n_streams = (int)base;
     p->grid = 0;
@@ -1747,12 +1756,18 @@ int ensure_wave_lds()
     return rc || !hinted ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), bytes, "attention");
 }
 
+// `per_head` workgroups for every KV head of every sequence, as attend_rows reads them
+dim3 stream_grid(const AttnArgs &a, int per_head)
+{
+    return a.spread ? dim3(8 * per_head, ceil_div(a.n_streams, 8)) : dim3(8 * per_head, a.n_kv_heads / 8, a.n_streams / a.n_kv_heads);
+}
+
 template <int D, int NW, int DS, int QT>
 int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_wave_lds<D, NW, DS, QT>())
         return rc;
-    const dim3 grid(8 * ceil_div(a.n_qg, QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    const dim3 grid = stream_grid(a, ceil_div(a.n_qg, QT) * DS);
     constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
     if (hinted && a.once)
         hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, hinted>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
@@ -1775,7 +1790,7 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_pair_lds<D, DS, QT>())
         return rc;
-    const dim3 grid(8 * ceil_div(a.n_qg, 2 * QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 2 * QT) * DS);
     if (a.once)
         hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, true>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
     else
@@ -1797,7 +1812,7 @@ int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_quad_lds<D, DS, QT>())
         return rc;
-    const dim3 grid(8 * ceil_div(a.n_qg, 4 * QT) * DS, ceil_div(a.n_kv_heads, 8), p.n_groups / a.n_kv_heads);
+    const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 4 * QT) * DS);
     if (a.once)
         hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, true>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, a);
     else
@@ -1933,6 +1948,7 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     a.tiles_per_head = p.tiles_per_head; a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
     auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
     a.nq_magic = magic(n_q);
+    a.spread = d->n_kv_heads % 8 ? (65536 + d->n_kv_heads - 1) / d->n_kv_heads : 0;
     // The nontemporal hint, from 8 MB of keys and values on.  Verification reads every layer's caches once a round; from 8 MB a layer on the 24 to 48 layers of a
     // model displace each other in the 256 MB memory-side cache anyway, and the hint keeps them from displacing the rows other workgroups still read (us with
     // plain loads / with the hint: 32 heads of head_dim 128 and 764 keys 8.97 / 8.73, 4 sequences of them 15.2 / 13.2; 8 sequences of 10 rows, head_dim 64, 20.1 / 17.8;

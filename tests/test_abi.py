@@ -325,6 +325,21 @@ def test_few_stream_kernels_launch_at_most_one_workgroup_per_cu(lib):
     assert len(seen) >= 15
 
 
+def test_few_stream_kernels_fit_the_cus_of_every_xcd(lib):
+    """A KV head's workgroups share an XCD, so it is the XCD with most KV heads whose 32 CUs have to hold them, whatever the number of heads."""
+    seen = set()
+    for D in (64, 128, 256):
+        for hkv, g in ((1, 4), (2, 3), (3, 1), (4, 4), (5, 3), (5, 4), (7, 2), (12, 1), (20, 1)):
+            for B in list(range(1, 25)) + [32, 40, 48]:
+                for n_q in (1, 8, 16, 17, 33, 60):
+                    plan = dream.dream_attn_plan_describe(dream.attn_desc(B, hkv * g, hkv, D, dream.BF16, 400), n_q, 400)
+                    if re.match("attn_(wave|pair|quad)_kernel", plan):
+                        per_head = int(re.search(r"workgroups=(\d+)", plan).group(1)) // (B * hkv)
+                        assert -(-B * hkv // 8) * per_head <= 32, (D, hkv, g, B, n_q, plan)
+                        seen.add(plan.split(" ")[0])
+    assert len(seen) >= 15
+
+
 def _signature(name):
     """Parameters of an entry point as include/dream.h declares them: [(type, name)]."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))

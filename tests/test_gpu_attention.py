@@ -291,6 +291,23 @@ def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     assert np.abs(got - want).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("kernel,B,Hq,Hkv,D,T", [("wave", 3, 20, 5, 128, 17), ("wave", 2, 15, 5, 64, 33), ("wave", 7, 12, 12, 64, 9), ("wave", 5, 8, 4, 256, 33), ("wave", 33, 4, 1, 128, 16),
+                                                 ("pair", 13, 16, 4, 128, 33), ("pair", 23, 20, 5, 128, 17), ("quad", 25, 20, 5, 128, 33), ("quad", 23, 8, 4, 256, 60)])
+def test_kv_heads_that_do_not_fill_the_xcds(gu, kernel, B, Hq, Hkv, D, T):
+    """KV heads and sequences are numbered together over the XCDs: counts that are no multiple of 8, ragged sequences."""
+    assert B * Hkv % 8
+    cfg = _cfg("odd", "bf16", B, Hq, Hkv, D, 740 - T, 0, T, 4, 57)
+    x = di.verify_inputs(cfg, prefix_len=[(740 - T) // (1 + b % 4) for b in range(B)])
+    assert gu.verify_plan(x).startswith("attn_%s_kernel" % kernel), gu.verify_plan(x)
+    got, lse = gu.run_verify(x)
+    oracle.set_threads(16)
+    try:
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+    finally:
+        oracle.set_threads(1)
+    assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3
+
+
 @pytest.mark.parametrize("shape,kv_len", [((2, 32, 32, 128, 9), 1984), ((1, 32, 32, 64, 9), 2016), ((1, 32, 8, 128, 64), 2688), ((2, 24, 8, 128, 33), 1568), ((8, 16, 8, 256, 9), 2304),
                                           ((3, 32, 32, 64, 9), 3840), ((24, 32, 8, 128, 17), 736), ((24, 32, 8, 128, 17), 737)])
 def test_the_longest_ranges_of_single_launches(gu, shape, kv_len):
