@@ -301,7 +301,10 @@ __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *p
         for (int j = 0; j < PART; j++)
             pk[j] = lane + j * 64 < n_part ? part_key[row * n_part + lane + j * 64] : 0ull;
         const int depth = (k + n_chunks - 1) / n_chunks, q = (k + depth - 1) / depth;
-        const uint64_t deep = lane < n_chunks ? part_key[row * n_part + lane * k + depth - 1] : 0ull;
+        // A few rounds cost less than the bound, whose chunks are counted one by one.  us, a level of 1 row / 10 rows, rounds and bound: 262144 tokens, k = 1 6.9 and 8.6 / 8.7 and
+        // 10.8, k = 4 8.1 and 8.9 / 9.6 and 10.1; 131072 tokens, 10 rows, k = 1 7.7 and 8.7, k = 3 9.0 and 9.3, k = 4 9.3 and 9.3; 32000 tokens, 10 rows, k = 2 8.4 and 8.6, k = 3 9.0 and 8.7.
+        const bool bounded = n_chunks <= 64 && k > 2 + n_chunks / 16;
+        const uint64_t deep = bounded && lane < n_chunks ? part_key[row * n_part + lane * k + depth - 1] : 0ull;
         // log-sum-exp of the row from the chunk partials (8 per lane: with k = 1 there may be 512 chunks)
         float M = -INFINITY, cm[8], cs[8];
 #pragma unroll
@@ -330,7 +333,7 @@ __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *p
         // A lower bound of the k-th key: with q = ceil(k / depth) chunks whose depth-th key is at or above it there are k keys
         // at or above it.  Lane c holds the depth-th of chunk c; the q-th of those is found by counting.
         int n_left = 65;
-        if (n_chunks <= 64) {
+        if (bounded) {
             int above = 0;
             for (int c = 0; c < n_chunks; c++)
                 above += lane_value(deep, c) > deep ? 1 : 0;

@@ -102,6 +102,14 @@ def test_best_tokens_of_a_row_wherever_they_lie(gu, V, k, where):
     _check_level(gu, logits, "f32", np.array([[-1.0, -1.5], [0.0, -3.0]], dtype=np.float32), k)
 
 
+@pytest.mark.parametrize("V,k", [(8000, 2), (8000, 3), (131072, 3), (131072, 4), (262144, 1), (262144, 4), (262144, 5), (540000, 6)])
+def test_both_ways_of_merging_the_chunks(gu, V, k):
+    """On both sides of the line between rounds and the bound of the k-th, whose position depends on k and on the number of chunks; ties included."""
+    g = di.rng(750 + V + k, 403)
+    logits = (np.round(g.standard_normal((2, 3, V)) * 32.0) / 32.0).astype(np.float32)
+    _check_level(gu, logits, "f32", np.array([[-1.0, -1.5, -0.5], [0.0, -3.0, -0.25]], dtype=np.float32), k)
+
+
 def test_finalize_bit_exact_including_ties(gu):
     g = di.rng(77, 400)
     for N, budget in [(85, 32), (85, 100), (2, 1), (1, 5), (1024, 59), (601, 600), (333, 0)]:
