@@ -334,6 +334,7 @@ const char *dream_last_error(void);
 /* Host-only: writes a short description of the launch plan the attention calls would use for n_q query
  * rows per sequence and keys up to max_kv_len (kernel and its template arguments, workgroups, key splits,
  * whether a merge launch follows) into buf (NUL-terminated, truncated to buf_bytes).  Needs no GPU.
+ * Where it names key splits, a cross-attention call whose cache the memory-side cache holds may still be one launch without.
  * More than 64 query rows are taken as a verification call over a tree of n_q nodes (the plan of a tree above 64
  * nodes differs: four mask words per node, see DREAM_MAX_TREE).
  * DREAM_OK, or DREAM_ERR_INVALID_ARG / DREAM_ERR_UNSUPPORTED for a descriptor the attention calls reject. */

@@ -1453,17 +1453,22 @@ const Decomposition DECOMPOSITIONS[] = {
 //   head_dim 64: 32 heads, 1 sequence, 8 rows, 64 workgroups, 60 tiles 10.4 / 10.7, 64 tiles 11.4 / 10.7; 64 rows, 256 workgroups, 90 tiles 13.5 / 13.9, 104 tiles
 //   15.1 / 14.8; 3 sequences of 8 rows, against two splits, 104 tiles 19.8 / 22.6
 //   head_dim 256, 8 KV heads, groups of 2: 64 rows 56 tiles 20.2 / 21.7, 64 tiles 22.5 / 21.4; 2 sequences of 8 rows, 64 workgroups, 36 tiles 16.0 / 16.1, 44 tiles 18.5 / 17.1
-int64_t longest_range(const dream_attn_desc *d, int n_qtiles, int64_t workgroups, int slots, int line)
+// While the memory-side cache holds the caches (`near`), every workgroup pulls faster and few of them are no reason to change early: at most 8 % behind at the last length
+// over 16 groupings, 1 to 8 sequences, 1 to 60 rows and 28 to 160 tiles, where the lines above lost up to 1.5x.  us, single launch / general plan, cross-attention of 10 rows: head_dim 128, 32 heads,
+// 1 sequence 64 tiles 10.8 / 13.2, 90 tiles 15.2 / 15.2, 100 tiles 16.3 / 15.6; 8 KV heads, groups of 2, 3 sequences 100 tiles 15.9 / 15.9, 112 tiles 17.6 / 16.7, groups of 4, 4 sequences 80 tiles
+// 14.6 / 18.2, 126 tiles 19.9 / 21.3; head_dim 64, 32 heads, 1 sequence 64 tiles 8.2 / 9.9, 112 tiles 11.7 / 11.9, 126 tiles 12.9 / 12.3; against two splits, 3 sequences, 126 tiles 17.2 / 25.4;
+// head_dim 256, groups of 2, 2 sequences 64 tiles 18.4 / 19.5, 72 tiles 20.1 / 20.2, 80 tiles 21.6 / 21.2.  Verification of one sequence: 8 heads of 128, 60 rows, 64 tiles 11.0 / 13.5.
+int64_t longest_range(const dream_attn_desc *d, int n_qtiles, int64_t workgroups, int slots, int line, bool near)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
     const int64_t splits = 256 / ((int64_t)d->batch * d->n_kv_heads * ceil_div(n_qtiles, 4));
     if (splits < 3)
-        return d->head_dim == 256 ? (G == 1 ? 96 : 128) : slots > 1 && G > 1 ? 1 << 30 : G == 1 ? 120 : 160;
-    const int64_t tiles = line * (384 + workgroups) / 640;
+        return d->head_dim == 256 ? (G == 1 ? 96 : 128) : near || (slots > 1 && G > 1) ? 1 << 30 : G == 1 ? 120 : 160;
+    const int64_t tiles = near ? std::max(line * 5 / 4, d->head_dim == 64 ? 112 : d->head_dim == 256 ? 72 : G == 1 ? 90 : 100) : line * (384 + workgroups) / 640;
     return splits == 4 ? tiles * 6 / 5 : splits == 3 ? tiles * 8 / 5 : tiles;
 }
 
-bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan *p)
+bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool near, Plan *p)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
     const int64_t base = (int64_t)d->batch * d->n_kv_heads;
@@ -1490,7 +1495,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
         // us on both sides of a line, 8 KV heads in groups of 3: head_dim 64, 2 sequences, 96 tiles 14.9 / 15.6, 128 tiles 19.2 / 17.5; head_dim 128, unsliced, 48 tiles 15.6 / 17.1,
         // 64 tiles 19.7 / 19.9; head_dim 256, 26 tiles 18.2 / 22.2, 40 tiles 26.8 / 25.5; one head of 256, 2 slices, 48 tiles 23.2 / 24.4, 56 tiles 26.3 / 25.2
         static const int LINES[3][3] = {{108, 108, 108}, {64, 74, 76}, {36, 50, 54}};    // by head_dim; unsliced, 2 slices, 4
-        if (tiles > longest_range(d, n_qtiles, workgroups, 1, LINES[d->head_dim / 128][p->wave_ds / 2]))
+        if (tiles > longest_range(d, n_qtiles, workgroups, 1, LINES[d->head_dim / 128][p->wave_ds / 2], near))
             return false;
     } else {
         const Decomposition *use = nullptr;
@@ -1501,7 +1506,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
         if (!line)
             return false;
         const int units = ceil_div(rows, use->slots * use->qt);
-        if (tiles > longest_range(d, n_qtiles, base * units * use->ds, use->slots, line))
+        if (tiles > longest_range(d, n_qtiles, base * units * use->ds, use->slots, line, near))
             return false;
         // Three exceptions.  Four slots for all rows of a KV head start slower than the 8 waves of the shared-tile kernel, which do the same, the more so
         // the more CUs are at work: 18 sequences of 17 rows 18 tiles 17.9 / 18.0, 24 sequences
@@ -1537,11 +1542,11 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, Plan 
     return true;
 }
 
-// direct: q and the caches are 16-byte aligned, as loads straight to LDS need them
-int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool direct, Plan *p)
+// direct: q and the caches are 16-byte aligned, as loads straight to LDS need them.  near: the memory-side cache still holds the caches
+int make_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool direct, bool near, Plan *p)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
-    if (make_wave_plan(d, n_q, max_kv_len, p)) {
+    if (make_wave_plan(d, n_q, max_kv_len, near, p)) {
         if (direct)
             return 0;
         p->wave_mode = false;
@@ -1910,6 +1915,14 @@ void variant_name(const Variant &v, char *buf, size_t n)
         snprintf(buf, n, "attn_bf16_kernel<%d,%d,%d,%d>", v.d, v.p1, v.p2, v.p3);
 }
 
+// Bytes of keys and values from which on a call finds them in HBM and not in the 256 MB memory-side cache.  Verification reads every layer's caches once a round: from
+// 8 MB a layer on the 24 to 48 layers of a model displace each other.  A draft's one cache is read again at the next level, and is still there while it fits beside
+// the level's projection weights.
+bool caches_near(const dream_attn_desc *d, int64_t max_kv_len, bool drafting)
+{
+    return (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 < (int64_t)(drafting ? 152 : 8) << 20;
+}
+
 int run_attention(const char *who, const dream_attn_desc *d, const void *q, const void *k, const void *v,
                   const int32_t *prefix_len, int n_tree, const int32_t *parent, const uint64_t *tree_mask,
                   int n_q, const int32_t *q_node, int include_self, int64_t max_kv_len, void *out, float *lse,
@@ -1930,8 +1943,10 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
         return fail(DREAM_ERR_INVALID_ARG, "%s: %d query rows but only %d tree nodes and no q_node", who, n_q, n_tree);
     if (max_kv_len < n_tree || max_kv_len > d->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: max_kv_len %lld outside [n_tree, s_max]", who, (long long)max_kv_len);
+    const bool direct = !((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15);
     Plan p;
-    make_plan(d, n_q, max_kv_len, !((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15), &p);
+    // (unaligned tensors get what the workspace was asked for, never more splits than that)
+    make_plan(d, n_q, max_kv_len, direct, caches_near(d, max_kv_len, !include_self && direct), &p);
     if (n_tree > 64 && d->dtype == DREAM_BF16)
         make_wide_plan(d, n_q, &p);
     if (!ws || ws_bytes < p.total)
@@ -1949,13 +1964,11 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
     a.nq_magic = magic(n_q);
     a.spread = d->n_kv_heads % 8 ? (65536 + d->n_kv_heads - 1) / d->n_kv_heads : 0;
-    // The nontemporal hint, from 8 MB of keys and values on.  Verification reads every layer's caches once a round; from 8 MB a layer on the 24 to 48 layers of a
-    // model displace each other in the 256 MB memory-side cache anyway, and the hint keeps them from displacing the rows other workgroups still read (us with
+    // The nontemporal hint where the caches come from HBM: it keeps them from displacing the rows other workgroups still read (us with
     // plain loads / with the hint: 32 heads of head_dim 128 and 764 keys 8.97 / 8.73, 4 sequences of them 15.2 / 13.2; 8 sequences of 10 rows, head_dim 64, 20.1 / 17.8;
     // but 5.5 MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2: never).
-    // A draft's one cache is read again at the next level, and is still in that cache while it fits beside the level's projection weights: up to 152 MB (a whole
-    // LLaVA draft: 4 sequences, 110 MB 324 / 332, 147 MB 364 / 371; 8 sequences, 156 MB 441 / 424, 192 MB 482 / 422, 294 MB 633 / 544).
-    a.once = (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 >= (include_self ? 8 : 152) << 20;
+    // (A whole LLaVA draft: 4 sequences, 110 MB 324 / 332, 147 MB 364 / 371; 8 sequences, 156 MB 441 / 424, 192 MB 482 / 422, 294 MB 633 / 544).
+    a.once = !caches_near(d, max_kv_len, !include_self);
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;
@@ -1981,7 +1994,7 @@ size_t workspace_for(const dream_attn_desc *d, int n_q, int64_t max_kv_len)
         d->batch < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
     Plan p;
-    make_plan(d, n_q, max_kv_len, true, &p);
+    make_plan(d, n_q, max_kv_len, true, caches_near(d, max_kv_len, false), &p);
     return p.total;
 }
 
@@ -2011,7 +2024,7 @@ int dream_attn_plan_describe(const dream_attn_desc *desc, int32_t n_q, int64_t m
     if (n_q < 1 || max_kv_len < 1 || max_kv_len > desc->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= max_kv_len <= s_max", who);
     Plan p;
-    make_plan(desc, n_q, max_kv_len, true, &p);
+    make_plan(desc, n_q, max_kv_len, true, caches_near(desc, max_kv_len, false), &p);
     if (n_q > 64 && desc->dtype == DREAM_BF16)   // more than 64 query rows: taken as a verification call over a tree of n_q nodes
         make_wide_plan(desc, n_q, &p);
     if (desc->dtype == DREAM_F32) {

@@ -47,7 +47,8 @@ def verify_plan(x: di.AttnInputs) -> str:
 
 
 def xattn_plan(x: di.AttnInputs, n_q: int) -> str:
-    """The launch plan run_xattn(x, rows with n_q columns, ...) will get (host-only)."""
+    """The launch plan run_xattn(x, rows with n_q columns, ...) will get (host-only), but for long ranges: where this one splits the keys the call may still be
+    one launch."""
     return dream.dream_attn_plan_describe(desc_for(x), n_q, int(x.prefix_len.max()) + x.parent.shape[1])
 
 

@@ -511,6 +511,16 @@ def test_single_launches_on_both_sides_of_their_line(lib, B, hq, hkv, D, n_q, li
     assert plans[0].startswith(upto) and plans[1].startswith(beyond), plans
 
 
+@pytest.mark.parametrize("B,hq,hkv,D,n_q,keys", [(1, 8, 8, 128, 60, 2047), (1, 8, 4, 256, 60, 2047), (1, 8, 8, 64, 60, 3584), (1, 32, 8, 128, 8, 2047), (1, 24, 8, 64, 33, 4095)])
+def test_single_launches_over_small_caches(lib, B, hq, hkv, D, n_q, keys):
+    """Up to 8 MB of keys and values a layer, which the memory-side cache holds for all layers, one launch without key splits is taken for longer."""
+    desc = dream.attn_desc(B, hq, hkv, D, dream.BF16, 4200)
+    plans = [dream.dream_attn_plan_describe(desc, n_q, n) for n in (keys, keys + 1)]
+    assert plans[0].startswith("attn_wave_kernel") and plans[1].startswith("attn_bf16_kernel"), plans
+    for n in (keys // 2, keys):
+        assert dream.dream_tree_verify_attn_workspace(desc, n_q, n) <= dream.dream_tree_verify_attn_workspace(desc, n_q, keys + 1)
+
+
 def test_a_workspace_for_the_longest_range_fits_every_shorter_call(lib):
     """Programs query once, for the longest key range; the plans of shorter ranges (other splits, other kernels) never need more."""
     for D in (64, 128, 256):

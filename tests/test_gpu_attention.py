@@ -347,6 +347,31 @@ def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
         assert np.abs(got - base).max() <= TOL["bf16"], name
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,line", [(1, 32, 32, 128, 90), (2, 16, 8, 128, 100), (1, 32, 32, 64, 112), (2, 16, 8, 256, 72), (3, 24, 8, 128, 152), (3, 16, 16, 64, 112)])
+def test_long_ranges_of_a_draft_cache(gu, B, Hq, Hkv, D, line):
+    """Cross-attention over a cache that the memory-side cache holds stays one launch for longer than the plan of a verification says: lengths where the two differ,
+    the last of them and the next, ragged sequences; a cache off the 16-byte boundaries in the workspace that the query returned."""
+    import torch
+    for kv_len in ((line - 11) * 32, line * 32, line * 32 + 1):
+        cfg = _cfg("near", "bf16", B, Hq, Hkv, D, kv_len - 17, 0, 17, 4, 58)
+        x = di.verify_inputs(cfg, prefix_len=[(kv_len - 17) // (1 + b) for b in range(B)], streams=(di.STREAM_XQ, di.STREAM_XK, di.STREAM_XV))
+        rows = np.stack([np.arange(6, 16, dtype=np.int32)] * B)
+        got, qsel = gu.run_xattn(x, rows, rows)
+        oracle.set_threads(16)
+        try:
+            want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
+        finally:
+            oracle.set_threads(1)
+        assert np.abs(got - want).max() <= TOL["bf16"], kv_len
+    dev = gu.DeviceAttn(x)
+    flat = torch.empty(dev.k.numel() + 8, dtype=dev.k.dtype, device="cuda")
+    shifted = flat[2:2 + dev.k.numel()].view(dev.k.shape)
+    shifted.copy_(dev.k)
+    dev.k = shifted
+    got, _ = gu.run_xattn(x, rows, rows, dev=dev)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+
+
 FULL = ["llava", "pixtral", "gemma3", "smolvlm_b1", "smolvlm_b8", "smolvlm_b32"]
 
 
