@@ -1,5 +1,7 @@
 """GPU parity: dream_tree_verify_attn and dream_draft_xattn against the float64 oracle on identical
 seeded inputs.  Tolerances (max-abs): 1e-5 for float32 tensors, 2e-2 for bf16 tensors."""
+import re
+
 import numpy as np
 import pytest
 
@@ -289,6 +291,22 @@ def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     got, qsel = gu.run_xattn(x, rows, rows)
     want, _ = oracle.tree_attn(qsel, x.k, x.v, "bf16", x.prefix_len, x.parent, False, q_node=rows)
     assert np.abs(got - want).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T", [(5, 32, 32, 16), (8, 32, 32, 7), (13, 16, 16, 10), (30, 16, 8, 8)])
+def test_one_query_tile_of_every_head_unsliced(gu, B, Hq, Hkv, T):
+    """More KV heads than two slices leave CUs for, one query tile each: no, fewer and more steps than waves, with four waves and with eight."""
+    for kv_len in (T, 32, 33, 160, 161, 256, 257, 700):
+        cfg = _cfg("one", "bf16", B, Hq, Hkv, 128, kv_len - T, 0, T, min(4, T - 1), 59)
+        x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) // (1 + b % 3) for b in range(B)])
+        assert re.match("attn_wave_kernel<128,[48],1,1> workgroups=%d " % (B * Hkv), gu.verify_plan(x)), gu.verify_plan(x)
+        got, lse = gu.run_verify(x)
+        oracle.set_threads(16)
+        try:
+            want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+        finally:
+            oracle.set_threads(1)
+        assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3, kv_len
 
 
 @pytest.mark.parametrize("kernel,B,Hq,Hkv,D,T", [("wave", 3, 20, 5, 128, 17), ("wave", 2, 15, 5, 64, 33), ("wave", 7, 12, 12, 64, 9), ("wave", 5, 8, 4, 256, 33), ("wave", 33, 4, 1, 128, 16),
