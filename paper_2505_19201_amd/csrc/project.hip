@@ -44,6 +44,7 @@ struct ProjArgs {
     int32_t n_rows;      // R: rows per sequence
     int32_t m_total;     // B * R
     int32_t hidden, head_dim;
+    int32_t row_groups;  // project_rows_kernel: workgroups that share the rows of a weight tile
     int64_t s_max;       // cache mode only
 };
 
@@ -198,19 +199,28 @@ template <int MT, int NT>
 __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
 {
     using G = RowsGeom<MT, NT>;
-    const ProjView a = select_job(args, blockIdx.x);
+    // the workgroups of a weight tile have ids congruent mod 8 (same XCD), and few lie between them
+    int tile = blockIdx.x, group = 0;
+    if (args.row_groups > 1) {
+        const int octet = tile >> 3;
+        group = octet % args.row_groups;
+        tile = octet / args.row_groups * 8 + (tile & 7);
+        if (tile >= args.job[args.n_jobs - 1].tile_end)
+            return;
+    }
+    const ProjView a = select_job(args, tile);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int n_tiles = a.n_heads * a.head_dim / 16, nt0 = ((int)blockIdx.x - a.first) * NT;
+    const int n_tiles = a.n_heads * a.head_dim / 16, nt0 = (tile - a.first) * NT;
     const int K = a.hidden, n_steps = (K / STEP - wave + RW - 1) / RW;   // this wave's: steps wave, wave + RW, ...
     unsigned char *stage = smem + wave * G::STAGE;
     // The workgroups of an XCD start at different steps: the rows are a power of two or nearly so apart, so one step's pieces
     // of all rows sit in few L2 channels, and everybody would ask the same ones at the same time (LLaVA, 20 rows: 29 us without, 18 with).
-    const int first = n_steps > 0 ? ((int)blockIdx.x >> 3) % n_steps : 0;
+    const int first = n_steps > 0 ? (tile >> 3) % n_steps : 0;
     const int lrow = lane >> 3, lchunk = lane & 7;           // a load instruction: 8 rows x 128 bytes
-    for (int m0 = 0; m0 < a.m_total; m0 += 16 * MT) {
+    for (int m0 = group * 16 * MT; m0 < a.m_total; m0 += args.row_groups * 16 * MT) {
         const uint16_t *wsrc[NT], *xsrc[MT * 2];
 #pragma unroll
         for (int nt = 0; nt < NT; nt++)                       // (tiles past the last repeat it, never stored)
@@ -220,18 +230,23 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
             xsrc[j] = a.x + (int64_t)min(m0 + j * 8 + lrow, a.m_total - 1) * K + wave * STEP + lchunk * 8;
         const int xj = min((a.m_total - m0 + 7) / 8, MT * 2);
         u32x4 wr[NT * 2], xr[MT * 2];
-        auto issue = [&](int s) {
+        auto column = [&](int s) {
             const int at = s + first;
-            const int col = (at < n_steps ? at : at - n_steps) * (RW * STEP);
+            return (at < n_steps ? at : at - n_steps) * (RW * STEP);
+        };
+        auto load_w = [&](int j, int col) { wr[j] = *reinterpret_cast<const u32x4 *>(wsrc[j / 2] + (j % 2 ? (int64_t)8 * K : 0) + col); };
+        auto load_x = [&](int j, int col) {
+            if (j < MT * 2 - 2 || j < xj)                     // all but the last tile are full
+                xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
+        };
+        auto issue = [&](int s) {
+            const int col = column(s);
 #pragma unroll
-            for (int nt = 0; nt < NT; nt++) {
-                wr[nt * 2] = *reinterpret_cast<const u32x4 *>(wsrc[nt] + col);
-                wr[nt * 2 + 1] = *reinterpret_cast<const u32x4 *>(wsrc[nt] + (int64_t)8 * K + col);
-            }
+            for (int j = 0; j < NT * 2; j++)
+                load_w(j, col);
 #pragma unroll
             for (int j = 0; j < MT * 2; j++)
-                if (j < MT * 2 - 2 || j < xj)                 // all but the last tile are full
-                    xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
+                load_x(j, col);
         };
         f32x4 acc[MT][NT];
 #pragma unroll
@@ -242,14 +257,24 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
         // chunk p of row r of a tile lies at p ^ (r & 7): the 16 rows of a fragment read sit in different banks
         const int put = lrow * STEP_BYTES + ((lchunk ^ lrow) * 16);
         auto step = [&](int s, bool more) {
+            // With 8 row tiles a register is asked for again as soon as its piece is in LDS: writing all 20 KB first left the loads idle (128 rows,
+            // weights in HBM, LLaVA 50.2 us, 48.2 so; SmolVLM 15.9 and 15.2; but with one or two steps a wave, hidden dimension 768, 6.6 and 6.9)
+            constexpr bool EARLY = MT == 8;
+            const int col = more ? column(s + 1) : 0;
 #pragma unroll
-            for (int j = 0; j < NT * 2; j++)
+            for (int j = 0; j < NT * 2; j++) {
                 *reinterpret_cast<u32x4 *>(stage + j * 1024 + put) = wr[j];
+                if (EARLY && more)
+                    load_w(j, col);
+            }
 #pragma unroll
-            for (int j = 0; j < MT * 2; j++)
+            for (int j = 0; j < MT * 2; j++) {
                 if (j < MT * 2 - 2 || j < xj)
                     *reinterpret_cast<u32x4 *>(stage + (NT * 2 + j) * 1024 + put) = xr[j];
-            if (more)
+                if (EARLY && more)
+                    load_x(j, col);
+            }
+            if (!EARLY && more)
                 issue(s + 1);
             wave_lds_fence();
 #pragma unroll
@@ -385,27 +410,40 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         hipLaunchKernelGGL(project_kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, a);
         return check_launch("project_kernel");
     }
-    // row tiles per pass: as few passes of up to 8 tiles as there have to be, of about equal size (2 to 8 tiles: there are at least 17 rows)
-    const int m_tiles = ceil_div(a.m_total, 16), mt = ceil_div(m_tiles, ceil_div(m_tiles, MAX_MT));
-    // feature tiles per workgroup: the fewest bytes through the busiest CU
-    int nt = 1;
+    // Row tiles per pass (2 to 8: there are at least 17 rows), feature tiles per workgroup and how many workgroups share the rows of a feature tile: the fewest bytes
+    // through the busiest CU.  Up to 128 rows are one pass; above, a workgroup goes through as few passes as there have to be, of about equal size, or every pass is a workgroup of its
+    // own, which leaves fewer CUs idle and reads weights that another pass has brought to L2.  us, one after the other / side by side: LLaVA 256 rows 72.3 / 53.8 (weights in HBM 84.2 / 66.0),
+    // 144 rows 50.1 / 40.3, 1000 rows 266 / 205; SmolVLM 192 rows 19.3 / 17.3, 1000 rows 83.8 / 66.6; hidden dimension 768, 1000 rows 32.7 / 16.8.
+    const int m_tiles = ceil_div(a.m_total, 16), passes = ceil_div(m_tiles, MAX_MT);
+    int mt = 0, nt = 1;
     int64_t best = 0;
-    for (int t = 1; t <= max_nt(mt); t++) {
+    auto try_split = [&](int m, int n, int groups) {
         int64_t wgs = 0;
         for (int j = 0; j < n_jobs; j++)
-            wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, t);
-        const int64_t cost = ceil_div(wgs, 256) * (int64_t)(a.m_total + 16 * t);
-        if (t == 1 || cost < best) {
+            wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, n);
+        if (groups > 1)
+            wgs = (int64_t)ceil_div(wgs, 8) * 8 * groups;
+        const int64_t cost = (wgs + 255) / 256 * (groups > 1 ? 16 * (m + n) * 11 : (a.m_total + 16 * n * passes) * 10);   // (Gemma3, 1000 rows: 8 % fewer, and 5 % slower)
+        if (mt == 0 || (cost < best && wgs <= (1 << 22))) {      // (a grid has fewer than 2^32 threads)
             best = cost;
-            nt = t;
+            mt = m;
+            nt = n;
+            a.row_groups = groups;
         }
-    }
+    };
+    a.row_groups = 1;
+    for (int n = 1; n <= max_nt(ceil_div(m_tiles, passes)); n++)
+        try_split(ceil_div(m_tiles, passes), n, 1);
+    if (passes > 1)
+        for (int m = 2; m <= MAX_MT; m++)
+            for (int n = 1; n <= max_nt(m); n++)
+                try_split(m, n, ceil_div(m_tiles, m));
     int wgs = 0;
     for (int j = 0; j < n_jobs; j++) {
         wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
         a.job[j].tile_end = wgs;
     }
-    return ROWS[mt - 2][nt - 1].launch(wgs, st, a);
+    return ROWS[mt - 2][nt - 1].launch(a.row_groups > 1 ? ceil_div(wgs, 8) * 8 * a.row_groups : wgs, st, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,

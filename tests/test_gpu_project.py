@@ -120,3 +120,22 @@ def test_row_and_feature_tile_edges(gu, B, R, hidden, H, D):
     """One row past a tile, whole tiles, every tile count, a second pass (129 rows), a last workgroup with fewer feature tiles (770)."""
     x, w = _inputs(B, R, hidden, H, D, 140 + R)
     _close(gu.run_project(x, w, H, D), oracle.project(x, w, "bf16", H, D))
+
+
+@pytest.mark.parametrize("R", [129, 150, 200, 321, 513])
+@pytest.mark.parametrize("hidden,Hq,Hkv,D", [(256, 5, 3, 16), (768, 12, 12, 64), (1280, 70, 9, 32)])
+def test_passes_side_by_side(gu, R, hidden, Hq, Hkv, D):
+    """More than 128 rows: several workgroups share a feature tile's rows (or one goes through them), three maps of different widths, a number of feature tiles that
+    is no multiple of 8, a last pass with one row or several."""
+    e = di.normal((1, R, hidden), "bf16", 301, di.STREAM_ROWS)
+    s = di.normal((1, R, hidden), "bf16", 302, di.STREAM_ROWS)
+    ws = [di.f32_to_bf16_bits(di.normal((h * D, hidden), "f32", 303 + i, di.STREAM_ROWS) * np.float32(hidden ** -0.5))
+          for i, h in enumerate((Hq, Hkv, Hkv))]
+    kc = di.normal((1, Hkv, R + 9, D), "bf16", 310, di.STREAM_K)
+    vc = di.normal((1, Hkv, R + 9, D), "bf16", 311, di.STREAM_V)
+    row_index = np.arange(R, dtype=np.int32)[None]
+    q, k, v = gu.run_project_qkv(e, s, ws[0], ws[1], ws[2], Hq, Hkv, D, np.array([4], dtype=np.int32), row_index, kc, vc)
+    _close(q, oracle.project(e, ws[0], "bf16", Hq, D))
+    for got, w, cache in ((k, ws[1], kc), (v, ws[2], vc)):
+        _close(di.bf16_bits_to_f32(got[0][:, 4:4 + R].view(np.uint16)).astype(np.float64), oracle.project(s, w, "bf16", Hkv, D)[0].transpose(1, 0, 2))
+        assert np.array_equal(got[0][:, :4], cache[0][:, :4].view(np.int16)) and np.array_equal(got[0][:, 4 + R:], cache[0][:, 4 + R:].view(np.int16))
