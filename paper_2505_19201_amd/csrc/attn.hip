@@ -31,6 +31,7 @@
 // tensors (the small configuration).
 #include "common.h"
 #include "dream_tuning.h"
+#include "lds_tiles.h"
 #include <math.h>
 #include <type_traits>
 
@@ -373,14 +374,6 @@ __device__ __forceinline__ void tiles_compute(const uint16_t *stage, int key0, i
     tiles_scores<D, QG, KT>(stage, qf, sacc, c, g);
     __builtin_amdgcn_sched_barrier(0);
     tiles_softmax_pv<D, QG, KT, MW>(stage, key0, P, key_end, n_tree, scale_log2, sacc, qmask, st, c, g);
-}
-
-// LDS traffic inside one wave needs no barrier, only program order.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // KT: 32-key tiles handled per step (per barrier, per softmax update); PFD: steps kept in flight in registers;
@@ -752,8 +745,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 // keys x 33 rows of 2 heads, head_dim 256, 27.3 / 20.6 us; 8 sequences x 8 KV heads x up to 1340 keys x 60 rows of 4 heads 23.2 / 20.8 us
 // (start to scores 3 us, loop 11, states and rows 2.3); 16 sequences of that, in four slots, 40.6 / 33.5 us.
 //
-// 16-byte chunk i of row r of a K tile sits at i ^ (r mod 16) (at head_dim 64, two rows to a bank line: i ^ (r/2 mod 8)), and pair i of the
-// chunks of a V row at i ^ (r mod 8) (slices of 64 columns: r/2 mod 4, of 32: r/4 mod 2), so that neither the 16-byte reads of K nor the
+// The 16-byte pieces of a tile's rows lie swapped (lds_tiles.h), so that neither the 16-byte reads of K nor the
 // transposing reads of V meet in a bank.  The loads need 16-byte aligned tensors: others take attn_bf16_kernel.
 template <int D, int DS, int QT, int QS, int KG, int KEYS>
 struct RowsGeom {
@@ -793,14 +785,6 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 
 // x / d for x * d below 2^32: magic = ceil(2^32 / d), or 0 for d = 1
 __device__ __forceinline__ int quick_div(int x, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)x, magic) : x; }
-
-// what the rows of load instruction j of a tile add to a lane's 16-byte chunk (in bytes), and the pair number that row r of V is swizzled by
-template <int ROW>
-__device__ __forceinline__ constexpr int swizzle_k(int j) { return ROW == 128 ? ((j * 4) & 7) * 16 : ((j * (1024 / ROW)) & 15) * 16; }
-template <int ROW>
-__device__ __forceinline__ constexpr int swizzle_v(int j) { return ROW <= 128 ? 0 : ((j * (1024 / ROW)) & 7) * 32; }
-template <int ROW>
-__device__ __forceinline__ constexpr int pair_of_v(int r) { return ROW == 64 ? (r >> 2) & 1 : ROW == 128 ? (r >> 1) & 3 : r & 7; }
 
 // The SLOTS adjacent waves of a key group wait for each other: each writes how often it has been here and reads the others' counts until they
 // have come as far.  The LDS operations of a wave take effect in order, so what a wave wrote or read before, the others find done.
@@ -878,7 +862,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     static_assert(G::LOADERS == 1 || ((swizzle_k<KROW>(KJ) & swizzle_k<KROW>(KJ - 1)) == 0 && (swizzle_v<VROW>(VJ) & swizzle_v<VROW>(VJ - 1)) == 0), "loaders");
     const int half = G::LOADERS == 2 ? qs & 1 : 0, k_half = half * (KJ * (64 / LPK)), v_half = half * (VJ * (64 / LPV));
     const int krow = lane / LPK, vrow = lane / LPV;
-    const int kl = (((lane % LPK) ^ (D == 64 ? krow >> 1 : krow)) * 16) ^ (half * swizzle_k<KROW>(KJ)), vl = (((lane % LPV) ^ (2 * pair_of_v<VROW>(vrow))) * 16) ^ (half * swizzle_v<VROW>(VJ));
+    const int kl = piece_k<KROW>(lane) ^ (half * swizzle_k<KROW>(KJ)), vl = piece_v<VROW>(lane) ^ (half * swizzle_v<VROW>(VJ));
     auto issue_k = [&](int t, int at) {
         const uint32_t dst = scalar(lds0 + at + half * (KJ * 1024));
         if ((t + 1) * KEYS <= kv_len) {
@@ -964,12 +948,12 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     __syncthreads();
     // ---- query fragments
     bf16x8 qf[QT][NKS];
-    const int foff = c * KROW + ((g ^ (D == 64 ? c >> 1 : c)) * 16);
+    const int foff = fragment_k<KROW>(c, g);
 #pragma unroll
     for (int qt = 0; qt < QT; qt++)
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(smem_raw + G::q_at(qs * QT + qt) + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
+            qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(smem_raw + G::q_at(qs * QT + qt) + at_key_step(foff, ks));
     if constexpr (!G::Q_APART)
         __syncthreads();                // every wave has its queries
     if constexpr (QS == 1) {
@@ -1013,7 +997,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         for (int dt = 0; dt < NDT; dt++)
             o[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int trow = g * 4 + (c >> 2), voff = trow * VROW + pair_of_v<VROW>(trow) * 32 + (c & 3) * 8;
+    const int voff = fragment_v<VROW>(c, g);
     const float scale_log2 = a.scale_log2;
 
     // S^T = K Q^T of the tile at `at`: its fragments are all requested first
@@ -1023,7 +1007,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         for (int ks = 0; ks < NKS; ks++)
 #pragma unroll
             for (int h = 0; h < NH; h++)
-                kf[ks][h] = *reinterpret_cast<const bf16x8 *>(smem_raw + at + h * 16 * KROW + (foff ^ ((ks & 3) * 64)) + (ks >> 2) * 256);
+                kf[ks][h] = *reinterpret_cast<const bf16x8 *>(smem_raw + at + h * 16 * KROW + at_key_step(foff, ks));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int h = 0; h < NH; h++)
@@ -1042,7 +1026,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     auto read_v = [&](int at, int dt0, auto &vf) {
 #pragma unroll
         for (int i = 0; i < (int)(sizeof vf / sizeof vf[0]); i++) {
-            const unsigned char *vp = smem_raw + at + (voff ^ (((dt0 + i) & 7) * 32)) + ((dt0 + i) >> 3) * 256;
+            const unsigned char *vp = smem_raw + at + at_column_tile(voff, dt0 + i);
 #pragma unroll
             for (int h = 0; h < NH; h++)
                 vf[i][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vp + h * 16 * VROW));

@@ -41,6 +41,43 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
+// LDS traffic inside one wave needs no barrier, only program order.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Wave-wide reductions in a fixed order, in every lane: rotations inside the rows of 16 lanes (register moves; a shuffle is a trip through
+// LDS), then the four rows' values as scalars.
+template <int ROT>
+__device__ __forceinline__ float row_rotate(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));   // row_ror:ROT
+}
+__device__ __forceinline__ float of_row(float v, int row) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16)); }
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, row_rotate<8>(v));
+    v = fmaxf(v, row_rotate<4>(v));
+    v = fmaxf(v, row_rotate<2>(v));
+    return fmaxf(v, row_rotate<1>(v));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = row_max(v);
+    return fmaxf(fmaxf(of_row(v, 0), of_row(v, 1)), fmaxf(of_row(v, 2), of_row(v, 3)));
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    v += row_rotate<1>(v);
+    return (of_row(v, 0) + of_row(v, 1)) + (of_row(v, 2) + of_row(v, 3));
+}
+
 // 16 bytes per lane from base + offset straight to LDS: lane i's land at lds + 16 * i.  Inline assembly, because the compiler
 // makes every LDS read wait for all such loads in flight; the caller waits with s_waitcnt vmcnt.  (Loads that the compiler
 // counts itself are only waited for longer than needed beside these.)  ONCE: with the nontemporal hint.

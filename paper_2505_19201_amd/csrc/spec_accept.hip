@@ -43,30 +43,6 @@ __device__ __forceinline__ float load_logit(const void *p, int64_t i)
     return BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[i]) : reinterpret_cast<const float *>(p)[i];
 }
 
-// Wave-wide reductions in a fixed order, in every lane: rotations inside the rows of 16 lanes (register moves; a shuffle is a trip through
-// LDS), then the four rows' values as scalars.
-template <int ROT>
-__device__ __forceinline__ float rotate(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));   // row_ror:ROT
-}
-__device__ __forceinline__ float of_row(float v, int row) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16)); }
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v += rotate<8>(v);
-    v += rotate<4>(v);
-    v += rotate<2>(v);
-    v += rotate<1>(v);
-    return (of_row(v, 0) + of_row(v, 1)) + (of_row(v, 2) + of_row(v, 3));
-}
-__device__ __forceinline__ float wave_max(float v)
-{
-    v = fmaxf(v, rotate<8>(v));
-    v = fmaxf(v, rotate<4>(v));
-    v = fmaxf(v, rotate<2>(v));
-    v = fmaxf(v, rotate<1>(v));
-    return fmaxf(fmaxf(of_row(v, 0), of_row(v, 1)), fmaxf(of_row(v, 2), of_row(v, 3)));
-}
 __device__ __forceinline__ int block_min_int(int v, int *red, int tid)
 {
     for (int off = 32; off > 0; off >>= 1)

@@ -45,17 +45,12 @@ __device__ __forceinline__ int index_of(uint64_t k) { return (int)(0xffffffffu -
 // combined with its rotations by 8, 4, 2 and 1 lanes (DPP row_ror: a VALU move, no LDS round trip), which
 // leaves the row maximum in all 16 lanes; the four row maxima are then read as scalars.
 template <int ROT>
-__device__ __forceinline__ uint64_t row_rotate(uint64_t k)
+__device__ __forceinline__ uint64_t row_rotate_u64(uint64_t k)
 {
     constexpr int ctrl = 0x120 + ROT;   // DPP row_ror:ROT
     const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)k, ctrl, 0xf, 0xf, false);
     const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(k >> 32), ctrl, 0xf, 0xf, false);
     return ((uint64_t)hi << 32) | lo;
-}
-template <int ROT>
-__device__ __forceinline__ float row_rotate_f(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));
 }
 __device__ __forceinline__ uint64_t lane_value(uint64_t k, int lane)
 {
@@ -63,48 +58,17 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t k, int lane)
 }
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t k)
 {
-    uint64_t o = row_rotate<8>(k);
+    uint64_t o = row_rotate_u64<8>(k);
     k = o > k ? o : k;
-    o = row_rotate<4>(k);
+    o = row_rotate_u64<4>(k);
     k = o > k ? o : k;
-    o = row_rotate<2>(k);
+    o = row_rotate_u64<2>(k);
     k = o > k ? o : k;
-    o = row_rotate<1>(k);
+    o = row_rotate_u64<1>(k);
     k = o > k ? o : k;
     const uint64_t a = lane_value(k, 0), b = lane_value(k, 16), c = lane_value(k, 32), d = lane_value(k, 48);
     const uint64_t ab = a > b ? a : b, cd = c > d ? c : d;
     return ab > cd ? ab : cd;
-}
-
-// Sum and maximum over the wave in every lane: rotations inside the rows of 16 lanes, then the four row values as scalars.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v += row_rotate_f<8>(v);
-    v += row_rotate_f<4>(v);
-    v += row_rotate_f<2>(v);
-    v += row_rotate_f<1>(v);
-    auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
-    return (row(0) + row(16)) + (row(32) + row(48));
-}
-__device__ __forceinline__ float row_max(float v)
-{
-    v = fmaxf(v, row_rotate_f<8>(v));
-    v = fmaxf(v, row_rotate_f<4>(v));
-    v = fmaxf(v, row_rotate_f<2>(v));
-    return fmaxf(v, row_rotate_f<1>(v));
-}
-__device__ __forceinline__ float wave_max(float v)
-{
-    v = row_max(v);
-    auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
-    return fmaxf(fmaxf(row(0), row(16)), fmaxf(row(32), row(48)));
-}
-
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // What bounds it is latency, not bytes (one LLaVA level is 0.6 MB): the chunk is read once, and between the loads and the

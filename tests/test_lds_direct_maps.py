@@ -1,19 +1,32 @@
 """Host model of the LDS layout of the attention kernels whose tiles go from memory straight to LDS (attend_rows in csrc/attn.hip; the
-areas in test_lds_index_maps.py are those of tiles staged in registers).  Restated from the source: where every lane of a load
-instruction puts its 16 bytes, where the fragment reads look for them, and which banks the lanes of a read touch together."""
+areas in test_lds_index_maps.py are those of tiles staged in registers).  The address maps are the kernel's own (csrc/lds_tiles.h, built for the host); this
+file says what they have to do: where every lane of a load instruction puts its 16 bytes, where the fragment reads look for them, and which banks the lanes of a read
+touch together."""
+import ctypes
+import os
+import subprocess
+
 import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def maps(tmp_path_factory):
+    """tests/c/lds_tiles_check.cpp, which instantiates the header's templates for every row size."""
+    out = str(tmp_path_factory.mktemp("maps") / "lds_tiles_check.so")
+    csrc = os.path.join(os.path.dirname(HERE), "paper_2505_19201_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wall", "-Werror", "-I" + csrc, os.path.join(HERE, "c", "lds_tiles_check.cpp"), "-o", out], check=True)
+    global LIB
+    LIB = ctypes.CDLL(out)
 
 
 def swizzle_k(row_bytes, j):
-    return ((j * 4) & 7) * 16 if row_bytes == 128 else ((j * (1024 // row_bytes)) & 15) * 16
+    return LIB.map_swizzle_k(row_bytes, j, 0)
 
 
 def swizzle_v(row_bytes, j):
-    return 0 if row_bytes <= 128 else ((j * (1024 // row_bytes)) & 7) * 32
-
-
-def pair_of_v(row_bytes, r):
-    return (r >> 2) & 1 if row_bytes == 64 else (r >> 1) & 3 if row_bytes == 128 else r & 7
+    return LIB.map_swizzle_v(row_bytes, j, 0)
 
 
 def loaded(row_bytes, keys, kind):
@@ -22,11 +35,11 @@ def loaded(row_bytes, keys, kind):
     at = {}
     for j in range(keys * row_bytes // 1024):
         for lane in range(64):
-            row, ch = lane // lanes, lane % lanes
+            row = lane // lanes
             if kind == "k":
-                chunk = ((ch ^ (row >> 1 if row_bytes == 128 else row)) * 16) ^ swizzle_k(row_bytes, j)
+                chunk = LIB.map_piece_k(row_bytes, lane, 0) ^ swizzle_k(row_bytes, j)
             else:
-                chunk = ((ch ^ (2 * pair_of_v(row_bytes, row))) * 16) ^ swizzle_v(row_bytes, j)
+                chunk = LIB.map_piece_v(row_bytes, lane, 0) ^ swizzle_v(row_bytes, j)
             assert 0 <= chunk < row_bytes
             for i in range(0, 16, 2):
                 at[j * 1024 + lane * 16 + i] = (j * (64 // lanes) + row, chunk + i)
@@ -44,8 +57,8 @@ def test_two_loaders_put_the_tile_where_one_does(row_bytes, keys, kind):
     for half in range(2):
         for j in range(n):
             for lane in range(64):
-                row, ch = lane // lanes, lane % lanes
-                own = (ch ^ (row if kind == "k" else 2 * pair_of_v(row_bytes, row))) * 16 ^ half * swizzle(row_bytes, n)
+                row = lane // lanes
+                own = (LIB.map_piece_k if kind == "k" else LIB.map_piece_v)(row_bytes, lane, 0) ^ half * swizzle(row_bytes, n)
                 for i in range(0, 16, 2):
                     at[half * n * 1024 + j * 1024 + lane * 16 + i] = (half * n * (64 // lanes) + j * (64 // lanes) + row, (own ^ swizzle(row_bytes, j)) + i)
     assert at == loaded(row_bytes, keys, kind)
@@ -67,7 +80,7 @@ def test_key_fragments(D, keys):
             addresses = []
             for lane in range(64):
                 c, g = lane & 15, lane >> 4
-                a = h * 16 * row_bytes + ((c * row_bytes + (g ^ (c >> 1 if D == 64 else c)) * 16) ^ ((ks & 3) * 64)) + (ks >> 2) * 256
+                a = h * 16 * row_bytes + LIB.map_at_key_step(LIB.map_fragment_k(row_bytes, c, g), ks)
                 addresses.append(a)
                 for e in range(8):               # lane (c, g): key c of the half, dimensions 32 ks + 8 g ..
                     assert at[a + 2 * e] == (h * 16 + c, (ks * 32 + g * 8 + e) * 2)
@@ -85,7 +98,7 @@ def test_value_fragments(DV, keys):
             for lane in range(64):
                 c, g = lane & 15, lane >> 4
                 row = g * 4 + (c >> 2)
-                a = h * 16 * row_bytes + ((row * row_bytes + pair_of_v(row_bytes, row) * 32 + (c & 3) * 8) ^ ((dt & 7) * 32)) + (dt >> 3) * 256
+                a = h * 16 * row_bytes + LIB.map_at_column_tile(LIB.map_fragment_v(row_bytes, c, g), dt)
                 addresses.append(a)
                 for e in range(4):               # the transposing read takes 4 columns of row g*4 + c/4 from lane (c, g)
                     assert at[a + 2 * e] == (h * 16 + row, (dt * 16 + (c & 3) * 4 + e) * 2)
