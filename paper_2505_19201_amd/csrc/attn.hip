@@ -1929,7 +1929,7 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     if (max_kv_len < n_tree || max_kv_len > d->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: max_kv_len %lld outside [n_tree, s_max]", who, (long long)max_kv_len);
     const bool direct = !((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) & 15);
-    Plan p;
+    Plan p = {};
     // (unaligned tensors get what the workspace was asked for, never more splits than that)
     make_plan(d, n_q, max_kv_len, direct, caches_near(d, max_kv_len, !include_self && direct), &p);
     if (n_tree > 64 && d->dtype == DREAM_BF16)
@@ -1970,6 +1970,8 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     if (!variant)
         return fail(DREAM_ERR_UNSUPPORTED, "%s: no kernel variant for head_dim %d with launch parameters (%d, %d, %d)", who, d->head_dim,
                     p.wave_mode ? p.wave_nw : p.qg, p.wave_mode ? p.wave_ds : p.kt, p.wave_mode ? p.wave_qt : p.pfd);
+    if (p.wave_mode && (n_tree > 64 || a.group > 4 || a.group * n_q > 16 * 16 || p.n_streams > 256))
+        return fail(DREAM_ERR_UNSUPPORTED, "%s: the plan names a kernel that cannot serve %d streams of %d rows", who, p.n_streams, a.group * n_q);
     return variant->launch(a, p, st);
 }
 
@@ -1978,7 +1980,7 @@ size_t workspace_for(const dream_attn_desc *d, int n_q, int64_t max_kv_len)
     if (!d || d->n_kv_heads < 1 || d->n_q_heads < 1 || d->n_q_heads % d->n_kv_heads || n_q < 1 || max_kv_len < 1 ||
         d->batch < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
-    Plan p;
+    Plan p = {};
     make_plan(d, n_q, max_kv_len, true, caches_near(d, max_kv_len, false), &p);
     return p.total;
 }
@@ -2008,7 +2010,7 @@ int dream_attn_plan_describe(const dream_attn_desc *desc, int32_t n_q, int64_t m
         return rc;
     if (n_q < 1 || max_kv_len < 1 || max_kv_len > desc->s_max)
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= max_kv_len <= s_max", who);
-    Plan p;
+    Plan p = {};
     make_plan(desc, n_q, max_kv_len, true, caches_near(desc, max_kv_len, false), &p);
     if (n_q > 64 && desc->dtype == DREAM_BF16)   // more than 64 query rows: taken as a verification call over a tree of n_q nodes
         make_wide_plan(desc, n_q, &p);
