@@ -293,6 +293,22 @@ def test_four_slots_at_tile_edges(gu, B, Hq, Hkv, D, T):
     assert np.abs(got - want).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T", [(20, 32, 8, 10), (32, 16, 8, 24), (17, 32, 8, 13)])
+def test_two_slots_with_few_query_tiles(gu, B, Hq, Hkv, T):
+    """One workgroup for a KV head's three or four query tiles: the second slot's last tile is empty or half full."""
+    for kv_len in (T, 64, 65, 128, 160, 257, 700):
+        cfg = _cfg("few", "bf16", B, Hq, Hkv, 128, kv_len - T, 0, T, min(4, T - 1), 60)
+        x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) // (1 + b % 3) for b in range(B)])
+        assert gu.verify_plan(x).startswith("attn_pair_kernel<128,1,2> workgroups=%d " % (B * Hkv)), gu.verify_plan(x)
+        got, lse = gu.run_verify(x)
+        oracle.set_threads(16)
+        try:
+            want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+        finally:
+            oracle.set_threads(1)
+        assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3, kv_len
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,T", [(5, 32, 32, 16), (8, 32, 32, 7), (13, 16, 16, 10), (30, 16, 8, 8)])
 def test_one_query_tile_of_every_head_unsliced(gu, B, Hq, Hkv, T):
     """More KV heads than two slices leave CUs for, one query tile each: no, fewer and more steps than waves, with four waves and with eight."""

@@ -247,6 +247,20 @@ def test_statistics_formed_by_the_walk(gu, B, T, V, dtype, temperature, polls):
 
 
 @pytest.mark.parametrize("polls", [0, -1])
+@pytest.mark.parametrize("B,T,V,dtype", [(1, 5, 1048577, "f32"), (2, 6, 1060003, "bf16")])
+def test_segments_of_two_chunks_with_statistics_beforehand(gu, B, T, V, dtype, polls):
+    """More than 64 chunks of 16384 tokens: a segment is two of them, the last one alone in its segment or not."""
+    import paper_2505_19201_amd as dream
+    assert not _formed_by_the_walk(B, T, V, dtype)
+    dream.dream_set_accept_spin(polls)
+    try:
+        for i in range(3):
+            _case(gu, B, T, 3, V, dtype, 4970 + V + i, noise=1.0, min_clear=0.0)
+    finally:
+        dream.dream_set_accept_spin(0)
+
+
+@pytest.mark.parametrize("polls", [0, -1])
 def test_every_branch_with_statistics_formed_by_the_walk(gu, polls):
     """Accepted as first, second and third child, all of one, two and three children rejected, a walk that ends at a leaf."""
     import paper_2505_19201_amd as dream
