@@ -58,6 +58,7 @@ struct AttnArgs {
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
     int32_t once;            // the caches will not be read again before others have displaced them (the ONCE forms of attend_rows)
+    int32_t swap;            // attend_rows: the order of RowsGeom::SWAPPED is used
 };
 
 // Visibility of the tree nodes to one query: bit (a % 64) of word a / 64 is set iff node a is visible.  MW = 1 serves
@@ -919,7 +920,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             issue_v(t, at + G::KTILE);
     };
     const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
-    const int odd = G::SWAPPED ? unit & 1 : 0;
+    const int odd = G::SWAPPED && a.swap ? unit & 1 : 0;
     auto tile = [&](int i) { return kg + KG * (G::SWAPPED && (i | 1) < n_steps ? i ^ odd : i); };   // the key tile of this wave's step i
     const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
     const uint32_t meet = lds0 + G::MEET_OFF;
@@ -1954,6 +1955,9 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     // but 5.5 MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2: never).
     // (A whole LLaVA draft: 4 sequences, 110 MB 324 / 332, 147 MB 364 / 371; 8 sequences, 156 MB 441 / 424, 192 MB 482 / 422, 294 MB 633 / 544).
     a.once = !caches_near(d, max_kv_len, !include_self);
+    // (In a draft, whose caches come from the memory-side cache, only while the heads of an XCD fit its 4 MB L2 or nearly: 3 sequences of 32 heads, 10 rows, 1657 keys, 5.1 MB an XCD, us
+    // with the order / without: 10.1 / 9.5, 2233 keys 12.1 / 11.1; 4 sequences of 1145 keys, 4.7 MB, 7.4 / 7.7; a whole level of one sequence 9.4 / 9.6.)
+    a.swap = include_self || (int64_t)ceil_div((int64_t)d->batch * d->n_kv_heads, 8) * max_kv_len * d->head_dim * 4 < 5000000;
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;

@@ -381,7 +381,8 @@ def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
         assert np.abs(got - base).max() <= TOL["bf16"], name
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D,line", [(1, 32, 32, 128, 90), (2, 16, 8, 128, 100), (1, 32, 32, 64, 112), (2, 16, 8, 256, 72), (3, 24, 8, 128, 152), (3, 16, 16, 64, 112)])
+@pytest.mark.parametrize("B,Hq,Hkv,D,line", [(1, 32, 32, 128, 90), (2, 16, 8, 128, 100), (1, 32, 32, 64, 112), (2, 16, 8, 256, 72), (3, 24, 8, 128, 152), (3, 16, 16, 64, 112),
+                                                  (3, 32, 32, 64, 60)])      # (the last: more keys than an XCD's L2 holds, steps in their own order)
 def test_long_ranges_of_a_draft_cache(gu, B, Hq, Hkv, D, line):
     """Cross-attention over a cache that the memory-side cache holds stays one launch for longer than the plan of a verification says: lengths where the two differ,
     the last of them and the next, ragged sequences; a cache off the 16-byte boundaries in the workspace that the query returned."""
