@@ -175,7 +175,7 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
 // were slower at short hidden dimensions and no faster at long ones.)
 // Measured per call of three maps (Q, K, V), shared stages / here: 80 rows SmolVLM 11.4 / 10.3 us, LLaVA 40.9 / 40.0, Pixtral 27.1 / 27.3, 40 rows
 // 9.1 / 7.2, 30.4 / 28.4, 21.0 / 20.3 with the weights in HBM; as much of them as the memory-side cache kept from the level before, 80 rows LLaVA
-// 34.7 / 28.1, Pixtral 21.9 / 19.1, 20 rows LLaVA 25.3 / 18.0.  Whole drafts of 6 levels are 8 to 19 % faster, the expansion's share included.
+// 34.7 / 28.1, Pixtral 21.9 / 19.1, 20 rows LLaVA 25.3 / 18.0.  Whole drafts of 6 levels are 4 to 12 % faster, the expansion's share included.
 // At 10 rows project_kernel and this one are equal within 5 % but for LLaVA (warm 16.5 against 18.0).
 constexpr int RW = 8;                                // waves per workgroup
 constexpr int STEP = 64, STEP_BYTES = STEP * 2;      // elements, bytes of a row per step
@@ -192,15 +192,9 @@ template <int MT, int NT>
 __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
 {
     using G = RowsGeom<MT, NT>;
-    // the workgroups of a weight tile have ids congruent mod 8 (same XCD), and few lie between them
-    int tile = blockIdx.x, group = 0;
-    if (args.row_groups > 1) {
-        const int octet = tile >> 3;
-        group = octet % args.row_groups;
-        tile = octet / args.row_groups * 8 + (tile & 7);
-        if (tile >= args.job[args.n_jobs - 1].tile_end)
-            return;
-    }
+    // one row group: a line of workgroups; several: 8 tiles x groups x eighths of the tiles, so that the workgroups of a weight tile have ids congruent
+    // mod 8 (same XCD) and few lie between them (a tile past the last repeats it and stores nothing)
+    const int tile = blockIdx.z * 8 + blockIdx.x, group = blockIdx.y;
     const ProjView a = select_job(args, tile);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -326,17 +320,18 @@ int ensure_rows_lds(const char *who)
 }
 
 template <int MT, int NT>
-int launch_rows(unsigned wgs, hipStream_t st, const ProjArgs &a)
+int launch_rows(int wgs, hipStream_t st, const ProjArgs &a)
 {
     if (int rc = ensure_rows_lds<MT, NT>("dream_project_rows"))
         return rc;
-    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), dim3(wgs), dim3(64 * RW), (RowsGeom<MT, NT>::LDS_BYTES), st, a);
+    const dim3 grid = a.row_groups == 1 ? dim3(wgs) : dim3(8, a.row_groups, ceil_div(wgs, 8));
+    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), grid, dim3(64 * RW), (RowsGeom<MT, NT>::LDS_BYTES), st, a);
     return check_launch("project_rows_kernel");
 }
 
 // The variants, by row tiles per pass and feature tiles per workgroup: project_init walks the table, a call picks from it.
 struct RowsVariant {
-    int (*launch)(unsigned, hipStream_t, const ProjArgs &);
+    int (*launch)(int, hipStream_t, const ProjArgs &);
     int (*ensure)(const char *);
 };
 #define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, max_nt(MT)>, &ensure_rows_lds<MT, max_nt(MT)>}}
@@ -406,7 +401,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     // Row tiles per pass (2 to 8: there are at least 17 rows), feature tiles per workgroup and how many workgroups share the rows of a feature tile: the fewest bytes
     // through the busiest CU.  Up to 128 rows are one pass; above, a workgroup goes through as few passes as there have to be, of about equal size, or every pass is a workgroup of its
     // own, which leaves fewer CUs idle and reads weights that another pass has brought to L2.  us, one after the other / side by side: LLaVA 256 rows 72.3 / 53.8 (weights in HBM 84.2 / 66.0),
-    // 144 rows 50.1 / 40.3, 1000 rows 266 / 205; SmolVLM 192 rows 19.3 / 17.3, 1000 rows 83.8 / 66.6; hidden dimension 768, 1000 rows 32.7 / 16.8.
+    // 144 rows 50.1 / 40.3, 1000 rows 266 / 205; SmolVLM 192 rows 19.3 / 17.3, 1000 rows 83.8 / 66.6; hidden dimension 768, 1000 rows 32.7 / 16.4.
     const int m_tiles = ceil_div(a.m_total, 16), passes = ceil_div(m_tiles, MAX_MT);
     int mt = 0, nt = 1;
     int64_t best = 0;
@@ -414,10 +409,11 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         int64_t wgs = 0;
         for (int j = 0; j < n_jobs; j++)
             wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, n);
+        const bool fits = groups <= 65535 && wgs <= 8 * 65535 && (wgs + 7) / 8 * 8 * groups <= (1 << 22);      // (a grid's extents, its 2^32 threads)
         if (groups > 1)
-            wgs = (int64_t)ceil_div(wgs, 8) * 8 * groups;
+            wgs = (wgs + 7) / 8 * 8 * groups;
         const int64_t cost = (wgs + 255) / 256 * (groups > 1 ? 16 * (m + n) * 11 : (a.m_total + 16 * n * passes) * 10);   // (Gemma3, 1000 rows: 8 % fewer, and 5 % slower)
-        if (mt == 0 || (cost < best && wgs <= (1 << 22))) {      // (a grid has fewer than 2^32 threads)
+        if (mt == 0 || (cost < best && (groups == 1 || fits))) {
             best = cost;
             mt = m;
             nt = n;
@@ -436,7 +432,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
         a.job[j].tile_end = wgs;
     }
-    return ROWS[mt - 2][nt - 1].launch(a.row_groups > 1 ? ceil_div(wgs, 8) * 8 * a.row_groups : wgs, st, a);
+    return ROWS[mt - 2][nt - 1].launch(wgs, st, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,
