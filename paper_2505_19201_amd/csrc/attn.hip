@@ -1439,7 +1439,8 @@ const Decomposition DECOMPOSITIONS[] = {
 //   head_dim 64: 32 heads, 1 sequence, 8 rows, 64 workgroups, 60 tiles 10.4 / 10.7, 64 tiles 11.4 / 10.7; 64 rows, 256 workgroups, 90 tiles 13.5 / 13.9, 104 tiles
 //   15.1 / 14.8; 3 sequences of 8 rows, against two splits, 104 tiles 19.8 / 22.6
 //   head_dim 256, 8 KV heads, groups of 2: 64 rows 56 tiles 20.2 / 21.7, 64 tiles 22.5 / 21.4; 2 sequences of 8 rows, 64 workgroups, 36 tiles 16.0 / 16.1, 44 tiles 18.5 / 17.1
-// While the memory-side cache holds the caches (`near`), every workgroup pulls faster and few of them are no reason to change early: at most 8 % behind at the last length
+// While the memory-side cache holds the caches (`near`), every workgroup pulls faster and few of them are no reason to change early (but for groups of 3 heads of 256, whose rows fill
+// few slices: 3 sequences of 8 KV heads, 44 tiles equal, 63 tiles 25.5 / 22.2): at most 8 % behind at the last length
 // over 16 groupings, 1 to 8 sequences, 1 to 60 rows and 28 to 160 tiles, where the lines above lost up to 1.5x.  us, single launch / general plan, cross-attention of 10 rows: head_dim 128, 32 heads,
 // 1 sequence 64 tiles 10.8 / 13.2, 90 tiles 15.2 / 15.2, 100 tiles 16.3 / 15.6; 8 KV heads, groups of 2, 3 sequences 100 tiles 15.9 / 15.9, 112 tiles 17.6 / 16.7, groups of 4, 4 sequences 80 tiles
 // 14.6 / 18.2, 126 tiles 19.9 / 21.3; head_dim 64, 32 heads, 1 sequence 64 tiles 8.2 / 9.9, 112 tiles 11.7 / 11.9, 126 tiles 12.9 / 12.3; against two splits, 3 sequences, 126 tiles 17.2 / 25.4;
@@ -1450,7 +1451,8 @@ int64_t longest_range(const dream_attn_desc *d, int n_qtiles, int64_t workgroups
     const int64_t splits = 256 / ((int64_t)d->batch * d->n_kv_heads * ceil_div(n_qtiles, 4));
     if (splits < 3)
         return d->head_dim == 256 ? (G == 1 ? 96 : 128) : near || (slots > 1 && G > 1) ? 1 << 30 : G == 1 ? 120 : 160;
-    const int64_t tiles = near ? std::max(line * 5 / 4, d->head_dim == 64 ? 112 : d->head_dim == 256 ? 72 : G == 1 ? 90 : 100) : line * (384 + workgroups) / 640;
+    const int64_t cold = line * (384 + workgroups) / 640;
+    const int64_t tiles = !near ? cold : d->head_dim == 64 ? std::max(line * 5 / 4, 112) : d->head_dim == 128 ? std::max(line * 5 / 4, G == 1 ? 90 : 100) : G == 3 ? std::max<int64_t>(cold, 45) : std::max(line * 5 / 4, 72);
     return splits == 4 ? tiles * 6 / 5 : splits == 3 ? tiles * 8 / 5 : tiles;
 }
 
