@@ -47,13 +47,14 @@ struct AttnArgs {
     float *lse;
     float *part;             // [groups, splits, 4 waves, state] per-wave states of every split
     int32_t n_q_heads, n_kv_heads, group;
-    int32_t n_q, n_tree, include_self;
+    int32_t n_q;
+    uint32_t spread;         // attend_rows: ceil(2^16 / Hkv) where the KV heads of all sequences are numbered together, 0 where Hkv is a multiple of 8
+    int32_t n_streams;       // B * Hkv * n_splits
+    int32_t n_tree, include_self;
     int32_t tiles_per_head;  // 16-row query tiles per head
     int32_t n_qg;            // query groups per KV head
     int32_t mask_words;      // 64-bit words of a node's visibility mask: ceil(n_tree / 64)
     int32_t n_splits;
-    int32_t n_streams;       // B * Hkv * n_splits
-    uint32_t spread;         // attend_rows: ceil(2^16 / Hkv) where the KV heads of all sequences are numbered together, 0 where Hkv is a multiple of 8
     int64_t s_max;
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
@@ -827,7 +828,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     // per sequence left XCDs idle (24 sequences of 4 KV heads, 33 rows of 4 heads, 340 keys: 27.1 us, 15.0 in turn)
     int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z;
     const int unit = blockIdx.x >> 3, ds = unit % DS;
-    if (a.spread) {
+    if (__builtin_expect(a.spread != 0, 0)) {
         const int stream = kvh;
         b = (int)((stream * a.spread) >> 16);          // exact: fewer than 264 streams
         kvh = stream < a.n_streams ? stream - b * a.n_kv_heads : a.n_kv_heads;
