@@ -49,12 +49,12 @@ struct AttnArgs {
     int32_t n_q_heads, n_kv_heads, group;
     int32_t n_q;
     uint32_t spread;         // attend_rows: ceil(2^16 / Hkv) where the KV heads of all sequences are numbered together, 0 where Hkv is a multiple of 8
-    int32_t n_streams;       // B * Hkv * n_splits
     int32_t n_tree, include_self;
     int32_t tiles_per_head;  // 16-row query tiles per head
     int32_t n_qg;            // query groups per KV head
     int32_t mask_words;      // 64-bit words of a node's visibility mask: ceil(n_tree / 64)
     int32_t n_splits;
+    int32_t n_streams;       // B * Hkv * n_splits
     int64_t s_max;
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
