@@ -1199,7 +1199,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     static_assert(NDT % UPW == 0, "a wave's column tiles belong to one query tile");
     const int qt = wave * UPW / NDT, dt0 = wave * UPW % NDT;
     const int f = row0 + qt * 16 + c, hh = quick_div(min(f, n_rows - 1), a.nq_magic), row = f - hh * a.n_q, head = kvh * a.group + hh;
-    uint16_t *op = reinterpret_cast<uint16_t *>(a.out) + (((int64_t)b * a.n_q + row) * a.n_q_heads + head) * D + ds * G::DV + dt0 * 16 + g * 4;
+    uint16_t *op = reinterpret_cast<uint16_t *>(a.out) + (((int64_t)b * a.n_q + row) * a.n_q_heads + head) * D + ds * G::DV + dt0 * 16;
     __syncthreads();
     if (wave * UPW >= UNITS)
         return;
@@ -1222,17 +1222,35 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         for (int u = 0; u < UPW; u++)
             sum[u] += src[u * 64] * wgt[k];
     }
-    if (f >= n_rows)
-        return;
+    // The rows leave with the nontemporal hint, 64 adjacent bytes of each per instruction where a wave has two column tiles side by side: the launch is not over
+    // before its rows have left the L2s.  40 launches of 8 sequences x 8 KV heads x 60 rows of 4 heads (3.9 MB of rows each), us: 32-byte pieces 821, 64-byte pieces 807, with
+    // the hint 804, no rows at all 774; the same rows 40 launches later, still in the memory-side cache, 786 -> 749.  One column tile a wave: as before.
     const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
+    uint2 ob[UPW];
 #pragma unroll
     for (int u = 0; u < UPW; u++) {
-        bf16x4 ob;
+        bf16x4 x;
 #pragma unroll
         for (int r = 0; r < 4; r++)
-            ob[r] = (__bf16)(sum[u][r] * inv);
-        *reinterpret_cast<bf16x4 *>(op + u * 16) = ob;
+            x[r] = (__bf16)(sum[u][r] * inv);
+        ob[u] = __builtin_bit_cast(uint2, x);
     }
+    if constexpr (UPW % 2 == 0) {
+#pragma unroll
+        for (int u = 0; u < UPW; u += 2) {
+            // lanes of g = 1 and 3 give their columns of tile u for those that g = 0 and 2 have of tile u + 1: 8 adjacent columns per lane
+            const auto x = __builtin_amdgcn_permlane16_swap(ob[u].x, ob[u + 1].x, false, false), y = __builtin_amdgcn_permlane16_swap(ob[u].y, ob[u + 1].y, false, false);
+            const u32x4 w = {x[0], y[0], x[1], y[1]};
+            if (f < n_rows)
+                __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(op + (u + (g & 1)) * 16 + (g >> 1) * 8));
+        }
+    } else if (f < n_rows) {
+#pragma unroll
+        for (int u = 0; u < UPW; u++)
+            *reinterpret_cast<uint2 *>(op + u * 16 + g * 4) = ob[u];
+    }
+    if (f >= n_rows)
+        return;
     if (ds == 0 && dt0 == 0 && g == 0 && a.lse)
         a.lse[((int64_t)b * a.n_q_heads + head) * a.n_q + row] = lt > 0.0f ? (mt + log2f(lt)) * 0.6931471805599453f : -INFINITY;
 }

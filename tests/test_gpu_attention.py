@@ -381,6 +381,28 @@ def test_tensors_off_16_byte_boundaries_take_another_kernel(gu):
         assert np.abs(got - base).max() <= TOL["bf16"], name
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,kernel", [(8, 32, 8, 128, 60, "attn_pair_kernel"), (16, 32, 8, 128, 60, "attn_quad_kernel"), (4, 16, 8, 256, 33, "attn_wave_kernel"),
+                                                    (1, 32, 32, 128, 60, "attn_wave_kernel")])
+def test_rows_leave_the_same_wherever_the_output_starts(gu, B, Hq, Hkv, D, T, kernel):
+    """The few-stream kernels store 16 bytes a lane, whatever the output's alignment: the same bits, nothing beside the rows."""
+    import torch
+    import paper_2505_19201_amd as dream
+    cfg = _cfg("out", "bf16", B, Hq, Hkv, D, 200, 43, T, 6, 60)
+    x = di.verify_inputs(cfg, prefix_len=[243 - 9 * (b % 5) for b in range(B)])
+    assert gu.verify_plan(x).startswith(kernel)
+    base, _ = gu.run_verify(x)
+    dev = gu.DeviceAttn(x)
+    n = base.size
+    flat = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = flat[2:2 + n].view(base.shape)
+    assert out.data_ptr() % 16 == 4
+    desc = dream.attn_desc(B, Hq, Hkv, D, dream.BF16, dev.k.shape[2])
+    ws = dream.alloc_workspace(dream.dream_tree_verify_attn_workspace(desc, T, dev.max_kv))
+    dream.dream_tree_verify_attn(desc, dev.q, dev.k, dev.v, dev.prefix_len, T, dev.parent, None, dev.max_kv, out, None, ws)
+    assert np.array_equal(out.float().cpu().numpy(), base.astype(np.float32))
+    assert (flat[:2] == 7.0).all() and (flat[2 + n:] == 7.0).all()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,line", [(1, 32, 32, 128, 90), (2, 16, 8, 128, 100), (1, 32, 32, 64, 112), (2, 16, 8, 256, 72), (3, 24, 8, 128, 152), (3, 16, 16, 64, 112),
                                                   (3, 32, 32, 64, 60)])      # (the last: more keys than an XCD's L2 holds, steps in their own order)
 def test_long_ranges_of_a_draft_cache(gu, B, Hq, Hkv, D, line):
