@@ -19,13 +19,12 @@
 // workgroups share a sequence, each sums its chunks and all exchange one float per chunk.  The masses also give the
 // draw, which then reads one chunk.  Every reduction has a fixed order, so the result is reproducible.
 // Bound by latency: the exchanges between the workgroups of a sequence follow each other, one per rejection and, with few statistics
-// beforehand, one per node.
+// beforehand, one per node.  spec_walk_small_kernel is the walk with that chain cut short; spec_walk_kernel serves what it does not take.
 //
 // Why several workgroups: one CU pulls 60 to 75 GB/s, 14 us and more for one pass over two float32 rows of 131072 tokens.
-// Measured, us per call, one read of all rows with children and a walk in chunks of 8192 tokens / now, the same tensors every call (mean of 4 inputs);
-// then 1.2 GB and more of tensors in turn, so that no row is left in a cache: 4 sequences x 60 nodes x 131072 float32 logits 57.7 / 45.9; 64.9 / 46.3,
-// 8 x 60 x 262144 bf16 103 / 67; 111 / 68, 32 x 60 x 32000 float32 93 / 51; 102 / 52, 1 x 60 x 32000 bf16 34.3 / 30.3; 32.7 / 28.4.  The very
-// first call on a new set of tensors, with its page translations to be fetched too: 71.6 / 63.5 at 4 x 60 x 131072.
+// Measured, us per call, one read of all rows with children and a walk in chunks of 8192 tokens / chunks as now, spec_walk_kernel / spec_walk_small_kernel (the first two the same
+// tensors every call, the last with several sets in turn): 4 sequences x 60 nodes x 131072 float32 logits 57.7 / 45.9 / 30.4, 8 x 60 x 262144 bf16 103 / 67 / (spec_walk_kernel),
+// 1 x 60 x 32000 bf16 34.3 / 30.3 / 20.8.
 #include "common.h"
 #include <algorithm>
 #include <type_traits>
@@ -90,6 +89,44 @@ __device__ __forceinline__ void load8(const void *base, int64_t row, int t, int 
     }
 }
 
+// The same tokens as they lie in memory, so that they can be asked for long before they are looked at.  VEC stands for `vec`, known when compiling.
+template <bool BF16, bool VEC>
+struct Raw8 {
+    uint4 w[BF16 ? 1 : 2];
+    __device__ __forceinline__ void load(const void *base, int64_t row, int t, int vocab)
+    {
+        if (VEC) {
+            const uint32_t none = BF16 ? 0xff80ff80u : 0xff800000u;    // -inf
+            w[0] = {none, none, none, none};
+            w[BF16 ? 0 : 1] = {none, none, none, none};
+            if (t < vocab) {
+                const uint4 *p = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(base) + (row + t) * (BF16 ? 2 : 4));
+                w[0] = p[0];
+                if (!BF16)
+                    w[BF16 ? 0 : 1] = p[1];
+            }
+        } else {
+            uint32_t x[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                x[j] = __float_as_uint(t + j < vocab ? load_logit<BF16>(base, row + t + j) : -INFINITY);
+            if (BF16) {
+                w[0] = {x[0] >> 16 | x[1], x[2] >> 16 | x[3], x[4] >> 16 | x[5], x[6] >> 16 | x[7]};
+            } else {
+                w[0] = {x[0], x[1], x[2], x[3]};
+                w[BF16 ? 0 : 1] = {x[4], x[5], x[6], x[7]};
+            }
+        }
+    }
+    __device__ __forceinline__ void unpack(float v[8]) const
+    {
+        const uint4 c = w[BF16 ? 0 : 1];
+        const uint32_t x[8] = {w[0].x, w[0].y, w[0].z, w[0].w, c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            v[j] = __uint_as_float(!BF16 ? x[j] : j & 1 ? x[j / 2] & 0xffff0000u : x[j / 2] << 16);
+    }
+};
 // A token's exponential times its row's normaliser, and one step of the residual chain.  Written with explicit fused operations, so that
 // every loop that evaluates a token (in registers, from memory, at one token) gives it the same bits.
 __device__ __forceinline__ float token_mass(float logit, float inv_temp, float m, float inv_z) { return __expf(fmaf(logit, inv_temp, -m)) * inv_z; }
@@ -99,6 +136,9 @@ __device__ __forceinline__ float residual(float P, float jp, float Q, float jq) 
 // softmax_stats_kernel, which the stream orders before the walk.
 constexpr int MAX_SEG = 64, MAX_VAL = 4;
 constexpr int SLOTS = 2 * MAX_VAL * MAX_SEG;
+// Units of 64 cycles from publishing to the first poll.  A word takes about 900 cycles to get to the others, and a poll that comes too early holds up the one that would find it.
+// spec_walk_small_kernel, 4 sequences x 60 nodes x 131072 float32 logits: first poll at once 36.6 us, after 320 cycles 33.5, 770 30.7, 1020 30.4, 1280 31.1, 1660 32.4.
+constexpr int POLL_DELAY = 14;
 
 // (max, sum of exp(x/temp - max)) of one chunk of one row of the first n_nodes nodes of a sequence.  z = 0: target rows;
 // z = 1: draft rows; nothing for nodes without children (a leaf's target row is summed by the walk if the walk ends there).
@@ -115,11 +155,13 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
     if (slots && chunk == 0 && node == 0 && which == 0)
         for (int i = tid; i < SLOTS; i += 256)
             slots[(int64_t)b * SLOTS + i] = 0;
-    int kids = 0;
-    for (int i = tid; i < n_tree; i += 256)
-        kids |= parent[(int64_t)b * n_tree + i] == node;
-    if (!__syncthreads_or(kids))
-        return;
+    if (n_nodes > 1) {           // (the root alone is not worth the trip to memory that tells whether it has children)
+        int kids = 0;
+        for (int i = tid; i < n_tree; i += 256)
+            kids |= parent[(int64_t)b * n_tree + i] == node;
+        if (!__syncthreads_or(kids))
+            return;
+    }
     const void *base = which ? dlogits : tlogits;
     const int64_t row = node_row * vocab;
     constexpr int STAT_CHUNK = CHUNK<PER>;
@@ -207,21 +249,22 @@ struct WalkArgs {
 // Nothing depends on the workgroups running at the same time: a wait is bounded, workgroup 0 sums missing segments itself
 // (token_mass and residual, added in the same order, so the same bits) and waits for nobody again, any other workgroup that waited in vain ends.
 // Only workgroup 0 writes results.
-template <bool BF16, int PER>
-__global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
+// ALONE: this workgroup sums all segments, whoever else is there.  TREE: nodes there is room for.
+template <bool BF16, int PER, bool ALONE, int TREE>
+__device__ __forceinline__ void walk(const WalkArgs &a)
 {
-    __shared__ int32_t s_par[DREAM_MAX_TREE_ACCEPT];
-    __shared__ int32_t s_tok[DREAM_MAX_TREE_ACCEPT];
-    __shared__ int32_t s_first[DREAM_MAX_TREE_ACCEPT];     // first child of a node, or NONE
-    __shared__ float s_mt[DREAM_MAX_TREE_ACCEPT], s_zt[DREAM_MAX_TREE_ACCEPT];   // target row: max, sum (nodes with children)
-    __shared__ float s_md[DREAM_MAX_TREE_ACCEPT], s_zd[DREAM_MAX_TREE_ACCEPT];   // draft row
-    __shared__ float s_px[DREAM_MAX_TREE_ACCEPT], s_qx[DREAM_MAX_TREE_ACCEPT];   // a node's token at its parent: target and draft exponential
-    __shared__ float s_u[DREAM_MAX_TREE_ACCEPT];
-    __shared__ uint8_t s_ok[DREAM_MAX_TREE_ACCEPT];        // the node passes its test when it is the first child tried
+    __shared__ int32_t s_par[TREE];
+    __shared__ int32_t s_tok[TREE];
+    __shared__ int32_t s_first[TREE];     // first child of a node, or NONE
+    __shared__ float s_mt[TREE], s_zt[TREE];   // target row: max, sum (nodes with children)
+    __shared__ float s_md[TREE], s_zd[TREE];   // draft row
+    __shared__ float s_px[TREE], s_qx[TREE];   // a node's token at its parent: target and draft exponential
+    __shared__ float s_u[TREE];
+    __shared__ uint8_t s_ok[TREE];        // the node passes its test when it is the first child tried
     // rejections at the current node: P <- max(P * ip - Q * iq, 0) if `take`, then Q[x] <- 0
-    __shared__ float s_ip[DREAM_MAX_TREE_ACCEPT], s_iq[DREAM_MAX_TREE_ACCEPT];
-    __shared__ int32_t s_x[DREAM_MAX_TREE_ACCEPT];
-    __shared__ uint8_t s_take[DREAM_MAX_TREE_ACCEPT];
+    __shared__ float s_ip[TREE], s_iq[TREE];
+    __shared__ int32_t s_x[TREE];
+    __shared__ uint8_t s_take[TREE];
     __shared__ float s_part[MAX_VAL][MAX_SEG], s_mass[MAX_SEG];
     __shared__ float s_red[2][4][NW], s_scan[NW];
     __shared__ int s_redi[NW];
@@ -504,7 +547,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         return wave_sum(lane < n_seg ? v[lane] : 0.0f);
     };
     int round = 0;
-    bool alone = n_wg == 1;
+    bool alone = ALONE || n_wg == 1;
     // One round: fills s_part for all segments.  False: this workgroup waited in vain and ends.
     auto exchange = [&](int n) {
         round++;
@@ -530,6 +573,7 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
                 break;
             bool missing = false;
             const int val = tid / MAX_SEG, seg = tid % MAX_SEG;
+            __builtin_amdgcn_s_sleep(POLL_DELAY);
             if (val < n_val && seg < n_seg && seg % n_wg != wg) {
                 uint64_t w = 0;
                 missing = true;
@@ -778,6 +822,531 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
         a.accept_len[b] = depth;
 }
 
+template <bool BF16, int PER>
+__global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
+{
+    walk<BF16, PER, false, DREAM_MAX_TREE_ACCEPT>(a);
+}
+
+// The walk of a tree of up to 64 nodes whose segments have a workgroup each and are one chunk: what serving asks for.  The same rounds, exchange and
+// arithmetic as above, but a round is a chain of trips to memory and LDS and of dependent instructions, so here it has two barriers and what can be had beforehand is:
+// - NW waves hold the tokens; one more, the messenger, adds their sums behind the first barrier, publishes and polls, and hands out everybody's sums at the second.
+// - Lane i of every wave holds node i: parent, token, random number, the logits of its token at its parent, and what the rejections so far have left of target and draft
+//   there.  Each wave takes every decision by itself, in registers.
+// - While a round is on its way, the waves work out all of the next step that does not need its sum, and ask for the rows of the node that comes next if the
+//   test passes which the round decides.
+// A workgroup that waits in vain ends, workgroup 0 then starts over with the walk above, alone.
+// us per rejection / visited node with statistics to work out, walk above 3.3 / 4.9, here 1.8 / 3.0.  A call, both: 4 sequences x 60 nodes x 131072 float32 logits 50.5 / 30.4,
+// 4 x 60 x 262144 bf16 56.5 / 28.0, 32 x 60 x 32000 bf16 53.8 / 33.3, 1 x 60 x 32000 bf16 24.9 / 20.8, 16 x 60 x 131072 bf16 59.7 / 36.7.  (Workgroups of a sequence on one XCD: 40.6
+// instead of 37.5 before the first poll was put off.)
+template <bool BF16, int PER, bool VEC>
+__global__ __launch_bounds__(NT + 64) void spec_walk_small_kernel(WalkArgs a)
+{
+    __shared__ float s_part[2][MAX_VAL][MAX_SEG];
+    __shared__ __attribute__((aligned(16))) float s_red[2][MAX_VAL][NW];
+    __shared__ int s_missing[2];
+    __shared__ float s_stat[4][64], s_logit[2][64];
+    struct alignas(16) Step {
+        float jp, jq;
+        int32_t x, take;
+    };
+    __shared__ Step s_step[64];
+    __shared__ float s_scan[NW];
+    __shared__ int s_redi[NW], s_last[NW];
+    constexpr int PIECES = BF16 ? 1 : 2, ROW_BYTES = NT * 16 * PIECES * PER;      // 16-byte pieces of 8 tokens; bytes of a workgroup's tokens
+    constexpr bool AHEAD = VEC && ROW_BYTES <= 16384;       // (up to 8 MB a round; workgroups with more to read are bound by that)
+    __shared__ __attribute__((aligned(16))) unsigned char s_rows[AHEAD ? 4 * ROW_BYTES : 16];   // target and draft row of the root, and of the node asked for ahead
+    const int b = blockIdx.y, wg = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool messenger = wave == NW;
+    const int n_tree = a.n_tree, vocab = a.vocab, n_seg = a.n_seg, max_depth = a.max_depth;
+    const float inv_temp = a.inv_temp;
+    const int64_t bt = (int64_t)b * n_tree;
+    using Row = Raw8<BF16, VEC>;
+    const int t_own = (wg * PER * NT + tid) * 8;            // this thread's tokens: 8 from here on, and from every NT * 8 behind
+    auto of_lane = [](float x, int i) __attribute__((always_inline)) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), i)); };
+
+    // ---- (parent, token, random number), then (the logits of every node's token at its parent; the statistics there are)
+    int cur = 0, depth = 0, n_rej = 0;
+    // Rows asked for ahead go straight to LDS, each wave's to where it reads them: as values in registers the compiler waits for them at the next branch.
+    const uint32_t lds_rows = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)s_rows;
+    auto ask_row = [&](const void *logits, int n, int at) __attribute__((always_inline)) {
+        const char *base = reinterpret_cast<const char *>(logits) + (bt + n) * vocab * (BF16 ? 2 : 4);
+#pragma unroll
+        for (int i = 0; i < PER * PIECES; i++) {
+            const int t = t_own + i / PIECES * (NT * 8);
+            if (AHEAD && t < vocab)
+                lds_load16(base, (uint32_t)t * (BF16 ? 2 : 4) + i % PIECES * 16, __builtin_amdgcn_readfirstlane(lds_rows + at * ROW_BYTES + (wave * PER * PIECES + i) * 1024));
+        }
+    };
+    auto asked_row = [&](int at, float(&v)[PER][8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < PER; h++) {
+            Row r;
+#pragma unroll
+            for (int i = 0; i < PIECES; i++)
+                r.w[i] = *reinterpret_cast<const uint4 *>(s_rows + at * ROW_BYTES + (wave * PER * PIECES + h * PIECES + i) * 1024 + lane * 16);
+            r.unpack(v[h]);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                v[h][j] = t_own + h * (NT * 8) < vocab ? v[h][j] : -INFINITY;
+        }
+    };
+    auto read_row = [&](const void *logits, float(&v)[PER][8]) __attribute__((always_inline)) {
+        Row r[PER];
+#pragma unroll
+        for (int h = 0; h < PER; h++)
+            r[h].load(logits, (bt + cur) * vocab, t_own + h * (NT * 8), vocab);
+#pragma unroll
+        for (int h = 0; h < PER; h++)
+            r[h].unpack(v[h]);
+    };
+    const bool node = lane < n_tree;
+    int par_l = node ? a.parent[bt + lane] : -1;
+    const int tok_l = node ? min(max(a.token[bt + lane], 0), vocab - 1) : 0;     // device metadata is trusted but kept inside the row
+    const float u_l = node ? a.u_accept[bt + lane] : 0.0f, u_bonus = a.u_bonus[b];
+    par_l = lane > 0 && par_l >= 0 && par_l < lane ? par_l : -1;
+    uint64_t kids = __ballot(par_l == 0);                   // children of the current node that have not been tried
+    int asked = -1;                                         // the node whose rows were asked for last (where AHEAD)
+    auto ask_rows = [&](int n) __attribute__((always_inline)) {
+        if (!AHEAD)
+            return;
+        asked = n;
+        ask_row(a.tlogits, n, 2);
+        if (__ballot(par_l == n))                           // (of a leaf only the target is needed)
+            ask_row(a.dlogits, n, 3);
+    };
+    // (a wave waits for its loads in order: those of the messenger are the ones that the first test needs)
+    const int64_t rows_all = (int64_t)gridDim.y * n_tree;
+    float m[2], z[2];
+    auto load_stats = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < 2; w++) {
+            const int64_t at = (w * rows_all + bt + n) * n_seg + lane;
+            m[w] = lane < n_seg ? a.stat_m[at] : -INFINITY;
+            z[w] = lane < n_seg ? a.stat_s[at] : 0.0f;
+        }
+    };
+    auto store_stats = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < 2; w++) {
+            const float mx = wave_max(m[w]), sum = wave_sum(z[w] > 0.0f ? z[w] * __expf(m[w] - mx) : 0.0f);
+            if (lane == 0) {
+                s_stat[2 * w][n] = mx;
+                s_stat[2 * w + 1][n] = sum;
+            }
+        }
+    };
+    if (messenger) {
+        float t = 0.0f, d = 0.0f;
+        if (par_l >= 0) {
+            t = load_logit<BF16>(a.tlogits, (bt + par_l) * vocab + tok_l);
+            d = load_logit<BF16>(a.dlogits, (bt + par_l) * vocab + tok_l);
+        }
+        if (a.lazy)
+            load_stats(0);
+        s_logit[0][lane] = t * inv_temp;
+        s_logit[1][lane] = d * inv_temp;
+        if (a.lazy)
+            store_stats(0);
+        int32_t *path = a.accept_path + (int64_t)b * (max_depth + 1);
+        if (wg == 0)
+            for (int i = lane; i <= max_depth; i += 64)
+                path[i] = i == 0 ? 0 : -1;
+    } else {
+        if (!a.lazy)                                        // (what a node without children has there is of no use, and not used)
+            for (int i = wave; i < n_tree; i += NW) {
+                load_stats(i);
+                store_stats(i);
+            }
+        ask_row(a.tlogits, 0, 0);
+        if (kids)
+            ask_row(a.dlogits, 0, 1);
+        if (kids && max_depth > 0)
+            ask_rows(__builtin_ctzll(kids));
+    }
+    __syncthreads();
+    const float tx_l = s_logit[0][lane], dx_l = s_logit[1][lane];
+    const float mt_l = s_stat[0][lane], zt_l = s_stat[1][lane], md_l = s_stat[2][lane], zd_l = s_stat[3][lane];
+
+    float rp[PER][8], rq[PER][8];                           // this thread's residual target and reduced draft at the current node
+    float mt = of_lane(mt_l, 0), zt = of_lane(zt_l, 0), md = of_lane(md_l, 0), zd = of_lane(zd_l, 0);   // of its rows
+    float ip = 0.0f, iq = 0.0f;                             // normalisers: p = exp(t - mt) * ip, q = exp(d - md) * iq
+    float mass_l = 0.0f;                                    // of segment `lane` of the current target,
+    bool have_mass = false;                                 // if this is set
+    float left_l = 0.0f;
+    // the current node's logits
+    auto read_own = [&](bool draft) __attribute__((always_inline)) {
+        if (AHEAD && (cur == 0 || asked == cur)) {
+            const int at = cur == 0 ? 0 : 2;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            asked_row(at, rp);
+            if (draft)
+                asked_row(at + 1, rq);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (before others are asked for)
+        } else {
+            read_row(a.tlogits, rp);
+            if (draft)
+                read_row(a.dlogits, rq);
+        }
+    };
+    // (max, sum of exponentials) of this wave's share of a row
+    auto wave_stats = [&](const float(&x)[PER][8], float &m, float &z) __attribute__((always_inline)) {
+        float mx = -INFINITY, sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < PER * 8; i++)
+            mx = fmaxf(mx, x[i / 8][i % 8] * inv_temp);
+        mx = wave_max(mx);
+        const float ms = mx == -INFINITY ? 0.0f : mx;
+#pragma unroll
+        for (int i = 0; i < PER * 8; i++)
+            sum += __expf(x[i / 8][i % 8] * inv_temp - ms);  // (0 for the padding)
+        m = mx;
+        z = wave_sum(sum);
+    };
+    uint32_t round = 0;
+    // The waves' values of a round are in s_red[round & 1]; behind this all segments' are in s_part[round & 1].  V: 1 the mass of a residual, 2 and 4 (max, sum
+    // of exponentials) of the target, and of the draft.  `then`: what else the waves that hold tokens have to do.
+    auto exchange = [&](auto values, auto then) __attribute__((always_inline)) {
+        constexpr int V = decltype(values)::value;
+        const int at = round & 1;
+        __syncthreads();
+        if (messenger) {
+            float mine;                                     // value `lane`
+            if (V == 1) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(&s_red[at][0][0]), y = *reinterpret_cast<const f32x4 *>(&s_red[at][0][4]);
+                mine = ((((((x[0] + x[1]) + x[2]) + x[3]) + y[0]) + y[1]) + y[2]) + y[3];
+            } else {
+                const int w = lane >> 4 & 1, i = lane & 15;      // a row of 16 lanes: the target's waves, the next one: the draft's
+                const bool has = lane < 16 * (V / 2) && i < NW;
+                const float m = has ? s_red[at][2 * w][i & (NW - 1)] : -INFINITY, z = has ? s_red[at][2 * w + 1][i & (NW - 1)] : 0.0f;
+                const float mx = row_max(m), e = z > 0.0f ? z * __expf(m - mx) : 0.0f;
+                float sum[2] = {0.0f, 0.0f};
+#pragma unroll
+                for (int v = 0; v < V / 2; v++)
+#pragma unroll
+                    for (int k = 0; k < NW; k++)
+                        sum[v] += of_lane(e, 16 * v + k);
+                const float m0 = of_lane(mx, 0), m1 = of_lane(mx, 16);
+                mine = lane == 0 ? m0 : lane == 1 ? sum[0] : lane == 2 ? m1 : sum[1];
+            }
+            uint64_t *slot = a.slots + (int64_t)b * SLOTS + at * MAX_VAL * MAX_SEG;
+            if (lane < V) {
+                s_part[at][lane][wg] = mine;
+                if (n_seg > 1)
+                    __hip_atomic_store(slot + lane * MAX_SEG + wg, ((uint64_t)round << 32) | __float_as_uint(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const bool theirs = lane < n_seg && lane != wg;
+            bool missing = theirs;
+            uint64_t w[V];
+            __builtin_amdgcn_s_sleep(POLL_DELAY);
+            if (theirs)
+                for (int spin = 0; spin < a.spin_limit && missing; spin++) {
+#pragma unroll
+                    for (int v = 0; v < V; v++)
+                        w[v] = __hip_atomic_load(slot + v * MAX_SEG + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    missing = false;
+#pragma unroll
+                    for (int v = 0; v < V; v++)
+                        missing |= (uint32_t)(w[v] >> 32) != round;
+                }
+            if (theirs && !missing)
+#pragma unroll
+                for (int v = 0; v < V; v++)
+                    s_part[at][v][lane] = __uint_as_float((uint32_t)w[v]);
+            const bool any = __ballot(missing) != 0;
+            if (lane == 0)
+                s_missing[at] = any;
+        } else {
+            then();
+        }
+        __syncthreads();
+        return s_missing[at] == 0;
+    };
+    auto part = [&](int v) __attribute__((always_inline)) { return lane < n_seg ? s_part[round & 1][v][lane] : 0.0f; };
+    auto visit = [&](int n) __attribute__((always_inline)) {
+        cur = n;
+        depth++;
+        if (wg == 0 && tid == 0)
+            a.accept_path[(int64_t)b * (max_depth + 1) + depth] = cur;
+        kids = __ballot(par_l == cur);
+        have_mass = false;
+    };
+
+    bool known = true, in_time = true;                      // the current node's statistics are there; nobody was missing
+    for (;;) {
+        // ---- at a node whose children are all untried
+        n_rej = 0;
+        if (!kids) {
+            // a leaf: (max, sum of exponentials) of its target row's segments
+            round++;
+            if (!messenger) {
+                read_own(false);
+                float m, z;
+                wave_stats(rp, m, z);
+                if (lane == 0) {
+                    s_red[round & 1][0][wave] = m;
+                    s_red[round & 1][1][wave] = z;
+                }
+            }
+            in_time = exchange(std::integral_constant<int, 2>{}, [] {});
+            mt = wave_max(lane < n_seg ? part(0) : -INFINITY);
+            ip = 1.0f;
+            const float zs = part(1);
+            mass_l = zs > 0.0f ? zs * __expf(part(0) - mt) : 0.0f;
+            have_mass = true;
+            break;
+        }
+        if (!known) {
+            // its rows' statistics, and the masses of its target's segments
+            round++;
+            if (!messenger) {
+                read_own(true);
+                float m, z, m2, z2;
+                wave_stats(rp, m, z);
+                wave_stats(rq, m2, z2);
+                if (lane == 0) {
+                    s_red[round & 1][0][wave] = m;
+                    s_red[round & 1][1][wave] = z;
+                    s_red[round & 1][2][wave] = m2;
+                    s_red[round & 1][3][wave] = z2;
+                }
+            }
+            in_time = exchange(std::integral_constant<int, 4>{}, [&] {
+                if (depth < max_depth)
+                    ask_rows(__builtin_ctzll(kids));
+            });
+            if (!in_time)
+                break;
+            const float m = lane < n_seg ? part(0) : -INFINITY, m2 = lane < n_seg ? part(2) : -INFINITY, z = part(1), z2 = part(3);
+            mt = wave_max(m);                               // (lane s: segment s; the same tree over the segments in every wave)
+            md = wave_max(m2);
+            zt = wave_sum(z > 0.0f ? z * __expf(m - mt) : 0.0f);
+            zd = wave_sum(z2 > 0.0f ? z2 * __expf(m2 - md) : 0.0f);
+            mass_l = z > 0.0f ? z * __expf(m - mt) * (1.0f / zt) : 0.0f;
+            have_mass = true;
+        }
+        ip = 1.0f / zt;
+        iq = zd > 0.0f ? 1.0f / zd : 0.0f;
+        if (depth >= max_depth)                             // (a node at the depth limit may have children)
+            break;
+        // ---- the first child against the untouched distributions
+        const float px = __expf(tx_l - mt), qx = __expf(dx_l - md);
+        const float ratio = qx > 0.0f ? (px / zt) / (qx / zd) : (px > 0.0f ? INFINITY : 0.0f);
+        const uint64_t pass = __ballot(u_l < fminf(1.0f, ratio));
+        int child = __builtin_ctzll(kids);
+        kids &= kids - 1;
+        bool accepted = pass >> child & 1;
+        if (!accepted) {
+            // ---- one rejection after the other: the target becomes the positive part of (target - draft), the token leaves the draft
+            if (!messenger) {
+                if (known)                                  // (otherwise the round before has read them)
+                    read_own(true);
+#pragma unroll
+                for (int i = 0; i < PER * 8; i++) {
+                    rp[i / 8][i % 8] = token_mass(rp[i / 8][i % 8], inv_temp, mt, ip);     // (0 past the end: the logits read as -inf there)
+                    rq[i / 8][i % 8] = token_mass(rq[i / 8][i % 8], inv_temp, md, iq);
+                }
+            }
+            float P_l = px * ip, Q_l = qx * iq, Zq = 1.0f, jp = 1.0f, jq = 1.0f, Zp = 1.0f;
+            for (;;) {
+                const int x = __builtin_amdgcn_readlane(tok_l, child), mine = x - t_own;
+                round++;
+                float r[PER][8];
+                if (!messenger) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < PER * 8; i++) {
+                        r[i / 8][i % 8] = residual(rp[i / 8][i % 8], jp, rq[i / 8][i % 8], jq);
+                        s += r[i / 8][i % 8];
+                    }
+                    s = wave_sum(s);
+                    if (lane == 0)
+                        s_red[round & 1][0][wave] = s;
+                }
+                // what follows if something is left of the target
+                const float rP_l = residual(P_l, jp, Q_l, jq);
+                Zq = fmaxf(Zq - of_lane(Q_l, child), 0.0f);
+                Q_l = tok_l == x ? 0.0f : Q_l;
+                const int next = kids ? __builtin_ctzll(kids) : -1;
+                const float Qn = of_lane(Q_l, next & 63), un = of_lane(u_l, next & 63), Pn = of_lane(rP_l, next & 63), qn = Qn / Zq;
+                in_time = exchange(std::integral_constant<int, 1>{}, [&] {
+                    if (tid == 0)
+                        s_step[n_rej] = {jp, jq, x, 1};
+#pragma unroll
+                    for (int i = 0; i < PER * 8; i++)
+                        rq[i / 8][i % 8] = mine == i / 8 * (NT * 8) + i % 8 ? 0.0f : rq[i / 8][i % 8];
+                    // (rows on their way slow the polls down, so only if the test passes should half of the target be left)
+                    if (next >= 0 && un * qn < 2.0f * Pn)
+                        ask_rows(next);
+                });
+                if (!in_time)
+                    break;
+                left_l = part(0);
+                const float Z = wave_sum(left_l);
+                const bool take = Z > 0.0f;
+                if (take) {
+                    Zp = Z;
+                    have_mass = true;
+                    mass_l = left_l;
+                    P_l = rP_l;
+#pragma unroll
+                    for (int i = 0; i < PER * 8; i++)
+                        rp[i / 8][i % 8] = r[i / 8][i % 8];
+                } else if (tid == 0) {
+                    s_step[n_rej].take = 0;                 // target == draft: the residual is empty and the target stays as it is
+                }
+                n_rej++;
+                child = next;
+                if (child < 0)
+                    break;
+                kids &= kids - 1;
+                jp = 1.0f / Zp;
+                jq = Zq > 0.0f ? 1.0f / Zq : 0.0f;
+                const float P = of_lane(P_l, child), again = Qn > 0.0f ? (P / Zp) / qn : (P > 0.0f ? INFINITY : 0.0f);
+                accepted = un < fminf(1.0f, again);
+                if (accepted)
+                    break;
+            }
+        }
+        if (!accepted)
+            break;
+        visit(child);
+        known = !a.lazy;
+        if (known) {
+            mt = of_lane(mt_l, cur); zt = of_lane(zt_l, cur); md = of_lane(md_l, cur); zd = of_lane(zd_l, cur);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (nothing is on its way to LDS when a wave ends)
+    if (!in_time) {
+        if (wg == 0 && !messenger)
+            walk<BF16, PER, true, 64>(a);
+        return;
+    }
+    // ---- no child, or every child rejected: draw from the current target
+    if (wg != 0 || messenger)
+        return;
+    if (!have_mass) {                                       // the untouched target
+        const float z = lane < n_seg ? a.stat_s[(bt + cur) * n_seg + lane] : 0.0f;
+        mass_l = z > 0.0f ? z * __expf(a.stat_m[(bt + cur) * n_seg + lane] - mt) * ip : 0.0f;
+    }
+    // the segment with the drawn point is found from the masses, in order, and only that one is read
+    float upto = mass_l;                                    // of the segments up to lane's
+    for (int off = 1; off < 64; off <<= 1) {
+        const float o = __shfl_up(upto, off);
+        if (lane >= off)
+            upto += o;
+    }
+    const float prev = __shfl_up(upto, 1), below_l = lane ? prev : 0.0f;
+    const float target = u_bonus * of_lane(upto, 63);
+    const uint64_t past = __ballot(mass_l > 0.0f && upto > target), some = __ballot(mass_l > 0.0f);
+    // (rounding may leave the target at or above the total: the last segment with mass)
+    const int pick = past ? __builtin_ctzll(past) : some ? 63 - __builtin_clzll(some) : 0;
+    // Inverse-CDF draw over the segment's tokens, up to PER groups of 8 contiguous ones per thread: block scan, the thread with the drawn point goes over its own again.  Without one
+    // (rounding left the target at or above the sum) the last token with mass is taken.
+    const int r0 = pick * (PER * NT * 8), r1 = min(r0 + PER * NT * 8, vocab);
+    const int cpt = ((r1 - r0 + NT - 1) / NT + 7) & ~7, t0 = min(r0 + tid * cpt, r1), t1 = min(t0 + cpt, r1);
+    const int64_t row = (bt + cur) * vocab;
+    Row rt[PER], rd[PER];
+#pragma unroll
+    for (int h = 0; h < PER; h++)
+        if (t0 + h * 8 < t1) {
+            rt[h].load(a.tlogits, row, t0 + h * 8, vocab);
+            if (n_rej)
+                rd[h].load(a.dlogits, row, t0 + h * 8, vocab);
+        }
+    float v[PER][8], local = 0.0f;
+    __syncthreads();                                        // (the list of steps)
+#pragma unroll
+    for (int h = 0; h < PER; h++) {
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            v[h][j] = 0.0f;
+        if (t0 + h * 8 >= t1)
+            continue;
+        rt[h].unpack(v[h]);
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            v[h][j] = token_mass(v[h][j], inv_temp, mt, ip);
+        if (n_rej) {
+            float dv[8];
+            rd[h].unpack(dv);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                dv[j] = token_mass(dv[j], inv_temp, md, iq);
+            Step s = s_step[0];
+            for (int i = 0; i < n_rej; i++) {
+                const Step after = s_step[min(i + 1, n_rej - 1)];
+                const int x = s.x - t0 - h * 8;
+                if (__builtin_amdgcn_readfirstlane(s.take))
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        v[h][j] = residual(v[h][j], s.jp, dv[j], s.jq);
+                if (__ballot((unsigned)x < 8))
+#pragma unroll
+                    for (int j = 0; j < 8; j++)
+                        dv[j] = x == j ? 0.0f : dv[j];
+                s = after;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            local += v[h][j];
+    }
+    float inc = local;   // inclusive scan of the per-thread sums: inside a wave by shuffles, wave totals through LDS
+    for (int off = 1; off < 64; off <<= 1) {
+        const float o = __shfl_up(inc, off);
+        if (lane >= off)
+            inc += o;
+    }
+    if (lane == 63)
+        s_scan[wave] = inc;
+    __syncthreads();
+    float base = of_lane(below_l, pick);
+#pragma unroll
+    for (int w = 0; w < NW; w++)
+        if (w < wave)
+            base += s_scan[w];
+    const float below = base + inc - local;                 // mass of all tokens below t0
+    const uint64_t hit = __ballot(below + local > target && t1 > t0);
+    int last = -1;                                          // the thread's last token with mass, then the wave's
+#pragma unroll
+    for (int i = 0; i < PER * 8; i++)
+        last = v[i / 8][i % 8] > 0.0f ? t0 + i : last;
+    const uint64_t any = __ballot(last >= 0);
+    last = any ? __builtin_amdgcn_readlane(last, 63 - __builtin_clzll(any | 1)) : -1;
+    if (lane == 0) {
+        s_redi[wave] = hit ? wave * 64 + __builtin_ctzll(hit) : 0x7fffffff;
+        s_last[wave] = last;
+    }
+    __syncthreads();
+    int owner = 0x7fffffff;
+    last = -1;
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        owner = min(owner, s_redi[w]);
+        last = max(last, s_last[w]);
+    }
+    if (tid == owner) {
+        float run = below;
+        int token = t1 - 1;
+        bool found = false;
+#pragma unroll
+        for (int i = 0; i < PER * 8; i++) {
+            run += v[i / 8][i % 8];
+            if (!found && run > target && t0 + i < t1) {
+                token = t0 + i;
+                found = true;
+            }
+        }
+        a.bonus_token[b] = token;
+    }
+    if (tid == 0) {
+        if (owner == 0x7fffffff)
+            a.bonus_token[b] = last >= 0 ? last : min(r0, vocab - 1);
+        a.accept_len[b] = depth;
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -843,9 +1412,12 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
     // 52 / 46; 59 / 50; 24 nodes, 101 MB 33 / 41; 37 / 43, 151 MB 39 / 39; 42 / 41, 201 MB 43 / 43; 47 / 46; 32 nodes, 67 MB 33 / 36; 35 / 37, 134 MB 43 / 42;
     // 45 / 43; 48 nodes, 50 MB 27 / 37; 29 / 34, 75 MB 36 / 36; 39 / 39, 101 MB 38 / 38; 43 / 39; 64 nodes, 50 MB 42 / 44; 37 / 41, 67 MB 29 / 29; 31 / 31,
     // 134 MB 48 / 44; 53 / 48.  Over 262 shapes of 40 to 500 MB, 8 to 64 nodes and 1 to 32 sequences the line takes 0.5 % more than the better of both on average, 16 % at
-    // worst (bytes alone, 60 MB: 4.7 %, 53 %).
+    // worst (bytes alone, 60 MB: 4.7 %, 53 %).  spec_walk_small_kernel visits nodes for less and changes at 1.2 GB of bytes times nodes: 8 nodes, 67 MB 21 / 28, 134 MB 31 / 31 to 33;
+    // 12 nodes, 50 MB 22 / 24, 101 MB 26 / 26; 16 nodes, 34 MB 19 / 19 and 20 / 24, 67 MB 24 / 21, 134 MB 29 / 25; 24 nodes, 25 MB 19 / 20, 50 MB 23 / 22 and 24 / 26, 101 MB 27 / 23;
+    // 33 nodes, 17 MB 19 / 23, 35 MB 26 / 20 and 29 / 28, 138 MB 31 / 25; 60 nodes, 8 MB 23 / 25, 31 MB 34 / 29, 252 MB 50 / 30, 503 MB 71 / 30.
     const int64_t logit_bytes = (int64_t)2 * batch * n_tree * vocab * esz;
-    const bool lazy = logit_bytes >= 60000000 && logit_bytes * n_tree >= 3000000000ll;
+    const bool small = per <= 2 && n_tree <= 64 && n_chunks <= n_wg;        // (with four groups a thread the registers do not suffice for a ninth wave)
+    const bool lazy = small ? logit_bytes * n_tree >= 1200000000ll : logit_bytes >= 60000000 && logit_bytes * n_tree >= 3000000000ll;
     const int n_nodes = lazy ? 1 : n_tree;
     const dim3 sgrid(n_chunks, batch * n_nodes, 2);
     const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, lazy, token, parent, u_accept, u_bonus, max_depth,
@@ -855,6 +1427,15 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
         constexpr int PER = decltype(groups)::value;
         hipLaunchKernelGGL((softmax_stats_kernel<BF, PER>), sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, n_nodes, vocab, n_chunks, vec,
                            parent, inv_temp, stat_m, stat_s, slots);
+        if constexpr (PER <= 2) {
+            if (small) {
+                if (vec)
+                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, true>), dim3(n_wg, batch), dim3(NT + 64), 0, st, wa);
+                else
+                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, false>), dim3(n_wg, batch), dim3(NT + 64), 0, st, wa);
+                return;
+            }
+        }
         hipLaunchKernelGGL((spec_walk_kernel<BF, PER>), dim3(n_wg, batch), dim3(NT), 0, st, wa);
     };
     auto with_groups = [&](auto bf16) {

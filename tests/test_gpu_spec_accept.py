@@ -74,7 +74,12 @@ def _draft_children(parent, dl_f64, g):
 def _formed_by_the_walk(B, T, V, dtype):
     """Whether the statistics of the nodes' rows are formed by the walk (the line of spec_accept.hip) and not beforehand."""
     nbytes = 2 * B * T * V * (4 if dtype == "f32" else 2)
-    return nbytes >= 60000000 and nbytes * T >= 3000000000
+    return nbytes * T >= 1200000000 if _small(B, T, V) else nbytes >= 60000000 and nbytes * T >= 3000000000
+
+
+def _small(B, T, V):
+    """Whether spec_walk_small_kernel takes the call: a workgroup per segment, of one chunk of 4096 or 8192 tokens, trees of up to 64 nodes."""
+    return T <= 64 and any(-(-V // n) <= min(64, max(1, 256 // B)) for n in (4096, 8192))
 
 
 def _branches(parent, detail, clear):
@@ -340,3 +345,31 @@ def test_whoever_sums_a_segment_the_result_is_the_same(gu, V, dtype):
         dream.dream_set_accept_spin(0)
     for a, b in zip(got, want):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("B,T,V,dtype", [
+    (3, 64, 4096, "f32"), (3, 65, 4097, "f32"),          # the largest tree of spec_walk_small_kernel and the next; one segment of one chunk, two with one token in the last
+    (2, 1, 9000, "bf16"), (2, 2, 8200, "f32"),           # no test at all; one
+    (4, 64, 40000, "f32"), (4, 65, 40000, "f32"), (4, 64, 40003, "bf16"), (20, 30, 70000, "bf16"),   # statistics formed by the walk; rows off the 16-byte boundaries; 8192 tokens a workgroup
+    (64, 40, 16384, "f32"), (65, 40, 16384, "f32")])     # 256 workgroups; a fifth too many: spec_walk_kernel
+@pytest.mark.parametrize("limit", [5, 2, 0])
+def test_both_walks_give_the_same(gu, B, T, V, dtype, limit):
+    """Trees, rows and batches on both sides of the lines between the two walks, close calls included: the same whether the workgroups exchange their sums or (polls < 0) workgroup 0
+    forms them all, which is spec_walk_kernel's way; down to a depth limit of 0, where a root with children is drawn from."""
+    import paper_2505_19201_amd as dream
+    g = di.rng(5990 + V + T, 700)
+    parent = np.stack([di.random_tree(T, 5, 5991, b) for b in range(B)]) if T > 1 else np.full((B, 1), -1, dtype=np.int32)
+    t32 = di.normal((B, T, V), "f32", 5992, di.STREAM_LOGITS) * np.float32(2.0)
+    d32 = t32 + di.normal((B, T, V), "f32", 5993, di.STREAM_DRAFT_LOGITS)
+    token = _draft_children(parent, d32.astype(np.float64), g)
+    tl, dl = (t32, d32) if dtype == "f32" else (di.f32_to_bf16_bits(t32), di.f32_to_bf16_bits(d32))
+    ua, ub = g.uniform(0.2, 1.0, size=(B, T)).astype(np.float32), g.uniform(size=B).astype(np.float32)
+    got = gu.run_spec_accept(tl, dl, dtype, token, parent, ua, ub, limit)
+    dream.dream_set_accept_spin(-1)
+    try:
+        want = gu.run_spec_accept(tl, dl, dtype, token, parent, ua, ub, limit)
+    finally:
+        dream.dream_set_accept_spin(0)
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
+    assert got[0].max() <= limit and (got[2] >= 0).all() and (got[2] < V).all()
