@@ -32,8 +32,18 @@ struct SplitMap {
 struct SplitUnit {
     int rank, split, n;     // block (by rank), its split, and how many splits it has
 };
-__device__ __forceinline__ SplitUnit split_unit(const SplitMap &map, int u)
+// The units of a launch whose workgroups all run at once, in the order of dispatch: 16 bits each, block * 64 + split * 8 + splits - 1.  See order_units().
+constexpr int MAX_ORDERED = 128, MAX_ORDERED_BLOCKS = 1024;
+struct UnitOrder {
+    uint32_t pair[MAX_ORDERED / 2];
+    int32_t n;              // units, or 0: the order of the map
+};
+__device__ __forceinline__ SplitUnit split_unit(const SplitMap &map, const UnitOrder &order, int u)
 {
+    if (order.n) {
+        const uint32_t e = order.pair[u >> 1] >> (u & 1) * 16;
+        return {(int)(e >> 6 & (MAX_ORDERED_BLOCKS - 1)), (int)(e >> 3 & 7), (int)(e & 7) + 1};
+    }
     SplitUnit r = {u, 0, 0};
 #pragma unroll
     for (int j = 0; j < MAX_SPLITS - 1; j++)
@@ -55,8 +65,10 @@ struct ScoreArgs {
     float *part;   // [B, Hq, ns2, vis_len]  column sums per head and row split
     int32_t n_q, n_q_pad, n_keys, n_q_heads, n_kv_heads, vis_start, vis_len;
     float *ent_part;    // [ns1, B, Hq, n_q_pad]  expected score of the row under its attention weights, per split (entropy only)
+    float *row_entropy, *block_sum;   // entropy of unsplit blocks: nullable [B, Hq, n_q], and [B, Hq, blocks, 2] sums of 32 rows each (else null: entropy_rows_kernel)
     int32_t ns1, ns2;   // most splits of the streamed axis a block has: keys in pass 1, query rows in pass 2
     SplitMap map1, map2;
+    UnitOrder order1, order2;
     int64_t lse_split_stride;   // B * Hq * n_q_pad
     int64_t s_max;
     float scale, scale_log2;
@@ -146,6 +158,13 @@ struct RowStream {
     }
 };
 
+// Entropy of a row from its log-sum-exp and its expected score, both in log2 units.  Rounding can leave a tiny negative value for a one-hot row; NaN stays.
+__device__ __forceinline__ float entropy_of(float lse, float expected)
+{
+    const float H = 0.6931471805599453f * (lse - expected);
+    return H < 0.0f ? 0.0f : H;
+}
+
 // Pass 1: log-sum-exp of every causal row.  One workgroup per (32 CT query rows, head, sequence, key split).  K is streamed (RowStream, one
 // barrier per step of 64 keys); the four waves are two row slots x two key halves of a step, each with CT MFMA column tiles of
 // 16 rows, so that a K fragment read once serves both.  Scores are formed transposed (lane = query column), so a lane keeps a
@@ -172,8 +191,8 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     // (when there are 8 or more KV heads), so its K is fetched into one XCD's L2 only
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
     // later row blocks see more keys: they come first
-    const SplitUnit unit = split_unit(a.map1, blockIdx.y);
-    const int blk = a.map1.count[0] - 1 - unit.rank, b = blockIdx.z, split = unit.split;
+    const SplitUnit unit = split_unit(a.map1, a.order1, a.order1.n ? blockIdx.z : blockIdx.y);
+    const int blk = a.map1.count[0] - 1 - unit.rank, b = a.order1.n ? blockIdx.y : blockIdx.z, split = unit.split;
     int row[CT], pos[CT];
     bool valid[CT];
 #pragma unroll
@@ -351,6 +370,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     __syncthreads();
     if (half == 1 || g != 0)
         return;
+    float entropies = 0.0f;
 #pragma unroll
     for (int q = 0; q < CT; q++) {
         const float mo = s_half[slot][q][0][c], mt = fmaxf(m[q], mo), ms = (mt == -INFINITY) ? 0.0f : mt;
@@ -359,9 +379,18 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row[q];
         if (valid[q]) {
             const bool some = ENT ? lw != 0.0f : lw > 0.0f;   // (a row with a NaN score: its entropy is NaN, its column sums leave it out)
-            a.lse2[o] = some ? mt + log2f(lw) : -INFINITY;
+            const float lse = some ? mt + log2f(lw) : -INFINITY;
+            const float expected = ENT && some ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
+            if (ENT && a.block_sum) {
+                const float H = some ? entropy_of(lse, expected) : 0.0f;
+                entropies += H;
+                if (a.row_entropy)
+                    a.row_entropy[((int64_t)b * a.n_q_heads + h) * a.n_q + row[q]] = H;
+                continue;
+            }
+            a.lse2[o] = lse;
             if (ENT)
-                a.ent_part[o] = some ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
+                a.ent_part[o] = expected;
             if (split == 0)                                  // splits that other blocks have and this one does not: both values, since
                 for (int s = unit.n; s < a.ns1; s++) {       // a weight of 0 does not make a NaN left in the workspace harmless
                     a.lse2[o + s * a.lse_split_stride] = -INFINITY;
@@ -370,12 +399,20 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
                 }
         }
     }
+    if (ENT && a.block_sum) {
+        for (int off = 8; off > 0; off >>= 1)
+            entropies += __shfl_xor(entropies, off);
+        if (c == 0)
+            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * 2 + slot] = entropies;
+    }
 }
 
 // Entropy of every row from pass 1's per-split (log-sum-exp, expected score) pairs (Eq. 2).  One thread per
-// (head, row); each workgroup also leaves the sum of its 256 entropies for entropy_mean_kernel, which adds the
-// workgroup sums of a sequence in a fixed order, so the mean is reproducible.
+// (head, row), its pairs requested together; each workgroup also leaves the sum of its 256 entropies for entropy_mean_kernel, which adds the
+// workgroup sums of a sequence in a fixed order, so the mean is reproducible.  (The last workgroup to arrive in the place of the second launch: 3 us
+// slower at 200 workgroups, for what a release and an acquire between the XCDs' L2s cost.)
 // log2_domain: bf16 path (scores in log2 units); otherwise natural units and a single split.
+template <int NS1>
 __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2_domain, float *row_entropy, float *block_sum)
 {
     __shared__ float s_part[4];
@@ -387,27 +424,34 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2
         const int h = i / a.n_q, r = i - h * a.n_q;
         const int64_t o = ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + r;
         if (log2_domain) {
+            float L[NS1], E[NS1];
+#pragma unroll
+            for (int s = 0; s < NS1; s++) {
+                L[s] = a.lse2[s * a.lse_split_stride + o];
+                E[s] = a.ent_part[s * a.lse_split_stride + o];
+            }
             float M = -INFINITY;
             bool some = false;
-            for (int s = 0; s < a.ns1; s++) {
-                const float L = a.lse2[s * a.lse_split_stride + o];
-                M = fmaxf(M, L);
-                some |= L != -INFINITY;                       // (a NaN, which the maximum drops and the weights below keep)
+#pragma unroll
+            for (int s = 0; s < NS1; s++) {
+                M = fmaxf(M, L[s]);
+                some |= L[s] != -INFINITY;                    // (a NaN, which the maximum drops and the weights below keep)
             }
             if (some) {
                 float W = 0.0f, U = 0.0f;
-                for (int s = 0; s < a.ns1; s++) {
-                    const float w = __builtin_amdgcn_exp2f(a.lse2[s * a.lse_split_stride + o] - M);
+#pragma unroll
+                for (int s = 0; s < NS1; s++) {
+                    const float w = __builtin_amdgcn_exp2f(L[s] - M);
                     W += w;
-                    U += w * a.ent_part[s * a.lse_split_stride + o];
+                    U += w * E[s];
                 }
-                H = 0.6931471805599453f * ((M + log2f(W)) - U / W);
+                H = entropy_of(M + log2f(W), U / W);
             }
         } else {
             const float L = a.lse2[o];
             H = L == INFINITY ? 0.0f : L - a.ent_part[o];
+            H = H < 0.0f ? 0.0f : H;
         }
-        H = H < 0.0f ? 0.0f : H;   // rounding can leave a tiny negative value for a one-hot row; NaN stays
         if (row_entropy)
             row_entropy[((int64_t)b * a.n_q_heads + h) * a.n_q + r] = H;
     }
@@ -421,19 +465,23 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(ScoreArgs a, int log2
         block_sum[(int64_t)b * gridDim.x + blockIdx.x] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
 }
 
-// One wave per sequence; lane i adds the sums i, i + 64, ... in order, then a fixed tree over the lanes.  (One thread adding
+// One workgroup per sequence; thread i adds the sums i, i + 256, ... in order, then a fixed tree over lanes and waves.  (One thread adding
 // them one after the other took 7.7 us for 160 sums.)
-__global__ __launch_bounds__(64) void entropy_mean_kernel(const float *block_sum, int n_blocks, int n_rows, float *ae)
+__global__ __launch_bounds__(256) void entropy_mean_kernel(const float *block_sum, int n_blocks, int n_rows, float *ae)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
+    __shared__ float s_part[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
     float t = 0.0f;
-#pragma unroll 4
-    for (int i = lane; i < n_blocks; i += 64)
+#pragma unroll 8
+    for (int i = tid; i < n_blocks; i += 256)
         t += block_sum[(int64_t)b * n_blocks + i];
     for (int off = 32; off > 0; off >>= 1)
         t += __shfl_xor(t, off);
-    if (lane == 0)
-        ae[b] = t / (float)n_rows;
+    if ((tid & 63) == 0)
+        s_part[tid >> 6] = t;
+    __syncthreads();
+    if (tid == 0)
+        ae[b] = ((s_part[0] + s_part[1]) + (s_part[2] + s_part[3])) / (float)n_rows;
 }
 
 // Pass 2: column sums of the probabilities.  One workgroup per (32 CT visual keys, head, sequence, row split).  The query
@@ -460,8 +508,8 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     const int vis_end = a.vis_start + a.vis_len;
     // x walks the heads with the KV head fastest (see pass 1): the query rows of a head stay in one XCD's L2
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
-    const SplitUnit unit = split_unit(a.map2, blockIdx.y);      // earlier key blocks are seen by more rows: they come first
-    const int blk0 = a.vis_start + unit.rank * 32 * CT, b = blockIdx.z, split = unit.split;
+    const SplitUnit unit = split_unit(a.map2, a.order2, a.order2.n ? blockIdx.z : blockIdx.y);      // earlier key blocks are seen by more rows: they come first
+    const int blk0 = a.vis_start + unit.rank * 32 * CT, b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
     const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
     bool kvalid[CT];
 #pragma unroll
@@ -577,15 +625,21 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
                     cs[q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L1[r]));
                 }
         } else {
+            i32x4 at0 = {0, 1, 2, 3}, at1 = {16, 17, 18, 19};      // positions, or without them the rows from the lane's first one on
+            if (a.q_pos) {
+                at0 = *reinterpret_cast<const i32x4 *>(pp);
+                at1 = *reinterpret_cast<const i32x4 *>(pp + 16);
+            }
 #pragma unroll
             for (int q = 0; q < CT; q++) {
-                const int key = j0 + q * 16 + c, from = key - r0 - g * 4;     // without positions, rows of the half from here on see the key
+                // rows of the half from here on see the key: row r of this lane at position at0[r] or at1[r]
+                const int key = j0 + q * 16 + c - (a.q_pos ? 0 : r0 + g * 4);
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     const float p0 = __builtin_amdgcn_exp2f(acc[q][0][r] * a.scale_log2 - L0[r]);
                     const float p1 = __builtin_amdgcn_exp2f(acc[q][1][r] * a.scale_log2 - L1[r]);
-                    cs[q] += (a.q_pos ? key <= pp[r] : from <= r) ? p0 : 0.0f;
-                    cs[q] += (a.q_pos ? key <= pp[16 + r] : from <= 16 + r) ? p1 : 0.0f;
+                    cs[q] += key <= at0[r] ? p0 : 0.0f;
+                    cs[q] += key <= at1[r] ? p1 : 0.0f;
                 }
             }
         }
@@ -1056,16 +1110,20 @@ void launch_colsum(int ns1, dim3 grid, hipStream_t st, const ScoreArgs &a)
     }
 }
 
-// Workgroups a launch is split into at most: two or three per CU.  (Four and more hold their own on a CU, but every one of them
-// loads its own first step and its own rows: 1024 is 2-8 % slower at one sequence, 2048 20 %.)
+// Blocks are split while the launch would have fewer workgroups than this: two or three per CU.
 int resident_groups(int head_dim) { return head_dim == 256 ? 512 : 768; }
 
 // Splits of one pass.  `len(rank)`: steps of 64 keys or rows of a block, longest first; `heads`: workgroups per unit (heads times
-// sequences); `resident`: see above.  Divided so that the launch is one round of workgroups with as
-// few steps each as that allows, at least two (a workgroup spends about 3 us before its first step) and at most 8 splits of a block; if
-// the blocks as they are already fill the chip, they stay whole.
+// sequences); `resident`: see above.  If the blocks as they are already fill the chip, they stay whole.  Otherwise a block is divided over workgroups of at
+// most S steps, two at least and at most 8 workgroups a block, with the S of least 3 R + 1.2 S, R = ceil(workgroups / 256): a workgroup that shares
+// its CU costs it about three steps (its own first loads and its end), and the longest one runs its steps one after the other, a step at 1.2
+// of what it takes of a CU's time when others fill the gaps.  At most four workgroups a CU are at work together (two at head_dim 256), and more were always slower.
+// `whole`: what a launch with whole blocks is worth, in these units: without partial values the entropies need one launch less
+// (all launches, us, split / whole: LLaVA 704 rows 13.7 / 13.4, 2 x 500 Pixtral rows 14.9 / 12.2; whole before / now: SmolVLM 1600 rows 22.1 / 20.6).
+// Entropy of one prompt, us, by S (all its launches, units in the order below): Pixtral 1279 rows 9 21.4, 10 20.1, 13 19.8, 16 20.5, 20 21.6; LLaVA 704
+// rows 3 14.8, 4 15.3, 5 14.7, 6 13.7, 7 14.0, 9 15.0; Gemma3 1280 rows 9 20.5, 10 19.2, 12 20.8, 16 23.8.  The rule takes 10, 6 and 10.
 template <class Len>
-int plan_splits(int blocks, int64_t heads, int resident, Len len, SplitMap *map, int *units)
+int plan_splits(int blocks, int64_t heads, int resident, float whole, Len len, SplitMap *map, int *units)
 {
     auto units_of = [&](int S) {
         int64_t n = 0;
@@ -1076,11 +1134,16 @@ int plan_splits(int blocks, int64_t heads, int resident, Len len, SplitMap *map,
     const int longest = len(0) > 1 ? len(0) : 1;
     int S = longest;
     if ((int64_t)blocks * heads < resident) {
-        S = ceil_div(longest, MAX_SPLITS);
-        if (S < 2)
-            S = 2;
-        while (S < longest && units_of(S) * heads > resident)
-            S++;
+        float best = INFINITY;
+        const int64_t together = resident > 512 ? 1024 : 512;
+        for (int s = std::max(2, ceil_div(longest, MAX_SPLITS)); s <= std::max(longest, 2); s++) {
+            const int64_t wgs = units_of(s) * heads;
+            const float cost = 3.0f * ceil_div(wgs, 256) + 1.2f * s - (s == longest ? whole : 0.0f);
+            if (wgs <= together && cost < best) {
+                best = cost;
+                S = s;
+            }
+        }
     }
     int most = 1;
     *units = 0;
@@ -1099,33 +1162,84 @@ int plan_splits(int blocks, int64_t heads, int resident, Len len, SplitMap *map,
     return pow2;
 }
 
+// Order of dispatch of a launch that is one round of workgroups.  Workgroup i starts on CU i mod 256, `heads` workgroups to a unit, so units 256 / heads
+// apart share a CU until the end of the launch: the longest go first, and every further round gives its longest to the CU with the fewest steps so far.
+template <class Len>
+void order_units(int64_t heads, int units, int at_once, Len len, const SplitMap &map, UnitOrder *order)
+{
+    order->n = 0;
+    if (units > MAX_ORDERED || units < 2 || map.count[0] > MAX_ORDERED_BLOCKS || units * heads > at_once || units * heads <= 256)
+        return;
+    struct Unit { int steps; uint32_t code; } unit[MAX_ORDERED];
+    int n = 0;
+    for (int r = 0; r < map.count[0]; r++) {
+        int of = 0;
+        while (of < MAX_SPLITS && r < map.count[of])
+            of++;
+        const int all = len(r), each = ceil_div(all, of);
+        for (int j = 0; j < of; j++)
+            unit[n++] = {std::max(std::min(each, all - j * each), 0), (uint32_t)(r << 6 | j << 3 | (of - 1))};
+    }
+    std::sort(unit, unit + n, [](const Unit &x, const Unit &y) { return x.steps != y.steps ? x.steps > y.steps : x.code < y.code; });
+    const int bins = (int)std::max<int64_t>(256 / heads, 1), rounds = ceil_div(n, bins);
+    struct Bin { int load; uint32_t code[MAX_ORDERED]; } bin[MAX_ORDERED];
+    for (int i = 0; i < std::min(bins, n); i++)
+        bin[i].load = 0;
+    int by_load[MAX_ORDERED];
+    for (int i = 0; i < std::min(bins, n); i++)
+        by_load[i] = i;
+    for (int t = 0; t < rounds; t++) {
+        std::sort(by_load, by_load + std::min(bins, n), [&](int x, int y) { return bin[x].load != bin[y].load ? bin[x].load < bin[y].load : x < y; });
+        for (int i = 0; i < std::min(bins, n - t * bins); i++) {
+            bin[by_load[i]].load += unit[t * bins + i].steps;
+            bin[by_load[i]].code[t] = unit[t * bins + i].code;
+        }
+    }
+    // the last round may be short: its bins come first in every round (by_load still says in which order it was dealt)
+    for (int i = 0; i < MAX_ORDERED / 2; i++)
+        order->pair[i] = 0;
+    for (int u = 0; u < n; u++)
+        order->pair[u >> 1] |= bin[by_load[u % bins]].code[u / bins] << (u & 1) * 16;
+    order->n = n;
+}
+
 struct CompressPlan {
     int n_q_pad, ns1, ns2;
     int units1, units2;            // (block, split) units of the two passes
     SplitMap map1, map2;
+    UnitOrder order1, order2;
     size_t off_lse, off_part;
 };
 
 // `with_pos`: rows come with explicit positions, so any block may have to walk everything
-CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos)
+CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos, bool entropy)
 {
     CompressPlan p;
     p.n_q_pad = (n_q + 15) / 16 * 16;
     p.ns1 = p.ns2 = 1;
     p.units1 = p.units2 = 1;
+    p.order1.n = p.order2.n = 0;
     if (dtype == DREAM_BF16) {
         const int resident = resident_groups(head_dim);
         const int b1 = ceil_div(n_q, 32 * CT), b2 = ceil_div(vis_len > 0 ? vis_len : 1, 32 * CT), rows = ceil_div(n_q, 64);
-        p.ns1 = plan_splits(b1, (int64_t)n_heads * batch, resident, [&](int r) {
-            return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * 32 * CT, n_q), n_keys), 64);
-        }, &p.map1, &p.units1);
-        p.ns2 = plan_splits(b2, (int64_t)n_heads * batch, resident, [&](int r) {
-            return with_pos ? rows : std::max(rows - std::min((vis_start + r * 32 * CT) / 64, rows), 0);
-        }, &p.map2, &p.units2);
+        const int64_t heads = (int64_t)n_heads * batch;
+        auto len1 = [&](int r) { return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * 32 * CT, n_q), n_keys), 64); };
+        auto len2 = [&](int r) { return with_pos ? rows : std::max(rows - std::min((vis_start + r * 32 * CT) / 64, rows), 0); };
+        p.ns1 = plan_splits(b1, heads, resident, entropy ? 10.0f : 0.0f, len1, &p.map1, &p.units1);
+        p.ns2 = plan_splits(b2, heads, resident, 0.0f, len2, &p.map2, &p.units2);
+        const int at_once = batch == 1 ? 2048 : 1024;
+        order_units(heads, p.units1, at_once, len1, p.map1, &p.order1);
+        order_units(heads, p.units2, at_once, len2, p.map2, &p.order2);
     }
     p.off_lse = DREAM_WORKSPACE_MIN_BYTES;
     p.off_part = align_up(p.off_lse + (size_t)p.ns1 * batch * n_heads * p.n_q_pad * sizeof(float), 256);
     return p;
+}
+
+// One round of workgroups: unit by unit.  More: sequence by sequence, so that the heads at work fit the caches.
+dim3 score_grid(const dream_attn_desc *desc, int units, const UnitOrder &order)
+{
+    return order.n ? dim3(desc->n_q_heads, desc->batch, units) : dim3(desc->n_q_heads, units, desc->batch);
 }
 
 // The most splits a plan of these sizes takes, whatever the keys and positions are (the workspace query knows neither).
@@ -1225,7 +1339,7 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
             return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
         if ((int64_t)vis_start + vis_len > n_keys)
             return fail(DREAM_ERR_INVALID_ARG, "%s: visual span [%d, %d) exceeds the %d live keys", who, vis_start, vis_start + vis_len, n_keys);
-        const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, vis_start, vis_len, desc->dtype, q_pos != nullptr);
+        const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, vis_start, vis_len, desc->dtype, q_pos != nullptr, false);
         const size_t need = compress_most(desc->batch, desc->n_q_heads, desc->head_dim, n_q, vis_len, desc->dtype);
         if (!workspace || workspace_bytes < need)
             return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
@@ -1234,7 +1348,7 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
         a.lse2 = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_lse);
         a.part = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_part);
         a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
-        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.map1 = p.map1; a.map2 = p.map2; a.ent_part = nullptr; a.lse_in = row_lse_in;
+        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.map1 = p.map1; a.map2 = p.map2; a.order1 = p.order1; a.order2 = p.order2; a.ent_part = a.row_entropy = a.block_sum = nullptr; a.lse_in = row_lse_in;
         a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
         a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
         a.vis_start = vis_start; a.vis_len = vis_len; a.s_max = desc->s_max;
@@ -1243,7 +1357,7 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
         if (desc->dtype == DREAM_BF16) {
             if (p.units1 > 65535)
                 return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grids", who, n_q);
-            const dim3 g1(desc->n_q_heads, p.units1, desc->batch), g2(desc->n_q_heads, p.units2, desc->batch);
+            const dim3 g1 = score_grid(desc, p.units1, p.order1), g2 = score_grid(desc, p.units2, p.order2);
             // pass 1 (the rows' log-sum-exps) only when the caller does not bring them
             with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
                 constexpr int D = decltype(dim)::value;
@@ -1348,7 +1462,7 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= n_keys <= s_max", who);
     if (!q_pos && n_q > n_keys)
         return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
-    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, 0, 0, desc->dtype, q_pos != nullptr);
+    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, 0, 0, desc->dtype, q_pos != nullptr, true);
     const size_t part = align_up((size_t)p.ns1 * desc->batch * desc->n_q_heads * p.n_q_pad * sizeof(float), 256);
     const int n_blocks = ceil_div((int64_t)desc->n_q_heads * n_q, 256);
     const size_t need = dream_attention_entropy_workspace(desc, n_q);
@@ -1357,6 +1471,11 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
     hipStream_t st = as_stream(stream);
     ScoreArgs a;
     a.q = q; a.k = k_cache; a.q_pos = q_pos;
+    // Blocks that are not split leave entropies in the place of partial values, and their sums, two of a block's 64 rows, fit where those would stand.
+    const bool whole = desc->dtype == DREAM_BF16 && p.ns1 == 1;
+    float *block_sum = reinterpret_cast<float *>(static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES + (whole ? 0 : 2 * part));
+    a.row_entropy = whole ? row_entropy : nullptr;
+    a.block_sum = whole ? block_sum : nullptr;
     a.lse2 = reinterpret_cast<float *>(static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES);
     a.lse_in = nullptr;
     a.ent_part = reinterpret_cast<float *>(static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES + part);
@@ -1364,14 +1483,14 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
     a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
     a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
     a.vis_start = 0; a.vis_len = 0; a.s_max = desc->s_max;
-    a.ns1 = p.ns1; a.ns2 = 1; a.map1 = p.map1; a.map2 = p.map2;
+    a.ns1 = p.ns1; a.ns2 = 1; a.map1 = p.map1; a.map2 = p.map2; a.order1 = p.order1; a.order2 = p.order2;
     a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
     a.scale = desc->scale != 0.0f ? desc->scale : 1.0f / sqrtf((float)desc->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;
     if (desc->dtype == DREAM_BF16) {
         if (p.units1 > 65535)
             return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grid", who, n_q);
-        dim3 g1(desc->n_q_heads, p.units1, desc->batch);
+        const dim3 g1 = score_grid(desc, p.units1, p.order1);
         with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
             hipLaunchKernelGGL((scores_lse_bf16_kernel<decltype(dim)::value, true, decltype(direct)::value>), g1, dim3(256), 0, st, a);
         });
@@ -1383,10 +1502,13 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
     int rc = check_launch("entropy score kernel");
     if (rc)
         return rc;
-    float *block_sum = reinterpret_cast<float *>(static_cast<char *>(workspace) + DREAM_WORKSPACE_MIN_BYTES + 2 * part);
-    hipLaunchKernelGGL(entropy_rows_kernel, dim3(n_blocks, desc->batch), dim3(256), 0, st, a, desc->dtype == DREAM_BF16 ? 1 : 0, row_entropy,
-                       block_sum);
-    hipLaunchKernelGGL(entropy_mean_kernel, dim3(desc->batch), dim3(64), 0, st, block_sum, n_blocks, desc->n_q_heads * n_q, ae);
+    if (!whole) {
+        static constexpr decltype(&entropy_rows_kernel<1>) ROWS[] = {entropy_rows_kernel<1>, entropy_rows_kernel<2>, entropy_rows_kernel<4>, entropy_rows_kernel<8>};
+        hipLaunchKernelGGL(ROWS[p.ns1 == 8 ? 3 : p.ns1 / 2], dim3(n_blocks, desc->batch), dim3(256), 0, st, a, desc->dtype == DREAM_BF16 ? 1 : 0, row_entropy,
+                           block_sum);
+    }
+    hipLaunchKernelGGL(entropy_mean_kernel, dim3(desc->batch), dim3(256), 0, st, block_sum, whole ? desc->n_q_heads * p.map1.count[0] * 2 : n_blocks,
+                       desc->n_q_heads * n_q, ae);
     return check_launch("entropy reduction kernels");
 }
 

@@ -260,6 +260,17 @@ def test_score_steps_and_splits(gu, D, P, v, vis_start, with_pos):
     np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
 
 
+@pytest.mark.parametrize("B,H,D,P,v,vis_start,with_pos", [(2, 16, 64, 700, 640, 9, False), (2, 8, 64, 1279, 1100, 0, False), (3, 7, 64, 900, 833, 64, False),
+                                                          (1, 16, 128, 1025, 1025, 0, False), (2, 8, 64, 1000, 700, 100, True)])
+def test_blocks_dealt_to_the_cus(gu, B, H, D, P, v, vis_start, with_pos):
+    """More than one workgroup per CU and one round of them: blocks come in another order than by their length, over several sequences."""
+    q = di.normal((B, P, H, D), "bf16", 1101 + P, di.STREAM_PREFILL_Q)
+    k = di.normal((B, H, P + 3, D), "bf16", 1102 + P, di.STREAM_K)
+    pos = np.stack([np.random.default_rng(P + b).permutation(P) for b in range(B)]).astype(np.int32) if with_pos else None
+    scores, _, _ = gu.run_compress("bf16", q, k, P, vis_start, v, 1, 2, q_pos=pos)
+    np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
+
+
 @pytest.mark.parametrize("D,P,v", [(128, 1279, 1023), (64, 333, 300), (256, 449, 200)])
 def test_stale_workspace_is_never_read(gu, D, P, v):
     """Blocks with fewer splits than others, in both score passes, over a workspace of NaN patterns (the harness fills it)."""
