@@ -20,7 +20,8 @@ using namespace dream;
 
 namespace {
 
-constexpr int CT = 2;              // MFMA column tiles per wave of both passes (4 halves the loads per score and measured 5-20 % slower: fewer workgroups)
+constexpr int COLS = 32;           // held rows or keys of a wave (64 halve the loads per score and measured 5-20 % slower: fewer workgroups)
+constexpr int BLOCK = 2 * COLS;    // of a workgroup: two column slots
 constexpr int MAX_SPLITS = 8;
 
 // Which blocks are split how often.  The causal triangle gives the blocks of a pass different numbers of steps; a block with
@@ -165,10 +166,10 @@ __device__ __forceinline__ float entropy_of(float lse, float expected)
     return H < 0.0f ? 0.0f : H;
 }
 
-// Pass 1: log-sum-exp of every causal row.  One workgroup per (32 CT query rows, head, sequence, key split).  K is streamed (RowStream, one
-// barrier per step of 64 keys); the four waves are two row slots x two key halves of a step, each with CT MFMA column tiles of
-// 16 rows, so that a K fragment read once serves both.  Scores are formed transposed (lane = query column), so a lane keeps a
-// private running (max, sum) per column; the row groups of the wave and the two halves are combined once at the end.  With
+// Pass 1: log-sum-exp of every causal row.  One workgroup per (64 query rows, head, sequence, key split).  K is streamed (RowStream, one
+// barrier per step of 64 keys); the four waves are two row slots x two key halves of a step, each with one MFMA tile of 32 keys by
+// 32 rows.  Scores are formed transposed (lane = query column), so a lane keeps a
+// private running (max, sum); the row groups of the wave and the two halves are combined once at the end.  With
 // several splits each workgroup writes a partial log-sum-exp that pass 2 combines.
 // With ENT the kernel also keeps t = sum_j 2^(x_j - m) x_j, so that the expected score sum_j A_j x_j = t / l of
 // the row is known and the row's entropy -sum A log A = LSE - sum A_j s_j (Eq. 2, Section 3.2) needs no
@@ -176,46 +177,40 @@ __device__ __forceinline__ float entropy_of(float lse, float expected)
 // Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 22.2 us, 16 SmolVLM sequences 251 -> 200 us.
 // The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
 // The reference raised by octaves and a step's fragments requested together: 22.7 -> 21.7 us and 188 -> 185 us for larger prompts, all launches.
+// What bounds it there is the issue of instructions.  One tile of 32x32 in the place of four of 16x16 is half the MFMAs for the same products, one
+// reference and one pair of sums per lane: 16 SmolVLM sequences 193 -> 171 us, 8 of Gemma3 with 900 rows 58.5 -> 54.0, one LLaVA prompt 13.4 -> 12.7.
 template <int D, bool ENT, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
-    constexpr int NKS = D / 32;
+    constexpr int NKS = D / 16;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
-    __shared__ float s_half[2][CT][ENT ? 3 : 2][16];
+    __shared__ float s_half[2][ENT ? 3 : 2][COLS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = wave & 1, half = wave >> 1;
-    const int c = lane & 15, g = lane >> 4;
+    const int c = lane & 31, g = lane >> 5;
     // x walks the heads with the KV head fastest: workgroup ids that share a KV head are congruent mod 8
     // (when there are 8 or more KV heads), so its K is fetched into one XCD's L2 only
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
     // later row blocks see more keys: they come first
     const SplitUnit unit = split_unit(a.map1, a.order1, a.order1.n ? blockIdx.z : blockIdx.y);
     const int blk = a.map1.count[0] - 1 - unit.rank, b = a.order1.n ? blockIdx.y : blockIdx.z, split = unit.split;
-    int row[CT], pos[CT];
-    bool valid[CT];
-#pragma unroll
-    for (int q = 0; q < CT; q++) {
-        row[q] = (blk * 2 + slot) * 16 * CT + q * 16 + c;
-        valid[q] = row[q] < a.n_q;
-        pos[q] = valid[q] ? (a.q_pos ? a.q_pos[(int64_t)b * a.n_q + row[q]] : row[q]) : -1;
-    }
+    const int row = (blk * 2 + slot) * COLS + c;
+    const bool valid = row < a.n_q;
+    int pos = valid ? row : -1;
     // keys this workgroup has to see: without explicit positions, up to its last row
-    const int key_lim = a.q_pos ? a.n_keys : min(min((blk + 1) * 32 * CT, a.n_q), a.n_keys);
+    const int key_lim = a.q_pos ? a.n_keys : min(min((blk + 1) * BLOCK, a.n_q), a.n_keys);
     const int n_steps_all = (key_lim + STEP - 1) / STEP;
     const int sps = (n_steps_all + unit.n - 1) / unit.n;
     const int s0 = split * sps, n_steps = max(min(sps, n_steps_all - s0), 0);   // steps s0 .. s0 + n_steps - 1
     // the wave's first and last position (rows that do not exist keep nothing, so they do not count)
-    int wave_min_pos = (blk * 2 + slot) * 16 * CT, wave_max_pos = min(wave_min_pos + 16 * CT, a.n_q) - 1;
+    int wave_min_pos = (blk * 2 + slot) * COLS, wave_max_pos = wave_min_pos < a.n_q ? min(wave_min_pos + COLS, a.n_q) - 1 : -1;
     if (a.q_pos) {
-        wave_max_pos = -1;
-        wave_min_pos = 0x7fffffff;
-#pragma unroll
-        for (int q = 0; q < CT; q++) {
-            wave_max_pos = max(wave_max_pos, pos[q]);
-            wave_min_pos = min(wave_min_pos, valid[q] ? pos[q] : 0x7fffffff);
-        }
+        if (valid)
+            pos = a.q_pos[(int64_t)b * a.n_q + row];
+        wave_max_pos = max(pos, -1);
+        wave_min_pos = valid ? pos : 0x7fffffff;
         for (int off = 32; off > 0; off >>= 1) {
             wave_max_pos = max(wave_max_pos, __shfl_xor(wave_max_pos, off));
             wave_min_pos = min(wave_min_pos, __shfl_xor(wave_min_pos, off));
@@ -239,21 +234,14 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
 #pragma unroll
     for (int ks = 0; ks < NKS; ks++)
-        frag[ks] = c * G::ROW + ((ks * 4 + g) ^ swizzle<D>(c)) * 16;
-    bf16x8 qf[CT][NKS];
+        frag[ks] = c * G::ROW + ((ks * 2 + g) ^ swizzle<D>(c)) * 16;
+    bf16x8 qf[NKS];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < CT; q++)
-#pragma unroll
-        for (int ks = 0; ks < NKS; ks++)
-            qf[q][ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + (slot * CT + q) * 16 * G::ROW + frag[ks]);
-    float m[CT], l[CT], tx[CT];
-#pragma unroll
-    for (int q = 0; q < CT; q++) {
-        m[q] = -INFINITY;
-        l[q] = tx[q] = 0.0f;
-    }
+    for (int ks = 0; ks < NKS; ks++)
+        qf[ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + slot * COLS * G::ROW + frag[ks]);
+    float m = -INFINITY, l = 0.0f, tx = 0.0f;
     for (int i = 0, stage = 0; i < n_steps; i++) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step i has landed
         __syncthreads();                                                               // everybody's has, and step i - 1 is no longer read
@@ -263,147 +251,109 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         const int key0 = (s0 + i) * STEP + half * 32;
         if (key0 > wave_max_pos)
             continue;   // causal: nothing in this half is visible to this wave's rows
-        f32x4 acc[CT][2];
+        f32x16 acc = {};
+        bf16x8 kf[NKS];                                          // requested together: the waits then fall behind the first products
 #pragma unroll
-        for (int q = 0; q < CT; q++)
-            acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bf16x8 kf[NKS][2];                                       // requested together: the waits then fall behind the first products
-#pragma unroll
-        for (int ks = 0; ks < NKS; ks++) {
-            kf[ks][0] = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
-            kf[ks][1] = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
-        }
+        for (int ks = 0; ks < NKS; ks++)
+            kf[ks] = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-#pragma unroll
-            for (int q = 0; q < CT; q++) {
-                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][0], qf[q][ks], acc[q][0], 0, 0, 0);
-                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][1], qf[q][ks], acc[q][1], 0, 0, 0);
-            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], acc, 0, 0, 0);
         const bool open = key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f;
-        // A column's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
+        // The row's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
         // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores; masked: some are -inf, the mark of a
         // key that the row does not see (a NaN is no mark: it makes the row's sums NaN)
-        auto add_scores = [&](const float(&mx)[CT], float mult, auto masked) {
-            bool raise = false;
-#pragma unroll
-            for (int q = 0; q < CT; q++)
-                raise = raise || mx[q] > m[q] + 8.0f;
-            if (__any(raise)) {
-#pragma unroll
-                for (int q = 0; q < CT; q++) {
-                    const float m_new = mx[q] > m[q] + 8.0f ? mx[q] : m[q], alpha = m_new == m[q] ? 1.0f : __builtin_amdgcn_exp2f(m[q] - m_new);   // (0 when the old reference was -inf)
-                    m[q] = m_new;
-                    l[q] *= alpha;
-                    if (ENT)
-                        tx[q] *= alpha;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < CT; q++) {
-                const float neg_m = m[q] == -INFINITY ? 0.0f : -m[q];
-                float sum = 0.0f, xsum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float x = acc[q][e >> 2][e & 3], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
-                    sum += p;
-                    if (ENT)
-                        xsum = fmaf(p, decltype(masked)::value ? fmaxf(x, -3.0e38f) : x, xsum);   // (finite, so that times a probability of 0 it is 0)
-                }
-                l[q] += sum;
+        auto add_scores = [&](float mx, float mult, auto masked) {
+            if (__any(mx > m + 8.0f)) {
+                const float m_new = mx > m + 8.0f ? mx : m, alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);   // (0 when the old reference was -inf)
+                m = m_new;
+                l *= alpha;
                 if (ENT)
-                    tx[q] = fmaf(xsum, mult, tx[q]);
+                    tx *= alpha;
             }
+            const float neg_m = m == -INFINITY ? 0.0f : -m;
+            float sum = 0.0f, xsum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const float x = acc[e], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
+                sum += p;
+                if (ENT)
+                    xsum = fmaf(p, decltype(masked)::value ? fmaxf(x, -3.0e38f) : x, xsum);   // (finite, so that times a probability of 0 it is 0)
+            }
+            l += sum;
+            if (ENT)
+                tx = fmaf(xsum, mult, tx);
         };
-        float mx[CT];
         if (open) {
             // every key of the half is visible to every row of the wave (all but those on the diagonal):
             // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
+            float x = -INFINITY;
 #pragma unroll
-            for (int q = 0; q < CT; q++) {
-                float x = -INFINITY;
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    x = fmaxf(x, acc[q][e >> 2][e & 3]);
-                mx[q] = x * a.scale_log2;
-            }
-            add_scores(mx, a.scale_log2, std::false_type{});
+            for (int e = 0; e < 16; e++)
+                x = fmaxf(x, acc[e]);
+            add_scores(x * a.scale_log2, a.scale_log2, std::false_type{});
         } else {
+            const int lim = min(pos, a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 8 * (e / 4) + e % 4 is visible up to here
+            float mx = -INFINITY;
 #pragma unroll
-            for (int q = 0; q < CT; q++) {
-                const int lim = min(pos[q], a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 16 * (e / 4) + e % 4 is visible up to here
-                mx[q] = -INFINITY;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float x = (e >> 2) * 16 + (e & 3) <= lim ? acc[q][e >> 2][e & 3] * a.scale_log2 : -INFINITY;
-                    acc[q][e >> 2][e & 3] = x;
-                    mx[q] = fmaxf(mx[q], x);
-                }
+            for (int e = 0; e < 16; e++) {
+                const float x = (e >> 2) * 8 + (e & 3) <= lim ? acc[e] * a.scale_log2 : -INFINITY;
+                acc[e] = x;
+                mx = fmaxf(mx, x);
             }
             add_scores(mx, 1.0f, std::true_type{});
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
-    // the four row groups of the wave, then the two halves
-#pragma unroll
-    for (int q = 0; q < CT; q++) {
-        float mt = fmaxf(m[q], __shfl_xor(m[q], 16));
-        mt = fmaxf(mt, __shfl_xor(mt, 32));
-        const float wgt = __builtin_amdgcn_exp2f(m[q] - ((mt == -INFINITY) ? 0.0f : mt));
-        l[q] *= wgt;
-        l[q] += __shfl_xor(l[q], 16);
-        l[q] += __shfl_xor(l[q], 32);
-        if (ENT) {
-            tx[q] *= wgt;
-            tx[q] += __shfl_xor(tx[q], 16);
-            tx[q] += __shfl_xor(tx[q], 32);
-        }
-        m[q] = mt;
-        if (half == 1 && g == 0) {
-            s_half[slot][q][0][c] = m[q];
-            s_half[slot][q][1][c] = l[q];
-            if (ENT)
-                s_half[slot][q][ENT ? 2 : 1][c] = tx[q];
-        }
+    // the two row groups of the wave, then the two halves
+    float mt = fmaxf(m, __shfl_xor(m, 32));
+    const float wgt = __builtin_amdgcn_exp2f(m - ((mt == -INFINITY) ? 0.0f : mt));
+    l *= wgt;
+    l += __shfl_xor(l, 32);
+    if (ENT) {
+        tx *= wgt;
+        tx += __shfl_xor(tx, 32);
+    }
+    m = mt;
+    if (half == 1 && g == 0) {
+        s_half[slot][0][c] = m;
+        s_half[slot][1][c] = l;
+        if (ENT)
+            s_half[slot][ENT ? 2 : 1][c] = tx;
     }
     __syncthreads();
     if (half == 1 || g != 0)
         return;
-    float entropies = 0.0f;
-#pragma unroll
-    for (int q = 0; q < CT; q++) {
-        const float mo = s_half[slot][q][0][c], mt = fmaxf(m[q], mo), ms = (mt == -INFINITY) ? 0.0f : mt;
-        const float w0 = __builtin_amdgcn_exp2f(m[q] - ms), w1 = __builtin_amdgcn_exp2f(mo - ms);
-        const float lw = l[q] * w0 + s_half[slot][q][1][c] * w1;
-        const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row[q];
-        if (valid[q]) {
-            const bool some = ENT ? lw != 0.0f : lw > 0.0f;   // (a row with a NaN score: its entropy is NaN, its column sums leave it out)
-            const float lse = some ? mt + log2f(lw) : -INFINITY;
-            const float expected = ENT && some ? (tx[q] * w0 + s_half[slot][q][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
-            if (ENT && a.block_sum) {
-                const float H = some ? entropy_of(lse, expected) : 0.0f;
-                entropies += H;
-                if (a.row_entropy)
-                    a.row_entropy[((int64_t)b * a.n_q_heads + h) * a.n_q + row[q]] = H;
-                continue;
-            }
-            a.lse2[o] = lse;
-            if (ENT)
-                a.ent_part[o] = expected;
-            if (split == 0)                                  // splits that other blocks have and this one does not: both values, since
-                for (int s = unit.n; s < a.ns1; s++) {       // a weight of 0 does not make a NaN left in the workspace harmless
-                    a.lse2[o + s * a.lse_split_stride] = -INFINITY;
-                    if (ENT)
-                        a.ent_part[o + s * a.lse_split_stride] = 0.0f;
-                }
-        }
-    }
+    const float mo = s_half[slot][0][c];
+    mt = fmaxf(m, mo);
+    const float ms = (mt == -INFINITY) ? 0.0f : mt;
+    const float w0 = __builtin_amdgcn_exp2f(m - ms), w1 = __builtin_amdgcn_exp2f(mo - ms);
+    const float lw = l * w0 + s_half[slot][1][c] * w1;
+    const bool some = ENT ? lw != 0.0f : lw > 0.0f;          // (a row with a NaN score: its entropy is NaN, its column sums leave it out)
+    const float lse = some ? mt + log2f(lw) : -INFINITY;
+    const float expected = ENT && some ? (tx * w0 + s_half[slot][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
     if (ENT && a.block_sum) {
-        for (int off = 8; off > 0; off >>= 1)
-            entropies += __shfl_xor(entropies, off);
+        float H = valid && some ? entropy_of(lse, expected) : 0.0f;
+        if (valid && a.row_entropy)
+            a.row_entropy[((int64_t)b * a.n_q_heads + h) * a.n_q + row] = H;
+        for (int off = 16; off > 0; off >>= 1)
+            H += __shfl_xor(H, off);
         if (c == 0)
-            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * 2 + slot] = entropies;
+            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * 2 + slot] = H;
+        return;
+    }
+    if (valid) {
+        const int64_t o = split * a.lse_split_stride + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad + row;
+        a.lse2[o] = lse;
+        if (ENT)
+            a.ent_part[o] = expected;
+        if (split == 0)                                      // splits that other blocks have and this one does not: both values, since
+            for (int s = unit.n; s < a.ns1; s++) {           // a weight of 0 does not make a NaN left in the workspace harmless
+                a.lse2[o + s * a.lse_split_stride] = -INFINITY;
+                if (ENT)
+                    a.ent_part[o + s * a.lse_split_stride] = 0.0f;
+            }
     }
 }
 
@@ -484,19 +434,20 @@ __global__ __launch_bounds__(256) void entropy_mean_kernel(const float *block_su
         ae[b] = ((s_part[0] + s_part[1]) + (s_part[2] + s_part[3])) / (float)n_rows;
 }
 
-// Pass 2: column sums of the probabilities.  One workgroup per (32 CT visual keys, head, sequence, row split).  The query
+// Pass 2: column sums of the probabilities.  One workgroup per (64 visual keys, head, sequence, row split).  The query
 // rows are streamed (RowStream); the four waves are two key slots x two row halves of a step, each with the K fragments of 32
 // keys in registers.  A lane sums its key columns over the rows it holds; the four row groups and the two halves are
 // combined at the end, so every (head, row split, key) sum has one fixed order.  The rows' log-sum-exps (combined from pass
 // 1's partial values) and positions are put into LDS for 512 rows at a time.
 // Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 19, Pixtral 37.4 -> 27.1, 16 SmolVLM sequences
 // 197 -> 151 us.  What bounds it there is the issue of vector instructions: the counters of that launch (123 us alone) show the vector ALU
-// busy 69 % of the time, the matrix cores 25 %, LDS 21 % without a bank conflict, 4.9 waves per SIMD.
+// busy 69 % of the time, the matrix cores 25 %, LDS 21 % without a bank conflict, 4.9 waves per SIMD.  Tiles of 32x32, which pass 1 takes, need more
+// registers or more LDS reads here and were 3-6 % slower; workgroups of 8 waves that hold 128 keys gained at most 3 % at 8 and 16 sequences and lost at fewer.
 template <int D, int NS1, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
-    constexpr int NKS = D / 32, WINDOW = 512;
+    constexpr int NKS = D / 32, WINDOW = 512, CT = COLS / 16;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
     __shared__ __attribute__((aligned(16))) float lds_lse[WINDOW];
     __shared__ __attribute__((aligned(16))) int32_t lds_pos[WINDOW];
@@ -509,7 +460,7 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     // x walks the heads with the KV head fastest (see pass 1): the query rows of a head stay in one XCD's L2
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
     const SplitUnit unit = split_unit(a.map2, a.order2, a.order2.n ? blockIdx.z : blockIdx.y);      // earlier key blocks are seen by more rows: they come first
-    const int blk0 = a.vis_start + unit.rank * 32 * CT, b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
+    const int blk0 = a.vis_start + unit.rank * BLOCK, b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
     const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
     bool kvalid[CT];
 #pragma unroll
@@ -1221,10 +1172,10 @@ CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_
     p.order1.n = p.order2.n = 0;
     if (dtype == DREAM_BF16) {
         const int resident = resident_groups(head_dim);
-        const int b1 = ceil_div(n_q, 32 * CT), b2 = ceil_div(vis_len > 0 ? vis_len : 1, 32 * CT), rows = ceil_div(n_q, 64);
+        const int b1 = ceil_div(n_q, BLOCK), b2 = ceil_div(vis_len > 0 ? vis_len : 1, BLOCK), rows = ceil_div(n_q, 64);
         const int64_t heads = (int64_t)n_heads * batch;
-        auto len1 = [&](int r) { return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * 32 * CT, n_q), n_keys), 64); };
-        auto len2 = [&](int r) { return with_pos ? rows : std::max(rows - std::min((vis_start + r * 32 * CT) / 64, rows), 0); };
+        auto len1 = [&](int r) { return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * BLOCK, n_q), n_keys), 64); };
+        auto len2 = [&](int r) { return with_pos ? rows : std::max(rows - std::min((vis_start + r * BLOCK) / 64, rows), 0); };
         p.ns1 = plan_splits(b1, heads, resident, entropy ? 10.0f : 0.0f, len1, &p.map1, &p.units1);
         p.ns2 = plan_splits(b2, heads, resident, 0.0f, len2, &p.map2, &p.units2);
         const int at_once = batch == 1 ? 2048 : 1024;
@@ -1252,8 +1203,8 @@ size_t compress_most(int batch, int n_heads, int head_dim, int n_q, int vis_len,
 {
     const int64_t heads = (int64_t)n_heads * batch;
     const int v = vis_len > 0 ? vis_len : 1;
-    const size_t lse = most_splits(ceil_div(n_q, 32 * CT), heads, head_dim, dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float);
-    const size_t part = most_splits(ceil_div(v, 32 * CT), heads, head_dim, dtype) * heads * v * sizeof(float);
+    const size_t lse = most_splits(ceil_div(n_q, BLOCK), heads, head_dim, dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float);
+    const size_t part = most_splits(ceil_div(v, BLOCK), heads, head_dim, dtype) * heads * v * sizeof(float);
     return DREAM_WORKSPACE_MIN_BYTES + align_up(lse, 256) + align_up(part, 256);
 }
 
@@ -1439,7 +1390,7 @@ size_t dream_attention_entropy_workspace(const dream_attn_desc *desc, int32_t n_
     if (!desc || desc->batch < 1 || desc->n_q_heads < 1 || n_q < 1)
         return DREAM_WORKSPACE_MIN_BYTES;
     const int64_t heads = (int64_t)desc->n_q_heads * desc->batch;
-    const size_t part = align_up(most_splits(ceil_div(n_q, 32 * CT), heads, desc->head_dim, desc->dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float), 256);
+    const size_t part = align_up(most_splits(ceil_div(n_q, BLOCK), heads, desc->head_dim, desc->dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float), 256);
     const size_t sums = align_up((size_t)desc->batch * ceil_div((int64_t)desc->n_q_heads * n_q, 256) * sizeof(float), 256);
     return DREAM_WORKSPACE_MIN_BYTES + 2 * part + sums;
 }
