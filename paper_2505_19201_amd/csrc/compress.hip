@@ -177,18 +177,20 @@ __device__ __forceinline__ float entropy_of(float lse, float expected)
 // Measured (attention entropy, all its launches): Pixtral prompt of 1279 tokens 28.6 -> 22.2 us, 16 SmolVLM sequences 251 -> 200 us.
 // The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
 // The reference raised by octaves and a step's fragments requested together: 22.7 -> 21.7 us and 188 -> 185 us for larger prompts, all launches.
-// What bounds it there is the issue of instructions.  One tile of 32x32 in the place of four of 16x16 is half the MFMAs for the same products, one
+// What bounds it there is the issue of instructions.  Where workgroups are many (take_double()) they hold 128 rows: four row slots, and a wave takes both halves of a step.
+// One tile of 32x32 in the place of four of 16x16 is half the MFMAs for the same products, one
 // reference and one pair of sums per lane: 16 SmolVLM sequences 193 -> 171 us, 8 of Gemma3 with 900 rows 58.5 -> 54.0, one LLaVA prompt 13.4 -> 12.7.
-template <int D, bool ENT, bool DIRECT>
+template <int D, bool ENT, bool DIRECT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
-    constexpr int NKS = D / 16;
+    constexpr int NKS = D / 16, HALVES = 4 / SLOTS, TILES = 2 / HALVES;      // TILES: halves of a step that a wave takes
+    static_assert(SLOTS == 2 || SLOTS == 4, "two row slots by two halves, or four row slots");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
-    __shared__ float s_half[2][ENT ? 3 : 2][COLS];
+    __shared__ float s_half[HALVES == 2 ? SLOTS : 1][ENT ? 3 : 2][COLS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slot = wave & 1, half = wave >> 1;
+    const int slot = wave & (SLOTS - 1), half = wave / SLOTS;
     const int c = lane & 31, g = lane >> 5;
     // x walks the heads with the KV head fastest: workgroup ids that share a KV head are congruent mod 8
     // (when there are 8 or more KV heads), so its K is fetched into one XCD's L2 only
@@ -196,16 +198,19 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     // later row blocks see more keys: they come first
     const SplitUnit unit = split_unit(a.map1, a.order1, a.order1.n ? blockIdx.z : blockIdx.y);
     const int blk = a.map1.count[0] - 1 - unit.rank, b = a.order1.n ? blockIdx.y : blockIdx.z, split = unit.split;
-    const int row = (blk * 2 + slot) * COLS + c;
-    const bool valid = row < a.n_q;
+    // Blocks of 128 rows are counted from the last row up, so that with an odd number of 64s the half empty one is the shortest: the rows 0 to 63
+    const int from_end = (a.n_q + BLOCK - 1) / BLOCK - 2 * (unit.rank + 1);
+    const int row0 = SLOTS == 2 ? blk * BLOCK : max(from_end, 0) * BLOCK, row_end = SLOTS == 4 && from_end < 0 ? min(BLOCK, a.n_q) : a.n_q;
+    const int row = row0 + slot * COLS + c;
+    const bool valid = row < row_end;
     int pos = valid ? row : -1;
     // keys this workgroup has to see: without explicit positions, up to its last row
-    const int key_lim = a.q_pos ? a.n_keys : min(min((blk + 1) * BLOCK, a.n_q), a.n_keys);
+    const int key_lim = a.q_pos ? a.n_keys : min(min(row0 + SLOTS * COLS, row_end), a.n_keys);
     const int n_steps_all = (key_lim + STEP - 1) / STEP;
     const int sps = (n_steps_all + unit.n - 1) / unit.n;
     const int s0 = split * sps, n_steps = max(min(sps, n_steps_all - s0), 0);   // steps s0 .. s0 + n_steps - 1
     // the wave's first and last position (rows that do not exist keep nothing, so they do not count)
-    int wave_min_pos = (blk * 2 + slot) * COLS, wave_max_pos = wave_min_pos < a.n_q ? min(wave_min_pos + COLS, a.n_q) - 1 : -1;
+    int wave_min_pos = row0 + slot * COLS, wave_max_pos = wave_min_pos < row_end ? min(wave_min_pos + COLS, row_end) - 1 : -1;
     if (a.q_pos) {
         if (valid)
             pos = a.q_pos[(int64_t)b * a.n_q + row];
@@ -222,14 +227,21 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     const uint16_t *kb = reinterpret_cast<const uint16_t *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * D;
     RowStream<D, DIRECT> keys;
     keys.init(kb, D * 2, a.n_keys, s0, lds, wave, lane);
-    if (n_steps > 0) {
+    auto first_keys = [&] {
+        if (n_steps > 0) {
 #pragma unroll
-        for (int i = 0; i < G::NS - 1; i++)
-            keys.issue(i);
-    }
-    // the rows come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
+            for (int i = 0; i < G::NS - 1; i++)
+                keys.issue(i);
+        }
+    };
+    // the rows come the same way, as whole lines, and once for all waves that hold them: 64 of them into the stage that step 1 will take, 128 into both stages
+    // before the keys
     RowStream<D, DIRECT> rows;
-    rows.init(reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D, (int64_t)a.n_q_heads * D * 2, a.n_q, blk, lds, wave, lane);
+    rows.init(reinterpret_cast<const uint16_t *>(a.q) + ((int64_t)b * a.n_q * a.n_q_heads + h) * D, (int64_t)a.n_q_heads * D * 2, a.n_q, row0 / STEP, lds, wave, lane);
+    if (SLOTS == 2)
+        first_keys();
+    else
+        rows.issue(0);
     rows.issue(1);
     int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
 #pragma unroll
@@ -240,7 +252,11 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < NKS; ks++)
-        qf[ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + slot * COLS * G::ROW + frag[ks]);
+        qf[ks] = *reinterpret_cast<const bf16x8 *>(lds + (SLOTS == 2 ? G::STAGE : 0) + slot * COLS * G::ROW + frag[ks]);
+    if (SLOTS == 4) {
+        __syncthreads();                                         // the rows have been read
+        first_keys();
+    }
     float m = -INFINITY, l = 0.0f, tx = 0.0f;
     for (int i = 0, stage = 0; i < n_steps; i++) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * G::NLD) : "memory");   // this wave's share of step i has landed
@@ -249,22 +265,22 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         const unsigned char *st = lds + stage * G::STAGE + half * 32 * G::ROW;
         stage = stage == G::NS - 1 ? 0 : stage + 1;
         const int key0 = (s0 + i) * STEP + half * 32;
-        if (key0 > wave_max_pos)
-            continue;   // causal: nothing in this half is visible to this wave's rows
-        f32x16 acc = {};
-        bf16x8 kf[NKS];                                          // requested together: the waits then fall behind the first products
+        // tile t: keys key0 + t * 32 .. + 31
+        auto products = [&](int t, f32x16 &acc) {
+            acc = f32x16{};
+            bf16x8 kf[NKS];                                      // requested together: the waits then fall behind the first products
 #pragma unroll
-        for (int ks = 0; ks < NKS; ks++)
-            kf[ks] = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int ks = 0; ks < NKS; ks++)
+                kf[ks] = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[ks]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < NKS; ks++)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], acc, 0, 0, 0);
-        const bool open = key0 + 31 <= wave_min_pos && key0 + 31 < a.n_keys && a.scale_log2 > 0.0f;
+            for (int ks = 0; ks < NKS; ks++)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], acc, 0, 0, 0);
+        };
         // The row's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
         // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores; masked: some are -inf, the mark of a
         // key that the row does not see (a NaN is no mark: it makes the row's sums NaN)
-        auto add_scores = [&](float mx, float mult, auto masked) {
+        auto add_scores = [&](const auto &acc, float mx, float mult, auto masked) {
             if (__any(mx > m + 8.0f)) {
                 const float m_new = mx > m + 8.0f ? mx : m, alpha = m_new == m ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);   // (0 when the old reference was -inf)
                 m = m_new;
@@ -275,38 +291,61 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
             const float neg_m = m == -INFINITY ? 0.0f : -m;
             float sum = 0.0f, xsum = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const float x = acc[e], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
-                sum += p;
-                if (ENT)
-                    xsum = fmaf(p, decltype(masked)::value ? fmaxf(x, -3.0e38f) : x, xsum);   // (finite, so that times a probability of 0 it is 0)
-            }
+            for (int t = 0; t < (int)std::extent<std::remove_reference_t<decltype(acc)>>::value; t++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const float x = acc[t][e], p = __builtin_amdgcn_exp2f(fmaf(x, mult, neg_m));
+                    sum += p;
+                    if (ENT)
+                        xsum = fmaf(p, decltype(masked)::value ? fmaxf(x, -3.0e38f) : x, xsum);   // (finite, so that times a probability of 0 it is 0)
+                }
             l += sum;
             if (ENT)
                 tx = fmaf(xsum, mult, tx);
         };
-        if (open) {
-            // every key of the half is visible to every row of the wave (all but those on the diagonal):
-            // no masking, the maximum is taken before scaling and the scale rides in the exponent's fma
+        // the last key of `n` tiles from tile t on is visible to every row of the wave (all but those on the diagonal): no masking,
+        // the maximum is taken before scaling and the scale rides in the exponent's fma
+        auto open = [&](int t, int n) { return key0 + (t + n) * 32 - 1 <= wave_min_pos && key0 + (t + n) * 32 - 1 < a.n_keys && a.scale_log2 > 0.0f; };
+        auto add_open = [&](const auto &acc) {
             float x = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < 16; e++)
-                x = fmaxf(x, acc[e]);
-            add_scores(x * a.scale_log2, a.scale_log2, std::false_type{});
-        } else {
-            const int lim = min(pos, a.n_keys - 1) - key0 - g * 4;      // key g * 4 + 8 * (e / 4) + e % 4 is visible up to here
-            float mx = -INFINITY;
+            for (int t = 0; t < (int)std::extent<std::remove_reference_t<decltype(acc)>>::value; t++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const float x = (e >> 2) * 8 + (e & 3) <= lim ? acc[e] * a.scale_log2 : -INFINITY;
-                acc[e] = x;
-                mx = fmaxf(mx, x);
+                for (int e = 0; e < 16; e++)
+                    x = fmaxf(x, acc[t][e]);
+            add_scores(acc, x * a.scale_log2, a.scale_log2, std::false_type{});
+        };
+        if (TILES == 2 && open(0, TILES)) {
+            f32x16 acc[TILES];
+#pragma unroll
+            for (int t = 0; t < TILES; t++)
+                products(t, acc[t]);
+            add_open(acc);
+            continue;
+        }
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            if (key0 + t * 32 > wave_max_pos)
+                continue;   // causal: nothing in this tile is visible to this wave's rows
+            f32x16 acc[1];
+            products(t, acc[0]);
+            if (open(t, 1)) {
+                add_open(acc);
+            } else {
+                const int lim = min(pos, a.n_keys - 1) - key0 - t * 32 - g * 4;      // key g * 4 + 8 * (e / 4) + e % 4 is visible up to here
+                float mx = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const float x = (e >> 2) * 8 + (e & 3) <= lim ? acc[0][e] * a.scale_log2 : -INFINITY;
+                    acc[0][e] = x;
+                    mx = fmaxf(mx, x);
+                }
+                add_scores(acc, mx, 1.0f, std::true_type{});
             }
-            add_scores(mx, 1.0f, std::true_type{});
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
-    // the two row groups of the wave, then the two halves
+    // the two row groups of the wave, then the halves of the steps where two waves took them
     float mt = fmaxf(m, __shfl_xor(m, 32));
     const float wgt = __builtin_amdgcn_exp2f(m - ((mt == -INFINITY) ? 0.0f : mt));
     l *= wgt;
@@ -316,23 +355,30 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         tx += __shfl_xor(tx, 32);
     }
     m = mt;
-    if (half == 1 && g == 0) {
-        s_half[slot][0][c] = m;
-        s_half[slot][1][c] = l;
+    float lw = l, ew = tx;
+    if constexpr (HALVES == 2) {
+        if (half == 1 && g == 0) {
+            s_half[slot][0][c] = m;
+            s_half[slot][1][c] = l;
+            if (ENT)
+                s_half[slot][ENT ? 2 : 1][c] = tx;
+        }
+        __syncthreads();
+        if (half == 1 || g != 0)
+            return;
+        const float mo = s_half[slot][0][c];
+        mt = fmaxf(m, mo);
+        const float ms = (mt == -INFINITY) ? 0.0f : mt;
+        const float w0 = __builtin_amdgcn_exp2f(m - ms), w1 = __builtin_amdgcn_exp2f(mo - ms);
+        lw = l * w0 + s_half[slot][1][c] * w1;
         if (ENT)
-            s_half[slot][ENT ? 2 : 1][c] = tx;
-    }
-    __syncthreads();
-    if (half == 1 || g != 0)
+            ew = tx * w0 + s_half[slot][ENT ? 2 : 1][c] * w1;
+    } else if (g != 0) {
         return;
-    const float mo = s_half[slot][0][c];
-    mt = fmaxf(m, mo);
-    const float ms = (mt == -INFINITY) ? 0.0f : mt;
-    const float w0 = __builtin_amdgcn_exp2f(m - ms), w1 = __builtin_amdgcn_exp2f(mo - ms);
-    const float lw = l * w0 + s_half[slot][1][c] * w1;
+    }
     const bool some = ENT ? lw != 0.0f : lw > 0.0f;          // (a row with a NaN score: its entropy is NaN, its column sums leave it out)
     const float lse = some ? mt + log2f(lw) : -INFINITY;
-    const float expected = ENT && some ? (tx * w0 + s_half[slot][ENT ? 2 : 1][c] * w1) / lw : 0.0f;
+    const float expected = ENT && some ? ew / lw : 0.0f;
     if (ENT && a.block_sum) {
         float H = valid && some ? entropy_of(lse, expected) : 0.0f;
         if (valid && a.row_entropy)
@@ -340,7 +386,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         for (int off = 16; off > 0; off >>= 1)
             H += __shfl_xor(H, off);
         if (c == 0)
-            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * 2 + slot] = H;
+            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * SLOTS + slot] = H;
         return;
     }
     if (valid) {
@@ -442,25 +488,28 @@ __global__ __launch_bounds__(256) void entropy_mean_kernel(const float *block_su
 // Measured (compression with the caller's log-sum-exps, all its launches): LLaVA 25.4 -> 19, Pixtral 37.4 -> 27.1, 16 SmolVLM sequences
 // 197 -> 151 us.  What bounds it there is the issue of vector instructions: the counters of that launch (123 us alone) show the vector ALU
 // busy 69 % of the time, the matrix cores 25 %, LDS 21 % without a bank conflict, 4.9 waves per SIMD.  Tiles of 32x32, which pass 1 takes, need more
-// registers or more LDS reads here and were 3-6 % slower; workgroups of 8 waves that hold 128 keys gained at most 3 % at 8 and 16 sequences and lost at fewer.
-template <int D, int NS1, bool DIRECT>
+// registers or more LDS reads here and were 3-6 % slower.  Where workgroups are many (take_double()) they hold 128 keys in four key slots, and a wave takes both halves of a
+// step: 16 Pixtral sequences of 1279 tokens 160.8 -> 144.3, 32 Gemma3 of 2000 296 -> 263, 16 SmolVLM of 1600 137.8 -> 132.8 us, the same bits.  (8 waves that hold 128 keys, halves
+// apart: 3 % at most.)
+template <int D, int NS1, bool DIRECT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
-    constexpr int NKS = D / 32, WINDOW = 512, CT = COLS / 16;
+    constexpr int NKS = D / 32, WINDOW = 512, CT = COLS / 16, HALVES = 4 / SLOTS, TILES = 2 / HALVES;   // TILES: halves of a step that a wave takes
+    static_assert(SLOTS == 2 || SLOTS == 4, "two key slots by two halves, or four key slots");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
     __shared__ __attribute__((aligned(16))) float lds_lse[WINDOW];
     __shared__ __attribute__((aligned(16))) int32_t lds_pos[WINDOW];
-    __shared__ float s_half[2][CT][16];
+    __shared__ float s_half[HALVES == 2 ? SLOTS : 1][CT][16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slot = wave & 1, half = wave >> 1;
+    const int slot = wave & (SLOTS - 1), half = wave / SLOTS;
     const int c = lane & 15, g = lane >> 4;
     const int vis_end = a.vis_start + a.vis_len;
     // x walks the heads with the KV head fastest (see pass 1): the query rows of a head stay in one XCD's L2
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
     const SplitUnit unit = split_unit(a.map2, a.order2, a.order2.n ? blockIdx.z : blockIdx.y);      // earlier key blocks are seen by more rows: they come first
-    const int blk0 = a.vis_start + unit.rank * BLOCK, b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
+    const int blk0 = a.vis_start + unit.rank * (SLOTS * COLS), b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
     const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
     bool kvalid[CT];
 #pragma unroll
@@ -477,14 +526,21 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     const float *lrow = a.lse2 + ((int64_t)b * a.n_q_heads + h) * a.n_q_pad;
     RowStream<D, DIRECT> rows;
     rows.init(qb, (int64_t)a.n_q_heads * D * 2, a.n_q, s_first, lds, wave, lane);
-    if (n_steps > 0) {
+    auto first_rows = [&] {
+        if (n_steps > 0) {
 #pragma unroll
-        for (int i = 0; i < G::NS - 1; i++)
-            rows.issue(i);
-    }
-    // the keys come the same way, into the stage that step 1 will take: as whole lines, and once for the two halves
+            for (int i = 0; i < G::NS - 1; i++)
+                rows.issue(i);
+        }
+    };
+    // the keys come the same way, as whole lines, and once for all waves that hold them: 64 of them into the stage that step 1 will take, 128 into both stages
+    // before the rows
     RowStream<D, DIRECT> keys;
     keys.init(reinterpret_cast<const uint16_t *>(a.k) + (((int64_t)b * a.n_kv_heads + kvh) * a.s_max + blk0) * D, D * 2, a.n_keys - blk0, 0, lds, wave, lane);
+    if (SLOTS == 2)
+        first_rows();
+    else
+        keys.issue(0);
     keys.issue(1);
     // log-sum-exps over all keys (in log2 units) and positions of rows row0 .. row0 + WINDOW - 1
     auto fill_window = [&](int row0) {
@@ -519,10 +575,12 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
             lds_lse[w] = L > -INFINITY ? L : INFINITY;           // +inf makes the probability zero: rows that do not exist or see no key
         }
     };
-    float cs[CT];
+    float cs[TILES][CT];
 #pragma unroll
-    for (int q = 0; q < CT; q++)
-        cs[q] = 0.0f;
+    for (int t = 0; t < TILES; t++)
+#pragma unroll
+        for (int q = 0; q < CT; q++)
+            cs[t][q] = 0.0f;
     int frag[NKS];                 // byte offsets of this lane's fragments in a half of a stage
 #pragma unroll
     for (int ks = 0; ks < NKS; ks++)
@@ -534,7 +592,12 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     for (int q = 0; q < CT; q++)
 #pragma unroll
         for (int ks = 0; ks < NKS; ks++)
-            kf[q][ks] = *reinterpret_cast<const bf16x8 *>(lds + G::STAGE + (slot * CT + q) * 16 * G::ROW + frag[ks]);
+            kf[q][ks] = *reinterpret_cast<const bf16x8 *>(lds + (SLOTS == 2 ? G::STAGE : 0) + (slot * CT + q) * 16 * G::ROW + frag[ks]);
+    if (SLOTS == 4) {
+        __syncthreads();                                         // the keys have been read
+        first_rows();
+    }
+    const bool none = SLOTS == 4 && j0 >= vis_end;               // a wave past the last key only loads
     for (int i = 0, stage = 0; i < n_steps; i++) {
         if (i % (WINDOW / STEP) == 0) {
             if (i > 0)
@@ -547,50 +610,74 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
         const unsigned char *st = lds + stage * G::STAGE + half * 32 * G::ROW;
         stage = stage == G::NS - 1 ? 0 : stage + 1;
         const int r0 = (s_first + i) * STEP + half * 32, w0 = i % (WINDOW / STEP) * STEP + half * 32;
-        if (!a.q_pos && r0 + 31 < j0)
-            continue;   // causal: these rows sit before this wave's keys
-        const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + g * 4]);
-        const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + 16 + g * 4]);
-        const int32_t *pp = &lds_pos[w0 + g * 4];
-        f32x4 acc[CT][2];
+        // tile t: rows r0 + t * 32 .. + 31, in two accumulators of 16
+        auto products = [&](int t, f32x4 (&acc)[CT][2]) {
 #pragma unroll
-        for (int q = 0; q < CT; q++)
-            acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int q = 0; q < CT; q++)
+                acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < NKS; ks++) {
-            const bf16x8 q0 = *reinterpret_cast<const bf16x8 *>(st + frag[ks]);
-            const bf16x8 q1 = *reinterpret_cast<const bf16x8 *>(st + 16 * G::ROW + frag[ks]);
+            for (int ks = 0; ks < NKS; ks++) {
+                const bf16x8 q0 = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[ks]);
+                const bf16x8 q1 = *reinterpret_cast<const bf16x8 *>(st + (t * 32 + 16) * G::ROW + frag[ks]);
 #pragma unroll
-            for (int q = 0; q < CT; q++) {
-                acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kf[q][ks], acc[q][0], 0, 0, 0);
-                acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kf[q][ks], acc[q][1], 0, 0, 0);
+                for (int q = 0; q < CT; q++) {
+                    acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kf[q][ks], acc[q][0], 0, 0, 0);
+                    acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kf[q][ks], acc[q][1], 0, 0, 0);
+                }
             }
-        }
-        if (!a.q_pos && r0 >= j0 + 16 * CT - 1) {
-            // every row of the half sits at or after every key of this wave: nothing to mask
+        };
+        // every row of the tile sits at or after every key of this wave: nothing to mask
+        auto add_open = [&](int t, const f32x4 (&acc)[CT][2]) {
+            const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + g * 4]);
+            const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + 16 + g * 4]);
 #pragma unroll
             for (int q = 0; q < CT; q++)
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                    cs[q] += __builtin_amdgcn_exp2f(fmaf(acc[q][0][r], a.scale_log2, -L0[r]));
-                    cs[q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L1[r]));
+                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][0][r], a.scale_log2, -L0[r]));
+                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L1[r]));
                 }
-        } else {
+        };
+        if (none)
+            continue;
+        if (TILES == 2 && !a.q_pos && r0 >= j0 + 16 * CT - 1) {
+            f32x4 acc[TILES][CT][2];
+#pragma unroll
+            for (int t = 0; t < TILES; t++)
+                products(t, acc[t]);
+#pragma unroll
+            for (int t = 0; t < TILES; t++)
+                add_open(t, acc[t]);
+            continue;
+        }
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            const int rt = r0 + t * 32;
+            if (!a.q_pos && rt + 31 < j0)
+                continue;   // causal: these rows sit before this wave's keys
+            f32x4 acc[CT][2];
+            products(t, acc);
+            if (!a.q_pos && rt >= j0 + 16 * CT - 1) {
+                add_open(t, acc);
+                continue;
+            }
+            const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + g * 4]);
+            const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + 16 + g * 4]);
             i32x4 at0 = {0, 1, 2, 3}, at1 = {16, 17, 18, 19};      // positions, or without them the rows from the lane's first one on
             if (a.q_pos) {
-                at0 = *reinterpret_cast<const i32x4 *>(pp);
-                at1 = *reinterpret_cast<const i32x4 *>(pp + 16);
+                at0 = *reinterpret_cast<const i32x4 *>(&lds_pos[w0 + t * 32 + g * 4]);
+                at1 = *reinterpret_cast<const i32x4 *>(&lds_pos[w0 + t * 32 + 16 + g * 4]);
             }
 #pragma unroll
             for (int q = 0; q < CT; q++) {
-                // rows of the half from here on see the key: row r of this lane at position at0[r] or at1[r]
-                const int key = j0 + q * 16 + c - (a.q_pos ? 0 : r0 + g * 4);
+                // rows of the tile from here on see the key: row r of this lane at position at0[r] or at1[r]
+                const int key = j0 + q * 16 + c - (a.q_pos ? 0 : rt + g * 4);
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     const float p0 = __builtin_amdgcn_exp2f(acc[q][0][r] * a.scale_log2 - L0[r]);
                     const float p1 = __builtin_amdgcn_exp2f(acc[q][1][r] * a.scale_log2 - L1[r]);
-                    cs[q] += key <= at0[r] ? p0 : 0.0f;
-                    cs[q] += key <= at1[r] ? p1 : 0.0f;
+                    cs[t][q] += key <= at0[r] ? p0 : 0.0f;
+                    cs[t][q] += key <= at1[r] ? p1 : 0.0f;
                 }
             }
         }
@@ -598,12 +685,16 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the last step have landed before the LDS is given up
 #pragma unroll
     for (int q = 0; q < CT; q++) {
-        cs[q] += __shfl_xor(cs[q], 16);
-        cs[q] += __shfl_xor(cs[q], 32);
-        if (half == 1 && g == 0)
-            s_half[slot][q][c] = cs[q];
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            cs[t][q] += __shfl_xor(cs[t][q], 16);
+            cs[t][q] += __shfl_xor(cs[t][q], 32);
+        }
+        if (HALVES == 2 && half == 1 && g == 0)
+            s_half[slot][q][c] = cs[0][q];
     }
-    __syncthreads();
+    if (HALVES == 2)
+        __syncthreads();
     if (half == 1 || g != 0)
         return;
 #pragma unroll
@@ -611,7 +702,7 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
         const int key = j0 + q * 16 + c;
         if (key < vis_end) {
             float *to = a.part + ((int64_t)b * a.n_q_heads + h) * a.ns2 * a.vis_len + (key - a.vis_start);
-            to[split * a.vis_len] = kvalid[q] ? cs[q] + s_half[slot][q][c] : 0.0f;
+            to[split * a.vis_len] = kvalid[q] ? cs[0][q] + (HALVES == 2 ? s_half[HALVES == 2 ? slot : 0][q][c] : cs[TILES - 1][q]) : 0.0f;
             if (split == 0)                                  // splits that other blocks have and this one does not
                 for (int s = unit.n; s < a.ns2; s++)
                     to[s * a.vis_len] = 0.0f;
@@ -1050,14 +1141,30 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const unsigned char *s
     }
 }
 
-template <int D, bool DIRECT>
-void launch_colsum(int ns1, dim3 grid, hipStream_t st, const ScoreArgs &a)
+template <int D, bool ENT, bool DIRECT>
+void launch_lse(bool wide, dim3 grid, hipStream_t st, const ScoreArgs &a)
 {
+    if constexpr (DIRECT && D != 64)
+        if (wide) {
+            hipLaunchKernelGGL((scores_lse_bf16_kernel<D, ENT, true, 4>), grid, dim3(256), 0, st, a);
+            return;
+        }
+    hipLaunchKernelGGL((scores_lse_bf16_kernel<D, ENT, DIRECT, 2>), grid, dim3(256), 0, st, a);
+}
+
+template <int D, bool DIRECT>
+void launch_colsum(int ns1, bool wide, dim3 grid, hipStream_t st, const ScoreArgs &a)
+{
+    if constexpr (DIRECT)
+        if (wide) {
+            hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 1, true, 4>), grid, dim3(256), 0, st, a);
+            return;
+        }
     switch (ns1) {
-    case 1:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 1, DIRECT>), grid, dim3(256), 0, st, a); break;
-    case 2:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 2, DIRECT>), grid, dim3(256), 0, st, a); break;
-    case 4:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 4, DIRECT>), grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 8, DIRECT>), grid, dim3(256), 0, st, a); break;
+    case 1:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 1, DIRECT, 2>), grid, dim3(256), 0, st, a); break;
+    case 2:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 2, DIRECT, 2>), grid, dim3(256), 0, st, a); break;
+    case 4:  hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 4, DIRECT, 2>), grid, dim3(256), 0, st, a); break;
+    default: hipLaunchKernelGGL((scores_colsum_bf16_kernel<D, 8, DIRECT, 2>), grid, dim3(256), 0, st, a); break;
     }
 }
 
@@ -1154,22 +1261,38 @@ void order_units(int64_t heads, int units, int at_once, Len len, const SplitMap 
     order->n = n;
 }
 
+// Workgroups of two blocks (SLOTS = 4) in the place of one, where the blocks are whole and in the order of the map.  A wave then takes whole steps: half the barriers,
+// loads and first steps per score.  It pays where workgroups that are half as many still come to several rounds.  us, one block / two, by their number (of two), all launches:
+// column sums, head_dim 64: 1440 57.6 / 58.5, 1728 63.7 / 63.3, 2016 72.1 / 73.3, 2304 79.0 / 78.8, 3072 45.0 / 43.2, 4608 137.8 / 132.8; 128: 1024 52.2 / 56.0,
+// 1280 43.6 / 44.0 and 68.9 / 65.9, 1440 98.5 / 90.7, 1920 57.1 / 55.9, 4096 160.8 / 144.3; 256: 640 131.8 / 122.0, 1024 138.2 / 116.4, 2048 296 / 263 (fewer are dealt to the CUs).
+// Log-sum-exps (entropy), 128: 1152 29.6 / 33.1 and 74.0 / 63.6, 1536 62.6 / 64.8, 1760 68.1 / 68.4, 1920 44.3 / 45.8, 2304 74.8 / 72.3, 3072 65.9 / 64.3 but with 5 steps 39.7 / 40.7,
+// 5120 160 / 148; 256: 832 60.3 / 63.7, 1024 51.7 / 52.1, 1280 60.4 / 60.1 and 52.2 / 47.6, 1824 177 / 160, 2560 152 / 134; 64: 3328 91.6 / 93.4, 4096 39.8 / 44.6, 6656 169.8 / 165.4: one block.
+bool take_double(bool want, const UnitOrder &order, SplitMap *map, int *units)
+{
+    if (!want || order.n || *units != map->count[0])
+        return false;
+    *units = map->count[0] = ceil_div(map->count[0], 2);
+    return true;
+}
+
 struct CompressPlan {
     int n_q_pad, ns1, ns2;
     int units1, units2;            // (block, split) units of the two passes
     SplitMap map1, map2;
     UnitOrder order1, order2;
+    bool wide1, wide2;             // workgroups of twice a block
     size_t off_lse, off_part;
 };
 
 // `with_pos`: rows come with explicit positions, so any block may have to walk everything
-CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos, bool entropy)
+CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos, bool entropy, bool lse_given, bool direct)
 {
     CompressPlan p;
     p.n_q_pad = (n_q + 15) / 16 * 16;
     p.ns1 = p.ns2 = 1;
     p.units1 = p.units2 = 1;
     p.order1.n = p.order2.n = 0;
+    p.wide1 = p.wide2 = false;
     if (dtype == DREAM_BF16) {
         const int resident = resident_groups(head_dim);
         const int b1 = ceil_div(n_q, BLOCK), b2 = ceil_div(vis_len > 0 ? vis_len : 1, BLOCK), rows = ceil_div(n_q, 64);
@@ -1181,6 +1304,11 @@ CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_
         const int at_once = batch == 1 ? 2048 : 1024;
         order_units(heads, p.units1, at_once, len1, p.map1, &p.order1);
         order_units(heads, p.units2, at_once, len2, p.map2, &p.order2);
+        if (direct) {
+            const int64_t wgs1 = ceil_div(b1, 2) * heads, wgs2 = ceil_div(b2, 2) * heads;
+            p.wide1 = take_double(head_dim == 256 ? wgs1 >= 1280 : head_dim == 128 && wgs1 >= 2300 && len1(0) >= 8, p.order1, &p.map1, &p.units1);
+            p.wide2 = take_double((p.ns1 == 1 || lse_given) && wgs2 >= (head_dim == 64 ? 2048 : head_dim == 128 ? 1400 : 600), p.order2, &p.map2, &p.units2);
+        }
     }
     p.off_lse = DREAM_WORKSPACE_MIN_BYTES;
     p.off_part = align_up(p.off_lse + (size_t)p.ns1 * batch * n_heads * p.n_q_pad * sizeof(float), 256);
@@ -1208,6 +1336,9 @@ size_t compress_most(int batch, int n_heads, int head_dim, int n_q, int vis_len,
     return DREAM_WORKSPACE_MIN_BYTES + align_up(lse, 256) + align_up(part, 256);
 }
 
+// whether the rows of q and k start at multiples of 16 bytes (a row is D * 2 bytes, a multiple of 128)
+bool rows_aligned(const void *q, const void *k) { return ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k)) & 15) == 0; }
+
 // calls f with the head dimension, and whether the rows of q and k are 16-byte aligned (see RowStream), as compile-time constants
 template <class F>
 void with_rows(int head_dim, const void *q, const void *k, F f)
@@ -1220,7 +1351,7 @@ void with_rows(int head_dim, const void *q, const void *k, F f)
         else
             f(std::integral_constant<int, 256>{}, direct);
     };
-    if (((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k)) & 15) == 0)   // (a row is D * 2 bytes, a multiple of 128)
+    if (rows_aligned(q, k))
         with_dim(std::true_type{});
     else
         with_dim(std::false_type{});
@@ -1290,7 +1421,7 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
             return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
         if ((int64_t)vis_start + vis_len > n_keys)
             return fail(DREAM_ERR_INVALID_ARG, "%s: visual span [%d, %d) exceeds the %d live keys", who, vis_start, vis_start + vis_len, n_keys);
-        const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, vis_start, vis_len, desc->dtype, q_pos != nullptr, false);
+        const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, vis_start, vis_len, desc->dtype, q_pos != nullptr, false, row_lse_in != nullptr, rows_aligned(q, k_cache));
         const size_t need = compress_most(desc->batch, desc->n_q_heads, desc->head_dim, n_q, vis_len, desc->dtype);
         if (!workspace || workspace_bytes < need)
             return fail(DREAM_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", who, workspace_bytes, need);
@@ -1308,14 +1439,15 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
         if (desc->dtype == DREAM_BF16) {
             if (p.units1 > 65535)
                 return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grids", who, n_q);
-            const dim3 g1 = score_grid(desc, p.units1, p.order1), g2 = score_grid(desc, p.units2, p.order2);
+            const dim3 g1 = score_grid(desc, p.units1, p.order1);
+            const dim3 g2 = score_grid(desc, p.units2, p.order2);
             // pass 1 (the rows' log-sum-exps) only when the caller does not bring them
             with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
                 constexpr int D = decltype(dim)::value;
                 constexpr bool DIRECT = decltype(direct)::value;
                 if (!row_lse_in)
-                    hipLaunchKernelGGL((scores_lse_bf16_kernel<D, false, DIRECT>), g1, dim3(256), 0, st, a);
-                launch_colsum<D, DIRECT>(a.ns1, g2, st, a);
+                    launch_lse<D, false, DIRECT>(p.wide1, g1, st, a);
+                launch_colsum<D, DIRECT>(a.ns1, p.wide2, g2, st, a);
             });
         } else {
             if (n_q > 65535 * 1)
@@ -1413,7 +1545,7 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
         return fail(DREAM_ERR_INVALID_ARG, "%s: need n_q >= 1 and 1 <= n_keys <= s_max", who);
     if (!q_pos && n_q > n_keys)
         return fail(DREAM_ERR_INVALID_ARG, "%s: %d rows at positions 0..n_q-1 but only %d keys", who, n_q, n_keys);
-    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, 0, 0, desc->dtype, q_pos != nullptr, true);
+    const CompressPlan p = compress_plan(desc->batch, desc->n_q_heads, desc->head_dim, n_q, n_keys, 0, 0, desc->dtype, q_pos != nullptr, true, false, rows_aligned(q, k_cache));
     const size_t part = align_up((size_t)p.ns1 * desc->batch * desc->n_q_heads * p.n_q_pad * sizeof(float), 256);
     const int n_blocks = ceil_div((int64_t)desc->n_q_heads * n_q, 256);
     const size_t need = dream_attention_entropy_workspace(desc, n_q);
@@ -1443,7 +1575,9 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
             return fail(DREAM_ERR_UNSUPPORTED, "%s: n_q %d too large for the score grid", who, n_q);
         const dim3 g1 = score_grid(desc, p.units1, p.order1);
         with_rows(desc->head_dim, q, k_cache, [&](auto dim, auto direct) {
-            hipLaunchKernelGGL((scores_lse_bf16_kernel<decltype(dim)::value, true, decltype(direct)::value>), g1, dim3(256), 0, st, a);
+            constexpr int D = decltype(dim)::value;
+            constexpr bool DIRECT = decltype(direct)::value;
+            launch_lse<D, true, DIRECT>(p.wide1, g1, st, a);
         });
     } else {
         if (n_q > 65535)
@@ -1458,7 +1592,7 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
         hipLaunchKernelGGL(ROWS[p.ns1 == 8 ? 3 : p.ns1 / 2], dim3(n_blocks, desc->batch), dim3(256), 0, st, a, desc->dtype == DREAM_BF16 ? 1 : 0, row_entropy,
                            block_sum);
     }
-    hipLaunchKernelGGL(entropy_mean_kernel, dim3(desc->batch), dim3(256), 0, st, block_sum, whole ? desc->n_q_heads * p.map1.count[0] * 2 : n_blocks,
+    hipLaunchKernelGGL(entropy_mean_kernel, dim3(desc->batch), dim3(256), 0, st, block_sum, whole ? desc->n_q_heads * p.map1.count[0] * (p.wide1 ? 4 : 2) : n_blocks,
                        desc->n_q_heads * n_q, ae);
     return check_launch("entropy reduction kernels");
 }

@@ -271,6 +271,44 @@ def test_blocks_dealt_to_the_cus(gu, B, H, D, P, v, vis_start, with_pos):
     np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
 
 
+@pytest.mark.parametrize("with_pos", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,v,vis_start", [(32, 32, 32, 64, 200, 129, 3), (32, 32, 8, 64, 321, 128, 0), (15, 32, 32, 128, 520, 300, 17), (18, 32, 8, 128, 449, 385, 64),
+                                                      (27, 16, 8, 256, 300, 200, 0), (27, 16, 16, 256, 330, 193, 70)])
+def test_workgroups_of_two_blocks(gu, B, Hq, Hkv, D, P, v, vis_start, with_pos):
+    """Enough sequences for workgroups of 128 keys or rows, at odd and even numbers of 64s, against the same tensors one element further on, which take blocks of 64.
+    Column sums add the same terms in the same order: the same bits where the log-sum-exps are given.  Those themselves and the entropies are float32 sums of
+    a few hundred positive terms in another order: 2e-5 of a score, and of an entropy's scale (logarithms up to 10)."""
+    import torch
+    import paper_2505_19201_amd as dream
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1701 + P)
+    q = torch.empty(B, P, Hq, D, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    k = torch.empty(B, Hkv, P + 1, D, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    lse = torch.rand(B, Hq, P, generator=gen, device="cuda") + 5.0
+    pos = torch.stack([torch.randperm(P, generator=gen, device="cuda") for _ in range(B)]).int() if with_pos else None
+    desc = dream.attn_desc(B, Hq, Hkv, D, dream.BF16, P + 1)
+
+    def results(q, k):
+        out = []
+        for given in (lse, None):
+            scores = torch.full((B, v), float("nan"), device="cuda")
+            dream.dream_visual_compress(desc, q, pos, P, k, P, vis_start, v, 0, 1, None, scores, None, None, 0, None, 0,
+                                        gu.workspace(dream.dream_visual_compress_workspace(desc, P, v)), row_lse_in=given)
+            out.append(scores)
+        row, ae = torch.full((B, Hq, P), float("nan"), device="cuda"), torch.full((B,), float("nan"), device="cuda")
+        dream.dream_attention_entropy(desc, q, pos, P, k, P, row, ae, gu.workspace(dream.dream_attention_entropy_workspace(desc, P)))
+        return [x.cpu().numpy() for x in (*out, row, ae)]
+
+    q1 = torch.empty(q.numel() + 1, dtype=q.dtype, device="cuda")[1:].view(q.shape).copy_(q)
+    assert q1.data_ptr() % 16 == 2
+    got, want = results(q, k), results(q1, k)
+    assert all(np.isfinite(x).all() for x in got)
+    assert np.array_equal(got[0], want[0])
+    np.testing.assert_allclose(got[1], want[1], rtol=2e-5)
+    np.testing.assert_allclose(got[2], want[2], rtol=0, atol=2e-4 / 10)
+    np.testing.assert_allclose(got[3], want[3], rtol=0, atol=2e-4 / 10)
+
+
 @pytest.mark.parametrize("D,P,v", [(128, 1279, 1023), (64, 333, 300), (256, 449, 200)])
 def test_stale_workspace_is_never_read(gu, D, P, v):
     """Blocks with fewer splits than others, in both score passes, over a workspace of NaN patterns (the harness fills it)."""
