@@ -5,7 +5,7 @@
 // the target's own choice at the last accepted node is emitted as the bonus token (Section 4).
 //
 // argmax_partial_kernel streams the logits once (16-byte loads, one workgroup per row chunk) and
-// reduces (value, index) pairs with wavefront shuffles to one 64-bit key per chunk; ties always keep the lower
+// reduces (value, index) pairs to one 64-bit key per chunk; ties always keep the lower
 // index, so the result does not depend on how rows are chunked.  accept_walk_kernel, one workgroup per sequence, merges
 // the chunk keys of a node with adjacent lanes; then one wave lets every node check its own path to the root.
 #include "common.h"
@@ -23,14 +23,6 @@ namespace {
 constexpr int CHUNK_ELEMS = 8192;   // logits handled by one workgroup
 constexpr int MAX_DEVICES = 64;
 
-__device__ __forceinline__ void better(float &v, int &i, float ov, int oi)
-{
-    if (ov > v || (ov == v && oi < i)) {
-        v = ov;
-        i = oi;
-    }
-}
-
 // (value, index) as one integer whose order is "larger value, then lower index"
 __device__ __forceinline__ uint64_t make_key(float v, int i)
 {
@@ -39,74 +31,98 @@ __device__ __forceinline__ uint64_t make_key(float v, int i)
     return ((uint64_t)((u & 0x80000000u) ? ~u : (u | 0x80000000u)) << 32) | (0xffffffffu - (uint32_t)i);
 }
 
+// The smallest index of the wave, in every lane.
+__device__ __forceinline__ int wave_min(int v)
+{
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));   // row_ror:8, 4, 2, 1
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false));
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// Bound by the reading of the logits where there are many, by latency otherwise.  A thread asks for all of its 16-byte pieces at once, takes the maximum of each and looks for the
+// index only in the first piece that holds the wave's maximum: before, it waited for one piece after the other and compared element by
+// element.  Calls, us, before / now (both kernels): 60 rows of 262144 bf16 logits 13.1 / 11.0, of 32000 9.7 / 6.1, 16 x 60 of 49152 22.5 / 19.6, 4 x 33 of 131072 float32 21.0 / 15.8;
+// rows of odd lengths, which came one logit at a time: 60 of 32003 bf16 11.7 to 12.9 / 7.9, 8 x 60 of 50257 float32 43.6 / 21.0.
 template <bool BF16>
 __global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits, int vocab, int n_chunks, uint64_t *part)
 {
+    constexpr int PER = BF16 ? 8 : 4, PIECES = CHUNK_ELEMS / (256 * PER);     // logits of a piece, pieces of a thread
     const int chunk = blockIdx.x;
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int begin = chunk * CHUNK_ELEMS;
     const int end = min(begin + CHUNK_ELEMS, vocab);
-    float best = -INFINITY;
+    const char *p = reinterpret_cast<const char *>(logits) + (row * vocab + begin) * (BF16 ? 2 : 4);
+    // whole pieces in 16-byte loads, which global memory serves from any address of a logit, the tail one by one
+    typedef unsigned int piece __attribute__((ext_vector_type(4), aligned(2)));
+    const int n_vec = (end - begin) / PER;
+    u32x4 w[PIECES];
+    float piece_max[PIECES], best = -INFINITY;
     int best_i = 0x7fffffff;
-    if (BF16) {
-        const uint16_t *p = reinterpret_cast<const uint16_t *>(logits) + row * vocab;
-        // 16-byte vector loads when the row start allows it, scalar loads otherwise and for the tail
-        const bool aligned = (((uintptr_t)(p + begin)) & 15) == 0;
-        int vec_end = aligned ? begin + ((end - begin) & ~7) : begin;
-        for (int i = begin + tid * 8; i < vec_end; i += 256 * 8) {
-            const u32x4 u = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p + i));   // logits: read once
-            uint32_t w[4] = {u[0], u[1], u[2], u[3]};
+    auto at = [&](int j) { return min(j * 256 + tid, n_vec - 1); };           // past the last piece: that one again
+    auto element = [&](const u32x4 &v, int e) { return __uint_as_float(!BF16 ? v[e] : e & 1 ? v[e / 2] & 0xffff0000u : v[e / 2] << 16); };
+    float m = -INFINITY;
+    if (n_vec > 0) {
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                float lo = __uint_as_float(w[j] << 16), hi = __uint_as_float(w[j] & 0xffff0000u);
-                if (lo > best) { best = lo; best_i = i + 2 * j; }
-                if (hi > best) { best = hi; best_i = i + 2 * j + 1; }
+        for (int j = 0; j < PIECES; j++) {
+            const piece *from = reinterpret_cast<const piece *>(p) + at(j);
+            w[j] = BF16 ? __builtin_nontemporal_load(from) : *from;           // bf16 logits: read once
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < PIECES; j++) {
+            float x = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < PER; e++)
+                x = fmaxf(x, __builtin_canonicalizef(element(w[j], e)));      // passes a NaN over (a signalling one would take the maximum so far with it)
+            piece_max[j] = x;
+            m = fmaxf(m, x);
+        }
+    }
+    for (int i = begin + n_vec * PER + tid; i < end; i += 256) {
+        const float x = BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[i - begin]) : reinterpret_cast<const float *>(p)[i - begin];
+        if (x > best || (x == best && i < best_i)) { best = x; best_i = i; }
+    }
+    m = fmaxf(m, best);
+    m = wave_max(m);
+    int index = best == m ? best_i : 0x7fffffff;
+    if (n_vec > 0 && m > -INFINITY) {
+        // the thread's first piece with the maximum, the first logit of it (the pieces lie before the tail)
+        u32x4 first = {0, 0, 0, 0};
+        int from = -1;
+#pragma unroll
+        for (int j = PIECES - 1; j >= 0; j--)
+            if (piece_max[j] == m) {
+                first = w[j];
+                from = at(j);
             }
-        }
-        for (int i = vec_end + tid; i < end; i += 256) {
-            float x = bf16_bits_to_float(p[i]);
-            if (x > best || (x == best && i < best_i)) { best = x; best_i = i; }
-        }
-    } else {
-        const float *p = reinterpret_cast<const float *>(logits) + row * vocab;
-        const bool aligned = (((uintptr_t)(p + begin)) & 15) == 0;
-        int vec_end = aligned ? begin + ((end - begin) & ~3) : begin;
-        for (int i = begin + tid * 4; i < vec_end; i += 256 * 4) {
-            float4 u = *reinterpret_cast<const float4 *>(p + i);
-            if (u.x > best) { best = u.x; best_i = i; }
-            if (u.y > best) { best = u.y; best_i = i + 1; }
-            if (u.z > best) { best = u.z; best_i = i + 2; }
-            if (u.w > best) { best = u.w; best_i = i + 3; }
-        }
-        for (int i = vec_end + tid; i < end; i += 256) {
-            float x = p[i];
-            if (x > best || (x == best && i < best_i)) { best = x; best_i = i; }
+        if (from >= 0) {
+#pragma unroll
+            for (int e = PER - 1; e >= 0; e--)
+                index = element(first, e) == m ? begin + from * PER + e : index;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        float ov = __shfl_xor(best, off);
-        int oi = __shfl_xor(best_i, off);
-        better(best, best_i, ov, oi);
-    }
-    __shared__ float sv[4];
-    __shared__ int si[4];
-    if (lane == 0) {
-        sv[wave] = best;
-        si[wave] = best_i;
-    }
+    index = wave_min(index);
+    __shared__ uint64_t s_key[4];
+    if (lane == 0)
+        s_key[wave] = make_key(m, index);
     __syncthreads();
     if (tid == 0) {
+        uint64_t key = s_key[0];
         for (int w = 1; w < 4; w++)
-            better(best, best_i, sv[w], si[w]);
-        part[row * n_chunks + chunk] = make_key(best, best_i);
+            key = s_key[w] > key ? s_key[w] : key;
+        part[row * n_chunks + chunk] = key;
     }
 }
 
 // One workgroup per sequence.  `lanes` adjacent lanes (a power of two) merge the chunk results of a node; then one wave lets every
 // node check its own root path (a node is accepted iff every edge above it matches the target's arg-max and it is not deeper
-// than max_depth); the deepest accepted node, lowest index among equals, wins a wave reduction; lane 0 writes its path.
-// Latency bound.  Measured, 60 nodes of 32 chunks: 7.8 us with one wave that read a node's chunks one lane each, 5.6 us here.
+// than max_depth); the deepest accepted node, lowest index among equals, wins a wave reduction; lane 0 writes its path.  Trees of up to 64 nodes go down
+// level by level instead, a lane per node and a ballot per level, and up the path by lane reads: no chains of LDS reads.
+// Latency bound.  Measured, 60 nodes of 32 chunks: 7.8 us with one wave that read a node's chunks one lane each, 5.6 us with 512 threads, less by 1 to 2 us with these and with the
+// parents and tokens asked for beside the keys (the call with 60 nodes of 4 chunks: 9.7 / 6.1 us, with 200 nodes 11.1 / 9.8).
 constexpr int WALK = 512;
 
 __global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part, int n_chunks, int lanes, int n_tree, const int32_t *token,
@@ -118,20 +134,19 @@ __global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part,
     __shared__ int32_t s_tok[DREAM_MAX_TREE_ACCEPT];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int64_t bt = (int64_t)b * n_tree;
-    for (int i = tid; i < n_tree; i += WALK) {
-        const int par = parent[bt + i];
-        s_par[i] = par < i ? par : -1;   // a walk up the tree always ends
-        s_tok[i] = token[bt + i];
-    }
     const int sub = tid & (lanes - 1), per_pass = WALK / lanes;
     constexpr int U = 4;                 // passes whose loads are in flight together
-    for (int i0 = tid / lanes; i0 < n_tree; i0 += U * per_pass) {
+    const int own = min(tid, n_tree - 1);
+    int par_own = -1, tok_own = 0;       // of node tid
+    for (int i0 = tid / lanes; __any(i0 < n_tree); i0 += U * per_pass) {
         uint64_t best[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const int i = i0 + u * per_pass;
-            best[u] = i < n_tree && sub < n_chunks ? part[(bt + i) * n_chunks + sub] : 0ull;
+            const int i = min(i0 + u * per_pass, n_tree - 1);
+            best[u] = part[(bt + i) * n_chunks + min(sub, n_chunks - 1)];
         }
+        par_own = parent[bt + own];      // here, so that no wait for them stands before the keys are asked for
+        tok_own = token[bt + own];
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int i = i0 + u * per_pass;
@@ -150,9 +165,48 @@ __global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part,
             }
         }
     }
+    if (tid < n_tree) {                  // (its wave has been in the loop: lanes that share a node make no more than one node of a thread)
+        s_par[tid] = par_own < tid ? par_own : -1;   // a walk up the tree always ends
+        s_tok[tid] = tok_own;
+    }
+    for (int i = tid + WALK; i < n_tree; i += WALK) {
+        const int par = parent[bt + i];
+        s_par[i] = par < i ? par : -1;
+        s_tok[i] = token[bt + i];
+    }
     __syncthreads();
     if (tid >= 64)
         return;
+    int32_t *path = accept_path + (int64_t)b * (max_depth + 1);
+    if (n_tree <= 64) {
+        // lane i is node i: the accepted nodes of a level are those whose parent is one of the level before
+        const int par = lane > 0 && lane < n_tree && par_own < lane ? par_own : -1;
+        const bool fits = par >= 0 && tok_own == s_am[max(par, 0)];
+        uint64_t level = 1ull;
+        int depth = 0;
+        while (depth < max_depth) {
+            const uint64_t next = __ballot(fits && (level >> par & 1));
+            if (!next)
+                break;
+            level = next;
+            depth++;
+        }
+        const int deepest = __builtin_ctzll(level);
+        for (int t = depth + 1 + lane; t <= max_depth; t += 64)
+            path[t] = -1;
+        int n = deepest, mine = 0;       // lane t: node t of the path
+        for (int t = depth; t > 0; t--) {
+            mine = lane == t ? n : mine;
+            n = __builtin_amdgcn_readlane(par, n);
+        }
+        if (lane <= depth)
+            path[lane] = mine;
+        if (lane == 0) {
+            accept_len[b] = depth;
+            bonus_token[b] = s_am[deepest];
+        }
+        return;
+    }
     int best_d = -1, best_i = 0x7fffffff;
     for (int i = lane; i < n_tree; i += 64) {
         int d = 0;
@@ -176,7 +230,6 @@ __global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part,
     }
     if (lane == 0) {
         accept_len[b] = best_d;
-        int32_t *path = accept_path + (int64_t)b * (max_depth + 1);
         for (int t = best_d + 1; t <= max_depth; t++)
             path[t] = -1;
         int d = best_d;

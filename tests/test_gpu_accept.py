@@ -57,6 +57,55 @@ def test_ragged_vocab_and_planted_ties(gu, dtype, vocab):
     _compare(gu, logits, dtype, np.repeat(token, 2, 0), np.repeat(parent[None], 2, 0), 4)
 
 
+def _argmax(x):
+    """First index of the largest value, NaN passed over; a row without anything above -inf: not compared."""
+    return np.argmax(np.where(np.isnan(x), -np.inf, x), axis=-1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,vocab,depth", [(1, 9, 3), (2, 8, 0), (63, 4096, 5), (64, 16392, 2), (64, 8200, 70), (65, 8200, 70), (64, 50003, 4), (65, 16384, 2), (600, 40, 9)])
+def test_masked_logits_and_both_walks(gu, dtype, T, vocab, depth):
+    """Trees on both sides of 64 nodes, chains deeper than a wave, depth limits; logits of which most are -inf, some NaN (quiet and signalling), zeros of both signs, and ties in the
+    same 16 bytes, the same thread and others; rows on and off the 16-byte boundaries, chunks without and with a tail."""
+    g = di.rng(41, 903, vocab + T)
+    chain = depth >= 64
+    parent = np.array([[i - 1 for i in range(T)]] * 3 if chain else [di.random_tree(T, 5, 42 + b) if T > 1 else [-1] for b in range(3)], dtype=np.int32)
+    x = g.normal(size=(3, T, vocab)).astype(np.float32)
+    x = np.where(g.uniform(size=x.shape) < 0.7, np.float32(-np.inf), x)
+    x[..., g.integers(0, vocab, size=3)] = 0.0
+    x[0] = np.where(x[0] > 0, np.float32(-0.0), x[0])                 # zeros are the maximum of the first sequence, of either sign
+    x[0, :, vocab // 2] = 0.0
+    x[1, :, vocab // 3] = x[1, :, min(vocab // 3 + 1, vocab - 1)] = x[1, :, vocab - 1] = 7.0
+    x[2, :, vocab - 1] = 8.0
+    bits = di.f32_to_bf16_bits(x) if dtype == "bf16" else x.view(np.uint32).copy()
+    quiet, signalling = (0x7fc1, 0x7f81) if dtype == "bf16" else (0x7fc00001, 0x7f800001)
+    for nan in (quiet, signalling):
+        where = g.uniform(size=bits.shape) < 0.05
+        where[..., [vocab // 2, vocab // 3, vocab - 1]] = False
+        bits[where] = nan
+    logits = bits if dtype == "bf16" else bits.view(np.float32)
+    am = _argmax(di.bf16_bits_to_f32(bits) if dtype == "bf16" else logits).astype(np.int32)
+    token = g.integers(0, vocab, size=(3, T)).astype(np.int32)
+    follow = g.uniform(size=(3, T)) < (0.98 if chain else 0.6)         # these tokens are their parents' arg-max
+    for b in range(3):
+        for i in range(1, T):
+            if follow[b, i]:
+                token[b, i] = am[b, parent[b, i]]
+    node_argmax, accept_len, path, bonus = gu.run_accept(logits, dtype, token, parent, depth)
+    assert np.array_equal(node_argmax, am)
+    for b in range(3):
+        d = [0] + [-1] * (T - 1)
+        for i in range(1, T):
+            p = parent[b, i]
+            if d[p] >= 0 and token[b, i] == am[b, p] and d[p] < depth:
+                d[i] = d[p] + 1
+        end = int(np.argmax(d))
+        want, n = [-1] * (depth + 1), end
+        for t in range(d[end], -1, -1):
+            want[t], n = n, parent[b, n]
+        assert accept_len[b] == d[end] and path[b].tolist() == want and bonus[b] == am[b, end]
+
+
 def test_duplicate_siblings_chain_and_single_node(gu):
     parent = np.array([[-1, 0, 0, 1, 2]], dtype=np.int32)
     token = np.array([[0, 5, 5, 6, 6]], dtype=np.int32)
