@@ -48,6 +48,17 @@ def test_overlapping_moves_and_chain(gu):
     _compare(gu, [inp.k], "bf16", inp.prefix_len, 8, path, [0, 0])
 
 
+@pytest.mark.parametrize("alen", [(0, 15, 16), (31, 32, 63), (64, 127, 128), (254, 255, 100)])
+def test_every_number_of_chunks_a_thread(gu, alen):
+    """Paths of a tree of 256 nodes, rows of 16 chunks: one chunk a thread up to 16, with sources that other entries overwrite."""
+    T, B, Hkv, D, s_max = 256, 3, 2, 64, 270
+    caches = [di.normal((B, Hkv, s_max, D), "f32", 2200 + i, di.STREAM_K) for i in range(2)]
+    path = np.full((B, T), -1, dtype=np.int32)
+    for b in range(B):
+        path[b, :alen[b] + 1] = np.concatenate([[0], 1 + np.sort(di.rng(2201 + b, 904, alen[b]).permutation(T - 1)[:alen[b]])])
+    _compare(gu, caches, "f32", np.array([14, 0, 9], dtype=np.int32), T, path, list(alen))
+
+
 def test_more_caches_than_one_launch_carries(gu):
     cfg = di.Config("c", "f32", 1, 2, 2, 64, 128, 6, 2, 6, 3, 1, 2, 100, 1, 10)
     caches = [di.verify_inputs(cfg, sub=i).k for i in range(131)]
