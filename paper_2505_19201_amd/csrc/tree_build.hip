@@ -74,6 +74,9 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t k)
 // What bounds it is latency, not bytes (one LLaVA level is 0.6 MB): the chunk is read once, and between the loads and the
 // stores there are two barriers and no cross-lane exchange through LDS.  10 rows of 32000 bf16 logits: 7.0 -> 6.7 us, 80 rows of 49152 7.7 -> 7.1,
 // since a wave places its candidates by ballot (each one's LDS atomic before was waited for).
+// A call of both kernels, loads under conditions for the end of a row, each waited for before the next / all loads at once: 10 rows of 32000 bf16 10.8 / 9.8 us, 80 of 49152
+// 12.7 / 11.7, 10 of 262144 13.2 / 12.2, 10 of 32000 float32 10.9 / 10.0; rows of odd lengths one logit at a time / in pieces off their boundaries: 10 of 32003 bf16 12.6 / 11.2,
+// 80 of 50257 float32 24.0 / 22.8.
 template <bool BF16>
 __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits, int vocab, int n_chunks, int k, float *part_m,
                                                              float *part_s, uint64_t *part_key)
@@ -86,45 +89,42 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t below = (1ull << lane) - 1ull;
     const int begin = chunk * CHUNK;
-    // element e of this thread is token begin + (e / 8) * 2048 + tid * 8 + e % 8: 16-byte loads when the row allows
+    // element e of this thread is token begin + (e / 8) * 2048 + tid * 8 + e % 8.  Whole groups of 8 come in 16-byte loads, which global memory serves from any address of a logit (rows
+    // of an odd vocabulary start anywhere), the rest one by one.  All are asked for before the first is waited for, so there is no load under a condition: what lies past
+    // the end is another's and turned into -inf.
     float x[PER_THREAD];
-    if (BF16) {
-        const uint16_t *p = reinterpret_cast<const uint16_t *>(logits) + row * vocab;
-        const bool aligned = ((reinterpret_cast<uintptr_t>(p)) & 15) == 0;
+    constexpr int ESZ = BF16 ? 2 : 4, W = BF16 ? 1 : 2;   // bytes of a logit, 16-byte pieces of a group
+    typedef unsigned int piece __attribute__((ext_vector_type(4), aligned(2)));
+    const char *p = reinterpret_cast<const char *>(logits) + (row * vocab + begin) * ESZ;
+    const int n_here = min(CHUNK, vocab - begin), n_groups = n_here / 8;
+    auto one = [&](int t) { return BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[t]) : reinterpret_cast<const float *>(p)[t]; };
+    if (n_groups > 0) {
+        u32x4 w[PER_THREAD / 8][W];
 #pragma unroll
-        for (int j = 0; j < PER_THREAD / 8; j++) {
-            const int t0 = begin + j * 2048 + tid * 8;
-            if (aligned && t0 + 8 <= vocab) {
-                const u32x4 u = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p + t0));   // logits: read once
+        for (int j = 0; j < PER_THREAD / 8; j++)
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    x[j * 8 + 2 * q] = __uint_as_float(u[q] << 16);
-                    x[j * 8 + 2 * q + 1] = __uint_as_float(u[q] & 0xffff0000u);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    x[j * 8 + e] = t0 + e < vocab ? bf16_bits_to_float(p[t0 + e]) : -INFINITY;
+            for (int i = 0; i < W; i++) {
+                const piece *from = reinterpret_cast<const piece *>(p) + min(j * 256 + tid, n_groups - 1) * W + i;
+                w[j][i] = BF16 ? __builtin_nontemporal_load(from) : *from;     // bf16 logits: read once
             }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < PER_THREAD; e++) {
+            const int j = e / 8, q = e % 8;
+            x[e] = __uint_as_float(!BF16 ? w[j][q / 4 % W][q % 4] : q & 1 ? w[j][0][q / 2] & 0xffff0000u : w[j][0][q / 2] << 16);
         }
-    } else {
-        const float *p = reinterpret_cast<const float *>(logits) + row * vocab;
-        const bool aligned = ((reinterpret_cast<uintptr_t>(p)) & 15) == 0;
+    }
+    if (n_groups < CHUNK / 8) {
 #pragma unroll
-        for (int j = 0; j < PER_THREAD / 8; j++) {
-            const int t0 = begin + j * 2048 + tid * 8;
-            if (aligned && t0 + 8 <= vocab) {
-                const f32x4 u0 = *reinterpret_cast<const f32x4 *>(p + t0), u1 = *reinterpret_cast<const f32x4 *>(p + t0 + 4);
+        for (int e = 0; e < PER_THREAD; e++)
+            x[e] = e / 8 * 256 + tid < n_groups ? x[e] : -INFINITY;
+        if (n_here % 8) {                                                      // the last group is no whole one
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    x[j * 8 + q] = u0[q];
-                    x[j * 8 + 4 + q] = u1[q];
-                }
-            } else {
+            for (int j = 0; j < PER_THREAD / 8; j++)
+                if (j * 256 + tid == n_groups)
 #pragma unroll
-                for (int e = 0; e < 8; e++)
-                    x[j * 8 + e] = t0 + e < vocab ? p[t0 + e] : -INFINITY;
-            }
+                    for (int q = 0; q < 8; q++)
+                        x[j * 8 + q] = q < n_here % 8 ? one(min(n_groups * 8 + q, n_here - 1)) : -INFINITY;
         }
     }
 
