@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits,
     }
     m = fmaxf(m, best);
     m = wave_max(m);
-    int index = best == m ? best_i : 0x7fffffff;
+    int index = m > -INFINITY ? (best == m ? best_i : 0x7fffffff) : begin;     // nothing above -inf: the chunk's first, so that a fully masked row has index 0
     if (n_vec > 0 && m > -INFINITY) {
         // the thread's first piece with the maximum, the first logit of it (the pieces lie before the tail)
         u32x4 first = {0, 0, 0, 0};

@@ -106,6 +106,35 @@ def test_masked_logits_and_both_walks(gu, dtype, T, vocab, depth):
         assert accept_len[b] == d[end] and path[b].tolist() == want and bonus[b] == am[b, end]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [1, 3, 9, 300, 8192, 8200, 16384, 16387, 50257])
+def test_rows_without_anything_above_minus_infinity(gu, dtype, V):
+    """Fully masked rows (all -inf; -inf and NaN; all NaN) have index 0 as the oracle has, on and off the 16-byte boundaries, over one chunk and several, with and without a tail; a
+    chunk of -inf does not take the row from a finite logit in another one."""
+    import torch
+    import paper_2505_19201_amd as dream
+    x = np.full((1, 6, V), -np.inf, dtype=np.float32)
+    x[0, 1, V // 2] = np.nan
+    x[0, 2, 1:] = np.nan
+    x[0, 3] = np.nan
+    x[0, 4, V - 1] = -3.0
+    x[0, 5, V // 3] = -3.0e38
+    token, parent = np.zeros((1, 6), dtype=np.int32), np.array([[-1, 0, 1, 2, 3, 4]], dtype=np.int32)
+    logits = di.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    want = oracle.accept_path(logits, dtype, token, parent, 5)
+    assert want[0].tolist() == [[0, 0, 0, 0, V - 1, V // 3]]
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for off in (0, 1):
+        buf = torch.empty(x.size + off, dtype=tdt, device="cuda")
+        lg = buf[off:].view(x.shape).copy_(torch.from_numpy(x))
+        got = [torch.full((1, 6), -7, **i32), torch.full((1,), -7, **i32), torch.full((1, 6), -7, **i32), torch.full((1,), -7, **i32)]
+        dream.dream_accept_path(lg, dream.BF16 if dtype == "bf16" else dream.F32, 1, 6, V, torch.from_numpy(token).cuda(), torch.from_numpy(parent).cuda(), 5, *got,
+                                dream.alloc_workspace(dream.dream_accept_path_workspace(1, 6, V)))
+        for g, w, what in zip(got, want, ("node_argmax", "accept_len", "accept_path", "bonus_token")):
+            assert np.array_equal(g.cpu().numpy(), w), (what, off)
+
+
 def test_duplicate_siblings_chain_and_single_node(gu):
     parent = np.array([[-1, 0, 0, 1, 2]], dtype=np.int32)
     token = np.array([[0, 5, 5, 6, 6]], dtype=np.int32)
