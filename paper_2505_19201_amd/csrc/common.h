@@ -6,6 +6,7 @@
 #include <stdarg.h>
 #include <atomic>
 #include "dream.h"
+#include "sizes.h"
 
 namespace dream {
 
@@ -15,8 +16,6 @@ int fail(int status, const char *fmt, ...) __attribute__((format(printf, 2, 3)))
 int check_launch(const char *what);
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
-inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // Raises the dynamic-LDS limit of `kernel` on the current device, once per device; `done` is the kernel's own mask of devices.  (dream_init does it
 // for every kernel, a call that is first to one otherwise.  Two threads may both do it: harmless.)

@@ -1,0 +1,211 @@
+// How the two score passes of compress.hip are cut into workgroups: plain integer arithmetic, also compiled for the host by the test of these plans.
+#pragma once
+#include "dream.h"
+#include "sizes.h"
+#include <algorithm>
+#include <cmath>
+
+namespace dream {
+
+constexpr int COLS = 32;           // held rows or keys of a wave (64 halve the loads per score and measured 5-20 % slower: fewer workgroups)
+constexpr int BLOCK = 2 * COLS;    // of a workgroup: two column slots
+constexpr int STEP = 64;           // rows per step
+constexpr int MAX_SPLITS = 8;
+
+// Which blocks are split how often.  The causal triangle gives the blocks of a pass different numbers of steps; a block with
+// more than `S` of them is divided evenly over several workgroups, so that no workgroup of the launch walks more than S.
+// rank: position of a block when they are sorted by falling length; the first count[j] of them have a split j.
+struct SplitMap {
+    int32_t count[MAX_SPLITS];
+};
+struct SplitUnit {
+    int rank, split, n;     // block (by rank), its split, and how many splits it has
+};
+// The units of a launch whose workgroups all run at once, in the order of dispatch: 16 bits each, block * 64 + split * 8 + splits - 1.  See order_units().
+constexpr int MAX_ORDERED = 128, MAX_ORDERED_BLOCKS = 1024;
+struct UnitOrder {
+    uint32_t pair[MAX_ORDERED / 2];
+    int32_t n;              // units, or 0: the order of the map
+};
+__attribute__((always_inline)) constexpr SplitUnit split_unit(const SplitMap &map, const UnitOrder &order, int u)
+{
+    if (order.n) {
+        const uint32_t e = order.pair[u >> 1] >> (u & 1) * 16;
+        return {(int)(e >> 6 & (MAX_ORDERED_BLOCKS - 1)), (int)(e >> 3 & 7), (int)(e & 7) + 1};
+    }
+    SplitUnit r = {u, 0, 0};
+#pragma unroll
+    for (int j = 0; j < MAX_SPLITS - 1; j++)
+        if (r.split == j && r.rank >= map.count[j]) {
+            r.rank -= map.count[j];
+            r.split = j + 1;
+        }
+#pragma unroll
+    for (int j = 0; j < MAX_SPLITS; j++)
+        r.n += r.rank < map.count[j];
+    return r;
+}
+
+// Blocks are split while the launch would have fewer workgroups than this: two or three per CU.
+inline int resident_groups(int head_dim) { return head_dim == 256 ? 512 : 768; }
+
+// Splits of one pass.  `len(rank)`: steps of 64 keys or rows of a block, longest first; `heads`: workgroups per unit (heads times
+// sequences); `resident`: see above.  If the blocks as they are already fill the chip, they stay whole.  Otherwise a block is divided over workgroups of at
+// most S steps, two at least and at most 8 workgroups a block, with the S of least 3 R + 1.2 S, R = ceil(workgroups / 256): a workgroup that shares
+// its CU costs it about three steps (its own first loads and its end), and the longest one runs its steps one after the other, a step at 1.2
+// of what it takes of a CU's time when others fill the gaps.  At most four workgroups a CU are at work together (two at head_dim 256), and more were always slower.
+// `whole`: what a launch with whole blocks is worth, in these units: without partial values the entropies need one launch less
+// (all launches, us, split / whole: LLaVA 704 rows 13.7 / 13.4, 2 x 500 Pixtral rows 14.9 / 12.2; whole before / now: SmolVLM 1600 rows 22.1 / 20.6).
+// Entropy of one prompt, us, by S (all its launches, units in the order below): Pixtral 1279 rows 9 21.4, 10 20.1, 13 19.8, 16 20.5, 20 21.6; LLaVA 704
+// rows 3 14.8, 4 15.3, 5 14.7, 6 13.7, 7 14.0, 9 15.0; Gemma3 1280 rows 9 20.5, 10 19.2, 12 20.8, 16 23.8.  The rule takes 10, 6 and 10.
+template <class Len>
+int plan_splits(int blocks, int64_t heads, int resident, float whole, Len len, SplitMap *map, int *units)
+{
+    auto units_of = [&](int S) {
+        int64_t n = 0;
+        for (int r = 0; r < blocks; r++)
+            n += ceil_div(len(r), S);
+        return n;
+    };
+    const int longest = len(0) > 1 ? len(0) : 1;
+    int S = longest;
+    if ((int64_t)blocks * heads < resident) {
+        float best = INFINITY;
+        const int64_t together = resident > 512 ? 1024 : 512;
+        for (int s = std::max(2, ceil_div(longest, MAX_SPLITS)); s <= std::max(longest, 2); s++) {
+            const int64_t wgs = units_of(s) * heads;
+            const float cost = 3.0f * ceil_div(wgs, 256) + 1.2f * s - (s == longest ? whole : 0.0f);
+            if (wgs <= together && cost < best) {
+                best = cost;
+                S = s;
+            }
+        }
+    }
+    int most = 1;
+    *units = 0;
+    for (int j = 0; j < MAX_SPLITS; j++) {
+        int n = 0;
+        for (int r = 0; r < blocks; r++)
+            n += j == 0 || len(r) > j * S;
+        map->count[j] = n;
+        *units += n;
+        if (n > 0)
+            most = j + 1;
+    }
+    int pow2 = 1;   // 1, 2, 4 or 8: pass 2 is compiled for these counts of pass-1 splits
+    while (pow2 < most)
+        pow2 *= 2;
+    return pow2;
+}
+
+// Order of dispatch of a launch that is one round of workgroups.  Workgroup i starts on CU i mod 256, `heads` workgroups to a unit, so units 256 / heads
+// apart share a CU until the end of the launch: the longest go first, and every further round gives its longest to the CU with the fewest steps so far.
+template <class Len>
+void order_units(int64_t heads, int units, int at_once, Len len, const SplitMap &map, UnitOrder *order)
+{
+    order->n = 0;
+    if (units > MAX_ORDERED || units < 2 || map.count[0] > MAX_ORDERED_BLOCKS || units * heads > at_once || units * heads <= 256)
+        return;
+    struct Unit { int steps; uint32_t code; } unit[MAX_ORDERED];
+    int n = 0;
+    for (int r = 0; r < map.count[0]; r++) {
+        int of = 0;
+        while (of < MAX_SPLITS && r < map.count[of])
+            of++;
+        const int all = len(r), each = ceil_div(all, of);
+        for (int j = 0; j < of; j++)
+            unit[n++] = {std::max(std::min(each, all - j * each), 0), (uint32_t)(r << 6 | j << 3 | (of - 1))};
+    }
+    std::sort(unit, unit + n, [](const Unit &x, const Unit &y) { return x.steps != y.steps ? x.steps > y.steps : x.code < y.code; });
+    const int bins = (int)std::max<int64_t>(256 / heads, 1), rounds = ceil_div(n, bins);
+    struct Bin { int load; uint32_t code[MAX_ORDERED]; } bin[MAX_ORDERED];
+    for (int i = 0; i < std::min(bins, n); i++)
+        bin[i].load = 0;
+    int by_load[MAX_ORDERED];
+    for (int i = 0; i < std::min(bins, n); i++)
+        by_load[i] = i;
+    for (int t = 0; t < rounds; t++) {
+        std::sort(by_load, by_load + std::min(bins, n), [&](int x, int y) { return bin[x].load != bin[y].load ? bin[x].load < bin[y].load : x < y; });
+        for (int i = 0; i < std::min(bins, n - t * bins); i++) {
+            bin[by_load[i]].load += unit[t * bins + i].steps;
+            bin[by_load[i]].code[t] = unit[t * bins + i].code;
+        }
+    }
+    // the last round may be short: its bins come first in every round (by_load still says in which order it was dealt)
+    for (int i = 0; i < MAX_ORDERED / 2; i++)
+        order->pair[i] = 0;
+    for (int u = 0; u < n; u++)
+        order->pair[u >> 1] |= bin[by_load[u % bins]].code[u / bins] << (u & 1) * 16;
+    order->n = n;
+}
+
+// Workgroups of two blocks (SLOTS = 4) in the place of one, where the blocks are whole and in the order of the map.  A wave then takes whole steps: half the barriers,
+// loads and first steps per score.  It pays where workgroups that are half as many still come to several rounds.  us, one block / two, by their number (of two), all launches:
+// column sums, head_dim 64: 1440 57.6 / 58.5, 1728 63.7 / 63.3, 2016 72.1 / 73.3, 2304 79.0 / 78.8, 3072 45.0 / 43.2, 4608 137.8 / 132.8; 128: 1024 52.2 / 56.0,
+// 1280 43.6 / 44.0 and 68.9 / 65.9, 1440 98.5 / 90.7, 1920 57.1 / 55.9, 4096 160.8 / 144.3; 256: 640 131.8 / 122.0, 1024 138.2 / 116.4, 2048 296 / 263 (fewer are dealt to the CUs).
+// Log-sum-exps (entropy), 128: 1152 29.6 / 33.1 and 74.0 / 63.6, 1536 62.6 / 64.8, 1760 68.1 / 68.4, 1920 44.3 / 45.8, 2304 74.8 / 72.3, 3072 65.9 / 64.3 but with 5 steps 39.7 / 40.7,
+// 5120 160 / 148; 256: 832 60.3 / 63.7, 1024 51.7 / 52.1, 1280 60.4 / 60.1 and 52.2 / 47.6, 1824 177 / 160, 2560 152 / 134; 64: 3328 91.6 / 93.4, 4096 39.8 / 44.6, 6656 169.8 / 165.4: one block.
+inline bool take_double(bool want, const UnitOrder &order, SplitMap *map, int *units)
+{
+    if (!want || order.n || *units != map->count[0])
+        return false;
+    *units = map->count[0] = ceil_div(map->count[0], 2);
+    return true;
+}
+
+struct CompressPlan {
+    int n_q_pad, ns1, ns2;
+    int units1, units2;            // (block, split) units of the two passes
+    SplitMap map1, map2;
+    UnitOrder order1, order2;
+    bool wide1, wide2;             // workgroups of twice a block
+    size_t off_lse, off_part;
+};
+
+// `with_pos`: rows come with explicit positions, so any block may have to walk everything
+inline CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q, int n_keys, int vis_start, int vis_len, int dtype, bool with_pos, bool entropy, bool lse_given, bool direct)
+{
+    CompressPlan p;
+    p.n_q_pad = (n_q + 15) / 16 * 16;
+    p.ns1 = p.ns2 = 1;
+    p.units1 = p.units2 = 1;
+    p.order1.n = p.order2.n = 0;
+    p.wide1 = p.wide2 = false;
+    if (dtype == DREAM_BF16) {
+        const int resident = resident_groups(head_dim);
+        const int b1 = ceil_div(n_q, BLOCK), b2 = ceil_div(vis_len > 0 ? vis_len : 1, BLOCK), rows = ceil_div(n_q, 64);
+        const int64_t heads = (int64_t)n_heads * batch;
+        auto len1 = [&](int r) { return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * BLOCK, n_q), n_keys), 64); };
+        auto len2 = [&](int r) { return with_pos ? rows : std::max(rows - std::min((vis_start + r * BLOCK) / 64, rows), 0); };
+        p.ns1 = plan_splits(b1, heads, resident, entropy ? 10.0f : 0.0f, len1, &p.map1, &p.units1);
+        p.ns2 = plan_splits(b2, heads, resident, 0.0f, len2, &p.map2, &p.units2);
+        const int at_once = batch == 1 ? 2048 : 1024;
+        order_units(heads, p.units1, at_once, len1, p.map1, &p.order1);
+        order_units(heads, p.units2, at_once, len2, p.map2, &p.order2);
+        if (direct) {
+            const int64_t wgs1 = ceil_div(b1, 2) * heads, wgs2 = ceil_div(b2, 2) * heads;
+            p.wide1 = take_double(head_dim == 256 ? wgs1 >= 1280 : head_dim == 128 && wgs1 >= 2300 && len1(0) >= 8, p.order1, &p.map1, &p.units1);
+            p.wide2 = take_double((p.ns1 == 1 || lse_given) && wgs2 >= (head_dim == 64 ? 2048 : head_dim == 128 ? 1400 : 600), p.order2, &p.map2, &p.units2);
+        }
+    }
+    p.off_lse = DREAM_WORKSPACE_MIN_BYTES;
+    p.off_part = align_up(p.off_lse + (size_t)p.ns1 * batch * n_heads * p.n_q_pad * sizeof(float), 256);
+    return p;
+}
+
+// The most splits a plan of these sizes takes, whatever the keys and positions are (the workspace query knows neither).
+inline int most_splits(int64_t blocks, int64_t heads, int head_dim, int dtype)
+{
+    return dtype == DREAM_BF16 && blocks * heads < resident_groups(head_dim) ? MAX_SPLITS : 1;
+}
+
+inline size_t compress_most(int batch, int n_heads, int head_dim, int n_q, int vis_len, int dtype)
+{
+    const int64_t heads = (int64_t)n_heads * batch;
+    const int v = vis_len > 0 ? vis_len : 1;
+    const size_t lse = most_splits(ceil_div(n_q, BLOCK), heads, head_dim, dtype) * heads * ((n_q + 15) / 16 * 16) * sizeof(float);
+    const size_t part = most_splits(ceil_div(v, BLOCK), heads, head_dim, dtype) * heads * v * sizeof(float);
+    return DREAM_WORKSPACE_MIN_BYTES + align_up(lse, 256) + align_up(part, 256);
+}
+
+}  // namespace dream

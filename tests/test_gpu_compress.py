@@ -271,9 +271,13 @@ def test_blocks_dealt_to_the_cus(gu, B, H, D, P, v, vis_start, with_pos):
     np.testing.assert_allclose(scores, oracle.visual_scores(q, k, "bf16", vis_start, v, q_pos=pos), rtol=SCORE_RTOL["bf16"])
 
 
+# sizes, and whether workgroups of 128 keys or rows take the column sums with given log-sum-exps, those without, and the log-sum-exps (tests/test_score_plan.py asks the plan)
+TWO_BLOCKS = [((32, 32, 32, 64, 200, 129, 3), (1, 1, 0)), ((32, 32, 8, 64, 321, 250, 0), (1, 1, 0)), ((15, 32, 32, 128, 520, 300, 17), (1, 1, 1)), ((18, 32, 8, 128, 449, 385, 64), (1, 1, 1)),
+              ((16, 32, 8, 128, 600, 340, 5), (1, 1, 1)), ((27, 16, 8, 256, 300, 200, 0), (1, 1, 1)), ((27, 16, 16, 256, 330, 193, 70), (1, 1, 1)), ((27, 16, 8, 256, 400, 300, 9), (1, 1, 1))]
+
+
 @pytest.mark.parametrize("with_pos", [False, True])
-@pytest.mark.parametrize("B,Hq,Hkv,D,P,v,vis_start", [(32, 32, 32, 64, 200, 129, 3), (32, 32, 8, 64, 321, 128, 0), (15, 32, 32, 128, 520, 300, 17), (18, 32, 8, 128, 449, 385, 64),
-                                                      (27, 16, 8, 256, 300, 200, 0), (27, 16, 16, 256, 330, 193, 70)])
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,v,vis_start", [sizes for sizes, _ in TWO_BLOCKS])
 def test_workgroups_of_two_blocks(gu, B, Hq, Hkv, D, P, v, vis_start, with_pos):
     """Enough sequences for workgroups of 128 keys or rows, at odd and even numbers of 64s, against the same tensors one element further on, which take blocks of 64.
     Column sums add the same terms in the same order: the same bits where the log-sum-exps are given.  Those themselves and the entropies are float32 sums of
