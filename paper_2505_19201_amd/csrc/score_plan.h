@@ -49,8 +49,27 @@ __attribute__((always_inline)) constexpr SplitUnit split_unit(const SplitMap &ma
 // Blocks are split while the launch would have fewer workgroups than this: two or three per CU.
 inline int resident_groups(int head_dim) { return head_dim == 256 ? 512 : 768; }
 
-// Splits of one pass.  `len(rank)`: steps of 64 keys or rows of a block, longest first; `heads`: workgroups per unit (heads times
-// sequences); `resident`: see above.  If the blocks as they are already fill the chip, they stay whole.  Otherwise a block is divided over workgroups of at
+// Steps of 64 keys or rows that the blocks of a pass have, longest first: all the same, or (falls) one less from block to block down to none.
+struct BlockSteps {
+    int first;
+    bool falls;
+    int operator()(int rank) const { return falls ? std::max(first - rank, 0) : first; }
+    // of `blocks` blocks, those with more than n steps
+    int longer_than(int n, int blocks) const { return falls ? std::min(std::max(first - n, 0), blocks) : first > n ? blocks : 0; }
+    // workgroups of at most S steps that `blocks` blocks make
+    int64_t workgroups(int S, int blocks) const
+    {
+        if (!falls)
+            return (int64_t)blocks * ceil_div(first, S);
+        auto up_to = [S](int64_t n) {              // of blocks of 1, 2, .. n steps
+            const int64_t whole = n > 0 ? n / S : 0, rest = n > 0 ? n % S : 0;
+            return S * (whole * (whole + 1) / 2) + rest * (whole + 1);
+        };
+        return up_to(first) - up_to((int64_t)first - blocks);
+    }
+};
+
+// Splits of one pass.  `heads`: workgroups per unit (heads times sequences); `resident`: see above.  If the blocks as they are already fill the chip, they stay whole.  Otherwise a block is divided over workgroups of at
 // most S steps, two at least and at most 8 workgroups a block, with the S of least 3 R + 1.2 S, R = ceil(workgroups / 256): a workgroup that shares
 // its CU costs it about three steps (its own first loads and its end), and the longest one runs its steps one after the other, a step at 1.2
 // of what it takes of a CU's time when others fill the gaps.  At most four workgroups a CU are at work together (two at head_dim 256), and more were always slower.
@@ -58,38 +77,33 @@ inline int resident_groups(int head_dim) { return head_dim == 256 ? 512 : 768; }
 // (all launches, us, split / whole: LLaVA 704 rows 13.7 / 13.4, 2 x 500 Pixtral rows 14.9 / 12.2; whole before / now: SmolVLM 1600 rows 22.1 / 20.6).
 // Entropy of one prompt, us, by S (all its launches, units in the order below): Pixtral 1279 rows 9 21.4, 10 20.1, 13 19.8, 16 20.5, 20 21.6; LLaVA 704
 // rows 3 14.8, 4 15.3, 5 14.7, 6 13.7, 7 14.0, 9 15.0; Gemma3 1280 rows 9 20.5, 10 19.2, 12 20.8, 16 23.8.  The rule takes 10, 6 and 10.
-template <class Len>
-int plan_splits(int blocks, int64_t heads, int resident, float whole, Len len, SplitMap *map, int *units)
+// Every call makes its plan, so nothing here goes over the blocks once per S: with that it took 500 us of the host for one head of 32768 rows, 1.3 us for 32 heads of 704 (both passes, order
+// included), now 0.6 and 0.5, and the entropy of one head of 16384 rows took 84 us, now 49.
+inline int plan_splits(int blocks, int64_t heads, int resident, float whole, BlockSteps len, SplitMap *map, int *units)
 {
-    auto units_of = [&](int S) {
-        int64_t n = 0;
-        for (int r = 0; r < blocks; r++)
-            n += ceil_div(len(r), S);
-        return n;
-    };
     const int longest = len(0) > 1 ? len(0) : 1;
     int S = longest;
     if ((int64_t)blocks * heads < resident) {
         float best = INFINITY;
         const int64_t together = resident > 512 ? 1024 : 512;
-        for (int s = std::max(2, ceil_div(longest, MAX_SPLITS)); s <= std::max(longest, 2); s++) {
-            const int64_t wgs = units_of(s) * heads;
+        auto take_if_best = [&](int s) {
+            const int64_t wgs = len.workgroups(s, blocks) * heads;
             const float cost = 3.0f * ceil_div(wgs, 256) + 1.2f * s - (s == longest ? whole : 0.0f);
             if (wgs <= together && cost < best) {
                 best = cost;
                 S = s;
             }
-        }
+        };
+        for (int s = std::max(2, ceil_div(longest, MAX_SPLITS)); s < longest && 3.0f + 1.2f * s < best; s++)      // (a launch has one workgroup at least)
+            take_if_best(s);
+        take_if_best(std::max(longest, 2));
     }
     int most = 1;
     *units = 0;
     for (int j = 0; j < MAX_SPLITS; j++) {
-        int n = 0;
-        for (int r = 0; r < blocks; r++)
-            n += j == 0 || len(r) > j * S;
-        map->count[j] = n;
-        *units += n;
-        if (n > 0)
+        map->count[j] = j == 0 ? blocks : len.longer_than(j * S, blocks);
+        *units += map->count[j];
+        if (map->count[j] > 0)
             most = j + 1;
     }
     int pow2 = 1;   // 1, 2, 4 or 8: pass 2 is compiled for these counts of pass-1 splits
@@ -100,8 +114,7 @@ int plan_splits(int blocks, int64_t heads, int resident, float whole, Len len, S
 
 // Order of dispatch of a launch that is one round of workgroups.  Workgroup i starts on CU i mod 256, `heads` workgroups to a unit, so units 256 / heads
 // apart share a CU until the end of the launch: the longest go first, and every further round gives its longest to the CU with the fewest steps so far.
-template <class Len>
-void order_units(int64_t heads, int units, int at_once, Len len, const SplitMap &map, UnitOrder *order)
+inline void order_units(int64_t heads, int units, int at_once, BlockSteps len, const SplitMap &map, UnitOrder *order)
 {
     order->n = 0;
     if (units > MAX_ORDERED || units < 2 || map.count[0] > MAX_ORDERED_BLOCKS || units * heads > at_once || units * heads <= 256)
@@ -117,25 +130,24 @@ void order_units(int64_t heads, int units, int at_once, Len len, const SplitMap 
             unit[n++] = {std::max(std::min(each, all - j * each), 0), (uint32_t)(r << 6 | j << 3 | (of - 1))};
     }
     std::sort(unit, unit + n, [](const Unit &x, const Unit &y) { return x.steps != y.steps ? x.steps > y.steps : x.code < y.code; });
-    const int bins = (int)std::max<int64_t>(256 / heads, 1), rounds = ceil_div(n, bins);
-    struct Bin { int load; uint32_t code[MAX_ORDERED]; } bin[MAX_ORDERED];
-    for (int i = 0; i < std::min(bins, n); i++)
-        bin[i].load = 0;
-    int by_load[MAX_ORDERED];
-    for (int i = 0; i < std::min(bins, n); i++)
+    const int bins = std::min(std::max((int)(256 / heads), 1), n), rounds = ceil_div(n, bins);
+    int load[MAX_ORDERED], by_load[MAX_ORDERED], dealt[2 * MAX_ORDERED];      // dealt: the unit that round t gives bin i, at t * bins + i
+    for (int i = 0; i < bins; i++) {
+        load[i] = 0;
         by_load[i] = i;
+    }
     for (int t = 0; t < rounds; t++) {
-        std::sort(by_load, by_load + std::min(bins, n), [&](int x, int y) { return bin[x].load != bin[y].load ? bin[x].load < bin[y].load : x < y; });
+        std::sort(by_load, by_load + bins, [&](int x, int y) { return load[x] != load[y] ? load[x] < load[y] : x < y; });
         for (int i = 0; i < std::min(bins, n - t * bins); i++) {
-            bin[by_load[i]].load += unit[t * bins + i].steps;
-            bin[by_load[i]].code[t] = unit[t * bins + i].code;
+            load[by_load[i]] += unit[t * bins + i].steps;
+            dealt[t * bins + by_load[i]] = t * bins + i;
         }
     }
     // the last round may be short: its bins come first in every round (by_load still says in which order it was dealt)
     for (int i = 0; i < MAX_ORDERED / 2; i++)
         order->pair[i] = 0;
     for (int u = 0; u < n; u++)
-        order->pair[u >> 1] |= bin[by_load[u % bins]].code[u / bins] << (u & 1) * 16;
+        order->pair[u >> 1] |= unit[dealt[u / bins * bins + by_load[u % bins]]].code << (u & 1) * 16;
     order->n = n;
 }
 
@@ -175,8 +187,8 @@ inline CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q,
         const int resident = resident_groups(head_dim);
         const int b1 = ceil_div(n_q, BLOCK), b2 = ceil_div(vis_len > 0 ? vis_len : 1, BLOCK), rows = ceil_div(n_q, 64);
         const int64_t heads = (int64_t)n_heads * batch;
-        auto len1 = [&](int r) { return with_pos ? ceil_div(n_keys, 64) : ceil_div(std::min(std::min((b1 - r) * BLOCK, n_q), n_keys), 64); };
-        auto len2 = [&](int r) { return with_pos ? rows : std::max(rows - std::min((vis_start + r * BLOCK) / 64, rows), 0); };
+        // (without positions there are no more rows than keys)
+        const BlockSteps len1 = {with_pos ? ceil_div(n_keys, STEP) : b1, !with_pos}, len2 = {with_pos ? rows : rows - vis_start / STEP, !with_pos};
         p.ns1 = plan_splits(b1, heads, resident, entropy ? 10.0f : 0.0f, len1, &p.map1, &p.units1);
         p.ns2 = plan_splits(b2, heads, resident, 0.0f, len2, &p.map2, &p.units2);
         const int at_once = batch == 1 ? 2048 : 1024;

@@ -5,6 +5,7 @@ import math
 import os
 import random
 import subprocess
+import time
 
 import pytest
 from numpy import float32 as f32
@@ -99,6 +100,18 @@ def test_every_step_once_and_the_splits_of_least_cost(seed):
             if p["order%d" % which]:
                 assert p["order%d" % which] == n
         assert LIB.score_needs() <= LIB.score_workspace(B, H, D, n_q, v)
+
+
+def test_a_plan_is_made_in_no_time():
+    """Every call makes one.  One head of 32768 rows and another of two million take microseconds (sums over all blocks for every number of steps: 500 us and minutes);
+    a tenth of a millisecond leaves room for a busy machine."""
+    for n in (32768, 1 << 21):
+        best = math.inf
+        for _ in range(10):
+            start = time.perf_counter()
+            plan(1, 1, 128, n, n, 0, 3000, entropy=True)
+            best = min(best, time.perf_counter() - start)
+        assert best < 1e-4
 
 
 @pytest.mark.parametrize("case", TWO_BLOCKS)
