@@ -1129,7 +1129,7 @@ void launch_colsum(int ns1, bool wide, dim3 grid, hipStream_t st, const ScoreArg
     }
 }
 
-// One round of workgroups: unit by unit.  More: sequence by sequence, so that the heads at work fit the caches.
+// With an order of the units: unit by unit.  Without: sequence by sequence, so that the heads at work fit the caches.
 dim3 score_grid(const dream_attn_desc *desc, int units, const UnitOrder &order)
 {
     return order.n ? dim3(desc->n_q_heads, desc->batch, units) : dim3(desc->n_q_heads, units, desc->batch);

@@ -21,7 +21,7 @@ struct SplitMap {
 struct SplitUnit {
     int rank, split, n;     // block (by rank), its split, and how many splits it has
 };
-// The units of a launch whose workgroups all run at once, in the order of dispatch: 16 bits each, block * 64 + split * 8 + splits - 1.  See order_units().
+// The units of a launch of a few rounds of workgroups at most, in the order of dispatch: 16 bits each, block * 64 + split * 8 + splits - 1.  See order_units().
 constexpr int MAX_ORDERED = 128, MAX_ORDERED_BLOCKS = 1024;
 struct UnitOrder {
     uint32_t pair[MAX_ORDERED / 2];
@@ -112,12 +112,23 @@ inline int plan_splits(int blocks, int64_t heads, int resident, float whole, Blo
     return pow2;
 }
 
-// Order of dispatch of a launch that is one round of workgroups.  Workgroup i starts on CU i mod 256, `heads` workgroups to a unit, so units 256 / heads
-// apart share a CU until the end of the launch: the longest go first, and every further round gives its longest to the CU with the fewest steps so far.
-inline void order_units(int64_t heads, int units, int at_once, BlockSteps len, const SplitMap &map, UnitOrder *order)
+// Order of dispatch of a launch of a few rounds of workgroups at most.  Workgroup i starts on CU i mod 256, `heads` workgroups to a unit, so units 256 / heads
+// apart share a CU, all of them until the end of the launch where they are at work together: the longest go first, and every further round gives its longest to the CU with the fewest
+// steps so far.
+//
+// Up to how many workgroups (order_limit()).  Without an order one sequence goes longest block first, and each workgroup to the CU that is first free; several sequences go one after the other, and
+// the long blocks of the last one come when the CUs run empty.  At head_dim 64 and 128 four workgroups share a CU and an order pays up to 2048.  us, no order / order, by the number of workgroups:
+// one sequence, entropy: 960 22.8 / 21.5, 1120 27.5 / 25.2, 1152 36.7 / 35.8, 1328 63.5 / 60 and 82 / 83, 1664 90.7 / 87, 1712 126 / 126; column sums: 1216 34.5 / 34.8, 1408 36.6 / 35.7, 1888 67.2 / 65.2;
+// several, entropy: 640 10.4 / 9.1, 1024 21.0 / 14.3, 1200 58 / 49, 1568 75 / 60, 1792 31.9 / 27, 2048 19.5 / 17.5; column sums: 1024 23.6 / 20.3, 1408 52.8 / 38.5, 1536 23.5 / 19.5, 1920 65.6 / 67.2,
+// 2048 48.6 / 38.9.  At head_dim 256 two share a CU.  One sequence: an order that is not over after 512 takes the choice from CUs that would have made it better: 364 60.9 / 58.7, 384 29.6 / 28.5,
+// 512 30.1 / 29.6, 656 48.0 / 48.4, 752 102 / 102, 832 35 / 40, 896 (both passes) 49.4 / 54.0, 1024 82 / 90, 1856 241 / 260.  Several sequences: 640 28.7 / 24.4, 924 112 / 103, 996 129 / 120,
+// 1024 25.0 / 24.2, 1152 48.6 / 43.5, 1200 51.8 / 47.5, 1280 27.1 / 28.1 and 52.3 / 42.5, 2016 66 / 67, 2048 29.6 / 31.7 and 118 / 96: up to 1024.
+inline int order_limit(int head_dim, int batch) { return head_dim != 256 ? 2048 : batch == 1 ? 512 : 1024; }
+
+inline void order_units(int64_t heads, int units, int limit, BlockSteps len, const SplitMap &map, UnitOrder *order)
 {
     order->n = 0;
-    if (units > MAX_ORDERED || units < 2 || map.count[0] > MAX_ORDERED_BLOCKS || units * heads > at_once || units * heads <= 256)
+    if (units > MAX_ORDERED || units < 2 || map.count[0] > MAX_ORDERED_BLOCKS || units * heads > limit || units * heads <= 256)
         return;
     struct Unit { int steps; uint32_t code; } unit[MAX_ORDERED];
     int n = 0;
@@ -191,9 +202,8 @@ inline CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q,
         const BlockSteps len1 = {with_pos ? ceil_div(n_keys, STEP) : b1, !with_pos}, len2 = {with_pos ? rows : rows - vis_start / STEP, !with_pos};
         p.ns1 = plan_splits(b1, heads, resident, entropy ? 10.0f : 0.0f, len1, &p.map1, &p.units1);
         p.ns2 = plan_splits(b2, heads, resident, 0.0f, len2, &p.map2, &p.units2);
-        const int at_once = batch == 1 ? 2048 : 1024;
-        order_units(heads, p.units1, at_once, len1, p.map1, &p.order1);
-        order_units(heads, p.units2, at_once, len2, p.map2, &p.order2);
+        order_units(heads, p.units1, order_limit(head_dim, batch), len1, p.map1, &p.order1);
+        order_units(heads, p.units2, order_limit(head_dim, batch), len2, p.map2, &p.order2);
         if (direct) {
             const int64_t wgs1 = ceil_div(b1, 2) * heads, wgs2 = ceil_div(b2, 2) * heads;
             p.wide1 = take_double(head_dim == 256 ? wgs1 >= 1280 : head_dim == 128 && wgs1 >= 2300 && len1(0) >= 8, p.order1, &p.map1, &p.units1);

@@ -114,6 +114,16 @@ def test_a_plan_is_made_in_no_time():
         assert best < 1e-4
 
 
+@pytest.mark.parametrize("B,H,D,n_q,ordered", [(1, 32, 128, 1279, True), (1, 16, 64, 6627, True), (8, 32, 64, 269, True), (16, 2, 128, 3084, True), (1, 16, 256, 1389, True), (1, 32, 256, 1619, False),
+                                               (1, 16, 256, 4013, False), (1, 16, 256, 7417, False), (3, 4, 256, 5290, True), (8, 64, 256, 246, False), (1, 64, 128, 2100, False)])
+def test_launches_with_an_order(B, H, D, n_q, ordered):
+    """One sequence at head_dim 256 has an order of its workgroups only where all of them are at work together."""
+    p = plan(B, H, D, n_q, n_q, entropy=True)
+    assert (p["order1"] > 0) == ordered
+    if ordered:
+        assert 256 < p["units1"] * H * B <= (2048 if D != 256 else 512 if B == 1 else 1024)
+
+
 @pytest.mark.parametrize("case", TWO_BLOCKS)
 def test_sizes_of_the_gpu_test_take_workgroups_of_two_blocks(case):
     (B, Hq, _, D, P, v, vis_start), (sums, sums_own, entropies) = case
