@@ -31,12 +31,27 @@ struct ScoreArgs {
     float *ent_part;    // [ns1, B, Hq, n_q_pad]  expected score of the row under its attention weights, per split (entropy only)
     float *row_entropy, *block_sum;   // entropy of unsplit blocks: nullable [B, Hq, n_q], and [B, Hq, blocks, 2] sums of 32 rows each (else null: entropy_rows_kernel)
     int32_t ns1, ns2;   // most splits of the streamed axis a block has: keys in pass 1, query rows in pass 2
-    SplitMap map1, map2;
-    UnitOrder order1, order2;
     int64_t lse_split_stride;   // B * Hq * n_q_pad
     int64_t s_max;
     float scale, scale_log2;
+    SplitMap map;       // of the pass that is launched
+    UnitOrder order;    // (last: what every workgroup reads lies together)
 };
+
+// This workgroup's unit and sequence (score_grid() says which index is which).  All arguments that the first loads need are asked for at once: one after the other, each under a condition that
+// the one before decides, they were up to ten trips to memory, as the arguments of a launch are in no cache.  The arguments of one pass, 428 bytes, where those of
+// both were 720.  Calls, us, before / now: one sequence, column sums only, 4 heads of 128 x 1500 rows 16.0 / 15.4,
+// 8 of 256 x 1500 18.9 / 18.5; both passes, 32 of 128 x 704 22.3 / 21.3; entropy 32 of 128 x 1279 18.0 / 17.5.
+__device__ __forceinline__ SplitUnit own_unit(const ScoreArgs &a, int &b)
+{
+    SplitMap map = a.map;
+    int ordered = a.order.n;
+    uint32_t pair = a.order.pair[min(blockIdx.z >> 1, (unsigned)MAX_ORDERED / 2 - 1)];
+    asm volatile("" : "+s"(map.count[0]), "+s"(map.count[1]), "+s"(map.count[2]), "+s"(map.count[3]), "+s"(map.count[4]), "+s"(map.count[5]), "+s"(map.count[6]), "+s"(map.count[7]),
+                 "+s"(ordered), "+s"(pair) : "s"(a.q), "s"(a.k), "s"(a.q_pos), "s"(a.n_q), "s"(a.n_keys), "s"(a.n_q_heads), "s"(a.n_kv_heads), "s"(a.vis_start), "s"(a.vis_len), "s"(a.s_max));
+    b = ordered ? blockIdx.y : blockIdx.z;
+    return split_unit(map, ordered > 0, pair, ordered ? blockIdx.z : blockIdx.y);
+}
 
 // ---- what the two passes share: a stream of 64-row steps from memory straight into LDS ------------------------------------
 // Both passes hold one operand of q k^T in registers and stream the other.  Ablations of the first versions (rows through
@@ -155,10 +170,11 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
     const int c = lane & 31, g = lane >> 5;
     // x walks the heads with the KV head fastest: workgroup ids that share a KV head are congruent mod 8
     // (when there are 8 or more KV heads), so its K is fetched into one XCD's L2 only
-    const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
     // later row blocks see more keys: they come first
-    const SplitUnit unit = split_unit(a.map1, a.order1, a.order1.n ? blockIdx.z : blockIdx.y);
-    const int blk = a.map1.count[0] - 1 - unit.rank, b = a.order1.n ? blockIdx.y : blockIdx.z, split = unit.split;
+    int b;
+    const SplitUnit unit = own_unit(a, b);
+    const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
+    const int blk = a.map.count[0] - 1 - unit.rank, split = unit.split;
     // Blocks of 128 rows are counted from the last row up, so that with an odd number of 64s the half empty one is the shortest: the rows 0 to 63
     const int from_end = (a.n_q + BLOCK - 1) / BLOCK - 2 * (unit.rank + 1);
     const int row0 = SLOTS == 2 ? blk * BLOCK : max(from_end, 0) * BLOCK, row_end = SLOTS == 4 && from_end < 0 ? min(BLOCK, a.n_q) : a.n_q;
@@ -347,7 +363,7 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         for (int off = 16; off > 0; off >>= 1)
             H += __shfl_xor(H, off);
         if (c == 0)
-            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map1.count[0] + blk) * SLOTS + slot] = H;
+            a.block_sum[(((int64_t)b * a.n_q_heads + h) * a.map.count[0] + blk) * SLOTS + slot] = H;
         return;
     }
     if (valid) {
@@ -468,9 +484,10 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
     const int c = lane & 15, g = lane >> 4;
     const int vis_end = a.vis_start + a.vis_len;
     // x walks the heads with the KV head fastest (see pass 1): the query rows of a head stay in one XCD's L2
+    int b;
+    const SplitUnit unit = own_unit(a, b);        // earlier key blocks are seen by more rows: they come first
     const int kvh = blockIdx.x % a.n_kv_heads, h = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
-    const SplitUnit unit = split_unit(a.map2, a.order2, a.order2.n ? blockIdx.z : blockIdx.y);      // earlier key blocks are seen by more rows: they come first
-    const int blk0 = a.vis_start + unit.rank * (SLOTS * COLS), b = a.order2.n ? blockIdx.y : blockIdx.z, split = unit.split;
+    const int blk0 = a.vis_start + unit.rank * (SLOTS * COLS), split = unit.split;
     const int j0 = blk0 + slot * 16 * CT;                 // this wave's keys: j0 + q * 16 + c
     bool kvalid[CT];
 #pragma unroll
@@ -1229,7 +1246,7 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
         a.lse2 = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_lse);
         a.part = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.off_part);
         a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
-        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.map1 = p.map1; a.map2 = p.map2; a.order1 = p.order1; a.order2 = p.order2; a.ent_part = a.row_entropy = a.block_sum = nullptr; a.lse_in = row_lse_in;
+        a.ns1 = row_lse_in ? 1 : p.ns1; a.ns2 = p.ns2; a.map = p.map1; a.order = p.order1; a.ent_part = a.row_entropy = a.block_sum = nullptr; a.lse_in = row_lse_in;
         a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
         a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
         a.vis_start = vis_start; a.vis_len = vis_len; a.s_max = desc->s_max;
@@ -1246,6 +1263,8 @@ int dream_visual_compress(const dream_attn_desc *desc, const void *q, const int3
                 constexpr bool DIRECT = decltype(direct)::value;
                 if (!row_lse_in)
                     launch_lse<D, false, DIRECT>(p.wide1, g1, st, a);
+                a.map = p.map2;
+                a.order = p.order2;
                 launch_colsum<D, DIRECT>(a.ns1, p.wide2, g2, st, a);
             });
         } else {
@@ -1365,7 +1384,7 @@ int dream_attention_entropy(const dream_attn_desc *desc, const void *q, const in
     a.n_q = n_q; a.n_q_pad = p.n_q_pad; a.n_keys = n_keys;
     a.n_q_heads = desc->n_q_heads; a.n_kv_heads = desc->n_kv_heads;
     a.vis_start = 0; a.vis_len = 0; a.s_max = desc->s_max;
-    a.ns1 = p.ns1; a.ns2 = 1; a.map1 = p.map1; a.map2 = p.map2; a.order1 = p.order1; a.order2 = p.order2;
+    a.ns1 = p.ns1; a.ns2 = 1; a.map = p.map1; a.order = p.order1;
     a.lse_split_stride = (int64_t)desc->batch * desc->n_q_heads * p.n_q_pad;
     a.scale = desc->scale != 0.0f ? desc->scale : 1.0f / sqrtf((float)desc->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;

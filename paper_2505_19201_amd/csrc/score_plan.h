@@ -24,15 +24,13 @@ struct SplitUnit {
 // The units of a launch of a few rounds of workgroups at most, in the order of dispatch: 16 bits each, block * 64 + split * 8 + splits - 1.  See order_units().
 constexpr int MAX_ORDERED = 128, MAX_ORDERED_BLOCKS = 1024;
 struct UnitOrder {
-    uint32_t pair[MAX_ORDERED / 2];
     int32_t n;              // units, or 0: the order of the map
+    uint32_t pair[MAX_ORDERED / 2];
 };
-__attribute__((always_inline)) constexpr SplitUnit split_unit(const SplitMap &map, const UnitOrder &order, int u)
+// Unit u of a launch: by its pair of the order if that is an `ordered` one, else by the map
+__attribute__((always_inline)) constexpr SplitUnit split_unit(const SplitMap &map, bool ordered, uint32_t pair, int u)
 {
-    if (order.n) {
-        const uint32_t e = order.pair[u >> 1] >> (u & 1) * 16;
-        return {(int)(e >> 6 & (MAX_ORDERED_BLOCKS - 1)), (int)(e >> 3 & 7), (int)(e & 7) + 1};
-    }
+    const uint32_t e = pair >> (u & 1) * 16;
     SplitUnit r = {u, 0, 0};
 #pragma unroll
     for (int j = 0; j < MAX_SPLITS - 1; j++)
@@ -43,7 +41,7 @@ __attribute__((always_inline)) constexpr SplitUnit split_unit(const SplitMap &ma
 #pragma unroll
     for (int j = 0; j < MAX_SPLITS; j++)
         r.n += r.rank < map.count[j];
-    return r;
+    return {ordered ? (int)(e >> 6 & (MAX_ORDERED_BLOCKS - 1)) : r.rank, ordered ? (int)(e >> 3 & 7) : r.split, ordered ? (int)(e & 7) + 1 : r.n};
 }
 
 // Blocks are split while the launch would have fewer workgroups than this: two or three per CU.

@@ -14,7 +14,9 @@ extern "C" void score_plan(int batch, int heads, int head_dim, int n_q, int n_ke
 // (block by rank, split, splits of the block) of unit u of a pass of the last plan
 extern "C" void score_unit(int pass, int u, int *out)
 {
-    const SplitUnit r = pass == 1 ? split_unit(plan.map1, plan.order1, u) : split_unit(plan.map2, plan.order2, u);
+    const SplitMap &map = pass == 1 ? plan.map1 : plan.map2;
+    const UnitOrder &order = pass == 1 ? plan.order1 : plan.order2;
+    const SplitUnit r = split_unit(map, order.n > 0, order.n > 0 ? order.pair[u / 2] : 0, u);
     out[0] = r.rank;
     out[1] = r.split;
     out[2] = r.n;
