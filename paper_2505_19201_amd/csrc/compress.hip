@@ -38,19 +38,20 @@ struct ScoreArgs {
     UnitOrder order;    // (last: what every workgroup reads lies together)
 };
 
-// This workgroup's unit and sequence (score_grid() says which index is which).  All arguments that the first loads need are asked for at once: one after the other, each under a condition that
-// the one before decides, they were up to ten trips to memory, as the arguments of a launch are in no cache.  The arguments of one pass, 428 bytes, where those of
-// both were 720.  Calls, us, before / now: one sequence, column sums only, 4 heads of 128 x 1500 rows 16.0 / 15.4,
-// 8 of 256 x 1500 18.9 / 18.5; both passes, 32 of 128 x 704 22.3 / 21.3; entropy 32 of 128 x 1279 18.0 / 17.5.
+// This workgroup's unit and sequence (score_grid() says which index is which).  All arguments that the first loads need are asked for at once, the entry of an order behind them: one after the
+// other, each under a condition that the one before decides, they were up to ten trips to memory, as the arguments of a launch are in no cache.  The arguments of one pass, 428 bytes, where
+// those of both were 720.  Calls, us, before / now / with the entry asked for beside the others: column sums of one sequence, 4 heads of 128 x 1500 rows 15.6 / 15.4 / 15.5, 8 of 256 x 1500
+// 19.1 / 18.2 / 18.5, 32 of 128 x 1280 20.0 / 19.8 / 20.5; both passes, 32 of 128 x 1280 31.8 / 31.7 / 32.5, 4 sequences of 500 24.8 / 24.2 / 25.0; entropy, 32 of 64 x 1600 17.6 / 17.1 / 17.3.
 __device__ __forceinline__ SplitUnit own_unit(const ScoreArgs &a, int &b)
 {
     SplitMap map = a.map;
     int ordered = a.order.n;
-    uint32_t pair = a.order.pair[min(blockIdx.z >> 1, (unsigned)MAX_ORDERED / 2 - 1)];
-    asm volatile("" : "+s"(map.count[0]), "+s"(map.count[1]), "+s"(map.count[2]), "+s"(map.count[3]), "+s"(map.count[4]), "+s"(map.count[5]), "+s"(map.count[6]), "+s"(map.count[7]),
-                 "+s"(ordered), "+s"(pair) : "s"(a.q), "s"(a.k), "s"(a.q_pos), "s"(a.n_q), "s"(a.n_keys), "s"(a.n_q_heads), "s"(a.n_kv_heads), "s"(a.vis_start), "s"(a.vis_len), "s"(a.s_max));
+    asm volatile("" : "+s"(map.count[0]), "+s"(map.count[1]), "+s"(map.count[2]), "+s"(map.count[3]), "+s"(map.count[4]), "+s"(map.count[5]), "+s"(map.count[6]), "+s"(map.count[7]), "+s"(ordered)
+                 : "s"(a.q), "s"(a.k), "s"(a.q_pos), "s"(a.n_q), "s"(a.n_keys), "s"(a.n_q_heads), "s"(a.n_kv_heads), "s"(a.vis_start), "s"(a.vis_len), "s"(a.s_max));
     b = ordered ? blockIdx.y : blockIdx.z;
-    return split_unit(map, ordered > 0, pair, ordered ? blockIdx.z : blockIdx.y);
+    if (ordered)
+        return split_unit(map, true, a.order.pair[blockIdx.z >> 1], blockIdx.z);
+    return split_unit(map, false, 0, blockIdx.y);
 }
 
 // ---- what the two passes share: a stream of 64-row steps from memory straight into LDS ------------------------------------
