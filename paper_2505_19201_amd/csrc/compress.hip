@@ -246,14 +246,28 @@ __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
         // tile t: keys key0 + t * 32 .. + 31
         auto products = [&](int t, f32x16 &acc) {
             acc = f32x16{};
-            bf16x8 kf[NKS];                                      // requested together: the waits then fall behind the first products
+            // Requested together: the waits then fall behind the first products.  At head_dim 256 four at a time, the next four before the products of the last: 16 at once hold the first product up
+            // for longer than the two waves of a SIMD have work for.  Entropy, us, 16 / four at a time (four tiles of 16x16 before: the third): 16 heads x 7417 rows 255 / 240 / 235, 8 x 6003 101.5 / 95.7 / 96.8,
+            // 28 x 4 x 2013 162 / 153 / 171.
+            constexpr int AT_ONCE = D == 256 ? 4 : NKS, GROUPS = NKS / AT_ONCE;
+            bf16x8 kf[2][AT_ONCE];
+            auto request = [&](int n) {
 #pragma unroll
-            for (int ks = 0; ks < NKS; ks++)
-                kf[ks] = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[ks]);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < AT_ONCE; i++)
+                    kf[n & 1][i] = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[n * AT_ONCE + i]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            request(0);
 #pragma unroll
-            for (int ks = 0; ks < NKS; ks++)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], acc, 0, 0, 0);
+            for (int n = 0; n < GROUPS; n++) {
+                if (n + 1 < GROUPS)
+                    request(n + 1);
+#pragma unroll
+                for (int i = 0; i < AT_ONCE; i++)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[n & 1][i], qf[n * AT_ONCE + i], acc, 0, 0, 0);
+                if (n + 1 < GROUPS)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
         };
         // The row's reference m is raised only when a score exceeds it by 8 octaves: powers of two stay below 2^8, and the sums are
         // rescaled a few times per row instead of in every step.  mult: what still multiplies the scores; masked: some are -inf, the mark of a
