@@ -138,6 +138,8 @@ constexpr int MAX_SEG = 64, MAX_VAL = 4;
 constexpr int SLOTS = 2 * MAX_VAL * MAX_SEG;
 // Units of 64 cycles from publishing to the first poll.  A word takes about 900 cycles to get to the others, and a poll that comes too early holds up the one that would find it.
 // spec_walk_small_kernel, 4 sequences x 60 nodes x 131072 float32 logits: first poll at once 36.6 us, after 320 cycles 33.5, 770 30.7, 1020 30.4, 1280 31.1, 1660 32.4.
+// spec_walk_kernel, at once / after 900 cycles, by the workgroups of a sequence: 2 73.6 / 75.9, 3 87.1 / 89.9, 4 98.4 / 100.2, 8 88.3 / 88.7 and 46.7 / 47.0, 12 51.2 / 51.2, 13 58.8 / 58.6, 16 54.9 / 54.0,
+// 19 59.5 / 57.9, 32 53.5 / 47.7, 64 48.3 / 40.7: from 16 on.
 constexpr int POLL_DELAY = 14;
 
 // (max, sum of exp(x/temp - max)) of one chunk of one row of the first n_nodes nodes of a sequence.  z = 0: target rows;
@@ -573,7 +575,8 @@ __device__ __forceinline__ void walk(const WalkArgs &a)
                 break;
             bool missing = false;
             const int val = tid / MAX_SEG, seg = tid % MAX_SEG;
-            __builtin_amdgcn_s_sleep(POLL_DELAY);
+            if (n_wg >= 16)              // fewer workgroups do not hold each other up
+                __builtin_amdgcn_s_sleep(POLL_DELAY);
             if (val < n_val && seg < n_seg && seg % n_wg != wg) {
                 uint64_t w = 0;
                 missing = true;
