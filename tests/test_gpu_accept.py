@@ -63,7 +63,8 @@ def _argmax(x):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("T,vocab,depth", [(1, 9, 3), (2, 8, 0), (63, 4096, 5), (64, 16392, 2), (64, 8200, 70), (65, 8200, 70), (64, 50003, 4), (65, 16384, 2), (600, 40, 9)])
+@pytest.mark.parametrize("T,vocab,depth", [(1, 9, 3), (2, 8, 0), (63, 4096, 5), (64, 16392, 2), (64, 8200, 70), (65, 8200, 70), (64, 50003, 4), (65, 16384, 2), (600, 40, 9),
+                                           (7, 1024, 3), (7, 1031, 3), (7, 2048, 3), (7, 2063, 3), (7, 4097, 3), (7, 4111, 3)])      # (around one piece a thread, and half of them)
 def test_masked_logits_and_both_walks(gu, dtype, T, vocab, depth):
     """Trees on both sides of 64 nodes, chains deeper than a wave, depth limits; logits of which most are -inf, some NaN (quiet and signalling), zeros of both signs, and ties in the
     same 16 bytes, the same thread and others; rows on and off the 16-byte boundaries, chunks without and with a tail."""
