@@ -66,7 +66,8 @@ def test_full_size_configs(gu, name):
 
 # whole blocks and split ones, in the order of the blocks or dealt to the CUs, with heads that divide 256 and others, one sequence and several
 @pytest.mark.parametrize("B,Hq,Hkv,D,n,with_pos", [(2, 16, 16, 64, 700, False), (2, 8, 2, 64, 1279, False), (3, 7, 7, 64, 900, False), (1, 16, 4, 128, 1025, False),
-                                                   (2, 8, 8, 64, 1000, True), (5, 1, 1, 64, 1600, False), (1, 32, 8, 64, 1601, False)])
+                                                   (2, 8, 8, 64, 1000, True), (5, 1, 1, 64, 1600, False), (1, 32, 8, 64, 1601, False),
+                                                   (2, 40, 8, 64, 1700, False)])      # (the last: more sums than the mean asks for at once)
 def test_blocks_whole_and_split(gu, B, Hq, Hkv, D, n, with_pos):
     cfg = di.Config("e", "bf16", B, Hq, Hkv, D, Hq * D, n, 0, 4, 2, 1, 2, 100, 1, 38)
     pos = np.stack([np.random.default_rng(39 + b).permutation(n) for b in range(B)]).astype(np.int32) if with_pos else None
