@@ -57,7 +57,6 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits,
     const int end = min(begin + CHUNK_ELEMS, vocab);
     const char *p = reinterpret_cast<const char *>(logits) + (row * vocab + begin) * (BF16 ? 2 : 4);
     // whole pieces in 16-byte loads, which global memory serves from any address of a logit, the tail one by one
-    typedef unsigned int piece __attribute__((ext_vector_type(4), aligned(2)));
     const int n_vec = (end - begin) / PER;
     float best = -INFINITY, m;
     int best_i = 0x7fffffff, index;
@@ -72,7 +71,7 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const void *logits,
         if (n_vec > 0) {
 #pragma unroll
             for (int j = 0; j < N; j++) {
-                const piece *from = reinterpret_cast<const piece *>(p) + at(j);
+                const u32x4_any *from = reinterpret_cast<const u32x4_any *>(p) + at(j);
                 w[j] = BF16 ? __builtin_nontemporal_load(from) : *from;       // bf16 logits: read once
             }
             __builtin_amdgcn_sched_barrier(0);

@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * NW, (QG == 1 && D <= 128) ? (NW == 4 ? DREAM_Q
             RowOwner ro2 = row_owner(a, kvh, qg, wave, QG, qt, r2, QW);
             if (ro2.row >= 0) {
                 uint16_t *op = reinterpret_cast<uint16_t *>(a.out) + (((int64_t)b * a.n_q + ro2.row) * a.n_q_heads + ro2.head) * D + col;
-                __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(ot + r2 * OSTR + col), reinterpret_cast<u32x4 *>(op));
+                __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(ot + r2 * OSTR + col), reinterpret_cast<u32x4_any *>(op));
             }
         }
         wave_lds_fence();
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 #pragma unroll
         for (int r = 0; r < 4; r++)
             ob[r] = (__bf16)(o[d][r] * inv);
-        *reinterpret_cast<bf16x4 *>(op + (w + 4 * d) * 16) = ob;
+        *reinterpret_cast<u32x2_any *>(op + (w + 4 * d) * 16) = __builtin_bit_cast(u32x2_any, ob);
     }
     if (a.lse && g == 0 && w == 0)
         a.lse[((int64_t)b * a.n_q_heads + ro.head) * a.n_q + ro.row] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
@@ -1242,12 +1242,12 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             const auto x = __builtin_amdgcn_permlane16_swap(ob[u].x, ob[u + 1].x, false, false), y = __builtin_amdgcn_permlane16_swap(ob[u].y, ob[u + 1].y, false, false);
             const u32x4 w = {x[0], y[0], x[1], y[1]};
             if (f < n_rows)
-                __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(op + (u + (g & 1)) * 16 + (g >> 1) * 8));
+                __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any *>(op + (u + (g & 1)) * 16 + (g >> 1) * 8));
         }
     } else if (f < n_rows) {
 #pragma unroll
         for (int u = 0; u < UPW; u++)
-            *reinterpret_cast<uint2 *>(op + u * 16 + g * 4) = ob[u];
+            *reinterpret_cast<u32x2_any *>(op + u * 16 + g * 4) = __builtin_bit_cast(u32x2_any, ob[u]);
     }
     if (f >= n_rows)
         return;

@@ -38,6 +38,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// the same from and to any address of a 16-bit value in global memory
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

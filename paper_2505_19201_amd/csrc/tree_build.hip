@@ -94,7 +94,6 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
     // the end is another's and turned into -inf.
     float x[PER_THREAD];
     constexpr int ESZ = BF16 ? 2 : 4, W = BF16 ? 1 : 2;   // bytes of a logit, 16-byte pieces of a group
-    typedef unsigned int piece __attribute__((ext_vector_type(4), aligned(2)));
     const char *p = reinterpret_cast<const char *>(logits) + (row * vocab + begin) * ESZ;
     const int n_here = min(CHUNK, vocab - begin), n_groups = n_here / 8;
     auto one = [&](int t) { return BF16 ? bf16_bits_to_float(reinterpret_cast<const uint16_t *>(p)[t]) : reinterpret_cast<const float *>(p)[t]; };
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
         for (int j = 0; j < PER_THREAD / 8; j++)
 #pragma unroll
             for (int i = 0; i < W; i++) {
-                const piece *from = reinterpret_cast<const piece *>(p) + min(j * 256 + tid, n_groups - 1) * W + i;
+                const u32x4_any *from = reinterpret_cast<const u32x4_any *>(p) + min(j * 256 + tid, n_groups - 1) * W + i;
                 w[j][i] = BF16 ? __builtin_nontemporal_load(from) : *from;     // bf16 logits: read once
             }
         __builtin_amdgcn_sched_barrier(0);

@@ -393,14 +393,15 @@ def test_rows_leave_the_same_wherever_the_output_starts(gu, B, Hq, Hkv, D, T, ke
     base, _ = gu.run_verify(x)
     dev = gu.DeviceAttn(x)
     n = base.size
-    flat = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
-    out = flat[2:2 + n].view(base.shape)
-    assert out.data_ptr() % 16 == 4
     desc = dream.attn_desc(B, Hq, Hkv, D, dream.BF16, dev.k.shape[2])
     ws = dream.alloc_workspace(dream.dream_tree_verify_attn_workspace(desc, T, dev.max_kv))
-    dream.dream_tree_verify_attn(desc, dev.q, dev.k, dev.v, dev.prefix_len, T, dev.parent, None, dev.max_kv, out, None, ws)
-    assert np.array_equal(out.float().cpu().numpy(), base.astype(np.float32))
-    assert (flat[:2] == 7.0).all() and (flat[2 + n:] == 7.0).all()
+    for off in (2, 1):
+        flat = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+        out = flat[off:off + n].view(base.shape)
+        assert out.data_ptr() % 16 == 2 * off
+        dream.dream_tree_verify_attn(desc, dev.q, dev.k, dev.v, dev.prefix_len, T, dev.parent, None, dev.max_kv, out, None, ws)
+        assert np.array_equal(out.float().cpu().numpy(), base.astype(np.float32))
+        assert (flat[:off] == 7.0).all() and (flat[off + n:] == 7.0).all()
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,line", [(1, 32, 32, 128, 90), (2, 16, 8, 128, 100), (1, 32, 32, 64, 112), (2, 16, 8, 256, 72), (3, 24, 8, 128, 152), (3, 16, 16, 64, 112),
