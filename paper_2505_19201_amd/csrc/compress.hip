@@ -495,6 +495,10 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 {
     using G = StreamGeom<D>;
     constexpr int NKS = D / 32, WINDOW = 512, CT = COLS / 16, HALVES = 4 / SLOTS, TILES = 2 / HALVES;   // TILES: halves of a step that a wave takes
+    // At head_dim 256 a SIMD has two waves, which do not cover what the compiler leaves to be waited for: there the log-sum-exps are read before the products and the fragments ahead of theirs.
+    // Column sums, us, as at the other head_dims / so: 16 heads x 7000 rows 124 / 121.5, 32 x 4024 123 / 118, 9 sequences of 8 x 2584 127 / 123.5, 8 of 16 x 1280 76.4 / 73.6, one of 8 x 1500 18.8 / 17.7.
+    // At head_dim 128 it is the other way: 16 of 32 x 1279 131 / 133.
+    constexpr bool FEW_WAVES = D == 256;
     static_assert(SLOTS == 2 || SLOTS == 4, "two key slots by two halves, or four key slots");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[G::NS * G::STAGE];
     __shared__ __attribute__((aligned(16))) float lds_lse[WINDOW];
@@ -615,39 +619,77 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
 #pragma unroll
             for (int q = 0; q < CT; q++)
                 acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (FEW_WAVES) {
+                // two key steps at a time, the next two requested before the products of the last: see FEW_WAVES
+                constexpr int AT_ONCE = 2, GROUPS = NKS / AT_ONCE;
+                bf16x8 f[2][AT_ONCE][2];
+                auto request = [&](int n) {
 #pragma unroll
-            for (int ks = 0; ks < NKS; ks++) {
-                const bf16x8 q0 = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[ks]);
-                const bf16x8 q1 = *reinterpret_cast<const bf16x8 *>(st + (t * 32 + 16) * G::ROW + frag[ks]);
+                    for (int i = 0; i < AT_ONCE; i++)
 #pragma unroll
-                for (int q = 0; q < CT; q++) {
-                    acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kf[q][ks], acc[q][0], 0, 0, 0);
-                    acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kf[q][ks], acc[q][1], 0, 0, 0);
+                        for (int r = 0; r < 2; r++)
+                            f[n & 1][i][r] = *reinterpret_cast<const bf16x8 *>(st + (t * 32 + r * 16) * G::ROW + frag[n * AT_ONCE + i]);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                request(0);
+#pragma unroll
+                for (int n = 0; n < GROUPS; n++) {
+                    if (n + 1 < GROUPS)
+                        request(n + 1);
+#pragma unroll
+                    for (int i = 0; i < AT_ONCE; i++)
+#pragma unroll
+                        for (int q = 0; q < CT; q++)
+#pragma unroll
+                            for (int r = 0; r < 2; r++)
+                                acc[q][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n & 1][i][r], kf[q][n * AT_ONCE + i], acc[q][r], 0, 0, 0);
+                    if (n + 1 < GROUPS)
+                        __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ks++) {
+                    const bf16x8 q0 = *reinterpret_cast<const bf16x8 *>(st + t * 32 * G::ROW + frag[ks]);
+                    const bf16x8 q1 = *reinterpret_cast<const bf16x8 *>(st + (t * 32 + 16) * G::ROW + frag[ks]);
+#pragma unroll
+                    for (int q = 0; q < CT; q++) {
+                        acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kf[q][ks], acc[q][0], 0, 0, 0);
+                        acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kf[q][ks], acc[q][1], 0, 0, 0);
+                    }
                 }
             }
         };
+        // the log-sum-exps of the lane's rows of a tile
+        auto row_lse = [&](int t, f32x4 (&L)[2]) {
+            L[0] = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + g * 4]);
+            L[1] = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + 16 + g * 4]);
+        };
         // every row of the tile sits at or after every key of this wave: nothing to mask
-        auto add_open = [&](int t, const f32x4 (&acc)[CT][2]) {
-            const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + g * 4]);
-            const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + 16 + g * 4]);
+        auto add_open = [&](int t, const f32x4 (&acc)[CT][2], const f32x4 (&L)[2]) {
 #pragma unroll
             for (int q = 0; q < CT; q++)
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][0][r], a.scale_log2, -L0[r]));
-                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L1[r]));
+                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][0][r], a.scale_log2, -L[0][r]));
+                    cs[t][q] += __builtin_amdgcn_exp2f(fmaf(acc[q][1][r], a.scale_log2, -L[1][r]));
                 }
         };
         if (none)
             continue;
         if (TILES == 2 && !a.q_pos && r0 >= j0 + 16 * CT - 1) {
-            f32x4 acc[TILES][CT][2];
+            f32x4 acc[TILES][CT][2], L[TILES][2];
 #pragma unroll
-            for (int t = 0; t < TILES; t++)
+            for (int t = 0; t < TILES; t++) {
+                if (FEW_WAVES)
+                    row_lse(t, L[t]);
                 products(t, acc[t]);
+            }
 #pragma unroll
-            for (int t = 0; t < TILES; t++)
-                add_open(t, acc[t]);
+            for (int t = 0; t < TILES; t++) {
+                if (!FEW_WAVES)
+                    row_lse(t, L[t]);
+                add_open(t, acc[t], L[t]);
+            }
             continue;
         }
 #pragma unroll
@@ -655,14 +697,16 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
             const int rt = r0 + t * 32;
             if (!a.q_pos && rt + 31 < j0)
                 continue;   // causal: these rows sit before this wave's keys
-            f32x4 acc[CT][2];
+            f32x4 acc[CT][2], L[2];
+            if (FEW_WAVES)
+                row_lse(t, L);
             products(t, acc);
+            if (!FEW_WAVES)
+                row_lse(t, L);
             if (!a.q_pos && rt >= j0 + 16 * CT - 1) {
-                add_open(t, acc);
+                add_open(t, acc, L);
                 continue;
             }
-            const f32x4 L0 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + g * 4]);
-            const f32x4 L1 = *reinterpret_cast<const f32x4 *>(&lds_lse[w0 + t * 32 + 16 + g * 4]);
             i32x4 at0 = {0, 1, 2, 3}, at1 = {16, 17, 18, 19};      // positions, or without them the rows from the lane's first one on
             if (a.q_pos) {
                 at0 = *reinterpret_cast<const i32x4 *>(&lds_pos[w0 + t * 32 + g * 4]);
@@ -674,8 +718,8 @@ __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)
                 const int key = j0 + q * 16 + c - (a.q_pos ? 0 : rt + g * 4);
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                    const float p0 = __builtin_amdgcn_exp2f(acc[q][0][r] * a.scale_log2 - L0[r]);
-                    const float p1 = __builtin_amdgcn_exp2f(acc[q][1][r] * a.scale_log2 - L1[r]);
+                    const float p0 = __builtin_amdgcn_exp2f(acc[q][0][r] * a.scale_log2 - L[0][r]);
+                    const float p1 = __builtin_amdgcn_exp2f(acc[q][1][r] * a.scale_log2 - L[1][r]);
                     cs[t][q] += key <= at0[r] ? p0 : 0.0f;
                     cs[t][q] += key <= at1[r] ? p1 : 0.0f;
                 }
