@@ -52,6 +52,12 @@ struct BlockSteps {
     int first;
     bool falls;
     int operator()(int rank) const { return falls ? std::max(first - rank, 0) : first; }
+    // all steps of `blocks` blocks
+    int64_t total(int blocks) const
+    {
+        const int64_t n = falls ? std::max(std::min(blocks, first), 0) : blocks;
+        return n * first - (falls ? n * (n - 1) / 2 : 0);
+    }
     // of `blocks` blocks, those with more than n steps
     int longer_than(int n, int blocks) const { return falls ? std::min(std::max(first - n, 0), blocks) : first > n ? blocks : 0; }
     // workgroups of at most S steps that `blocks` blocks make
@@ -164,6 +170,8 @@ inline void order_units(int64_t heads, int units, int limit, BlockSteps len, con
 // loads and first steps per score.  It pays where workgroups that are half as many still come to several rounds.  us, one block / two, by their number (of two), all launches:
 // column sums, head_dim 64: 1440 57.6 / 58.5, 1728 63.7 / 63.3, 2016 72.1 / 73.3, 2304 79.0 / 78.8, 3072 45.0 / 43.2, 4608 137.8 / 132.8; 128: 1024 52.2 / 56.0,
 // 1280 43.6 / 44.0 and 68.9 / 65.9, 1440 98.5 / 90.7, 1920 57.1 / 55.9, 4096 160.8 / 144.3; 256: 640 131.8 / 122.0, 1024 138.2 / 116.4, 2048 296 / 263 (fewer are dealt to the CUs).
+// Sums at head_dim 256 from 600 on and only where a CU's share of the steps is at least 2.1 times the longest block: below that the end of the launch, when the last of these workgroups run alone, costs more than
+// they save.  By that ratio: 1.55 61.7 / 66.8, 1.8 59.0 / 61.0, 1.9 80.9 / 81.8, 2.07 64.7 / 69.0, 2.1 30.2 / 29.6, 2.2 39.7 / 36.0, 2.4 67.0 / 65.5, 2.5 72.1 / 63.8, 2.6 42.9 / 40.0, 3.1 109 / 92, 3.0 201 / 205, 3.4 51.5 / 49.6.
 // Log-sum-exps (entropy), 128: 1152 29.6 / 33.1 and 74.0 / 63.6, 1536 62.6 / 64.8, 1760 68.1 / 68.4, 1920 44.3 / 45.8, 2304 74.8 / 72.3, 3072 65.9 / 64.3 but with 5 steps 39.7 / 40.7,
 // 5120 160 / 148; 256: 832 60.3 / 63.7, 1024 51.7 / 52.1, 1280 60.4 / 60.1 and 52.2 / 47.6, 1824 177 / 160, 2560 152 / 134; 64: 3328 91.6 / 93.4, 4096 39.8 / 44.6, 6656 169.8 / 165.4: one block.
 inline bool take_double(bool want, const UnitOrder &order, SplitMap *map, int *units)
@@ -205,7 +213,8 @@ inline CompressPlan compress_plan(int batch, int n_heads, int head_dim, int n_q,
         if (direct) {
             const int64_t wgs1 = ceil_div(b1, 2) * heads, wgs2 = ceil_div(b2, 2) * heads;
             p.wide1 = take_double(head_dim == 256 ? wgs1 >= 1280 : head_dim == 128 && wgs1 >= 2300 && len1(0) >= 8, p.order1, &p.map1, &p.units1);
-            p.wide2 = take_double((p.ns1 == 1 || lse_given) && wgs2 >= (head_dim == 64 ? 2048 : head_dim == 128 ? 1400 : 600), p.order2, &p.map2, &p.units2);
+            const bool many2 = head_dim == 64 ? wgs2 >= 2048 : head_dim == 128 ? wgs2 >= 1400 : wgs2 >= 600 && 10 * heads * len2.total(b2) >= 21 * 512 * (int64_t)len2(0);
+            p.wide2 = take_double((p.ns1 == 1 || lse_given) && many2, p.order2, &p.map2, &p.units2);
         }
     }
     p.off_lse = DREAM_WORKSPACE_MIN_BYTES;

@@ -124,6 +124,14 @@ def test_launches_with_an_order(B, H, D, n_q, ordered):
         assert 256 < p["units1"] * H * B <= (2048 if D != 256 else 512 if B == 1 else 1024)
 
 
+@pytest.mark.parametrize("B,H,n_q,v,two", [(27, 16, 1280, 256, 1), (20, 16, 382, 327, 1), (12, 32, 376, 325, 1), (15, 8, 1033, 909, 0), (20, 4, 1211, 1140, 0), (13, 16, 1083, 305, 0), (9, 8, 1638, 1605, 0)])
+def test_two_blocks_of_keys_at_head_dim_256(B, H, n_q, v, two):
+    """Only where a CU's share of the steps is a good two times the longest block."""
+    steps = lengths(2, n_q, n_q, 0, v, False)
+    assert (10 * B * H * sum(steps) >= 21 * 512 * steps[0]) == two
+    assert plan(B, H, 256, n_q, n_q, 0, v, lse_given=True)["wide2"] == two
+
+
 @pytest.mark.parametrize("case", TWO_BLOCKS)
 def test_sizes_of_the_gpu_test_take_workgroups_of_two_blocks(case):
     (B, Hq, _, D, P, v, vis_start), (sums, sums_own, entropies) = case
