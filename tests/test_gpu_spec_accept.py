@@ -347,15 +347,17 @@ def test_whoever_sums_a_segment_the_result_is_the_same(gu, V, dtype):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("B,T,V,dtype", [
-    (3, 64, 4096, "f32"), (3, 65, 4097, "f32"),          # the largest tree of spec_walk_small_kernel and the next; one segment of one chunk, two with one token in the last
-    (2, 1, 9000, "bf16"), (2, 2, 8200, "f32"),           # no test at all; one
-    (4, 64, 40000, "f32"), (4, 65, 40000, "f32"), (4, 64, 40003, "bf16"), (20, 30, 70000, "bf16"),   # statistics formed by the walk; rows off the 16-byte boundaries; 8192 tokens a workgroup
-    (64, 40, 16384, "f32"), (65, 40, 16384, "f32")])     # 256 workgroups; a fifth too many: spec_walk_kernel
+@pytest.mark.parametrize("B,T,V,dtype,small", [
+    (3, 64, 4096, "f32", True), (3, 65, 4097, "f32", False),    # the largest tree of spec_walk_small_kernel and the next; one segment of one chunk, two with one token in the last
+    (2, 1, 9000, "bf16", True), (2, 2, 8200, "f32", True),      # no test at all; one
+    (4, 64, 40000, "f32", True), (4, 65, 40000, "f32", False), (4, 64, 40003, "bf16", True), (20, 30, 70000, "bf16", True),   # statistics formed by the walk; rows off the 16-byte boundaries; 8192 tokens a workgroup
+    (64, 40, 16384, "f32", True), (65, 40, 16384, "f32", True),        # 256 workgroups of 4096 tokens; 130 of 8192
+    (80, 12, 25000, "bf16", False), (130, 9, 8200, "f32", False)])     # more chunks of 8192 tokens than workgroups of a sequence: two workgroups, and one
 @pytest.mark.parametrize("limit", [5, 2, 0])
-def test_both_walks_give_the_same(gu, B, T, V, dtype, limit):
+def test_both_walks_give_the_same(gu, B, T, V, dtype, small, limit):
     """Trees, rows and batches on both sides of the lines between the two walks, close calls included: the same whether the workgroups exchange their sums or (polls < 0) workgroup 0
     forms them all, which is spec_walk_kernel's way; down to a depth limit of 0, where a root with children is drawn from."""
+    assert _small(B, T, V) == small
     import paper_2505_19201_amd as dream
     g = di.rng(5990 + V + T, 700)
     parent = np.stack([di.random_tree(T, 5, 5991, b) for b in range(B)]) if T > 1 else np.full((B, 1), -1, dtype=np.int32)
