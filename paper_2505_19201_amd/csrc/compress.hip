@@ -2,10 +2,9 @@
 //
 // The importance of key token j is the attention weight it receives, summed over the rows and
 // heads of the last-layer causal attention matrix.  The probabilities need each row's softmax
-// normaliser first, so stage A runs two passes over q k^T (both on v_mfma_f32_16x16x32_bf16, no
-// attention matrix is ever stored):
-//   scores_lse_*     one workgroup per 64 query rows, K streamed through LDS: log-sum-exp of every causal row;
-//   scores_colsum_*  one workgroup per 64 visual keys, query rows streamed through LDS: sum over rows of
+// normaliser first, so stage A runs two passes over q k^T on the matrix cores, no attention matrix is ever stored:
+//   scores_lse_*     one workgroup per 64 or 128 query rows, K streamed through LDS, tiles of 32x32: log-sum-exp of every causal row;
+//   scores_colsum_*  one workgroup per 64 or 128 visual keys, query rows streamed through LDS, tiles of 16x16: sum over rows of
 //                    exp(score - lse), per head.
 // Every (sequence, head, row split, key) partial sum has one fixed order of additions, and the selection kernel adds
 // heads and splits in a fixed order (in a launch of its own where they are many), so scores are reproducible bit for bit.  Stage B finds the
@@ -155,8 +154,9 @@ __device__ __forceinline__ float entropy_of(float lse, float expected)
 // The held rows as whole lines instead of 16-byte pieces of 16 rows per load: 57.8 -> 49.6 us at 32 LLaVA sequences of 320 tokens.
 // The reference raised by octaves and a step's fragments requested together: 22.7 -> 21.7 us and 188 -> 185 us for larger prompts, all launches.
 // What bounds it there is the issue of instructions.  Where workgroups are many (take_double()) they hold 128 rows: four row slots, and a wave takes both halves of a step.
-// One tile of 32x32 in the place of four of 16x16 is half the MFMAs for the same products, one
-// reference and one pair of sums per lane: 16 SmolVLM sequences 193 -> 171 us, 8 of Gemma3 with 900 rows 58.5 -> 54.0, one LLaVA prompt 13.4 -> 12.7.
+// One tile of 32x32 in the place of four of 16x16 is half the MFMAs for the same products, one reference and one pair of sums per lane.  Entropy, all launches, with four tiles, blocks of 64 rows in
+// their own order and a launch that forms the entropies / now: 16 SmolVLM sequences 175.7 / 166.2, 16 of 32 x 1200 rows at head_dim 128 149.5 / 134.7, one LLaVA prompt 14.4 / 11.2; the pass alone at
+// one Pixtral prompt 18.0 / 17.0: there it is the launch that counts.
 template <int D, bool ENT, bool DIRECT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void scores_lse_bf16_kernel(ScoreArgs a)
 {
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(256) void entropy_mean_kernel(const float *block_su
 // 197 -> 151 us.  What bounds it there is the issue of vector instructions: the counters of that launch (123 us alone) show the vector ALU
 // busy 69 % of the time, the matrix cores 25 %, LDS 21 % without a bank conflict, 4.9 waves per SIMD.  Tiles of 32x32, which pass 1 takes, need more
 // registers or more LDS reads here and were 3-6 % slower.  Where workgroups are many (take_double()) they hold 128 keys in four key slots, and a wave takes both halves of a
-// step: 16 Pixtral sequences of 1279 tokens 160.8 -> 144.3, 32 Gemma3 of 2000 296 -> 263, 16 SmolVLM of 1600 137.8 -> 132.8 us, the same bits.  (8 waves that hold 128 keys, halves
+// step: 16 Pixtral sequences of 1279 tokens 148.7 -> 129.7, 32 Gemma3 of 2000 272 -> 243, 16 SmolVLM of 1600 128.4 -> 125.6 us, the same bits.  (8 waves that hold 128 keys, halves
 // apart: 3 % at most.)
 template <int D, int NS1, bool DIRECT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void scores_colsum_bf16_kernel(ScoreArgs a)

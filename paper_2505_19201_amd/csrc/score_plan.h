@@ -168,8 +168,8 @@ inline void order_units(int64_t heads, int units, int limit, BlockSteps len, con
 
 // Workgroups of two blocks (SLOTS = 4) in the place of one, where the blocks are whole and in the order of the map.  A wave then takes whole steps: half the barriers,
 // loads and first steps per score.  It pays where workgroups that are half as many still come to several rounds.  us, one block / two, by their number (of two), all launches:
-// column sums, head_dim 64: 1440 57.6 / 58.5, 1728 63.7 / 63.3, 2016 72.1 / 73.3, 2304 79.0 / 78.8, 3072 45.0 / 43.2, 4608 137.8 / 132.8; 128: 1024 52.2 / 56.0,
-// 1280 43.6 / 44.0 and 68.9 / 65.9, 1440 98.5 / 90.7, 1920 57.1 / 55.9, 4096 160.8 / 144.3; 256: 640 131.8 / 122.0, 1024 138.2 / 116.4, 2048 296 / 263 (fewer are dealt to the CUs).
+// column sums, head_dim 64: 1440 57.6 / 58.5, 1728 63.7 / 63.3, 2016 72.1 / 73.3, 2304 79.0 / 78.8, 3072 45.0 / 43.2, 4608 128.4 / 125.6; 128: 1024 52.2 / 56.0,
+// 1280 43.6 / 44.0 and 68.9 / 65.9, 1440 98.5 / 90.7, 1920 57.1 / 55.9, 4096 148.7 / 129.7; 256: 640 131.8 / 122.0, 1024 138.2 / 116.4, 2048 272 / 243 (fewer are dealt to the CUs).
 // Sums at head_dim 256 from 600 on and only where a CU's share of the steps is at least 2.1 times the longest block: below that the end of the launch, when the last of these workgroups run alone, costs more than
 // they save.  By that ratio: 1.55 61.7 / 66.8, 1.8 59.0 / 61.0, 1.9 80.9 / 81.8, 2.07 64.7 / 69.0, 2.1 30.2 / 29.6, 2.2 39.7 / 36.0, 2.4 67.0 / 65.5, 2.5 72.1 / 63.8, 2.6 42.9 / 40.0, 3.1 109 / 92, 3.0 201 / 205, 3.4 51.5 / 49.6.
 // Log-sum-exps (entropy), 128: 1152 29.6 / 33.1 and 74.0 / 63.6, 1536 62.6 / 64.8, 1760 68.1 / 68.4, 1920 44.3 / 45.8, 2304 74.8 / 72.3, 3072 65.9 / 64.3 but with 5 steps 39.7 / 40.7,

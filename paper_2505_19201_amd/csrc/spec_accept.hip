@@ -22,9 +22,8 @@
 // beforehand, one per node.  spec_walk_small_kernel is the walk with that chain cut short; spec_walk_kernel serves what it does not take.
 //
 // Why several workgroups: one CU pulls 60 to 75 GB/s, 14 us and more for one pass over two float32 rows of 131072 tokens.
-// Measured, us per call, one read of all rows with children and a walk in chunks of 8192 tokens / chunks as now, spec_walk_kernel / spec_walk_small_kernel (the first two the same
-// tensors every call, the last with several sets in turn): 4 sequences x 60 nodes x 131072 float32 logits 57.7 / 45.9 / 30.4, 8 x 60 x 262144 bf16 103 / 67 / (spec_walk_kernel),
-// 1 x 60 x 32000 bf16 34.3 / 30.3 / 20.8.
+// Measured, us per call, four sets of tensors in turn, spec_walk_kernel / spec_walk_small_kernel: 4 sequences x 60 nodes x 131072 float32 logits 46.9 / 28.5, 8 x 60 x 262144 bf16 61.2 / 36.2, 1 x 60 x
+// 32000 bf16 31.3 / 23.2; 1 to 1.5 us less where every call has the same tensors.
 #include "common.h"
 #include <algorithm>
 #include <type_traits>
@@ -839,8 +838,8 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 // - While a round is on its way, the waves work out all of the next step that does not need its sum, and ask for the rows of the node that comes next if the
 //   test passes which the round decides.
 // A workgroup that waits in vain ends, workgroup 0 then starts over with the walk above, alone.
-// us per rejection / visited node with statistics to work out, walk above 3.3 / 4.9, here 1.8 / 3.0.  A call, both: 4 sequences x 60 nodes x 131072 float32 logits 50.5 / 30.4,
-// 4 x 60 x 262144 bf16 56.5 / 28.0, 32 x 60 x 32000 bf16 53.8 / 33.3, 1 x 60 x 32000 bf16 24.9 / 20.8, 16 x 60 x 131072 bf16 59.7 / 36.7.  (Workgroups of a sequence on one XCD: 40.6
+// us per rejection / visited node with statistics to work out, walk above 3.3 / 4.9, here 1.8 / 3.0.  A call, both, four sets of tensors in turn: 4 sequences x 60 nodes x 131072 float32 logits 46.9 / 28.5,
+// 4 x 60 x 262144 bf16 56.3 / 28.8, 32 x 60 x 32000 bf16 49.8 / 30.0, 1 x 60 x 32000 bf16 31.3 / 23.2, 16 x 60 x 131072 bf16 59.7 / 37.4.  (Workgroups of a sequence on one XCD: 40.6
 // instead of 37.5 before the first poll was put off.)
 template <bool BF16, int PER, bool VEC>
 __global__ __launch_bounds__(NT + 64) void spec_walk_small_kernel(WalkArgs a)
