@@ -50,7 +50,10 @@ struct AttnArgs {
     int32_t n_q;
     uint32_t spread;         // attend_rows: ceil(2^16 / Hkv) where the KV heads of all sequences are numbered together, 0 where Hkv is a multiple of 8
     int32_t n_tree, include_self;
-    int32_t tiles_per_head;  // 16-row query tiles per head
+    union {
+        int32_t tiles_per_head;  // 16-row query tiles per head (attn_bf16_kernel)
+        uint32_t turn;           // attend_rows: 2^16 * TURN / workgroups of a KV head where the order of RowsGeom::TURNED or SWAPPED is used, or 0
+    };
     int32_t n_qg;            // query groups per KV head
     int32_t mask_words;      // 64-bit words of a node's visibility mask: ceil(n_tree / 64)
     int32_t n_splits;
@@ -59,7 +62,6 @@ struct AttnArgs {
     float scale, scale_log2;
     uint32_t nq_magic;       // for quick_div by n_q
     int32_t once;            // the caches will not be read again before others have displaced them (the ONCE forms of attend_rows)
-    int32_t swap;            // attend_rows: the order of RowsGeom::SWAPPED is used
 };
 
 // Visibility of the tree nodes to one query: bit (a % 64) of word a / 64 is set iff node a is visible.  MW = 1 serves
@@ -772,6 +774,11 @@ struct RowsGeom {
     // (10.0 with both).  With the keys still in the memory-side cache, as between the levels of a draft, the same within 1 % (7.38 / 7.45), the first
     // level 11.2 -> 10.2.
     static constexpr bool SWAPPED = QS == 1 && D == 64 && DS == 2;
+    // The same with more steps and workgroups: of every TURN steps behind the first, which all take together (the first scores come as early), the workgroups of a KV head start
+    // with another one each and go round, so that most of what they read is in L2.  For launches where the pull is far longer than the MFMAs and exponentials beside it: one
+    // query tile, or head_dim 256 in slices.  Nothing but the loads, 1 sequence of 8 KV heads, 60 rows of 4 heads, 1340 keys: 11.5 us, with the order 9.1; the launch 11.7 and 10.4.
+    // TURN 2, 4, 8, 16 there: 11.2, 11.0, 10.7, 10.7, with the first step turned too 0.1 us more each; which workgroups take it: see order_of_tiles().
+    static constexpr bool TURNED = QS == 1 && !SWAPPED && (QT == 1 || D == 256);
     static constexpr int LOADERS = QS == 4 ? 2 : 1;                                // waves that share the loads of a K tile, and of a V tile
     static constexpr int ML_OFF = TILES + (Q_APART ? QS * QT * QTILE : 0), MASK_OFF = ML_OFF + NW * QT * 32 * 4, PAR_OFF = MASK_OFF + NW * QT * 16 * 8, MEET_OFF = PAR_OFF + 64 * 4;
     static constexpr size_t BYTES = MEET_OFF + NW * 4;
@@ -921,8 +928,12 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             issue_v(t, at + G::KTILE);
     };
     const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
-    const int odd = G::SWAPPED && a.swap ? unit & 1 : 0;
-    auto tile = [&](int i) { return kg + KG * (G::SWAPPED && (i | 1) < n_steps ? i ^ odd : i); };   // the key tile of this wave's step i
+    const int odd = G::SWAPPED && a.turn ? unit & 1 : 0, turned = G::TURNED ? (int)((unit * a.turn) >> 16) : 0;
+    auto tile = [&](int i) {                  // the key tile of this wave's step i
+        if (G::SWAPPED)
+            i = (i | 1) < n_steps ? i ^ odd : i;
+        return kg + KG * (G::TURNED ? turned_step(i, n_steps, turned) : i);
+    };
     const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
     const uint32_t meet = lds0 + G::MEET_OFF;
     if (QS > 1)
@@ -1930,6 +1941,27 @@ bool caches_near(const dream_attn_desc *d, int64_t max_kv_len, bool drafting)
     return (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 < (int64_t)(drafting ? 152 : 8) << 20;
 }
 
+// AttnArgs::turn.  The orders that make a CU find most of its keys in L2 pay while what the heads of an XCD have in flight stays there.
+//
+// RowsGeom::SWAPPED: always in a verification.  In a draft, whose caches come from the memory-side cache, only while the heads of an XCD fit its 4 MB L2 or nearly: 3 sequences of 32 heads,
+// 10 rows, 1657 keys, 5.1 MB an XCD, us with the order / without: 10.1 / 9.5, 2233 keys 12.1 / 11.1; 4 sequences of 1145 keys, 4.7 MB, 7.4 / 7.7; a whole level of one sequence 9.4 / 9.6.
+// RowsGeom::TURNED: with three workgroups to a KV head or more, up to 6 MB an XCD, and not in a draft (one sequence of 16 heads of 256, 1640 keys, 4 % more with it; 32 of 128 1 to 3 %).
+// Verifications over 402 shapes (1 to 12 sequences, 17 to 60 rows, 250 to 2300 keys), us in lock step / with the order: head_dim 128, one sequence of 32 heads, 60 rows, 1340 keys 12.3 / 11.4, 1860 keys 15.9 / 14.8;
+// 32 on 8 heads, 1 sequence of 60 rows, 2360 keys 17.3 / 15.2, 3 of 17 rows, 1297 keys 12.0 / 11.0; head_dim 256, 16 on 8 heads, 1 sequence of 60 rows, 1340 keys 16.8 / 15.5, 2 sequences 18.1 / 16.9, 4 of 33 rows, 5.4 MB,
+// 20.5 / 20.2; head_dim 64, 2 sequences of 32 heads, 60 rows, 1860 keys 12.0 / 11.5.  On the other side: two workgroups to a head, 2 sequences of 32 heads of 128, 60 rows, 1340 keys, and the hint gone, 5 %
+// slower; 6 of 16 on 8 heads of 256, 17 rows, 7 MB 6 %, 10 MB 16 %.  Two and three query tiles of head_dim 128, pairs and four slots, whose MFMAs take as long as the pull: 1 to 10 % slower, so they have no such order.
+uint32_t order_of_tiles(const dream_attn_desc *d, const Plan &p, int n_q, int64_t max_kv_len, int verification)
+{
+    if (!p.wave_mode || p.slots != 1)
+        return 0;
+    const int64_t per_xcd = (int64_t)ceil_div((int64_t)d->batch * d->n_kv_heads, 8) * max_kv_len * d->head_dim * 4;
+    const int workgroups = ceil_div(ceil_div((int64_t)(d->n_q_heads / d->n_kv_heads) * n_q, 16), p.wave_qt) * p.wave_ds;
+    const bool swapped = d->head_dim == 64 && p.wave_ds == 2, turned = !swapped && (p.wave_qt == 1 || d->head_dim == 256);
+    if ((swapped && (verification || per_xcd < 5000000)) || (turned && verification && workgroups >= 3 && per_xcd < 6000000))
+        return (uint32_t)(TURN << 16) / workgroups;
+    return 0;
+}
+
 int run_attention(const char *who, const dream_attn_desc *d, const void *q, const void *k, const void *v,
                   const int32_t *prefix_len, int n_tree, const int32_t *parent, const uint64_t *tree_mask,
                   int n_q, const int32_t *q_node, int include_self, int64_t max_kv_len, void *out, float *lse,
@@ -1967,7 +1999,7 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     a.n_q_heads = d->n_q_heads; a.n_kv_heads = d->n_kv_heads; a.group = d->n_q_heads / d->n_kv_heads;
     a.n_q = n_q; a.n_tree = n_tree; a.include_self = include_self;
     a.mask_words = ceil_div(n_tree, 64);
-    a.tiles_per_head = p.tiles_per_head; a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
+    a.n_qg = p.n_qg; a.n_splits = p.n_splits; a.n_streams = p.n_streams;
     auto magic = [](int x) { return x == 1 ? 0u : (uint32_t)(((1ull << 32) + x - 1) / x); };
     a.nq_magic = magic(n_q);
     a.spread = d->n_kv_heads % 8 ? (65536 + d->n_kv_heads - 1) / d->n_kv_heads : 0;
@@ -1976,9 +2008,13 @@ int run_attention(const char *who, const dream_attn_desc *d, const void *q, cons
     // but 5.5 MB a layer 9.4 / 11.0; in 4 column slices, whose workgroups read a quarter of a V row each, head_dim 256, 4 sequences of 33 rows, 20.6 / 21.2: never).
     // (A whole LLaVA draft: 4 sequences, 110 MB 324 / 332, 147 MB 364 / 371; 8 sequences, 156 MB 441 / 424, 192 MB 482 / 422, 294 MB 633 / 544).
     a.once = !caches_near(d, max_kv_len, !include_self);
-    // (In a draft, whose caches come from the memory-side cache, only while the heads of an XCD fit its 4 MB L2 or nearly: 3 sequences of 32 heads, 10 rows, 1657 keys, 5.1 MB an XCD, us
-    // with the order / without: 10.1 / 9.5, 2233 keys 12.1 / 11.1; 4 sequences of 1145 keys, 4.7 MB, 7.4 / 7.7; a whole level of one sequence 9.4 / 9.6.)
-    a.swap = include_self || (int64_t)ceil_div((int64_t)d->batch * d->n_kv_heads, 8) * max_kv_len * d->head_dim * 4 < 5000000;
+    if (p.wave_mode) {
+        a.turn = order_of_tiles(d, p, n_q, max_kv_len, include_self);
+        if (a.turn)
+            a.once = 0;      // (a row that goes back into L2 as the first to leave is not found there)
+    } else {
+        a.tiles_per_head = p.tiles_per_head;
+    }
     a.s_max = d->s_max;
     a.scale = d->scale != 0.0f ? d->scale : 1.0f / sqrtf((float)d->head_dim);
     a.scale_log2 = a.scale * 1.4426950408889634f;

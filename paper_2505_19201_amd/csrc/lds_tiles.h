@@ -36,4 +36,15 @@ constexpr int fragment_v(int c, int g)
 }
 constexpr int at_column_tile(int fragment, int dt) { return (fragment ^ ((dt & 7) * 32)) + (dt >> 3) * 256; }
 
+
+// The step that a workgroup which is `turned` (0 .. TURN - 1) takes as its i-th of n_steps: of every TURN steps behind the first, another one first and then round.
+constexpr int TURN = 8;
+constexpr int turned_step(int i, int n_steps, int turned)
+{
+    if (i <= 0)
+        return i;
+    const int at = (unsigned)(i - 1) % TURN, first = i - at, n = n_steps - first < TURN ? n_steps - first : TURN, k = at + (unsigned)(turned * n) / TURN;
+    return first + (k < n ? k : k - n);
+}
+
 }  // namespace dream

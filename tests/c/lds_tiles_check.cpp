@@ -29,3 +29,5 @@ MAP(map_fragment_k, dream::fragment_k<ROW>(a, b))
 MAP(map_fragment_v, dream::fragment_v<ROW>(a, b))
 extern "C" int map_at_key_step(int fragment, int ks) { return dream::at_key_step(fragment, ks); }
 extern "C" int map_at_column_tile(int fragment, int dt) { return dream::at_column_tile(fragment, dt); }
+extern "C" int map_turned_step(int i, int n_steps, int turned) { return dream::turned_step(i, n_steps, turned); }
+extern "C" int map_turn() { return dream::TURN; }

@@ -252,6 +252,34 @@ def test_swapped_steps(gu, kv_len):
     assert np.abs(lse - want_lse).max() <= 2e-3
 
 
+# one sequence and several ragged ones, two, four and one slices, one and more query tiles of several heads: batch, heads, KV heads, head_dim, rows, keys of a step of all waves
+TURNED = [(1, 32, 32, 128, 60, 128), (3, 32, 8, 128, 17, 128), (1, 32, 8, 128, 17, 256), (2, 32, 32, 64, 33, 256), (1, 16, 8, 256, 60, 128), (3, 16, 8, 256, 17, 128), (3, 16, 8, 256, 33, 128)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,step", TURNED)
+def test_turned_steps(gu, B, Hq, Hkv, D, T, step):
+    """Workgroups that take their steps in turned order: one to three rounds of steps behind the first, whole and not, a last round of one step, the tree and the ragged end in a
+    tile that is taken early; an explicit mask; keys on both sides of the line up to which the order is taken."""
+    per_key = -(-B * Hkv // 8) * D * 4                       # bytes of an XCD's heads
+    line = 6000000 // per_key
+    for kv_len in [n * step + more for n, more in ((1, 0), (1, 1), (2, 0), (5, 0), (8, 1), (9, 0), (9, 1), (10, 40), (16, 1))] + [line - 1, line]:
+        cfg = _cfg("turn", "bf16", B, Hq, Hkv, D, kv_len - T, 0, T, min(5, T - 1), 54)
+        x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) * (3 - b) // 3 for b in range(B)])
+        if not gu.verify_plan(x).startswith("attn_wave_kernel"):
+            continue
+        oracle.set_threads(16)
+        try:
+            got, lse = gu.run_verify(x)
+            want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+            assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3, kv_len
+        finally:
+            oracle.set_threads(1)
+    star = di.star_tree(T)
+    got, _ = gu.run_verify(x, tree_mask=np.stack([di.ancestor_mask_bits(star, True)[:, 0]] * B))
+    want, _ = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, np.stack([star] * B), True)
+    assert np.abs(got - want).max() <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("kv_len", [300, 513, 1024, 1300])
 @pytest.mark.parametrize("B,T", [(2, 17), (3, 9)])
 def test_swapped_steps_of_ragged_sequences_under_a_mask(gu, B, T, kv_len):

@@ -104,3 +104,18 @@ def test_value_fragments(DV, keys):
                     assert at[a + 2 * e] == (h * 16 + row, (dt * 16 + (c & 3) * 4 + e) * 2)
             for banks in bank_groups(addresses, 8):
                 assert len(set(banks)) == len(banks)
+
+
+def test_turned_steps_are_an_order_of_all_steps():
+    """Every step once, the first one first, whatever the number of steps and the workgroup; the workgroups of a head start the steps behind it apart."""
+    turn = LIB.map_turn()
+    for n in range(1, 70):
+        for workgroups in (3, 4, 5, 8, 10, 12, 32):
+            starts = set()
+            for unit in range(workgroups):
+                turned = unit * ((turn << 16) // workgroups) >> 16
+                assert 0 <= turned < turn
+                order = [LIB.map_turned_step(i, n, turned) for i in range(n)]
+                assert order[0] == 0 and sorted(order) == list(range(n)), (n, turned, order)
+                starts.add(order[1] if n > 1 else 0)
+            assert len(starts) >= (min(workgroups, turn) if n > turn else 2 if n > 2 else 1), (n, workgroups)
