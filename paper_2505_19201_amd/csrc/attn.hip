@@ -831,6 +831,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     const int c = lane & 15, g = lane >> 4;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
 
+    // All arguments at once: they are in no cache, and a second batch behind the first condition was a second trip to memory.  (Not a volatile statement: behind one a scalar load
+    // becomes a vector load.)
+    int n_kv_heads = a.n_kv_heads;
+    asm("" : "+s"(n_kv_heads) : "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.prefix_len), "s"(a.parent), "s"(a.tree_mask), "s"(a.group), "s"(a.n_q), "s"(a.spread), "s"(a.n_tree), "s"(a.s_max), "s"(a.nq_magic));
     // workgroups of a KV head have ids congruent mod 8 (same XCD).  The KV heads of all sequences take the XCDs in turn: 4 or 5 heads numbered
     // per sequence left XCDs idle (24 sequences of 4 KV heads, 33 rows of 4 heads, 340 keys: 27.1 us, 15.0 in turn)
     int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z;
@@ -838,10 +842,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     if (__builtin_expect(a.spread != 0, 0)) {
         const int stream = kvh;
         b = (int)((stream * a.spread) >> 16);          // exact: fewer than 264 streams
-        kvh = stream < a.n_streams ? stream - b * a.n_kv_heads : a.n_kv_heads;
+        kvh = stream < a.n_streams ? stream - b * n_kv_heads : n_kv_heads;
     }
     const int n_rows = a.group * a.n_q, row0 = unit / DS * (TILES_Q * 16);
-    if (kvh >= a.n_kv_heads || row0 >= n_rows)
+    if (kvh >= n_kv_heads || row0 >= n_rows)
         return;
     const int prefix = a.prefix_len[b];   // (ahead of the first asm statement, so that it stays a scalar load)
 
