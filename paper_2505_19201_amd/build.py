@@ -25,6 +25,9 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first 14 dwords of a kernel's plain arguments in scalar registers when a wave starts: the arguments of a launch are in no cache, and reading
+    # them is a trip to memory ahead of everything else
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 
 

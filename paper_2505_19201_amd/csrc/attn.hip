@@ -785,6 +785,34 @@ struct RowsGeom {
     static_assert(BYTES <= 160 * 1024 && (Q_APART || QS * QT <= KG * Q_PER) && (QS > 1 || QTILE <= KTILE) && EARLY >= 1 && EARLY <= NS, "a workgroup's LDS");
 };
 
+// What a workgroup needs ahead of its first loads, as plain arguments: the 14 dwords that are in scalar registers when a wave starts (a structure is read from memory).  The
+// plan's limits make them fit: at most 256 streams of up to 4 query heads, 256 rows, s_max below 2^24.  What comes behind them is asked for together with the prefix length.
+// us a launch, all arguments from a structure in two batches / in one / so: one LLaVA sequence 8.71 / 8.46 / 8.36, 30 rows of it 8.42 / 8.15 / 7.99, two Gemma3 sequences of 33 rows 16.9 / 16.6 / 16.3 (with RowsGeom::TURNED).
+struct RowsHead {
+    const int32_t *prefix_len;
+    const void *q, *k, *v;
+    uint32_t heads, rows;    // n_kv_heads + 2^16 * group, n_q + 2^16 * n_tree
+    uint32_t spread, nq_magic, s_max, n_streams;
+};
+#define ROWS_PARAMETERS const int32_t *prefix_len, const void *q, const void *k, const void *v, uint32_t heads, uint32_t rows, uint32_t spread, uint32_t nq_magic, uint32_t s_max, uint32_t n_streams, AttnArgs rest
+#define ROWS_ARGUMENTS with_head(rest, {prefix_len, q, k, v, heads, rows, spread, nq_magic, s_max, n_streams})
+__device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHead &h)
+{
+    AttnArgs a = rest;
+    a.prefix_len = h.prefix_len;
+    a.q = h.q; a.k = h.k; a.v = h.v;
+    a.n_kv_heads = (int)(h.heads & 0xffff);
+    a.group = (int)(h.heads >> 16);
+    a.n_q_heads = a.n_kv_heads * a.group;
+    a.n_q = (int)(h.rows & 0xffff);
+    a.n_tree = (int)(h.rows >> 16);
+    a.spread = h.spread;
+    a.nq_magic = h.nq_magic;
+    a.s_max = h.s_max;
+    a.n_streams = (int)h.n_streams;
+    return a;
+}
+
 template <int N>
 __device__ __forceinline__ void wait_loads()   // until at most N of this wave's loads are in flight
 {
@@ -831,10 +859,6 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     const int c = lane & 15, g = lane >> 4;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
 
-    // All arguments at once: they are in no cache, and a second batch behind the first condition was a second trip to memory.  (Not a volatile statement: behind one a scalar load
-    // becomes a vector load.)
-    int n_kv_heads = a.n_kv_heads;
-    asm("" : "+s"(n_kv_heads) : "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.prefix_len), "s"(a.parent), "s"(a.tree_mask), "s"(a.group), "s"(a.n_q), "s"(a.spread), "s"(a.n_tree), "s"(a.s_max), "s"(a.nq_magic));
     // workgroups of a KV head have ids congruent mod 8 (same XCD).  The KV heads of all sequences take the XCDs in turn: 4 or 5 heads numbered
     // per sequence left XCDs idle (24 sequences of 4 KV heads, 33 rows of 4 heads, 340 keys: 27.1 us, 15.0 in turn)
     int kvh = blockIdx.y * 8 + (blockIdx.x & 7), b = blockIdx.z;
@@ -842,10 +866,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     if (__builtin_expect(a.spread != 0, 0)) {
         const int stream = kvh;
         b = (int)((stream * a.spread) >> 16);          // exact: fewer than 264 streams
-        kvh = stream < a.n_streams ? stream - b * n_kv_heads : n_kv_heads;
+        kvh = stream < a.n_streams ? stream - b * a.n_kv_heads : a.n_kv_heads;
     }
     const int n_rows = a.group * a.n_q, row0 = unit / DS * (TILES_Q * 16);
-    if (kvh >= n_kv_heads || row0 >= n_rows)
+    if (kvh >= a.n_kv_heads || row0 >= n_rows)
         return;
     const int prefix = a.prefix_len[b];   // (ahead of the first asm statement, so that it stays a scalar load)
 
@@ -1283,23 +1307,23 @@ using QuadGeom = RowsGeom<D, DS, QT, 4, 2, D == 256 ? 16 : 32>;
 // ONCE: the loads of whole tiles carry the nontemporal hint (see AttnArgs::once)
 // one query slot: NW key groups of one wave, QT query tiles and one of DS column slices a workgroup
 template <int D, int NW, int DS, int QT, bool ONCE>
-__global__ __launch_bounds__(64 * NW) void attn_wave_kernel(AttnArgs a)
+__global__ __launch_bounds__(64 * NW) void attn_wave_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), ONCE>(a);
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), ONCE>(ROWS_ARGUMENTS);
 }
 
 // two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
 template <int D, int DS, int QT, bool ONCE>
-__global__ __launch_bounds__(512) void attn_pair_kernel(AttnArgs a)
+__global__ __launch_bounds__(512) void attn_pair_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, ONCE>(a);
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, ONCE>(ROWS_ARGUMENTS);
 }
 
 // four query slots: 2 key groups of four waves, 4 * QT query tiles a workgroup
 template <int D, int DS, int QT, bool ONCE>
-__global__ __launch_bounds__(512) void attn_quad_kernel(AttnArgs a)
+__global__ __launch_bounds__(512) void attn_quad_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, ONCE>(a);
+    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, ONCE>(ROWS_ARGUMENTS);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1783,6 +1807,8 @@ int ensure_wave_lds()
     return rc || !hinted ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), bytes, "attention");
 }
 
+#define ROWS_OF(a) a.prefix_len, a.q, a.k, a.v, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
+
 // `per_head` workgroups for every KV head of every sequence, as attend_rows reads them
 dim3 stream_grid(const AttnArgs &a, int per_head)
 {
@@ -1797,9 +1823,9 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, QT) * DS);
     constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
     if (hinted && a.once)
-        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, hinted>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, hinted>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, ROWS_OF(a));
     else
-        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, false>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, false>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, ROWS_OF(a));
     return check_launch("attn_wave_kernel");
 }
 
@@ -1819,9 +1845,9 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 2 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, true>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, true>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     else
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, false>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, false>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     return check_launch("attn_pair_kernel");
 }
 
@@ -1841,9 +1867,9 @@ int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 4 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, true>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, true>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     else
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, false>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, a);
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, false>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     return check_launch("attn_quad_kernel");
 }
 
