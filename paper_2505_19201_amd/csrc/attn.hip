@@ -790,17 +790,18 @@ struct RowsGeom {
 // us a launch, all arguments from a structure in two batches / in one / so: one LLaVA sequence 8.71 / 8.46 / 8.36, 30 rows of it 8.42 / 8.15 / 7.99, two Gemma3 sequences of 33 rows 16.9 / 16.6 / 16.3 (with RowsGeom::TURNED).
 struct RowsHead {
     const int32_t *prefix_len;
-    const void *q, *k, *v;
+    const void *q, *k;
+    const int32_t *parent;   // null: there is a mask
     uint32_t heads, rows;    // n_kv_heads + 2^16 * group, n_q + 2^16 * n_tree
     uint32_t spread, nq_magic, s_max, n_streams;
 };
-#define ROWS_PARAMETERS const int32_t *prefix_len, const void *q, const void *k, const void *v, uint32_t heads, uint32_t rows, uint32_t spread, uint32_t nq_magic, uint32_t s_max, uint32_t n_streams, AttnArgs rest
-#define ROWS_ARGUMENTS with_head(rest, {prefix_len, q, k, v, heads, rows, spread, nq_magic, s_max, n_streams})
+#define ROWS_PARAMETERS const int32_t *prefix_len, const void *q, const void *k, const int32_t *parent, uint32_t heads, uint32_t rows, uint32_t spread, uint32_t nq_magic, uint32_t s_max, uint32_t n_streams, AttnArgs rest
+#define ROWS_ARGUMENTS with_head(rest, {prefix_len, q, k, parent, heads, rows, spread, nq_magic, s_max, n_streams})
 __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHead &h)
 {
     AttnArgs a = rest;
     a.prefix_len = h.prefix_len;
-    a.q = h.q; a.k = h.k; a.v = h.v;
+    a.q = h.q; a.k = h.k; a.parent = h.parent;
     a.n_kv_heads = (int)(h.heads & 0xffff);
     a.group = (int)(h.heads >> 16);
     a.n_q_heads = a.n_kv_heads * a.group;
@@ -881,13 +882,9 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             const int f = min(row0 + r, n_rows - 1), hh = quick_div(f, a.nq_magic), row = f - hh * a.n_q;
             lds_load16(qb, (uint32_t)((row * a.n_q_heads + hh) * KROW + (((lane % LPK) ^ (D == 64 ? (r >> 1) & 7 : r & 15)) * 16)), lds0 + G::q_at(i / (G::QTILE / 1024)) + i % (G::QTILE / 1024) * 1024);
         }
-        if (wave == NW - 1 && !a.tree_mask)
+        if (wave == NW - 1 && a.parent)
             lds_load4(a.parent + (int64_t)b * a.n_tree, (uint32_t)min(lane, a.n_tree - 1) * 4, lds0 + G::PAR_OFF);
     }
-
-    const int P = (int)min((int64_t)max(prefix, 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
-    const int kv_len = P + a.n_tree;
-    const int t_end = (kv_len + KEYS - 1) / KEYS;
 
     // ---- tile loads: a lane's 16 bytes of instruction j go to 1024 * j + 16 * lane of the tile's area
     const unsigned char *kbase = reinterpret_cast<const unsigned char *>(a.k) + ((int64_t)b * a.n_kv_heads + kvh) * a.s_max * KROW;
@@ -900,9 +897,10 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     const int half = G::LOADERS == 2 ? qs & 1 : 0, k_half = half * (KJ * (64 / LPK)), v_half = half * (VJ * (64 / LPV));
     const int krow = lane / LPK, vrow = lane / LPV;
     const int kl = piece_k<KROW>(lane) ^ (half * swizzle_k<KROW>(KJ)), vl = piece_v<VROW>(lane) ^ (half * swizzle_v<VROW>(VJ));
-    auto issue_k = [&](int t, int at) {
+    // (`rows`: the live ones, or those of the cache)
+    auto issue_k = [&](int t, int at, int rows) {
         const uint32_t dst = scalar(lds0 + at + half * (KJ * 1024));
-        if ((t + 1) * KEYS <= kv_len) {
+        if ((t + 1) * KEYS <= rows) {
             const unsigned char *p = kbase + (int64_t)t * (KEYS * KROW) + k_half * KROW;
 #pragma unroll
             for (int j = 0; j < KJ; j++)
@@ -911,9 +909,19 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             // the ragged end: rows past the last live one are that one again (their scores are masked)
 #pragma unroll
             for (int j = 0; j < KJ; j++)
-                lds_load16(kbase, (uint32_t)(min(t * KEYS + k_half + j * (64 / LPK) + krow, kv_len - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
+                lds_load16(kbase, (uint32_t)(min(t * KEYS + k_half + j * (64 / LPK) + krow, rows - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
         }
     };
+    // Every wave's first keys are asked for before it is known how many there are: any row of the cache may be read, and a score behind the last live one is masked (a value is
+    // multiplied with its zero, so those wait).  us a launch, behind the prefix length / ahead of it: one LLaVA sequence 8.36 / 8.14, 250 keys 5.94 / 5.73, one Gemma3 sequence 15.25 / 14.99, twelve 27.9 / 27.9.
+    constexpr bool FIRST = !G::SWAPPED;
+    if (FIRST && (QS == 1 || qs < QS / 2))
+        issue_k(kg, kg * G::STRIDE, (int)a.s_max);
+
+    const int P = (int)min((int64_t)max(prefix, 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
+    const int kv_len = P + a.n_tree;
+    const int t_end = (kv_len + KEYS - 1) / KEYS;
+
     auto issue_v = [&](int t, int at) {
         const uint32_t dst = scalar(lds0 + at + half * (VJ * 1024));
         if ((t + 1) * KEYS <= kv_len) {
@@ -951,7 +959,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     };
     auto issue_slot = [&](int t, int at) {
         if (qs < QS / 2)
-            issue_k(t, at);
+            issue_k(t, at, kv_len);
         else
             issue_v(t, at + G::KTILE);
     };
@@ -970,14 +978,15 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         if constexpr (QS > 1) {
 #pragma unroll
             for (int i = 0; i < G::EARLY; i++)
-                if (i < n_steps)
+                if (i < n_steps && (i > 0 || qs >= QS / 2))
                     issue_slot(t + i * KG, ktile + i * G::GROUP);
             wait_steps(min(n_steps, G::EARLY));   // the queries and parents are there; the first tiles stay in flight
         } else {
-            issue_k(tile(0), ktile);
+            if (!FIRST)
+                issue_k(tile(0), ktile, kv_len);
             issue_v(tile(0), vtile);
             if (early && n_steps > 1) {
-                issue_k(tile(1), ktile2);
+                issue_k(tile(1), ktile2, kv_len);
                 wait_loads<2 * NK + NV>();
             } else {
                 wait_loads<NK + NV>();
@@ -999,7 +1008,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         __syncthreads();                // every wave has its queries
     if constexpr (QS == 1) {
         if (!early && n_steps > 1)
-            issue_k(tile(1), ktile2);
+            issue_k(tile(1), ktile2, kv_len);
     } else {
 #pragma unroll
         for (int i = G::EARLY; i < G::NS; i++)
@@ -1195,7 +1204,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             scores(ktile, s);
             wait_lds();
             if (more2)
-                issue_k(after, ktile);
+                issue_k(after, ktile, kv_len);
             softmax(now, s, p);
             if (more2)
                 wait_loads<NK>();       // this tile's V
@@ -1807,7 +1816,7 @@ int ensure_wave_lds()
     return rc || !hinted ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), bytes, "attention");
 }
 
-#define ROWS_OF(a) a.prefix_len, a.q, a.k, a.v, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
+#define ROWS_OF(a) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
 
 // `per_head` workgroups for every KV head of every sequence, as attend_rows reads them
 dim3 stream_grid(const AttnArgs &a, int per_head)
