@@ -15,6 +15,7 @@
 // reads them again, and what the memory-side cache has kept of them by then is worth more than the hint (drafting 6 levels:
 // LLaVA 243 -> 237 us, 8 SmolVLM sequences 285 -> 279; a single call on cold weights is 0-3 us faster but for LLaVA at 10
 // rows, 19.2 -> 20.6).
+#include <type_traits>
 #include "common.h"
 
 using namespace dream;
@@ -24,84 +25,99 @@ namespace {
 constexpr int NWAVE = 4;   // (8 waves measured 5-8 % slower on the narrower maps, 2 no faster)
 
 struct ProjJob {
-    const uint16_t *x, *w;
+    const uint16_t *x;
     uint16_t *out;
     const int32_t *row_base, *row_index;
     int32_t n_heads;
-    int32_t tile_end;    // one past this job's last workgroup (jobs occupy consecutive workgroup ranges)
 };
 
+// What stands ahead of the weights' first loads comes as plain arguments, which are in scalar registers when a wave starts (14 dwords of them): the weights of the jobs, the ends of the
+// jobs' workgroup ranges (consecutive; the last end where there is no further job) and the sizes.  The rest is a trip to memory, taken while the weights are on their way.
+// (With everything in one structure, looked through job by job, a workgroup made four such trips one after the other ahead of its first load, and two behind its last product, for
+// row_base and row_index, which are asked for at the start now: us a call of three maps, before / now, weights in the memory-side cache: 1 row SmolVLM 5.2 / 4.4, LLaVA 16.4 / 15.6,
+// 20 rows SmolVLM 6.9 / 6.3, Gemma3 11.8 / 11.1, 80 rows SmolVLM 10.1 / 8.5, Pixtral 19.7 / 18.0, LLaVA 28.5 / 25.9; in HBM 80 rows Gemma3 22.2 / 20.4, LLaVA 40.6 / 39.5.)
 struct ProjArgs {
     ProjJob job[DREAM_MAX_PROJ_JOBS];
-    int32_t n_jobs;
     int32_t n_rows;      // R: rows per sequence
-    int32_t m_total;     // B * R
-    int32_t hidden, head_dim;
+    int32_t head_dim;
     int32_t row_groups;  // project_rows_kernel: workgroups that share the rows of a weight tile
     int64_t s_max;       // cache mode only
 };
+static_assert(DREAM_MAX_PROJ_JOBS == 4, "the kernels' arguments");
+// (m_and_lack: B * R, at most 2^20, and from bit 24 on, 2 bits a job, by how many feature tiles its last workgroup has fewer than the others)
+#define PROJ_PARAMS const uint16_t *w0, const uint16_t *w1, const uint16_t *w2, const uint16_t *w3, int end0, int end1, int end2, int end3, int hidden, uint32_t m_and_lack, ProjArgs args
+#define PROJ_SELECT(wg) select_job(w0, w1, w2, w3, end0, end1, end2, end3, m_and_lack, wg)
 
-// The job a workgroup belongs to (uniform: scalar selects) and the first workgroup of that job.
+// The job a workgroup belongs to (uniform), its place among that job's, and how many feature tiles fewer it has.
 struct ProjView {
-    const uint16_t *x, *w;
-    uint16_t *out;
-    const int32_t *row_base, *row_index;
-    int32_t n_heads, n_rows, m_total, hidden, head_dim;
-    int64_t s_max;
-    int first;
+    const uint16_t *w;
+    int job, at, lack;
 };
-__device__ __forceinline__ ProjView select_job(const ProjArgs &args, int wg)
+__device__ __forceinline__ ProjView select_job(const uint16_t *w0, const uint16_t *w1, const uint16_t *w2, const uint16_t *w3, int end0, int end1, int end2, int end3,
+                                               uint32_t m_and_lack, int wg)
 {
-    int ji = 0;
-    for (int j = 0; j + 1 < args.n_jobs; j++)
-        ji += wg >= args.job[j].tile_end;
     ProjView a;
-    a.first = 0;
-    a.x = args.job[0].x; a.w = args.job[0].w; a.out = args.job[0].out; a.row_base = args.job[0].row_base;
-    a.row_index = args.job[0].row_index; a.n_heads = args.job[0].n_heads;
-#pragma unroll
-    for (int j = 1; j < DREAM_MAX_PROJ_JOBS; j++)
-        if (ji == j) {
-            a.x = args.job[j].x; a.w = args.job[j].w; a.out = args.job[j].out; a.row_base = args.job[j].row_base;
-            a.row_index = args.job[j].row_index; a.n_heads = args.job[j].n_heads;
-            a.first = args.job[j - 1].tile_end;
-        }
-    a.n_rows = args.n_rows; a.m_total = args.m_total; a.hidden = args.hidden; a.head_dim = args.head_dim; a.s_max = args.s_max;
+    a.job = wg >= end2 ? 3 : wg >= end1 ? 2 : wg >= end0 ? 1 : 0;
+    a.w = wg >= end2 ? w3 : wg >= end1 ? w2 : wg >= end0 ? w1 : w0;
+    a.at = wg - (wg >= end2 ? end2 : wg >= end1 ? end1 : wg >= end0 ? end0 : 0);
+    const int end = wg >= end2 ? end3 : wg >= end1 ? end2 : wg >= end0 ? end1 : end0;
+    a.lack = wg + 1 == end ? m_and_lack >> (24 + 2 * a.job) & 3 : 0;
     return a;
 }
 
-// The lane's four results, outputs n0 + g*4 .. +3 of feature row m, to where they belong.
-__device__ __forceinline__ void store_row_piece(const ProjView &a, int m, int n0, int g, f32x4 sum)
+// The job's arguments, all asked for at once.
+__device__ __forceinline__ ProjJob job_arguments(const ProjArgs &args, int j)
 {
-    if (m >= a.m_total)
+    const ProjJob job = args.job[j];
+    asm volatile("" ::"s"(job.x), "s"(job.out), "s"(job.row_base), "s"(job.row_index), "s"(job.n_heads), "s"(args.n_rows), "s"(args.head_dim),
+                 "s"(args.row_groups), "s"(args.s_max));
+    return job;
+}
+
+// Where feature row m belongs: its sequence, and the two numbers whose sum is the row in that sequence's cache (or among its rows).  Asked for early, added up behind the products.
+struct RowPlace {
+    int base, index;
+};
+__device__ __forceinline__ RowPlace ask_row(const ProjJob &job, int m, int n_rows)
+{
+    const int b = m / n_rows, r = m - b * n_rows;
+    RowPlace p = {0, r};
+    if (job.row_base) {
+        p.base = job.row_base[b];
+        if (job.row_index)
+            p.index = job.row_index[m];
+    }
+    return p;
+}
+
+// The lane's four results, outputs n0 + g*4 .. +3 of feature row m, which belongs at `row`, to where they belong.
+__device__ __forceinline__ void store_row_piece(const ProjArgs &args, const ProjJob &job, int m, int m_total, int row, int n0, int g, f32x4 sum)
+{
+    const bool cache = job.row_base != nullptr;
+    if (m >= m_total || (cache && (row < 0 || row >= args.s_max)))      // a row outside the cache is dropped, never written
         return;
-    const int h = n0 / a.head_dim, d0 = n0 % a.head_dim;
-    const int b = m / a.n_rows, r = m - b * a.n_rows;
+    const int h = n0 / args.head_dim, d0 = n0 % args.head_dim;
+    const int b = m / args.n_rows;
     bf16x4 o;
 #pragma unroll
     for (int i = 0; i < 4; i++)
         o[i] = (__bf16)sum[i];
-    int64_t dst;
-    if (a.row_base) {
-        const int row = a.row_base[b] + (a.row_index ? a.row_index[(int64_t)b * a.n_rows + r] : r);
-        dst = row >= 0 && row < a.s_max ? (((int64_t)b * a.n_heads + h) * a.s_max + row) * a.head_dim + d0 + g * 4 : -1;
-    } else {
-        dst = (((int64_t)b * a.n_rows + r) * a.n_heads + h) * a.head_dim + d0 + g * 4;
-    }
-    if (dst >= 0)                                        // a row outside the cache is dropped, never written
-        *reinterpret_cast<bf16x4 *>(a.out + dst) = o;
+    const int64_t at = cache ? ((int64_t)b * job.n_heads + h) * args.s_max + row : (int64_t)m * job.n_heads + h;
+    *reinterpret_cast<bf16x4 *>(job.out + at * args.head_dim + d0 + g * 4) = o;
 }
 
-// At most 16 feature rows.
-__global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
+// At most 16 feature rows, XJ * 4 of them loaded.  (With XJ a variable every load of a row is under a condition, and the waits count for the worst of them.)
+template <int XJ>
+__global__ __launch_bounds__(64 * NWAVE) void project_kernel(PROJ_PARAMS)
 {
-    const ProjView a = select_job(args, blockIdx.x);
+    const ProjView a = PROJ_SELECT(blockIdx.x);
+    const int m_total = m_and_lack & 0xffffff;
     __shared__ __attribute__((aligned(16))) float s_part[NWAVE][64][4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int n0 = ((int)blockIdx.x - a.first) * 16;
-    const int K = a.hidden, kw = K / NWAVE;          // this wave's slice of the hidden dimension
+    const int n0 = a.at * 16;
+    const int K = hidden, kw = K / NWAVE;          // this wave's slice of the hidden dimension
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // Rows are fetched 256 contiguous bytes at a time (4 rows per load instruction: full cache lines) into
     // a wave-private LDS area and read back in operand layout; loading the operands directly would make
@@ -113,44 +129,61 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
     const int lrow = lane / LPR, lcol = (lane % LPR) * 8;
     const int n_ss = (kw + SS - 1) / SS;
     const uint16_t *wsrc = a.w + (int64_t)n0 * K + wave * kw;
-    const uint16_t *xsrc = a.x + wave * kw;
-    const int xj = min((a.m_total + RPI - 1) / RPI, NI);
-    auto issue = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
+    static_assert(XJ <= NI, "rows");
+    const uint16_t *xsrc = nullptr;
+    auto column = [&](int s) {
         s = min(s, n_ss - 1);                              // the prefetch past the end re-reads and is dropped
         const int nvalid = min(SS, kw - s * SS);
-        const int col = s * SS + (lcol < nvalid ? lcol : 0);
+        return s * SS + (lcol < nvalid ? lcol : 0);
+    };
+    auto issue_w = [&](int col, u32x4 (&wr)[NI]) {
 #pragma unroll
-        for (int j = 0; j < NI; j++) {
+        for (int j = 0; j < NI; j++)
             wr[j] = *reinterpret_cast<const u32x4 *>(wsrc + (int64_t)(j * RPI + lrow) * K + col);
-            if (j < xj) {   // feature rows are fetched RPI at a time, only as many as exist
-                const int m = min(j * RPI + lrow, a.m_total - 1);
-                xr[j] = *reinterpret_cast<const u32x4 *>(xsrc + (int64_t)m * K + col);
-            }
+    };
+    auto issue_x = [&](int col, u32x4 (&xr)[XJ]) {
+#pragma unroll
+        for (int j = 0; j < XJ; j++) {     // feature rows are fetched RPI at a time, only as many as exist
+            const int m = min(j * RPI + lrow, m_total - 1);
+            xr[j] = *reinterpret_cast<const u32x4 *>(xsrc + (int64_t)m * K + col);
         }
     };
     // one super-step: registers -> LDS, request the super-step that reuses these registers, multiply
-    auto step = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[NI]) {
+    auto step = [&](int s, u32x4 (&wr)[NI], u32x4 (&xr)[XJ]) {
 #pragma unroll
         for (int j = 0; j < NI; j++) {
             *reinterpret_cast<u32x4 *>(lw + (j * RPI + lrow) * RSTR + lcol) = wr[j];
-            if (j < xj)     // (the other LDS rows feed output columns that are never stored)
-                *reinterpret_cast<u32x4 *>(lx + (j * RPI + lrow) * RSTR + lcol) = xr[j];
+            if (j < XJ)     // (the other LDS rows feed output columns that are never stored)
+                *reinterpret_cast<u32x4 *>(lx + (j * RPI + lrow) * RSTR + lcol) = xr[j < XJ ? j : 0];
         }
-        issue(s + 1, wr, xr);
+        issue_w(column(s + 1), wr);
+        issue_x(column(s + 1), xr);
         wave_lds_fence();
-        const int nvalid = min(SS, kw - s * SS);
+        // (a wave's share is a multiple of 64: the last step may be half a one)
+        auto multiply = [&](auto n) {
+            bf16x8 af[n], bfr[n];
 #pragma unroll
-        for (int ks = 0; ks < SS / 32; ks++) {
-            if (ks * 32 < nvalid) {
-                const bf16x8 af = *reinterpret_cast<const bf16x8 *>(lw + c * RSTR + ks * 32 + g * 8);
-                const bf16x8 bfr = *reinterpret_cast<const bf16x8 *>(lx + c * RSTR + ks * 32 + g * 8);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc, 0, 0, 0);
+            for (int ks = 0; ks < n; ks++) {
+                af[ks] = *reinterpret_cast<const bf16x8 *>(lw + c * RSTR + ks * 32 + g * 8);
+                bfr[ks] = *reinterpret_cast<const bf16x8 *>(lx + c * RSTR + ks * 32 + g * 8);
             }
-        }
+#pragma unroll
+            for (int ks = 0; ks < n; ks++)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks], bfr[ks], acc, 0, 0, 0);
+        };
+        if (kw - s * SS >= SS)
+            multiply(std::integral_constant<int, SS / 32>());
+        else
+            multiply(std::integral_constant<int, SS / 64>());
         wave_lds_fence();
     };
-    u32x4 wr[NI], xr[NI];
-    issue(0, wr, xr);
+    u32x4 wr[NI], xr[XJ];
+    issue_w(column(0), wr);
+    __builtin_amdgcn_sched_barrier(0);                     // (the first weights do not wait for the other arguments)
+    const ProjJob job = job_arguments(args, a.job);
+    xsrc = job.x + wave * kw;
+    issue_x(column(0), xr);
+    const RowPlace place = ask_row(job, min(c, m_total - 1), args.n_rows);
     for (int s = 0; s < n_ss; s++)
         step(s, wr, xr);
     // sum the waves' partial tiles in wave order
@@ -161,7 +194,7 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(ProjArgs args)
 #pragma unroll
         for (int w = 0; w < NWAVE; w++)
             sum += *reinterpret_cast<const f32x4 *>(s_part[w][lane]);
-        store_row_piece(a, c, n0, g, sum);
+        store_row_piece(args, job, c, m_total, place.base + place.index, n0, g, sum);
     }
 }
 
@@ -184,57 +217,76 @@ constexpr int TILE_BYTES = 16 * STEP_BYTES;
 template <int MT, int NT>
 struct RowsGeom {
     static constexpr int STAGE = (MT + NT) * TILE_BYTES;                          // of a wave
-    static constexpr size_t LDS_BYTES = RW * (STAGE > MT * NT * 1024 ? STAGE : MT * NT * 1024);   // (the partial tiles reuse the stages)
+    static constexpr int ROWS_OFF = RW * MT * NT * 1024;                           // where the rows belong, behind the partial tiles, which reuse the stages
+    static constexpr size_t LDS_BYTES = RW * STAGE > ROWS_OFF + 16 * MT * 4 ? RW * STAGE : ROWS_OFF + 16 * MT * 4;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
 template <int MT, int NT>
-__global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
+__global__ __launch_bounds__(64 * RW) void project_rows_kernel(PROJ_PARAMS)
 {
     using G = RowsGeom<MT, NT>;
     // one row group: a line of workgroups; several: 8 tiles x groups x eighths of the tiles, so that the workgroups of a weight tile have ids congruent
-    // mod 8 (same XCD) and few lie between them (a tile past the last repeats it and stores nothing)
+    // mod 8 (same XCD) and few lie between them
     const int tile = blockIdx.z * 8 + blockIdx.x, group = blockIdx.y;
-    const ProjView a = select_job(args, tile);
+    if (tile >= end3)
+        return;
+    const ProjView a = PROJ_SELECT(tile);
+    const int m_total = m_and_lack & 0xffffff;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int n_tiles = a.n_heads * a.head_dim / 16, nt0 = (tile - a.first) * NT;
-    const int K = a.hidden, n_steps = (K / STEP - wave + RW - 1) / RW;   // this wave's: steps wave, wave + RW, ...
+    const int n_here = NT - a.lack, nt0 = a.at * NT;         // feature tiles of this workgroup
+    const int K = hidden, n_steps = (K / STEP - wave + RW - 1) / RW;   // this wave's: steps wave, wave + RW, ...
     unsigned char *stage = smem + wave * G::STAGE;
     // The workgroups of an XCD start at different steps: the rows are a power of two or nearly so apart, so one step's pieces
     // of all rows sit in few L2 channels, and everybody would ask the same ones at the same time (LLaVA, 20 rows: 29 us without, 18 with).
     const int first = n_steps > 0 ? (tile >> 3) % n_steps : 0;
     const int lrow = lane >> 3, lchunk = lane & 7;           // a load instruction: 8 rows x 128 bytes
-    for (int m0 = group * 16 * MT; m0 < a.m_total; m0 += args.row_groups * 16 * MT) {
-        const uint16_t *wsrc[NT], *xsrc[MT * 2];
+    const uint16_t *wsrc[NT], *xsrc[MT * 2];
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++)                       // (tiles past the last repeat it, never stored)
-            wsrc[nt] = a.w + ((int64_t)min(nt0 + nt, n_tiles - 1) * 16 + lrow) * K + wave * STEP + lchunk * 8;
+    for (int nt = 0; nt < NT; nt++)                          // (tiles past the last repeat it, never stored)
+        wsrc[nt] = a.w + ((int64_t)(nt0 + min(nt, n_here - 1)) * 16 + lrow) * K + wave * STEP + lchunk * 8;
+    u32x4 wr[NT * 2], xr[MT * 2];
+    auto column = [&](int s) {
+        const int at = s + first;
+        return (at < n_steps ? at : at - n_steps) * (RW * STEP);
+    };
+    auto load_w = [&](int j, int col) { wr[j] = *reinterpret_cast<const u32x4 *>(wsrc[j / 2] + (j % 2 ? (int64_t)8 * K : 0) + col); };
+    auto issue_w = [&](int col) {
+#pragma unroll
+        for (int j = 0; j < NT * 2; j++)
+            load_w(j, col);
+    };
+    if (n_steps > 0)
+        issue_w(column(0));
+    __builtin_amdgcn_sched_barrier(0);                       // (the first weights do not wait for the other arguments)
+    const ProjJob job = job_arguments(args, a.job);
+    int m0 = group * 16 * MT, xj = 0;
+    RowPlace place = {0, 0};
+    auto load_x = [&](int j, int col) {
+        if (j < MT * 2 - 2 || j < xj)                        // all but the last tile are full
+            xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
+    };
+    auto issue_x = [&](int col) {
 #pragma unroll
         for (int j = 0; j < MT * 2; j++)
-            xsrc[j] = a.x + (int64_t)min(m0 + j * 8 + lrow, a.m_total - 1) * K + wave * STEP + lchunk * 8;
-        const int xj = min((a.m_total - m0 + 7) / 8, MT * 2);
-        u32x4 wr[NT * 2], xr[MT * 2];
-        auto column = [&](int s) {
-            const int at = s + first;
-            return (at < n_steps ? at : at - n_steps) * (RW * STEP);
-        };
-        auto load_w = [&](int j, int col) { wr[j] = *reinterpret_cast<const u32x4 *>(wsrc[j / 2] + (j % 2 ? (int64_t)8 * K : 0) + col); };
-        auto load_x = [&](int j, int col) {
-            if (j < MT * 2 - 2 || j < xj)                     // all but the last tile are full
-                xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
-        };
-        auto issue = [&](int s) {
-            const int col = column(s);
+            load_x(j, col);
+    };
+    auto start_rows = [&] {                                  // the pass over the rows from m0 on
+        xj = min((m_total - m0 + 7) / 8, MT * 2);
 #pragma unroll
-            for (int j = 0; j < NT * 2; j++)
-                load_w(j, col);
-#pragma unroll
-            for (int j = 0; j < MT * 2; j++)
-                load_x(j, col);
-        };
+        for (int j = 0; j < MT * 2; j++)
+            xsrc[j] = job.x + (int64_t)min(m0 + j * 8 + lrow, m_total - 1) * K + wave * STEP + lchunk * 8;
+        if (n_steps > 0)
+            issue_x(column(0));
+        if (tid < 16 * MT)
+            place = ask_row(job, min(m0 + tid, m_total - 1), args.n_rows);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    start_rows();
+    for (;;) {
         f32x4 acc[MT][NT];
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
@@ -261,8 +313,10 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
                 if (EARLY && more)
                     load_x(j, col);
             }
-            if (!EARLY && more)
-                issue(s + 1);
+            if (!EARLY && more) {
+                issue_w(col);
+                issue_x(col);
+            }
             wave_lds_fence();
 #pragma unroll
             for (int i = 0; i < STEP / 32; i++) {
@@ -282,7 +336,6 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
             wave_lds_fence();
         };
         if (n_steps > 0) {                                    // (a wave of a narrow map may have none)
-            issue(0);
             for (int s = 0; s + 1 < n_steps; s++)
                 step(s, true);
             step(n_steps - 1, false);
@@ -290,6 +343,9 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
         // the waves' partial tiles, summed in wave order
         __syncthreads();
         f32x4 *part = reinterpret_cast<f32x4 *>(smem);
+        int *s_row = reinterpret_cast<int *>(smem + G::ROWS_OFF);
+        if (tid < 16 * MT)
+            s_row[tid] = place.base + place.index;
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
 #pragma unroll
@@ -302,10 +358,16 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(ProjArgs args)
             for (int w = 1; w < RW; w++)
                 sum += part[(t * RW + w) * 64 + lane];
             const int mt = t / NT, nt = t - mt * NT;
-            if (nt0 + nt < n_tiles)
-                store_row_piece(a, m0 + mt * 16 + c, (nt0 + nt) * 16, g, sum);
+            if (nt < n_here)
+                store_row_piece(args, job, m0 + mt * 16 + c, m_total, s_row[mt * 16 + c], (nt0 + nt) * 16, g, sum);
         }
+        m0 += args.row_groups * 16 * MT;
+        if (m0 >= m_total)
+            return;
         __syncthreads();
+        if (n_steps > 0)
+            issue_w(column(0));
+        start_rows();
     }
 }
 
@@ -319,19 +381,27 @@ int ensure_rows_lds(const char *who)
     return raise_lds_limit(done, reinterpret_cast<const void *>(&project_rows_kernel<MT, NT>), RowsGeom<MT, NT>::LDS_BYTES, who);
 }
 
+struct Launch {          // the plain arguments
+    const uint16_t *w[DREAM_MAX_PROJ_JOBS];
+    int end[DREAM_MAX_PROJ_JOBS];
+    int hidden;
+    uint32_t m_and_lack;
+};
+
 template <int MT, int NT>
-int launch_rows(int wgs, hipStream_t st, const ProjArgs &a)
+int launch_rows(int wgs, hipStream_t st, const Launch &l, const ProjArgs &a)
 {
     if (int rc = ensure_rows_lds<MT, NT>("dream_project_rows"))
         return rc;
     const dim3 grid = a.row_groups == 1 ? dim3(wgs) : dim3(8, a.row_groups, ceil_div(wgs, 8));
-    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), grid, dim3(64 * RW), (RowsGeom<MT, NT>::LDS_BYTES), st, a);
+    hipLaunchKernelGGL((project_rows_kernel<MT, NT>), grid, dim3(64 * RW), (RowsGeom<MT, NT>::LDS_BYTES), st, l.w[0], l.w[1], l.w[2], l.w[3], l.end[0], l.end[1],
+                       l.end[2], l.end[3], l.hidden, l.m_and_lack, a);
     return check_launch("project_rows_kernel");
 }
 
 // The variants, by row tiles per pass and feature tiles per workgroup: project_init walks the table, a call picks from it.
 struct RowsVariant {
-    int (*launch)(int, hipStream_t, const ProjArgs &);
+    int (*launch)(int, hipStream_t, const Launch &, const ProjArgs &);
     int (*ensure)(const char *);
 };
 #define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, max_nt(MT)>, &ensure_rows_lds<MT, max_nt(MT)>}}
@@ -371,6 +441,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     if (hidden < 256 || hidden % 256)
         return fail(DREAM_ERR_UNSUPPORTED, "%s: hidden %d is not a positive multiple of 256", who, hidden);
     ProjArgs a = {};
+    Launch l = {};
     int64_t tiles = 0;
     for (int j = 0; j < n_jobs; j++) {
         const dream_proj_job &jb = jobs[j];
@@ -387,22 +458,26 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         tiles += (int64_t)jb.n_heads * desc->head_dim / 16;
         if (tiles > (1 << 24))
             return fail(DREAM_ERR_UNSUPPORTED, "%s: more than 2^24 tiles of 16 output features", who);
-        a.job[j].x = static_cast<const uint16_t *>(jb.x); a.job[j].w = static_cast<const uint16_t *>(jb.w);
+        a.job[j].x = static_cast<const uint16_t *>(jb.x); l.w[j] = static_cast<const uint16_t *>(jb.w);
         a.job[j].out = static_cast<uint16_t *>(jb.out); a.job[j].row_base = jb.row_base; a.job[j].row_index = jb.row_index;
-        a.job[j].n_heads = jb.n_heads; a.job[j].tile_end = (int32_t)tiles;
+        a.job[j].n_heads = jb.n_heads; l.end[j] = (int32_t)tiles;
     }
-    a.n_jobs = n_jobs; a.n_rows = n_rows; a.m_total = desc->batch * n_rows; a.hidden = hidden; a.head_dim = desc->head_dim;
+    const int m_total = desc->batch * n_rows;
+    for (int j = n_jobs; j < DREAM_MAX_PROJ_JOBS; j++)
+        l.end[j] = (int32_t)tiles;
+    a.n_rows = n_rows; l.m_and_lack = m_total; l.hidden = hidden; a.head_dim = desc->head_dim;
     a.s_max = desc->s_max;
     hipStream_t st = as_stream(stream);
-    if (a.m_total <= 16) {
-        hipLaunchKernelGGL(project_kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, a);
+    if (m_total <= 16) {
+        auto *kernel = m_total > 12 ? &project_kernel<4> : m_total > 8 ? &project_kernel<3> : m_total > 4 ? &project_kernel<2> : &project_kernel<1>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, l.w[0], l.w[1], l.w[2], l.w[3], l.end[0], l.end[1], l.end[2], l.end[3], hidden, l.m_and_lack, a);
         return check_launch("project_kernel");
     }
     // Row tiles per pass (2 to 8: there are at least 17 rows), feature tiles per workgroup and how many workgroups share the rows of a feature tile: the fewest bytes
     // through the busiest CU.  Up to 128 rows are one pass; above, a workgroup goes through as few passes as there have to be, of about equal size, or every pass is a workgroup of its
     // own, which leaves fewer CUs idle and reads weights that another pass has brought to L2.  us, one after the other / side by side: LLaVA 256 rows 72.3 / 53.8 (weights in HBM 84.2 / 66.0),
     // 144 rows 50.1 / 40.3, 1000 rows 266 / 205; SmolVLM 192 rows 19.3 / 17.3, 1000 rows 83.8 / 66.6; hidden dimension 768, 1000 rows 32.7 / 16.4.
-    const int m_tiles = ceil_div(a.m_total, 16), passes = ceil_div(m_tiles, MAX_MT);
+    const int m_tiles = ceil_div(m_total, 16), passes = ceil_div(m_tiles, MAX_MT);
     int mt = 0, nt = 1;
     int64_t best = 0;
     auto try_split = [&](int m, int n, int groups) {
@@ -412,7 +487,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         const bool fits = groups <= 65535 && wgs <= 8 * 65535 && (wgs + 7) / 8 * 8 * groups <= (1 << 22);      // (a grid's extents, its 2^32 threads)
         if (groups > 1)
             wgs = (wgs + 7) / 8 * 8 * groups;
-        const int64_t cost = (wgs + 255) / 256 * (groups > 1 ? 16 * (m + n) * 11 : (a.m_total + 16 * n * passes) * 10);   // (Gemma3, 1000 rows: 8 % fewer, and 5 % slower)
+        const int64_t cost = (wgs + 255) / 256 * (groups > 1 ? 16 * (m + n) * 11 : (m_total + 16 * n * passes) * 10);   // (Gemma3, 1000 rows: 8 % fewer, and 5 % slower)
         if (mt == 0 || (cost < best && (groups == 1 || fits))) {
             best = cost;
             mt = m;
@@ -428,11 +503,15 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
             for (int n = 1; n <= max_nt(m); n++)
                 try_split(m, n, ceil_div(m_tiles, m));
     int wgs = 0;
-    for (int j = 0; j < n_jobs; j++) {
-        wgs += ceil_div((int64_t)a.job[j].n_heads * a.head_dim / 16, nt);
-        a.job[j].tile_end = wgs;
+    for (int j = 0; j < DREAM_MAX_PROJ_JOBS; j++) {
+        if (j < n_jobs) {
+            const int64_t n = (int64_t)a.job[j].n_heads * a.head_dim / 16;
+            wgs += ceil_div(n, nt);
+            l.m_and_lack |= (uint32_t)(ceil_div(n, nt) * nt - n) << (24 + 2 * j);
+        }
+        l.end[j] = wgs;
     }
-    return ROWS[mt - 2][nt - 1].launch(wgs, st, a);
+    return ROWS[mt - 2][nt - 1].launch(wgs, st, l, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,
