@@ -266,7 +266,7 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(PROJ_PARAMS)
     int m0 = group * 16 * MT, xj = 0;
     RowPlace place = {0, 0};
     auto load_x = [&](int j, int col) {
-        if (j < MT * 2 - 2 || j < xj)                        // all but the last tile are full
+        if (j < MT * 2 - 2 || j == 0 || j < xj)              // all but the last tile are full
             xr[j] = *reinterpret_cast<const u32x4 *>(xsrc[j] + col);
     };
     auto issue_x = [&](int col) {
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(PROJ_PARAMS)
             }
 #pragma unroll
             for (int j = 0; j < MT * 2; j++) {
-                if (j < MT * 2 - 2 || j < xj)
+                if (j < MT * 2 - 2 || j == 0 || j < xj)
                     *reinterpret_cast<u32x4 *>(stage + (NT * 2 + j) * 1024 + put) = xr[j];
                 if (EARLY && more)
                     load_x(j, col);
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(64 * RW) void project_rows_kernel(PROJ_PARAMS)
 }
 
 constexpr int MAX_MT = 8, MAX_NT = 3;
-constexpr int max_nt(int mt) { return mt < 7 ? 3 : 2; }   // (what LDS holds)
+constexpr int max_nt(int mt) { return mt == 1 || mt > 6 ? 2 : 3; }   // (what LDS holds; what a call with one row tile takes)
 
 template <int MT, int NT>
 int ensure_rows_lds(const char *who)
@@ -405,7 +405,7 @@ struct RowsVariant {
     int (*ensure)(const char *);
 };
 #define ROWS_VARIANTS(MT) {{&launch_rows<MT, 1>, &ensure_rows_lds<MT, 1>}, {&launch_rows<MT, 2>, &ensure_rows_lds<MT, 2>}, {&launch_rows<MT, max_nt(MT)>, &ensure_rows_lds<MT, max_nt(MT)>}}
-const RowsVariant ROWS[MAX_MT - 1][MAX_NT] = {ROWS_VARIANTS(2), ROWS_VARIANTS(3), ROWS_VARIANTS(4), ROWS_VARIANTS(5),
+const RowsVariant ROWS[MAX_MT][MAX_NT] = {ROWS_VARIANTS(1), ROWS_VARIANTS(2), ROWS_VARIANTS(3), ROWS_VARIANTS(4), ROWS_VARIANTS(5),
                                               ROWS_VARIANTS(6), ROWS_VARIANTS(7), ROWS_VARIANTS(8)};
 #undef ROWS_VARIANTS
 
@@ -468,7 +468,13 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     a.n_rows = n_rows; l.m_and_lack = m_total; l.hidden = hidden; a.head_dim = desc->head_dim;
     a.s_max = desc->s_max;
     hipStream_t st = as_stream(stream);
-    if (m_total <= 16) {
+    // Up to 16 rows: where a workgroup per CU holds the feature tiles, one each or two, the eight waves of project_rows_kernel, which pull a row once for both; above, where workgroups share
+    // CUs unevenly, the smaller ones of project_kernel, and for two tiles also with rows 8 KB apart, whose pieces sit in few channels.  us, project_kernel / project_rows_kernel, weights in
+    // the memory-side cache and in HBM: 10 rows, 8 tiles of hidden dimension 768 4.0 / 3.3 and 4.1 / 3.4, 128 of 3840 5.0 / 4.6 and 6.1 / 5.6, 256 of 4096 5.9 / 5.7 and 7.0 / 6.7;
+    // two tiles: 384 of 5120 (Pixtral, three maps) 11.7 / 10.8 and 15.4 / 14.1, 512 of 3840 (Gemma3) 11.5 / 10.8 and 12.7 / 11.9, 384 of 2048 4.9 / 4.7 and 6.1 / 6.0, but
+    // 384 of 4096 7.6 / 9.1 and 11.1 / 12.2, 512 of 4096 11.5 / 11.2 and 13.2 / 16.8, 768 of 4096 (LLaVA) 16.2 / 16.4 and 19.6 / 23.6.  One row: the same, the gains smaller.
+    const int tiles_16 = tiles <= 256 ? 1 : tiles <= 512 && hidden % 4096 ? 2 : 0;
+    if (m_total <= 16 && tiles_16 == 0) {
         auto *kernel = m_total > 12 ? &project_kernel<4> : m_total > 8 ? &project_kernel<3> : m_total > 4 ? &project_kernel<2> : &project_kernel<1>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, l.w[0], l.w[1], l.w[2], l.w[3], l.end[0], l.end[1], l.end[2], l.end[3], hidden, l.m_and_lack, a);
         return check_launch("project_kernel");
@@ -496,7 +502,11 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         }
     };
     a.row_groups = 1;
-    for (int n = 1; n <= max_nt(ceil_div(m_tiles, passes)); n++)
+    if (m_total <= 16) {
+        mt = 1;
+        nt = tiles_16;
+    }
+    for (int n = 1; mt != 1 && n <= max_nt(ceil_div(m_tiles, passes)); n++)
         try_split(ceil_div(m_tiles, passes), n, 1);
     if (passes > 1)
         for (int m = 2; m <= MAX_MT; m++)
@@ -511,7 +521,7 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
         }
         l.end[j] = wgs;
     }
-    return ROWS[mt - 2][nt - 1].launch(wgs, st, l, a);
+    return ROWS[mt - 1][nt - 1].launch(wgs, st, l, a);
 }
 
 int dream_project_rows(const dream_attn_desc *desc, const void *x, int32_t n_rows, int32_t hidden, const void *w, int32_t n_heads,

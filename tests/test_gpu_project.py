@@ -139,3 +139,31 @@ def test_passes_side_by_side(gu, R, hidden, Hq, Hkv, D):
     for got, w, cache in ((k, ws[1], kc), (v, ws[2], vc)):
         _close(di.bf16_bits_to_f32(got[0][:, 4:4 + R].view(np.uint16)).astype(np.float64), oracle.project(s, w, "bf16", Hkv, D)[0].transpose(1, 0, 2))
         assert np.array_equal(got[0][:, :4], cache[0][:, :4].view(np.int16)) and np.array_equal(got[0][:, 4 + R:], cache[0][:, 4 + R:].view(np.int16))
+
+
+@pytest.mark.parametrize("R", [1, 4, 5, 8, 9, 12, 13, 16])
+@pytest.mark.parametrize("hidden,tiles", [(256, 1), (768, 256), (1280, 257), (768, 511), (768, 513), (4096, 258)])
+def test_up_to_sixteen_rows(gu, R, hidden, tiles):
+    """Both kernels on both sides of the lines between them (256 and 512 feature tiles, rows a multiple of 8 KB apart), one to four pieces of rows, a workgroup with one tile of two,
+    a wave whose share of the hidden dimension ends in half a step."""
+    x, w = _inputs(1, R, hidden, tiles, 16, 150 + R)
+    _close(gu.run_project(x, w, tiles, 16), oracle.project(x, w, "bf16", tiles, 16))
+
+
+@pytest.mark.parametrize("hidden,Hq,Hkv", [(512, 7, 3), (512, 151, 55), (512, 255, 129), (512, 171, 171)])
+def test_maps_of_odd_widths_in_one_launch(gu, hidden, Hq, Hkv):
+    """Every map's last workgroup has one feature tile of two, and none writes into another map."""
+    B, R, D = 1, 10, 16
+    e, s = (di.normal((B, R, hidden), "bf16", 401 + i, di.STREAM_ROWS) for i in range(2))
+    ws = [di.f32_to_bf16_bits(di.normal((h * D, hidden), "f32", 403 + i, di.STREAM_ROWS) * np.float32(hidden ** -0.5)) for i, h in enumerate((Hq, Hkv, Hkv))]
+    kc, vc = (di.normal((B, Hkv, 40, D), "bf16", 410 + i, di.STREAM_K) for i in range(2))
+    row_index = np.array([[9, 0, 3, 1, 30, 12, 5, 6, 7, 35]], dtype=np.int32)              # 35: outside the cache
+    q, k, v = gu.run_project_qkv(e, s, ws[0], ws[1], ws[2], Hq, Hkv, D, np.array([5], dtype=np.int32), row_index, kc, vc)
+    _close(q, oracle.project(e, ws[0], "bf16", Hq, D))
+    for got, w, cache in ((k, ws[1], kc), (v, ws[2], vc)):
+        want = oracle.project(s, w, "bf16", Hkv, D)[0].transpose(1, 0, 2)
+        rows = 5 + row_index[0, :9]
+        _close(di.bf16_bits_to_f32(got[0][:, rows].view(np.uint16)).astype(np.float64), want[:, :9])
+        keep = np.ones(40, dtype=bool)
+        keep[rows] = False
+        assert np.array_equal(got[0][:, keep], cache[0][:, keep].view(np.int16))
