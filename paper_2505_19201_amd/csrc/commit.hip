@@ -21,18 +21,17 @@ constexpr int MAX_CACHES_PER_LAUNCH = 128;
 constexpr int CHUNKS_PER_THREAD = 16;   // 256 threads x 16 chunks x 16 bytes = 64 KB of rows per workgroup
 
 struct CommitArgs {
-    void *cache[MAX_CACHES_PER_LAUNCH];
-    const int32_t *prefix_len, *path, *accept_len;
     int32_t *prefix_len_out;
-    int32_t n_kv_heads, n_tree, path_stride, chunks_per_row, first_cache, heads_per_wg;
     int64_t s_max;
+    int32_t n_kv_heads, first_cache;
+    void *cache[MAX_CACHES_PER_LAUNCH];
 };
 
 // The chunks of a workgroup, N to a thread.  All path entries are asked for, then all chunks, without a condition (past the end: the last chunk again), since a load under a
 // condition is waited for where the condition ends: with one entry and its chunk after the other a thread made two trips to memory per chunk.
 // 16 sequences of 48 caches of 32 heads of 64: 11.5 -> 9.4 us, 8 of 96 of 16 of 256 18.7 -> 18.5; one sequence, one chunk a thread: no difference beside the launch.
 template <int N>
-__device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int total, int per_head, int cpr, int n_tree, int64_t head_stride)
+__device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int first_nodes, int total, int per_head, int cpr, int n_tree, int64_t head_stride)
 {
     const int tid = threadIdx.x;
     int32_t node[N];
@@ -43,7 +42,7 @@ __device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int 
         const int idx = min(tid + i * 256, total - 1);
         const int hl = idx / per_head, rest = idx - hl * per_head;
         const int j = rest / cpr, c = rest - j * cpr;
-        node[i] = path[j];
+        node[i] = per_head <= 64 * cpr ? __shfl(first_nodes, j) : path[j];
         from[i] = hl * head_stride + c;
     }
 #pragma unroll
@@ -61,32 +60,39 @@ __device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int 
     }
 }
 
-__global__ __launch_bounds__(256) void kv_commit_kernel(CommitArgs a)
+// One sequence is a chain of trips to memory: the plain arguments are in scalar registers when a wave starts, then what says which rows move (length, path, prefix, cache) is asked for
+// at once, then the rows.  Everything in one structure and the path behind the length were four trips: greedy acceptance and commit of one Gemma3 sequence 13.6 us, 14.2 so.
+__global__ __launch_bounds__(256) void kv_commit_kernel(const int32_t *accept_len, const int32_t *path, const int32_t *prefix_len, int path_stride, int n_tree, int chunks_per_row,
+                                                        int heads_per_wg, CommitArgs a)
 {
-    const int h0 = blockIdx.x * a.heads_per_wg, b = blockIdx.y, ci = blockIdx.z;
-    const int n_heads = min(a.heads_per_wg, a.n_kv_heads - h0);
-    const int tid = threadIdx.x;
-    const int P = (int)min((int64_t)max(a.prefix_len[b], 0), a.s_max - a.n_tree);
+    const int b = blockIdx.y, ci = blockIdx.z, tid = threadIdx.x;
+    path += (int64_t)b * path_stride;
+    const int first_nodes = path[min(tid & 63, path_stride - 1)];      // lane j: entry j
+    const int prefix = prefix_len[b], accepted = accept_len[b];
+    void *cache = a.cache[ci];
+    const int64_t s_max = a.s_max;
+    asm volatile("" ::"s"(prefix), "s"(accepted), "s"(cache), "s"(s_max), "s"(a.n_kv_heads), "s"(a.first_cache), "s"(a.prefix_len_out));
+    const int h0 = blockIdx.x * heads_per_wg, n_heads = min(heads_per_wg, a.n_kv_heads - h0);
+    const int P = (int)min((int64_t)max(prefix, 0), s_max - n_tree);
     // device metadata is trusted, but stay inside the tree rows whatever it holds
-    const int n = min(max(a.accept_len[b], 0), min(a.path_stride, a.n_tree) - 1);
+    const int n = min(max(accepted, 0), min(path_stride, n_tree) - 1);
     if (blockIdx.x == 0 && ci == 0 && a.first_cache == 0 && tid == 0 && a.prefix_len_out)
         a.prefix_len_out[b] = P + n + 1;
-    const int cpr = a.chunks_per_row;
+    const int cpr = chunks_per_row;
     const int per_head = (n + 1) * cpr;          // chunks of one head: destination rows 0..n of its tree area are contiguous
     const int total = n_heads * per_head;
-    const int64_t head_stride = a.s_max * cpr;   // chunks between the same row of consecutive heads
-    u32x4 *tree = reinterpret_cast<u32x4 *>(a.cache[ci]) + (((int64_t)b * a.n_kv_heads + h0) * a.s_max + P) * cpr;
-    const int32_t *path = a.path + (int64_t)b * a.path_stride;
+    const int64_t head_stride = s_max * cpr;   // chunks between the same row of consecutive heads
+    u32x4 *tree = reinterpret_cast<u32x4 *>(cache) + (((int64_t)b * a.n_kv_heads + h0) * s_max + P) * cpr;
     if (total <= 256)
-        move_rows<1>(tree, path, total, per_head, cpr, a.n_tree, head_stride);
+        move_rows<1>(tree, path, first_nodes, total, per_head, cpr, n_tree, head_stride);
     else if (total <= 512)
-        move_rows<2>(tree, path, total, per_head, cpr, a.n_tree, head_stride);
+        move_rows<2>(tree, path, first_nodes, total, per_head, cpr, n_tree, head_stride);
     else if (total <= 1024)
-        move_rows<4>(tree, path, total, per_head, cpr, a.n_tree, head_stride);
+        move_rows<4>(tree, path, first_nodes, total, per_head, cpr, n_tree, head_stride);
     else if (total <= 2048)
-        move_rows<8>(tree, path, total, per_head, cpr, a.n_tree, head_stride);
+        move_rows<8>(tree, path, first_nodes, total, per_head, cpr, n_tree, head_stride);
     else
-        move_rows<CHUNKS_PER_THREAD>(tree, path, total, per_head, cpr, a.n_tree, head_stride);
+        move_rows<CHUNKS_PER_THREAD>(tree, path, first_nodes, total, per_head, cpr, n_tree, head_stride);
 }
 
 }  // namespace
@@ -126,24 +132,23 @@ int dream_kv_commit(const dream_attn_desc *desc, void *const *caches_host, int32
             return fail(DREAM_ERR_INVALID_ARG, "%s: cache %d is not 16-byte aligned", who, i);
     }
     CommitArgs a;
-    a.prefix_len = prefix_len; a.path = accept_path; a.accept_len = accept_len; a.prefix_len_out = prefix_len_out;
-    a.n_kv_heads = desc->n_kv_heads; a.n_tree = n_tree; a.path_stride = path_stride;
-    a.chunks_per_row = (int)(row_bytes / 16); a.s_max = desc->s_max;
+    const int chunks_per_row = (int)(row_bytes / 16);
+    a.prefix_len_out = prefix_len_out; a.n_kv_heads = desc->n_kv_heads; a.s_max = desc->s_max;
     // heads per workgroup: as many as the registers of a workgroup hold, while about a thousand workgroups remain
-    const int64_t fit = (256 * CHUNKS_PER_THREAD) / (max_rows * a.chunks_per_row);
+    const int64_t fit = (256 * CHUNKS_PER_THREAD) / (max_rows * chunks_per_row);
     const int64_t spare = ((int64_t)desc->n_kv_heads * desc->batch * (n_caches < MAX_CACHES_PER_LAUNCH ? n_caches : MAX_CACHES_PER_LAUNCH)) / 1024;
     int64_t hpw = fit < spare ? fit : spare;
     if (hpw > desc->n_kv_heads)
         hpw = desc->n_kv_heads;
     if (hpw < 1)
         hpw = 1;
-    a.heads_per_wg = (int)hpw;
     for (int32_t first = 0; first < n_caches; first += MAX_CACHES_PER_LAUNCH) {
         const int m = n_caches - first < MAX_CACHES_PER_LAUNCH ? n_caches - first : MAX_CACHES_PER_LAUNCH;
         for (int i = 0; i < MAX_CACHES_PER_LAUNCH; i++)
             a.cache[i] = i < m ? caches_host[first + i] : nullptr;
         a.first_cache = first;
-        hipLaunchKernelGGL(kv_commit_kernel, dim3(ceil_div(desc->n_kv_heads, a.heads_per_wg), desc->batch, m), dim3(256), 0, as_stream(stream), a);
+        hipLaunchKernelGGL(kv_commit_kernel, dim3(ceil_div(desc->n_kv_heads, hpw), desc->batch, m), dim3(256), 0, as_stream(stream), accept_len, accept_path, prefix_len,
+                           path_stride, n_tree, chunks_per_row, (int)hpw, a);
         int rc = check_launch("kv_commit_kernel");
         if (rc)
             return rc;
