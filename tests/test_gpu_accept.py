@@ -176,3 +176,19 @@ def test_parent_array_with_cycles_still_terminates(gu):
     assert (am == 3).all() and 0 <= alen[0] <= 6 and bonus[0] == 3
     assert ((path >= -1) & (path < T)).all()
     assert alen[0] == 1 and path[0].tolist()[:2] == [0, 7]                  # only node 7 has a well-formed path
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 3, 5, 9, 17, 33, 65, 130])
+def test_chunks_merged_by_every_number_of_lanes(gu, chunks):
+    """1 to 64 lanes merge the chunks of a node (one of them has two or three of more than 64): the maximum in any chunk, and the same in a later one."""
+    T, vocab = max(3, min(chunks, 40)), 8192 * (chunks - 1) + 5
+    parent = di.random_tree(T, 4, 7)
+    logits = di.normal((1, T, vocab), "f32", 71 + chunks, di.STREAM_LOGITS)
+    token = np.zeros((1, T), dtype=np.int32)
+    for i in range(T):
+        at = (i * 7 + 3) % chunks
+        for ch in (at, chunks - 1):
+            logits[0, i, ch * 8192 + (i % 5)] = np.float32(9.0)
+        if i:
+            token[0, i] = (((parent[i] * 7 + 3) % chunks) * 8192 + parent[i] % 5 + (i % 3 == 2)) % vocab
+    _compare(gu, logits, "f32", token, parent[None], 4)
