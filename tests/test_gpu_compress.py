@@ -391,3 +391,17 @@ def test_selection_with_its_rows(gu, v, B, row_elems):
     assert np.array_equal(kept, want)
     for b in range(B):
         assert np.array_equal(rows[b], src[b][want[b]])
+
+
+@pytest.mark.parametrize("v", [1, 64, 65, 257, 600, 1088, 2047, 2048])
+@pytest.mark.parametrize("bit", [-1, 0, 3, 4, 11, 15, 20, 28, 31])
+def test_selection_from_the_first_bit_that_differs(gu, v, bit):
+    """Scores that agree in all bits above `bit` (-1: in all), kept shares from one token to all of them, ties at the cut."""
+    g = di.rng(91, 905, v * 64 + bit + 1)
+    low = g.integers(0, 1 << (bit + 1), size=v, dtype=np.int64) if bit >= 0 else np.zeros(v, dtype=np.int64)
+    low[::3] = low[0]
+    s = ((0x3f5a5a5a5a & ~((1 << (bit + 1)) - 1) | low) & 0xffffffff).astype(np.uint32).view(np.float32)[None]
+    s = np.nan_to_num(s, nan=0.5, posinf=3.0e38, neginf=-3.0e38)
+    for num, den in ((1, v), (1, 4), (2, 3), (1, 1)):
+        _, kept, _ = gu.run_compress("bf16", None, None, 0, 3, v, num, den, scores_in=s)
+        assert np.array_equal(kept, oracle.topk_keep(s.astype(np.float64), 3, num, den)), (num, den)
