@@ -918,6 +918,9 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     if (FIRST && (QS == 1 || qs < QS / 2))
         issue_k(kg, kg * G::STRIDE, (int)a.s_max);
 
+    // All other arguments, in the same trip to memory as the prefix length: those that stand behind the barrier below were asked for there, one or two trips ahead of the first scores.  us a launch,
+    // there / here: one LLaVA sequence 8.54 / 8.41, 1400 keys 11.9 / 11.5, two of 704 keys 10.4 / 10.1, four of 33 rows 11.6 / 11.2, four Gemma3 sequences of 33 rows 18.9 / 18.6, eight Pixtral ones 19.4 / 18.9.
+    asm volatile("" ::"s"(a.v), "s"(a.q_node), "s"(a.tree_mask), "s"(a.out), "s"(a.lse), "s"(a.include_self), "s"(a.turn), "s"(a.scale_log2));
     const int P = (int)min((int64_t)max(prefix, 0), a.s_max - a.n_tree);   // never past the cache, whatever the array holds
     const int kv_len = P + a.n_tree;
     const int t_end = (kv_len + KEYS - 1) / KEYS;
