@@ -145,18 +145,20 @@ constexpr int POLL_DELAY = 14;
 // z = 1: draft rows; nothing for nodes without children (a leaf's target row is summed by the walk if the walk ends there).
 template <bool BF16, int PER>
 __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits, const void *dlogits, int n_tree, int n_nodes, int vocab,
-                                                            int n_chunks, bool vec, const int32_t *parent, float inv_temp,
-                                                            float *stat_m, float *stat_s, uint64_t *slots)
+                                                            int n_chunks, int vec, const int32_t *parent, float inv_temp, float *stat_m, float *stat_s,
+                                                            uint64_t *slots, int64_t rows_all)
 {
     const int chunk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.y / n_nodes, node = blockIdx.y - b * n_nodes, which = blockIdx.z;
-    const int64_t node_row = (int64_t)b * n_tree + node, rows_all = (int64_t)(gridDim.y / n_nodes) * n_tree;
-    const int64_t slot = (which * rows_all + node_row) * n_chunks + chunk;
+    const int b = n_nodes == 1 ? blockIdx.y : blockIdx.y / n_nodes, node = blockIdx.y - b * n_nodes, which = blockIdx.z;
+    const int64_t node_row = (int64_t)b * n_tree + node;
     __shared__ float red[4];
-    if (slots && chunk == 0 && node == 0 && which == 0)
-        for (int i = tid; i < SLOTS; i += 256)
-            slots[(int64_t)b * SLOTS + i] = 0;
+    auto clear_slots = [&] {
+        if (slots && chunk == 0 && node == 0 && which == 0)
+            for (int i = tid; i < SLOTS; i += 256)
+                slots[(int64_t)b * SLOTS + i] = 0;
+    };
     if (n_nodes > 1) {           // (the root alone is not worth the trip to memory that tells whether it has children)
+        clear_slots();
         int kids = 0;
         for (int i = tid; i < n_tree; i += 256)
             kids |= parent[(int64_t)b * n_tree + i] == node;
@@ -180,6 +182,9 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const void *tlogits,
         for (int r = 0; r < STAT_CHUNK / 2048; r++)
             load8<BF16>(base, row, begin + (r * 256 + tid) * 8, vocab, vec, x + 8 * r);
     }
+    if (n_nodes == 1)            // (behind the loads: they wait for nothing that way)
+        clear_slots();
+    const int64_t slot = (which * rows_all + node_row) * n_chunks + chunk;
 #pragma unroll
     for (int j = 0; j < STAT_CHUNK / 256; j++) {
         x[j] *= inv_temp;
@@ -230,8 +235,8 @@ struct WalkArgs {
     const void *tlogits, *dlogits;
     int n_tree, vocab, n_chunks;
     int seg_chunks, n_seg;         // a row is n_seg <= MAX_SEG segments of seg_chunks chunks (one chunk up to 1048576 tokens)
-    bool vec;
-    bool lazy;                     // statistics of the roots only; the walk works out those of the nodes it comes to
+    int vec;                       // (whole words: a byte of one is taken from it as soon as the wave starts)
+    int lazy;                      // statistics of the roots only; the walk works out those of the nodes it comes to
     const int32_t *token, *parent;
     const float *u_accept, *u_bonus;
     int max_depth;
@@ -842,8 +847,13 @@ __global__ __launch_bounds__(NT) void spec_walk_kernel(WalkArgs a)
 // 4 x 60 x 262144 bf16 56.3 / 28.8, 32 x 60 x 32000 bf16 49.8 / 30.0, 1 x 60 x 32000 bf16 31.3 / 23.2, 16 x 60 x 131072 bf16 59.7 / 37.4.  (Workgroups of a sequence on one XCD: 40.6
 // instead of 37.5 before the first poll was put off.)
 template <bool BF16, int PER, bool VEC>
-__global__ __launch_bounds__(NT + 64) void spec_walk_small_kernel(WalkArgs a)
+__global__ __launch_bounds__(NT + 64) void spec_walk_small_kernel(const int32_t *parent, const int32_t *token, const float *u_accept, const float *u_draw, const void *tlogits, const void *dlogits,
+                                                                  int tree_nodes, int tokens, WalkArgs rest)
 {
+    // (Plain arguments: in scalar registers when a wave starts, so the first loads wait for nothing; all others are asked for at once.  With them in memory, the random numbers behind the
+    // tokens, and what softmax_stats_kernel reads behind what it clears, 4 sequences x 60 nodes x 131072 float32 25.1 to 25.8 us, 23.8 to 24.4 so.)
+    WalkArgs a = rest;
+    a.parent = parent; a.token = token; a.u_accept = u_accept; a.u_bonus = u_draw; a.tlogits = tlogits; a.dlogits = dlogits; a.n_tree = tree_nodes; a.vocab = tokens;
     __shared__ float s_part[2][MAX_VAL][MAX_SEG];
     __shared__ __attribute__((aligned(16))) float s_red[2][MAX_VAL][NW];
     __shared__ int s_missing[2];
@@ -903,9 +913,16 @@ __global__ __launch_bounds__(NT + 64) void spec_walk_small_kernel(WalkArgs a)
             r[h].unpack(v[h]);
     };
     const bool node = lane < n_tree;
-    int par_l = node ? a.parent[bt + lane] : -1;
-    const int tok_l = node ? min(max(a.token[bt + lane], 0), vocab - 1) : 0;     // device metadata is trusted but kept inside the row
-    const float u_l = node ? a.u_accept[bt + lane] : 0.0f, u_bonus = a.u_bonus[b];
+    // (all asked for at once: a load under a condition is waited for where the condition ends)
+    const int64_t own = bt + min(lane, n_tree - 1);
+    const int par_own = a.parent[own], tok_own = a.token[own];
+    const float u_own = a.u_accept[own], u_bonus = a.u_bonus[b];
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::"s"(u_bonus), "s"(a.n_seg), "s"(a.max_depth), "s"(a.inv_temp), "s"(a.spin_limit), "s"(a.stat_m), "s"(a.stat_s), "s"(a.slots), "s"(a.accept_len), "s"(a.accept_path),
+                 "s"(a.bonus_token));
+    int par_l = node ? par_own : -1;
+    const int tok_l = node ? min(max(tok_own, 0), vocab - 1) : 0;                // device metadata is trusted but kept inside the row
+    const float u_l = node ? u_own : 0.0f;
     par_l = lane > 0 && par_l >= 0 && par_l < lane ? par_l : -1;
     uint64_t kids = __ballot(par_l == 0);                   // children of the current node that have not been tried
     int asked = -1;                                         // the node whose rows were asked for last (where AHEAD)
@@ -1422,19 +1439,19 @@ int dream_spec_accept(const void *target_logits, const void *draft_logits, int32
     const bool lazy = small ? logit_bytes * n_tree >= 1200000000ll : logit_bytes >= 60000000 && logit_bytes * n_tree >= 3000000000ll;
     const int n_nodes = lazy ? 1 : n_tree;
     const dim3 sgrid(n_chunks, batch * n_nodes, 2);
-    const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec, lazy, token, parent, u_accept, u_bonus, max_depth,
+    const WalkArgs wa = {target_logits, draft_logits, n_tree, vocab, n_chunks, seg_chunks, n_seg, vec ? 1 : 0, lazy ? 1 : 0, token, parent, u_accept, u_bonus, max_depth,
                          inv_temp, accept_spin_limit(), stat_m, stat_s, slots, accept_len, accept_path, bonus_token};
     auto launch_all = [&](auto bf16, auto groups) {
         constexpr bool BF = decltype(bf16)::value;
         constexpr int PER = decltype(groups)::value;
-        hipLaunchKernelGGL((softmax_stats_kernel<BF, PER>), sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, n_nodes, vocab, n_chunks, vec,
-                           parent, inv_temp, stat_m, stat_s, slots);
+        hipLaunchKernelGGL((softmax_stats_kernel<BF, PER>), sgrid, dim3(256), 0, st, target_logits, draft_logits, n_tree, n_nodes, vocab, n_chunks, vec ? 1 : 0,
+                           parent, inv_temp, stat_m, stat_s, slots, (int64_t)batch * n_tree);
         if constexpr (PER <= 2) {
             if (small) {
                 if (vec)
-                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, true>), dim3(n_wg, batch), dim3(NT + 64), 0, st, wa);
+                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, true>), dim3(n_wg, batch), dim3(NT + 64), 0, st, parent, token, u_accept, u_bonus, target_logits, draft_logits, n_tree, vocab, wa);
                 else
-                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, false>), dim3(n_wg, batch), dim3(NT + 64), 0, st, wa);
+                    hipLaunchKernelGGL((spec_walk_small_kernel<BF, PER, false>), dim3(n_wg, batch), dim3(NT + 64), 0, st, parent, token, u_accept, u_bonus, target_logits, draft_logits, n_tree, vocab, wa);
                 return;
             }
         }
