@@ -245,9 +245,11 @@ __global__ __launch_bounds__(256) void expand_partial_kernel(const void *logits,
 // holds (1, 2, 4 or 8).  Latency bound: every load of a row is issued before the first result is needed, and four waves share a
 // SIMD, so instructions count: k rounds of a wave arg-max over all candidates, one lane writing, took 6.1 us at 10 rows and k = 10, ranking the
 // few above a bound of the k-th 4.5 (one row 4.2 -> 3.5; drafting 6 levels: LLaVA 233 -> 223 us, 8 SmolVLM sequences 273 -> 263).
+// bound: ceil(k / chunks) and, from bit 8 on, ceil(k / that), which were divisions ahead of the loads; with up to 64 chunks one load of their sums a lane instead of eight conditions: drafts 202.5 -> 200.5
+// and 231.9 -> 229.6 us.
 template <int PART>
 __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *part_m, const float *part_s, const uint64_t *part_key,
-                                                                  int n_frontier, int n_chunks, int k, const float *cum_in,
+                                                                  int n_frontier, int n_chunks, int k, int bound, const float *cum_in,
                                                                   int32_t *cand_token, float *cand_score, int32_t *next_frontier)
 {
     __shared__ uint64_t s_key[MAX_F * MAX_K];   // (score, flat index) keys of the level's candidates
@@ -263,28 +265,42 @@ __global__ __launch_bounds__(64 * MAX_F) void expand_merge_kernel(const float *p
 #pragma unroll
         for (int j = 0; j < PART; j++)
             pk[j] = lane + j * 64 < n_part ? part_key[row * n_part + lane + j * 64] : 0ull;
-        const int depth = (k + n_chunks - 1) / n_chunks, q = (k + depth - 1) / depth;
+        const int depth = bound & 0xff, q = bound >> 8;       // ceil(k / chunks), ceil(k / depth)
         // A few rounds cost less than the bound, whose chunks are counted one by one.  us, a level of 1 row / 10 rows, rounds and bound: 262144 tokens, k = 1 6.9 and 8.6 / 8.7 and
         // 10.8, k = 4 8.1 and 8.9 / 9.6 and 10.1; 131072 tokens, 10 rows, k = 1 7.7 and 8.7, k = 3 9.0 and 9.3, k = 4 9.3 and 9.3; 32000 tokens, 10 rows, k = 2 8.4 and 8.6, k = 3 9.0 and 8.7.
         const bool bounded = n_chunks <= 64 && k > 2 + n_chunks / 16;
         const uint64_t deep = bounded && lane < n_chunks ? part_key[row * n_part + lane * k + depth - 1] : 0ull;
         // log-sum-exp of the row from the chunk partials (8 per lane: with k = 1 there may be 512 chunks)
         float M = -INFINITY, cm[8], cs[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const int ch = lane + j * 64;
-            cm[j] = ch < n_chunks ? part_m[row * n_chunks + ch] : -INFINITY;
-            cs[j] = ch < n_chunks ? part_s[row * n_chunks + ch] : 0.0f;
-        }
         const float cum = cum_in[row];
+        const bool many = n_chunks > 64;
+        cm[0] = lane < n_chunks ? part_m[row * n_chunks + lane] : -INFINITY;
+        cs[0] = lane < n_chunks ? part_s[row * n_chunks + lane] : 0.0f;
+#pragma unroll
+        for (int j = 1; j < 8; j++) {
+            cm[j] = -INFINITY;
+            cs[j] = 0.0f;
+        }
+        if (many) {
+#pragma unroll
+            for (int j = 1; j < 8; j++) {
+                const int ch = min(lane + j * 64, n_chunks - 1);
+                cm[j] = part_m[row * n_chunks + ch];
+                cs[j] = part_s[row * n_chunks + ch];
+            }
+#pragma unroll
+            for (int j = 1; j < 8; j++)
+                cm[j] = lane + j * 64 < n_chunks ? cm[j] : -INFINITY;
+        }
 #pragma unroll
         for (int j = 0; j < 8; j++)
             M = fmaxf(M, cm[j]);
         M = wave_max(M);
-        float S = 0.0f;
+        float S = cm[0] == -INFINITY ? 0.0f : cs[0] * __expf(cm[0] - M);
+        if (many)
 #pragma unroll
-        for (int j = 0; j < 8; j++)
-            S += cm[j] == -INFINITY ? 0.0f : cs[j] * __expf(cm[j] - M);
+            for (int j = 1; j < 8; j++)
+                S += cm[j] == -INFINITY ? 0.0f : cs[j] * __expf(cm[j] - M);
         S = wave_sum(S);
         const float lse = M + __logf(S);
         auto emit = [&](int r, uint64_t best) {
@@ -501,7 +517,8 @@ int dream_tree_expand_level(const void *logits, int32_t logits_dtype, int32_t ba
         return rc;
     const int n_part = p.n_chunks * k;
     auto merge = n_part <= 64 ? expand_merge_kernel<1> : n_part <= 128 ? expand_merge_kernel<2> : n_part <= 256 ? expand_merge_kernel<4> : expand_merge_kernel<8>;
-    hipLaunchKernelGGL(merge, dim3(batch), dim3(64 * n_frontier), 0, st, pm, ps, pkey, n_frontier, p.n_chunks, k, cum_in, cand_token, cand_score, next_frontier);
+    const int depth = ceil_div(k, p.n_chunks), bound = depth | ceil_div(k, depth) << 8;
+    hipLaunchKernelGGL(merge, dim3(batch), dim3(64 * n_frontier), 0, st, pm, ps, pkey, n_frontier, p.n_chunks, k, bound, cum_in, cand_token, cand_score, next_frontier);
     return check_launch("expand_merge_kernel");
 }
 
