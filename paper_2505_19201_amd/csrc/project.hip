@@ -7,10 +7,10 @@
 // streaming the weights once from HBM.  One workgroup owns 16 output features (16 weight rows, contiguous in
 // memory); its 4 waves split the hidden dimension, each computing C^T[n][m] += W[n][k] X[m][k] with
 // v_mfma_f32_16x16x32_bf16 (A = weight rows, B = feature rows).  With at most 16 feature rows (the paper's
-// shapes) a wave fetches 256 contiguous bytes of each row at a time and passes them through a private LDS area
+// shapes) and more feature tiles than two per CU a wave fetches 256 contiguous bytes of each row at a time and passes them through a private LDS area
 // to reach the operand layout: nobody else reads those bytes, but an operand-layout load touches 16 rows x 64
-// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows project_rows_kernel (below)
-// is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
+// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows or fewer tiles project_rows_kernel
+// (below) is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
 // Roofline: HBM, N*hidden*2 weight bytes per call.  The weights are loaded without the nontemporal hint: the next level
 // reads them again, and what the memory-side cache has kept of them by then is worth more than the hint (drafting 6 levels:
 // LLaVA 243 -> 237 us, 8 SmolVLM sequences 285 -> 279; a single call on cold weights is 0-3 us faster but for LLaVA at 10
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(PROJ_PARAMS)
     }
 }
 
-// More than 16 feature rows.  Every workgroup reads all of them (from L2) beside its own weight rows, so what bounds the
+// More than 16 feature rows, or few feature tiles.  Every workgroup reads all of the rows (from L2) beside its own weight rows, so what bounds the
 // call is feature rows + weight rows per workgroup times workgroups per CU (a CU pulls 60 to 75 GB/s): a workgroup owns NT tiles of 16 output
 // features and MT tiles of 16 rows (up to 128 rows per pass), and the launch picks NT for the fewest bytes through the
 // busiest CU.  The hidden dimension is dealt to the 8 waves in steps of 64 elements, 1024 contiguous bytes of every row for the eight;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(64 * NWAVE) void project_kernel(PROJ_PARAMS)
 // Measured per call of three maps (Q, K, V), shared stages / here: 80 rows SmolVLM 11.4 / 10.3 us, LLaVA 40.9 / 40.0, Pixtral 27.1 / 27.3, 40 rows
 // 9.1 / 7.2, 30.4 / 28.4, 21.0 / 20.3 with the weights in HBM; as much of them as the memory-side cache kept from the level before, 80 rows LLaVA
 // 34.7 / 28.1, Pixtral 21.9 / 19.1, 20 rows LLaVA 25.3 / 18.0.  Whole drafts of 6 levels are 4 to 12 % faster, the expansion's share included.
-// At 10 rows project_kernel and this one are equal within 5 % but for LLaVA (warm 16.5 against 18.0).
+// Which calls of up to 16 rows take this one: see dream_project_rows_multi.
 constexpr int RW = 8;                                // waves per workgroup
 constexpr int STEP = 64, STEP_BYTES = STEP * 2;      // elements, bytes of a row per step
 constexpr int TILE_BYTES = 16 * STEP_BYTES;
