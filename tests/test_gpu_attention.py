@@ -252,32 +252,57 @@ def test_swapped_steps(gu, kv_len):
     assert np.abs(lse - want_lse).max() <= 2e-3
 
 
-# one sequence and several ragged ones, two, four and one slices, one and more query tiles of several heads: batch, heads, KV heads, head_dim, rows, keys of a step of all waves
-TURNED = [(1, 32, 32, 128, 60, 128), (3, 32, 8, 128, 17, 128), (1, 32, 8, 128, 17, 256), (2, 32, 32, 64, 33, 256), (1, 16, 8, 256, 60, 128), (3, 16, 8, 256, 17, 128), (3, 16, 8, 256, 33, 128)]
+# one sequence and several ragged ones, two, four and one slices, one and more query tiles of several heads: batch, heads, KV heads, head_dim, rows, kernel,
+# kv_lens (steps of all waves are 128 or 256 keys).  A last round of the order with one step, whole ones, the ragged end and the tree in a tile that is taken early; where the kernel serves ranges that long, three rounds.
+TURNED = [
+    (1, 32, 32, 128, 60, "attn_wave_kernel<128,8,2,1>", (128, 129, 256, 640, 1025, 1152, 1153, 1320)),
+    (3, 32, 8, 128, 17, "attn_wave_kernel<128,8,2,1>", (128, 129, 256, 640, 1025, 1152, 1153, 1320, 2049)),
+    (1, 32, 8, 128, 17, "attn_wave_kernel<128,8,4,1>", (256, 257, 512, 1025, 1280)),
+    (2, 32, 32, 64, 33, "attn_wave_kernel<64,8,1,1>", (256, 257, 512, 1280, 2049, 2304)),
+    (1, 16, 8, 256, 60, "attn_wave_kernel<256,4,4,1>", (128, 129, 256, 640, 1025, 1152, 1153, 1320)),
+    (3, 16, 8, 256, 17, "attn_wave_kernel<256,8,4,2>", (128, 129, 256, 640, 1025, 1152, 1153, 1320)),
+    (3, 16, 8, 256, 33, "attn_wave_kernel<256,8,4,3>", (128, 129, 256, 640, 1025, 1152, 1153, 1320)),
+]
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D,T,step", TURNED)
-def test_turned_steps(gu, B, Hq, Hkv, D, T, step):
-    """Workgroups that take their steps in turned order: one to three rounds of steps behind the first, whole and not, a last round of one step, the tree and the ragged end in a
-    tile that is taken early; an explicit mask; keys on both sides of the line up to which the order is taken."""
-    per_key = -(-B * Hkv // 8) * D * 4                       # bytes of an XCD's heads
-    line = 6000000 // per_key
-    for kv_len in [n * step + more for n, more in ((1, 0), (1, 1), (2, 0), (5, 0), (8, 1), (9, 0), (9, 1), (10, 40), (16, 1))] + [line - 1, line]:
+def _compare_verify(gu, x, parent=None, **kw):
+    oracle.set_threads(16)
+    try:
+        got, lse = gu.run_verify(x, **kw)
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent if parent is None else parent, True)
+    finally:
+        oracle.set_threads(1)
+    assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,kernel,kv_lens", TURNED)
+def test_turned_steps(gu, B, Hq, Hkv, D, T, kernel, kv_lens):
+    """Workgroups that take their steps in turned order, the mask derived from the parents and an explicit one."""
+    for kv_len in kv_lens:
         cfg = _cfg("turn", "bf16", B, Hq, Hkv, D, kv_len - T, 0, T, min(5, T - 1), 54)
         x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) * (3 - b) // 3 for b in range(B)])
-        if not gu.verify_plan(x).startswith("attn_wave_kernel"):
-            continue
-        oracle.set_threads(16)
-        try:
-            got, lse = gu.run_verify(x)
-            want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
-            assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3, kv_len
-        finally:
-            oracle.set_threads(1)
-    star = di.star_tree(T)
-    got, _ = gu.run_verify(x, tree_mask=np.stack([di.ancestor_mask_bits(star, True)[:, 0]] * B))
-    want, _ = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, np.stack([star] * B), True)
-    assert np.abs(got - want).max() <= TOL["bf16"]
+        assert gu.verify_plan(x).split(" ")[0] == kernel, (kv_len, gu.verify_plan(x))
+        _compare_verify(gu, x)
+        if kv_len in kv_lens[-2:]:
+            star = di.star_tree(T)
+            _compare_verify(gu, x, parent=np.stack([star] * B), tree_mask=np.stack([di.ancestor_mask_bits(star, True)[:, 0]] * B))
+
+
+# verifications of three workgroups to a KV head or more, the last kv_len below 6 MB of keys and values an XCD: up to there the order is turned, above it is not and the caches are read with
+# the nontemporal hint (but in four slices)
+LINE = [(5, 16, 16, 64, 33, "attn_wave_kernel<64,8,1,1>", 2343), (5, 24, 8, 128, 17, "attn_wave_kernel<128,8,1,1>", 2343), (2, 32, 32, 128, 17, "attn_wave_kernel<128,8,2,1>", 1464),
+        (2, 32, 32, 128, 10, "attn_wave_kernel<128,8,4,1>", 1464), (9, 8, 8, 256, 33, "attn_wave_kernel<256,4,1,1>", 651), (6, 8, 8, 256, 17, "attn_wave_kernel<256,4,2,1>", 976),
+        (3, 16, 8, 256, 33, "attn_wave_kernel<256,8,4,3>", 1953)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,kernel,line", LINE)
+def test_both_sides_of_the_turned_order(gu, B, Hq, Hkv, D, T, kernel, line):
+    for kv_len in (line, line + 1):
+        assert (-(-B * Hkv // 8) * kv_len * D * 4 < 6000000) == (kv_len == line)
+        cfg = _cfg("line", "bf16", B, Hq, Hkv, D, kv_len - T, 0, T, min(5, T - 1), 58)
+        x = di.verify_inputs(cfg, prefix_len=[(kv_len - T) * (B - b) // B for b in range(B)])
+        assert gu.verify_plan(x).split(" ")[0] == kernel, (kv_len, gu.verify_plan(x))
+        _compare_verify(gu, x)
 
 
 @pytest.mark.parametrize("kv_len", [300, 513, 1024, 1300])
