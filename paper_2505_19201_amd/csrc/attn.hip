@@ -814,6 +814,11 @@ __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHe
     return a;
 }
 
+// How a launch reads its tiles, each a form of the kernel of its own: in the order of the keys, the same with the nontemporal hint (AttnArgs::once), or in turned order
+// (RowsGeom::TURNED, AttnArgs::turn).  (With the turn a number that may be zero, every step of a launch in the order of the keys worked out its place for nothing: drafting, 10 rows of 32 on 8 heads of 128,
+// 4 sequences of 1283 keys 9.7 us, 9.2 so, 900 keys 8.2 and 7.9.)
+enum { READ_PLAIN, READ_ONCE, READ_TURNED };
+
 template <int N>
 __device__ __forceinline__ void wait_loads()   // until at most N of this wave's loads are in flight
 {
@@ -848,10 +853,12 @@ __device__ __forceinline__ void slots_meet(uint32_t meet, int wave, int count)
     asm volatile("" ::: "memory");
 }
 
-template <int D, int DS, int QT, int QS, int KG, int KEYS, bool ONCE>
+template <int D, int DS, int QT, int QS, int KG, int KEYS, int FORM>
 __device__ __forceinline__ void attend_rows(const AttnArgs &a)
 {
     using G = RowsGeom<D, DS, QT, QS, KG, KEYS>;
+    constexpr bool ONCE = FORM == READ_ONCE, TURNED = FORM == READ_TURNED;
+    static_assert(!TURNED || G::TURNED, "a form of its own for the order that this geometry has");
     constexpr int KROW = G::KROW, VROW = G::VROW, NW = G::NW, NDT = G::NDT, NKS = G::NKS, NH = G::NH, NK = G::NK, NV = G::NV, TILES_Q = QS * QT;
     constexpr int LPK = KROW / 16, LPV = VROW / 16;                // lanes per row of a load
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -967,11 +974,11 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
             issue_v(t, at + G::KTILE);
     };
     const int n_steps = (max(t_end - kg, 0) + KG - 1) / KG;
-    const int odd = G::SWAPPED && a.turn ? unit & 1 : 0, turned = G::TURNED ? (int)((unit * a.turn) >> 16) : 0;
+    const int odd = G::SWAPPED && a.turn ? unit & 1 : 0, turned = TURNED ? (int)((unit * a.turn) >> 16) : 0;
     auto tile = [&](int i) {                  // the key tile of this wave's step i
         if (G::SWAPPED)
             i = (i | 1) < n_steps ? i ^ odd : i;
-        return kg + KG * (G::TURNED ? turned_step(i, n_steps, turned) : i);
+        return kg + KG * (TURNED ? turned_step(i, n_steps, turned) : i);
     };
     const bool early = QS == 1 && kg >= QT;   // the second K stage holds no queries
     const uint32_t meet = lds0 + G::MEET_OFF;
@@ -1316,26 +1323,25 @@ using PairGeom = RowsGeom<D, DS, QT, 2, 4, D == 256 ? 16 : 32>;
 template <int D, int DS, int QT>
 using QuadGeom = RowsGeom<D, DS, QT, 4, 2, D == 256 ? 16 : 32>;
 
-// ONCE: the loads of whole tiles carry the nontemporal hint (see AttnArgs::once)
 // one query slot: NW key groups of one wave, QT query tiles and one of DS column slices a workgroup
-template <int D, int NW, int DS, int QT, bool ONCE>
+template <int D, int NW, int DS, int QT, int FORM>
 __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), ONCE>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), FORM>(ROWS_ARGUMENTS);
 }
 
 // two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
-template <int D, int DS, int QT, bool ONCE>
+template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_pair_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, ONCE>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
 }
 
 // four query slots: 2 key groups of four waves, 4 * QT query tiles a workgroup
-template <int D, int DS, int QT, bool ONCE>
+template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_quad_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, ONCE>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1809,14 +1815,18 @@ int launch_bf16(const AttnArgs &a, const Plan &p, hipStream_t st)
     return check_launch("attn_merge_kernel");
 }
 
+template <class G>
+constexpr bool has_hint(int slices) { return slices != 4 && !G::SWAPPED; }
+
 template <int D, int NW, int DS, int QT>
 int ensure_wave_lds()
 {
-    static std::atomic<uint64_t> done[2];
-    constexpr size_t bytes = WaveGeom<D, NW, DS, QT>::BYTES;
-    constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
-    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, false>), bytes, "attention");
-    return rc || !hinted ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), bytes, "attention");
+    using G = WaveGeom<D, NW, DS, QT>;
+    constexpr int hinted = has_hint<G>(DS) ? READ_ONCE : READ_PLAIN, turned = G::TURNED ? READ_TURNED : READ_PLAIN;     // (the plain form again where there is no such form)
+    static std::atomic<uint64_t> done[3];
+    int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, READ_PLAIN>), G::BYTES, "attention");
+    rc = rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), G::BYTES, "attention");
+    return rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, turned>), G::BYTES, "attention");
 }
 
 #define ROWS_OF(a) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
@@ -1832,12 +1842,14 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_wave_lds<D, NW, DS, QT>())
         return rc;
+    using G = WaveGeom<D, NW, DS, QT>;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, QT) * DS);
-    constexpr bool hinted = DS != 4 && !WaveGeom<D, NW, DS, QT>::SWAPPED;
-    if (hinted && a.once)
-        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, hinted>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, ROWS_OF(a));
-    else
-        hipLaunchKernelGGL((attn_wave_kernel<D, NW, DS, QT, false>), grid, dim3(64 * NW), (WaveGeom<D, NW, DS, QT>::BYTES), st, ROWS_OF(a));
+    auto *kernel = &attn_wave_kernel<D, NW, DS, QT, READ_PLAIN>;
+    if constexpr (has_hint<G>(DS))
+        kernel = a.once ? &attn_wave_kernel<D, NW, DS, QT, READ_ONCE> : kernel;
+    if constexpr (G::TURNED)
+        kernel = a.turn ? &attn_wave_kernel<D, NW, DS, QT, READ_TURNED> : kernel;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), G::BYTES, st, ROWS_OF(a));
     return check_launch("attn_wave_kernel");
 }
 
@@ -1846,8 +1858,8 @@ int ensure_pair_lds()
 {
     static std::atomic<uint64_t> done[2];
     constexpr size_t bytes = PairGeom<D, DS, QT>::BYTES;
-    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, false>), bytes, "attention");
-    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, true>), bytes, "attention");
+    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_PLAIN>), bytes, "attention");
+    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_ONCE>), bytes, "attention");
 }
 
 template <int D, int DS, int QT>
@@ -1857,9 +1869,9 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 2 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, true>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     else
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, false>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     return check_launch("attn_pair_kernel");
 }
 
@@ -1868,8 +1880,8 @@ int ensure_quad_lds()
 {
     static std::atomic<uint64_t> done[2];
     constexpr size_t bytes = QuadGeom<D, DS, QT>::BYTES;
-    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, false>), bytes, "attention");
-    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, true>), bytes, "attention");
+    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_PLAIN>), bytes, "attention");
+    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_ONCE>), bytes, "attention");
 }
 
 template <int D, int DS, int QT>
@@ -1879,9 +1891,9 @@ int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 4 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, true>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     else
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, false>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
     return check_launch("attn_quad_kernel");
 }
 
