@@ -754,6 +754,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 template <int D, int DS, int QT, int QS, int KG, int KEYS>
 struct RowsGeom {
     static constexpr int DV = D / DS, KROW = D * 2, VROW = DV * 2, NW = QS * KG;   // bytes of a K row, of a V slice's row; waves
+    static constexpr int STEP_KEYS = KG * KEYS;                                    // keys of a step of all key groups
     static constexpr int KTILE = KEYS * KROW, VTILE = KEYS * VROW, NK = KTILE / 1024, NV = VTILE / 1024;   // bytes and 16-byte loads per lane of a tile
     static constexpr int NDT = DV / 16, NKS = D / 32, NH = KEYS / 16;              // column tiles, key steps, 16-key halves
     static constexpr int UNIT = QT * NDT * 1024, QTILE = 16 * KROW;                // bytes of a wave's outputs, of a query tile
@@ -792,9 +793,10 @@ struct RowsHead {
     const int32_t *prefix_len;
     const void *q, *k;
     const int32_t *parent;   // null: there is a mask
-    uint32_t heads, rows;    // n_kv_heads + 2^16 * group, n_q + 2^16 * n_tree
+    uint32_t heads, rows;    // n_kv_heads + 2^16 * group (+ FIRST_KEYS_EARLY), n_q + 2^16 * n_tree
     uint32_t spread, nq_magic, s_max, n_streams;
 };
+constexpr uint32_t FIRST_KEYS_EARLY = 1u << 31;      // the launch asks for every wave's first keys before the prefix length is known (attend_rows)
 #define ROWS_PARAMETERS const int32_t *prefix_len, const void *q, const void *k, const int32_t *parent, uint32_t heads, uint32_t rows, uint32_t spread, uint32_t nq_magic, uint32_t s_max, uint32_t n_streams, AttnArgs rest
 #define ROWS_ARGUMENTS with_head(rest, {prefix_len, q, k, parent, heads, rows, spread, nq_magic, s_max, n_streams})
 __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHead &h)
@@ -803,7 +805,7 @@ __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHe
     a.prefix_len = h.prefix_len;
     a.q = h.q; a.k = h.k; a.parent = h.parent;
     a.n_kv_heads = (int)(h.heads & 0xffff);
-    a.group = (int)(h.heads >> 16);
+    a.group = (int)(h.heads >> 16 & 0x7fff);
     a.n_q_heads = a.n_kv_heads * a.group;
     a.n_q = (int)(h.rows & 0xffff);
     a.n_tree = (int)(h.rows >> 16);
@@ -854,7 +856,7 @@ __device__ __forceinline__ void slots_meet(uint32_t meet, int wave, int count)
 }
 
 template <int D, int DS, int QT, int QS, int KG, int KEYS, int FORM>
-__device__ __forceinline__ void attend_rows(const AttnArgs &a)
+__device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
 {
     using G = RowsGeom<D, DS, QT, QS, KG, KEYS>;
     constexpr bool ONCE = FORM == READ_ONCE, TURNED = FORM == READ_TURNED;
@@ -904,7 +906,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
     const int half = G::LOADERS == 2 ? qs & 1 : 0, k_half = half * (KJ * (64 / LPK)), v_half = half * (VJ * (64 / LPV));
     const int krow = lane / LPK, vrow = lane / LPV;
     const int kl = piece_k<KROW>(lane) ^ (half * swizzle_k<KROW>(KJ)), vl = piece_v<VROW>(lane) ^ (half * swizzle_v<VROW>(VJ));
-    // (`rows`: the live ones, or those of the cache)
+    // (`rows`: the live ones, or more than the tile needs)
     auto issue_k = [&](int t, int at, int rows) {
         const uint32_t dst = scalar(lds0 + at + half * (KJ * 1024));
         if ((t + 1) * KEYS <= rows) {
@@ -919,11 +921,13 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
                 lds_load16(kbase, (uint32_t)(min(t * KEYS + k_half + j * (64 / LPK) + krow, rows - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
         }
     };
-    // Every wave's first keys are asked for before it is known how many there are: any row of the cache may be read, and a score behind the last live one is masked (a value is
-    // multiplied with its zero, so those wait).  us a launch, behind the prefix length / ahead of it: one LLaVA sequence 8.36 / 8.14, 250 keys 5.94 / 5.73, one Gemma3 sequence 15.25 / 14.99, twelve 27.9 / 27.9.
-    constexpr bool FIRST = !G::SWAPPED;
-    if (FIRST && (QS == 1 || qs < QS / 2))
-        issue_k(kg, kg * G::STRIDE, (int)a.s_max);
+    // Every wave's first keys are asked for before it is known how many there are, where max_kv_len covers the first step of all waves: the rows below it may be read whatever they hold, and a
+    // score behind the last live one is masked (a value is multiplied with its zero, so those wait).  us a launch, behind the prefix length / ahead of it: one LLaVA sequence 8.36 / 8.14, 250 keys
+    // 5.94 / 5.73, one Gemma3 sequence 15.25 / 14.99, twelve 27.9 / 27.9.  With a shorter range waves that have no keys would pull rows that nobody needs, and be waited for: 10 rows of 32 heads of 128,
+    // 58 keys 4.00 / 4.15.  (A sequence shorter than the step beside longer ones, or under a max_kv_len that is far above: 3 sequences of 54 keys, 39 rows of 32 on 8 heads of 128, 5.01 / 5.23.)
+    const bool first = !G::SWAPPED && keys_early, first_mine = first && (QS == 1 || qs < QS / 2);
+    if (first_mine)
+        issue_k(kg, kg * G::STRIDE, 1 << 30);
 
     // All other arguments, in the same trip to memory as the prefix length: those that stand behind the barrier below were asked for there, one or two trips ahead of the first scores.  us a launch,
     // there / here: one LLaVA sequence 8.54 / 8.41, 1400 keys 11.9 / 11.5, two of 704 keys 10.4 / 10.1, four of 33 rows 11.6 / 11.2, four Gemma3 sequences of 33 rows 18.9 / 18.6, eight Pixtral ones 19.4 / 18.9.
@@ -988,11 +992,11 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         if constexpr (QS > 1) {
 #pragma unroll
             for (int i = 0; i < G::EARLY; i++)
-                if (i < n_steps && (i > 0 || qs >= QS / 2))
+                if (i < n_steps && (i > 0 || !first_mine))
                     issue_slot(t + i * KG, ktile + i * G::GROUP);
             wait_steps(min(n_steps, G::EARLY));   // the queries and parents are there; the first tiles stay in flight
         } else {
-            if (!FIRST)
+            if (!first)
                 issue_k(tile(0), ktile, kv_len);
             issue_v(tile(0), vtile);
             if (early && n_steps > 1) {
@@ -1002,6 +1006,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
                 wait_loads<NK + NV>();
             }
         }
+    } else if (first_mine) {
+        wait_loads<KJ>();               // (a wave without keys: what it asked for all the same is waited for behind the masks)
     } else {
         wait_loads<0>();
     }
@@ -1045,6 +1051,8 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a)
         }
         masks[lane] = mk;
     }
+    if (n_steps == 0)
+        wait_loads<0>();
     wave_lds_fence();
 
     f32x4 o[QT][NDT];
@@ -1327,21 +1335,21 @@ using QuadGeom = RowsGeom<D, DS, QT, 4, 2, D == 256 ? 16 : 32>;
 template <int D, int NW, int DS, int QT, int FORM>
 __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), FORM>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
 }
 
 // two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
 template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_pair_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
 }
 
 // four query slots: 2 key groups of four waves, 4 * QT query tiles a workgroup
 template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_quad_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
+    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1483,6 +1491,7 @@ struct Plan {
     int wave_ds;      // workgroups that share the output columns of a query tile in that mode (1, 2 or 4)
     int wave_qt;      // query tiles per wave in that mode
     int slots;        // query slots of a workgroup in that mode: 1, 2 (attn_pair_kernel) or 4 (attn_quad_kernel)
+    int64_t max_kv_len;
     size_t state_floats, off_part, total;
 };
 
@@ -1603,6 +1612,7 @@ bool make_wave_plan(const dream_attn_desc *d, int n_q, int64_t max_kv_len, bool 
     p->state_floats = 0;
     p->off_part = DREAM_WORKSPACE_MIN_BYTES;
     p->total = DREAM_WORKSPACE_MIN_BYTES;
+    p->max_kv_len = max_kv_len;
     return true;
 }
 
@@ -1829,7 +1839,8 @@ int ensure_wave_lds()
     return rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, turned>), G::BYTES, "attention");
 }
 
-#define ROWS_OF(a) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
+// (`keys`: those of the first step of all key groups; RowsHead::heads says whether the launch has that many)
+#define ROWS_OF(a, keys) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16 | (p.max_kv_len >= (keys) ? FIRST_KEYS_EARLY : 0u), (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
 
 // `per_head` workgroups for every KV head of every sequence, as attend_rows reads them
 dim3 stream_grid(const AttnArgs &a, int per_head)
@@ -1849,7 +1860,7 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
         kernel = a.once ? &attn_wave_kernel<D, NW, DS, QT, READ_ONCE> : kernel;
     if constexpr (G::TURNED)
         kernel = a.turn ? &attn_wave_kernel<D, NW, DS, QT, READ_TURNED> : kernel;
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), G::BYTES, st, ROWS_OF(a));
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), G::BYTES, st, ROWS_OF(a, G::STEP_KEYS));
     return check_launch("attn_wave_kernel");
 }
 
@@ -1869,9 +1880,9 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 2 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (PairGeom<D, DS, QT>::STEP_KEYS)));
     else
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (PairGeom<D, DS, QT>::STEP_KEYS)));
     return check_launch("attn_pair_kernel");
 }
 
@@ -1891,9 +1902,9 @@ int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
         return rc;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 4 * QT) * DS);
     if (a.once)
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (QuadGeom<D, DS, QT>::STEP_KEYS)));
     else
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a));
+        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (QuadGeom<D, DS, QT>::STEP_KEYS)));
     return check_launch("attn_quad_kernel");
 }
 

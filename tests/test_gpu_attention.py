@@ -305,6 +305,32 @@ def test_both_sides_of_the_turned_order(gu, B, Hq, Hkv, D, T, kernel, line):
         _compare_verify(gu, x)
 
 
+SINGLE_LAUNCH = [c for c in VARIANT_CASES if "bf16" not in c.variant]
+
+
+@pytest.mark.parametrize("case", SINGLE_LAUNCH, ids=[c.variant for c in SINGLE_LAUNCH])
+@pytest.mark.parametrize("bound", [70, 127, 128, 129, 255, 256, 300])
+def test_rows_behind_the_last_live_one_hold_anything(gu, case, bound):
+    """NaN in every row of the caches behind the live ones, which the kernels may ask for before they know how many are live: max_kv_len on both sides of the first step of all waves
+    (128 or 256 keys), sequences that end in it, without a prefix too, a capacity above."""
+    prefix = [max(bound - case.n_tree, 0), 0, 9, max(bound - case.n_tree, 0) // 2] * case.batch
+    cfg = _cfg("dead", "bf16", case.batch, case.n_q_heads, case.n_kv_heads, case.head_dim, 0, 0, case.n_tree, case.depth, 57)
+    x = di.verify_inputs(cfg, prefix_len=prefix[:case.batch], slack_rows=200)
+    assert gu.verify_plan(x).startswith(("attn_wave", "attn_pair", "attn_quad")), gu.verify_plan(x)
+    dev = gu.DeviceAttn(x)
+    for b in range(case.batch):
+        for cache in (dev.k, dev.v):
+            cache[b, :, int(x.prefix_len[b]) + case.n_tree:] = float("nan")
+    oracle.set_threads(16)
+    try:
+        want, want_lse = oracle.tree_attn(x.q, x.k, x.v, "bf16", x.prefix_len, x.parent, True)
+    finally:
+        oracle.set_threads(1)
+    for dev.max_kv in (dev.max_kv, x.s_max):
+        got, lse = gu.run_verify(x, dev=dev)
+        assert np.abs(got - want).max() <= TOL["bf16"] and np.abs(lse - want_lse).max() <= 2e-3
+
+
 @pytest.mark.parametrize("kv_len", [300, 513, 1024, 1300])
 @pytest.mark.parametrize("B,T", [(2, 17), (3, 9)])
 def test_swapped_steps_of_ragged_sequences_under_a_mask(gu, B, T, kv_len):
