@@ -199,7 +199,14 @@ __global__ __launch_bounds__(WALK) void accept_walk_kernel(const uint64_t *part,
                 const uint64_t o = part[(bt + i) * n_chunks + ch];
                 best[u] = o > best[u] ? o : best[u];
             }
-            best[u] = max_of_lanes(best[u], lanes);
+        }
+        if (lanes > 1)
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                best[u] = max_of_lanes(best[u], lanes);
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int i = i0 + u * per_pass;
             if (i < n_tree && sub == 0) {
                 const int idx = (int)(0xffffffffu - (uint32_t)best[u]);
                 s_am[i] = idx;
