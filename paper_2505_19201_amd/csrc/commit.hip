@@ -34,7 +34,7 @@ template <int N>
 __device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int first_nodes, int total, int per_head, int cpr, int n_tree, int64_t head_stride)
 {
     const int tid = threadIdx.x;
-    int32_t node[N];
+    int32_t node[N], at[N];
     int64_t from[N];
     u32x4 r[N];
 #pragma unroll
@@ -42,8 +42,17 @@ __device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int 
         const int idx = min(tid + i * 256, total - 1);
         const int hl = idx / per_head, rest = idx - hl * per_head;
         const int j = rest / cpr, c = rest - j * cpr;
-        node[i] = per_head <= 64 * cpr ? __shfl(first_nodes, j) : path[j];
+        at[i] = j;
         from[i] = hl * head_stride + c;
+    }
+    if (per_head <= 64 * cpr) {
+#pragma unroll
+        for (int i = 0; i < N; i++)
+            node[i] = __shfl(first_nodes, at[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i++)
+            node[i] = path[at[i]];
     }
 #pragma unroll
     for (int i = 0; i < N; i++)
@@ -75,7 +84,7 @@ __global__ __launch_bounds__(256) void kv_commit_kernel(const int32_t *accept_le
     const int h0 = blockIdx.x * heads_per_wg, n_heads = min(heads_per_wg, a.n_kv_heads - h0);
     const int P = (int)min((int64_t)max(prefix, 0), s_max - n_tree);
     // device metadata is trusted, but stay inside the tree rows whatever it holds
-    const int n = min(max(accepted, 0), min(path_stride, n_tree) - 1);
+    const int n = __builtin_amdgcn_readfirstlane(min(max(accepted, 0), min(path_stride, n_tree) - 1));
     if (blockIdx.x == 0 && ci == 0 && a.first_cache == 0 && tid == 0 && a.prefix_len_out)
         a.prefix_len_out[b] = P + n + 1;
     const int cpr = chunks_per_row;
