@@ -7,10 +7,10 @@
 // streaming the weights once from HBM.  One workgroup owns 16 output features (16 weight rows, contiguous in
 // memory); its 4 waves split the hidden dimension, each computing C^T[n][m] += W[n][k] X[m][k] with
 // v_mfma_f32_16x16x32_bf16 (A = weight rows, B = feature rows).  With at most 16 feature rows (the paper's
-// shapes) and more feature tiles than two per CU a wave fetches 256 contiguous bytes of each row at a time and passes them through a private LDS area
+// shapes) a wave fetches 256 contiguous bytes of each row at a time and passes them through a private LDS area
 // to reach the operand layout: nobody else reads those bytes, but an operand-layout load touches 16 rows x 64
-// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows or fewer tiles project_rows_kernel
-// (below) is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
+// bytes per instruction, half cache lines, and measures 10-13 % slower.  With more rows, and where its eight waves serve fewer rows better (few feature tiles:
+// dream_project_rows_multi has the lines), project_rows_kernel (below) is used.  The partial tiles are summed through LDS in wave order and the rows are rounded to bf16 and scattered.
 // Roofline: HBM, N*hidden*2 weight bytes per call.  The weights are loaded without the nontemporal hint: the next level
 // reads them again, and what the memory-side cache has kept of them by then is worth more than the hint (drafting 6 levels:
 // LLaVA 243 -> 237 us, 8 SmolVLM sequences 285 -> 279; a single call on cold weights is 0-3 us faster but for LLaVA at 10
@@ -22,7 +22,7 @@ using namespace dream;
 
 namespace {
 
-constexpr int NWAVE = 4;   // (8 waves measured 5-8 % slower on the narrower maps, 2 no faster)
+constexpr int NWAVE = 4;   // of project_kernel (8 waves of this kernel measured 5-8 % slower on the narrower maps, 2 no faster)
 
 struct ProjJob {
     const uint16_t *x;
@@ -468,18 +468,21 @@ int dream_project_rows_multi(const dream_attn_desc *desc, const dream_proj_job *
     a.n_rows = n_rows; l.m_and_lack = m_total; l.hidden = hidden; a.head_dim = desc->head_dim;
     a.s_max = desc->s_max;
     hipStream_t st = as_stream(stream);
-    // Up to 16 rows: where a workgroup per CU holds the feature tiles, one each or two, the eight waves of project_rows_kernel, which pull a row once for both; above, where workgroups share
-    // CUs unevenly, the smaller ones of project_kernel, and for two tiles also with rows 8 KB apart, whose pieces sit in few channels.  us, project_kernel / project_rows_kernel, weights in
-    // the memory-side cache and in HBM: 10 rows, 8 tiles of hidden dimension 768 4.0 / 3.3 and 4.1 / 3.4, 128 of 3840 5.0 / 4.6 and 6.1 / 5.6, 256 of 4096 5.9 / 5.7 and 7.0 / 6.7;
+    // Up to 16 rows: where there are no more feature tiles than CUs, the eight waves of project_rows_kernel, one tile a workgroup; up to twice as many, two tiles, which pull a row once for both,
+    // from 9 rows on and from a hidden dimension of 2048 on, where rows count in what is pulled and eight waves have steps enough, but not with rows a multiple of 8 KB apart, whose pieces sit in few channels;
+    // else, and above, where workgroups share CUs unevenly, the smaller workgroups of project_kernel.  us, project_kernel / project_rows_kernel, weights in the memory-side cache and in HBM: 10 rows,
+    // 8 tiles of hidden dimension 768 4.0 / 3.3 and 4.1 / 3.4, 128 of 3840 5.0 / 4.6 and 6.1 / 5.6, 256 of 4096 5.9 / 5.7 and 7.0 / 6.7;
     // two tiles: 384 of 5120 (Pixtral, three maps) 11.7 / 10.8 and 15.4 / 14.1, 512 of 3840 (Gemma3) 11.5 / 10.8 and 12.7 / 11.9, 384 of 2048 4.9 / 4.7 and 6.1 / 6.0, but
-    // 384 of 4096 7.6 / 9.1 and 11.1 / 12.2, 512 of 4096 11.5 / 11.2 and 13.2 / 16.8, 768 of 4096 (LLaVA) 16.2 / 16.4 and 19.6 / 23.6.  One row: the same, the gains smaller.
-    const int tiles_16 = tiles <= 256 ? 1 : tiles <= 512 && hidden % 4096 ? 2 : 0;
+    // 384 of 4096 7.6 / 9.1 and 11.1 / 12.2, 512 of 4096 11.5 / 11.2 and 13.2 / 16.8, 768 of 4096 (LLaVA) 16.2 / 16.4 and 19.6 / 23.6.  Two tiles on the other side of the lines, 257 to 512 tiles of nine hidden
+    // dimensions, project_rows_kernel over project_kernel in the mean: hidden 512 and 1024, 10 rows 1.09 and 1.04; from 2048 on, 1 row 1.01 and 1.02, 5 rows 0.98 and 0.99, 10 rows 0.95 and 0.96, 16 rows 0.90 and 0.91
+    // (what is left of a loss at 10 rows: 512 of 5120 14.2 / 14.8 and 17.8 / 17.1).
+    const int tiles_16 = tiles <= 256 ? 1 : tiles <= 512 && m_total > 8 && hidden >= 2048 && hidden % 4096 ? 2 : 0;
     if (m_total <= 16 && tiles_16 == 0) {
         auto *kernel = m_total > 12 ? &project_kernel<4> : m_total > 8 ? &project_kernel<3> : m_total > 4 ? &project_kernel<2> : &project_kernel<1>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * NWAVE), 0, st, l.w[0], l.w[1], l.w[2], l.w[3], l.end[0], l.end[1], l.end[2], l.end[3], hidden, l.m_and_lack, a);
         return check_launch("project_kernel");
     }
-    // Row tiles per pass (2 to 8: there are at least 17 rows), feature tiles per workgroup and how many workgroups share the rows of a feature tile: the fewest bytes
+    // Row tiles per pass (1 for up to 16 rows, else 2 to 8), feature tiles per workgroup and how many workgroups share the rows of a feature tile: the fewest bytes
     // through the busiest CU.  Up to 128 rows are one pass; above, a workgroup goes through as few passes as there have to be, of about equal size, or every pass is a workgroup of its
     // own, which leaves fewer CUs idle and reads weights that another pass has brought to L2.  us, one after the other / side by side: LLaVA 256 rows 72.3 / 53.8 (weights in HBM 84.2 / 66.0),
     // 144 rows 50.1 / 40.3, 1000 rows 266 / 205; SmolVLM 192 rows 19.3 / 17.3, 1000 rows 83.8 / 66.6; hidden dimension 768, 1000 rows 32.7 / 16.4.

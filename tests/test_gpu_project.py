@@ -142,15 +142,15 @@ def test_passes_side_by_side(gu, R, hidden, Hq, Hkv, D):
 
 
 @pytest.mark.parametrize("R", [1, 4, 5, 8, 9, 12, 13, 16])
-@pytest.mark.parametrize("hidden,tiles", [(256, 1), (768, 256), (1280, 257), (768, 511), (768, 513), (4096, 258)])
+@pytest.mark.parametrize("hidden,tiles", [(256, 1), (768, 256), (1280, 257), (768, 511), (768, 513), (4096, 258), (2048, 257), (2304, 511), (2304, 513), (1792, 300)])
 def test_up_to_sixteen_rows(gu, R, hidden, tiles):
-    """Both kernels on both sides of the lines between them (256 and 512 feature tiles, rows a multiple of 8 KB apart), one to four pieces of rows, a workgroup with one tile of two,
-    a wave whose share of the hidden dimension ends in half a step."""
+    """Both kernels on both sides of the lines between them (256 and 512 feature tiles, 8 rows, a hidden dimension of 2048, rows a multiple of 8 KB apart), one to four pieces of rows, a
+    workgroup with one tile of two, a wave whose share of the hidden dimension ends in half a step."""
     x, w = _inputs(1, R, hidden, tiles, 16, 150 + R)
     _close(gu.run_project(x, w, tiles, 16), oracle.project(x, w, "bf16", tiles, 16))
 
 
-@pytest.mark.parametrize("hidden,Hq,Hkv", [(512, 7, 3), (512, 151, 55), (512, 255, 129), (512, 171, 171)])
+@pytest.mark.parametrize("hidden,Hq,Hkv", [(512, 7, 3), (512, 151, 55), (512, 255, 129), (512, 171, 171), (2048, 151, 55), (2048, 255, 129), (2048, 171, 171)])
 def test_maps_of_odd_widths_in_one_launch(gu, hidden, Hq, Hkv):
     """Every map's last workgroup has one feature tile of two, and none writes into another map."""
     B, R, D = 1, 10, 16
@@ -167,3 +167,37 @@ def test_maps_of_odd_widths_in_one_launch(gu, hidden, Hq, Hkv):
         keep = np.ones(40, dtype=bool)
         keep[rows] = False
         assert np.array_equal(got[0][:, keep], cache[0][:, keep].view(np.int16))
+
+
+@pytest.mark.parametrize("hidden,R,tiles", [(512, 8, (31, 17, 5, 9)), (512, 2, (99, 101, 55, 77)), (512, 8, (299, 101, 85, 77)), (2048, 5, (99, 101, 55, 77)), (256, 10, (99, 1, 55, 77)),
+                                            (256, 10, (199, 188, 170, 181)), (256, 130, (199, 188, 170, 181))])
+def test_four_maps_in_one_launch(gu, hidden, R, tiles):
+    """As many maps as a call takes, dense and into caches in turn, some rows outside the cache: one feature tile a workgroup, the small workgroups, two tiles and three, where the last
+    workgroup of a map lacks one or two; several passes over the rows."""
+    import torch
+    import paper_2505_19201_amd as dream
+    B, D, s_max = 2, 16, 300
+    xs = [di.normal((B, R, hidden), "bf16", 501 + i, di.STREAM_ROWS) for i in range(4)]
+    ws = [di.f32_to_bf16_bits(di.normal((t * D, hidden), "f32", 511 + i, di.STREAM_ROWS) * np.float32(hidden ** -0.5)) for i, t in enumerate(tiles)]
+    base = np.array([7, 160], dtype=np.int32)
+    index = np.stack([di.rng(520 + b, 800).permutation(s_max)[:R] for b in range(B)]).astype(np.int32)    # (some past the end, behind the base)
+    place = [None, base[:, None] + np.arange(R)[None], None, base[:, None] + index]
+    rb, ri = dream.to_device(base), dream.to_device(index)
+    fill = 1024.0             # (results are about 1: no row that was written holds it)
+    outs = [torch.full((B, R, t, D) if i % 2 == 0 else (B, t, s_max, D), fill, dtype=torch.bfloat16, device="cuda") for i, t in enumerate(tiles)]
+    jobs = [(dream.to_device(xs[i], "bf16"), dream.to_device(ws[i], "bf16"), t, rb if i % 2 else None, ri if i == 3 else None, outs[i]) for i, t in enumerate(tiles)]
+    dream.dream_project_rows_multi(dream.attn_desc(B, 1, 1, D, dream.BF16, s_max), jobs, R, hidden)
+    torch.cuda.synchronize()
+    for i, t in enumerate(tiles):
+        want = oracle.project(xs[i], ws[i], "bf16", t, D)
+        got = gu.out_to_f64(outs[i])
+        if i % 2 == 0:
+            _close(got, want)
+            continue
+        full = np.full(got.shape, fill)
+        for b in range(B):
+            for r in range(R):
+                if 0 <= place[i][b, r] < s_max:
+                    full[b, :, place[i][b, r]] = want[b, r]
+        _close(got, full)
+        assert np.array_equal(got == fill, full == fill)
