@@ -18,8 +18,10 @@ Prints ONE JSON line.
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -41,27 +43,39 @@ def verify_bytes_per_launch(cfg) -> int:
     return 2 * cfg.batch * cfg.n_kv_heads * S * cfg.head_dim * e + 2 * cfg.batch * cfg.n_q_heads * cfg.n_tree * cfg.head_dim * e
 
 
+def attention_sources() -> str:
+    """Hash of what the attention kernels are compiled from: their sources without comments and blanks, and the compiler's flags.  A kernel keeps its name and its template arguments
+    when it comes to read its tiles in another order or with another cache hint."""
+    from paper_2505_19201_amd import build
+    csrc = os.path.join(ROOT, "paper_2505_19201_amd", "csrc")
+    h = hashlib.sha256(" ".join(f for f in build.HIPCC_FLAGS if not f.startswith("-I")).encode())
+    for name in ("attn.hip", "common.h", "lds_tiles.h", "sizes.h"):
+        with open(os.path.join(csrc, name)) as f:
+            h.update("".join(re.sub(r"//[^\n]*|/\*.*?\*/", "", f.read(), flags=re.S).split()).encode())
+    return h.hexdigest()[:16]
+
+
 def read_traffic(name: str, plan: str):
     """HBM traffic per launch of the verification kernel, from the committed summary of the two rocprofv3 --pmc runs
     (FETCH_SIZE, WRITE_SIZE; counters cannot be read from inside this process).  Returns (bytes or None, where the
     figure comes from: file, the kernel it was measured on and the date of that measurement).  A figure measured on
-    another kernel than the one the launch plan names now is stale: it is dropped and the source says so."""
+    another kernel than the one the launch plan names now, or on one built from other sources, is stale: it is dropped
+    and the source says so."""
     rel = os.path.join("profiles", f"attn_verify_{name}_traffic.txt")
-    traffic, kernel, date = None, "?", "?"
+    field = {}
     try:
-        for line in open(os.path.join(ROOT, rel)):
-            key, _, val = line.partition(":")
-            if key == "traffic_bytes_per_launch":
-                traffic = float(val)
-            elif key == "kernel":
-                kernel = val.strip()
-            elif key == "measured":
-                date = val.strip()
+        with open(os.path.join(ROOT, rel)) as f:
+            for line in f:
+                key, _, val = line.partition(":")
+                field[key] = val.strip()
     except OSError:
         return None, "no rocprofv3 summary committed for this configuration"
+    kernel, date = field.get("kernel", "?"), field.get("measured", "?")
     if kernel != plan.split(" ")[0]:
         return None, f"{rel} is stale: measured on {kernel} ({date}), the plan now names {plan.split(' ')[0]}"
-    return traffic, f"{rel} (rocprofv3 --pmc FETCH_SIZE/WRITE_SIZE, kernel {kernel}, measured {date})"
+    if field.get("sources") != attention_sources():
+        return None, f"{rel} is stale: measured on {kernel} as it was on {date}, its sources have changed since"
+    return float(field["traffic_bytes_per_launch"]), f"{rel} (rocprofv3 --pmc FETCH_SIZE/WRITE_SIZE, kernel {kernel}, measured {date})"
 
 
 def main() -> int:
