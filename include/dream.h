@@ -88,8 +88,8 @@ typedef struct {
  *              replaces the mask derived from `parent` (node i sees itself and its ancestors).
  *   max_kv_len host-known upper bound of P_b + n_tree over the batch (<= s_max); only used to
  *              choose the launch shape, pass s_max if unknown.
- *              Rows of a cache behind the last live one may be read too (up to s_max in float32; K rows
- *              below max_kv_len in bf16) and may hold anything: the results do not depend on them.
+ *              Rows of a cache behind the last live one may be read too (all are below s_max) and may
+ *              hold anything: the results do not depend on them.
  *   out        [B, n_tree, Hq, D]   same dtype as q
  *   lse        nullable, [B, Hq, n_tree] float32: natural-log sum of exp of the scaled scores.
  * Node i attends keys {0..P_b-1} and {P_b + a : a visible to i}.  n_tree in [1, DREAM_MAX_TREE].

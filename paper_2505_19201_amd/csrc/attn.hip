@@ -793,10 +793,9 @@ struct RowsHead {
     const int32_t *prefix_len;
     const void *q, *k;
     const int32_t *parent;   // null: there is a mask
-    uint32_t heads, rows;    // n_kv_heads + 2^16 * group (+ FIRST_KEYS_EARLY), n_q + 2^16 * n_tree
+    uint32_t heads, rows;    // n_kv_heads + 2^16 * group, n_q + 2^16 * n_tree
     uint32_t spread, nq_magic, s_max, n_streams;
 };
-constexpr uint32_t FIRST_KEYS_EARLY = 1u << 31;      // the launch asks for every wave's first keys before the prefix length is known (attend_rows)
 #define ROWS_PARAMETERS const int32_t *prefix_len, const void *q, const void *k, const int32_t *parent, uint32_t heads, uint32_t rows, uint32_t spread, uint32_t nq_magic, uint32_t s_max, uint32_t n_streams, AttnArgs rest
 #define ROWS_ARGUMENTS with_head(rest, {prefix_len, q, k, parent, heads, rows, spread, nq_magic, s_max, n_streams})
 __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHead &h)
@@ -805,7 +804,7 @@ __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHe
     a.prefix_len = h.prefix_len;
     a.q = h.q; a.k = h.k; a.parent = h.parent;
     a.n_kv_heads = (int)(h.heads & 0xffff);
-    a.group = (int)(h.heads >> 16 & 0x7fff);
+    a.group = (int)(h.heads >> 16);
     a.n_q_heads = a.n_kv_heads * a.group;
     a.n_q = (int)(h.rows & 0xffff);
     a.n_tree = (int)(h.rows >> 16);
@@ -816,10 +815,10 @@ __device__ __forceinline__ AttnArgs with_head(const AttnArgs &rest, const RowsHe
     return a;
 }
 
-// How a launch reads its tiles, each a form of the kernel of its own: in the order of the keys, the same with the nontemporal hint (AttnArgs::once), or in turned order
-// (RowsGeom::TURNED, AttnArgs::turn).  (With the turn a number that may be zero, every step of a launch in the order of the keys worked out its place for nothing: drafting, 10 rows of 32 on 8 heads of 128,
+// How a launch reads its tiles, each a form of the kernel of its own: in the order of the keys, the same with the nontemporal hint (AttnArgs::once), in turned order
+// (RowsGeom::TURNED, AttnArgs::turn), or in the order of the keys with nothing asked for before it is known how many there are (short_range()).  (With the turn a number that may be zero, every step of a launch in the order of the keys worked out its place for nothing: drafting, 10 rows of 32 on 8 heads of 128,
 // 4 sequences of 1283 keys 9.7 us, 9.2 so, 900 keys 8.2 and 7.9.)
-enum { READ_PLAIN, READ_ONCE, READ_TURNED };
+enum { READ_PLAIN, READ_ONCE, READ_TURNED, READ_SHORT };
 
 template <int N>
 __device__ __forceinline__ void wait_loads()   // until at most N of this wave's loads are in flight
@@ -856,7 +855,7 @@ __device__ __forceinline__ void slots_meet(uint32_t meet, int wave, int count)
 }
 
 template <int D, int DS, int QT, int QS, int KG, int KEYS, int FORM>
-__device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
+__device__ __forceinline__ void attend_rows(const AttnArgs &a)
 {
     using G = RowsGeom<D, DS, QT, QS, KG, KEYS>;
     constexpr bool ONCE = FORM == READ_ONCE, TURNED = FORM == READ_TURNED;
@@ -906,7 +905,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
     const int half = G::LOADERS == 2 ? qs & 1 : 0, k_half = half * (KJ * (64 / LPK)), v_half = half * (VJ * (64 / LPV));
     const int krow = lane / LPK, vrow = lane / LPV;
     const int kl = piece_k<KROW>(lane) ^ (half * swizzle_k<KROW>(KJ)), vl = piece_v<VROW>(lane) ^ (half * swizzle_v<VROW>(VJ));
-    // (`rows`: the live ones, or more than the tile needs)
+    // (`rows`: the live ones, or those of the cache)
     auto issue_k = [&](int t, int at, int rows) {
         const uint32_t dst = scalar(lds0 + at + half * (KJ * 1024));
         if ((t + 1) * KEYS <= rows) {
@@ -921,13 +920,14 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
                 lds_load16(kbase, (uint32_t)(min(t * KEYS + k_half + j * (64 / LPK) + krow, rows - 1) * KROW + (kl ^ swizzle_k<KROW>(j))), dst + j * 1024);
         }
     };
-    // Every wave's first keys are asked for before it is known how many there are, where max_kv_len covers the first step of all waves: the rows below it may be read whatever they hold, and a
-    // score behind the last live one is masked (a value is multiplied with its zero, so those wait).  us a launch, behind the prefix length / ahead of it: one LLaVA sequence 8.36 / 8.14, 250 keys
-    // 5.94 / 5.73, one Gemma3 sequence 15.25 / 14.99, twelve 27.9 / 27.9.  With a shorter range waves that have no keys would pull rows that nobody needs, and be waited for: 10 rows of 32 heads of 128,
-    // 58 keys 4.00 / 4.15.  (A sequence shorter than the step beside longer ones, or under a max_kv_len that is far above: 3 sequences of 54 keys, 39 rows of 32 on 8 heads of 128, 5.01 / 5.23.)
-    const bool first = !G::SWAPPED && keys_early, first_mine = first && (QS == 1 || qs < QS / 2);
+    // Every wave's first keys are asked for before it is known how many there are: any row of the cache may be read, whatever it holds, and a score behind the last live one is masked (a value is
+    // multiplied with its zero, so those wait).  us a launch, behind the prefix length / ahead of it: one LLaVA sequence 8.36 / 8.14, 250 keys 5.94 / 5.73, one Gemma3 sequence 15.25 / 14.99,
+    // twelve 27.9 / 27.9.  Not in short ranges: see short_range().
+    // (With 1 << 30 rows, which leaves the compiler no branch here, one LLaVA sequence 8.37 instead of 8.18: the other arguments are then asked for ahead of these loads.)
+    constexpr bool FIRST = !G::SWAPPED && FORM != READ_SHORT;
+    const bool first_mine = FIRST && (QS == 1 || qs < QS / 2);
     if (first_mine)
-        issue_k(kg, kg * G::STRIDE, 1 << 30);
+        issue_k(kg, kg * G::STRIDE, (int)a.s_max);
 
     // All other arguments, in the same trip to memory as the prefix length: those that stand behind the barrier below were asked for there, one or two trips ahead of the first scores.  us a launch,
     // there / here: one LLaVA sequence 8.54 / 8.41, 1400 keys 11.9 / 11.5, two of 704 keys 10.4 / 10.1, four of 33 rows 11.6 / 11.2, four Gemma3 sequences of 33 rows 18.9 / 18.6, eight Pixtral ones 19.4 / 18.9.
@@ -996,7 +996,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
                     issue_slot(t + i * KG, ktile + i * G::GROUP);
             wait_steps(min(n_steps, G::EARLY));   // the queries and parents are there; the first tiles stay in flight
         } else {
-            if (!first)
+            if (!FIRST)
                 issue_k(tile(0), ktile, kv_len);
             issue_v(tile(0), vtile);
             if (early && n_steps > 1) {
@@ -1007,7 +1007,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
             }
         }
     } else if (first_mine) {
-        wait_loads<KJ>();               // (a wave without keys: what it asked for all the same is waited for behind the masks)
+        wait_loads<KJ>();               // (a wave without keys: what it asked for all the same is waited for ahead of the states)
     } else {
         wait_loads<0>();
     }
@@ -1051,8 +1051,6 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
         }
         masks[lane] = mk;
     }
-    if (n_steps == 0)
-        wait_loads<0>();
     wave_lds_fence();
 
     f32x4 o[QT][NDT];
@@ -1208,6 +1206,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
             ktile = G::NS == 2 ? before : i % G::NS ? ktile + G::GROUP : kg * G::STRIDE;
             before = x;
         }
+        wait_loads<0>();                           // (of a wave without keys)
         wait_lds();
         slots_meet<QS>(meet, wave, n_steps + 1);   // (the tiles are nobody's any more)
     } else {
@@ -1242,6 +1241,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs &a, bool keys_early)
             ktile = ktile2;
             ktile2 = x;
         }
+        wait_loads<0>();                           // (of a wave without keys)
     }
 
     // ---- the key groups' states meet: every wave leaves its outputs, references and sums where its own tiles were, and takes its share of
@@ -1335,21 +1335,21 @@ using QuadGeom = RowsGeom<D, DS, QT, 4, 2, D == 256 ? 16 : 32>;
 template <int D, int NW, int DS, int QT, int FORM>
 __global__ __launch_bounds__(64 * NW) void attn_wave_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
+    attend_rows<D, DS, QT, 1, NW, wave_keys<D, NW, DS>(), FORM>(ROWS_ARGUMENTS);
 }
 
 // two query slots: 4 key groups of two waves, 2 * QT query tiles a workgroup
 template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_pair_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
+    attend_rows<D, DS, QT, 2, 4, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
 }
 
 // four query slots: 2 key groups of four waves, 4 * QT query tiles a workgroup
 template <int D, int DS, int QT, int FORM>
 __global__ __launch_bounds__(512) void attn_quad_kernel(ROWS_PARAMETERS)
 {
-    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS, (heads & FIRST_KEYS_EARLY) != 0);
+    attend_rows<D, DS, QT, 4, 2, D == 256 ? 16 : 32, FORM>(ROWS_ARGUMENTS);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1832,15 +1832,23 @@ template <int D, int NW, int DS, int QT>
 int ensure_wave_lds()
 {
     using G = WaveGeom<D, NW, DS, QT>;
-    constexpr int hinted = has_hint<G>(DS) ? READ_ONCE : READ_PLAIN, turned = G::TURNED ? READ_TURNED : READ_PLAIN;     // (the plain form again where there is no such form)
-    static std::atomic<uint64_t> done[3];
+    constexpr int hinted = has_hint<G>(DS) ? READ_ONCE : READ_PLAIN, turned = G::TURNED ? READ_TURNED : READ_PLAIN, brief = G::SWAPPED ? READ_PLAIN : READ_SHORT;     // (the plain form again where there is no such form)
+    static std::atomic<uint64_t> done[4];
     int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, READ_PLAIN>), G::BYTES, "attention");
     rc = rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, hinted>), G::BYTES, "attention");
-    return rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, turned>), G::BYTES, "attention");
+    rc = rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, turned>), G::BYTES, "attention");
+    return rc ? rc : raise_lds_limit(done[3], reinterpret_cast<const void *>(&attn_wave_kernel<D, NW, DS, QT, brief>), G::BYTES, "attention");
 }
 
-// (`keys`: those of the first step of all key groups; RowsHead::heads says whether the launch has that many)
-#define ROWS_OF(a, keys) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16 | (p.max_kv_len >= (keys) ? FIRST_KEYS_EARLY : 0u), (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
+#define ROWS_OF(a) a.prefix_len, a.q, a.k, a.tree_mask ? nullptr : a.parent, (uint32_t)a.n_kv_heads | (uint32_t)a.group << 16, (uint32_t)a.n_q | (uint32_t)a.n_tree << 16, a.spread, a.nq_magic, (uint32_t)a.s_max, (uint32_t)a.n_streams, a
+
+// With few keys most waves of the first step have none, and would pull rows that nobody needs: from three quarters of a step on they are asked for before it is known how many there are.
+// us a launch, asked for behind the prefix length / ahead of it, steps of 256 keys: 2 sequences of 16 heads of 128, 18 rows, 104 keys 4.17 / 4.44, 170 keys 4.41 / 4.54, 200 keys 4.54 / 4.56, 240 keys 4.58 / 4.49,
+// 3 sequences of 32 heads of 64, 17 rows, 170 keys 4.73 / 4.66, 200 keys 4.95 / 4.69; steps of 128: 4 sequences of 32 heads of 128, 60 rows, 64 keys 6.06 / 6.44, 96 keys 6.64 / 6.78, 104 keys 6.70 / 6.64,
+// 120 keys 7.02 / 6.88; 33 rows 64 keys 5.59 / 5.94, 120 keys 6.37 / 6.53, 190 keys 7.13 / 6.88.
+// (A sequence of fewer keys beside longer ones, or under a max_kv_len far above its length, still pays: 3 of 54 keys, 39 rows of 32 on 8 heads of 128, max_kv_len 1500, 5.01 / 5.23.)
+template <class G>
+bool short_range(const Plan &p) { return p.max_kv_len * 4 < G::STEP_KEYS * 3; }
 
 // `per_head` workgroups for every KV head of every sequence, as attend_rows reads them
 dim3 stream_grid(const AttnArgs &a, int per_head)
@@ -1860,17 +1868,20 @@ int launch_wave(const AttnArgs &a, const Plan &p, hipStream_t st)
         kernel = a.once ? &attn_wave_kernel<D, NW, DS, QT, READ_ONCE> : kernel;
     if constexpr (G::TURNED)
         kernel = a.turn ? &attn_wave_kernel<D, NW, DS, QT, READ_TURNED> : kernel;
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), G::BYTES, st, ROWS_OF(a, G::STEP_KEYS));
+    if constexpr (!G::SWAPPED)
+        kernel = short_range<G>(p) ? &attn_wave_kernel<D, NW, DS, QT, READ_SHORT> : kernel;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), G::BYTES, st, ROWS_OF(a));
     return check_launch("attn_wave_kernel");
 }
 
 template <int D, int DS, int QT>
 int ensure_pair_lds()
 {
-    static std::atomic<uint64_t> done[2];
-    constexpr size_t bytes = PairGeom<D, DS, QT>::BYTES;
-    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_PLAIN>), bytes, "attention");
-    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_ONCE>), bytes, "attention");
+    using G = PairGeom<D, DS, QT>;
+    static std::atomic<uint64_t> done[3];
+    int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_PLAIN>), G::BYTES, "attention");
+    rc = rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_ONCE>), G::BYTES, "attention");
+    return rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_pair_kernel<D, DS, QT, READ_SHORT>), G::BYTES, "attention");
 }
 
 template <int D, int DS, int QT>
@@ -1878,21 +1889,21 @@ int launch_pair(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_pair_lds<D, DS, QT>())
         return rc;
+    using G = PairGeom<D, DS, QT>;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 2 * QT) * DS);
-    if (a.once)
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (PairGeom<D, DS, QT>::STEP_KEYS)));
-    else
-        hipLaunchKernelGGL((attn_pair_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (PairGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (PairGeom<D, DS, QT>::STEP_KEYS)));
+    auto *kernel = short_range<G>(p) ? &attn_pair_kernel<D, DS, QT, READ_SHORT> : a.once ? &attn_pair_kernel<D, DS, QT, READ_ONCE> : &attn_pair_kernel<D, DS, QT, READ_PLAIN>;
+    hipLaunchKernelGGL(kernel, grid, dim3(512), G::BYTES, st, ROWS_OF(a));
     return check_launch("attn_pair_kernel");
 }
 
 template <int D, int DS, int QT>
 int ensure_quad_lds()
 {
-    static std::atomic<uint64_t> done[2];
-    constexpr size_t bytes = QuadGeom<D, DS, QT>::BYTES;
-    const int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_PLAIN>), bytes, "attention");
-    return rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_ONCE>), bytes, "attention");
+    using G = QuadGeom<D, DS, QT>;
+    static std::atomic<uint64_t> done[3];
+    int rc = raise_lds_limit(done[0], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_PLAIN>), G::BYTES, "attention");
+    rc = rc ? rc : raise_lds_limit(done[1], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_ONCE>), G::BYTES, "attention");
+    return rc ? rc : raise_lds_limit(done[2], reinterpret_cast<const void *>(&attn_quad_kernel<D, DS, QT, READ_SHORT>), G::BYTES, "attention");
 }
 
 template <int D, int DS, int QT>
@@ -1900,11 +1911,10 @@ int launch_quad(const AttnArgs &a, const Plan &p, hipStream_t st)
 {
     if (int rc = ensure_quad_lds<D, DS, QT>())
         return rc;
+    using G = QuadGeom<D, DS, QT>;
     const dim3 grid = stream_grid(a, ceil_div(a.n_qg, 4 * QT) * DS);
-    if (a.once)
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_ONCE>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (QuadGeom<D, DS, QT>::STEP_KEYS)));
-    else
-        hipLaunchKernelGGL((attn_quad_kernel<D, DS, QT, READ_PLAIN>), grid, dim3(512), (QuadGeom<D, DS, QT>::BYTES), st, ROWS_OF(a, (QuadGeom<D, DS, QT>::STEP_KEYS)));
+    auto *kernel = short_range<G>(p) ? &attn_quad_kernel<D, DS, QT, READ_SHORT> : a.once ? &attn_quad_kernel<D, DS, QT, READ_ONCE> : &attn_quad_kernel<D, DS, QT, READ_PLAIN>;
+    hipLaunchKernelGGL(kernel, grid, dim3(512), G::BYTES, st, ROWS_OF(a));
     return check_launch("attn_quad_kernel");
 }
 
