@@ -768,15 +768,16 @@ struct RowsGeom {
     static constexpr int EARLY = QS == 4 ? (STRIDE - Q_PER * QTILE) / GROUP : NS;  // stages that hold no queries
     static constexpr int Q_OFF = Q_APART ? TILES : QS > 1 ? EARLY * GROUP : GROUP, Q_STRIDE = Q_APART ? QTILE : STRIDE;
     static constexpr int q_at(int i) { return Q_OFF + i / Q_PER * Q_STRIDE + i % Q_PER * QTILE; }
-    // Odd workgroups of a KV head take the tiles of every two steps in the other order: half of what a workgroup reads it then finds in L2, where a CU
-    // pulls twice as fast (138 against 70 GB/s).  That pays while the keys and values which an XCD's heads have in flight stay in L2: 32 heads of 64 in two
+    // Odd workgroups of a KV head take the tiles of every two steps in the other order: half of what a workgroup reads has then come to L2 for another one, and from there a CU
+    // pulls twice as fast (138 against 70 GB/s).  (In lock step it asks for lines that are still on their way; L2 counts those as hits too.)  That pays while the keys and values which an XCD's heads have in flight stay in L2: 32 heads of 64 in two
     // slices, 1660 keys 9.9 -> 9.3 us, 2260 keys 12.4 -> 11.5, up to 560 keys equal.  Elsewhere sharing a miss in lock step is better: two tiles unsliced
     // at 4 sequences 13.3 -> 16.6, pairs at 8 sequences 20.3 -> 21.0; four slices 1 % either way.  The hint undoes it, so these kernels read without
     // (10.0 with both).  With the keys still in the memory-side cache, as between the levels of a draft, the same within 1 % (7.38 / 7.45), the first
     // level 11.2 -> 10.2.
     static constexpr bool SWAPPED = QS == 1 && D == 64 && DS == 2;
     // The same with more steps and workgroups: of every TURN steps behind the first, which all take together (the first scores come as early), the workgroups of a KV head start
-    // with another one each and go round, so that most of what they read is in L2.  For launches where the pull is far longer than the MFMAs and exponentials beside it: one
+    // with another one each and go round, so that most of what they read has come to L2 before they ask for it: a read request of a CU takes 390 clocks instead of 552 (one LLaVA sequence, 60 rows),
+    // 465 instead of 555 (four Gemma3 sequences of 33), while L2 counts as many hits and misses either way (0.83 and 0.79 of the requests hit).  For launches where the pull is far longer than the MFMAs and exponentials beside it: one
     // query tile, or head_dim 256 in slices.  Nothing but the loads, 1 sequence of 8 KV heads, 60 rows of 4 heads, 1340 keys: 11.5 us, with the order 9.1; the launch 11.7 and 10.4.
     // TURN 2, 4, 8, 16 there: 11.2, 11.0, 10.7, 10.7, with the first step turned too 0.1 us more each; which workgroups take it: see order_of_tiles().
     static constexpr bool TURNED = QS == 1 && !SWAPPED && (QT == 1 || D == 256);
@@ -1846,7 +1847,8 @@ int ensure_wave_lds()
 // us a launch, asked for behind the prefix length / ahead of it, steps of 256 keys: 2 sequences of 16 heads of 128, 18 rows, 104 keys 4.17 / 4.44, 170 keys 4.41 / 4.54, 200 keys 4.54 / 4.56, 240 keys 4.58 / 4.49,
 // 3 sequences of 32 heads of 64, 17 rows, 170 keys 4.73 / 4.66, 200 keys 4.95 / 4.69; steps of 128: 4 sequences of 32 heads of 128, 60 rows, 64 keys 6.06 / 6.44, 96 keys 6.64 / 6.78, 104 keys 6.70 / 6.64,
 // 120 keys 7.02 / 6.88; 33 rows 64 keys 5.59 / 5.94, 120 keys 6.37 / 6.53, 190 keys 7.13 / 6.88.
-// (A sequence of fewer keys beside longer ones, or under a max_kv_len far above its length, still pays: 3 of 54 keys, 39 rows of 32 on 8 heads of 128, max_kv_len 1500, 5.01 / 5.23.)
+// (A sequence of fewer keys beside longer ones, or under a max_kv_len far above its length, still pays: 3 of 54 keys, 39 rows of 32 on 8 heads of 128, max_kv_len 1500, 5.01 / 5.23; at worst
+// 4 of 66 keys, 10 rows of 16 heads of 128, 4.55 / 4.95; from 300 keys on the keys asked for early gain.)
 template <class G>
 bool short_range(const Plan &p) { return p.max_kv_len * 4 < G::STEP_KEYS * 3; }
 
@@ -2016,7 +2018,7 @@ bool caches_near(const dream_attn_desc *d, int64_t max_kv_len, bool drafting)
     return (int64_t)d->batch * d->n_kv_heads * max_kv_len * d->head_dim * 4 < (int64_t)(drafting ? 152 : 8) << 20;
 }
 
-// AttnArgs::turn.  The orders that make a CU find most of its keys in L2 pay while what the heads of an XCD have in flight stays there.
+// AttnArgs::turn.  The orders in which most of a CU's keys have come to L2 before it asks for them pay while what the heads of an XCD have in flight stays there.
 //
 // RowsGeom::SWAPPED: always in a verification.  In a draft, whose caches come from the memory-side cache, only while the heads of an XCD fit its 4 MB L2 or nearly: 3 sequences of 32 heads,
 // 10 rows, 1657 keys, 5.1 MB an XCD, us with the order / without: 10.1 / 9.5, 2233 keys 12.1 / 11.1; 4 sequences of 1145 keys, 4.7 MB, 7.4 / 7.7; a whole level of one sequence 9.4 / 9.6.
