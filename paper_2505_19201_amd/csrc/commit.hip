@@ -70,7 +70,8 @@ __device__ __forceinline__ void move_rows(u32x4 *tree, const int32_t *path, int 
 }
 
 // One sequence is a chain of trips to memory: the plain arguments are in scalar registers when a wave starts, then what says which rows move (length, path, prefix, cache) is asked for
-// at once, then the rows.  Everything in one structure and the path behind the length were four trips: greedy acceptance and commit of one Gemma3 sequence 13.6 us, 14.2 so.
+// at once, then the rows.  Everything in one structure and the path behind the length were four trips.  us a call in a graph, four trips / at once: one Gemma3 sequence (96 caches) 2.82 / 2.76,
+// one LLaVA sequence (64) 3.32 / 3.25, 16 SmolVLM sequences (48) 9.15 / 8.98; at once, but with the number of rows in vector registers and the entries under a condition each, 2.85, 3.38 and 9.50.
 __global__ __launch_bounds__(256) void kv_commit_kernel(const int32_t *accept_len, const int32_t *path, const int32_t *prefix_len, int path_stride, int n_tree, int chunks_per_row,
                                                         int heads_per_wg, CommitArgs a)
 {
